@@ -127,7 +127,7 @@ Plan make_plan(const agzo_layer& L, bool need_ybuf, bool ce = false, bool shared
     p.rp = round16(L.r);
     p.m_pad = fused_sketch ? gemm_bf16_sketch_mpad(L.n_tokens) : round32(L.n_tokens);
     p.nsplit = !bf ? 1 : fused_sketch ? gemm_bf16_sketch_splits(L.n_tokens) : xtt_num_splits(L.n_tokens, L.d_in);
-    const int n_gemm = bf ? gemm_bf16_num_workgroups(L.n_tokens, L.d_out, !ce && !shared && L.tiling != AGZO_TILING_LARGE) : epilogue_f32_num_workgroups(L.n_tokens, L.d_out);
+    const int n_gemm = bf ? gemm_bf16_num_workgroups(L.n_tokens, L.d_out, !ce && !shared && L.tiling != AGZO_TILING_LARGE) : forward_f32_num_workgroups(L.n_tokens, L.d_out);
     p.n_part = n_gemm;
     size_t o = align_up(base);
     auto take = [&](size_t bytes) { size_t at = o; o += align_up(bytes); return at; };
@@ -243,7 +243,8 @@ int sketch_range(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* 
     } else {
         float* om = wsf(ctx, p.off_T);
         HIPCHK(launch_fill_normal(om, L.n_tokens, L.r, seed, AGZO_TAG_OMEGA, st));
-        HIPCHK(launch_gemm_f32(static_cast<const float*>(X), 1, L.ldx, om, L.r, 1, S, L.r, L.d_in, L.r, L.n_tokens, st));
+        const F32SkinnyArgs a{static_cast<const float*>(X), L.ldx, L.n_tokens, L.d_in, om, L.r, S};
+        HIPCHK(launch_xtt_f32_many(&a, 1, st));
     }
     return 0;
 }
@@ -263,8 +264,9 @@ int sketch_power(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* 
     } else {
         const float* Xf = static_cast<const float*>(X);
         float* T = wsf(ctx, p.off_T);
-        HIPCHK(launch_gemm_f32(Xf, L.ldx, 1, Q, L.r, 1, T, L.r, L.n_tokens, L.r, L.d_in, st));
-        HIPCHK(launch_gemm_f32(Xf, 1, L.ldx, T, L.r, 1, S, L.r, L.d_in, L.r, L.n_tokens, st));
+        const F32SkinnyArgs q{Xf, L.ldx, L.n_tokens, L.d_in, Q, L.r, T}, t{Xf, L.ldx, L.n_tokens, L.d_in, T, L.r, S};
+        HIPCHK(launch_xq_f32_many(&q, 1, st));
+        HIPCHK(launch_xtt_f32_many(&t, 1, st));
     }
     return 0;
 }
@@ -301,9 +303,24 @@ int op_project(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* X,
         HIPCHK(launch_xq_bf16(static_cast<const bf16_t*>(X), L.ldx, L.n_tokens, L.d_in, wsh(ctx, p.off_pack), L.r, p.rp,
                               P, nullptr, p.m_pad, wsf(ctx, p.off_xqpart), st));
     } else {
-        HIPCHK(launch_gemm_f32(static_cast<const float*>(X), L.ldx, 1, B, L.r, 1, P, L.r, L.n_tokens, L.r, L.d_in, st));
+        const F32SkinnyArgs a{static_cast<const float*>(X), L.ldx, L.n_tokens, L.d_in, B, L.r, P};
+        HIPCHK(launch_xq_f32_many(&a, 1, st));
     }
     return 0;
+}
+
+F32FwdArgs forward_f32_args(const agzo_layer& L, const void* W, const void* X, const float* P, float eps_signed, uint64_t seed,
+                            const GemmLossArgs& loss, bool shared) {
+    F32FwdArgs a;
+    a.X = static_cast<const float*>(X); a.ldx = L.ldx;
+    a.W = static_cast<const float*>(W); a.ldw = L.ldw;
+    a.M = L.n_tokens; a.N = L.d_out; a.K = L.d_in;
+    a.Y = nullptr; a.ldy = 0;
+    a.P = P; a.r = L.r; a.eps_signed = eps_signed; a.s_lo = (uint32_t)seed; a.s_hi = (uint32_t)(seed >> 32);
+    a.target = (loss.kind == AGZO_LOSS_MSE) ? loss.target : nullptr;
+    a.target_dtype = loss.target_dtype; a.ldt = loss.ldt; a.partials = loss.partials;
+    a.shared = shared ? 1 : 0;
+    return a;
 }
 
 // Y = X W^T (+ eps (P) G^T), loss
@@ -358,24 +375,21 @@ int op_forward(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* W,
             HIPCHK(launch_ce_combine(la.ce_ms, la.ce_tl, ids, L.n_tokens, L.d_out, gemm_bf16_ce_chunks(L.d_out), shared ? 3 : 1,
                                      la.partials, loss_dev, st));
     } else {
-        float* Yf = Y ? static_cast<float*>(Y) : wsf(ctx, p.off_Ybuf);
-        const int64_t ldy = Y ? L.ldy : L.d_out;
-        HIPCHK(launch_gemm_f32(static_cast<const float*>(X), L.ldx, 1, static_cast<const float*>(W), 1, L.ldw, Yf, ldy,
-                               L.n_tokens, L.d_out, L.d_in, st));
-        if (shared) {
-            // Y0 -> f0; Y0 + eps D -> f+; then - 2 eps D -> f-   (all in the stored fp32 Y buffer)
-            GemmLossArgs l1 = la, l2 = la;
-            l1.partials = la.partials + p.n_part;
-            l2.partials = la.partials + 2 * p.n_part;
-            HIPCHK(launch_epilogue_f32(Yf, ldy, L.n_tokens, L.d_out, nullptr, L.r, 0.f, seed, la, st));
-            if (ce) HIPCHK(launch_ce_rows_f32(Yf, ldy, L.n_tokens, L.d_out, ids, la.partials, loss_dev + 0, st));
-            HIPCHK(launch_epilogue_f32(Yf, ldy, L.n_tokens, L.d_out, P, L.r, eps_signed, seed, l1, st));
-            if (ce) HIPCHK(launch_ce_rows_f32(Yf, ldy, L.n_tokens, L.d_out, ids, la.partials, loss_dev + 1, st));
-            HIPCHK(launch_epilogue_f32(Yf, ldy, L.n_tokens, L.d_out, P, L.r, -2.f * eps_signed, seed, l2, st));
-            if (ce) HIPCHK(launch_ce_rows_f32(Yf, ldy, L.n_tokens, L.d_out, ids, la.partials, loss_dev + 2, st));
+        F32FwdArgs a = forward_f32_args(L, W, X, P, eps_signed, seed, la, shared);
+        if (!ce) {
+            a.Y = static_cast<float*>(Y); a.ldy = L.ldy;
+            HIPCHK(launch_forward_f32_many(&a, 1, st));
         } else {
-            HIPCHK(launch_epilogue_f32(Yf, ldy, L.n_tokens, L.d_out, P, L.r, eps_signed, seed, la, st));
-            if (ce) HIPCHK(launch_ce_rows_f32(Yf, ldy, L.n_tokens, L.d_out, ids, la.partials, loss_dev, st));
+            // the logits go through memory: Y, or the workspace
+            a.Y = Y ? static_cast<float*>(Y) : wsf(ctx, p.off_Ybuf);
+            a.ldy = Y ? L.ldy : L.d_out;
+            if (shared) { a.P = nullptr; a.shared = 0; }
+            HIPCHK(launch_forward_f32_many(&a, 1, st));
+            HIPCHK(launch_ce_rows_f32(a.Y, a.ldy, L.n_tokens, L.d_out, ids, la.partials, loss_dev, st));
+            for (int ph = 1; shared && ph < 3; ++ph) {      // Y0 + eps D, then - 2 eps D
+                HIPCHK(launch_rank_term_f32(a.Y, a.ldy, L.n_tokens, L.d_out, P, L.r, ph == 1 ? eps_signed : -2.f * eps_signed, seed, st));
+                HIPCHK(launch_ce_rows_f32(a.Y, a.ldy, L.n_tokens, L.d_out, ids, la.partials, loss_dev + ph, st));
+            }
         }
     }
     if (has_loss && !ce && !defer_finish)
@@ -447,8 +461,26 @@ struct LayerJob {
     float* B;          // where the basis goes
 };
 
-// one stage for the bf16 jobs idx[0..n): Omega^T planes + range sketch, or T = X Q planes + power sketch
+// the same for fp32 storage: S (or T and S) of every job in the workspace
+int stage_sketch_many_f32(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, const int* idx, int n, bool range) {
+    FillNormalArgs f[kBatchMax];
+    F32SkinnyArgs q[kBatchMax], t[kBatchMax];
+    for (int i = 0; i < n; ++i) {
+        const LayerJob& j = jobs[idx[i]];
+        const float* X = static_cast<const float*>(j.X);
+        f[i] = FillNormalArgs{wsf(ctx, j.p.off_T), j.L.n_tokens, j.L.r, j.seed};
+        q[i] = F32SkinnyArgs{X, j.L.ldx, j.L.n_tokens, j.L.d_in, wsf(ctx, j.p.off_Q), j.L.r, wsf(ctx, j.p.off_T)};
+        t[i] = F32SkinnyArgs{X, j.L.ldx, j.L.n_tokens, j.L.d_in, wsf(ctx, j.p.off_T), j.L.r, wsf(ctx, j.p.off_S)};
+    }
+    if (range) HIPCHK(launch_fill_normal_many(f, n, AGZO_TAG_OMEGA, ctx->stream));
+    else HIPCHK(launch_xq_f32_many(q, n, ctx->stream));
+    HIPCHK(launch_xtt_f32_many(t, n, ctx->stream));
+    return 0;
+}
+
+// one stage for the jobs idx[0..n) (one dtype): Omega^T planes + range sketch, or T = X Q planes + power sketch
 int stage_sketch_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, const int* idx, int n, bool range) {
+    if (n > 0 && jobs[idx[0]].L.dtype != AGZO_BF16) return stage_sketch_many_f32(ctx, jobs, idx, n, range);
     hipStream_t st = ctx->stream;
     if (range) {
         FillPackTArgs f[kBatchMax];
@@ -479,22 +511,18 @@ int stage_sketch_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, const in
     return 0;
 }
 
-// Alg. 1 for every job.  bf16 jobs that share a padded rank go through the batched kernels, at most kBatchMax per
-// launch; the others one by one.  On return every bf16 job's workspace planes hold its basis.
+// Alg. 1 for every job.  Jobs that share a dtype and a padded rank go through the batched kernels, at most kBatchMax per
+// launch.  On return every bf16 job's workspace planes hold its basis.
 int basis_many_impl(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, int K, int flags) {
     std::vector<char> done(jobs.size(), 0);
     for (size_t a = 0; a < jobs.size(); ++a) {
         if (done[a]) continue;
         const LayerJob& ja = jobs[a];
-        if (ja.L.dtype != AGZO_BF16) {
-            TRY(op_basis(ctx, ja.L, ja.p, ja.X, K, ja.seed, ja.S0, flags, ja.B));
-            done[a] = 1;
-            continue;
-        }
+        const bool bf = ja.L.dtype == AGZO_BF16;
         int idx[kBatchMax], n = 0;
         // (single columns are normalised rather than factored: launches of their own)
         for (size_t b = a; b < jobs.size() && n < kBatchMax; ++b)
-            if (!done[b] && jobs[b].L.dtype == AGZO_BF16 && jobs[b].p.rp == ja.p.rp && (jobs[b].L.r == 1) == (ja.L.r == 1)) {
+            if (!done[b] && jobs[b].L.dtype == ja.L.dtype && jobs[b].p.rp == ja.p.rp && (jobs[b].L.r == 1) == (ja.L.r == 1)) {
                 idx[n++] = (int)b;
                 done[b] = 1;
             }
@@ -506,7 +534,7 @@ int basis_many_impl(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, int K, int
             given[i] = false;
             if (flags & AGZO_INIT_FEATURE) {
                 HIPCHK(launch_fill_normal(wsf(ctx, j.p.off_Q), j.L.d_in, j.L.r, j.seed, AGZO_TAG_Q0, ctx->stream));
-                HIPCHK(launch_pack_planes(wsf(ctx, j.p.off_Q), j.L.d_in, j.L.r, j.p.rp, wsh(ctx, j.p.off_pack), ctx->stream));
+                if (bf) HIPCHK(launch_pack_planes(wsf(ctx, j.p.off_Q), j.L.d_in, j.L.r, j.p.rp, wsh(ctx, j.p.off_pack), ctx->stream));
                 need_idx[n_need++] = idx[i];
             } else if (j.S0) {
                 given[i] = true;
@@ -520,8 +548,9 @@ int basis_many_impl(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, int K, int
             for (int i = 0; i < n; ++i) {
                 const LayerJob& j = jobs[idx[i]];
                 float* out = (k == K) ? j.B : wsf(ctx, j.p.off_Q);
-                if (k == 0 && given[i])
-                    q[i] = QrArgs{j.S0, nullptr, 0, j.p.rp, nullptr, j.L.d_in, j.L.r, out, wsh(ctx, j.p.off_pack), ctx->ws + j.p.off_qr};
+                if ((k == 0 && given[i]) || !bf)
+                    q[i] = QrArgs{(k == 0 && given[i]) ? j.S0 : wsf(ctx, j.p.off_S), nullptr, 0, j.p.rp, nullptr, j.L.d_in, j.L.r, out,
+                                  bf ? wsh(ctx, j.p.off_pack) : nullptr, ctx->ws + j.p.off_qr};
                 else
                     q[i] = QrArgs{nullptr, wsf(ctx, j.p.off_xtt), j.p.nsplit, j.p.rp, wsf(ctx, j.p.off_S), j.L.d_in, j.L.r, out,
                                   wsh(ctx, j.p.off_pack), ctx->ws + j.p.off_qr};
@@ -536,15 +565,22 @@ int basis_many_impl(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, int K, int
     return 0;
 }
 
-// P = X B for every bf16 job whose planes hold its basis (one launch per kBatchMax jobs of a padded rank)
+// P = X B for every job (one launch per kBatchMax jobs of a dtype and padded rank); bf16: the planes hold its basis
 int project_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs) {
     std::vector<char> done(jobs.size(), 0);
     for (size_t a = 0; a < jobs.size(); ++a) {
         if (done[a]) continue;
         const LayerJob& ja = jobs[a];
         if (ja.L.dtype != AGZO_BF16) {
-            TRY(op_project(ctx, ja.L, ja.p, ja.X, ja.B, wsf(ctx, ja.p.off_T), true));
-            done[a] = 1;
+            F32SkinnyArgs s[kBatchMax];
+            int n = 0;
+            for (size_t b = a; b < jobs.size() && n < kBatchMax; ++b) {
+                const LayerJob& j = jobs[b];
+                if (done[b] || j.L.dtype == AGZO_BF16 || j.p.rp != ja.p.rp) continue;
+                s[n++] = F32SkinnyArgs{static_cast<const float*>(j.X), j.L.ldx, j.L.n_tokens, j.L.d_in, j.B, j.L.r, wsf(ctx, j.p.off_T)};
+                done[b] = 1;
+            }
+            HIPCHK(launch_xq_f32_many(s, n, ctx->stream));
             continue;
         }
         XqArgs q[kBatchMax];
@@ -960,13 +996,42 @@ int agzo_step_many(agzo_ctx* ctx, const agzo_step_item* items, int32_t n, int32_
         const LayerJob& j = jobs[(size_t)m];
         return op_forward(ctx, j.L, j.p, it.W, it.X, P, e, it.seed, nullptr, &it.loss, dst, sh, slot, it.loss.kind == AGZO_LOSS_MSE);
     };
+    // squared-error layers in fp32 storage: the evaluations of part `perturbed` (0: f0, 1: f+ and f-, or all three in the
+    // shared schedule) of up to kBatchMax / 2 layers per launch; the loss partials of phase ph go to slot ph
+    auto batched_f32 = [&](int m) { return items[m].layer.dtype == AGZO_F32 && items[m].loss.kind == AGZO_LOSS_MSE; };
+    auto forward_f32_batched = [&](bool perturbed) -> int {
+        F32FwdArgs a[kBatchMax];
+        int na = 0;
+        for (int m = 0; m < n; ++m) {
+            if (!batched_f32(m)) continue;
+            const agzo_step_item& it = items[m];
+            const LayerJob& j = jobs[(size_t)m];
+            double* part = reinterpret_cast<double*>(ctx->ws + j.p.off_part);
+            if (3 * (size_t)j.p.n_part > j.p.part_count) return fail(ctx, AGZO_EHIP, "internal: loss scratch");
+            GemmLossArgs la;
+            la.kind = AGZO_LOSS_MSE; la.target_dtype = it.loss.target_dtype; la.target = it.loss.target; la.ldt = it.loss.ldt;
+            const float* P = perturbed ? wsf(ctx, j.p.off_T) : nullptr;
+            for (int ph = perturbed && !shared ? 1 : 0; ph < (perturbed && !shared ? (one_sided ? 2 : 3) : 1); ++ph) {
+                la.partials = part + (size_t)ph * j.p.n_part;
+                a[na++] = forward_f32_args(j.L, it.W, it.X, P, ph == 2 ? -eps : eps, it.seed, la, perturbed && shared);
+            }
+            if (na + 2 > kBatchMax) { HIPCHK(launch_forward_f32_many(a, na, st)); na = 0; }
+        }
+        HIPCHK(launch_forward_f32_many(a, na, st));
+        return 0;
+    };
     // Alg. 2, part 1: the base forward of every layer, and every layer's basis from the same activations
-    if (!shared)
-        for (int m = 0; m < n; ++m) TRY(forward(m, nullptr, 0.f, items[m].out_dev, false, 0));
+    if (!shared) {
+        TRY(forward_f32_batched(false));
+        for (int m = 0; m < n; ++m)
+            if (!batched_f32(m)) TRY(forward(m, nullptr, 0.f, items[m].out_dev, false, 0));
+    }
     TRY(basis_many_impl(ctx, jobs, K, flags & AGZO_INIT_FEATURE));
     // parts 2-3: the perturbed evaluations
     TRY(project_many(ctx, jobs));
+    TRY(forward_f32_batched(true));
     for (int m = 0; m < n; ++m) {
+        if (batched_f32(m)) continue;
         const float* P = wsf(ctx, jobs[(size_t)m].p.off_T);
         if (shared) {
             TRY(forward(m, P, eps, items[m].out_dev, true, 0));

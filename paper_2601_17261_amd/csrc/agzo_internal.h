@@ -124,6 +124,9 @@ struct GemmLossArgs {
 // philox.hip
 hipError_t launch_philox_words(uint32_t* dst, int64_t rows, int cols, uint64_t seed, uint32_t tag, hipStream_t st);
 hipError_t launch_fill_normal(float* dst, int64_t rows, int cols, uint64_t seed, uint32_t tag, hipStream_t st);
+// several matrices of one tag in one launch
+struct FillNormalArgs { float* dst; int64_t rows; int cols; uint64_t seed; };
+hipError_t launch_fill_normal_many(const FillNormalArgs* a, int n, uint32_t tag, hipStream_t st);
 // bf16 [3][rp][n_pad] hi/mid/lo planes of Omega^T (rows of Omega are tokens)
 hipError_t launch_fill_normal_packT(bf16_t* dst, int64_t n, int64_t n_pad, int r, int rp, uint64_t seed,
                                     uint32_t tag, hipStream_t st);
@@ -169,13 +172,27 @@ inline int64_t gemm_bf16_sketch_mpad(int64_t M) { return (M + 127) / 128 * 128; 
 inline int gemm_bf16_sketch_splits(int64_t M) { return (int)((M + 127) / 128); }
 hipError_t launch_gemm_bf16(const GemmBf16Args& a, hipStream_t st);
 
-// gemm_f32.hip : generic strided fp32 GEMM with fp64 accumulation, and the fp32 epilogue
-hipError_t launch_gemm_f32(const float* A, int64_t sam, int64_t sak, const float* B, int64_t sbk, int64_t sbn,
-                           float* C, int64_t ldc, int64_t M, int64_t N, int64_t K, hipStream_t st);
-int epilogue_f32_num_workgroups(int64_t M, int64_t N);
-// Y[t][j] += eps_signed * sum_k P[t][k] G[j][k] (if P), then loss partials (if loss.kind)
-hipError_t launch_epilogue_f32(float* Y, int64_t ldy, int64_t M, int64_t N, const float* P, int r,
-                               float eps_signed, uint64_t seed, const GemmLossArgs& loss, hipStream_t st);
+// gemm_f32.hip : fp32 storage, fp64 accumulation on the matrix cores.  Up to kBatchMax problems per launch
+struct F32FwdArgs {
+    const float* X; int64_t ldx;
+    const float* W; int64_t ldw;
+    int64_t M, N, K;            // tokens, d_out, d_in
+    float* Y; int64_t ldy;      // nullable: stored outputs
+    const float* P; int r;      // projection X B [M][r] (NULL: no rank-r term)
+    float eps_signed; uint32_t s_lo, s_hi;
+    const void* target; int target_dtype; int64_t ldt;   // squared error (NULL: none)
+    double* partials;           // [forward_f32_num_workgroups()], shared: three times that
+    int shared;                 // f0, f+ and f- (eps = eps_signed) from one pass; needs P and target, no Y
+};
+int forward_f32_num_workgroups(int64_t M, int64_t N);
+hipError_t launch_forward_f32_many(const F32FwdArgs* a, int n, hipStream_t st);
+// Y[t][j] += eps_signed * sum_k P[t][k] G[j][k]
+hipError_t launch_rank_term_f32(float* Y, int64_t ldy, int64_t M, int64_t N, const float* P, int r, float eps_signed, uint64_t seed,
+                                hipStream_t st);
+// X [M][K]; xq: out [M][r] = X V, V [K][r]; xtt: out [K][r] = X^T V, V [M][r].  One padded rank (r rounded up to 16) per launch
+struct F32SkinnyArgs { const float* X; int64_t ldx, M, K; const float* V; int r; float* out; };
+hipError_t launch_xq_f32_many(const F32SkinnyArgs* a, int n, hipStream_t st);
+hipError_t launch_xtt_f32_many(const F32SkinnyArgs* a, int n, hipStream_t st);
 
 // skinny.hip : bf16 tall-skinny products
 // T = X Qp, Qp given as bf16 planes [3][rp][d_in]; writes T fp32 [M][r] (nullable) and

@@ -1,161 +1,454 @@
-// fp32-storage path: a generic strided GEMM whose products are accumulated in fp64 on the vector
-// ALUs (CDNA4 issues fp64 FMA at the plain-fp32 rate), and the epilogue that adds the rank-r
-// perturbation term eps * (X B) G^T (Eq. 7, factored) and reduces the loss.  Used for every
-// product of the fp32 configuration: Y = X W^T, T = X Q, S = X^T T, S = X^T Omega.
+// fp32-storage path: every product accumulates in fp64 on the matrix cores (v_mfma_f64_16x16x4_f64) and is rounded once.
+//   forward : Y = X W^T (+ eps (X B) G^T, Eq. 7 factored), optional Y store, squared-error loss from the fp64 accumulators
+//   xq      : T = X Q      (tokens x r)
+//   xtt     : S = X^T T    (d_in x r), T = Omega or X Q
+// All three take several problems per launch (the layers of a set; both signs of a perturbed evaluation).
+//
+// Operand layout of the instruction: lane l supplies element (l % 16, k = l / 16) of A (rows) and of B (columns), and
+// register i of the result is row 4 i + l / 16, column l % 16.  A product does not care about the order of its k, so a
+// lane fetches four consecutive k of its row at once (16 bytes) and feeds them to four instructions: instruction s takes
+// k = 4 (l / 16) + s of a 16-wide chunk from both operands.
 #include "agzo_internal.h"
 
 namespace agzo {
 
-constexpr int TS = 64;   // C tile is TS x TS
-constexpr int TK = 16;
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+template <int V> struct IC { static constexpr int value = V; };
 
-// C[m][n] = sum_k A[m*sam + k*sak] * B[k*sbk + n*sbn]
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int64_t sam, int64_t sak,
-                                                       const float* __restrict__ B, int64_t sbk, int64_t sbn,
-                                                       float* __restrict__ C, int64_t ldc, int64_t M, int64_t N,
-                                                       int64_t K) {
-    __shared__ float As[TK][TS + 4];
-    __shared__ float Bs[TK][TS + 4];
-    const int tid = threadIdx.x;
-    const int64_t m0 = (int64_t)blockIdx.y * TS, n0 = (int64_t)blockIdx.x * TS;
-    const int tx = tid % 16, ty = tid / 16;
-    double acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
+// ---------------------------------------------------------------------------
+// Forward.  64 x 64 tile per workgroup, four waves of 32 x 32, d_in in slices of 32 double buffered in LDS (32 KiB per
+// workgroup, up to four workgroups per compute unit), the next slice in flight in registers.
+// Bound by the fp64 rate (78.6 TFLOP/s, the same on the matrix cores and the vector units): one instruction takes 64 cycles
+// for two operand registers, so that a slice is 2048 cycles of matrix work per wave against eight LDS reads and 32
+// conversions.  The vector-unit version it replaces (a 4 x 4 register tile per thread) converted eight values from LDS for
+// every 16 multiplications, loaded without a prefetch, and ran at 7 TFLOP/s.  The small tile is for few tokens: 1000 x 1024
+// outputs give one wave to each of the 1024 SIMDs.
+// ---------------------------------------------------------------------------
+constexpr int FT = 64;      // tile edge
+constexpr int FK = 32;      // slice of d_in: a tile row is 128 bytes in LDS
 
-    // loader mapping: choose the index that is contiguous in memory to run fastest over threads
-    const bool a_k_fast = (sak == 1);
-    const bool b_k_fast = (sbk == 1);
-    for (int64_t k0 = 0; k0 < K; k0 += TK) {
+struct F32FwdDev {
+    F32FwdArgs a;
+    int tiles_m, tiles_n;
+};
+
+// byte offset of 16-byte chunk c of tile row `row` (the XOR spreads the rows of one read over the banks)
+__device__ __forceinline__ int f32_lds_off(int row, int c) { return row * 128 + ((c ^ ((row >> 1) & 7)) << 4); }
+
+// (at least two waves per SIMD: the accumulators then stay in ordinary registers; with the whole file to itself the compiler moves
+// all of them to the accumulation half and back around every slice)
+template <bool VEC>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void forward_f32_kernel(const KBatch<F32FwdDev> tb) {
+    __shared__ __align__(16) char smem[2 * 2 * FT * FK * 4];
+    __shared__ double red[4];
+    uint32_t bx, by;
+    const F32FwdDev& d = tb.a[kbatch_find(tb, bx, by)];
+    const F32FwdArgs& a = d.a;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lc = lane & 15, lg = lane >> 4;
+    const int wt = wave & 1, wo = wave >> 1;               // the wave's half of the tokens and of the outputs
+    // each XCD (workgroup id mod 8) takes a contiguous run of tiles, in bands of eight token tiles per output tile
+    const int count = d.tiles_m * d.tiles_n, per = count / 8;
+    int lin = (int)bx;
+    if (lin < per * 8) lin = (lin % 8) * per + lin / 8;
+    constexpr int BAND = 8;
+    const int band = lin / (BAND * d.tiles_n), first = band * BAND;
+    const int rows = min(BAND, d.tiles_m - first), in_band = lin - band * BAND * d.tiles_n;
+    const int tm = first + in_band % rows, tn = in_band / rows;
+    const int64_t m0 = (int64_t)tm * FT, n0 = (int64_t)tn * FT;
+    char* const Xs = smem;                                 // [2 buffers][FT][FK]
+    char* const Ws = smem + 2 * FT * FK * 4;
+
+    doublex4 acc[2][2];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            int e = tid + q * 256;  // 0..1023
-            int mm, kk;
-            if (a_k_fast) { kk = e % TK; mm = e / TK; } else { mm = e % TS; kk = e / TS; }
-            int64_t gm = m0 + mm, gk = k0 + kk;
-            As[kk][mm] = (gm < M && gk < K) ? A[gm * sam + gk * sak] : 0.f;
-            int nn;
-            if (b_k_fast) { kk = e % TK; nn = e / TK; } else { nn = e % TS; kk = e / TS; }
-            int64_t gn = n0 + nn;
-            gk = k0 + kk;
-            Bs[kk][nn] = (gn < N && gk < K) ? B[gk * sbk + gn * sbn] : 0.f;
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
+
+    // staging: two 16-byte chunks per thread and operand.  Rows past the end repeat the last one (they only feed outputs that
+    // the epilogue masks), columns past d_in are zero
+    const int ch = tid & 7, r0 = tid >> 3;                 // rows r0 and r0 + 32
+    const float *xr[2], *wr[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        xr[i] = a.X + min(m0 + r0 + 32 * i, a.M - 1) * a.ldx;
+        wr[i] = a.W + min(n0 + r0 + 32 * i, a.N - 1) * a.ldw;
+    }
+    float4 rx[2], rw[2];
+    // MASK: the slice may reach past d_in
+    auto load4 = [&](const float* p, int64_t k, auto MASK) __attribute__((always_inline)) -> float4 {
+        constexpr bool mask = decltype(MASK)::value != 0;
+        if constexpr (VEC) {
+            if constexpr (!mask) return *reinterpret_cast<const float4*>(p + k);
+            return (k < a.K) ? *reinterpret_cast<const float4*>(p + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+        } else {
+            float v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = (!mask || k + e < a.K) ? p[k + e] : 0.f;
+            return make_float4(v[0], v[1], v[2], v[3]);
         }
-        __syncthreads();
+    };
+    auto gload = [&](int64_t k0, auto MASK) __attribute__((always_inline)) {
 #pragma unroll
-        for (int kk = 0; kk < TK; ++kk) {
-            double a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = (double)As[kk][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = (double)Bs[kk][tx * 4 + j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fma(a[i], b[j], acc[i][j]);
+        for (int i = 0; i < 2; ++i) {
+            rx[i] = load4(xr[i], k0 + ch * 4, MASK);
+            rw[i] = load4(wr[i], k0 + ch * 4, MASK);
         }
+    };
+    auto sstore = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int off = buf * FT * FK * 4 + f32_lds_off(r0 + 32 * i, ch);
+            *reinterpret_cast<float4*>(Xs + off) = rx[i];
+            *reinterpret_cast<float4*>(Ws + off) = rw[i];
+        }
+    };
+    // scale: factor on the W side in fp64 (1 for the d_in slices)
+    auto multiply = [&](int buf, double scale) {
+#pragma unroll
+        for (int c = 0; c < FK / 16; ++c) {
+            float av[2][4], bv[2][4];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const float4 x = *reinterpret_cast<const float4*>(Xs + buf * FT * FK * 4 + f32_lds_off(wt * 32 + i * 16 + lc, 4 * c + lg));
+                const float4 w = *reinterpret_cast<const float4*>(Ws + buf * FT * FK * 4 + f32_lds_off(wo * 32 + i * 16 + lc, 4 * c + lg));
+                av[i][0] = x.x; av[i][1] = x.y; av[i][2] = x.z; av[i][3] = x.w;
+                bv[i][0] = w.x; bv[i][1] = w.y; bv[i][2] = w.z; bv[i][3] = w.w;
+            }
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                double ad[2], bd[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) { ad[i] = (double)av[i][s]; bd[i] = (double)bv[i][s] * scale; }
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ad[i], bd[j], acc[i][j], 0, 0, 0);
+            }
+        }
+    };
+    const int nfull = (int)(a.K / FK), nk = (int)((a.K + FK - 1) / FK);
+    gload(0, IC<1>{});
+    sstore(0);
+    __syncthreads();
+    int kt = 0;
+    for (; kt + 1 < nfull; ++kt) {
+        gload((int64_t)(kt + 1) * FK, IC<0>{});
+        multiply(kt & 1, 1.0);
+        sstore((kt + 1) & 1);
         __syncthreads();
     }
+    for (; kt < nk; ++kt) {                                // the last one or two slices
+        if (kt + 1 < nk) gload((int64_t)(kt + 1) * FK, IC<1>{});
+        multiply(kt & 1, 1.0);
+        if (kt + 1 < nk) sstore((kt + 1) & 1);
+        __syncthreads();
+    }
+    // the rank-r term as more slices: P rows against G rows regenerated from the seed, eps applied in fp64
+    auto rank_term = [&](double coef) {
+        for (int k0 = 0; k0 < a.r; k0 += FK) {
+            const int row_t = tid >> 2;                    // 64 rows, four threads each
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        int64_t gm = m0 + ty * 4 + i;
-        if (gm >= M) continue;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            int64_t gn = n0 + tx * 4 + j;
-            if (gn < N) C[gm * ldc + gn] = (float)acc[i][j];
+            for (int i = 0; i < 2; ++i) {
+                const int c = (tid & 3) * 2 + i, k = k0 + 4 * c;
+                float4 pv = make_float4(0.f, 0.f, 0.f, 0.f), gv = pv;
+                if (k < a.r) {
+                    const float* p = a.P + min(m0 + row_t, a.M - 1) * a.r + k;
+                    pv.x = p[0];
+                    if (k + 1 < a.r) pv.y = p[1];
+                    if (k + 2 < a.r) pv.z = p[2];
+                    if (k + 3 < a.r) pv.w = p[3];
+                    gv = philox_normal4(a.s_lo, a.s_hi, AGZO_TAG_G, (uint32_t)min(n0 + row_t, a.N - 1), (uint32_t)(k >> 2));
+                    if (k + 1 >= a.r) gv.y = 0.f;
+                    if (k + 2 >= a.r) gv.z = 0.f;
+                    if (k + 3 >= a.r) gv.w = 0.f;
+                }
+                *reinterpret_cast<float4*>(Xs + f32_lds_off(row_t, c)) = pv;
+                *reinterpret_cast<float4*>(Ws + f32_lds_off(row_t, c)) = gv;
+            }
+            __syncthreads();
+            multiply(0, coef);
+            __syncthreads();
         }
+    };
+    auto evaluate = [&](int phase) {
+        double part = 0.0;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int64_t col = n0 + wo * 32 + j * 16 + lc;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int64_t row = m0 + wt * 32 + i * 16 + 4 * e + lg;
+                    if (row >= a.M || col >= a.N) continue;
+                    const double y = acc[i][j][e];
+                    if (a.Y != nullptr) a.Y[row * a.ldy + col] = (float)y;
+                    if (a.target != nullptr) {
+                        const float t = (a.target_dtype == AGZO_BF16) ? bf16_to_f32(reinterpret_cast<const bf16_t*>(a.target)[row * a.ldt + col])
+                                                                      : reinterpret_cast<const float*>(a.target)[row * a.ldt + col];
+                        const double r = y - (double)t;
+                        part = fma(r, r, part);
+                    }
+                }
+            }
+        if (a.target == nullptr) return;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
+        if (lane == 0) red[wave] = part;
+        __syncthreads();
+        if (tid == 0) a.partials[(int64_t)phase * count + tm * d.tiles_n + tn] = (red[0] + red[1]) + (red[2] + red[3]);
+        __syncthreads();
+    };
+    if (a.shared) {
+        // one pass over X and W for f0, f+ and f-
+        evaluate(0);
+        rank_term((double)a.eps_signed);
+        evaluate(1);
+        rank_term(-2.0 * (double)a.eps_signed);
+        evaluate(2);
+    } else {
+        if (a.P != nullptr) rank_term((double)a.eps_signed);
+        evaluate(0);
     }
 }
 
-hipError_t launch_gemm_f32(const float* A, int64_t sam, int64_t sak, const float* B, int64_t sbk, int64_t sbn,
-                           float* C, int64_t ldc, int64_t M, int64_t N, int64_t K, hipStream_t st) {
-    if (M == 0 || N == 0) return hipSuccess;
-    dim3 grid((unsigned)((N + TS - 1) / TS), (unsigned)((M + TS - 1) / TS));
-    hipLaunchKernelGGL(gemm_f32_kernel, grid, dim3(256), 0, st, A, sam, sak, B, sbk, sbn, C, ldc, M, N, K);
+int forward_f32_num_workgroups(int64_t M, int64_t N) { return (int)(((M + FT - 1) / FT) * ((N + FT - 1) / FT)); }
+
+hipError_t launch_forward_f32_many(const F32FwdArgs* a, int n, hipStream_t st) {
+    if (n < 0 || n > kBatchMax) return hipErrorInvalidValue;
+    KBatch<F32FwdDev> tb;
+    tb.n = 0;
+    uint64_t blocks = 0;
+    int order[kBatchMax], m = 0;
+    bool vec = true;            // every row starts on 16 bytes
+    for (int i = 0; i < n; ++i) {
+        if (a[i].M == 0 || a[i].N == 0) continue;
+        if (a[i].K < 1 || (a[i].shared && (!a[i].P || a[i].Y || !a[i].target))) return hipErrorInvalidValue;
+        // deepest first, so that the launch does not end on a few long tiles
+        int at = m++;
+        for (; at > 0 && a[order[at - 1]].K < a[i].K; --at) order[at] = order[at - 1];
+        order[at] = i;
+    }
+    for (int i = 0; i < m; ++i) {
+        F32FwdDev d;
+        d.a = a[order[i]];
+        d.tiles_m = (int)((d.a.M + FT - 1) / FT);
+        d.tiles_n = (int)((d.a.N + FT - 1) / FT);
+        vec = vec && d.a.K % 4 == 0 && d.a.ldx % 4 == 0 && d.a.ldw % 4 == 0 && ((reinterpret_cast<uintptr_t>(d.a.X) | reinterpret_cast<uintptr_t>(d.a.W)) & 15) == 0;
+        tb.first[tb.n] = (uint32_t)blocks;
+        tb.gx[tb.n] = (uint32_t)((int64_t)d.tiles_m * d.tiles_n);
+        blocks += tb.gx[tb.n];
+        tb.a[tb.n++] = d;
+    }
+    if (tb.n == 0) return hipSuccess;
+    if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    if (vec) hipLaunchKernelGGL(forward_f32_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, st, tb);
+    else hipLaunchKernelGGL(forward_f32_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, st, tb);
     return hipGetLastError();
 }
 
-// ---------------------------------------------------------------------------
-// epilogue: tile of EP_T tokens x EP_J outputs per workgroup
-// ---------------------------------------------------------------------------
+// Y[t][j] += eps_signed sum_k P[t][k] G[j][k] on stored outputs: the shared-forward schedule with a cross-entropy loss, which
+// needs every evaluation's logits in memory.  32 tokens x 64 outputs per workgroup, fp64.
 constexpr int EP_T = 32;
 constexpr int EP_J = 64;
 
-int epilogue_f32_num_workgroups(int64_t M, int64_t N) {
-    return (int)(((M + EP_T - 1) / EP_T) * ((N + EP_J - 1) / EP_J));
-}
-
-__global__ __launch_bounds__(256) void epilogue_f32_kernel(float* __restrict__ Y, int64_t ldy, int64_t M, int64_t N,
-                                                           const float* __restrict__ P, int r, float eps_signed,
-                                                           uint32_t s_lo, uint32_t s_hi, int loss_kind,
-                                                           int target_dtype, const void* __restrict__ target,
-                                                           int64_t ldt, double* __restrict__ partials) {
+__global__ __launch_bounds__(256) void rank_term_f32_kernel(float* __restrict__ Y, int64_t ldy, int64_t M, int64_t N,
+                                                            const float* __restrict__ P, int r, float eps_signed, uint32_t s_lo,
+                                                            uint32_t s_hi) {
     __shared__ float Gs[EP_J][kMaxRank + 1];
     __shared__ float Ps[EP_T][kMaxRank + 1];
-    __shared__ double red[256];
     const int tid = threadIdx.x;
     const int64_t t0 = (int64_t)blockIdx.y * EP_T, j0 = (int64_t)blockIdx.x * EP_J;
-    if (P != nullptr) {
-        const int nquad = (r + 3) / 4;
-        for (int e = tid; e < EP_J * nquad; e += 256) {
-            int jj = e / nquad, q = e % nquad;
-            int64_t j = j0 + jj;
-            float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (j < N) z = philox_normal4(s_lo, s_hi, AGZO_TAG_G, (uint32_t)j, (uint32_t)q);
-            float v[4] = {z.x, z.y, z.z, z.w};
+    const int nquad = (r + 3) / 4;
+    for (int e = tid; e < EP_J * nquad; e += 256) {
+        const int jj = e / nquad, q = e % nquad;
+        float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (j0 + jj < N) z = philox_normal4(s_lo, s_hi, AGZO_TAG_G, (uint32_t)(j0 + jj), (uint32_t)q);
+        const float v[4] = {z.x, z.y, z.z, z.w};
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (q * 4 + i < r) Gs[jj][q * 4 + i] = v[i];
-        }
-        for (int e = tid; e < EP_T * r; e += 256) {
-            int tt = e / r, k = e % r;
-            int64_t t = t0 + tt;
-            Ps[tt][k] = (t < M) ? P[t * r + k] : 0.f;
-        }
-        __syncthreads();
+        for (int i = 0; i < 4; ++i)
+            if (q * 4 + i < r) Gs[jj][q * 4 + i] = v[i];
     }
-    double part = 0.0;
+    for (int e = tid; e < EP_T * r; e += 256) {
+        const int tt = e / r, k = e % r;
+        Ps[tt][k] = (t0 + tt < M) ? P[(t0 + tt) * r + k] : 0.f;
+    }
+    __syncthreads();
     const int jj = tid % EP_J;
     const int64_t j = j0 + jj;
     for (int tt = tid / EP_J; tt < EP_T; tt += 256 / EP_J) {
-        int64_t t = t0 + tt;
+        const int64_t t = t0 + tt;
         if (t >= M || j >= N) continue;
-        double y = (double)Y[t * ldy + j];
-        if (P != nullptr) {
-            double d = 0.0;
-            for (int k = 0; k < r; ++k) d = fma((double)Ps[tt][k], (double)Gs[jj][k], d);
-            y += (double)eps_signed * d;
-            Y[t * ldy + j] = (float)y;
-        }
-        if (loss_kind == AGZO_LOSS_MSE) {
-            float tv = (target_dtype == AGZO_BF16)
-                           ? bf16_to_f32(reinterpret_cast<const bf16_t*>(target)[t * ldt + j])
-                           : reinterpret_cast<const float*>(target)[t * ldt + j];
-            double d = y - (double)tv;
-            part = fma(d, d, part);
-        }
-    }
-    if (loss_kind == AGZO_LOSS_MSE) {
-        red[tid] = part;
-        __syncthreads();
-        for (int s = 128; s > 0; s >>= 1) {
-            if (tid < s) red[tid] += red[tid + s];
-            __syncthreads();
-        }
-        if (tid == 0) partials[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = red[0];
+        double s = 0.0;
+        for (int k = 0; k < r; ++k) s = fma((double)Ps[tt][k], (double)Gs[jj][k], s);
+        Y[t * ldy + j] = (float)((double)Y[t * ldy + j] + (double)eps_signed * s);
     }
 }
 
-hipError_t launch_epilogue_f32(float* Y, int64_t ldy, int64_t M, int64_t N, const float* P, int r, float eps_signed,
-                               uint64_t seed, const GemmLossArgs& loss, hipStream_t st) {
+hipError_t launch_rank_term_f32(float* Y, int64_t ldy, int64_t M, int64_t N, const float* P, int r, float eps_signed,
+                                uint64_t seed, hipStream_t st) {
     if (M == 0 || N == 0) return hipSuccess;
-    if (P == nullptr && loss.kind != AGZO_LOSS_MSE) return hipSuccess;
     dim3 grid((unsigned)((N + EP_J - 1) / EP_J), (unsigned)((M + EP_T - 1) / EP_T));
-    hipLaunchKernelGGL(epilogue_f32_kernel, grid, dim3(256), 0, st, Y, ldy, M, N, P, r, eps_signed, (uint32_t)seed,
-                       (uint32_t)(seed >> 32), loss.kind, loss.target_dtype, loss.target, loss.ldt, loss.partials);
+    hipLaunchKernelGGL(rank_term_f32_kernel, grid, dim3(256), 0, st, Y, ldy, M, N, P, r, eps_signed, (uint32_t)seed, (uint32_t)(seed >> 32));
     return hipGetLastError();
 }
+
+// ---------------------------------------------------------------------------
+// Tall-skinny products, bound by latency at the sizes this path sees: a workgroup is 16 waves that share one block of 16
+// result rows and split the contraction between them, so that the whole chip has loads in flight after one launch and no
+// second one is needed to add partial sums (they meet in LDS, in wave order).  The result has up to four blocks of 16 columns.
+// (The generic 64 x 64 tile kernel that these replace walked the contraction alone, with r of its 64 columns in use: 50 us at
+// 512 x 256 and r = 4, now 5 (xq) and 8 (xtt); the seven layers of 1000 x 1024 .. 3072 in one launch take 34 and 29 us.)
+// ---------------------------------------------------------------------------
+constexpr int SK_WAVES = 16;
+
+struct F32SkinnyDev {
+    F32SkinnyArgs a;
+    int vec;
+};
+
+// the waves' 16 x 16 blocks -> sum in wave order -> out (row0 + row, col0 + col), rows < nrow, columns < r
+template <int NB>
+__device__ __forceinline__ void skinny_f32_finish(const doublex4 (&acc)[NB], double* red, int64_t row0, int64_t nrow, int r,
+                                                  float* __restrict__ out) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lc = lane & 15, lg = lane >> 4;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) red[wave * 256 + (4 * e + lg) * 16 + lc] = acc[nb][e];
+        __syncthreads();
+        if (tid < 256) {
+            double s = 0.0;
+#pragma unroll
+            for (int w = 0; w < SK_WAVES; ++w) s += red[w * 256 + tid];
+            const int64_t row = row0 + (tid >> 4);
+            const int col = nb * 16 + (tid & 15);
+            if (row < nrow && col < r) out[row * r + col] = (float)s;
+        }
+        __syncthreads();
+    }
+}
+
+// T = X Q: rows = tokens, 16-wide chunks of d_in dealt to the waves
+template <int NB>
+__global__ __launch_bounds__(64 * SK_WAVES) void xq_f32_kernel(const KBatch<F32SkinnyDev> tb) {
+    __shared__ double red[SK_WAVES * 256];
+    uint32_t bx, by;
+    const F32SkinnyDev& d = tb.a[kbatch_find(tb, bx, by)];
+    const F32SkinnyArgs& a = d.a;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lc = lane & 15, lg = lane >> 4;
+    const int64_t t0 = (int64_t)bx * 16;
+    const float* xr = a.X + min(t0 + lc, a.M - 1) * a.ldx;
+    doublex4 acc[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[nb] = doublex4{0.0, 0.0, 0.0, 0.0};
+    const int nchunk = (int)((a.K + 15) / 16);
+    constexpr int U = (NB == 1) ? 4 : 2;                   // chunks in flight per wave
+    for (int c0 = wave; c0 < nchunk; c0 += U * SK_WAVES) {
+        float x[U][4], q[U][NB][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t k = 16 * (int64_t)(c0 + u * SK_WAVES) + 4 * lg;
+            if (d.vec) {
+                const float4 v = (k < a.K) ? *reinterpret_cast<const float4*>(xr + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+                x[u][0] = v.x; x[u][1] = v.y; x[u][2] = v.z; x[u][3] = v.w;
+            } else {
+#pragma unroll
+                for (int s = 0; s < 4; ++s) x[u][s] = (k + s < a.K) ? xr[k + s] : 0.f;
+            }
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int s = 0; s < 4; ++s) q[u][nb][s] = (k + s < a.K && nb * 16 + lc < a.r) ? a.V[(k + s) * a.r + nb * 16 + lc] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (c0 + u * SK_WAVES >= nchunk) break;        // (wave-uniform)
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+                    acc[nb] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[u][s], (double)q[u][nb][s], acc[nb], 0, 0, 0);
+        }
+    }
+    skinny_f32_finish<NB>(acc, red, t0, a.M, a.r, a.out);
+}
+
+// S = X^T T: rows = features, groups of four tokens dealt to the waves
+template <int NB>
+__global__ __launch_bounds__(64 * SK_WAVES) void xtt_f32_kernel(const KBatch<F32SkinnyDev> tb) {
+    __shared__ double red[SK_WAVES * 256];
+    uint32_t bx, by;
+    const F32SkinnyDev& d = tb.a[kbatch_find(tb, bx, by)];
+    const F32SkinnyArgs& a = d.a;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lc = lane & 15, lg = lane >> 4;
+    const int64_t f0 = (int64_t)bx * 16;
+    const float* xc = a.X + min(f0 + lc, a.K - 1);
+    doublex4 acc[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[nb] = doublex4{0.0, 0.0, 0.0, 0.0};
+    const int ngroup = (int)((a.M + 3) / 4);
+    constexpr int U = (NB <= 2) ? 8 : 4;                   // groups in flight per wave
+    for (int g0 = wave; g0 < ngroup; g0 += U * SK_WAVES) {
+        float x[U], v[U][NB];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t t = 4 * (int64_t)(g0 + u * SK_WAVES) + lg;
+            const bool in = t < a.M;
+            x[u] = in ? xc[t * a.ldx] : 0.f;
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) v[u][nb] = (in && nb * 16 + lc < a.r) ? a.V[t * a.r + nb * 16 + lc] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (g0 + u * SK_WAVES >= ngroup) break;        // (wave-uniform)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) acc[nb] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[u], (double)v[u][nb], acc[nb], 0, 0, 0);
+        }
+    }
+    skinny_f32_finish<NB>(acc, red, f0, a.K, a.r, a.out);
+}
+
+static hipError_t launch_skinny_f32(const F32SkinnyArgs* a, int n, bool transposed, hipStream_t st) {
+    if (n < 0 || n > kBatchMax) return hipErrorInvalidValue;
+    KBatch<F32SkinnyDev> tb;
+    tb.n = 0;
+    uint64_t blocks = 0;
+    int nb = 0;
+    for (int i = 0; i < n; ++i) {
+        if (a[i].M == 0 || a[i].K == 0) continue;
+        if (a[i].r < 1 || a[i].r > kMaxRank) return hipErrorInvalidValue;
+        const int want = (a[i].r + 15) / 16;
+        if (nb == 0) nb = want;
+        if (nb != want) return hipErrorInvalidValue;        // one padded rank per launch
+        F32SkinnyDev d;
+        d.a = a[i];
+        d.vec = (a[i].K % 4 == 0 && a[i].ldx % 4 == 0 && (reinterpret_cast<uintptr_t>(a[i].X) & 15) == 0);
+        tb.first[tb.n] = (uint32_t)blocks;
+        tb.gx[tb.n] = (uint32_t)(((transposed ? a[i].K : a[i].M) + 15) / 16);
+        blocks += tb.gx[tb.n];
+        tb.a[tb.n++] = d;
+    }
+    if (tb.n == 0) return hipSuccess;
+    if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)blocks), block(64 * SK_WAVES);
+    switch (nb * 2 + (transposed ? 1 : 0)) {
+        case 2: hipLaunchKernelGGL(xq_f32_kernel<1>, grid, block, 0, st, tb); break;
+        case 3: hipLaunchKernelGGL(xtt_f32_kernel<1>, grid, block, 0, st, tb); break;
+        case 4: hipLaunchKernelGGL(xq_f32_kernel<2>, grid, block, 0, st, tb); break;
+        case 5: hipLaunchKernelGGL(xtt_f32_kernel<2>, grid, block, 0, st, tb); break;
+        case 6: hipLaunchKernelGGL(xq_f32_kernel<3>, grid, block, 0, st, tb); break;
+        case 7: hipLaunchKernelGGL(xtt_f32_kernel<3>, grid, block, 0, st, tb); break;
+        case 8: hipLaunchKernelGGL(xq_f32_kernel<4>, grid, block, 0, st, tb); break;
+        case 9: hipLaunchKernelGGL(xtt_f32_kernel<4>, grid, block, 0, st, tb); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_xq_f32_many(const F32SkinnyArgs* a, int n, hipStream_t st) { return launch_skinny_f32(a, n, false, st); }
+hipError_t launch_xtt_f32_many(const F32SkinnyArgs* a, int n, hipStream_t st) { return launch_skinny_f32(a, n, true, st); }
 
 }  // namespace agzo

@@ -97,6 +97,39 @@ hipError_t launch_fill_normal(float* dst, int64_t rows, int cols, uint64_t seed,
     return hipGetLastError();
 }
 
+__global__ __launch_bounds__(256) void fill_normal_many_kernel(const KBatch<FillNormalArgs> tb, uint32_t tag) {
+    uint32_t bx, by;
+    const FillNormalArgs& a = tb.a[kbatch_find(tb, bx, by)];
+    const int nquad = (a.cols + 3) / 4;
+    const int64_t idx = (int64_t)bx * 256 + threadIdx.x;
+    if (idx >= a.rows * nquad) return;
+    const int64_t row = idx / nquad;
+    const int quad = (int)(idx - row * nquad);
+    const float4 z = philox_normal4((uint32_t)a.seed, (uint32_t)(a.seed >> 32), tag, (uint32_t)row, (uint32_t)quad);
+    const float v[4] = {z.x, z.y, z.z, z.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (quad * 4 + i < a.cols) a.dst[row * a.cols + quad * 4 + i] = v[i];
+}
+
+hipError_t launch_fill_normal_many(const FillNormalArgs* a, int n, uint32_t tag, hipStream_t st) {
+    if (n < 0 || n > kBatchMax) return hipErrorInvalidValue;
+    KBatch<FillNormalArgs> tb;
+    tb.n = 0;
+    uint64_t blocks = 0;
+    for (int m = 0; m < n; ++m) {
+        if (a[m].rows == 0 || a[m].cols == 0) continue;
+        tb.first[tb.n] = (uint32_t)blocks;
+        tb.gx[tb.n] = (uint32_t)((a[m].rows * ((a[m].cols + 3) / 4) + 255) / 256);
+        blocks += tb.gx[tb.n];
+        tb.a[tb.n++] = a[m];
+    }
+    if (tb.n == 0) return hipSuccess;
+    if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(fill_normal_many_kernel, dim3((unsigned)blocks), dim3(256), 0, st, tb, tag);
+    return hipGetLastError();
+}
+
 hipError_t launch_fill_normal_packT(bf16_t* dst, int64_t n, int64_t n_pad, int r, int rp, uint64_t seed, uint32_t tag,
                                     hipStream_t st) {
     if (n_pad == 0) return hipSuccess;
