@@ -4,6 +4,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <initializer_list>
 #include <mutex>
 #include <new>
@@ -309,6 +310,22 @@ int op_project(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* X,
     return 0;
 }
 
+GemmBf16Args forward_bf16_args(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* W, const void* X, const float* P,
+                               float eps_signed, uint64_t seed, void* Y, const GemmLossArgs& loss, bool shared) {
+    GemmBf16Args a;
+    a.X = static_cast<const bf16_t*>(X); a.ldx = L.ldx;
+    a.W = static_cast<const bf16_t*>(W); a.ldw = L.ldw;
+    a.M = L.n_tokens; a.N = L.d_out; a.K = L.d_in;
+    a.Y = Y; a.y_dtype = L.y_dtype; a.ldy = L.ldy;
+    a.P = P; a.r = L.r; a.eps_signed = eps_signed; a.seed = seed;
+    a.loss = loss;
+    a.shared = shared;
+    a.large_tiles = (L.tiling == AGZO_TILING_LARGE);
+    a.ext_ws = P ? ctx->ws + p.off_ext : nullptr;
+    if (((ctx->prof >> AGZO_PROF_GEMM) & 1u) && ctx->clk_used < kClkSlots) a.clk = ctx->clk + 4 * ctx->clk_used++;
+    return a;
+}
+
 F32FwdArgs forward_f32_args(const agzo_layer& L, const void* W, const void* X, const float* P, float eps_signed, uint64_t seed,
                             const GemmLossArgs& loss, bool shared) {
     F32FwdArgs a;
@@ -355,18 +372,8 @@ int op_forward(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* W,
         la.ce_tl = wsf(ctx, p.off_ce_tl);
     }
     if (L.dtype == AGZO_BF16) {
-        GemmBf16Args a;
-        a.X = static_cast<const bf16_t*>(X); a.ldx = L.ldx;
-        a.W = static_cast<const bf16_t*>(W); a.ldw = L.ldw;
-        a.M = L.n_tokens; a.N = L.d_out; a.K = L.d_in;
-        a.Y = Y; a.y_dtype = L.y_dtype; a.ldy = L.ldy;
-        a.P = P; a.r = L.r; a.eps_signed = eps_signed; a.seed = seed;
-        a.loss = la;
-        a.shared = shared;
-        a.large_tiles = (L.tiling == AGZO_TILING_LARGE);
-        a.ext_ws = P ? ctx->ws + p.off_ext : nullptr;
+        GemmBf16Args a = forward_bf16_args(ctx, L, p, W, X, P, eps_signed, seed, Y, la, shared);
         if (fused_sketch) { a.sk_T = wsh(ctx, p.off_TpackT); a.sk_mpad = p.m_pad; a.sk_partial = wsf(ctx, p.off_xtt); }
-        if (((ctx->prof >> AGZO_PROF_GEMM) & 1u) && ctx->clk_used < kClkSlots) a.clk = ctx->clk + 4 * ctx->clk_used++;
         {
             ProfScope ps(ctx, AGZO_PROF_GEMM);
             HIPCHK(launch_gemm_bf16(a, st));
@@ -816,7 +823,7 @@ int agzo_layer_forward_sketch(agzo_ctx* ctx, const agzo_layer* L, const void* W,
         TRY(check_y(ctx, L, Y));
         TRY(check_loss(ctx, L, loss, loss_dev));
     }
-    const Plan p = make_plan(*L, gemm && L->dtype == AGZO_F32 && !Y, loss && loss->kind == AGZO_LOSS_CE, false, 0, fused);
+    const Plan p = make_plan(*L, gemm && L->dtype == AGZO_F32 && !Y && loss && loss->kind == AGZO_LOSS_CE, loss && loss->kind == AGZO_LOSS_CE, false, 0, fused);
     TRY(reserve(ctx, p.total));
     if (fused) {
         {
@@ -872,7 +879,7 @@ int agzo_perturbed_forward(agzo_ctx* ctx, const agzo_layer* L, const void* W, co
     TRY(check_operands(ctx, L, W, X));
     TRY(check_y(ctx, L, Y));
     TRY(check_loss(ctx, L, loss, loss_dev));
-    const Plan p = make_plan(*L, L->dtype == AGZO_F32 && !Y, loss && loss->kind == AGZO_LOSS_CE);
+    const Plan p = make_plan(*L, L->dtype == AGZO_F32 && !Y && loss && loss->kind == AGZO_LOSS_CE, loss && loss->kind == AGZO_LOSS_CE);
     TRY(reserve(ctx, p.total));
     float* P = wsf(ctx, p.off_T);
     TRY(op_project(ctx, *L, p, X, B, P, false));
@@ -963,12 +970,12 @@ int agzo_basis_many(agzo_ctx* ctx, const agzo_basis_item* items, int32_t n, int3
     return basis_many_impl(ctx, jobs, K, flags);
 }
 
-int agzo_step_many(agzo_ctx* ctx, const agzo_step_item* items, int32_t n, int32_t K, float eps, float lr, int32_t flags) {
-    if (!ctx) return AGZO_EINVAL;
-    if (n < 0 || (n > 0 && !items)) return fail(ctx, AGZO_EINVAL, "bad item list");
-    if (K < 0 || K > 64) return fail(ctx, AGZO_EINVAL, "K=%d outside 0..64", K);
-    if (!(eps > 0.f)) return fail(ctx, AGZO_EINVAL, "eps must be positive");
-    if (flags & AGZO_NAIVE_INPLACE) return fail(ctx, AGZO_EINVAL, "the in-place comparator runs layer by layer (agzo_step)");
+namespace {
+// Alg. 2 for n single-layer problems (agzo_step_many; agzo_step is the same with n = 1, so that their results agree bit for
+// bit).  Squared-error layers run every stage together: the evaluations of part 1 (f0, or all three in the shared schedule) and
+// of part 2 (f+ and f-) go to the launch functions as one list, and one launch finishes every loss and scalar.  Cross-entropy
+// layers evaluate one by one (every evaluation is finished by launches of its own).
+int step_many_impl(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, float eps, float lr, int flags) {
     const bool shared = (flags & AGZO_SHARED_FORWARD) != 0, one_sided = (flags & AGZO_ONE_SIDED) != 0;
     std::vector<LayerJob> jobs((size_t)n);
     size_t total = 0;
@@ -982,7 +989,7 @@ int agzo_step_many(agzo_ctx* ctx, const agzo_step_item* items, int32_t n, int32_
         TRY(check_update(ctx, it.W, reinterpret_cast<const float*>(it.X) /* B is the call's own: any non-NULL */, it.layer.dtype, it.layer.d_out, it.layer.d_in, it.layer.ldw, it.layer.r));
         LayerJob& j = jobs[(size_t)m];
         j.L = it.layer; j.X = it.X; j.seed = it.seed; j.S0 = nullptr;
-        j.p = make_plan(j.L, j.L.dtype == AGZO_F32, it.loss.kind == AGZO_LOSS_CE, shared, total);
+        j.p = make_plan(j.L, j.L.dtype == AGZO_F32 && it.loss.kind == AGZO_LOSS_CE, it.loss.kind == AGZO_LOSS_CE, shared, total);
         total = j.p.total;
     }
     size_t upd_bytes = 0;
@@ -991,64 +998,85 @@ int agzo_step_many(agzo_ctx* ctx, const agzo_step_item* items, int32_t n, int32_
     TRY(reserve(ctx, total + upd_bytes));
     for (int m = 0; m < n; ++m) jobs[(size_t)m].B = items[m].B_out ? items[m].B_out : wsf(ctx, jobs[(size_t)m].p.off_B);
     hipStream_t st = ctx->stream;
-    auto forward = [&](int m, const float* P, float e, double* dst, bool sh, int slot) -> int {
-        const agzo_step_item& it = items[m];
-        const LayerJob& j = jobs[(size_t)m];
-        return op_forward(ctx, j.L, j.p, it.W, it.X, P, e, it.seed, nullptr, &it.loss, dst, sh, slot, it.loss.kind == AGZO_LOSS_MSE);
-    };
-    // squared-error layers in fp32 storage: the evaluations of part `perturbed` (0: f0, 1: f+ and f-, or all three in the
-    // shared schedule) of up to kBatchMax / 2 layers per launch; the loss partials of phase ph go to slot ph
-    auto batched_f32 = [&](int m) { return items[m].layer.dtype == AGZO_F32 && items[m].loss.kind == AGZO_LOSS_MSE; };
-    auto forward_f32_batched = [&](bool perturbed) -> int {
-        F32FwdArgs a[kBatchMax];
-        int na = 0;
+
+    // the squared-error evaluations of phases [ph0, ph1): 0 = f0 (or, shared, all three from one pass), 1 = f+, 2 = f-; the
+    // loss partials of phase ph go to slot ph of the layer's region
+    auto forward_mse = [&](int ph0, int ph1) -> int {
+        std::vector<GemmBf16Args> bf;
+        std::vector<F32FwdArgs> f32;
+        std::vector<GemmExtArgs> ext;
+        const bool perturbed = shared || ph0 > 0;
         for (int m = 0; m < n; ++m) {
-            if (!batched_f32(m)) continue;
             const agzo_step_item& it = items[m];
+            if (it.loss.kind != AGZO_LOSS_MSE) continue;
             const LayerJob& j = jobs[(size_t)m];
-            double* part = reinterpret_cast<double*>(ctx->ws + j.p.off_part);
-            if (3 * (size_t)j.p.n_part > j.p.part_count) return fail(ctx, AGZO_EHIP, "internal: loss scratch");
+            if (3 * (size_t)j.p.n_part > j.p.part_count) return fail(ctx, AGZO_EHIP, "internal: loss scratch of layer %d", m);
             GemmLossArgs la;
             la.kind = AGZO_LOSS_MSE; la.target_dtype = it.loss.target_dtype; la.target = it.loss.target; la.ldt = it.loss.ldt;
             const float* P = perturbed ? wsf(ctx, j.p.off_T) : nullptr;
-            for (int ph = perturbed && !shared ? 1 : 0; ph < (perturbed && !shared ? (one_sided ? 2 : 3) : 1); ++ph) {
-                la.partials = part + (size_t)ph * j.p.n_part;
-                a[na++] = forward_f32_args(j.L, it.W, it.X, P, ph == 2 ? -eps : eps, it.seed, la, perturbed && shared);
+            const bool pair = perturbed && !shared && j.L.dtype == AGZO_BF16;      // both signs' operands in one preparation
+            if (pair) ext.push_back(GemmExtArgs{ctx->ws + j.p.off_ext, j.L.n_tokens, j.L.d_out, P, j.L.r, eps, -eps, ph1 > 2, it.seed});
+            for (int ph = ph0; ph < ph1; ++ph) {
+                la.partials = reinterpret_cast<double*>(ctx->ws + j.p.off_part) + (size_t)ph * j.p.n_part;
+                const float e = ph == 2 ? -eps : eps;
+                if (j.L.dtype == AGZO_F32) {
+                    f32.push_back(forward_f32_args(j.L, it.W, it.X, P, e, it.seed, la, shared));
+                } else {
+                    bf.push_back(forward_bf16_args(ctx, j.L, j.p, it.W, it.X, P, e, it.seed, nullptr, la, shared));
+                    bf.back().ext_ready = pair;
+                    bf.back().ext_side = ph == 2 ? 1 : 0;
+                }
             }
-            if (na + 2 > kBatchMax) { HIPCHK(launch_forward_f32_many(a, na, st)); na = 0; }
         }
-        HIPCHK(launch_forward_f32_many(a, na, st));
+        for (size_t b = 0; b < f32.size(); b += kBatchMax)
+            HIPCHK(launch_forward_f32_many(f32.data() + b, (int)std::min(f32.size() - b, (size_t)kBatchMax), st));
+        if (bf.empty()) return 0;
+        for (size_t b = 0; b < ext.size(); b += kBatchMax)
+            HIPCHK(launch_gemm_ext_prep_many(ext.data() + b, (int)std::min(ext.size() - b, (size_t)kBatchMax), st));
+        if (!((ctx->prof >> AGZO_PROF_GEMM) & 1u)) {
+            HIPCHK(launch_gemm_bf16_many(bf.data(), (int)bf.size(), st));
+            return 0;
+        }
+        for (const GemmBf16Args& a : bf) {      // timed: a launch of its own for every forward (the results are the same)
+            ProfScope ps(ctx, AGZO_PROF_GEMM);
+            HIPCHK(launch_gemm_bf16(a, st));
+        }
         return 0;
+    };
+    auto forward_ce = [&](int m, const float* P, float e, double* dst, bool sh, int slot) -> int {
+        const agzo_step_item& it = items[m];
+        if (it.loss.kind != AGZO_LOSS_CE) return 0;
+        const LayerJob& j = jobs[(size_t)m];
+        return op_forward(ctx, j.L, j.p, it.W, it.X, P, e, it.seed, nullptr, &it.loss, dst, sh, slot, false);
     };
     // Alg. 2, part 1: the base forward of every layer, and every layer's basis from the same activations
     if (!shared) {
-        TRY(forward_f32_batched(false));
-        for (int m = 0; m < n; ++m)
-            if (!batched_f32(m)) TRY(forward(m, nullptr, 0.f, items[m].out_dev, false, 0));
+        TRY(forward_mse(0, 1));
+        for (int m = 0; m < n; ++m) TRY(forward_ce(m, nullptr, 0.f, items[m].out_dev, false, 0));
     }
     TRY(basis_many_impl(ctx, jobs, K, flags & AGZO_INIT_FEATURE));
     // parts 2-3: the perturbed evaluations
     TRY(project_many(ctx, jobs));
-    TRY(forward_f32_batched(true));
+    if (shared) TRY(forward_mse(0, 1));
+    else TRY(forward_mse(1, one_sided ? 2 : 3));
     for (int m = 0; m < n; ++m) {
-        if (batched_f32(m)) continue;
         const float* P = wsf(ctx, jobs[(size_t)m].p.off_T);
         if (shared) {
-            TRY(forward(m, P, eps, items[m].out_dev, true, 0));
+            TRY(forward_ce(m, P, eps, items[m].out_dev, true, 0));
         } else {
-            TRY(forward(m, P, +eps, items[m].out_dev + 1, false, 1));
-            if (!one_sided) TRY(forward(m, P, -eps, items[m].out_dev + 2, false, 2));
+            TRY(forward_ce(m, P, +eps, items[m].out_dev + 1, false, 1));
+            if (!one_sided) TRY(forward_ce(m, P, -eps, items[m].out_dev + 2, false, 2));
         }
     }
     // the scalars, then every update in one batched call
     std::vector<agzo_update_item> upd;
+    std::vector<FinishTwoPointArgs> fin;
     for (int m = 0; m < n; ++m) {
         const agzo_step_item& it = items[m];
         const LayerJob& j = jobs[(size_t)m];
         if (it.loss.kind == AGZO_LOSS_MSE)
-            HIPCHK(launch_finish_two_point(reinterpret_cast<const double*>(ctx->ws + j.p.off_part), j.p.n_part,
-                                           1.0 / ((double)j.L.n_tokens * (double)j.L.d_out), (shared || !one_sided) ? 3 : 2,
-                                           it.out_dev, eps, one_sided ? 1 : 0, st));
+            fin.push_back(FinishTwoPointArgs{reinterpret_cast<const double*>(ctx->ws + j.p.off_part), j.p.n_part,
+                                             1.0 / ((double)j.L.n_tokens * (double)j.L.d_out), it.out_dev});
         else
             HIPCHK(launch_two_point(it.out_dev, eps, one_sided ? 1 : 0, st));
         if (!it.B_out) {
@@ -1059,15 +1087,22 @@ int agzo_step_many(agzo_ctx* ctx, const agzo_step_item* items, int32_t n, int32_
             upd.push_back(u);
         }
     }
+    for (size_t b = 0; b < fin.size(); b += kBatchMax)
+        HIPCHK(launch_finish_two_point_many(fin.data() + b, (int)std::min(fin.size() - b, (size_t)kBatchMax), (shared || !one_sided) ? 3 : 2, eps,
+                                            one_sided ? 1 : 0, st));
     if (upd.empty()) return AGZO_OK;
     // the update's factor fragments go behind the layers' carve-outs, which still hold the bases
-    size_t need = 0;
-    for (const agzo_update_item& u : upd) need += update_workspace_bytes(u.dtype, u.d_out, u.d_in, u.r);
-    if (total + need > ctx->ws_bytes) {
-        // (reserve() would move the workspace and with it the bases: sized up front instead)
-        return fail(ctx, AGZO_EHIP, "internal: update scratch was not reserved");
-    }
     return update_many_at(ctx, upd.data(), (int)upd.size(), total);
+}
+}  // namespace
+
+int agzo_step_many(agzo_ctx* ctx, const agzo_step_item* items, int32_t n, int32_t K, float eps, float lr, int32_t flags) {
+    if (!ctx) return AGZO_EINVAL;
+    if (n < 0 || (n > 0 && !items)) return fail(ctx, AGZO_EINVAL, "bad item list");
+    if (K < 0 || K > 64) return fail(ctx, AGZO_EINVAL, "K=%d outside 0..64", K);
+    if (!(eps > 0.f)) return fail(ctx, AGZO_EINVAL, "eps must be positive");
+    if (flags & AGZO_NAIVE_INPLACE) return fail(ctx, AGZO_EINVAL, "the in-place comparator runs layer by layer (agzo_step)");
+    return step_many_impl(ctx, items, n, K, eps, lr, flags);
 }
 
 namespace {
@@ -1133,8 +1168,13 @@ static int step_impl(agzo_ctx* ctx, const agzo_layer* L, void* W, const void* X,
     if (K < 0 || K > 64) return fail(ctx, AGZO_EINVAL, "K=%d outside 0..64", K);
     if (!(eps > 0.f)) return fail(ctx, AGZO_EINVAL, "eps must be positive");
     TRY(check_operands(ctx, L, W, X));
-    const Plan p = make_plan(*L, L->dtype == AGZO_F32, loss->kind == AGZO_LOSS_CE,
-                             (flags & AGZO_SHARED_FORWARD) && !(flags & AGZO_NAIVE_INPLACE));
+    if (!(flags & AGZO_NAIVE_INPLACE)) {
+        agzo_step_item it;
+        it.layer = *L; it.W = W; it.X = X; it.loss = *loss; it.seed = seed; it.out_dev = out_dev; it.B_out = B_out;
+        return step_many_impl(ctx, &it, 1, K, eps, lr, flags);
+    }
+    // the comparator: perturb in place, plain forward, undo
+    const Plan p = make_plan(*L, L->dtype == AGZO_F32 && loss->kind == AGZO_LOSS_CE, loss->kind == AGZO_LOSS_CE);
     TRY(reserve(ctx, p.total));
     hipStream_t st = ctx->stream;
     float* B = B_out ? B_out : wsf(ctx, p.off_B);
@@ -1143,53 +1183,32 @@ static int step_impl(agzo_ctx* ctx, const agzo_layer* L, void* W, const void* X,
     // cross-entropy finishes each loss on its own and only g is left to do
     const bool mse = loss->kind == AGZO_LOSS_MSE;
     auto finish = [&](int nphase) -> int {
-        if (mse)
-            HIPCHK(launch_finish_two_point(reinterpret_cast<const double*>(ctx->ws + p.off_part), p.n_part,
-                                           1.0 / ((double)L->n_tokens * (double)L->d_out), nphase, out_dev, eps,
-                                           one_sided ? 1 : 0, st));
-        else
+        if (mse) {
+            const FinishTwoPointArgs f{reinterpret_cast<const double*>(ctx->ws + p.off_part), p.n_part,
+                                       1.0 / ((double)L->n_tokens * (double)L->d_out), out_dev};
+            HIPCHK(launch_finish_two_point_many(&f, 1, nphase, eps, one_sided ? 1 : 0, st));
+        } else {
             HIPCHK(launch_two_point(out_dev, eps, one_sided ? 1 : 0, st));
+        }
         return 0;
     };
-
-    if ((flags & AGZO_SHARED_FORWARD) && !(flags & AGZO_NAIVE_INPLACE)) {
-        // extraction first, then f0, f+ and f- from one pass over X and W (valid for a single layer:
-        // all three evaluations read the same activations)
-        TRY(op_basis(ctx, *L, p, X, K, seed, nullptr, flags & AGZO_INIT_FEATURE, B));
-        float* P = wsf(ctx, p.off_T);
-        TRY(op_project(ctx, *L, p, X, B, P, true));
-        TRY(op_forward(ctx, *L, p, W, X, P, eps, seed, nullptr, loss, out_dev, true, 0, mse));
-        TRY(finish(3));
-        if (!B_out) TRY(op_update(ctx, *L, p.off_upd, W, B, seed, lr, out_dev + 3));
-        return AGZO_OK;
-    }
-    // 1. base forward f0 and subspace extraction from the same activations (Alg. 2, part 1)
     TRY(op_forward(ctx, *L, p, W, X, nullptr, 0.f, seed, nullptr, loss, out_dev + 0, false, 0, mse));
     TRY(op_basis(ctx, *L, p, X, K, seed, nullptr, flags & AGZO_INIT_FEATURE, B));
-    // 2. perturbed evaluations (Alg. 2, parts 2-3)
-    if (flags & AGZO_NAIVE_INPLACE) {
+    TRY(op_update(ctx, *L, p.off_upd, W, B, seed, -eps, nullptr));
+    TRY(op_forward(ctx, *L, p, W, X, nullptr, 0.f, seed, nullptr, loss, out_dev + 1, false, 1, mse));
+    if (!one_sided) {
+        TRY(op_update(ctx, *L, p.off_upd, W, B, seed, 2.f * eps, nullptr));
+        TRY(op_forward(ctx, *L, p, W, X, nullptr, 0.f, seed, nullptr, loss, out_dev + 2, false, 2, mse));
         TRY(op_update(ctx, *L, p.off_upd, W, B, seed, -eps, nullptr));
-        TRY(op_forward(ctx, *L, p, W, X, nullptr, 0.f, seed, nullptr, loss, out_dev + 1, false, 1, mse));
-        if (!one_sided) {
-            TRY(op_update(ctx, *L, p.off_upd, W, B, seed, 2.f * eps, nullptr));
-            TRY(op_forward(ctx, *L, p, W, X, nullptr, 0.f, seed, nullptr, loss, out_dev + 2, false, 2, mse));
-            TRY(op_update(ctx, *L, p.off_upd, W, B, seed, -eps, nullptr));
-        } else if (B_out) {
-            TRY(op_update(ctx, *L, p.off_upd, W, B, seed, eps, nullptr));
-        } else {
-            // Alg. 2 as printed: W still holds W + eps Z here, and the last line takes the perturbation out and applies
-            // the update in one sweep, W <- W - (eps + lr g) Z
-            TRY(finish(2));
-            TRY(op_update(ctx, *L, p.off_upd, W, B, seed, lr, out_dev + 3, eps));
-            return AGZO_OK;
-        }
+    } else if (B_out) {
+        TRY(op_update(ctx, *L, p.off_upd, W, B, seed, eps, nullptr));
     } else {
-        float* P = wsf(ctx, p.off_T);
-        TRY(op_project(ctx, *L, p, X, B, P, true));
-        TRY(op_forward(ctx, *L, p, W, X, P, +eps, seed, nullptr, loss, out_dev + 1, false, 1, mse));
-        if (!one_sided) TRY(op_forward(ctx, *L, p, W, X, P, -eps, seed, nullptr, loss, out_dev + 2, false, 2, mse));
+        // Alg. 2 as printed: W still holds W + eps Z here, and the last line takes the perturbation out and applies
+        // the update in one sweep, W <- W - (eps + lr g) Z
+        TRY(finish(2));
+        TRY(op_update(ctx, *L, p.off_upd, W, B, seed, lr, out_dev + 3, eps));
+        return AGZO_OK;
     }
-    // 3. scalar g and the rank-r update
     TRY(finish(one_sided ? 2 : 3));
     if (!B_out) TRY(op_update(ctx, *L, p.off_upd, W, B, seed, lr, out_dev + 3));
     return AGZO_OK;

@@ -153,6 +153,9 @@ struct GemmBf16Args {
     // gemm_bf16_ext_bytes() bytes of device scratch for the rank-r extension operands of a perturbed forward
     // (NULL: every tile builds them itself)
     void* ext_ws = nullptr;
+    // the extension operands are in ext_ws already (launch_gemm_ext_prep_many): ext_side 0 takes the W side with coef folded
+    // in, 1 the one with coef2
+    bool ext_ready = false; int ext_side = 0;
     // fused range sketch S = X^T Omega (NULL: none; only where gemm_bf16_fuses_sketch() says so): Omega^T as bf16
     // planes [3][16][sk_mpad], sk_mpad = gemm_bf16_sketch_mpad(M); sk_partial receives gemm_bf16_sketch_splits(M)
     // partial sums [split][K][16], one per 128-token tile
@@ -171,6 +174,12 @@ bool gemm_bf16_fuses_sketch(int64_t M, int64_t N, int r, bool large_tiles);
 inline int64_t gemm_bf16_sketch_mpad(int64_t M) { return (M + 127) / 128 * 128; }
 inline int gemm_bf16_sketch_splits(int64_t M) { return (int)((M + 127) / 128); }
 hipError_t launch_gemm_bf16(const GemmBf16Args& a, hipStream_t st);
+// several independent forwards: those that the kernel of gemm_bf16_mid.hip takes share launches, the others run one by one.
+// Every result has the bits of a launch of its own.  Workspaces (ext_ws unless ext_ready, loss partials) must not overlap.
+hipError_t launch_gemm_bf16_many(const GemmBf16Args* a, int n, hipStream_t st);
+// extension operands of several layers in one launch: the W side times coef and, with two = true, once more times coef2
+struct GemmExtArgs { void* ext_ws; int64_t M, N; const float* P; int r; float coef, coef2; bool two; uint64_t seed; };
+hipError_t launch_gemm_ext_prep_many(const GemmExtArgs* a, int n, hipStream_t st);
 
 // gemm_f32.hip : fp32 storage, fp64 accumulation on the matrix cores.  Up to kBatchMax problems per launch
 struct F32FwdArgs {
@@ -259,9 +268,10 @@ hipError_t launch_ce_rows_f32(const float* Y, int64_t ldy, int64_t M, int64_t N,
 // out[b] = scale * sum(partials[b*n .. b*n+n)), b < nout
 hipError_t launch_finish_loss(const double* partials, int n, double scale, double* out, int nout, hipStream_t st);
 hipError_t launch_two_point(double* out4, float eps, int one_sided, hipStream_t st);
-// both in one launch: partials [nphase][n] (phase 0 = f0, 1 = f+, 2 = f-; nphase = 2 for the one-sided form) -> out4
-hipError_t launch_finish_two_point(const double* partials, int n, double scale, int nphase, double* out4, float eps,
-                                   int one_sided, hipStream_t st);
+// finish_loss for nphase consecutive partial arrays [nphase][n] (phase 0 = f0, 1 = f+, 2 = f-; nphase = 2 for the one-sided
+// form) and two_point -> out4, for several layers (at most kBatchMax) in one launch
+struct FinishTwoPointArgs { const double* partials; int n; double scale; double* out4; };
+hipError_t launch_finish_two_point_many(const FinishTwoPointArgs* a, int n, int nphase, float eps, int one_sided, hipStream_t st);
 
 // update.hip : theta[i][j] += scale * (*g_dev or 1) * z(i, j), z = Philox normal of stream AGZO_TAG_DENSE (rows < 2^32)
 hipError_t launch_dense_axpy(void* theta, int dtype, int64_t rows, int64_t cols, int64_t ld, uint64_t seed, float scale,

@@ -560,19 +560,30 @@ __global__ __launch_bounds__(64 * WA * WB) void gemm_bf16_kernel(GemmParams p) {
 
 
 
-// Extension operands for one perturbed forward, written once instead of once per tile: eight columns per thread.
+// Extension operands of perturbed forwards, written once per layer instead of once per tile: eight columns per thread.
 // Rows 0..M-1 are the X side ([Ph | Ph | Pl | 0], P = X B split hi + lo in bf16), rows M..M+N-1 the W side
-// ([Gh | Gl | Gh | 0], G regenerated from the Philox seed, times the signed eps); n_w = 2 adds rows M+N..M+2N-1, the
-// W side once more with coef2 (the shared-forward kernel's second pass, -2 eps).
-__global__ __launch_bounds__(256) void gemm_ext_prep_kernel(bf16_t* __restrict__ Xext, bf16_t* __restrict__ Wext, int64_t M,
-                                                            int64_t N, int ext_ld, const float* __restrict__ P, int r, int rp,
-                                                            float coef, float coef2, int n_w, uint32_t s_lo, uint32_t s_hi) {
+// ([Gh | Gl | Gh | 0], G regenerated from the Philox seed, times coef: the signed eps); n_w = 2 adds rows M+N..M+2N-1, the
+// W side once more with coef2 (the other sign's, or the shared-forward kernel's second pass, -2 eps).  Several layers per
+// launch (fourteen launches of one operand set each took 62 us of a layer set's step).
+struct ExtDev {
+    bf16_t* Xext; bf16_t* Wext;
+    int64_t M, N; int ext_ld;
+    const float* P; int r, rp;
+    float coef, coef2; int n_w;
+    uint32_t s_lo, s_hi;
+};
+__global__ __launch_bounds__(256) void gemm_ext_prep_kernel(const KBatch<ExtDev> tb) {
+    uint32_t bx, by;
+    const ExtDev& a = tb.a[kbatch_find(tb, bx, by)];
+    const int ext_ld = a.ext_ld, r = a.r, rp = a.rp;
+    const int64_t M = a.M, N = a.N;
     const int chunks = ext_ld / 8;
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (M + n_w * N) * chunks) return;
+    const int64_t idx = (int64_t)bx * 256 + threadIdx.x;
+    if (idx >= (M + a.n_w * N) * chunks) return;
     int64_t row = idx / chunks;
     const bool second = row >= M + N;
-    if (second) { row -= N; coef = coef2; }
+    if (second) row -= N;
+    const float coef = second ? a.coef2 : a.coef;
     const int col0 = (int)(idx % chunks) * 8;
     const int seg = col0 / rp, k0 = col0 % rp;
     uint32_t hi[4] = {0, 0, 0, 0}, lo[4] = {0, 0, 0, 0};
@@ -581,15 +592,15 @@ __global__ __launch_bounds__(256) void gemm_ext_prep_kernel(bf16_t* __restrict__
         if (row < M) {
 #pragma unroll
             for (int i = 0; i < 8; ++i)
-                if (k0 + i < r) v[i] = P[row * r + k0 + i];
+                if (k0 + i < r) v[i] = a.P[row * r + k0 + i];
         } else {
             const int64_t j = row - M;
             if (k0 < r) {
-                const float4 z = philox_normal4(s_lo, s_hi, AGZO_TAG_G, (uint32_t)j, (uint32_t)(k0 >> 2));
+                const float4 z = philox_normal4(a.s_lo, a.s_hi, AGZO_TAG_G, (uint32_t)j, (uint32_t)(k0 >> 2));
                 v[0] = z.x; v[1] = z.y; v[2] = z.z; v[3] = z.w;
             }
             if (k0 + 4 < r) {
-                const float4 z = philox_normal4(s_lo, s_hi, AGZO_TAG_G, (uint32_t)j, (uint32_t)((k0 >> 2) + 1));
+                const float4 z = philox_normal4(a.s_lo, a.s_hi, AGZO_TAG_G, (uint32_t)j, (uint32_t)((k0 >> 2) + 1));
                 v[4] = z.x; v[5] = z.y; v[6] = z.z; v[7] = z.w;
             }
 #pragma unroll
@@ -604,14 +615,38 @@ __global__ __launch_bounds__(256) void gemm_ext_prep_kernel(bf16_t* __restrict__
     // X side: [hi | hi | lo]; W side: [hi | lo | hi]
     const bool use_lo = (row < M) ? (seg == 2) : (seg == 1);
     const uint4 out = use_lo ? make_uint4(lo[0], lo[1], lo[2], lo[3]) : make_uint4(hi[0], hi[1], hi[2], hi[3]);
-    bf16_t* dst = (row < M) ? Xext + row * ext_ld + col0 : Wext + (row - M + (second ? N : 0)) * ext_ld + col0;
+    bf16_t* dst = (row < M) ? a.Xext + row * ext_ld + col0 : a.Wext + (row - M + (second ? N : 0)) * ext_ld + col0;
     *reinterpret_cast<uint4*>(dst) = out;
 }
 
+static int ext_width(int r) { return (3 * ((r + 15) / 16 * 16) + BK - 1) / BK * BK; }
+
+hipError_t launch_gemm_ext_prep_many(const GemmExtArgs* a, int n, hipStream_t st) {
+    if (n < 0 || n > kBatchMax) return hipErrorInvalidValue;
+    KBatch<ExtDev> tb;
+    tb.n = 0;
+    uint64_t blocks = 0;
+    for (int m = 0; m < n; ++m) {
+        ExtDev d;
+        d.M = a[m].M; d.N = a[m].N; d.ext_ld = ext_width(a[m].r);
+        d.Xext = static_cast<bf16_t*>(a[m].ext_ws); d.Wext = d.Xext + d.M * d.ext_ld;
+        d.P = a[m].P; d.r = a[m].r; d.rp = (a[m].r + 15) / 16 * 16;
+        d.coef = a[m].coef; d.coef2 = a[m].coef2; d.n_w = a[m].two ? 2 : 1;
+        d.s_lo = (uint32_t)a[m].seed; d.s_hi = (uint32_t)(a[m].seed >> 32);
+        const int64_t items = (d.M + d.n_w * d.N) * (d.ext_ld / 8);
+        tb.first[tb.n] = (uint32_t)blocks;
+        tb.gx[tb.n] = (uint32_t)((items + 255) / 256);
+        blocks += tb.gx[tb.n];
+        tb.a[tb.n++] = d;
+    }
+    if (blocks == 0) return hipSuccess;
+    if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(gemm_ext_prep_kernel, dim3((unsigned)blocks), dim3(256), 0, st, tb);
+    return hipGetLastError();
+}
+
 size_t gemm_bf16_ext_bytes(int64_t M, int64_t N, int r) {
-    const int rp = (r + 15) / 16 * 16;
-    const int ext_ld = (3 * rp + BK - 1) / BK * BK;
-    return (size_t)(M + 2 * N) * ext_ld * sizeof(bf16_t);   // X side, W side, and the W side of a second pass
+    return (size_t)(M + 2 * N) * ext_width(r) * sizeof(bf16_t);   // X side, W side, and the W side of a second pass
 }
 
 template <int WA, int WB, bool SHARED, int EPI>
@@ -629,9 +664,20 @@ static hipError_t launch_variant(const GemmParams& p, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_gemm_bf16(const GemmBf16Args& a, hipStream_t st) {
-    if (a.M == 0 || a.N == 0) return hipSuccess;
+namespace {
+enum class Kernel { small, mid, aligned, general };
+
+// what a forward needs at its launch, and the kernel that takes it (by its own shape and operands alone)
+struct Choice {
     GemmParams p;
+    GemmItem g;         // mid
+    int out;            // mid: 0 squared error, 1 stored bf16 output
+    Kernel kernel;
+    bool prep;          // the extension operands still have to be written
+};
+
+hipError_t choose(const GemmBf16Args& a, Choice& c) {
+    GemmParams& p = c.p;
     p.X = a.X; p.ldx = a.ldx; p.W = a.W; p.ldw = a.ldw;
     p.M = a.M; p.N = a.N; p.K = a.K;
     p.Y = a.Y; p.y_dtype = a.y_dtype; p.ldy = a.ldy;
@@ -650,47 +696,96 @@ hipError_t launch_gemm_bf16(const GemmBf16Args& a, hipStream_t st) {
         vec = vec && (a.loss.ldt % 8 == 0) && ((reinterpret_cast<uintptr_t>(a.loss.target) & 15) == 0);
     p.vec_ok = vec ? 1 : 0;
     p.shared = a.shared ? 1 : 0;
-    p.Xext = nullptr; p.Wext = nullptr; p.Wext2 = nullptr; p.ext_ld = 0;
-    const bool small = small_shape(a.M, a.N) && !a.large_tiles && !a.shared && p.loss_kind != AGZO_LOSS_CE;
-    // the kernel of gemm_bf16_aligned.hip takes tile-aligned layers: squared error without a stored Y (also in
-    // shared-forward mode), the cross-entropy statistics without a stored Y, or a stored bf16 Y without a loss
-    const bool aligned_shape = !small && vec && a.M % BT == 0 && a.N % BT == 0 && a.K % BK == 0 && a.K >= 2 * BK && (!a.P || a.ext_ws);
-    const bool mse = aligned_shape && ((a.loss.kind == AGZO_LOSS_MSE && !a.Y) ||
-                                       (a.loss.kind == AGZO_LOSS_CE && !a.Y && !a.shared) ||
-                                       (a.loss.kind == AGZO_LOSS_NONE && a.Y && a.y_dtype == AGZO_BF16 && !a.shared));
-    if (a.P && a.ext_ws && (!a.shared || mse)) {
-        p.ext_ld = (3 * p.rp + BK - 1) / BK * BK;
-        bf16_t* xe = static_cast<bf16_t*>(a.ext_ws);
-        bf16_t* we = xe + a.M * p.ext_ld;
-        const int n_w = a.shared ? 2 : 1;
-        const int64_t items = (a.M + n_w * a.N) * (p.ext_ld / 8);
-        hipLaunchKernelGGL(gemm_ext_prep_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, xe, we, a.M, a.N, p.ext_ld,
-                           a.P, a.r, p.rp, a.eps_signed, -2.f * a.eps_signed, n_w, p.s_lo, p.s_hi);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        p.Xext = xe; p.Wext = we;
-        if (a.shared) p.Wext2 = we + a.N * p.ext_ld;
-    }
     p.ce_target = reinterpret_cast<const int32_t*>(a.loss.target);
     p.ce_ms = reinterpret_cast<float2*>(a.loss.ce_ms);
     p.ce_tl = a.loss.ce_tl;
     p.clk = a.clk;
-    p.sk_T = nullptr; p.sk_mpad = 0; p.sk_partial = nullptr;
-    if (a.sk_T) {
-        if (!small || a.P || !gemm_bf16_fuses_sketch(a.M, a.N, a.r, a.large_tiles)) return hipErrorInvalidValue;
-        p.sk_T = a.sk_T; p.sk_mpad = a.sk_mpad; p.sk_partial = a.sk_partial;
+    p.sk_T = a.sk_T; p.sk_mpad = a.sk_T ? a.sk_mpad : 0; p.sk_partial = a.sk_T ? a.sk_partial : nullptr;
+    const bool small = small_shape(a.M, a.N) && !a.large_tiles && !a.shared && p.loss_kind != AGZO_LOSS_CE;
+    // the kernel of gemm_bf16_aligned.hip takes tile-aligned layers: squared error without a stored Y (also in
+    // shared-forward mode), the cross-entropy statistics without a stored Y, or a stored bf16 Y without a loss
+    const bool aligned = !small && vec && a.M % BT == 0 && a.N % BT == 0 && a.K % BK == 0 && a.K >= 2 * BK && (!a.P || a.ext_ws) &&
+                         ((a.loss.kind == AGZO_LOSS_MSE && !a.Y) || (a.loss.kind == AGZO_LOSS_CE && !a.Y && !a.shared) ||
+                          (a.loss.kind == AGZO_LOSS_NONE && a.Y && a.y_dtype == AGZO_BF16 && !a.shared));
+    p.Xext = nullptr; p.Wext = nullptr; p.Wext2 = nullptr; p.ext_ld = 0;
+    c.prep = false;
+    if (a.P && a.ext_ws && (!a.shared || aligned)) {
+        p.ext_ld = ext_width(a.r);
+        bf16_t* xe = static_cast<bf16_t*>(a.ext_ws);
+        bf16_t* we = xe + a.M * p.ext_ld;
+        p.Xext = xe;
+        p.Wext = we + (a.ext_ready && a.ext_side ? a.N * p.ext_ld : 0);
+        if (a.shared) p.Wext2 = we + a.N * p.ext_ld;
+        c.prep = !a.ext_ready;
     }
-    if (small) {
-        // the workspace was sized for this tiling's partials (gemm_bf16_num_workgroups with small_ok)
-        if (a.P && !p.Xext) return hipErrorInvalidValue;      // the small tiling takes the rank-r term as operands only
-        p.tiles_m = (int)((a.M + BT_SMALL - 1) / BT_SMALL);
-        p.tiles_n = (int)((a.N + BT_SMALL - 1) / BT_SMALL);
-        return launch_gemm_bf16_small(p, st);
+    if (a.sk_T && (!small || a.P || !gemm_bf16_fuses_sketch(a.M, a.N, a.r, a.large_tiles))) return hipErrorInvalidValue;
+    if (!small) {
+        c.kernel = aligned ? Kernel::aligned : Kernel::general;
+        return hipSuccess;
     }
-    if (mse) return launch_gemm_bf16_aligned(p, st);
+    // the workspace was sized for this tiling's partials (gemm_bf16_num_workgroups with small_ok)
+    if (a.P && !p.Xext) return hipErrorInvalidValue;      // the small tilings take the rank-r term as operands only
+    p.tiles_m = (int)((a.M + BT_SMALL - 1) / BT_SMALL);
+    p.tiles_n = (int)((a.N + BT_SMALL - 1) / BT_SMALL);
+    GemmItem& g = c.g;
+    g.X = p.X; g.W = p.W; g.ldx = p.ldx; g.ldw = p.ldw; g.M = p.M; g.N = p.N; g.K = p.K;
+    g.Xext = p.Xext; g.Wext = p.Wext; g.ext_ld = p.ext_ld;
+    g.target = p.target; g.ldt = p.ldt; g.partials = p.partials; g.Y = p.Y; g.ldy = p.ldy; g.clk = p.clk;
+    g.sk_T = p.sk_T; g.sk_mpad = p.sk_mpad; g.sk_partial = p.sk_partial;
+    c.out = (p.Y && p.loss_kind == AGZO_LOSS_NONE && p.y_dtype == AGZO_BF16) ? 1 : (!p.Y && p.loss_kind == AGZO_LOSS_MSE) ? 0 : -1;
+    // one output or one loss, tiles that lie inside the layer and whole slices: the pipelined kernel
+    c.kernel = (c.out >= 0 && gemm_bf16_mid_ok(g, c.out)) ? Kernel::mid : Kernel::small;
+    return hipSuccess;
+}
+
+hipError_t launch_one(const Choice& c, hipStream_t st) {
+    const GemmParams& p = c.p;
+    switch (c.kernel) {
+        case Kernel::mid: return launch_gemm_bf16_mid(&c.g, 1, c.out, p.target_dtype != AGZO_BF16, st);
+        case Kernel::small: return launch_gemm_bf16_small(p, st);
+        case Kernel::aligned: return launch_gemm_bf16_aligned(p, st);
+        case Kernel::general: break;
+    }
     const bool ce = p.loss_kind == AGZO_LOSS_CE;
     if (p.shared) return ce ? launch_variant<2, 2, true, 1>(p, st) : launch_variant<2, 2, true, 0>(p, st);
     return ce ? launch_variant<2, 2, false, 1>(p, st) : launch_variant<2, 2, false, 0>(p, st);
 }
+}  // namespace
+
+hipError_t launch_gemm_bf16_many(const GemmBf16Args* a, int n, hipStream_t st) {
+    Choice c[kBatchMax];
+    for (int b = 0; b < n; b += kBatchMax) {
+        const int nb = n - b < kBatchMax ? n - b : kBatchMax;
+        GemmExtArgs ext[kBatchMax];
+        int next = 0;
+        for (int i = 0; i < nb; ++i) {
+            const GemmBf16Args& g = a[b + i];
+            hipError_t e = choose(g, c[i]);
+            if (e != hipSuccess) return e;
+            if (c[i].prep && g.M > 0 && g.N > 0)
+                ext[next++] = GemmExtArgs{g.ext_ws, g.M, g.N, g.P, g.r, g.eps_signed, -2.f * g.eps_signed, g.shared, g.seed};
+        }
+        hipError_t e = launch_gemm_ext_prep_many(ext, next, st);
+        if (e != hipSuccess) return e;
+        // the mid kernel's forwards by what they produce: squared error of bf16 or fp32 targets, stored outputs
+        for (int kind = 0; kind < 3; ++kind) {
+            GemmItem g[kBatchMax];
+            int ng = 0;
+            for (int i = 0; i < nb; ++i)
+                if (c[i].kernel == Kernel::mid && !c[i].g.sk_T && (c[i].out == 1 ? 2 : c[i].p.target_dtype != AGZO_BF16 ? 1 : 0) == kind) g[ng++] = c[i].g;
+            if (ng == 0) continue;
+            e = launch_gemm_bf16_mid(g, ng, kind == 2 ? 1 : 0, kind == 1, st);
+            if (e != hipSuccess) return e;
+        }
+        for (int i = 0; i < nb; ++i) {
+            if (a[b + i].M == 0 || a[b + i].N == 0 || (c[i].kernel == Kernel::mid && !c[i].g.sk_T)) continue;
+            e = launch_one(c[i], st);
+            if (e != hipSuccess) return e;
+        }
+    }
+    return hipSuccess;
+}
+
+hipError_t launch_gemm_bf16(const GemmBf16Args& a, hipStream_t st) { return launch_gemm_bf16_many(&a, 1, st); }
 
 }  // namespace agzo

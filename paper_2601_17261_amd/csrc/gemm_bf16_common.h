@@ -53,6 +53,22 @@ struct GemmParams {
 constexpr int BT_SMALL = 128;
 hipError_t launch_gemm_bf16_small(const GemmParams& p, hipStream_t st);
 
+// one forward of a launch that takes several (gemm_bf16_mid.hip)
+struct GemmItem {
+    const bf16_t* X; const bf16_t* W;
+    int64_t ldx, ldw, M, N, K;
+    const bf16_t* Xext; const bf16_t* Wext; int ext_ld;   // prepared rank-r extension operands (NULL: none)
+    const void* target; int64_t ldt; double* partials;    // squared error: [ceil(M / 128) * ceil(N / 128)] partial sums
+    void* Y; int64_t ldy;                                  // stored bf16 output
+    int tiles_m, tiles_n;                                  // (set by the launch)
+    // fused range sketch (a launch of one problem; NULL: none): as in GemmParams
+    const bf16_t* sk_T; int64_t sk_mpad; float* sk_partial;
+    unsigned long long* clk;
+};
+// out 0: squared error (target_f32: of fp32 targets), 1: stored bf16 output
+bool gemm_bf16_mid_ok(const GemmItem& g, int out);
+hipError_t launch_gemm_bf16_mid(const GemmItem* a, int n, int out, bool target_f32, hipStream_t st);
+
 // kernel for tile-aligned layers (gemm_bf16_aligned.hip): M, N multiples of 256, d_in a multiple of 64 and >= 128,
 // 16-byte target / output accesses, the rank-r term as prepared operands; either the squared-error loss without a
 // stored Y (p.shared: f0, f+, f- in one pass, needs Wext2, partials [3][tiles]) or a bf16 Y without a loss

@@ -1,0 +1,367 @@
+// Forward GEMM of the bf16 path in 128 x 128 tiles, for layers that give too few 256 x 256 tiles to fill the chip:
+//     OUT = 0:  f = sum over the tile of (X W^T (+ eps (X B) G^T) - Y*)^2     (f0, f+, f- of Sec. 4.1; Eq. 7 factored)
+//     OUT = 1:  Y = X W^T (+ eps (X B) G^T) stored as bf16
+// for d_in a multiple of 64 and at least 128, d_out a multiple of 16, at least 128 tokens and outputs, 16-byte rows of target
+// or output, the rank-r extension as prepared operands.  Other shapes keep gemm_bf16_small.hip.
+//
+// One launch takes up to kBatchMax problems (the layers of a set, both signs of a perturbed evaluation): a 2048-token layer of
+// 1024 outputs is 128 tiles, half a chip, and a launch of its own costs 5.6 us before its first and after its last slice.  The
+// 21 forwards of a step over the seven 0.6B-sized layers at 2048 tokens: 540 us in 21 launches of gemm_bf16_small.hip, 340 in
+// 21 of this kernel, 194 (1015 TFLOP/s) in two; over the 4B-sized layers at 512 tokens: 1130, 775 and 335 us.
+//
+// Four waves of 64 x 64 (4 x 4 blocks of v_mfma_f32_16x16x32_bf16), two workgroups per compute unit: while one starts or ends a
+// tile or waits at its slice barrier the other multiplies.  80 KiB of LDS: three stages of W and two of X, 64-wide slices,
+// filled by direct global -> LDS loads in the swizzled layout and with the row permutation of gemm_bf16_aligned.hip.  A slice is
+// two blocks of 16 instructions: in the first the wave reads the fragments of the second half and requests the W of the slice
+// after next, into the stage the previous slice left; then everything but those four loads has landed and the waves meet; in
+// the second it reads the next slice's first fragments and requests the X of the slice after next.
+//
+// Rows and columns that do not fill a tile: the last tile of a direction starts at the last 128 rows instead of hanging over the
+// edge, so that no load needs a bound; the squared error leaves out what the tile before it has counted, a stored output is
+// stored twice with the same bits.
+#include "gemm_bf16_common.h"
+
+namespace agzo {
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+constexpr int MT = BT_SMALL;                    // tile edge
+constexpr int MTILE_BYTES = MT * BK * 2;        // one operand slice: 16 KiB
+constexpr int MSK_RP = 16;                      // sketch columns (r <= 16)
+constexpr int MSK_ROW = MT * 2 + 16;            // bytes per row of the Omega^T planes in LDS (padded against bank conflicts)
+constexpr int MSK_SMEM = 3 * MSK_RP * MSK_ROW;
+
+// LDS row m' of a 64-row group of the W tile holds W row mid_perm(m'): a lane's 4 x 4 values over four blocks of 16 outputs
+// are then 16 consecutive outputs (as in gemm_bf16_aligned.hip)
+__device__ __forceinline__ int mid_perm(int m) { return ((m >> 2) & 3) * 16 + (m >> 4) * 4 + (m & 3); }
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t mid_rsrc(const bf16_t* base) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, (int)0xFFFFFFFFu, 0x00020000);
+}
+
+// SK: also emits the range sketch of Alg. 1 from the X slices in LDS, as gemm_bf16_small.hip describes; the planes of Omega^T
+// take another 12.75 KiB of LDS, which leaves one workgroup per compute unit
+// DEEP: five stages of both operands and one workgroup per compute unit, for launches that give a compute unit no second
+// workgroup anyway: 16 us a launch against 17.1 on the 0.6B-sized layers, 35.8 against 39.3 at 512 tokens on the 4B-sized ones
+// (with two workgroups for every compute unit it is the slower one, 42.6 against 34.7 us at 8192 x 2048 -> 1024).  Same bits
+template <int OUT, bool T_F32, bool SK, bool DEEP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_bf16_mid_kernel(const KBatch<GemmItem> tb) {
+    constexpr int WS = DEEP ? 5 : 3, XS = DEEP ? 5 : 2;      // stages
+    constexpr int AHEAD = DEEP ? 4 : 2;                       // slices between a request and its use
+    constexpr int X_BASE = WS * MTILE_BYTES;
+    static_assert(!(SK && DEEP), "the sketch planes share the LDS of the shallow ring");
+    extern __shared__ __align__(16) char smem[];
+    uint32_t bx_, by_;
+    const GemmItem& p = tb.a[kbatch_find(tb, bx_, by_)];
+    const int tid = threadIdx.x, lane = tid & 63;
+    if (p.clk && bx_ == 0 && tid == 0) { p.clk[0] = __builtin_readcyclecounter(); p.clk[1] = wall_clock64(); }
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wa = wave >> 1, wb = wave & 1;       // wa splits the outputs, wb the tokens
+    const int lc = lane & 15, lg = lane >> 4;
+
+    // workgroup -> tile: ids are dealt round-robin over the 8 XCDs; each XCD takes a contiguous run of the problem's tiles, in
+    // bands of eight token tiles per output tile
+    const int count = p.tiles_m * p.tiles_n, per = count / 8;
+    int lin = (int)bx_;
+    if (lin < per * 8) lin = (lin % 8) * per + lin / 8;
+    constexpr int BAND = 8;
+    const int band = lin / (BAND * p.tiles_n), first = band * BAND;
+    const int rows = min(BAND, p.tiles_m - first), in_band = lin - band * BAND * p.tiles_n;
+    const int tm = __builtin_amdgcn_readfirstlane(first + in_band % rows), tn = __builtin_amdgcn_readfirstlane(in_band / rows);
+    const int64_t m0 = min((int64_t)tm * MT, p.M - MT), n0 = min((int64_t)tn * MT, p.N - MT);
+
+    const bool has_ext = p.Xext != nullptr;
+    const bf16_t *xb = p.X + m0 * p.ldx, *wb_ = p.W + n0 * p.ldw;
+    const bf16_t *xb2 = has_ext ? p.Xext + m0 * p.ext_ld : xb, *wb2 = has_ext ? p.Wext + n0 * p.ext_ld : wb_;
+    const int row0 = 8 * wave + (lane >> 3);
+    const int chunk0 = (lane & 7) ^ ((row0 >> 1) & 7);
+    const int vx = (int)(((int64_t)row0 * p.ldx + chunk0 * 8) * 2), vw = (int)(((int64_t)mid_perm(row0) * p.ldw + chunk0 * 8) * 2);
+    const int vx2 = (row0 * p.ext_ld + chunk0 * 8) * 2, vw2 = (mid_perm(row0) * p.ext_ld + chunk0 * 8) * 2;
+    const int gsx = (int)(64 * p.ldx), gsw = (int)(64 * p.ldw), gs2 = 64 * p.ext_ld;   // bytes between row groups
+    const int nfull = (int)(p.K / BK), npipe = nfull + (has_ext ? p.ext_ld / BK : 0);
+    typedef __attribute__((address_space(3))) void* lptr_t;
+
+    // ---- accumulators <- minus the target tile, or zero ----
+    floatx4 acc[4][4];
+    uint4 traw[T_F32 ? 16 : 8];
+    if constexpr (OUT == 0) {
+#pragma unroll
+        for (int J = 0; J < 4; ++J) {
+            const int64_t row = m0 + wb * 64 + J * 16 + lc, col = n0 + wa * 64 + lg * 16;
+            const uint4* src = T_F32 ? reinterpret_cast<const uint4*>(reinterpret_cast<const float*>(p.target) + row * p.ldt + col)
+                                     : reinterpret_cast<const uint4*>(reinterpret_cast<const bf16_t*>(p.target) + row * p.ldt + col);
+#pragma unroll
+            for (int q = 0; q < (T_F32 ? 4 : 2); ++q) traw[J * (T_F32 ? 4 : 2) + q] = src[q];
+        }
+    }
+
+    // ---- fused range sketch: this tile contracts its tokens for the d_in slices tn, tn + tiles_n, ... ----
+    char* const Ts = smem + (WS + XS) * MTILE_BYTES;              // Omega^T planes [3][16][128 tokens]
+    int sk_next = tn;
+    if constexpr (SK) {
+        for (int e = tid; e < 3 * MSK_RP * MT; e += 256) {
+            const int row = e / MT, t = e % MT;
+            // (tokens that the tile before this one has covered add nothing)
+            *reinterpret_cast<bf16_t*>(Ts + row * MSK_ROW + 2 * t) = (m0 + t >= (int64_t)tm * MT) ? p.sk_T[(int64_t)row * p.sk_mpad + m0 + t] : (bf16_t)0;
+        }
+    }
+    auto sketch = [&](int buf, int it) __attribute__((always_inline)) {
+        const int n = lane & 15, g = lane >> 4, c = n & 7;
+        const uint32_t sel = (n >> 3) ? 0x07060302u : 0x05040100u;
+        floatx4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int tc = 0; tc < 4; ++tc) {
+            uint32_t wv[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                wv[i] = *reinterpret_cast<const uint32_t*>(smem + X_BASE + buf * MTILE_BYTES + lds_off(32 * tc + 8 * g + i, c) + 4 * wave);
+            union { uint4 u; bf16x8 v; } b, a;
+            b.u = make_uint4(__builtin_amdgcn_perm(wv[1], wv[0], sel), __builtin_amdgcn_perm(wv[3], wv[2], sel),
+                             __builtin_amdgcn_perm(wv[5], wv[4], sel), __builtin_amdgcn_perm(wv[7], wv[6], sel));
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) {
+                a.u = *reinterpret_cast<const uint4*>(Ts + (pl * MSK_RP + n) * MSK_ROW + (32 * tc + 8 * g) * 2);
+                s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, s, 0, 0, 0);
+            }
+        }
+        const int64_t f = (int64_t)it * BK + 8 * c + 2 * wave + (n >> 3);
+        *reinterpret_cast<float4*>(p.sk_partial + ((int64_t)tm * p.K + f) * MSK_RP + 4 * g) = make_float4(s[0], s[1], s[2], s[3]);
+    };
+
+    // ---- source of a slice: d_in slices, then the extension operands ----
+    __amdgpu_buffer_rsrc_t src_rsx = mid_rsrc(xb), src_rsw = mid_rsrc(wb_);
+    int src_so = 0, src_vxt[4], src_vwt[4];
+    auto set_offsets = [&](int v0x, int gx, int v0w, int gw) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) { src_vxt[t] = v0x + t * gx; src_vwt[t] = v0w + (t >> 1) * (2 * gw) + (t & 1) * (gw >> 2); }
+    };
+    set_offsets(vx, gsx, vw, gsw);
+    // past the last slice: that slice once more, into a stage nobody reads
+    auto select_slice = [&](int kt) __attribute__((always_inline)) {
+        const bf16_t *cxb = xb, *cwb = wb_, *cxb2 = xb2, *cwb2 = wb2;
+        const int cvx = vx, cvw = vw, cvx2 = vx2, cvw2 = vw2, cgsx = gsx, cgsw = gsw, cgs2 = gs2;
+        kt = min(kt, npipe - 1);
+        const bool e = kt >= nfull;
+        const bf16_t* xs = e ? cxb2 : cxb;
+        const bf16_t* ws = e ? cwb2 : cwb;
+        const int svx = e ? cvx2 : cvx, svw = e ? cvw2 : cvw, sgx = e ? cgs2 : cgsx, sgw = e ? cgs2 : cgsw;
+        src_rsx = mid_rsrc(xs);   src_rsw = mid_rsrc(ws);
+        set_offsets(svx, sgx, svw, sgw);
+        src_so = (e ? kt - nfull : kt) * (BK * 2);
+    };
+    auto dma_x = [&](int buf, int t) __attribute__((always_inline)) {
+        char* dst = smem + X_BASE + buf * MTILE_BYTES + wave * 1024 + t * 4096;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(src_rsx, (lptr_t)dst, 16, src_vxt[t], src_so, 0, 0);
+    };
+    auto dma_w = [&](int buf, int t) __attribute__((always_inline)) {
+        char* dst = smem + buf * MTILE_BYTES + wave * 1024 + t * 4096;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(src_rsw, (lptr_t)dst, 16, src_vwt[t], src_so, 0, 0);
+    };
+#pragma unroll
+    for (int sl = 0; sl < AHEAD; ++sl) {
+        select_slice(sl);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) dma_w(sl, t);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) dma_x(sl, t);
+    }
+
+#pragma unroll
+    for (int J = 0; J < 4; ++J) {
+        if constexpr (OUT == 0) {
+            float v[16];
+            if (T_F32) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const uint4 t = traw[J * 4 + q];
+                    v[4 * q] = -__uint_as_float(t.x); v[4 * q + 1] = -__uint_as_float(t.y);
+                    v[4 * q + 2] = -__uint_as_float(t.z); v[4 * q + 3] = -__uint_as_float(t.w);
+                }
+            } else {
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const uint4 t = traw[J * 2 + q];
+                    const uint32_t w[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        v[8 * q + 2 * u] = __uint_as_float((w[u] << 16) + 0x80000000u);
+                        v[8 * q + 2 * u + 1] = __uint_as_float((w[u] & 0xFFFF0000u) ^ 0x80000000u);
+                    }
+                }
+            }
+#pragma unroll
+            for (int I = 0; I < 4; ++I) acc[I][J] = floatx4{v[4 * I], v[4 * I + 1], v[4 * I + 2], v[4 * I + 3]};
+        } else {
+#pragma unroll
+            for (int I = 0; I < 4; ++I) acc[I][J] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+
+    // ---- multiply: fragment of block row I (W) or token block J (X), k step ks: lane (lc, lg) reads chunk 4 ks + lg of row 16 I + lc
+    int aoff[2], boff[2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        aoff[ks] = lds_off(wa * 64 + lc, ks * 4 + lg);
+        boff[ks] = X_BASE + lds_off(wb * 64 + lc, ks * 4 + lg);
+    }
+    bf16x8 aw[2][4], bx[2][4];
+    auto read_w = [&](int wbuf, int ks, int I) __attribute__((always_inline)) {
+        aw[ks][I] = *reinterpret_cast<const bf16x8*>(smem + wbuf * MTILE_BYTES + aoff[ks] + I * 2048);
+    };
+    auto read_x = [&](int xbuf, int ks, int J) __attribute__((always_inline)) {
+        bx[ks][J] = *reinterpret_cast<const bf16x8*>(smem + xbuf * MTILE_BYTES + boff[ks] + J * 2048);
+    };
+    // (written out with the accumulator tied to its registers, as in gemm_bf16_aligned.hip)
+    auto mfma1 = [&](int ks, int I, int J) __attribute__((always_inline)) {
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[I][J]) : "v"(aw[ks][I]), "v"(bx[ks][J]));
+    };
+    // 16 instructions of k step KS; rides along: the eight fragments of k step 1 - KS (of W stage rw, X stage rx), one per other
+    // instruction, and four direct loads (LOADS 1: W, 2: X)
+    auto block = [&](auto KS, int rw, int rx, auto LOADS, int lbuf) __attribute__((always_inline)) {
+        constexpr int ks = decltype(KS)::value, loads = decltype(LOADS)::value;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            mfma1(ks, q & 3, q >> 2);
+            // the first token block and all block rows come first: the next block starts with them
+            if (!(q & 1)) {
+                const int f = q >> 1;
+                if (f == 0) read_x(rx, ks ^ 1, 0);
+                else if (f < 5) read_w(rw, ks ^ 1, f - 1);
+                else read_x(rx, ks ^ 1, f - 4);
+            }
+            if ((q & 3) == 1) {
+                if (loads == 1) dma_w(lbuf, q >> 2);
+                if (loads == 2) dma_x(lbuf, q >> 2);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // (the instructions that start from the accumulators' first values read registers that vector instructions have just written)
+    asm volatile("s_nop 7");
+    // slice 0 has landed
+    constexpr int W0 = 8 * (AHEAD - 1), W1 = 8 * (AHEAD - 2) + 4;
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (W0 & 15) | ((W0 >> 4) << 14));
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int I = 0; I < 4; ++I) { read_w(0, 0, I); read_x(0, 0, I); }
+    int wcur = 0, xcur = 0, wput = (WS == AHEAD) ? 0 : AHEAD, xput = (XS == AHEAD) ? 0 : AHEAD;    // stages of this slice and of slice kt + AHEAD
+    for (int kt = 0; kt < npipe; ++kt) {
+        if (__builtin_expect(kt + AHEAD >= nfull, 0)) select_slice(kt + AHEAD);
+        else src_so = (kt + AHEAD) * (BK * 2);
+        block(IC<0>{}, wcur, xcur, IC<1>{}, wput);
+        if constexpr (SK) {
+            if (kt == sk_next && kt < nfull) { sketch(xcur, kt); sk_next += p.tiles_n; }
+            __builtin_amdgcn_s_waitcnt(0x0070);              // (its stores count as well)
+        }
+        // lgkmcnt(0) and all but the youngest loads: the whole next slice has landed (loads return in the order issued), this
+        // wave's reads of the current one are done
+        __builtin_amdgcn_s_waitcnt(0x0070 | (W1 & 15) | ((W1 >> 4) << 14));
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        wcur = (wcur == WS - 1) ? 0 : wcur + 1;
+        xcur = (xcur == XS - 1) ? 0 : xcur + 1;
+        block(IC<1>{}, wcur, xcur, IC<2>{}, xput);
+        wput = (wput == WS - 1) ? 0 : wput + 1;
+        xput = (xput == XS - 1) ? 0 : xput + 1;
+    }
+    // 24 wait states before the first read of a result: the compiler does not know of the instructions above
+    asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7");
+    __builtin_amdgcn_s_waitcnt(0x0F70);                      // the slices fetched past the end
+    const int64_t row_new = (int64_t)tm * MT, col_new = (int64_t)tn * MT;
+    if constexpr (OUT == 1) {
+#pragma unroll
+        for (int J = 0; J < 4; ++J) {
+            const int64_t row = m0 + wb * 64 + J * 16 + lc, col = n0 + wa * 64 + lg * 16;
+            uint32_t w[8];
+#pragma unroll
+            for (int I = 0; I < 4; ++I) {
+                w[2 * I] = pack_bf16x2(acc[I][J][0], acc[I][J][1]);
+                w[2 * I + 1] = pack_bf16x2(acc[I][J][2], acc[I][J][3]);
+            }
+            uint4* dst = reinterpret_cast<uint4*>(reinterpret_cast<bf16_t*>(p.Y) + row * p.ldy + col);
+            dst[0] = make_uint4(w[0], w[1], w[2], w[3]);
+            dst[1] = make_uint4(w[4], w[5], w[6], w[7]);
+        }
+    } else {
+        // squares in fp32 four at a time, summed in fp64; lanes, then waves, in a fixed order
+        double part = 0.0;
+        const bool col_in = n0 + wa * 64 + lg * 16 >= col_new;
+#pragma unroll
+        for (int J = 0; J < 4; ++J) {
+            const bool in = col_in && m0 + wb * 64 + J * 16 + lc >= row_new;
+#pragma unroll
+            for (int I = 0; I < 4; ++I) {
+                float s4 = 0.f;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s4 = fmaf(acc[I][J][e], acc[I][J][e], s4);
+                part += in ? (double)s4 : 0.0;
+            }
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
+        double* red = reinterpret_cast<double*>(smem);
+        __syncthreads();                                     // every wave's fetches past the end have landed
+        if (lane == 0) red[wave] = part;
+        __syncthreads();
+        if (tid == 0) p.partials[(int64_t)tm * p.tiles_n + tn] = (red[0] + red[1]) + (red[2] + red[3]);
+    }
+    if (p.clk && bx_ == 0 && tid == 0) { p.clk[2] = __builtin_readcyclecounter(); p.clk[3] = wall_clock64(); }
+}
+
+template <int OUT, bool T_F32, bool SK, bool DEEP>
+static hipError_t launch_mid_ring(const KBatch<GemmItem>& tb, unsigned blocks, hipStream_t st) {
+    const int smem = (DEEP ? 10 : 5) * MTILE_BYTES + (SK ? MSK_SMEM : 0);
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_bf16_mid_kernel<OUT, T_F32, SK, DEEP>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    hipLaunchKernelGGL((gemm_bf16_mid_kernel<OUT, T_F32, SK, DEEP>), dim3(blocks), dim3(256), smem, st, tb);
+    return hipGetLastError();
+}
+template <int OUT, bool T_F32>
+static hipError_t launch_mid_variant(const KBatch<GemmItem>& tb, unsigned blocks, bool sk, hipStream_t st) {
+    // (256: a workgroup per compute unit)
+    if (sk) return launch_mid_ring<OUT, T_F32, true, false>(tb, blocks, st);
+    return blocks <= 256 ? launch_mid_ring<OUT, T_F32, false, true>(tb, blocks, st) : launch_mid_ring<OUT, T_F32, false, false>(tb, blocks, st);
+}
+
+bool gemm_bf16_mid_ok(const GemmItem& g, int out) {
+    const bool shape = g.M >= MT && g.N >= MT && g.N % 16 == 0 && g.K % BK == 0 && g.K >= 2 * BK;
+    if (out == 1) return shape && g.Y && g.ldy % 8 == 0 && (reinterpret_cast<uintptr_t>(g.Y) & 15) == 0;
+    return shape && g.target && g.ldt % 8 == 0 && (reinterpret_cast<uintptr_t>(g.target) & 15) == 0;
+}
+
+hipError_t launch_gemm_bf16_mid(const GemmItem* a, int n, int out, bool target_f32, hipStream_t st) {
+    if (n < 0 || n > kBatchMax) return hipErrorInvalidValue;
+    KBatch<GemmItem> tb;
+    tb.n = 0;
+    uint64_t blocks = 0;
+    int order[kBatchMax];
+    for (int i = 0; i < n; ++i) {
+        if (!gemm_bf16_mid_ok(a[i], out)) return hipErrorInvalidValue;
+        int at = i;             // deepest first, so that the launch does not end on a few long tiles
+        for (; at > 0 && a[order[at - 1]].K < a[i].K; --at) order[at] = order[at - 1];
+        order[at] = i;
+    }
+    for (int i = 0; i < n; ++i) {
+        GemmItem g = a[order[i]];
+        g.tiles_m = (int)((g.M + MT - 1) / MT);
+        g.tiles_n = (int)((g.N + MT - 1) / MT);
+        tb.first[tb.n] = (uint32_t)blocks;
+        tb.gx[tb.n] = (uint32_t)((int64_t)g.tiles_m * g.tiles_n);
+        blocks += tb.gx[tb.n];
+        tb.a[tb.n++] = g;
+    }
+    if (tb.n == 0) return hipSuccess;
+    if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    const bool sk = a[0].sk_T != nullptr;
+    if (sk && (n != 1 || !a[0].sk_partial || a[0].sk_mpad < (int64_t)tb.a[0].tiles_m * MT)) return hipErrorInvalidValue;
+    if (out == 1) return launch_mid_variant<1, false>(tb, (unsigned)blocks, sk, st);
+    return target_f32 ? launch_mid_variant<0, true>(tb, (unsigned)blocks, sk, st) : launch_mid_variant<0, false>(tb, (unsigned)blocks, sk, st);
+}
+
+}  // namespace agzo
