@@ -142,7 +142,7 @@ Plan make_plan(const agzo_layer& L, bool need_ybuf, bool ce = false, bool shared
     p.off_qr = take(qr_workspace_bytes(L.d_in, L.r));
     {
         size_t part = (size_t)n_gemm * 3;                                          // MSE: one double per tile and phase
-        const size_t ce_part = (size_t)2 * L.n_tokens + 6 * ((L.n_tokens + 255) / 256);   // CE: (sum, count) pairs
+        const size_t ce_part = std::max((size_t)2 * L.n_tokens, (size_t)6 * ((L.n_tokens + kCeCombineTokens - 1) / kCeCombineTokens));   // CE: (sum, count) pairs
         if (ce && ce_part > part) part = ce_part;
         p.part_count = part;
         p.off_part = take(part * 8);
@@ -355,10 +355,10 @@ int op_forward(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* W,
     const bool ce = has_loss && loss->kind == AGZO_LOSS_CE;
     // squared error: a step keeps the tile partials of its forwards side by side (slot = 0, 1, 2) and finishes them in
     // one launch.  Cross-entropy: every loss is finished by launches of its own right behind the forward, so all of
-    // them use the region from its start: (sum, count) per token (fp32 storage) or per 256 tokens and phase (bf16).
+    // them use the region from its start: (sum, count) per token (fp32 storage) or per kCeCombineTokens tokens and phase (bf16).
     {
         const size_t at = ce ? 0 : (size_t)part_slot * p.n_part;
-        const size_t nblk = (size_t)((L.n_tokens + 255) / 256);
+        const size_t nblk = (size_t)((L.n_tokens + kCeCombineTokens - 1) / kCeCombineTokens);
         const size_t need = !has_loss ? 0 : ce ? (L.dtype == AGZO_BF16 ? 2 * nblk * (shared ? 3 : 1) : 2 * (size_t)L.n_tokens)
                                                : (size_t)p.n_part * (shared ? 3 : 1);
         if (at + need > p.part_count)

@@ -260,6 +260,8 @@ hipError_t launch_update_many(const UpdateDesc* d, int n, int nk, void* workspac
 // cross-entropy from the GEMM's per-chunk softmax statistics: out[ph] = mean over rows with target >= 0 of
 // log(sum exp) - logit[target];  ms: float2 [nphase][nchunk][M], tl: float [nphase][M]
 int gemm_bf16_ce_chunks(int64_t N);
+// tokens per (sum, count) pair of the scratch, 2 doubles a pair and phase
+constexpr int kCeCombineTokens = 16;
 hipError_t launch_ce_combine(const void* ms, const float* tl, const int32_t* target, int64_t M, int64_t N, int nchunk,
                              int nphase, double* scratch, double* out, hipStream_t st);
 // cross-entropy of stored fp32 logits Y [M][N] (fp32-storage path): out[0] as above

@@ -75,37 +75,64 @@ __global__ __launch_bounds__(256) void finish_two_point_many_kernel(const Finish
 }
 
 // ---- cross-entropy -----------------------------------------------------------------------------
-// one thread per token: merge the chunk statistics, loss_t = log(sum exp) - logit[target]; block sums
-// of (loss, count) go to scratch[2*block], the last stage divides.
+// Merge the chunk statistics, loss_t = log(sum exp) - logit[target]; block sums of (loss, count) go to scratch[2*block], the
+// last stage divides.  Bound by latency (16 MB for 8192 tokens of 250 chunks): 16 threads share a token and walk its chunks
+// CE_FLIGHT loads at a time, sixteen tokens (128-byte runs) to a workgroup.  With a thread per token, 256 to a workgroup and two
+// walks of one load at a time, it took 106 us for any number of tokens; this takes some 13 us for 385 or 3001.
+constexpr int CE_TOK = kCeCombineTokens, CE_LANES = 256 / CE_TOK, CE_FLIGHT = 8;
 __global__ __launch_bounds__(256) void ce_combine_kernel(const float2* __restrict__ ms, const float* __restrict__ tl,
                                                          const int32_t* __restrict__ target, int64_t M, int64_t N,
                                                          int nchunk, double* __restrict__ scratch) {
-    __shared__ double rs[256], rc[256];
-    const int tid = threadIdx.x;
+    __shared__ double rm[CE_LANES][CE_TOK], rs[CE_LANES][CE_TOK];
+    const int tid = threadIdx.x, tok = tid % CE_TOK, part = tid / CE_TOK;
     const int ph = blockIdx.y;
-    const int64_t t = (int64_t)blockIdx.x * 256 + tid;
-    double loss = 0.0, cnt = 0.0;
-    if (t < M && target[t] >= 0 && target[t] < N) {   // an id outside the layer's outputs has no logit: skipped
+    const int64_t t = (int64_t)blockIdx.x * CE_TOK + tok;
+    // an id outside the layer's outputs has no logit: skipped
+    const int tgt = t < M ? target[t] : -1;
+    const bool counted = tgt >= 0 && tgt < N;
+    double mx = -INFINITY, s = 0.0;
+    if (counted) {
         const float2* m = ms + (int64_t)ph * nchunk * M + t;
-        float mx = -INFINITY;
-        for (int c = 0; c < nchunk; ++c) mx = fmaxf(mx, m[(int64_t)c * M].x);
-        double s = 0.0;
-        for (int c = 0; c < nchunk; ++c) {
-            const float2 v = m[(int64_t)c * M];
-            s += (double)v.y * exp((double)v.x - (double)mx);
+        for (int c0 = part; c0 < nchunk; c0 += CE_LANES * CE_FLIGHT) {
+            float2 v[CE_FLIGHT];
+#pragma unroll
+            for (int u = 0; u < CE_FLIGHT; ++u) {
+                const int c = c0 + u * CE_LANES;
+                v[u] = c < nchunk ? m[(int64_t)c * M] : make_float2(-INFINITY, 0.f);
+            }
+            float top = v[0].x;                                // (the first of the eight exists)
+#pragma unroll
+            for (int u = 1; u < CE_FLIGHT; ++u) top = fmaxf(top, v[u].x);
+            const double mn = fmax(mx, (double)top);
+            // nothing to move to a new maximum while there is no sum yet (and no -inf - -inf)
+            s = s > 0.0 ? s * exp(mx - mn) : s;
+#pragma unroll
+            for (int u = 0; u < CE_FLIGHT; ++u)
+                if (v[u].y != 0.f) s += (double)v[u].y * exp((double)v[u].x - mn);      // (0: a chunk past the last column, maximum -inf)
+            mx = mn;
         }
-        loss = log(s) + (double)mx - (double)tl[(int64_t)ph * M + t];
+    }
+    rm[part][tok] = mx;
+    rs[part][tok] = s;
+    __syncthreads();
+    if (part != 0) return;
+    double loss = 0.0, cnt = 0.0;
+    if (counted) {
+        for (int l = 1; l < CE_LANES && l < nchunk; ++l) mx = fmax(mx, rm[l][tok]);
+        s = 0.0;
+        for (int l = 0; l < CE_LANES && l < nchunk; ++l) s += rs[l][tok] * exp(rm[l][tok] - mx);
+        loss = log(s) + mx - (double)tl[(int64_t)ph * M + t];
         cnt = 1.0;
     }
-    rs[tid] = loss; rc[tid] = cnt;
-    __syncthreads();
-    for (int k = 128; k > 0; k >>= 1) {
-        if (tid < k) { rs[tid] += rs[tid + k]; rc[tid] += rc[tid + k]; }
-        __syncthreads();
+    // (the first CE_TOK lanes of wave 0)
+#pragma unroll
+    for (int off = CE_TOK / 2; off > 0; off >>= 1) {
+        loss += __shfl_xor(loss, off);
+        cnt += __shfl_xor(cnt, off);
     }
     if (tid == 0) {
-        scratch[((int64_t)ph * gridDim.x + blockIdx.x) * 2] = rs[0];
-        scratch[((int64_t)ph * gridDim.x + blockIdx.x) * 2 + 1] = rc[0];
+        scratch[((int64_t)ph * gridDim.x + blockIdx.x) * 2] = loss;
+        scratch[((int64_t)ph * gridDim.x + blockIdx.x) * 2 + 1] = cnt;
     }
 }
 
@@ -128,7 +155,7 @@ __global__ __launch_bounds__(256) void ce_finish_kernel(const double* __restrict
 
 hipError_t launch_ce_combine(const void* ms, const float* tl, const int32_t* target, int64_t M, int64_t N, int nchunk,
                              int nphase, double* scratch, double* out, hipStream_t st) {
-    const int nblk = (int)((M + 255) / 256);
+    const int nblk = (int)((M + CE_TOK - 1) / CE_TOK);
     hipLaunchKernelGGL(ce_combine_kernel, dim3(nblk, nphase), dim3(256), 0, st, reinterpret_cast<const float2*>(ms), tl,
                        target, M, N, nchunk, scratch);
     hipLaunchKernelGGL(ce_finish_kernel, dim3(nphase), dim3(256), 0, st, scratch, nblk, out);
