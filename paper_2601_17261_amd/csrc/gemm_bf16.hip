@@ -40,8 +40,8 @@ int gemm_bf16_num_workgroups(int64_t M, int64_t N, bool small_ok) {
 
 // WA x WB waves: WA splits the 256 outputs, WB splits the 256 tokens
 // EPI selects the epilogue compiled into the kernel: 0 = general (stores, squared error, any bounds), 1 = cross-entropy
-// statistics.  (Tile-aligned layers with the squared-error loss and no stored Y, or a stored bf16 Y and no loss, take the kernel of
-// gemm_bf16_aligned.hip.)
+// statistics.  (What gemm_bf16_aligned.hip has an output form for and a tile fits into goes there: left here are fp32 outputs, an
+// output beside a loss, the shared cross-entropy and layers below a tile or two slices.)
 template <int WA, int WB, bool SHARED, int EPI>
 __global__ __launch_bounds__(64 * WA * WB) void gemm_bf16_kernel(GemmParams p) {
     constexpr bool CE = (EPI == 1);
@@ -702,14 +702,14 @@ hipError_t choose(const GemmBf16Args& a, Choice& c) {
     p.clk = a.clk;
     p.sk_T = a.sk_T; p.sk_mpad = a.sk_T ? a.sk_mpad : 0; p.sk_partial = a.sk_T ? a.sk_partial : nullptr;
     const bool small = small_shape(a.M, a.N) && !a.large_tiles && !a.shared && p.loss_kind != AGZO_LOSS_CE;
-    // the kernel of gemm_bf16_aligned.hip takes tile-aligned layers: squared error without a stored Y (also in
-    // shared-forward mode), the cross-entropy statistics without a stored Y, or a stored bf16 Y without a loss
-    const bool aligned = !small && vec && a.M % BT == 0 && a.N % BT == 0 && a.K % BK == 0 && a.K >= 2 * BK && (!a.P || a.ext_ws) &&
-                         ((a.loss.kind == AGZO_LOSS_MSE && !a.Y) || (a.loss.kind == AGZO_LOSS_CE && !a.Y && !a.shared) ||
-                          (a.loss.kind == AGZO_LOSS_NONE && a.Y && a.y_dtype == AGZO_BF16 && !a.shared));
+    // the persistent kernel of gemm_bf16_aligned.hip: squared error without a stored Y (also in shared-forward mode), the
+    // cross-entropy statistics without a stored Y, or a stored bf16 Y without a loss, where a tile fits into the layer
+    const bool persistent = !small && a.M >= BT && a.N >= BT && a.K >= 2 * BK && (!a.P || a.ext_ws) &&
+                            ((a.loss.kind == AGZO_LOSS_MSE && !a.Y) || (a.loss.kind == AGZO_LOSS_CE && !a.Y && !a.shared) ||
+                             (a.loss.kind == AGZO_LOSS_NONE && a.Y && a.y_dtype == AGZO_BF16 && !a.shared));
     p.Xext = nullptr; p.Wext = nullptr; p.Wext2 = nullptr; p.ext_ld = 0;
     c.prep = false;
-    if (a.P && a.ext_ws && (!a.shared || aligned)) {
+    if (a.P && a.ext_ws && (!a.shared || persistent)) {
         p.ext_ld = ext_width(a.r);
         bf16_t* xe = static_cast<bf16_t*>(a.ext_ws);
         bf16_t* we = xe + a.M * p.ext_ld;
@@ -720,7 +720,7 @@ hipError_t choose(const GemmBf16Args& a, Choice& c) {
     }
     if (a.sk_T && (!small || a.P || !gemm_bf16_fuses_sketch(a.M, a.N, a.r, a.large_tiles))) return hipErrorInvalidValue;
     if (!small) {
-        c.kernel = aligned ? Kernel::aligned : Kernel::general;
+        c.kernel = persistent ? Kernel::aligned : Kernel::general;
         return hipSuccess;
     }
     // the workspace was sized for this tiling's partials (gemm_bf16_num_workgroups with small_ok)
@@ -733,7 +733,7 @@ hipError_t choose(const GemmBf16Args& a, Choice& c) {
     g.target = p.target; g.ldt = p.ldt; g.partials = p.partials; g.Y = p.Y; g.ldy = p.ldy; g.clk = p.clk;
     g.sk_T = p.sk_T; g.sk_mpad = p.sk_mpad; g.sk_partial = p.sk_partial;
     c.out = (p.Y && p.loss_kind == AGZO_LOSS_NONE && p.y_dtype == AGZO_BF16) ? 1 : (!p.Y && p.loss_kind == AGZO_LOSS_MSE) ? 0 : -1;
-    // one output or one loss, tiles that lie inside the layer and whole slices: the pipelined kernel
+    // one output or one loss and tiles that lie inside the layer: the pipelined kernel
     c.kernel = (c.out >= 0 && gemm_bf16_mid_ok(g, c.out)) ? Kernel::mid : Kernel::small;
     return hipSuccess;
 }

@@ -1,12 +1,19 @@
-// Forward GEMM for tile-aligned layers, the case the benchmark configurations run:
+// Forward GEMM in 256 x 256 tiles, the kernel of the benchmark configurations:
 //     OUT = 0:  f = sum over the tile of (X W^T (+ eps (X B) G^T) - Y*)^2     (f0, f+, f- of Sec. 4.1; Eq. 7 factored)
 //     OUT = 1:  Y = X W^T (+ eps (X B) G^T) stored as bf16                     (a layer inside a model, Alg. 2)
 //     OUT = 2:  the same logits never stored: per token and 128-column chunk their maximum and the sum of exponentials
 //               around it, and the target's logit (token cross-entropy of a model's last layer; loss.hip combines them)
 // Same tile, tile layout in LDS and direct global -> LDS operand loads as gemm_bf16.hip (256 x 256 tile, four waves of
-// 128 x 128, 64-wide K slices), but a kernel of its own with one straight path and nothing else compiled in: M and N
-// multiples of 256, d_in a multiple of 64 and at least 128, 16-byte aligned target / output rows, the rank-r extension
-// as prepared operands.
+// 128 x 128, 64-wide K slices), but a kernel of its own with one straight path and nothing else compiled in: M and N of
+// at least 256, d_in of at least 128, the rank-r extension as prepared operands.
+//
+// RAGGED = false takes tile-aligned layers: M and N multiples of 256, d_in a multiple of 64, 16-byte aligned target / output
+// rows.  RAGGED = true takes the others.  The last tile of a direction starts at the last 256 rows (or columns) instead of
+// hanging over the edge, so no load needs a bound; squared error and softmax statistics leave out what the tile before it has
+// counted, stored outputs are stored twice with the same bits.  A last slice that d_in does not fill gets a descriptor with a
+// range, and the lanes past d_in an offset beyond it: they load zeros.  gemm_bf16.hip, which bounded every access and drained
+// its loads at every slice, ran 3001 x 2560 -> 9728 (both signs and none, with the smaller projections beside it) at 820
+// TFLOP/s and the cross-entropy head 3001 x 2048 -> 32000 at 937; this kernel at 1240 and 1290.
 //
 // Matrix instruction.
 // v_mfma_f32_16x16x32_bf16, 8 x 8 blocks per wave, two k steps of 32 per slice, where gemm_bf16.hip has 4 x 4 blocks of
@@ -36,7 +43,9 @@
 // Y - Y* and the epilogue is a sum of squares of registers with no memory access.  (Reading the target in the epilogue
 // left the matrix cores idle for 15 - 18 % of a tile: every workgroup asks for its 128 KiB at the same moment and
 // waits out the latency, and the staging registers spilled.)  All evaluations of a step start from the same -Y*, so
-// f+ and f- still share bit-identical accumulators up to the rank-r slices.
+// f+ and f- still share bit-identical accumulators up to the rank-r slices.  With RAGGED the target is subtracted behind the
+// last slice instead: these layers' losses were that far from their 64-bit values (4e-10 of them; with the accumulators
+// starting at minus the target 5e-9, as the sums' rounding then follows the sign of the residual), and they stay there.
 //
 // Persistent workgroups.
 // One workgroup per compute unit walks through a list of tiles (its LDS and accumulators leave no room for a second one,
@@ -65,9 +74,9 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 // 16 g + 4 t + e of the group: a lane's 4 x 4 values over four neighbouring blocks are 16 consecutive outputs.
 __device__ __forceinline__ int w_perm64(int m) { return ((m >> 2) & 3) * 16 + (m >> 4) * 4 + (m & 3); }
 
-// buffer descriptor over everything from `base` on (no range check: the kernel only takes tiles that lie inside)
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const bf16_t* base) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, (int)0xFFFFFFFFu, 0x00020000);
+// buffer descriptor over everything from `base` on (no range check: tiles lie inside their matrices), or over `bytes`
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const bf16_t* base, uint32_t bytes = 0xFFFFFFFFu) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, (int)bytes, 0x00020000);
 }
 
 // A value moved into an accumulation register by hand: the 256 start values of the accumulators are produced by
@@ -89,9 +98,10 @@ __device__ __forceinline__ float from_acc(float x) {
     return r;
 }
 
-template <int OUT, bool T_F32, int PHASES>
+template <int OUT, bool T_F32, int PHASES, bool RAGGED>
 __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
     static_assert(OUT == 0 || (PHASES == 1 && !T_F32), "the kernels without a squared-error target have one evaluation");
+    constexpr bool LATE_T = RAGGED && OUT == 0;    // the target is subtracted after the last slice
     constexpr int NT = 256, BA = 4, BB = 4;
     constexpr int W_BASE = 0, X_BASE = 3 * TILE_BYTES;       // LDS: three W stages, then two X stages (all 160 KiB)
     extern __shared__ __align__(16) char smem[];
@@ -127,7 +137,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
     };
     if (n_tiles == 0) return;
     tile_at(0, tm, tn);
-    int64_t m0 = tm * BT, n0 = tn * BT;
+    // first row and column of a tile
+    auto origin_m = [&](int64_t t) __attribute__((always_inline)) { return RAGGED ? min(t * BT, p.M - BT) : t * BT; };
+    auto origin_n = [&](int64_t t) __attribute__((always_inline)) { return RAGGED ? min(t * BT, p.N - BT) : t * BT; };
+    int64_t m0 = origin_m(tm), n0 = origin_n(tn);
 
     // ---- operand sources: X / W slices, then the prepared extension operands ----------------------
     const bool has_ext = p.Xext != nullptr;
@@ -145,8 +158,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
     auto next_sources = [&](int i) __attribute__((always_inline)) {
         int64_t tmn = tm, tnn = tn;
         if (i < n_tiles) tile_at(i, tmn, tnn);
-        xbn = p.X + tmn * BT * p.ldx;
-        wbn = p.W + tnn * BT * p.ldw;
+        xbn = p.X + origin_m(tmn) * p.ldx;
+        wbn = p.W + origin_n(tnn) * p.ldw;
     };
     tile_sources();
     next_sources(1);
@@ -157,11 +170,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
     const int vx = (int)(((int64_t)row0 * p.ldx + chunk0 * 8) * 2), vw = (int)(((int64_t)w_perm64(row0) * p.ldw + chunk0 * 8) * 2);
     const int vx2 = (row0 * p.ext_ld + chunk0 * 8) * 2, vw2 = (w_perm64(row0) * p.ext_ld + chunk0 * 8) * 2;
     const int gsx = (int)(64 * p.ldx), gsw = (int)(64 * p.ldw), gs2 = 64 * p.ext_ld;   // bytes between row groups
-    const int nfull = (int)(p.K / BK);
+    const int nfull = (int)(p.K / BK), nd = RAGGED ? (int)((p.K + BK - 1) / BK) : nfull;      // d_in slices: whole ones, all
+    const int tail_off = (RAGGED && chunk0 * 8 >= (int)(p.K % BK)) ? kPastEnd : 0;               // (of the slice that is not whole)
     const int next = has_ext ? p.ext_ld / BK : 0;
     // slices that ride the load pipeline: the d_in slices, and in the one-evaluation kernel the extension behind them
     // (at least two: the first two slices of a tile are always d_in slices)
-    const int npipe = nfull + (PHASES == 1 ? next : 0);
+    const int npipe = nd + (PHASES == 1 ? next : 0);
     typedef __attribute__((address_space(3))) void* lptr_t;
 
     // ---- accumulators <- minus the target tile ----------------------------------------------------
@@ -180,14 +194,25 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
 #pragma clang loop unroll(full)
             for (int i4 = 0; i4 < 2; ++i4)
 #pragma clang loop unroll(full)
-                for (int q = 0; q < 4; ++q) traw[(J & 3) * 8 + i4 * 4 + q] = src[i4 * 16 + q];
+                for (int q = 0; q < 4; ++q) traw[(J & 3) * 8 + i4 * 4 + q] = RAGGED ? load16_any(src + i4 * 16 + q) : src[i4 * 16 + q];
         } else {
             const uint4* src = reinterpret_cast<const uint4*>(reinterpret_cast<const bf16_t*>(p.target) + row * p.ldt + colw);
 #pragma clang loop unroll(full)
             for (int i4 = 0; i4 < 2; ++i4)
 #pragma clang loop unroll(full)
-                for (int q = 0; q < 2; ++q) traw[J * 4 + i4 * 2 + q] = src[i4 * 8 + q];
+                for (int q = 0; q < 2; ++q) traw[J * 4 + i4 * 2 + q] = RAGGED ? load16_any(src + i4 * 8 + q) : src[i4 * 8 + q];
         }
+    };
+    // value of element u of block (I, J) among the raw vectors
+    auto target_value = [&](int J, int I, int u) __attribute__((always_inline)) {
+        if (T_F32) {
+            const uint4 t = traw[(J & 3) * 8 + I];
+            return __uint_as_float(u == 0 ? t.x : u == 1 ? t.y : u == 2 ? t.z : t.w);
+        }
+        const uint4 t = traw[J * 4 + (I >> 2) * 2 + ((I & 3) >> 1)];
+        const int k = (I & 1) * 2 + (u >> 1);
+        const uint32_t w = k == 0 ? t.x : k == 1 ? t.y : k == 2 ? t.z : t.w;
+        return __uint_as_float((u & 1) ? w & 0xFFFF0000u : w << 16);
     };
     auto tneg = [&](auto JJ) __attribute__((always_inline)) {
         constexpr int J = decltype(JJ)::value;
@@ -266,17 +291,24 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
         // (copies first: the selects then see values, not addresses of captured variables)
         const bf16_t *cxb = xb, *cwb = wb_, *cxb2 = xb2, *cwb2 = wb2, *cxbn = xbn, *cwbn = wbn;
         const int cvx = vx, cvw = vw, cvx2 = vx2, cvw2 = vw2, cgsx = gsx, cgsw = gsw, cgs2 = gs2;
-        const bool e = kt >= nfull;                          // extension operands (or, past npipe, the next tile)
+        const bool e = kt >= nd;                             // extension operands (or, past npipe, the next tile)
         const bf16_t* xs = e ? cxb2 : cxb;
         const bf16_t* ws = e ? cwb2 : cwb;
         int svx = e ? cvx2 : cvx, svw = e ? cvw2 : cvw, sgx = e ? cgs2 : cgsx, sgw = e ? cgs2 : cgsw;
-        int so = e ? kt - nfull : kt;
+        int so = e ? kt - nd : kt;
         const bool nxt = kt >= npipe;
         xs = nxt ? cxbn : xs;
         ws = nxt ? cwbn : ws;
         svx = nxt ? cvx : svx;   svw = nxt ? cvw : svw;   sgx = nxt ? cgsx : sgx;   sgw = nxt ? cgsw : sgw;
         so = nxt ? kt - npipe : so;
-        src_rsx = rsrc(xs);   src_rsw = rsrc(ws);
+        uint32_t bytes = 0xFFFFFFFFu;
+        if constexpr (RAGGED) {
+            const bool last = kt == nfull && kt < nd;        // the slice that d_in does not fill
+            const int past = last ? tail_off : 0;
+            svx += past;   svw += past;
+            bytes = last ? (uint32_t)kPastEnd : bytes;
+        }
+        src_rsx = rsrc(xs, bytes);   src_rsw = rsrc(ws, bytes);
         set_offsets(svx, sgx, svw, sgw);
         src_so = so * (BK * 2);
     };
@@ -329,29 +361,41 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
         }
     };
 
-    // ---- sum of squares of the accumulators    // ---- sum of squares of the accumulators: fp32 squares four at a time, summed in fp64; lanes, then waves, in a
+    // ---- sum of squares of the accumulators: fp32 squares four at a time, summed in fp64; lanes, then waves, in a
     // fixed order ----
     // The four waves' sums meet in LDS, in `red`: the head of a W stage that nothing reads or fills at that moment
     // (the operand stages take all of the LDS)
-    auto eval_sum = [&]() __attribute__((always_inline)) {
+    // rs, cs: rows and columns of the tile that the tile before it has counted (the last tile of a direction starts at the
+    // last 256 rows or columns instead of hanging over the edge)
+    auto eval_sum = [&](int rs, int cs) __attribute__((always_inline)) {
         double part = 0.0;
         // 24 wait states between the last matrix instruction and the first read of a result: the matrix instructions are
         // written out, so the compiler does not know of them and keeps no distance itself
         asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7");
+        auto sum = [&](auto MASK) __attribute__((always_inline)) {
+            constexpr bool mask = decltype(MASK)::value != 0;
 #pragma clang loop unroll(full)
-        for (int J = 0; J < 8; ++J)
+            for (int J = 0; J < 8; ++J) {
+                if (LATE_T && PHASES == 1 && T_F32 && J == 4) { tload(IC<4>{}); tload(IC<5>{}); tload(IC<6>{}); tload(IC<7>{}); }
 #pragma clang loop unroll(full)
-            for (int I = 0; I < 8; ++I) {
-                const floatx4 v = acc[I][J];
-                float s4 = 0.f;
+                for (int I = 0; I < 8; ++I) {
+                    const floatx4 v = acc[I][J];
+                    float s4 = 0.f;
+                    const int left = mask ? ((wb * 128 + J * 16 + lc >= rs) ? cs - (wa * 128 + (I >> 2) * 64 + lg * 16 + (I & 3) * 4) : 4) : 0;
 #pragma clang loop unroll(full)
-                for (int u = 0; u < 4; ++u) {
-                    // (the shared-forward schedule multiplies on after an evaluation and nothing else is live there)
-                    const float x = (PHASES == 1) ? from_acc(v[u]) : v[u];
-                    s4 = fmaf(x, x, s4);
+                    for (int u = 0; u < 4; ++u) {
+                        // (the shared-forward schedule multiplies on after an evaluation and nothing else is live there)
+                        float x = (PHASES == 1) ? from_acc(v[u]) : v[u];
+                        if (LATE_T && PHASES == 1) x -= target_value(J, I, u);
+                        if (mask) x = u >= left ? x : 0.f;
+                        s4 = fmaf(x, x, s4);
+                    }
+                    part += (double)s4;
                 }
-                part += (double)s4;
             }
+        };
+        if (RAGGED && __builtin_expect((rs | cs) != 0, 0)) sum(IC<1>{});
+        else sum(IC<0>{});
         return part;
     };
     auto eval_finish = [&](double part, int phase, int64_t tm_, int64_t tn_, double* red) __attribute__((always_inline)) {
@@ -367,12 +411,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
         if constexpr (PHASES == 1) __syncthreads();
     };
     auto evaluate = [&](int phase, int64_t tm_, int64_t tn_, double* red) __attribute__((always_inline)) {
-        eval_finish(eval_sum(), phase, tm_, tn_, red);
+        eval_finish(eval_sum((int)(tm * BT - m0), (int)(tn * BT - n0)), phase, tm_, tn_, red);
     };
 
     // accumulators <- minus the target tile (squared error) or zero (stored output)
     auto start_tile = [&]() __attribute__((always_inline)) {
-        if constexpr (OUT == 0) {
+        if constexpr (OUT == 0 && !LATE_T) {
             tneg(IC<0>{}); tneg(IC<1>{}); tneg(IC<2>{}); tneg(IC<3>{});
             if (T_F32) { tload(IC<4>{}); tload(IC<5>{}); tload(IC<6>{}); tload(IC<7>{}); }
             tneg(IC<4>{}); tneg(IC<5>{}); tneg(IC<6>{}); tneg(IC<7>{});
@@ -393,7 +437,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
     };
 
     // ---- first tile: target and the first two slices ------------------------------------------------
-    request_target();
+    if constexpr (!LATE_T) request_target();
     select_slice(0);
 #pragma unroll
     for (int t = 0; t < 8; ++t) { dma_x(0, t); dma_w(0, t); }
@@ -476,7 +520,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
                 for (int n = 0; n < 8; ++n) {
                     const int t = 4 * n + (lane >> 4);
                     const uint4 v = *reinterpret_cast<const uint4*>(stg + t * 256 + ((cc ^ (t & 15)) << 4));
-                    *reinterpret_cast<uint4*>(reinterpret_cast<bf16_t*>(p.Y) + (m0 + wb * 128 + r2 * 32 + t) * p.ldy + n0 + wa * 128 + cc * 8) = v;
+                    bf16_t* dst = reinterpret_cast<bf16_t*>(p.Y) + (m0 + wb * 128 + r2 * 32 + t) * p.ldy + n0 + wa * 128 + cc * 8;
+                    if (RAGGED) store16_any(dst, v);
+                    else *reinterpret_cast<uint4*>(dst) = v;
                 }
             }
             __syncthreads();                                 // the next W loads go into that stage
@@ -485,6 +531,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
             // a lane holds 32 of the 128 logits of the wave's columns for each of eight tokens; the lanes lane ^ 16, ^ 32, ^ 48
             // hold the others.  Online softmax over the wave's 128 columns, per token
             asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7");
+            // columns that the tile before this one has counted stay out (rows that it has counted get the same values again);
+            // cskip: how many of the lane's 16 columns per group those are
+            const int cs = RAGGED ? (int)(tn * BT - n0) : 0;
+            const int cskip[2] = {cs - (wa * 128 + lg * 16), cs - (wa * 128 + 64 + lg * 16)};
 #pragma clang loop unroll(full)
             for (int J = 0; J < 8; ++J) {
                 const int64_t row = m0 + wb * 128 + J * 16 + lc;
@@ -499,7 +549,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
 #pragma clang loop unroll(full)
                         for (int e = 0; e < 4; ++e) {
                             const float y = acc[i4 * 4 + t][J][e];
-                            mx = fmaxf(mx, y);
+                            if (!RAGGED || 4 * t + e >= cskip[i4]) mx = fmaxf(mx, y);
                             if (4 * t + e == trel) { tl = y; has_tl = true; }
                         }
                 }
@@ -511,7 +561,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
 #pragma clang loop unroll(full)
                 for (int I = 0; I < 8; ++I)
 #pragma clang loop unroll(full)
-                    for (int e = 0; e < 4; ++e) sm += __builtin_amdgcn_exp2f((acc[I][J][e] - mx) * 1.44269504088896341f);
+                    for (int e = 0; e < 4; ++e) {
+                        const float ex = __builtin_amdgcn_exp2f((acc[I][J][e] - mx) * 1.44269504088896341f);
+                        sm += (!RAGGED || (I & 3) * 4 + e >= cskip[I >> 2]) ? ex : 0.f;
+                    }
                 sm += __shfl_xor(sm, 16);
                 sm += __shfl_xor(sm, 32);
                 const int64_t chunk = tn * 2 + wa;           // of tiles_n x 2 chunks per token
@@ -521,18 +574,26 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
             if (!more) break;
         } else if constexpr (PHASES == 1) {
             const int64_t tm_done = tm, tn_done = tn;
+            const int rs = RAGGED ? (int)(tm * BT - m0) : 0, cs = RAGGED ? (int)(tn * BT - n0) : 0;
             double part;
-            if (more) {
+            if constexpr (LATE_T) {
+                request_target();
+                part = eval_sum(rs, cs);
+                if (more) {
+                    tile_at(it + 1, tm, tn);
+                    m0 = origin_m(tm); n0 = origin_n(tn);
+                }
+            } else if (more) {
                 tile_at(it + 1, tm, tn);
-                m0 = tm * BT; n0 = tn * BT;
+                m0 = origin_m(tm); n0 = origin_n(tn);
                 // The next tile's target is requested and the finished tile summed, in one order by two of the waves and in
                 // the other by the other two: a request keeps its wave's issue port for as long as the address unit takes
                 // over its 64 rows, and the address unit is the compute unit's one, so four waves requesting at once wait
                 // for each other while nobody sums
-                if (wave < 2) { request_target(); part = eval_sum(); }
-                else { part = eval_sum(); request_target(); }
+                if (wave < 2) { request_target(); part = eval_sum(rs, cs); }
+                else { part = eval_sum(rs, cs); request_target(); }
             } else {
-                part = eval_sum();
+                part = eval_sum(rs, cs);
             }
             eval_finish(part, 0, tm_done, tn_done, reinterpret_cast<double*>(smem + W_BASE + ((wst == 0) ? 2 : wst - 1) * TILE_BYTES));
             if (!more) break;
@@ -554,6 +615,18 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
             };
             if (next > 0) ext_dma(rw2, 0, 0);
             double* red = reinterpret_cast<double*>(smem + W_BASE + 2 * TILE_BYTES);
+            if constexpr (LATE_T) {                          // from here on the accumulators hold residuals
+                asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7");
+                request_target();
+#pragma clang loop unroll(full)
+                for (int J = 0; J < 8; ++J) {
+                    if (T_F32 && J == 4) { tload(IC<4>{}); tload(IC<5>{}); tload(IC<6>{}); tload(IC<7>{}); }
+#pragma clang loop unroll(full)
+                    for (int I = 0; I < 8; ++I)
+#pragma clang loop unroll(full)
+                        for (int u = 0; u < 4; ++u) acc[I][J][u] -= target_value(J, I, u);
+                }
+            }
             evaluate(0, tm, tn, red);
             if (next > 0) {
                 ext_dma(rw3, 0, 1);
@@ -587,7 +660,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
         // ---- hand the accumulators to the next tile ----
         if constexpr (OUT != 0) {
             tile_at(it + 1, tm, tn);
-            m0 = tm * BT; n0 = tn * BT;
+            m0 = origin_m(tm); n0 = origin_n(tn);
         }
         tile_sources();
         next_sources(it + 2);
@@ -596,12 +669,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
     if (p.clk && blockIdx.x == 0 && tid == 0) { p.clk[2] = __builtin_readcyclecounter(); p.clk[3] = wall_clock64(); }
 }
 
-template <int OUT, bool T_F32, int PHASES>
+template <int OUT, bool T_F32, int PHASES, bool RAGGED>
 static hipError_t launch_aligned_variant(const GemmParams& p, hipStream_t st) {
     static bool attr_set = false;
     const int smem = 5 * TILE_BYTES;           // three W stages and two X stages: all 160 KiB of a compute unit's LDS
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_bf16_aligned_kernel<OUT, T_F32, PHASES>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_bf16_aligned_kernel<OUT, T_F32, PHASES, RAGGED>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, smem);
         if (e != hipSuccess) return e;
         attr_set = true;
@@ -619,26 +692,29 @@ static hipError_t launch_aligned_variant(const GemmParams& p, hipStream_t st) {
         if (G >= 8) G -= G % 8;
     }
     dim3 grid((unsigned)G);
-    hipLaunchKernelGGL((gemm_bf16_aligned_kernel<OUT, T_F32, PHASES>), grid, dim3(256), smem, st, p);
+    hipLaunchKernelGGL((gemm_bf16_aligned_kernel<OUT, T_F32, PHASES, RAGGED>), grid, dim3(256), smem, st, p);
     return hipGetLastError();
 }
 
-hipError_t launch_gemm_bf16_aligned(const GemmParams& p, hipStream_t st) {
-    const bool shape_ok = p.vec_ok && p.M % BT == 0 && p.N % BT == 0 && p.K % BK == 0 && p.K >= 2 * BK &&
-                          (p.P == nullptr || p.Xext != nullptr);
-    if (!shape_ok) return hipErrorInvalidValue;
+template <bool RAGGED>
+static hipError_t launch_aligned(const GemmParams& p, hipStream_t st) {
     if (p.Y != nullptr) {       // stored output, no loss
         if (p.loss_kind != AGZO_LOSS_NONE || p.y_dtype != AGZO_BF16 || p.shared) return hipErrorInvalidValue;
-        return launch_aligned_variant<1, false, 1>(p, st);
+        return launch_aligned_variant<1, false, 1, RAGGED>(p, st);
     }
     if (p.loss_kind == AGZO_LOSS_CE) {
         if (p.shared || !p.ce_target || !p.ce_ms || !p.ce_tl) return hipErrorInvalidValue;
-        return launch_aligned_variant<2, false, 1>(p, st);
+        return launch_aligned_variant<2, false, 1, RAGGED>(p, st);
     }
     if (p.loss_kind != AGZO_LOSS_MSE || (p.shared && p.Wext2 == nullptr)) return hipErrorInvalidValue;
     const bool f32 = p.target_dtype != AGZO_BF16;
-    if (p.shared) return f32 ? launch_aligned_variant<0, true, 3>(p, st) : launch_aligned_variant<0, false, 3>(p, st);
-    return f32 ? launch_aligned_variant<0, true, 1>(p, st) : launch_aligned_variant<0, false, 1>(p, st);
+    if (p.shared) return f32 ? launch_aligned_variant<0, true, 3, RAGGED>(p, st) : launch_aligned_variant<0, false, 3, RAGGED>(p, st);
+    return f32 ? launch_aligned_variant<0, true, 1, RAGGED>(p, st) : launch_aligned_variant<0, false, 1, RAGGED>(p, st);
+}
+
+hipError_t launch_gemm_bf16_aligned(const GemmParams& p, hipStream_t st) {
+    if (p.M < BT || p.N < BT || p.K < 2 * BK || (p.P != nullptr && p.Xext == nullptr)) return hipErrorInvalidValue;
+    return p.vec_ok && p.M % BT == 0 && p.N % BT == 0 && p.K % BK == 0 ? launch_aligned<false>(p, st) : launch_aligned<true>(p, st);
 }
 
 }  // namespace agzo

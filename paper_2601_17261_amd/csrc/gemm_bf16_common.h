@@ -22,6 +22,21 @@ __device__ __forceinline__ int lds_off(int row, int c) { return row * (BK * 2) +
 // row 8*(e/4) + 4*h + e%4 of the block, which this makes output column 16*h + e.
 __device__ __forceinline__ int w_perm(int m) { return ((m >> 2) & 1) * 16 + ((m >> 3) & 3) * 4 + (m & 3); }
 
+// 16 bytes at any 2-byte aligned address, one instruction each (global memory takes unaligned vectors; rows of an odd number
+// of outputs make them so)
+struct __attribute__((packed, aligned(2))) Any16 { uint32_t x, y, z, w; };
+__device__ __forceinline__ uint4 load16_any(const void* src) {
+    const Any16 v = *reinterpret_cast<const Any16*>(src);
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void store16_any(void* dst, uint4 v) {
+    *reinterpret_cast<Any16*>(dst) = Any16{v.x, v.y, v.z, v.w};
+}
+
+// Direct loads of a last slice that d_in does not fill: lanes whose chunk lies past d_in add this to their offset, which the
+// range of the slice's descriptor (below) turns into zeros.  Offsets inside a tile stay below it: 256 rows of 2^22 elements
+constexpr int kPastEnd = (int)0x80000000u;
+
 struct GemmParams {
     const bf16_t* X; int64_t ldx;
     const bf16_t* W; int64_t ldw;
@@ -69,9 +84,9 @@ struct GemmItem {
 bool gemm_bf16_mid_ok(const GemmItem& g, int out);
 hipError_t launch_gemm_bf16_mid(const GemmItem* a, int n, int out, bool target_f32, hipStream_t st);
 
-// kernel for tile-aligned layers (gemm_bf16_aligned.hip): M, N multiples of 256, d_in a multiple of 64 and >= 128,
-// 16-byte target / output accesses, the rank-r term as prepared operands; either the squared-error loss without a
-// stored Y (p.shared: f0, f+, f- in one pass, needs Wext2, partials [3][tiles]) or a bf16 Y without a loss
+// persistent kernel in 256 x 256 tiles (gemm_bf16_aligned.hip): M, N >= 256, d_in >= 128, the rank-r term as prepared operands;
+// either the squared-error loss without a stored Y (p.shared: f0, f+, f- in one pass, needs Wext2, partials [3][tiles]), the
+// cross-entropy statistics without a stored Y, or a bf16 Y without a loss
 hipError_t launch_gemm_bf16_aligned(const GemmParams& p, hipStream_t st);
 
 }  // namespace agzo

@@ -1,8 +1,8 @@
 // Forward GEMM of the bf16 path in 128 x 128 tiles, for layers that give too few 256 x 256 tiles to fill the chip:
 //     OUT = 0:  f = sum over the tile of (X W^T (+ eps (X B) G^T) - Y*)^2     (f0, f+, f- of Sec. 4.1; Eq. 7 factored)
 //     OUT = 1:  Y = X W^T (+ eps (X B) G^T) stored as bf16
-// for d_in a multiple of 64 and at least 128, d_out a multiple of 16, at least 128 tokens and outputs, 16-byte rows of target
-// or output, the rank-r extension as prepared operands.  Other shapes keep gemm_bf16_small.hip.
+// for d_in, tokens and outputs of at least 128, the rank-r extension as prepared operands.  Other shapes keep
+// gemm_bf16_small.hip.
 //
 // One launch takes up to kBatchMax problems (the layers of a set, both signs of a perturbed evaluation): a 2048-token layer of
 // 1024 outputs is 128 tiles, half a chip, and a launch of its own costs 5.6 us before its first and after its last slice.  The
@@ -18,7 +18,8 @@
 //
 // Rows and columns that do not fill a tile: the last tile of a direction starts at the last 128 rows instead of hanging over the
 // edge, so that no load needs a bound; the squared error leaves out what the tile before it has counted, a stored output is
-// stored twice with the same bits.
+// stored twice with the same bits.  A last slice that d_in does not fill: its direct loads get a descriptor with a range and the
+// lanes past d_in an offset beyond it, which loads zeros.  Rows of target or output need no alignment.
 #include "gemm_bf16_common.h"
 
 namespace agzo {
@@ -35,8 +36,8 @@ constexpr int MSK_SMEM = 3 * MSK_RP * MSK_ROW;
 // are then 16 consecutive outputs (as in gemm_bf16_aligned.hip)
 __device__ __forceinline__ int mid_perm(int m) { return ((m >> 2) & 3) * 16 + (m >> 4) * 4 + (m & 3); }
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t mid_rsrc(const bf16_t* base) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, (int)0xFFFFFFFFu, 0x00020000);
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t mid_rsrc(const bf16_t* base, uint32_t bytes = 0xFFFFFFFFu) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, (int)bytes, 0x00020000);
 }
 
 // SK: also emits the range sketch of Alg. 1 from the X slices in LDS, as gemm_bf16_small.hip describes; the planes of Omega^T
@@ -78,10 +79,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int vx = (int)(((int64_t)row0 * p.ldx + chunk0 * 8) * 2), vw = (int)(((int64_t)mid_perm(row0) * p.ldw + chunk0 * 8) * 2);
     const int vx2 = (row0 * p.ext_ld + chunk0 * 8) * 2, vw2 = (mid_perm(row0) * p.ext_ld + chunk0 * 8) * 2;
     const int gsx = (int)(64 * p.ldx), gsw = (int)(64 * p.ldw), gs2 = 64 * p.ext_ld;   // bytes between row groups
-    const int nfull = (int)(p.K / BK), npipe = nfull + (has_ext ? p.ext_ld / BK : 0);
+    const int nfull = (int)(p.K / BK), nd = (int)((p.K + BK - 1) / BK);             // d_in slices: whole ones, all
+    const int npipe = nd + (has_ext ? p.ext_ld / BK : 0);
+    const int tail_off = (chunk0 * 8 >= (int)(p.K % BK)) ? kPastEnd : 0;             // (of the slice that is not whole)
     typedef __attribute__((address_space(3))) void* lptr_t;
 
-    // ---- accumulators <- minus the target tile, or zero ----
+    // ---- accumulators, and the target tile, which waits in registers for the last slice ----
+    // (Accumulators that start at minus the target leave the loss 10 times further from its value in 64 bits, 5e-9 of it
+    // against 4e-10: the rounding of the sums then follows the residual's sign.)
     floatx4 acc[4][4];
     uint4 traw[T_F32 ? 16 : 8];
     if constexpr (OUT == 0) {
@@ -91,7 +96,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             const uint4* src = T_F32 ? reinterpret_cast<const uint4*>(reinterpret_cast<const float*>(p.target) + row * p.ldt + col)
                                      : reinterpret_cast<const uint4*>(reinterpret_cast<const bf16_t*>(p.target) + row * p.ldt + col);
 #pragma unroll
-            for (int q = 0; q < (T_F32 ? 4 : 2); ++q) traw[J * (T_F32 ? 4 : 2) + q] = src[q];
+            for (int q = 0; q < (T_F32 ? 4 : 2); ++q) traw[J * (T_F32 ? 4 : 2) + q] = load16_any(src + q);
         }
     }
 
@@ -125,7 +130,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             }
         }
         const int64_t f = (int64_t)it * BK + 8 * c + 2 * wave + (n >> 3);
-        *reinterpret_cast<float4*>(p.sk_partial + ((int64_t)tm * p.K + f) * MSK_RP + 4 * g) = make_float4(s[0], s[1], s[2], s[3]);
+        if (f < p.K) *reinterpret_cast<float4*>(p.sk_partial + ((int64_t)tm * p.K + f) * MSK_RP + 4 * g) = make_float4(s[0], s[1], s[2], s[3]);
     };
 
     // ---- source of a slice: d_in slices, then the extension operands ----
@@ -141,13 +146,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         const bf16_t *cxb = xb, *cwb = wb_, *cxb2 = xb2, *cwb2 = wb2;
         const int cvx = vx, cvw = vw, cvx2 = vx2, cvw2 = vw2, cgsx = gsx, cgsw = gsw, cgs2 = gs2;
         kt = min(kt, npipe - 1);
-        const bool e = kt >= nfull;
+        const bool e = kt >= nd, last = kt == nfull && !e;          // last: the slice that d_in does not fill
         const bf16_t* xs = e ? cxb2 : cxb;
         const bf16_t* ws = e ? cwb2 : cwb;
-        const int svx = e ? cvx2 : cvx, svw = e ? cvw2 : cvw, sgx = e ? cgs2 : cgsx, sgw = e ? cgs2 : cgsw;
-        src_rsx = mid_rsrc(xs);   src_rsw = mid_rsrc(ws);
+        const int past = last ? tail_off : 0, svx = (e ? cvx2 : cvx) + past, svw = (e ? cvw2 : cvw) + past;
+        const int sgx = e ? cgs2 : cgsx, sgw = e ? cgs2 : cgsw;
+        const uint32_t bytes = last ? (uint32_t)kPastEnd : 0xFFFFFFFFu;
+        src_rsx = mid_rsrc(xs, bytes);   src_rsw = mid_rsrc(ws, bytes);
         set_offsets(svx, sgx, svw, sgw);
-        src_so = (e ? kt - nfull : kt) * (BK * 2);
+        src_so = (e ? kt - nd : kt) * (BK * 2);
     };
     auto dma_x = [&](int buf, int t) __attribute__((always_inline)) {
         char* dst = smem + X_BASE + buf * MTILE_BYTES + wave * 1024 + t * 4096;
@@ -168,33 +175,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
 #pragma unroll
     for (int J = 0; J < 4; ++J) {
-        if constexpr (OUT == 0) {
-            float v[16];
-            if (T_F32) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const uint4 t = traw[J * 4 + q];
-                    v[4 * q] = -__uint_as_float(t.x); v[4 * q + 1] = -__uint_as_float(t.y);
-                    v[4 * q + 2] = -__uint_as_float(t.z); v[4 * q + 3] = -__uint_as_float(t.w);
-                }
-            } else {
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const uint4 t = traw[J * 2 + q];
-                    const uint32_t w[4] = {t.x, t.y, t.z, t.w};
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        v[8 * q + 2 * u] = __uint_as_float((w[u] << 16) + 0x80000000u);
-                        v[8 * q + 2 * u + 1] = __uint_as_float((w[u] & 0xFFFF0000u) ^ 0x80000000u);
-                    }
-                }
-            }
-#pragma unroll
-            for (int I = 0; I < 4; ++I) acc[I][J] = floatx4{v[4 * I], v[4 * I + 1], v[4 * I + 2], v[4 * I + 3]};
-        } else {
-#pragma unroll
-            for (int I = 0; I < 4; ++I) acc[I][J] = floatx4{0.f, 0.f, 0.f, 0.f};
-        }
+        for (int I = 0; I < 4; ++I) acc[I][J] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
 
     // ---- multiply: fragment of block row I (W) or token block J (X), k step ks: lane (lc, lg) reads chunk 4 ks + lg of row 16 I + lc
@@ -251,7 +233,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         else src_so = (kt + AHEAD) * (BK * 2);
         block(IC<0>{}, wcur, xcur, IC<1>{}, wput);
         if constexpr (SK) {
-            if (kt == sk_next && kt < nfull) { sketch(xcur, kt); sk_next += p.tiles_n; }
+            if (kt == sk_next && kt < nd) { sketch(xcur, kt); sk_next += p.tiles_n; }
             __builtin_amdgcn_s_waitcnt(0x0070);              // (its stores count as well)
         }
         // lgkmcnt(0) and all but the youngest loads: the whole next slice has landed (loads return in the order issued), this
@@ -279,23 +261,37 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 w[2 * I] = pack_bf16x2(acc[I][J][0], acc[I][J][1]);
                 w[2 * I + 1] = pack_bf16x2(acc[I][J][2], acc[I][J][3]);
             }
-            uint4* dst = reinterpret_cast<uint4*>(reinterpret_cast<bf16_t*>(p.Y) + row * p.ldy + col);
-            dst[0] = make_uint4(w[0], w[1], w[2], w[3]);
-            dst[1] = make_uint4(w[4], w[5], w[6], w[7]);
+            bf16_t* dst = reinterpret_cast<bf16_t*>(p.Y) + row * p.ldy + col;
+            store16_any(dst, make_uint4(w[0], w[1], w[2], w[3]));
+            store16_any(dst + 8, make_uint4(w[4], w[5], w[6], w[7]));
         }
     } else {
         // squares in fp32 four at a time, summed in fp64; lanes, then waves, in a fixed order
         double part = 0.0;
-        const bool col_in = n0 + wa * 64 + lg * 16 >= col_new;
+        // value of element e of block (I, J) among the raw vectors
+        auto target_value = [&](int J, int I, int e) __attribute__((always_inline)) {
+            if (T_F32) {
+                const uint4 t = traw[J * 4 + I];
+                return __uint_as_float(e == 0 ? t.x : e == 1 ? t.y : e == 2 ? t.z : t.w);
+            }
+            const uint4 t = traw[J * 2 + (I >> 1)];
+            const int k = (I & 1) * 2 + (e >> 1);
+            const uint32_t w = k == 0 ? t.x : k == 1 ? t.y : k == 2 ? t.z : t.w;
+            return __uint_as_float((e & 1) ? w & 0xFFFF0000u : w << 16);
+        };
+        const int skip = (int)(col_new - (n0 + wa * 64 + lg * 16));      // so many of the lane's 16 columns are counted already
 #pragma unroll
         for (int J = 0; J < 4; ++J) {
-            const bool in = col_in && m0 + wb * 64 + J * 16 + lc >= row_new;
+            const int from = m0 + wb * 64 + J * 16 + lc >= row_new ? skip : 16;
 #pragma unroll
             for (int I = 0; I < 4; ++I) {
                 float s4 = 0.f;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) s4 = fmaf(acc[I][J][e], acc[I][J][e], s4);
-                part += in ? (double)s4 : 0.0;
+                for (int e = 0; e < 4; ++e) {
+                    const float x = 4 * I + e >= from ? acc[I][J][e] - target_value(J, I, e) : 0.f;
+                    s4 = fmaf(x, x, s4);
+                }
+                part += (double)s4;
             }
         }
 #pragma unroll
@@ -330,9 +326,7 @@ static hipError_t launch_mid_variant(const KBatch<GemmItem>& tb, unsigned blocks
 }
 
 bool gemm_bf16_mid_ok(const GemmItem& g, int out) {
-    const bool shape = g.M >= MT && g.N >= MT && g.N % 16 == 0 && g.K % BK == 0 && g.K >= 2 * BK;
-    if (out == 1) return shape && g.Y && g.ldy % 8 == 0 && (reinterpret_cast<uintptr_t>(g.Y) & 15) == 0;
-    return shape && g.target && g.ldt % 8 == 0 && (reinterpret_cast<uintptr_t>(g.target) & 15) == 0;
+    return g.M >= MT && g.N >= MT && g.K >= 2 * BK && (out == 1 ? g.Y != nullptr : g.target != nullptr);
 }
 
 hipError_t launch_gemm_bf16_mid(const GemmItem* a, int n, int out, bool target_f32, hipStream_t st) {

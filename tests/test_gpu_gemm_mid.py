@@ -14,8 +14,10 @@ pytestmark = pytest.mark.gpu
 EPS, LR = float(np.float32(1e-3)), float(np.float32(1e-2))
 
 # tokens, d_out, d_in, r: one tile; a tile and one row or sixteen columns more; the shortest pipeline and one with a slice for
-# every stage; ranks of one and several extension slices; more tiles than one band
-SHAPES = [(128, 128, 128, 1), (129, 144, 192, 16), (255, 272, 320, 17), (257, 400, 704, 64), (1100, 1168, 256, 8), (130, 2064, 128, 4)]
+# every stage; ranks of one and several extension slices; more tiles than one band; a d_in that its last slice does not fill and
+# rows of odd length
+SHAPES = [(128, 128, 128, 1), (129, 144, 192, 16), (255, 272, 320, 17), (257, 400, 704, 64), (1100, 1168, 256, 8), (130, 2064, 128, 4),
+          (200, 131, 136, 4), (128, 300, 712, 16), (333, 1001, 248, 5)]
 
 
 def _problem(i, n, d_out, d_in, pad, target):
