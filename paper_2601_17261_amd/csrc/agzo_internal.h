@@ -88,19 +88,22 @@ __device__ __forceinline__ float4 philox_normal4(uint32_t seed_lo, uint32_t seed
 // sets travel as a kernel argument, a workgroup finds its problem from the running workgroup counts (uniform: a few
 // scalar compares) and then runs exactly the code of the single-problem kernel, so results are bit-identical.
 // ---------------------------------------------------------------------------
+// A launch of one problem takes the set for one (CAP = 1): 2 KB of arguments per launch are some 4 us of the host's time.
 constexpr int kBatchMax = 16;
-template <typename A>
+template <typename A, int CAP = kBatchMax>
 struct KBatch {
     int n;
-    uint32_t first[kBatchMax];   // first workgroup of problem m
-    uint32_t gx[kBatchMax];      // its grid width (workgroups along x); y = local / gx
-    A a[kBatchMax];
+    uint32_t first[CAP];         // first workgroup of problem m
+    uint32_t gx[CAP];            // its grid width (workgroups along x); y = local / gx
+    A a[CAP];
 };
-// index of the problem that workgroup blockIdx.x belongs to; bx, by: its coordinates inside that problem's grid
 template <typename A>
-__device__ __forceinline__ int kbatch_find(const KBatch<A>& tb, uint32_t& bx, uint32_t& by) {
+KBatch<A, 1> kbatch_one(const KBatch<A>& tb) { return KBatch<A, 1>{1, {0}, {tb.gx[0]}, {tb.a[0]}}; }
+// index of the problem that workgroup blockIdx.x belongs to; bx, by: its coordinates inside that problem's grid
+template <typename A, int CAP>
+__device__ __forceinline__ int kbatch_find(const KBatch<A, CAP>& tb, uint32_t& bx, uint32_t& by) {
     int m = 0;
-    while (m + 1 < tb.n && blockIdx.x >= tb.first[m + 1]) ++m;
+    while (CAP > 1 && m + 1 < tb.n && blockIdx.x >= tb.first[m + 1]) ++m;
     const uint32_t local = blockIdx.x - tb.first[m];
     by = local / tb.gx[m];
     bx = local - by * tb.gx[m];

@@ -572,7 +572,8 @@ struct ExtDev {
     float coef, coef2; int n_w;
     uint32_t s_lo, s_hi;
 };
-__global__ __launch_bounds__(256) void gemm_ext_prep_kernel(const KBatch<ExtDev> tb) {
+template <int CAP>
+__global__ __launch_bounds__(256) void gemm_ext_prep_kernel(const KBatch<ExtDev, CAP> tb) {
     uint32_t bx, by;
     const ExtDev& a = tb.a[kbatch_find(tb, bx, by)];
     const int ext_ld = a.ext_ld, r = a.r, rp = a.rp;
@@ -641,7 +642,8 @@ hipError_t launch_gemm_ext_prep_many(const GemmExtArgs* a, int n, hipStream_t st
     }
     if (blocks == 0) return hipSuccess;
     if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(gemm_ext_prep_kernel, dim3((unsigned)blocks), dim3(256), 0, st, tb);
+    if (tb.n == 1) hipLaunchKernelGGL(gemm_ext_prep_kernel<1>, dim3((unsigned)blocks), dim3(256), 0, st, kbatch_one(tb));
+    else hipLaunchKernelGGL(gemm_ext_prep_kernel<kBatchMax>, dim3((unsigned)blocks), dim3(256), 0, st, tb);
     return hipGetLastError();
 }
 

@@ -45,8 +45,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t mid_rsrc(const bf16_t* base, u
 // DEEP: five stages of both operands and one workgroup per compute unit, for launches that give a compute unit no second
 // workgroup anyway: 16 us a launch against 17.1 on the 0.6B-sized layers, 35.8 against 39.3 at 512 tokens on the 4B-sized ones
 // (with two workgroups for every compute unit it is the slower one, 42.6 against 34.7 us at 8192 x 2048 -> 1024).  Same bits
-template <int OUT, bool T_F32, bool SK, bool DEEP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_bf16_mid_kernel(const KBatch<GemmItem> tb) {
+template <int OUT, bool T_F32, bool SK, bool DEEP, int CAP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_bf16_mid_kernel(const KBatch<GemmItem, CAP> tb) {
     constexpr int WS = DEEP ? 5 : 3, XS = DEEP ? 5 : 2;      // stages
     constexpr int AHEAD = DEEP ? 4 : 2;                       // slices between a request and its use
     constexpr int X_BASE = WS * MTILE_BYTES;
@@ -305,23 +305,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (p.clk && bx_ == 0 && tid == 0) { p.clk[2] = __builtin_readcyclecounter(); p.clk[3] = wall_clock64(); }
 }
 
-template <int OUT, bool T_F32, bool SK, bool DEEP>
-static hipError_t launch_mid_ring(const KBatch<GemmItem>& tb, unsigned blocks, hipStream_t st) {
+template <int OUT, bool T_F32, bool SK, bool DEEP, int CAP>
+static hipError_t launch_mid_ring(const KBatch<GemmItem, CAP>& tb, unsigned blocks, hipStream_t st) {
     const int smem = (DEEP ? 10 : 5) * MTILE_BYTES + (SK ? MSK_SMEM : 0);
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_bf16_mid_kernel<OUT, T_F32, SK, DEEP>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_bf16_mid_kernel<OUT, T_F32, SK, DEEP, CAP>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, smem);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    hipLaunchKernelGGL((gemm_bf16_mid_kernel<OUT, T_F32, SK, DEEP>), dim3(blocks), dim3(256), smem, st, tb);
+    hipLaunchKernelGGL((gemm_bf16_mid_kernel<OUT, T_F32, SK, DEEP, CAP>), dim3(blocks), dim3(256), smem, st, tb);
     return hipGetLastError();
 }
 template <int OUT, bool T_F32>
 static hipError_t launch_mid_variant(const KBatch<GemmItem>& tb, unsigned blocks, bool sk, hipStream_t st) {
     // (256: a workgroup per compute unit)
-    if (sk) return launch_mid_ring<OUT, T_F32, true, false>(tb, blocks, st);
+    if (sk) return launch_mid_ring<OUT, T_F32, true, false>(kbatch_one(tb), blocks, st);
+    if (tb.n == 1) return blocks <= 256 ? launch_mid_ring<OUT, T_F32, false, true>(kbatch_one(tb), blocks, st) : launch_mid_ring<OUT, T_F32, false, false>(kbatch_one(tb), blocks, st);
     return blocks <= 256 ? launch_mid_ring<OUT, T_F32, false, true>(tb, blocks, st) : launch_mid_ring<OUT, T_F32, false, false>(tb, blocks, st);
 }
 

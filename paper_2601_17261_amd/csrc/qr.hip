@@ -5,17 +5,23 @@
 //
 // Three launches per QR, coherence between them by kernel boundaries only (no device-scope fences):
 //   1. gram        : Gram partials of Y per 128-row block (v_mfma_f64_16x16x4_f64)
-//   2. apply_gram  : every block sums the partials in block order and factors the r x r matrix in LDS
-//                    (right-looking, the whole workgroup on the trailing update) -> R1;
-//                    Q1 = Y R1^-1 by forward substitution, one thread per row (fp64, stored), then
-//                    the Gram partials of Q1
-//   3. apply_final : the same reduction and factorisation -> R2; Q = Q1 R2^-1 (fp32), optionally
+//   2. apply_gram  : every block sums the partials in block order and factors the r x r matrix in LDS -> R1^-1;
+//                    Q1 = Y R1^-1 (fp64, stored), then the Gram partials of Q1
+//   3. apply_final : the same reduction and factorisation -> R2^-1; Q = Q1 R2^-1 (fp32), optionally
 //                    also as three bf16 planes [3][rp][d]
 // The orthonormalisations between power steps run a single pass (launches 1 and 3 only, launch 3 applying R1 to Y):
 // Q1 = Q R2 with R2 upper triangular and positive on the diagonal, so the next sketch X^T X Q1 = (X^T X Q) R2 has
 // the same thin-QR Q factor; the second pass only matters for the orthonormality of the basis that is returned.
 // When the input arrives as per-token-range partial sketches, launch 1 sums them (fp64, fixed order)
 // on the way in and stores the fp32 sketch, so no separate reduction kernel is needed.
+//
+// All of it is bound by chains of dependent steps.  The factorisation is blocked: one wave eliminates a 16 x 16 diagonal block
+// in registers (its inverse along with it, no barrier), everything else - panels, trailing blocks, the inverse's other blocks,
+// Y R^-1 - is 16 x 16 products on the fp64 matrix cores.  A column-by-column factorisation by the whole workgroup (two
+// barriers a column) and a substitution with a thread per row took 159 us where this takes 42 (the single pass of seven 4B-sized
+// layers, r = 64) and 10.9 where it takes 8.3 (0.6B-sized, r = 8); launch 1 at r = 64 65 and 35 us.
+#include <type_traits>
+
 #include "agzo_internal.h"
 
 namespace agzo {
@@ -23,55 +29,187 @@ namespace agzo {
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 constexpr int QR_ROWS = 128;   // rows per workgroup
+constexpr int QR_LD = 17;      // row length of a 16 x 16 block in LDS (padded)
+constexpr int QR_BLK = 16 * QR_LD;
+
+template <int RP>
+struct QrShape {
+    static constexpr int NB = RP / 16, PAIRS = NB * (NB + 1) / 2;      // 16-column blocks; blocks of the upper triangle
+    static constexpr int WAVES = NB == 1 ? 4 : 8, THREADS = 64 * WAVES;
+    static constexpr int RB = QR_ROWS / 16 / WAVES;                     // 16-row blocks per wave
+    static constexpr int LD = RP + 1;                                   // row length of the rows in LDS
+    static constexpr size_t GRAM_SMEM = (size_t)QR_ROWS * LD * sizeof(float);
+    static constexpr size_t FACTOR_SMEM = (size_t)2 * PAIRS * QR_BLK * sizeof(double);
+    static constexpr size_t APPLY_GRAM_SMEM = FACTOR_SMEM + (size_t)QR_ROWS * LD * sizeof(double);
+    static constexpr int PLANE_LD = QR_ROWS + 4;
+    static constexpr size_t APPLY_FINAL_SMEM = FACTOR_SMEM + (size_t)RP * PLANE_LD * sizeof(float);
+    // index of block (a, b), a <= b
+    static __host__ __device__ constexpr int pair(int a, int b) { return a * NB - a * (a - 1) / 2 + (b - a); }
+};
 
 static inline int64_t qr_blocks(int64_t d) { return (d + QR_ROWS - 1) / QR_ROWS; }
 
 size_t qr_workspace_bytes(int64_t d, int r) {
     const int rp = (r + 15) / 16 * 16;
-    // [Q1 fp64 d*r][gram partials of Y and of Q1: nblk*rp*rp fp64 each]
+    // [Q1 fp64 d*r][gram partials of Y and of Q1: up to nblk*rp*rp fp64 each]
     return (size_t)d * r * sizeof(double) + (size_t)2 * qr_blocks(d) * rp * rp * sizeof(double);
 }
 
-// The workgroup factors G (rp x rp, row-major fp64 in LDS) = R^T R in place, right-looking, two barriers per column:
-// on exit G's upper triangle holds R and its diagonal 1 / R[j][j] (what the substitution needs).  Padding columns
-// (>= r) carry a unit diagonal.  Returns nonzero on a non-positive pivot (the same value in every thread).
-__device__ int chol_block(double* G, int r, int rp) {
-    __shared__ double dinv[kMaxRank];
-    const int tid = threadIdx.x, nt = blockDim.x;
-    int bad = 0;
-    if (tid >= r && tid < rp) dinv[tid] = 1.0;            // padding columns: zero rows and columns, unit diagonal
-    for (int j = 0; j < r; ++j) {                         // (they need no elimination step)
-        __syncthreads();                                  // the trailing update of the previous column is complete
-        double piv = G[j * rp + j];
-        if (!(piv > 0.0)) { bad = 1; piv = 1.0; }
-        // 1/sqrt(piv): hardware estimate refined by two Newton steps (full fp64 accuracy, no divide)
-        double inv = __builtin_amdgcn_rsq(piv);
-        inv = inv * fma(-0.5 * piv * inv, inv, 1.5);
-        inv = inv * fma(-0.5 * piv * inv, inv, 1.5);
-        if (tid == j) dinv[j] = inv;
-        if (tid > j && tid < rp) G[j * rp + tid] *= inv;  // row j of R (the pivot itself stays in place until the end)
-        __syncthreads();
-        // trailing update of the upper triangle: G[a][c] -= R[j][a] R[j][c], j < a <= c
-        const int m = rp - j - 1;
-        for (int e = tid; e < m * m; e += nt) {
-            const int a = j + 1 + e / m, c = j + 1 + e % m;
-            if (c >= a) G[a * rp + c] = fma(-G[j * rp + a], G[j * rp + c], G[a * rp + c]);
-        }
+// ---- 16 x 16 products on the fp64 matrix cores.  Operand layout of v_mfma_f64_16x16x4_f64: lane l supplies element
+// (l mod 16, k = l / 16) of both A and B; D (measured on gfx950): register i of lane l is row 4 i + l / 16, column l mod 16
+// acc += A^T B (neg: -= ), A and B row-major blocks in LDS
+__device__ __forceinline__ doublex4 mul_tn(const double* A, const double* B, doublex4 acc, bool neg) {
+    const int lane = threadIdx.x & 63, at = (lane >> 4) * QR_LD + (lane & 15);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        const double a = A[at + 4 * s * QR_LD];
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(neg ? -a : a, B[at + 4 * s * QR_LD], acc, 0, 0, 0);
     }
-    __syncthreads();
-    if (tid < rp) G[tid * rp + tid] = dinv[tid];
-    __syncthreads();
+    return acc;
+}
+// acc += A B
+__device__ __forceinline__ doublex4 mul_nn(const double* A, const double* B, doublex4 acc, bool neg) {
+    const int lane = threadIdx.x & 63, at = (lane >> 4) * QR_LD + (lane & 15), ta = (lane & 15) * QR_LD + (lane >> 4);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        const double a = A[ta + 4 * s];
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(neg ? -a : a, B[at + 4 * s * QR_LD], acc, 0, 0, 0);
+    }
+    return acc;
+}
+__device__ __forceinline__ doublex4 get_block(const double* G) {
+    const int lane = threadIdx.x & 63;
+    doublex4 v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = G[(4 * i + (lane >> 4)) * QR_LD + (lane & 15)];
+    return v;
+}
+__device__ __forceinline__ void put_block(double* G, doublex4 v) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) G[(4 * i + (lane >> 4)) * QR_LD + (lane & 15)] = v[i];
+}
+
+// ---- a wave eliminates one symmetric 16 x 16 block.  Lane (c, g) = (l mod 16, l / 16) holds rows 4 g .. 4 g + 3 of column c
+// of the block and of the identity, which the same row operations turn into L^-1 (unit lower triangular; block = L D L^T)
+// lane J of each 16 lanes, to all sixteen (row_newbcast)
+template <int J>
+__device__ __forceinline__ double row_bcast(double x) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)u, 0x150 + J, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(u >> 32), 0x150 + J, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double read_lane(double x, int lane) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+template <int J>
+__device__ __forceinline__ void eliminate(double (&v)[4], double (&w)[4], int c, int g, int& bad) {
+    if constexpr (J < 16) {
+        constexpr int src = (J >> 2) * 16;                       // the lanes that hold row J
+        double d = read_lane(v[J & 3], src + J);
+        if (!(d > 0.0)) { bad |= 1 << J; d = 1.0; }
+        double inv = __builtin_amdgcn_rcp(d);                    // hardware estimate, two Newton steps
+        inv = fma(inv, fma(-d, inv, 1.0), inv);
+        inv = fma(inv, fma(-d, inv, 1.0), inv);
+        const double f = __shfl(v[J & 3], src + c) * inv, fw = __shfl(w[J & 3], src + c) * inv;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            double col = row_bcast<J>(v[i]);                     // element (4 g + i, J)
+            if (4 * g + i <= J) col = 0.0;
+            v[i] = fma(-col, f, v[i]);
+            w[i] = fma(-col, fw, w[i]);
+        }
+        eliminate<J + 1>(v, w, c, g, bad);
+    }
+}
+// Rinv <- R^-1 of the block's factor R^T R (upper triangle, zeros below).  Rows and columns from n on are padding: unit diagonal.
+// Returns nonzero (wave-uniform) on a non-positive pivot
+__device__ int factor16(const double* G, double* Rinv, int n) {
+    const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+    double v[4], w[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int row = 4 * g + i;
+        w[i] = row == c ? 1.0 : 0.0;
+        v[i] = (row < n && c < n) ? G[row * QR_LD + c] : w[i];
+    }
+    int bad = 0;
+    eliminate<0>(v, w, c, g, bad);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int row = 4 * g + i;
+        double piv = __shfl(v[i], g * 16 + row);
+        if ((bad >> row) & 1) piv = 1.0;
+        // 1/sqrt(piv): hardware estimate refined by two Newton steps (full fp64 accuracy, no divide)
+        double rs = __builtin_amdgcn_rsq(piv);
+        rs = rs * fma(-0.5 * piv * rs, rs, 1.5);
+        rs = rs * fma(-0.5 * piv * rs, rs, 1.5);
+        Rinv[c * QR_LD + row] = c <= row ? w[i] * rs : 0.0;      // D^-1/2 L^-1, transposed
+    }
     return bad;
 }
 
-// Gram partial of the block's rows (fp64 in LDS: Ys[row][ld], zero padded to a multiple of 4 rows and rp
-// columns) with the fp64 matrix cores, written to partial[blockIdx.x][rp][rp].
-__device__ void gram_partial(const double* Ys, int ld, int rows_pad, int rp, double* partial, uint32_t bx) {
+// The workgroup turns the upper blocks of G = R^T R (LDS) into those of R^-1 (LDS), G's being overwritten.  Nonzero (the same
+// in every thread) on a non-positive pivot
+template <int RP>
+__device__ int factor_inverse(double* G, double* Rinv, int r) {
+    typedef QrShape<RP> Q;
+    __shared__ int bad_s;
+    const int tid = threadIdx.x, wave = tid >> 6;
+    if (tid == 0) bad_s = 0;
+    const doublex4 zero = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+    for (int p = 0; p < Q::NB; ++p) {
+        __syncthreads();
+        if (wave == 0) {
+            const int bad = factor16(G + Q::pair(p, p) * QR_BLK, Rinv + Q::pair(p, p) * QR_BLK, min(16, r - 16 * p));
+            if (bad && tid == 0) bad_s = 1;
+        }
+        __syncthreads();
+        if (p + 1 < Q::NB) {
+            const int q = p + 1 + wave;                          // panel: R_pq = R_pp^-T G_pq
+            if (q < Q::NB) {
+                double* blk = G + Q::pair(p, q) * QR_BLK;
+                put_block(blk, mul_tn(Rinv + Q::pair(p, p) * QR_BLK, blk, zero, false));
+            }
+            __syncthreads();
+            int job = 0;                                         // trailing blocks: G_ab -= R_pa^T R_pb
+            for (int a = p + 1; a < Q::NB; ++a)
+                for (int b = a; b < Q::NB; ++b, ++job) {
+                    if (job % Q::WAVES != wave) continue;
+                    double* blk = G + Q::pair(a, b) * QR_BLK;
+                    put_block(blk, mul_tn(G + Q::pair(p, a) * QR_BLK, G + Q::pair(p, b) * QR_BLK, get_block(blk), true));
+                }
+        }
+    }
+#pragma unroll 1
+    for (int dist = 1; dist < Q::NB; ++dist) {                   // R^-1_pq = -R^-1_pp sum over p < k <= q of R_pk R^-1_kq
+        const int p = wave, q = p + dist;
+        if (q < Q::NB) {
+            doublex4 t = zero;
+            for (int k = p + 1; k <= q; ++k) t = mul_nn(G + Q::pair(p, k) * QR_BLK, Rinv + Q::pair(k, q) * QR_BLK, t, false);
+            double* blk = Rinv + Q::pair(p, q) * QR_BLK;
+            put_block(blk, t);
+            put_block(blk, mul_nn(Rinv + Q::pair(p, p) * QR_BLK, blk, zero, true));
+        }
+        __syncthreads();
+    }
+    return bad_s;
+}
+
+// Gram partial of the block's rows (LDS: Ys[row][LD], zero padded to QR_ROWS rows and RP columns; rows_pad: its rows up to a
+// multiple of 4), written to
+// partial[bx] as the 16 x 16 blocks of the upper triangle
+template <int RP, typename T>
+__device__ void gram_partial(const T* Ys, int rows_pad, double* partial, uint32_t bx) {
+    typedef QrShape<RP> Q;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int nb = rp / 16;
-    // operand lane layout of the 16x16x4 fp64 MFMA: lane l supplies element (l % 16, k = l / 16) of both A (rows =
-    // Gram row) and B; D (measured on gfx950): register i of lane l is row 4*i + l/16, column l % 16
-    if (nb == 1) {
+    double* out = partial + (int64_t)bx * Q::PAIRS * 256;
+    if constexpr (Q::NB == 1) {
         // a single 16 x 16 block: the four waves split the rows (a lone wave would walk all of them through a chain
         // of dependent MFMAs) and their sums are added in wave order
         __shared__ double quarter[4][256];
@@ -79,93 +217,121 @@ __device__ void gram_partial(const double* Ys, int ld, int rows_pad, int rp, dou
         const int k_begin = min(wave * chunk, rows_pad), k_end = min(k_begin + chunk, rows_pad);
         doublex4 acc = {0.0, 0.0, 0.0, 0.0};
         for (int k0 = k_begin; k0 < k_end; k0 += 4) {
-            const double a = Ys[(k0 + (lane >> 4)) * ld + (lane & 15)];
+            const double a = (double)Ys[(k0 + (lane >> 4)) * Q::LD + (lane & 15)];
             acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, a, acc, 0, 0, 0);
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) quarter[wave][(4 * i + (lane >> 4)) * 16 + (lane & 15)] = acc[i];
         __syncthreads();
-        partial[(int64_t)bx * 256 + tid] = (quarter[0][tid] + quarter[1][tid]) + (quarter[2][tid] + quarter[3][tid]);
-        return;
-    }
-    // block pair (bi, bj) of the Gram matrix per wave, round robin
-    for (int blk = wave; blk < nb * nb; blk += 4) {
-        const int bi = blk / nb, bj = blk % nb;
-        doublex4 acc = {0.0, 0.0, 0.0, 0.0};
-        for (int k0 = 0; k0 < rows_pad; k0 += 4) {
-            const double a = Ys[(k0 + (lane >> 4)) * ld + bi * 16 + (lane & 15)];
-            const double b = Ys[(k0 + (lane >> 4)) * ld + bj * 16 + (lane & 15)];
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-        }
+        out[tid] = (quarter[0][tid] + quarter[1][tid]) + (quarter[2][tid] + quarter[3][tid]);
+    } else {
+        int job = 0;
+        for (int a = 0; a < Q::NB; ++a)
+            for (int b = a; b < Q::NB; ++b, ++job) {
+                if (job % Q::WAVES != wave) continue;
+                doublex4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
+                for (int k0 = 0; k0 < QR_ROWS; k0 += 4) {
+                    const T* row = Ys + (k0 + (lane >> 4)) * Q::LD + (lane & 15);
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)row[16 * a], (double)row[16 * b], acc, 0, 0, 0);
+                }
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            partial[((int64_t)bx * rp + bi * 16 + 4 * i + (lane >> 4)) * rp + bj * 16 + (lane & 15)] = acc[i];
+                for (int i = 0; i < 4; ++i) out[Q::pair(a, b) * 256 + (4 * i + (lane >> 4)) * 16 + (lane & 15)] = acc[i];
+            }
     }
 }
 
-// Every block: Gs <- sum over blocks of partial (block order, up to 32 loads in flight), then the workgroup factors
-// it in place (upper factor, reciprocal diagonal).  Block 0 reports a bad pivot.
-__device__ void reduce_and_factor(const double* partial, int nblk, double* Gs, int r, int rp, int* flag, uint32_t bx) {
+// Every block: sum over blocks of partial (block order, up to 32 loads of a thread in flight), then the workgroup factors
+// it -> R^-1.  Block 0 reports a bad pivot.  smem: FACTOR_SMEM bytes; returns R^-1's blocks in it
+template <int RP>
+__device__ const double* reduce_and_factor(const double* partial, int nblk, double* smem, int r, int* flag, uint32_t bx) {
+    typedef QrShape<RP> Q;
+    constexpr int VEC = Q::NB == 1 ? 1 : 2, SIZE = Q::PAIRS * 256;
+    typedef double vec_t __attribute__((ext_vector_type(VEC)));
     const int tid = threadIdx.x;
-    for (int e = tid; e < rp * rp; e += blockDim.x) {
-        double sum = 0.0;
+    for (int e = tid; e < SIZE / VEC; e += Q::THREADS) {
+        vec_t sum = 0.0;
+        const vec_t* src = reinterpret_cast<const vec_t*>(partial) + e;
         for (int b0 = 0; b0 < nblk; b0 += 32) {
-            double v[32];
+            vec_t v[32];
 #pragma unroll
-            for (int u = 0; u < 32; ++u) v[u] = (b0 + u < nblk) ? partial[(int64_t)(b0 + u) * rp * rp + e] : 0.0;
+            for (int u = 0; u < 32; ++u) v[u] = (b0 + u < nblk) ? src[(int64_t)(b0 + u) * (SIZE / VEC)] : (vec_t)0.0;
 #pragma unroll
             for (int u = 0; u < 32; ++u) sum += v[u];
         }
-        Gs[e] = sum;
+        const int at = e * VEC, blk = at >> 8, row = (at >> 4) & 15, col = at & 15;
+        double* dst = smem + blk * QR_BLK + row * QR_LD + col;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) dst[i] = sum[i];
     }
-    __syncthreads();
-    const int bad = chol_block(Gs, r, rp);
+    double* Rinv = smem + Q::PAIRS * QR_BLK;
+    const int bad = factor_inverse<RP>(smem, Rinv, r);
     if (bad && tid == 0 && bx == 0) *flag = 1;
+    if (Q::NB == 1) __syncthreads();
+    return Rinv;
 }
 
-// the block's input row of this thread, requested before the reduction and factorisation so that its memory latency
-// runs under them (RP is a compile-time bound, so the row lives in registers)
+// the wave's rows of Y as operands (row l mod 16 of a 16-row block, columns l / 16 + 4 s of a column block), requested before
+// the reduction and factorisation so that the memory latency runs under them
 template <int RP, typename Tin>
-__device__ __forceinline__ void load_row_t(const Tin* y, int r, bool active, Tin (&v)[RP]) {
+__device__ __forceinline__ void load_rows(const Tin* __restrict__ Y, int64_t i0, int rows, int r, Tin (&y)[QrShape<RP>::RB][RP / 4]) {
+    typedef QrShape<RP> Q;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-    for (int c = 0; c < RP; ++c) v[c] = (active && c < r) ? y[c] : (Tin)0;
-}
-
-// row <- row R^-1 for upper-triangular R held in LDS with reciprocal diagonal (forward substitution);
-// the row stays in registers, R is read with broadcast loads
-template <int RP, typename Tin>
-__device__ __forceinline__ void solve_row_t(const Tin (&y)[RP], const double* Rl, double* q_out) {
-    double q[RP];
+    for (int b = 0; b < Q::RB; ++b) {
+        const int row = (wave * Q::RB + b) * 16 + (lane & 15);
 #pragma unroll
-    for (int c = 0; c < RP; ++c) {
-        double s = (double)y[c];
-#pragma unroll
-        for (int k = 0; k < c; ++k) s = fma(-q[k], Rl[k * RP + c], s);
-        q[c] = s * Rl[c * RP + c];
+        for (int s = 0; s < RP / 4; ++s) {
+            const int col = 4 * s + (lane >> 4);
+            y[b][s] = (row < rows && col < r) ? Y[(i0 + row) * r + col] : (Tin)0;
+        }
     }
+}
+// column block q of a 16-row block of Y R^-1 (rows and columns as D lays them out)
+template <int RP, typename Tin>
+__device__ __forceinline__ doublex4 apply_rinv(const Tin (&y)[RP / 4], const double* Rinv, int q) {
+    typedef QrShape<RP> Q;
+    const int lane = threadIdx.x & 63, at = (lane >> 4) * QR_LD + (lane & 15);
+    doublex4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int c = 0; c < RP; ++c) q_out[c] = q[c];
+    for (int p = 0; p < Q::NB; ++p) {
+        if (p > q) break;
+        const double* blk = Rinv + Q::pair(p, q) * QR_BLK + at;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)y[4 * p + s], blk[4 * s * QR_LD], acc, 0, 0, 0);
+    }
+    return acc;
 }
 
-// launch 1.  Input: S fp32 [d][r], or (splits != nullptr) partial sketches [nsplit][d][rp] whose sum is
-// stored to S_out as fp32 and used (in its rounded form) for the factorisation.
-__device__ __forceinline__ void qr_gram_body(const float* __restrict__ S, const float* __restrict__ splits, int nsplit,
-                                             float* __restrict__ S_out, int64_t d, int r, int rp,
-                                             double* __restrict__ partial, uint32_t bx) {
-    extern __shared__ __align__(16) double qr_smem[];
-    const int ld = rp + 1;
-    double* Ys = qr_smem;                 // [QR_ROWS][ld]
-    const int tid = threadIdx.x;
-    const int64_t i0 = (int64_t)bx * QR_ROWS;
+// per problem, what the launches of one factorisation need.  Input: S fp32 [d][r], or (splits != nullptr) partial sketches
+// [nsplit][d][rp] whose sum is stored to S_out as fp32 and used (in its rounded form) for the factorisation
+struct QrDev {
+    const float* S; const float* splits; int nsplit; float* S_out; const float* Sin;
+    int64_t d; int r; int nblk;
+    double *Q1, *partial1, *partial2;
+    float* Q; bf16_t* planes;
+};
+
+// launch 1
+template <int RP, int CAP>
+__global__ __launch_bounds__(QrShape<RP>::THREADS) void qr_gram_kernel(const KBatch<QrDev, CAP> tb) {
+    typedef QrShape<RP> Q;
+    extern __shared__ __align__(16) char qr_smem[];
+    uint32_t bx, by;
+    const QrDev& a = tb.a[kbatch_find(tb, bx, by)];
+    float* Ys = reinterpret_cast<float*>(qr_smem);               // [QR_ROWS][LD]
+    const int tid = threadIdx.x, r = a.r, nsplit = a.nsplit;
+    const int64_t d = a.d, i0 = (int64_t)bx * QR_ROWS;
     const int rows = (int)min((int64_t)QR_ROWS, d - i0);
     const int rows_pad = (rows + 3) & ~3;
-    if (splits != nullptr) {
+    if (a.splits != nullptr) {
         // sum of the partial sketches: a block's rows are one contiguous run of rows * rp floats in every split, so the
         // loads are plain 16-byte vectors, all splits of a vector in flight together (fp64 sum in split order)
-        const int nvec = rows * rp / 4, total_vec = rows_pad * rp / 4;
-        const float* base = splits + i0 * rp;
+        const int nvec = rows * RP / 4, total_vec = QR_ROWS * RP / 4;
+        const float* base = a.splits + i0 * RP;
+        float* S_out = a.S_out;
         auto finish = [&](int v, const double (&acc)[4]) {
-            const int i = (v * 4) / rp, k0 = (v * 4) % rp;
+            const int i = (v * 4) / RP, k0 = (v * 4) % RP;
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 float f = 0.f;
@@ -173,350 +339,258 @@ __device__ __forceinline__ void qr_gram_body(const float* __restrict__ S, const 
                     f = (float)acc[c];
                     S_out[(i0 + i) * r + k0 + c] = f;
                 }
-                Ys[i * ld + k0 + c] = (double)f;
+                Ys[i * Q::LD + k0 + c] = f;
             }
         };
-        // two vectors per thread and pass, so that at rp = 16 a thread has all its loads in flight at once (the kernel
-        // is bound by the latency of these loads: the partials were written by the other XCDs)
-        for (int v0 = tid; v0 < total_vec; v0 += 512) {
-            const int v1 = v0 + 256;
-            double acc0[4] = {0.0, 0.0, 0.0, 0.0}, acc1[4] = {0.0, 0.0, 0.0, 0.0};
+        // (at RP = 16 two vectors per thread, so that it has all its loads in flight at once: the kernel is bound by the
+        // latency of these loads, the partials were written by the other XCDs)
+        constexpr int VPT = Q::NB == 1 ? 2 : 1;
+        for (int v0 = tid; v0 < total_vec; v0 += VPT * Q::THREADS) {
+            double acc[VPT][4] = {};
             for (int sp0 = 0; sp0 < nsplit; sp0 += 16) {
-                float4 x0[16], x1[16];
+                float4 x[VPT][16];
 #pragma unroll
                 for (int u = 0; u < 16; ++u) {
-                    const float4* src = reinterpret_cast<const float4*>(base + (int64_t)(sp0 + u) * d * rp);
-                    x0[u] = (v0 < nvec && sp0 + u < nsplit) ? src[v0] : make_float4(0.f, 0.f, 0.f, 0.f);
-                    x1[u] = (v1 < nvec && sp0 + u < nsplit) ? src[v1] : make_float4(0.f, 0.f, 0.f, 0.f);
+                    const float4* src = reinterpret_cast<const float4*>(base + (int64_t)(sp0 + u) * d * RP);
+#pragma unroll
+                    for (int k = 0; k < VPT; ++k) {
+                        const int v = v0 + k * Q::THREADS;
+                        x[k][u] = (v < nvec && sp0 + u < nsplit) ? src[v] : make_float4(0.f, 0.f, 0.f, 0.f);
+                    }
                 }
 #pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    acc0[0] += (double)x0[u].x; acc0[1] += (double)x0[u].y;
-                    acc0[2] += (double)x0[u].z; acc0[3] += (double)x0[u].w;
-                    acc1[0] += (double)x1[u].x; acc1[1] += (double)x1[u].y;
-                    acc1[2] += (double)x1[u].z; acc1[3] += (double)x1[u].w;
-                }
+                for (int u = 0; u < 16; ++u)
+#pragma unroll
+                    for (int k = 0; k < VPT; ++k) {
+                        acc[k][0] += (double)x[k][u].x; acc[k][1] += (double)x[k][u].y;
+                        acc[k][2] += (double)x[k][u].z; acc[k][3] += (double)x[k][u].w;
+                    }
             }
-            finish(v0, acc0);
-            if (v1 < total_vec) finish(v1, acc1);
+#pragma unroll
+            for (int k = 0; k < VPT; ++k)
+                if (v0 + k * Q::THREADS < total_vec) finish(v0 + k * Q::THREADS, acc[k]);
         }
     } else {
-        for (int e = tid; e < rows_pad * rp; e += 256) {
-            const int i = e / rp, k = e % rp;
-            const float v = (i < rows && k < r) ? S[(i0 + i) * r + k] : 0.f;
-            Ys[i * ld + k] = (double)v;
+        for (int e = tid; e < QR_ROWS * RP; e += Q::THREADS) {
+            const int i = e / RP, k = e % RP;
+            Ys[i * Q::LD + k] = (i < rows && k < r) ? a.S[(i0 + i) * r + k] : 0.f;
         }
     }
     __syncthreads();
-    gram_partial(Ys, ld, rows_pad, rp, partial, bx);
+    gram_partial<RP>(Ys, rows_pad, a.partial1, bx);
 }
 
-__global__ __launch_bounds__(256) void qr_gram_kernel(const float* __restrict__ S, const float* __restrict__ splits,
-                                                      int nsplit, float* __restrict__ S_out, int64_t d, int r, int rp,
-                                                      double* __restrict__ partial) {
-    qr_gram_body(S, splits, nsplit, S_out, d, r, rp, partial, blockIdx.x);
-}
-
-// several factorisations per launch: per problem, what the three launches of one factorisation need
-struct QrDev {
-    const float* S; const float* splits; int nsplit; float* S_out; const float* Sin;
-    int64_t d; int r; int nblk;
-    double *Q1, *partial1, *partial2;
-    float* Q; bf16_t* planes;
-};
-__global__ __launch_bounds__(256) void qr_gram_many_kernel(const KBatch<QrDev> tb, int rp) {
+// launch 2: R1^-1 from the partials, Q1 = S R1^-1 for the block's rows (fp64, stored), Gram partials of Q1.
+template <int RP, int CAP>
+__global__ __launch_bounds__(QrShape<RP>::THREADS) void qr_apply_gram_kernel(const KBatch<QrDev, CAP> tb, int* flag) {
+    typedef QrShape<RP> Q;
+    extern __shared__ __align__(16) char qr_smem[];
     uint32_t bx, by;
     const QrDev& a = tb.a[kbatch_find(tb, bx, by)];
-    qr_gram_body(a.S, a.splits, a.nsplit, a.S_out, a.d, a.r, rp, a.partial1, bx);
-}
-
-// launch 2: R1 from the partials, Q1 = S R1^-1 for the block's rows (fp64, stored), Gram partials of Q1.
-template <int RP>
-__device__ __forceinline__ void qr_apply_gram_body(const float* __restrict__ S, int64_t d, int r,
-                                                   const double* __restrict__ partial1, int nblk,
-                                                   double* __restrict__ Q1, double* __restrict__ partial2, int* flag,
-                                                   uint32_t bx) {
-    extern __shared__ __align__(16) double qr_smem[];
-    constexpr int rp = RP;
-    const int ld = rp + 1;
-    double* Ys = qr_smem;
-    double* Gs = qr_smem + QR_ROWS * ld;
-    const int tid = threadIdx.x;
+    double* Gs = reinterpret_cast<double*>(qr_smem);
+    double* Ys = reinterpret_cast<double*>(qr_smem + Q::FACTOR_SMEM);      // [QR_ROWS][LD]
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = a.r;
     const int64_t i0 = (int64_t)bx * QR_ROWS;
-    const int rows = (int)min((int64_t)QR_ROWS, d - i0);
-    const int rows_pad = (rows + 3) & ~3;
-    float y[RP];
-    load_row_t<RP>(S + (i0 + min(tid, rows - 1)) * r, r, tid < rows, y);
-    for (int e = tid; e < rows_pad * ld; e += 256) Ys[e] = 0.0;
-    reduce_and_factor(partial1, nblk, Gs, r, rp, flag, bx);
-    if (tid < rows) {
-        double* q = Ys + tid * ld;
-        solve_row_t<RP>(y, Gs, q);
-        for (int c = 0; c < r; ++c) Q1[(i0 + tid) * r + c] = q[c];
-    }
+    const int rows = (int)min((int64_t)QR_ROWS, a.d - i0);
+    float y[Q::RB][RP / 4];
+    load_rows<RP>(a.Sin, i0, rows, r, y);
+    const double* Rinv = reduce_and_factor<RP>(a.partial1, a.nblk, Gs, r, flag, bx);
+#pragma unroll
+    for (int b = 0; b < Q::RB; ++b)
+#pragma unroll
+        for (int q = 0; q < Q::NB; ++q) {
+            const doublex4 v = apply_rinv<RP>(y[b], Rinv, q);
+            const int col = 16 * q + (lane & 15);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int row = (wave * Q::RB + b) * 16 + 4 * i + (lane >> 4);
+                Ys[row * Q::LD + col] = v[i];                              // (rows past the end, padding columns: zero)
+                if (row < rows && col < r) a.Q1[(i0 + row) * r + col] = v[i];
+            }
+        }
     __syncthreads();
-    gram_partial(Ys, ld, rows_pad, rp, partial2, bx);
+    gram_partial<RP>(Ys, (rows + 3) & ~3, a.partial2, bx);
 }
 
-template <int RP>
-__global__ __launch_bounds__(256) void qr_apply_gram_kernel(const float* __restrict__ S, int64_t d, int r,
-                                                            const double* __restrict__ partial1, int nblk,
-                                                            double* __restrict__ Q1, double* __restrict__ partial2,
-                                                            int* flag) {
-    qr_apply_gram_body<RP>(S, d, r, partial1, nblk, Q1, partial2, flag, blockIdx.x);
-}
-
-template <int RP>
-__global__ __launch_bounds__(256) void qr_apply_gram_many_kernel(const KBatch<QrDev> tb, int* flag) {
+// launch 3: Q = Q1 R2^-1, rounded to fp32; planes (nullable, d % 8 == 0) receive the hi/mid/lo bf16 parts [3][rp][d].
+// DOUBLE_IN: second pass of CholeskyQR2 (input Q1, partials of Q1); otherwise the single-pass form, Q = Y R1^-1 straight from
+// launch 1's partials
+template <int RP, bool DOUBLE_IN, int CAP>
+__global__ __launch_bounds__(QrShape<RP>::THREADS) void qr_apply_final_kernel(const KBatch<QrDev, CAP> tb, int* flag) {
+    typedef QrShape<RP> Q;
+    extern __shared__ __align__(16) char qr_smem[];
     uint32_t bx, by;
     const QrDev& a = tb.a[kbatch_find(tb, bx, by)];
-    qr_apply_gram_body<RP>(a.Sin, a.d, a.r, a.partial1, a.nblk, a.Q1, a.partial2, flag, bx);
-}
-
-// launch 3: Q = Q1 R2^-1, rounded to fp32; planes (nullable) receive the hi/mid/lo bf16 parts [3][rp][d].
-// With Tin = float the same kernel closes a single-pass factorisation: Q = Y R1^-1 straight from launch 1's partials.
-template <int RP, typename Tin>
-__device__ __forceinline__ void qr_apply_final_body(const Tin* __restrict__ Q1, int64_t d, int r,
-                                                    const double* __restrict__ partial2, int nblk,
-                                                    float* __restrict__ Q, bf16_t* __restrict__ planes, int* flag,
-                                                    uint32_t bx) {
-    extern __shared__ __align__(16) double qr_smem[];
-    constexpr int rp = RP;
-    const int ld = rp + 1;
-    double* Gs = qr_smem;                 // [rp][rp]
-    double* Qs = qr_smem + rp * rp;       // [QR_ROWS][ld]
-    const int tid = threadIdx.x;
-    const int64_t i0 = (int64_t)bx * QR_ROWS;
+    double* Gs = reinterpret_cast<double*>(qr_smem);
+    float* Qt = reinterpret_cast<float*>(qr_smem + Q::FACTOR_SMEM);        // [RP][PLANE_LD], transposed
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = a.r;
+    const int64_t i0 = (int64_t)bx * QR_ROWS, d = a.d;
     const int rows = (int)min((int64_t)QR_ROWS, d - i0);
-    Tin y[RP];
-    load_row_t<RP>(Q1 + (i0 + min(tid, rows - 1)) * r, r, tid < rows, y);
-    reduce_and_factor(partial2, nblk, Gs, r, rp, flag, bx);
-    if (tid < rows) {
-        double* q = Qs + tid * ld;
-        solve_row_t<RP>(y, Gs, q);
-        for (int c = 0; c < r; ++c) Q[(i0 + tid) * r + c] = (float)q[c];
-        for (int c = r; c < rp; ++c) q[c] = 0.0;
-    }
-    if (planes == nullptr) return;
+    typename std::conditional<DOUBLE_IN, double, float>::type y[Q::RB][RP / 4];
+    if constexpr (DOUBLE_IN) load_rows<RP>(a.Q1, i0, rows, r, y);
+    else load_rows<RP>(a.Sin, i0, rows, r, y);
+    const double* Rinv = reduce_and_factor<RP>(DOUBLE_IN ? a.partial2 : a.partial1, a.nblk, Gs, r, flag, bx);
+#pragma unroll
+    for (int b = 0; b < Q::RB; ++b)
+#pragma unroll
+        for (int q = 0; q < Q::NB; ++q) {
+            const doublex4 v = apply_rinv<RP>(y[b], Rinv, q);
+            const int col = 16 * q + (lane & 15);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int row = (wave * Q::RB + b) * 16 + 4 * i + (lane >> 4);
+                const float f = col < r ? (float)v[i] : 0.f;
+                Qt[col * Q::PLANE_LD + row] = f;
+                if (row < rows && col < r) a.Q[(i0 + row) * r + col] = f;
+            }
+        }
+    if (a.planes == nullptr) return;
     __syncthreads();
-    // row index fastest so that the plane stores (row-contiguous per k) coalesce
-    for (int e = tid; e < QR_ROWS * rp; e += 256) {
-        const int i = e % QR_ROWS, c = e / QR_ROWS;
+    // eight rows of one column and plane per thread and pass: 16-byte stores
+    for (int e = tid; e < RP * (QR_ROWS / 8); e += Q::THREADS) {
+        const int i = (e % (QR_ROWS / 8)) * 8, c = e / (QR_ROWS / 8);
         if (i >= rows) continue;
-        bf16_t hi, mid, lo;
-        split3_bf16((float)Qs[i * ld + c], hi, mid, lo);
-        planes[((int64_t)0 * rp + c) * d + i0 + i] = hi;
-        planes[((int64_t)1 * rp + c) * d + i0 + i] = mid;
-        planes[((int64_t)2 * rp + c) * d + i0 + i] = lo;
+        uint32_t w[3][4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            bf16_t h[2], m[2], l[2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) split3_bf16(Qt[c * Q::PLANE_LD + i + 2 * u + k], h[k], m[k], l[k]);
+            w[0][u] = (uint32_t)h[0] | ((uint32_t)h[1] << 16);
+            w[1][u] = (uint32_t)m[0] | ((uint32_t)m[1] << 16);
+            w[2][u] = (uint32_t)l[0] | ((uint32_t)l[1] << 16);
+        }
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl)
+            *reinterpret_cast<uint4*>(a.planes + ((int64_t)pl * RP + c) * d + i0 + i) = make_uint4(w[pl][0], w[pl][1], w[pl][2], w[pl][3]);
     }
-}
-
-template <int RP, typename Tin>
-__global__ __launch_bounds__(256) void qr_apply_final_kernel(const Tin* __restrict__ Q1, int64_t d, int r,
-                                                             const double* __restrict__ partial2, int nblk,
-                                                             float* __restrict__ Q, bf16_t* __restrict__ planes,
-                                                             int* flag) {
-    qr_apply_final_body<RP, Tin>(Q1, d, r, partial2, nblk, Q, planes, flag, blockIdx.x);
-}
-
-// DOUBLE_IN: second pass of CholeskyQR2 (input Q1, partials of Q1); otherwise the single-pass form (input Y)
-template <int RP, bool DOUBLE_IN>
-__global__ __launch_bounds__(256) void qr_apply_final_many_kernel(const KBatch<QrDev> tb, int* flag) {
-    uint32_t bx, by;
-    const QrDev& a = tb.a[kbatch_find(tb, bx, by)];
-    if constexpr (DOUBLE_IN) qr_apply_final_body<RP, double>(a.Q1, a.d, a.r, a.partial2, a.nblk, a.Q, a.planes, flag, bx);
-    else qr_apply_final_body<RP, float>(a.Sin, a.d, a.r, a.partial1, a.nblk, a.Q, a.planes, flag, bx);
 }
 
 // ---- r = 1 (the paper's operating point): the thin QR of a single column with a positive diagonal is the column
 // divided by its norm, so the orthonormalisation is a sum of squares and a scaling: two small launches, no Gram
 // matrix, no factorisation, and nothing for a second pass to refine.
-constexpr int QR1_ROWS = 1024;   // rows per workgroup (4 per thread)
+constexpr int QR1_ROWS = 256;    // rows per workgroup, one per thread: the chain of loads is what takes the time
 
 // launch 1: y_i = the column (or the fp64 sum of its partial sketches in split order, rounded to fp32 and stored to
 // S_out like the general path does), partial[b] = sum of y_i^2 over the block's rows (fp64, fixed order)
-__device__ __forceinline__ void qr1_sumsq_body(const float* __restrict__ S, const float* __restrict__ splits, int nsplit, int rp,
-                                               float* __restrict__ S_out, int64_t d, double* __restrict__ partial, uint32_t bx) {
+template <int CAP>
+__global__ __launch_bounds__(256) void qr1_sumsq_kernel(const KBatch<QrDev, CAP> tb, int rp) {
     __shared__ double red[4];
+    uint32_t bx, by;
+    const QrDev& a = tb.a[kbatch_find(tb, bx, by)];
     const int tid = threadIdx.x;
-    double ss = 0.0;
-#pragma unroll
-    for (int u = 0; u < QR1_ROWS / 256; ++u) {
-        const int64_t i = (int64_t)bx * QR1_ROWS + u * 256 + tid;
-        if (i >= d) continue;
-        float y;
-        if (splits != nullptr) {
+    const int64_t i = (int64_t)bx * QR1_ROWS + tid;
+    float y = 0.f;
+    if (i < a.d) {
+        if (a.splits != nullptr) {
             double acc = 0.0;
-            for (int sp = 0; sp < nsplit; ++sp) acc += (double)splits[((int64_t)sp * d + i) * rp];
+            for (int sp0 = 0; sp0 < a.nsplit; sp0 += 16) {
+                float x[16];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) x[u] = sp0 + u < a.nsplit ? a.splits[((int64_t)(sp0 + u) * a.d + i) * rp] : 0.f;
+#pragma unroll
+                for (int u = 0; u < 16; ++u) acc += (double)x[u];
+            }
             y = (float)acc;
-            S_out[i] = y;
+            a.S_out[i] = y;
         } else {
-            y = S[i];
+            y = a.S[i];
         }
-        ss = fma((double)y, (double)y, ss);
     }
+    double ss = (double)y * (double)y;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
     if ((tid & 63) == 0) red[tid >> 6] = ss;
     __syncthreads();
-    if (tid == 0) partial[bx] = (red[0] + red[1]) + (red[2] + red[3]);
+    if (tid == 0) a.partial1[bx] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
 // launch 2: q = y / sqrt(sum of the partials) -> Q fp32 [d][1] and, if asked, the bf16 planes [3][rp][d] (rows of the
-// padding columns zero).  A sum that is not positive (an all-zero sketch) raises the numeric flag.
-__device__ __forceinline__ void qr1_scale_body(const float* __restrict__ Y, int64_t d, int rp, const double* __restrict__ partial,
-                                               int nblk, float* __restrict__ Q, bf16_t* __restrict__ planes, int* flag,
-                                               uint32_t bx) {
+// padding columns zero; d % 8 == 0).  A sum that is not positive (an all-zero sketch) raises the numeric flag.
+template <int CAP>
+__global__ __launch_bounds__(256) void qr1_scale_kernel(const KBatch<QrDev, CAP> tb, int rp, int* flag) {
+    uint32_t bx, by;
+    const QrDev& a = tb.a[kbatch_find(tb, bx, by)];
     const int tid = threadIdx.x;
+    const int64_t i0 = (int64_t)bx * QR1_ROWS, i = i0 + tid;
+    const float y = i < a.d ? a.Sin[i] : 0.f;
     double sum = 0.0;
-    for (int b = 0; b < nblk; ++b) sum += partial[b];          // uniform: every thread adds the same few values
+    for (int b0 = 0; b0 < a.nblk; b0 += 16) {                  // uniform: every thread adds the same values
+        double v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = b0 + u < a.nblk ? a.partial1[b0 + u] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) sum += v[u];
+    }
     if (!(sum > 0.0)) {
         if (tid == 0 && bx == 0) *flag = 1;
         sum = 1.0;
     }
-    const double inv = 1.0 / sqrt(sum);
+    const float q = (float)((double)y * (1.0 / sqrt(sum)));
+    if (i < a.d) a.Q[i] = q;
+    if (a.planes == nullptr) return;
+    if (i < a.d) {
+        bf16_t part[3];
+        split3_bf16(q, part[0], part[1], part[2]);
 #pragma unroll
-    for (int u = 0; u < QR1_ROWS / 256; ++u) {
-        const int64_t i = (int64_t)bx * QR1_ROWS + u * 256 + tid;
-        if (i >= d) continue;
-        const float q = (float)((double)Y[i] * inv);
-        Q[i] = q;
-        if (planes != nullptr) {
-            bf16_t hi, mid, lo;
-            split3_bf16(q, hi, mid, lo);
-            planes[((int64_t)0 * rp) * d + i] = hi;
-            planes[((int64_t)1 * rp) * d + i] = mid;
-            planes[((int64_t)2 * rp) * d + i] = lo;
-            for (int c = 1; c < rp; ++c) {
-                planes[((int64_t)0 * rp + c) * d + i] = 0;
-                planes[((int64_t)1 * rp + c) * d + i] = 0;
-                planes[((int64_t)2 * rp + c) * d + i] = 0;
-            }
-        }
+        for (int pl = 0; pl < 3; ++pl) a.planes[(int64_t)pl * rp * a.d + i] = part[pl];
     }
-}
-
-__global__ __launch_bounds__(256) void qr1_sumsq_kernel(const float* __restrict__ S, const float* __restrict__ splits, int nsplit,
-                                                        int rp, float* __restrict__ S_out, int64_t d, double* __restrict__ partial) {
-    qr1_sumsq_body(S, splits, nsplit, rp, S_out, d, partial, blockIdx.x);
-}
-__global__ __launch_bounds__(256) void qr1_scale_kernel(const float* __restrict__ Y, int64_t d, int rp,
-                                                        const double* __restrict__ partial, int nblk, float* __restrict__ Q,
-                                                        bf16_t* __restrict__ planes, int* flag) {
-    qr1_scale_body(Y, d, rp, partial, nblk, Q, planes, flag, blockIdx.x);
-}
-__global__ __launch_bounds__(256) void qr1_sumsq_many_kernel(const KBatch<QrDev> tb, int rp) {
-    uint32_t bx, by;
-    const QrDev& a = tb.a[kbatch_find(tb, bx, by)];
-    qr1_sumsq_body(a.S, a.splits, a.nsplit, rp, a.S_out, a.d, a.partial1, bx);
-}
-__global__ __launch_bounds__(256) void qr1_scale_many_kernel(const KBatch<QrDev> tb, int rp, int* flag) {
-    uint32_t bx, by;
-    const QrDev& a = tb.a[kbatch_find(tb, bx, by)];
-    qr1_scale_body(a.Sin, a.d, rp, a.partial1, a.nblk, a.Q, a.planes, flag, bx);
+    const int rest = rp - 1;
+    for (int e = tid; e < 3 * rest * (QR1_ROWS / 8); e += 256) {
+        const int64_t col = i0 + (e % (QR1_ROWS / 8)) * 8;
+        const int row = e / (QR1_ROWS / 8), pl = row / rest;
+        if (col < a.d) *reinterpret_cast<uint4*>(a.planes + ((int64_t)pl * rp + 1 + row - pl * rest) * a.d + col) = make_uint4(0, 0, 0, 0);
+    }
 }
 static inline int64_t qr1_blocks(int64_t d) { return (d + QR1_ROWS - 1) / QR1_ROWS; }
 
-// the launches after the first, for one padded rank (the rows' registers are sized by it)
-template <int RP>
-static hipError_t launch_apply(dim3 grid, size_t smem, hipStream_t st, const float* Sin, int64_t d, int r, const double* partial1,
-                               double* partial2, int nblk, double* Q1, float* Q, bf16_t* planes, int* numeric_flag, bool refine) {
-    static bool attr_set = false;
-    if (!attr_set) {
-        const int big = (QR_ROWS * (kMaxRank + 1) + kMaxRank * kMaxRank) * (int)sizeof(double);
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(qr_apply_gram_kernel<RP>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, big);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(qr_apply_final_kernel<RP, double>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, big);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(qr_apply_final_kernel<RP, float>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, big);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
-    const dim3 block(256);
-    if (!refine) {
-        hipLaunchKernelGGL((qr_apply_final_kernel<RP, float>), grid, block, smem, st, Sin, d, r, partial1, nblk, Q, planes, numeric_flag);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL(qr_apply_gram_kernel<RP>, grid, block, smem, st, Sin, d, r, partial1, nblk, Q1, partial2, numeric_flag);
-    {
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL((qr_apply_final_kernel<RP, double>), grid, block, smem, st, Q1, d, r, partial2, nblk, Q, planes, numeric_flag);
+template <int CAP>
+static hipError_t launch_qr1(const KBatch<QrDev, CAP>& tb, unsigned blocks, int rp, int* flag, hipStream_t st) {
+    hipLaunchKernelGGL(qr1_sumsq_kernel<CAP>, dim3(blocks), dim3(256), 0, st, tb, rp);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;      // the launch below consumes what this one would have written
+    hipLaunchKernelGGL(qr1_scale_kernel<CAP>, dim3(blocks), dim3(256), 0, st, tb, rp, flag);
     return hipGetLastError();
 }
 
-hipError_t launch_qr(const float* S, const float* splits, int nsplit, int rp, float* S_out, int64_t d, int r, float* Q,
-                     bf16_t* planes, void* workspace, int* numeric_flag, bool refine, hipStream_t st) {
-    if (d == 0) return hipSuccess;
-    if (r == 1) {
-        const int nb1 = (int)qr1_blocks(d);
-        double* part = reinterpret_cast<double*>(workspace);          // nb1 <= the d doubles reserved for Q1
-        const float* Y = splits ? S_out : S;
-        hipLaunchKernelGGL(qr1_sumsq_kernel, dim3((unsigned)nb1), dim3(256), 0, st, S, splits, nsplit, rp, S_out, d, part);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(qr1_scale_kernel, dim3((unsigned)nb1), dim3(256), 0, st, Y, d, rp, part, nb1, Q, planes, numeric_flag);
-        return hipGetLastError();
-    }
-    const int nblk = (int)qr_blocks(d);
-    double* Q1 = reinterpret_cast<double*>(workspace);
-    double* partial1 = Q1 + d * r;
-    double* partial2 = partial1 + (size_t)nblk * rp * rp;
-    dim3 grid((unsigned)nblk), block(256);
-    const size_t sm_full = ((size_t)QR_ROWS * (rp + 1) + (size_t)rp * rp) * sizeof(double);
-    const float* Sin = splits ? S_out : S;
+template <int RP, int CAP>
+static hipError_t launch_qr_rp(const KBatch<QrDev, CAP>& tb, unsigned blocks, int* flag, bool refine, hipStream_t st) {
+    typedef QrShape<RP> Q;
     static bool attr_set = false;
     if (!attr_set) {
-        const int big = (QR_ROWS * (kMaxRank + 1) + kMaxRank * kMaxRank) * (int)sizeof(double);
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(qr_gram_kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, big);
+        const auto allow = [](const void* f, size_t bytes) { return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes); };
+        hipError_t e = allow(reinterpret_cast<const void*>(qr_gram_kernel<RP, CAP>), Q::GRAM_SMEM);
+        if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(qr_apply_gram_kernel<RP, CAP>), Q::APPLY_GRAM_SMEM);
+        if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(qr_apply_final_kernel<RP, true, CAP>), Q::APPLY_FINAL_SMEM);
+        if (e == hipSuccess) e = allow(reinterpret_cast<const void*>(qr_apply_final_kernel<RP, false, CAP>), Q::APPLY_FINAL_SMEM);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    hipLaunchKernelGGL(qr_gram_kernel, grid, block, sm_full, st, S, splits, nsplit, S_out, d, r, rp, partial1);
-    {
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;      // the launches below consume what this one would have written
-    }
-    switch (rp) {
-        case 16: return launch_apply<16>(grid, sm_full, st, Sin, d, r, partial1, partial2, nblk, Q1, Q, planes, numeric_flag, refine);
-        case 32: return launch_apply<32>(grid, sm_full, st, Sin, d, r, partial1, partial2, nblk, Q1, Q, planes, numeric_flag, refine);
-        case 48: return launch_apply<48>(grid, sm_full, st, Sin, d, r, partial1, partial2, nblk, Q1, Q, planes, numeric_flag, refine);
-        case 64: return launch_apply<64>(grid, sm_full, st, Sin, d, r, partial1, partial2, nblk, Q1, Q, planes, numeric_flag, refine);
-        default: return hipErrorInvalidValue;
-    }
-}
-
-template <int RP>
-static hipError_t launch_apply_many(const KBatch<QrDev>& tb, unsigned blocks, size_t smem, int* flag, bool refine, hipStream_t st) {
-    static bool attr_set = false;
-    if (!attr_set) {
-        const int big = (QR_ROWS * (kMaxRank + 1) + kMaxRank * kMaxRank) * (int)sizeof(double);
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(qr_apply_gram_many_kernel<RP>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, big);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(qr_apply_final_many_kernel<RP, true>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, big);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(qr_apply_final_many_kernel<RP, false>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, big);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
-    const dim3 grid(blocks), block(256);
-    if (!refine) {
-        hipLaunchKernelGGL((qr_apply_final_many_kernel<RP, false>), grid, block, smem, st, tb, flag);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL(qr_apply_gram_many_kernel<RP>, grid, block, smem, st, tb, flag);
+    const dim3 grid(blocks), block(Q::THREADS);
+    hipLaunchKernelGGL((qr_gram_kernel<RP, CAP>), grid, block, Q::GRAM_SMEM, st, tb);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((qr_apply_final_many_kernel<RP, true>), grid, block, smem, st, tb, flag);
+    if (!refine) {
+        hipLaunchKernelGGL((qr_apply_final_kernel<RP, false, CAP>), grid, block, Q::APPLY_FINAL_SMEM, st, tb, flag);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL((qr_apply_gram_kernel<RP, CAP>), grid, block, Q::APPLY_GRAM_SMEM, st, tb, flag);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((qr_apply_final_kernel<RP, true, CAP>), grid, block, Q::APPLY_FINAL_SMEM, st, tb, flag);
     return hipGetLastError();
+}
+
+template <int CAP>
+static hipError_t launch_qr_cap(const KBatch<QrDev, CAP>& tb, unsigned blocks, int rp, bool rank1, int* flag, bool refine, hipStream_t st) {
+    if (rank1) return launch_qr1(tb, blocks, rp, flag, st);
+    switch (rp) {
+        case 16: return launch_qr_rp<16>(tb, blocks, flag, refine, st);
+        case 32: return launch_qr_rp<32>(tb, blocks, flag, refine, st);
+        case 48: return launch_qr_rp<48>(tb, blocks, flag, refine, st);
+        case 64: return launch_qr_rp<64>(tb, blocks, flag, refine, st);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_qr_many(const QrArgs* a, int n, int* numeric_flag, bool refine, hipStream_t st) {
@@ -535,44 +609,25 @@ hipError_t launch_qr_many(const QrArgs* a, int n, int* numeric_flag, bool refine
         q.S = a[m].S; q.splits = a[m].splits; q.nsplit = a[m].nsplit; q.S_out = a[m].S_out;
         q.Sin = a[m].splits ? a[m].S_out : a[m].S;
         q.d = a[m].d; q.r = a[m].r; q.nblk = (int)qr_blocks(a[m].d);
-        q.Q1 = reinterpret_cast<double*>(a[m].workspace);
-        q.partial1 = q.Q1 + a[m].d * a[m].r;
+        // (the partials first: their vectors are aligned whatever d and r are)
+        q.partial1 = reinterpret_cast<double*>(a[m].workspace);
         q.partial2 = q.partial1 + (size_t)q.nblk * rp * rp;
+        q.Q1 = q.partial2 + (size_t)q.nblk * rp * rp;
         q.Q = a[m].Q; q.planes = a[m].planes;
-        if (rank1 == 1) { q.nblk = (int)qr1_blocks(a[m].d); q.partial1 = q.Q1; }
+        if (rank1 == 1) q.nblk = (int)qr1_blocks(a[m].d);        // (partials: fewer than those reserved)
         tb.first[tb.n] = (uint32_t)blocks; tb.gx[tb.n] = (uint32_t)q.nblk; tb.a[tb.n++] = q;
         blocks += (uint64_t)q.nblk;
     }
     if (tb.n == 0) return hipSuccess;
     if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    if (rank1 == 1) {
-        hipLaunchKernelGGL(qr1_sumsq_many_kernel, dim3((unsigned)blocks), dim3(256), 0, st, tb, rp);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(qr1_scale_many_kernel, dim3((unsigned)blocks), dim3(256), 0, st, tb, rp, numeric_flag);
-        return hipGetLastError();
-    }
-    const size_t sm_full = ((size_t)QR_ROWS * (rp + 1) + (size_t)rp * rp) * sizeof(double);
-    static bool attr_set = false;
-    if (!attr_set) {
-        const int big = (QR_ROWS * (kMaxRank + 1) + kMaxRank * kMaxRank) * (int)sizeof(double);
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(qr_gram_many_kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, big);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
-    hipLaunchKernelGGL(qr_gram_many_kernel, dim3((unsigned)blocks), dim3(256), sm_full, st, tb, rp);
-    {
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    switch (rp) {
-        case 16: return launch_apply_many<16>(tb, (unsigned)blocks, sm_full, numeric_flag, refine, st);
-        case 32: return launch_apply_many<32>(tb, (unsigned)blocks, sm_full, numeric_flag, refine, st);
-        case 48: return launch_apply_many<48>(tb, (unsigned)blocks, sm_full, numeric_flag, refine, st);
-        case 64: return launch_apply_many<64>(tb, (unsigned)blocks, sm_full, numeric_flag, refine, st);
-        default: return hipErrorInvalidValue;
-    }
+    if (tb.n == 1) return launch_qr_cap(kbatch_one(tb), (unsigned)blocks, rp, rank1 == 1, numeric_flag, refine, st);
+    return launch_qr_cap(tb, (unsigned)blocks, rp, rank1 == 1, numeric_flag, refine, st);
+}
+
+hipError_t launch_qr(const float* S, const float* splits, int nsplit, int rp, float* S_out, int64_t d, int r, float* Q,
+                     bf16_t* planes, void* workspace, int* numeric_flag, bool refine, hipStream_t st) {
+    const QrArgs a{S, splits, nsplit, rp, S_out, d, r, Q, planes, workspace};
+    return launch_qr_many(&a, 1, numeric_flag, refine, st);
 }
 
 }  // namespace agzo

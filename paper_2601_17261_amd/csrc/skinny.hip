@@ -212,22 +212,15 @@ __device__ __forceinline__ void xq_bf16_body(const bf16_t* __restrict__ X, int64
     }
 }
 
-template <int NB>
-__global__ __launch_bounds__(256) void xq_bf16_kernel(const bf16_t* __restrict__ X, int64_t ldx, int64_t M, int64_t K,
-                                                      const bf16_t* __restrict__ Qpack, int r, float* __restrict__ T,
-                                                      bf16_t* __restrict__ TpackT, int64_t m_pad, float* __restrict__ part) {
-    xq_bf16_body<NB, true>(X, ldx, M, K, Qpack, r, T, TpackT, m_pad, part, blockIdx.x, blockIdx.y, gridDim.y);
-}
-
-// several products per launch (the layers of a model): what one launch of the kernel above needs, per product
+// what a launch needs per product (the layers of a model)
 struct XqDev {
     const bf16_t* X; int64_t ldx, M, K;
     const bf16_t* Qpack; int r;
     float* T; bf16_t* TpackT; int64_t m_pad; float* part;   // part: NULL unless ns > 1
     int ns; int64_t rows;
 };
-template <int NB, bool DEEP>
-__global__ __launch_bounds__(256) void xq_bf16_many_kernel(const KBatch<XqDev> tb) {
+template <int NB, bool DEEP, int CAP>
+__global__ __launch_bounds__(256) void xq_bf16_many_kernel(const KBatch<XqDev, CAP> tb) {
     uint32_t bx, by;
     const XqDev& a = tb.a[kbatch_find(tb, bx, by)];
     xq_bf16_body<NB, DEEP>(a.X, a.ldx, a.M, a.K, a.Qpack, a.r, a.T, a.TpackT, a.m_pad, a.part, bx, by, (uint32_t)a.ns);
@@ -254,13 +247,8 @@ __device__ __forceinline__ void xq_finish_body(const float* __restrict__ part, i
     }
 }
 
-__global__ __launch_bounds__(256) void xq_finish_kernel(const float* __restrict__ part, int nsplit, int64_t rows, int64_t M,
-                                                        int64_t m_pad, int r, int rp, float* __restrict__ T,
-                                                        bf16_t* __restrict__ TpackT) {
-    xq_finish_body(part, nsplit, rows, M, m_pad, r, rp, T, TpackT, blockIdx.x);
-}
-
-__global__ __launch_bounds__(256) void xq_finish_many_kernel(const KBatch<XqDev> tb, int rp) {
+template <int CAP>
+__global__ __launch_bounds__(256) void xq_finish_many_kernel(const KBatch<XqDev, CAP> tb, int rp) {
     uint32_t bx, by;
     const XqDev& a = tb.a[kbatch_find(tb, bx, by)];
     xq_finish_body(a.part, a.ns, a.rows, a.M, a.m_pad, a.r, rp, a.T, a.TpackT, bx);
@@ -283,40 +271,35 @@ size_t xq_part_bytes(int64_t M, int64_t K, int rp) {
     return ns > 1 ? (size_t)ns * m_pad * rp * sizeof(float) : 0;
 }
 
-template <int NB>
-static hipError_t launch_xq_nb(dim3 grid, hipStream_t st, const bf16_t* X, int64_t ldx, int64_t M, int64_t K,
-                               const bf16_t* Qpack, int r, float* T, bf16_t* TpackT, int64_t m_pad, float* part) {
-    constexpr int stages = (NB == 1) ? 8 : (NB == 2) ? 6 : 4;
-    const int smem = stages * (XQ_TOK + 3 * NB * 16) * 128;
-    static bool set = false;
-    if (!set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(xq_bf16_kernel<NB>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-        if (e != hipSuccess) return e;
-        set = true;
-    }
-    hipLaunchKernelGGL(xq_bf16_kernel<NB>, grid, dim3(256), smem, st, X, ldx, M, K, Qpack, r, T, TpackT, m_pad, part);
-    return hipGetLastError();
-}
-
-template <int NB, bool DEEP>
-static hipError_t launch_xq_many_ring(const KBatch<XqDev>& tb, unsigned blocks, hipStream_t st) {
+template <int NB, bool DEEP, int CAP>
+static hipError_t launch_xq_many_ring(const KBatch<XqDev, CAP>& tb, unsigned blocks, hipStream_t st) {
     const int smem = XqRing<NB, DEEP>::STAGES * (XQ_TOK + 3 * NB * 16) * 128;
     static bool set = false;
     if (!set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(xq_bf16_many_kernel<NB, DEEP>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(xq_bf16_many_kernel<NB, DEEP, CAP>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, smem);
         if (e != hipSuccess) return e;
         set = true;
     }
-    hipLaunchKernelGGL((xq_bf16_many_kernel<NB, DEEP>), dim3(blocks), dim3(256), smem, st, tb);
+    hipLaunchKernelGGL((xq_bf16_many_kernel<NB, DEEP, CAP>), dim3(blocks), dim3(256), smem, st, tb);
     return hipGetLastError();
 }
-template <int NB>
-static hipError_t launch_xq_many_nb(const KBatch<XqDev>& tb, unsigned blocks, hipStream_t st) {
+template <int NB, int CAP>
+static hipError_t launch_xq_many_nb(const KBatch<XqDev, CAP>& tb, unsigned blocks, hipStream_t st) {
     // (the result does not depend on the ring's depth: same slices, same order)
     if (NB <= 2 && blocks >= 512) return launch_xq_many_ring<NB, false>(tb, blocks, st);
     return launch_xq_many_ring<NB, true>(tb, blocks, st);
+}
+
+template <int CAP>
+static hipError_t launch_xq_cap(const KBatch<XqDev, CAP>& tb, unsigned blocks, int rp, hipStream_t st) {
+    switch (rp / 16) {
+        case 1: return launch_xq_many_nb<1>(tb, blocks, st);
+        case 2: return launch_xq_many_nb<2>(tb, blocks, st);
+        case 3: return launch_xq_many_nb<3>(tb, blocks, st);
+        case 4: return launch_xq_many_nb<4>(tb, blocks, st);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_xq_bf16_many(const XqArgs* a, int n, hipStream_t st) {
@@ -346,40 +329,18 @@ hipError_t launch_xq_bf16_many(const XqArgs* a, int n, hipStream_t st) {
     }
     if (tb.n == 0) return hipSuccess;
     if (blocks > 0x7FFFFFFFull || fin_blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    hipError_t e;
-    switch (rp / 16) {
-        case 1: e = launch_xq_many_nb<1>(tb, (unsigned)blocks, st); break;
-        case 2: e = launch_xq_many_nb<2>(tb, (unsigned)blocks, st); break;
-        case 3: e = launch_xq_many_nb<3>(tb, (unsigned)blocks, st); break;
-        case 4: e = launch_xq_many_nb<4>(tb, (unsigned)blocks, st); break;
-        default: return hipErrorInvalidValue;
-    }
+    hipError_t e = tb.n == 1 ? launch_xq_cap(kbatch_one(tb), (unsigned)blocks, rp, st) : launch_xq_cap(tb, (unsigned)blocks, rp, st);
     if (e != hipSuccess || fin.n == 0) return e;
-    hipLaunchKernelGGL(xq_finish_many_kernel, dim3((unsigned)fin_blocks), dim3(256), 0, st, fin, rp);
+    const dim3 fin_grid((unsigned)fin_blocks);
+    if (fin.n == 1) hipLaunchKernelGGL(xq_finish_many_kernel<1>, fin_grid, dim3(256), 0, st, kbatch_one(fin), rp);
+    else hipLaunchKernelGGL(xq_finish_many_kernel<kBatchMax>, fin_grid, dim3(256), 0, st, fin, rp);
     return hipGetLastError();
 }
 
 hipError_t launch_xq_bf16(const bf16_t* X, int64_t ldx, int64_t M, int64_t K, const bf16_t* Qpack, int r, int rp,
                           float* T, bf16_t* TpackT, int64_t m_pad, float* part, hipStream_t st) {
-    if (M == 0) return hipSuccess;
-    // cover the padded token range too so that the planes' tail is zeroed
-    const int64_t rows = TpackT ? m_pad : M;
-    // the split is sized for the padded range, which is what the workspace was sized for
-    const int ns = part ? xq_splits(m_pad, K) : 1;
-    dim3 grid((unsigned)((rows + XQ_TOK - 1) / XQ_TOK), (unsigned)ns);
-    float* p = ns > 1 ? part : nullptr;
-    hipError_t e;
-    switch (rp / 16) {
-        case 1: e = launch_xq_nb<1>(grid, st, X, ldx, M, K, Qpack, r, T, TpackT, m_pad, p); break;
-        case 2: e = launch_xq_nb<2>(grid, st, X, ldx, M, K, Qpack, r, T, TpackT, m_pad, p); break;
-        case 3: e = launch_xq_nb<3>(grid, st, X, ldx, M, K, Qpack, r, T, TpackT, m_pad, p); break;
-        case 4: e = launch_xq_nb<4>(grid, st, X, ldx, M, K, Qpack, r, T, TpackT, m_pad, p); break;
-        default: return hipErrorInvalidValue;
-    }
-    if (e != hipSuccess || ns == 1) return e;
-    const int64_t items = rows * rp;
-    hipLaunchKernelGGL(xq_finish_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, p, ns, rows, M, m_pad, r, rp, T, TpackT);
-    return hipGetLastError();
+    const XqArgs a{X, ldx, M, K, Qpack, r, rp, T, TpackT, m_pad, part};
+    return launch_xq_bf16_many(&a, 1, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -499,20 +460,13 @@ __device__ __forceinline__ void xtt_bf16_body(const bf16_t* __restrict__ X, int6
         if (idx < nvalid) out[idx] = sbuf[idx];
 }
 
-template <int NB>
-__global__ __launch_bounds__(256) void xtt_bf16_kernel(const bf16_t* __restrict__ X, int64_t ldx, int64_t M, int64_t K,
-                                                       const bf16_t* __restrict__ TpackT, int64_t m_pad,
-                                                       float* __restrict__ partial, int64_t tok_per_split) {
-    xtt_bf16_body<NB>(X, ldx, M, K, TpackT, m_pad, partial, tok_per_split, blockIdx.x, blockIdx.y);
-}
-
 struct XttDev {
     const bf16_t* X; int64_t ldx, M, K;
     const bf16_t* TpackT; int64_t m_pad;
     float* partial; int64_t tok_per_split;
 };
-template <int NB>
-__global__ __launch_bounds__(256) void xtt_bf16_many_kernel(const KBatch<XttDev> tb) {
+template <int NB, int CAP>
+__global__ __launch_bounds__(256) void xtt_bf16_many_kernel(const KBatch<XttDev, CAP> tb) {
     uint32_t bx, by;
     const XttDev& a = tb.a[kbatch_find(tb, bx, by)];
     xtt_bf16_body<NB>(a.X, a.ldx, a.M, a.K, a.TpackT, a.m_pad, a.partial, a.tok_per_split, bx, by);
@@ -521,6 +475,20 @@ __global__ __launch_bounds__(256) void xtt_bf16_many_kernel(const KBatch<XttDev>
 static int64_t xtt_tokens_per_split(int64_t m_pad, int nsplit) {
     const int64_t t = (m_pad + nsplit - 1) / nsplit;
     return (t + 4 * XTT_STEP - 1) / (4 * XTT_STEP) * (4 * XTT_STEP);
+}
+
+template <int CAP>
+static hipError_t launch_xtt_cap(const KBatch<XttDev, CAP>& tb, unsigned blocks, int rp, hipStream_t st) {
+    const size_t smem = (size_t)XTT_PANEL * rp * sizeof(float);
+    const dim3 grid(blocks);
+    switch (rp / 16) {
+        case 1: hipLaunchKernelGGL((xtt_bf16_many_kernel<1, CAP>), grid, dim3(256), smem, st, tb); break;
+        case 2: hipLaunchKernelGGL((xtt_bf16_many_kernel<2, CAP>), grid, dim3(256), smem, st, tb); break;
+        case 3: hipLaunchKernelGGL((xtt_bf16_many_kernel<3, CAP>), grid, dim3(256), smem, st, tb); break;
+        case 4: hipLaunchKernelGGL((xtt_bf16_many_kernel<4, CAP>), grid, dim3(256), smem, st, tb); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_xtt_bf16_many(const XttArgs* a, int n, hipStream_t st) {
@@ -542,32 +510,13 @@ hipError_t launch_xtt_bf16_many(const XttArgs* a, int n, hipStream_t st) {
     }
     if (tb.n == 0) return hipSuccess;
     if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    const size_t smem = (size_t)XTT_PANEL * rp * sizeof(float);
-    const dim3 grid((unsigned)blocks);
-    switch (rp / 16) {
-        case 1: hipLaunchKernelGGL(xtt_bf16_many_kernel<1>, grid, dim3(256), smem, st, tb); break;
-        case 2: hipLaunchKernelGGL(xtt_bf16_many_kernel<2>, grid, dim3(256), smem, st, tb); break;
-        case 3: hipLaunchKernelGGL(xtt_bf16_many_kernel<3>, grid, dim3(256), smem, st, tb); break;
-        case 4: hipLaunchKernelGGL(xtt_bf16_many_kernel<4>, grid, dim3(256), smem, st, tb); break;
-        default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    return tb.n == 1 ? launch_xtt_cap(kbatch_one(tb), (unsigned)blocks, rp, st) : launch_xtt_cap(tb, (unsigned)blocks, rp, st);
 }
 
 hipError_t launch_xtt_bf16(const bf16_t* X, int64_t ldx, int64_t M, int64_t K, const bf16_t* TpackT, int64_t m_pad,
                            int rp, float* partial, int nsplit, hipStream_t st) {
-    if (M == 0 || K == 0) return hipSuccess;
-    const int64_t tok_per_split = xtt_tokens_per_split(m_pad, nsplit);
-    dim3 grid((unsigned)((K + XTT_PANEL - 1) / XTT_PANEL), (unsigned)nsplit);
-    const size_t smem = (size_t)XTT_PANEL * rp * sizeof(float);
-    switch (rp / 16) {
-        case 1: hipLaunchKernelGGL(xtt_bf16_kernel<1>, grid, dim3(256), smem, st, X, ldx, M, K, TpackT, m_pad, partial, tok_per_split); break;
-        case 2: hipLaunchKernelGGL(xtt_bf16_kernel<2>, grid, dim3(256), smem, st, X, ldx, M, K, TpackT, m_pad, partial, tok_per_split); break;
-        case 3: hipLaunchKernelGGL(xtt_bf16_kernel<3>, grid, dim3(256), smem, st, X, ldx, M, K, TpackT, m_pad, partial, tok_per_split); break;
-        case 4: hipLaunchKernelGGL(xtt_bf16_kernel<4>, grid, dim3(256), smem, st, X, ldx, M, K, TpackT, m_pad, partial, tok_per_split); break;
-        default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    const XttArgs a{X, ldx, M, K, TpackT, m_pad, rp, partial, nsplit};
+    return launch_xtt_bf16_many(&a, 1, st);
 }
 
 // S[d][k] = sum over splits (fp64, fixed order) of partial[s][d][rp]
