@@ -257,7 +257,7 @@ int sketch_power(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* 
         {
             ProfScope ps(ctx, AGZO_PROF_XQ);
             HIPCHK(launch_xq_bf16(static_cast<const bf16_t*>(X), L.ldx, L.n_tokens, L.d_in, wsh(ctx, p.off_pack), L.r,
-                                  p.rp, nullptr, wsh(ctx, p.off_TpackT), p.m_pad, wsf(ctx, p.off_xqpart), st));
+                                  p.rp, nullptr, wsh(ctx, p.off_TpackT), p.m_pad, wsf(ctx, p.off_xqpart), nullptr, st));
         }
         ProfScope ps(ctx, AGZO_PROF_XTT);
         HIPCHK(launch_xtt_bf16(static_cast<const bf16_t*>(X), L.ldx, L.n_tokens, L.d_in, wsh(ctx, p.off_TpackT),
@@ -291,22 +291,6 @@ int op_qr_from_splits(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, float* 
     ProfScope ps(ctx, AGZO_PROF_QR);
     HIPCHK(launch_qr(nullptr, wsf(ctx, p.off_xtt), p.nsplit, p.rp, wsf(ctx, p.off_S), L.d_in, L.r, Q, planes,
                      ctx->ws + p.off_qr, ctx->flag, refine, ctx->stream));
-    return 0;
-}
-
-// P = X B  (N x r).  planes_ready: B already sits in the workspace as planes (left there by the last QR)
-int op_project(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* X, const float* B, float* P,
-               bool planes_ready) {
-    hipStream_t st = ctx->stream;
-    if (L.dtype == AGZO_BF16) {
-        if (!planes_ready) HIPCHK(launch_pack_planes(B, L.d_in, L.r, p.rp, wsh(ctx, p.off_pack), st));
-        ProfScope ps(ctx, AGZO_PROF_XQ);
-        HIPCHK(launch_xq_bf16(static_cast<const bf16_t*>(X), L.ldx, L.n_tokens, L.d_in, wsh(ctx, p.off_pack), L.r, p.rp,
-                              P, nullptr, p.m_pad, wsf(ctx, p.off_xqpart), st));
-    } else {
-        const F32SkinnyArgs a{static_cast<const float*>(X), L.ldx, L.n_tokens, L.d_in, B, L.r, P};
-        HIPCHK(launch_xq_f32_many(&a, 1, st));
-    }
     return 0;
 }
 
@@ -344,7 +328,7 @@ F32FwdArgs forward_f32_args(const agzo_layer& L, const void* W, const void* X, c
 // shared = true: one pass over X and W evaluates the loss at W, W + eps Z, W - eps Z -> loss_dev[0..2]
 int op_forward(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* W, const void* X, const float* P,
                float eps_signed, uint64_t seed, void* Y, const agzo_loss_spec* loss, double* loss_dev,
-               bool shared = false, int part_slot = 0, bool defer_finish = false, bool fused_sketch = false) {
+               bool shared = false, int part_slot = 0, bool defer_finish = false, bool fused_sketch = false, bool ext_ready = false) {
     hipStream_t st = ctx->stream;
     GemmLossArgs la;
     const bool has_loss = loss && loss->kind != AGZO_LOSS_NONE;
@@ -373,6 +357,7 @@ int op_forward(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* W,
     }
     if (L.dtype == AGZO_BF16) {
         GemmBf16Args a = forward_bf16_args(ctx, L, p, W, X, P, eps_signed, seed, Y, la, shared);
+        a.ext_ready = ext_ready;
         if (fused_sketch) { a.sk_T = wsh(ctx, p.off_TpackT); a.sk_mpad = p.m_pad; a.sk_partial = wsf(ctx, p.off_xtt); }
         {
             ProfScope ps(ctx, AGZO_PROF_GEMM);
@@ -882,8 +867,21 @@ int agzo_perturbed_forward(agzo_ctx* ctx, const agzo_layer* L, const void* W, co
     const Plan p = make_plan(*L, L->dtype == AGZO_F32 && !Y && loss && loss->kind == AGZO_LOSS_CE, loss && loss->kind == AGZO_LOSS_CE);
     TRY(reserve(ctx, p.total));
     float* P = wsf(ctx, p.off_T);
-    TRY(op_project(ctx, *L, p, X, B, P, false));
-    return op_forward(ctx, *L, p, W, X, P, eps_signed, seed, Y, loss, loss_dev);
+    if (L->dtype != AGZO_BF16) {
+        const F32SkinnyArgs a{static_cast<const float*>(X), L->ldx, L->n_tokens, L->d_in, B, L->r, P};
+        HIPCHK(launch_xq_f32_many(&a, 1, ctx->stream));
+        return op_forward(ctx, *L, p, W, X, P, eps_signed, seed, Y, loss, loss_dev);
+    }
+    // the W side of the extension operands and the planes of B in one launch, then the projection writes the X side: a model's
+    // step makes this chain once per linear layer and sign
+    const GemmExtArgs ext{ctx->ws + p.off_ext, L->n_tokens, L->d_out, nullptr, L->r, eps_signed, 0.f, false, seed, B, wsh(ctx, p.off_pack), L->d_in};
+    HIPCHK(launch_gemm_ext_prep_many(&ext, 1, ctx->stream));
+    {
+        ProfScope ps(ctx, AGZO_PROF_XQ);
+        HIPCHK(launch_xq_bf16(static_cast<const bf16_t*>(X), L->ldx, L->n_tokens, L->d_in, wsh(ctx, p.off_pack), L->r, p.rp, nullptr, nullptr,
+                              p.m_pad, wsf(ctx, p.off_xqpart), wsh(ctx, p.off_ext), ctx->stream));
+    }
+    return op_forward(ctx, *L, p, W, X, P, eps_signed, seed, Y, loss, loss_dev, false, 0, false, false, true);
 }
 
 int agzo_update(agzo_ctx* ctx, const agzo_layer* L, void* W, const float* B, uint64_t seed, float lr,

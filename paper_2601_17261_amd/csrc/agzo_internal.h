@@ -181,7 +181,13 @@ hipError_t launch_gemm_bf16(const GemmBf16Args& a, hipStream_t st);
 // Every result has the bits of a launch of its own.  Workspaces (ext_ws unless ext_ready, loss partials) must not overlap.
 hipError_t launch_gemm_bf16_many(const GemmBf16Args* a, int n, hipStream_t st);
 // extension operands of several layers in one launch: the W side times coef and, with two = true, once more times coef2
-struct GemmExtArgs { void* ext_ws; int64_t M, N; const float* P; int r; float coef, coef2; bool two; uint64_t seed; };
+// P = NULL: without the X side (launch_xq_bf16 writes it).  planes != NULL: also the bf16 planes [3][rp][d] of B fp32 [d][r]
+struct GemmExtArgs {
+    void* ext_ws; int64_t M, N; const float* P; int r; float coef, coef2; bool two; uint64_t seed;
+    const float* B = nullptr; bf16_t* planes = nullptr; int64_t d = 0;
+};
+// width of the extension operands, three segments of r rounded up to 16, to a multiple of 64
+inline int gemm_bf16_ext_width(int r) { return (3 * ((r + 15) / 16 * 16) + 63) / 64 * 64; }
 hipError_t launch_gemm_ext_prep_many(const GemmExtArgs* a, int n, hipStream_t st);
 
 // gemm_f32.hip : fp32 storage, fp64 accumulation on the matrix cores.  Up to kBatchMax problems per launch
@@ -210,10 +216,14 @@ hipError_t launch_xtt_f32_many(const F32SkinnyArgs* a, int n, hipStream_t st);
 // T = X Qp, Qp given as bf16 planes [3][rp][d_in]; writes T fp32 [M][r] (nullable) and
 // T^T planes bf16 [3][rp][m_pad] (nullable)
 // part: xq_part_bytes() bytes of scratch for the split over d_in that small token counts take (NULL: never split)
+// Xext: T as the X side of a forward's extension operands, [M][gemm_bf16_ext_width(r)] (nullable)
 size_t xq_part_bytes(int64_t M, int64_t K, int rp);
 hipError_t launch_xq_bf16(const bf16_t* X, int64_t ldx, int64_t M, int64_t K, const bf16_t* Qpack, int r, int rp,
-                          float* T, bf16_t* TpackT, int64_t m_pad, float* part, hipStream_t st);
-struct XqArgs { const bf16_t* X; int64_t ldx, M, K; const bf16_t* Qpack; int r, rp; float* T; bf16_t* TpackT; int64_t m_pad; float* part; };
+                          float* T, bf16_t* TpackT, int64_t m_pad, float* part, bf16_t* Xext, hipStream_t st);
+struct XqArgs {
+    const bf16_t* X; int64_t ldx, M, K; const bf16_t* Qpack; int r, rp; float* T; bf16_t* TpackT; int64_t m_pad; float* part;
+    bf16_t* Xext = nullptr;
+};
 // up to kBatchMax products with the same rp in one launch (plus one finishing launch if any of them splits d_in)
 hipError_t launch_xq_bf16_many(const XqArgs* a, int n, hipStream_t st);
 int xtt_num_splits(int64_t M, int64_t K);

@@ -564,13 +564,15 @@ __global__ __launch_bounds__(64 * WA * WB) void gemm_bf16_kernel(GemmParams p) {
 // Rows 0..M-1 are the X side ([Ph | Ph | Pl | 0], P = X B split hi + lo in bf16), rows M..M+N-1 the W side
 // ([Gh | Gl | Gh | 0], G regenerated from the Philox seed, times coef: the signed eps); n_w = 2 adds rows M+N..M+2N-1, the
 // W side once more with coef2 (the other sign's, or the shared-forward kernel's second pass, -2 eps).  Several layers per
-// launch (fourteen launches of one operand set each took 62 us of a layer set's step).
+// launch (fourteen launches of one operand set each took 62 us of a layer set's step).  M = 0 where the projection writes
+// the X side itself; then the threads behind the W side split B into planes for that projection.
 struct ExtDev {
     bf16_t* Xext; bf16_t* Wext;
     int64_t M, N; int ext_ld;
     const float* P; int r, rp;
     float coef, coef2; int n_w;
     uint32_t s_lo, s_hi;
+    const float* B; bf16_t* planes; int64_t d;
 };
 template <int CAP>
 __global__ __launch_bounds__(256) void gemm_ext_prep_kernel(const KBatch<ExtDev, CAP> tb) {
@@ -580,7 +582,26 @@ __global__ __launch_bounds__(256) void gemm_ext_prep_kernel(const KBatch<ExtDev,
     const int64_t M = a.M, N = a.N;
     const int chunks = ext_ld / 8;
     const int64_t idx = (int64_t)bx * 256 + threadIdx.x;
-    if (idx >= (M + a.n_w * N) * chunks) return;
+    if (idx >= (M + a.n_w * N) * chunks) {
+        // eight rows of one column of B
+        const int64_t e = idx - (M + a.n_w * N) * chunks;
+        if (a.planes == nullptr || e >= a.d / 8 * rp) return;
+        const int64_t i = e % (a.d / 8) * 8;
+        const int k = (int)(e / (a.d / 8));
+        uint32_t w[3][4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            bf16_t h[2], m[2], l[2];
+#pragma unroll
+            for (int v = 0; v < 2; ++v) split3_bf16(k < r ? a.B[(i + 2 * u + v) * r + k] : 0.f, h[v], m[v], l[v]);
+            w[0][u] = (uint32_t)h[0] | ((uint32_t)h[1] << 16);
+            w[1][u] = (uint32_t)m[0] | ((uint32_t)m[1] << 16);
+            w[2][u] = (uint32_t)l[0] | ((uint32_t)l[1] << 16);
+        }
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<uint4*>(a.planes + ((int64_t)pl * rp + k) * a.d + i) = make_uint4(w[pl][0], w[pl][1], w[pl][2], w[pl][3]);
+        return;
+    }
     int64_t row = idx / chunks;
     const bool second = row >= M + N;
     if (second) row -= N;
@@ -620,7 +641,7 @@ __global__ __launch_bounds__(256) void gemm_ext_prep_kernel(const KBatch<ExtDev,
     *reinterpret_cast<uint4*>(dst) = out;
 }
 
-static int ext_width(int r) { return (3 * ((r + 15) / 16 * 16) + BK - 1) / BK * BK; }
+static_assert(BK == 64, "the extension operands' width");
 
 hipError_t launch_gemm_ext_prep_many(const GemmExtArgs* a, int n, hipStream_t st) {
     if (n < 0 || n > kBatchMax) return hipErrorInvalidValue;
@@ -629,12 +650,15 @@ hipError_t launch_gemm_ext_prep_many(const GemmExtArgs* a, int n, hipStream_t st
     uint64_t blocks = 0;
     for (int m = 0; m < n; ++m) {
         ExtDev d;
-        d.M = a[m].M; d.N = a[m].N; d.ext_ld = ext_width(a[m].r);
+        d.M = a[m].M; d.N = a[m].N; d.ext_ld = gemm_bf16_ext_width(a[m].r);
         d.Xext = static_cast<bf16_t*>(a[m].ext_ws); d.Wext = d.Xext + d.M * d.ext_ld;
+        if (!a[m].P) d.M = 0;
+        d.B = a[m].B; d.planes = a[m].planes; d.d = a[m].d;
+        if (d.planes && d.d % 8) return hipErrorInvalidValue;
         d.P = a[m].P; d.r = a[m].r; d.rp = (a[m].r + 15) / 16 * 16;
         d.coef = a[m].coef; d.coef2 = a[m].coef2; d.n_w = a[m].two ? 2 : 1;
         d.s_lo = (uint32_t)a[m].seed; d.s_hi = (uint32_t)(a[m].seed >> 32);
-        const int64_t items = (d.M + d.n_w * d.N) * (d.ext_ld / 8);
+        const int64_t items = (d.M + d.n_w * d.N) * (d.ext_ld / 8) + (d.planes ? d.d / 8 * d.rp : 0);
         tb.first[tb.n] = (uint32_t)blocks;
         tb.gx[tb.n] = (uint32_t)((items + 255) / 256);
         blocks += tb.gx[tb.n];
@@ -648,7 +672,7 @@ hipError_t launch_gemm_ext_prep_many(const GemmExtArgs* a, int n, hipStream_t st
 }
 
 size_t gemm_bf16_ext_bytes(int64_t M, int64_t N, int r) {
-    return (size_t)(M + 2 * N) * ext_width(r) * sizeof(bf16_t);   // X side, W side, and the W side of a second pass
+    return (size_t)(M + 2 * N) * gemm_bf16_ext_width(r) * sizeof(bf16_t);   // X side, W side, and the W side of a second pass
 }
 
 template <int WA, int WB, bool SHARED, int EPI>
@@ -712,7 +736,7 @@ hipError_t choose(const GemmBf16Args& a, Choice& c) {
     p.Xext = nullptr; p.Wext = nullptr; p.Wext2 = nullptr; p.ext_ld = 0;
     c.prep = false;
     if (a.P && a.ext_ws && (!a.shared || persistent)) {
-        p.ext_ld = ext_width(a.r);
+        p.ext_ld = gemm_bf16_ext_width(a.r);
         bf16_t* xe = static_cast<bf16_t*>(a.ext_ws);
         bf16_t* we = xe + a.M * p.ext_ld;
         p.Xext = xe;

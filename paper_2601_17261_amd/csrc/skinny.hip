@@ -4,6 +4,8 @@
 // X is bf16; the small fp32 factor (Q, B, T, Omega) enters the matrix cores as three bf16 planes
 // hi + mid + lo, whose sum is the fp32 value, so the products carry fp32-level accuracy while the
 // kernels stay bound by the single read of X.  v_mfma_f32_16x16x32_bf16 throughout.
+#include <type_traits>
+
 #include "agzo_internal.h"
 
 namespace agzo {
@@ -33,17 +35,13 @@ __device__ __forceinline__ void wait_vmcnt() {
     static_assert(N >= 0 && N < 64, "vmcnt range");
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
-// wait until at most n loads of this wave are outstanding (n is wave-uniform)
-__device__ __forceinline__ void wait_vmcnt_dyn(int n) {
-    switch (n) {
-        case 0: wait_vmcnt<0>(); break;   case 3: wait_vmcnt<3>(); break;   case 4: wait_vmcnt<4>(); break;
-        case 5: wait_vmcnt<5>(); break;   case 6: wait_vmcnt<6>(); break;   case 7: wait_vmcnt<7>(); break;
-        case 8: wait_vmcnt<8>(); break;   case 9: wait_vmcnt<9>(); break;   case 10: wait_vmcnt<10>(); break;
-        case 12: wait_vmcnt<12>(); break; case 14: wait_vmcnt<14>(); break; case 15: wait_vmcnt<15>(); break;
-        case 16: wait_vmcnt<16>(); break; case 18: wait_vmcnt<18>(); break; case 20: wait_vmcnt<20>(); break;
-        case 21: wait_vmcnt<21>(); break; case 24: wait_vmcnt<24>(); break; case 28: wait_vmcnt<28>(); break;
-        default: wait_vmcnt<0>(); break;
-    }
+// T[t][k] as the X side of the extension operands: [hi | hi | lo | 0], segments of rp columns, the last one up to the width
+__device__ __forceinline__ void store_ext(bf16_t* Xext, int64_t t, int k, int rp, float v) {
+    const int ld = (3 * rp + 63) / 64 * 64;
+    bf16_t* dst = Xext + t * ld + k;
+    const bf16_t hi = f32_to_bf16(v), lo = f32_to_bf16(v - bf16_to_f32(hi));
+    dst[0] = hi; dst[rp] = hi; dst[2 * rp] = lo;
+    if (3 * rp < ld) dst[3 * rp] = 0;          // (ld - 3 rp is 0 or rp)
 }
 
 // bx: token block, by / ny: this workgroup's share of d_in (ny = 1: all of it)
@@ -53,15 +51,20 @@ __device__ __forceinline__ void wait_vmcnt_dyn(int n) {
 template <int NB, bool DEEP>
 struct XqRing { static constexpr int STAGES = DEEP ? ((NB == 1) ? 8 : (NB == 2) ? 6 : 4) : ((NB == 1) ? 5 : (NB == 2) ? 3 : 4); };
 
+// a slot holds the rows of a slice and, where four waves do not share their groups evenly, groups that nobody reads: every wave
+// then issues the same number of loads and waits by constants (a wait chosen among a dozen cases and a branch around each load
+// cost more than the slice's matrix work)
+constexpr int xq_slot_bytes(int nb) { return (XQ_TOK / 8 + 6 * nb + 3) / 4 * 4096; }
+
 template <int NB, bool DEEP>
 __device__ __forceinline__ void xq_bf16_body(const bf16_t* __restrict__ X, int64_t ldx, int64_t M, int64_t K,
                                              const bf16_t* __restrict__ Qpack, int r, float* __restrict__ T,
                                              bf16_t* __restrict__ TpackT, int64_t m_pad, float* __restrict__ part,
-                                             uint32_t bx, uint32_t by, uint32_t ny) {
+                                             bf16_t* __restrict__ Xext, uint32_t bx, uint32_t by, uint32_t ny) {
     constexpr int RP = NB * 16;
     constexpr int QROWS = 3 * RP;                          // plane rows: (plane, k)
     constexpr int NGROUP = XQ_TOK / 8 + QROWS / 8;         // 8-row groups per slice: X first, then the planes
-    constexpr int SLOT = (XQ_TOK + QROWS) * 128;           // bytes per ring slot
+    constexpr int SLOT = xq_slot_bytes(NB);                // bytes per ring slot
     constexpr int STAGES = XqRing<NB, DEEP>::STAGES;
     extern __shared__ __align__(16) char xq_smem[];
     typedef __attribute__((address_space(3))) void* lptr_t;
@@ -77,7 +80,6 @@ __device__ __forceinline__ void xq_bf16_body(const bf16_t* __restrict__ X, int64
 
     // this wave's row groups g = wave, wave + 4, ...: per-lane source pointers (row of the group, swizzled chunk)
     constexpr int MAXG = (NGROUP + 3) / 4;
-    const int ng = (NGROUP - wave + 3) / 4;                // groups of this wave
     const bf16_t* src[MAXG];
 #pragma unroll
     for (int i = 0; i < MAXG; ++i) {
@@ -94,76 +96,116 @@ __device__ __forceinline__ void xq_bf16_body(const bf16_t* __restrict__ X, int64
     const int kbeg = (int)((int64_t)nfull_all * split / nsplit);
     const int nfull = (int)((int64_t)nfull_all * (split + 1) / nsplit) - kbeg;      // this workgroup's slices
     const bool tail = (K % XQ_BK) != 0 && split == nsplit - 1;
-    auto issue = [&](int kt, int slot) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < MAXG; ++i) src[i] += (int64_t)kbeg * XQ_BK;
+    // the next slice not yet requested, into `slot`
+    auto issue = [&](int slot) __attribute__((always_inline)) {
         char* base = xq_smem + slot * SLOT + wave * 1024;
 #pragma unroll
-        for (int i = 0; i < MAXG; ++i)
-            if (i < ng)
-                __builtin_amdgcn_global_load_lds((gptr_t)(src[i] + (int64_t)(kbeg + kt) * XQ_BK), (lptr_t)(base + i * 4096), 16, 0, 0);
+        for (int i = 0; i < MAXG; ++i) {
+            __builtin_amdgcn_global_load_lds((gptr_t)src[i], (lptr_t)(base + i * 4096), 16, 0, 0);
+            src[i] += XQ_BK;
+        }
     };
     // Fragment reads go through inline assembly: for a plain LDS load the compiler, which cannot tell the ring's slots
-    // apart, first waits for every direct load in flight (vmcnt(0)) and so collapses the ring to one slice.  The
-    // waits that are needed are the explicit ones around the barrier and the lgkmcnt below.
-    auto lds_read16 = [&](const char* ptr) __attribute__((always_inline)) {
-        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-        u32x4 v;
-        const uint32_t addr = (uint32_t)(uintptr_t)(lptr_t)ptr;
-        asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(addr));
-        return v;
-    };
-    auto multiply = [&](int slot, bool dma) __attribute__((always_inline)) {
+    // apart, first waits for every direct load in flight (vmcnt(0)) and so collapses the ring to one slice.  The reads of a
+    // slice, both of its 32-wide sub-steps, and the wait for them are one block: with one workgroup per compute unit a slice is
+    // a chain of LDS latency and dependent matrix instructions, and one latency is less than two.
+    // Row 16 m + lm of an operand lies 2048 m bytes behind row lm, in the same chunk order.
+    auto multiply = [&](int slot) __attribute__((always_inline)) {
         const char* xs = xq_smem + slot * SLOT;
         const char* qs = xs + XQ_TOK * 128;
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+        u32x4 a[2], b[2][NB][3];
+        const uint32_t xaddr0 = (uint32_t)(uintptr_t)(lptr_t)(xs + xq_lds_off(wave * 16 + lm, lg)), xaddr1 = (uint32_t)(uintptr_t)(lptr_t)(xs + xq_lds_off(wave * 16 + lm, 4 + lg));
+        const uint32_t qaddr0 = (uint32_t)(uintptr_t)(lptr_t)(qs + xq_lds_off(lm, lg)), qaddr1 = (uint32_t)(uintptr_t)(lptr_t)(qs + xq_lds_off(lm, 4 + lg));
+        if constexpr (NB == 1)
+            asm volatile("ds_read_b128 %0, %8\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %10 offset:2048\n\t"
+                         "ds_read_b128 %4, %10 offset:4096\n\tds_read_b128 %1, %9\n\tds_read_b128 %5, %11\n\t"
+                         "ds_read_b128 %6, %11 offset:2048\n\tds_read_b128 %7, %11 offset:4096\n\ts_waitcnt lgkmcnt(0)"
+                         : "=&v"(a[0]), "=&v"(a[1]), "=&v"(b[0][0][0]), "=&v"(b[0][0][1]), "=&v"(b[0][0][2]),
+                           "=&v"(b[1][0][0]), "=&v"(b[1][0][1]), "=&v"(b[1][0][2])
+                         : "v"(xaddr0), "v"(xaddr1), "v"(qaddr0), "v"(qaddr1) : "memory");
+        else if constexpr (NB == 2)
+            asm volatile("ds_read_b128 %0, %14\n\tds_read_b128 %2, %16\n\tds_read_b128 %3, %16 offset:2048\n\t"
+                         "ds_read_b128 %4, %16 offset:4096\n\tds_read_b128 %5, %16 offset:6144\n\t"
+                         "ds_read_b128 %6, %16 offset:8192\n\tds_read_b128 %7, %16 offset:10240\n\tds_read_b128 %1, %15\n\t"
+                         "ds_read_b128 %8, %17\n\tds_read_b128 %9, %17 offset:2048\n\tds_read_b128 %10, %17 offset:4096\n\t"
+                         "ds_read_b128 %11, %17 offset:6144\n\tds_read_b128 %12, %17 offset:8192\n\t"
+                         "ds_read_b128 %13, %17 offset:10240\n\ts_waitcnt lgkmcnt(0)"
+                         : "=&v"(a[0]), "=&v"(a[1]), "=&v"(b[0][0][0]), "=&v"(b[0][1][0]), "=&v"(b[0][0][1]),
+                           "=&v"(b[0][1][1]), "=&v"(b[0][0][2]), "=&v"(b[0][1][2]), "=&v"(b[1][0][0]), "=&v"(b[1][1][0]),
+                           "=&v"(b[1][0][1]), "=&v"(b[1][1][1]), "=&v"(b[1][0][2]), "=&v"(b[1][1][2])
+                         : "v"(xaddr0), "v"(xaddr1), "v"(qaddr0), "v"(qaddr1) : "memory");
+        else if constexpr (NB == 3)
+            asm volatile("ds_read_b128 %0, %20\n\tds_read_b128 %2, %22\n\tds_read_b128 %3, %22 offset:2048\n\t"
+                         "ds_read_b128 %4, %22 offset:4096\n\tds_read_b128 %5, %22 offset:6144\n\t"
+                         "ds_read_b128 %6, %22 offset:8192\n\tds_read_b128 %7, %22 offset:10240\n\t"
+                         "ds_read_b128 %8, %22 offset:12288\n\tds_read_b128 %9, %22 offset:14336\n\t"
+                         "ds_read_b128 %10, %22 offset:16384\n\tds_read_b128 %1, %21\n\tds_read_b128 %11, %23\n\t"
+                         "ds_read_b128 %12, %23 offset:2048\n\tds_read_b128 %13, %23 offset:4096\n\t"
+                         "ds_read_b128 %14, %23 offset:6144\n\tds_read_b128 %15, %23 offset:8192\n\t"
+                         "ds_read_b128 %16, %23 offset:10240\n\tds_read_b128 %17, %23 offset:12288\n\t"
+                         "ds_read_b128 %18, %23 offset:14336\n\tds_read_b128 %19, %23 offset:16384\n\ts_waitcnt lgkmcnt(0)"
+                         : "=&v"(a[0]), "=&v"(a[1]), "=&v"(b[0][0][0]), "=&v"(b[0][1][0]), "=&v"(b[0][2][0]),
+                           "=&v"(b[0][0][1]), "=&v"(b[0][1][1]), "=&v"(b[0][2][1]), "=&v"(b[0][0][2]), "=&v"(b[0][1][2]),
+                           "=&v"(b[0][2][2]), "=&v"(b[1][0][0]), "=&v"(b[1][1][0]), "=&v"(b[1][2][0]), "=&v"(b[1][0][1]),
+                           "=&v"(b[1][1][1]), "=&v"(b[1][2][1]), "=&v"(b[1][0][2]), "=&v"(b[1][1][2]), "=&v"(b[1][2][2])
+                         : "v"(xaddr0), "v"(xaddr1), "v"(qaddr0), "v"(qaddr1) : "memory");
+        else
+            asm volatile("ds_read_b128 %0, %26\n\tds_read_b128 %2, %28\n\tds_read_b128 %3, %28 offset:2048\n\t"
+                         "ds_read_b128 %4, %28 offset:4096\n\tds_read_b128 %5, %28 offset:6144\n\t"
+                         "ds_read_b128 %6, %28 offset:8192\n\tds_read_b128 %7, %28 offset:10240\n\t"
+                         "ds_read_b128 %8, %28 offset:12288\n\tds_read_b128 %9, %28 offset:14336\n\t"
+                         "ds_read_b128 %10, %28 offset:16384\n\tds_read_b128 %11, %28 offset:18432\n\t"
+                         "ds_read_b128 %12, %28 offset:20480\n\tds_read_b128 %13, %28 offset:22528\n\tds_read_b128 %1, %27\n\t"
+                         "ds_read_b128 %14, %29\n\tds_read_b128 %15, %29 offset:2048\n\tds_read_b128 %16, %29 offset:4096\n\t"
+                         "ds_read_b128 %17, %29 offset:6144\n\tds_read_b128 %18, %29 offset:8192\n\t"
+                         "ds_read_b128 %19, %29 offset:10240\n\tds_read_b128 %20, %29 offset:12288\n\t"
+                         "ds_read_b128 %21, %29 offset:14336\n\tds_read_b128 %22, %29 offset:16384\n\t"
+                         "ds_read_b128 %23, %29 offset:18432\n\tds_read_b128 %24, %29 offset:20480\n\t"
+                         "ds_read_b128 %25, %29 offset:22528\n\ts_waitcnt lgkmcnt(0)"
+                         : "=&v"(a[0]), "=&v"(a[1]), "=&v"(b[0][0][0]), "=&v"(b[0][1][0]), "=&v"(b[0][2][0]),
+                           "=&v"(b[0][3][0]), "=&v"(b[0][0][1]), "=&v"(b[0][1][1]), "=&v"(b[0][2][1]), "=&v"(b[0][3][1]),
+                           "=&v"(b[0][0][2]), "=&v"(b[0][1][2]), "=&v"(b[0][2][2]), "=&v"(b[0][3][2]), "=&v"(b[1][0][0]),
+                           "=&v"(b[1][1][0]), "=&v"(b[1][2][0]), "=&v"(b[1][3][0]), "=&v"(b[1][0][1]), "=&v"(b[1][1][1]),
+                           "=&v"(b[1][2][1]), "=&v"(b[1][3][1]), "=&v"(b[1][0][2]), "=&v"(b[1][1][2]), "=&v"(b[1][2][2]),
+                           "=&v"(b[1][3][2])
+                         : "v"(xaddr0), "v"(xaddr1), "v"(qaddr0), "v"(qaddr1) : "memory");
 #pragma unroll
-        for (int sub = 0; sub < 2; ++sub) {
-            typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-            u32x4 a, b[NB][3];
-            a = lds_read16(xs + xq_lds_off(wave * 16 + lm, sub * 4 + lg));
+        for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
+            for (int pl = 0; pl < 3; ++pl)
 #pragma unroll
-                for (int pl = 0; pl < 3; ++pl) b[nb][pl] = lds_read16(qs + xq_lds_off(pl * RP + nb * 16 + lm, sub * 4 + lg));
-            // the wait names every loaded register as an in/out operand, so nothing that uses them can move above it
-            if constexpr (NB == 1)
-                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a), "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[0][2]) :: "memory");
-            else if constexpr (NB == 2)
-                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a), "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[0][2]), "+v"(b[1][0]),
-                             "+v"(b[1][1]), "+v"(b[1][2]) :: "memory");
-            else if constexpr (NB == 3)
-                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a), "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[0][2]), "+v"(b[1][0]),
-                             "+v"(b[1][1]), "+v"(b[1][2]), "+v"(b[2][0]), "+v"(b[2][1]), "+v"(b[2][2]) :: "memory");
-            else
-                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a), "+v"(b[0][0]), "+v"(b[0][1]), "+v"(b[0][2]), "+v"(b[1][0]),
-                             "+v"(b[1][1]), "+v"(b[1][2]), "+v"(b[2][0]), "+v"(b[2][1]), "+v"(b[2][2]), "+v"(b[3][0]),
-                             "+v"(b[3][1]), "+v"(b[3][2]) :: "memory");
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                for (int pl = 0; pl < 3; ++pl)
-                    acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b[nb][pl]),
+                for (int nb = 0; nb < NB; ++nb)
+                    acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[sub]), __builtin_bit_cast(bf16x8, b[sub][nb][pl]),
                                                                       acc[nb], 0, 0, 0);
-        }
-        (void)dma;
     };
     // ring: slices kt .. kt + STAGES - 2 in flight while slice kt is multiplied
 #pragma unroll
     for (int s = 0; s < STAGES - 1; ++s)
-        if (s < nfull) issue(s, s);
+        if (s < nfull) issue(s);
     int slot = 0;
-    for (int kt = 0; kt < nfull; ++kt) {
-        // this wave's loads of slice kt have landed when at most (younger slices in flight) * ng are outstanding
-        const int younger = min(STAGES - 2, nfull - 1 - kt);
-        wait_vmcnt_dyn(younger * ng);
-        // everybody's loads of slice kt have landed; the slot of slice kt-1 is free.  A bare barrier: __syncthreads()
+    // the slice in `slot`, with YOUNGER slices in flight behind it
+    auto step = [&](auto YOUNGER, bool more) __attribute__((always_inline)) {
+        wait_vmcnt<decltype(YOUNGER)::value * MAXG>();     // this wave's loads of the slice have landed
+        // everybody's have; the slot of the slice before is free.  A bare barrier: __syncthreads()
         // would first wait for every load in flight and collapse the ring to one slice.
-        __builtin_amdgcn_s_waitcnt(0xC07F);                // lgkmcnt(0)
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        if (kt + STAGES - 1 < nfull) issue(kt + STAGES - 1, (slot + STAGES - 1) % STAGES);
-        multiply(slot, true);
+        if (more) issue(slot == 0 ? STAGES - 1 : slot - 1);
+        multiply(slot);
         slot = (slot + 1 == STAGES) ? 0 : slot + 1;
-    }
+    };
+    const int rest = min(nfull, STAGES - 1);
+    for (int kt = 0; kt < nfull - rest; ++kt) step(std::integral_constant<int, STAGES - 2>{}, true);
+    auto drain = [&](auto self, auto YOUNGER) __attribute__((always_inline)) -> void {
+        constexpr int y = decltype(YOUNGER)::value;
+        if (y < rest) step(YOUNGER, false);
+        if constexpr (y > 0) self(self, std::integral_constant<int, y - 1>{});
+    };
+    drain(drain, std::integral_constant<int, STAGES - 2>{});
     if (tail) {
         // ragged end of d_in: the threads copy it themselves, zero past d_in
         __syncthreads();
@@ -180,7 +222,7 @@ __device__ __forceinline__ void xq_bf16_body(const bf16_t* __restrict__ X, int64
             *reinterpret_cast<uint4*>(base + xq_lds_off(row, c)) = v;
         }
         __syncthreads();
-        multiply(0, false);
+        multiply(0);
     }
     // D layout: row (token) = 4*(lane/16) + e, col (k) = lane%16
     if (part != nullptr) {
@@ -201,6 +243,7 @@ __device__ __forceinline__ void xq_bf16_body(const bf16_t* __restrict__ X, int64
             const int64_t t = t0 + wave * 16 + lg * 4 + e;
             const float v = (t < M && k < r) ? acc[nb][e] : 0.f;
             if (t < M && k < r && T != nullptr) T[t * r + k] = v;
+            if (t < M && Xext != nullptr) store_ext(Xext, t, k, RP, v);
             if (TpackT != nullptr && t < m_pad) {
                 bf16_t hi, mid, lo;
                 split3_bf16(v, hi, mid, lo);
@@ -218,18 +261,19 @@ struct XqDev {
     const bf16_t* Qpack; int r;
     float* T; bf16_t* TpackT; int64_t m_pad; float* part;   // part: NULL unless ns > 1
     int ns; int64_t rows;
+    bf16_t* Xext;
 };
 template <int NB, bool DEEP, int CAP>
 __global__ __launch_bounds__(256) void xq_bf16_many_kernel(const KBatch<XqDev, CAP> tb) {
     uint32_t bx, by;
     const XqDev& a = tb.a[kbatch_find(tb, bx, by)];
-    xq_bf16_body<NB, DEEP>(a.X, a.ldx, a.M, a.K, a.Qpack, a.r, a.T, a.TpackT, a.m_pad, a.part, bx, by, (uint32_t)a.ns);
+    xq_bf16_body<NB, DEEP>(a.X, a.ldx, a.M, a.K, a.Qpack, a.r, a.T, a.TpackT, a.m_pad, a.part, a.Xext, bx, by, (uint32_t)a.ns);
 }
 
 // sums the d_in splits of xq in fixed order and writes what the unsplit kernel's epilogue writes; one thread per (t, k)
 __device__ __forceinline__ void xq_finish_body(const float* __restrict__ part, int nsplit, int64_t rows, int64_t M,
                                                int64_t m_pad, int r, int rp, float* __restrict__ T,
-                                               bf16_t* __restrict__ TpackT, uint32_t bx) {
+                                               bf16_t* __restrict__ TpackT, bf16_t* __restrict__ Xext, uint32_t bx) {
     const int64_t idx = (int64_t)bx * 256 + threadIdx.x;
     if (idx >= rows * rp) return;
     const int64_t t = idx / rp;
@@ -238,6 +282,7 @@ __device__ __forceinline__ void xq_finish_body(const float* __restrict__ part, i
     if (t < M && k < r)
         for (int s = 0; s < nsplit; ++s) v += part[((int64_t)s * m_pad + t) * rp + k];
     if (t < M && k < r && T != nullptr) T[t * r + k] = v;
+    if (t < M && Xext != nullptr) store_ext(Xext, t, k, rp, v);
     if (TpackT != nullptr && t < m_pad) {
         bf16_t hi, mid, lo;
         split3_bf16(v, hi, mid, lo);
@@ -251,7 +296,7 @@ template <int CAP>
 __global__ __launch_bounds__(256) void xq_finish_many_kernel(const KBatch<XqDev, CAP> tb, int rp) {
     uint32_t bx, by;
     const XqDev& a = tb.a[kbatch_find(tb, bx, by)];
-    xq_finish_body(a.part, a.ns, a.rows, a.M, a.m_pad, a.r, rp, a.T, a.TpackT, bx);
+    xq_finish_body(a.part, a.ns, a.rows, a.M, a.m_pad, a.r, rp, a.T, a.TpackT, a.Xext, bx);
 }
 
 // number of d_in splits for M tokens (1 = the token blocks alone fill the chip, or d_in is too short to share)
@@ -273,7 +318,7 @@ size_t xq_part_bytes(int64_t M, int64_t K, int rp) {
 
 template <int NB, bool DEEP, int CAP>
 static hipError_t launch_xq_many_ring(const KBatch<XqDev, CAP>& tb, unsigned blocks, hipStream_t st) {
-    const int smem = XqRing<NB, DEEP>::STAGES * (XQ_TOK + 3 * NB * 16) * 128;
+    const int smem = XqRing<NB, DEEP>::STAGES * xq_slot_bytes(NB);
     static bool set = false;
     if (!set) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(xq_bf16_many_kernel<NB, DEEP, CAP>),
@@ -316,6 +361,7 @@ hipError_t launch_xq_bf16_many(const XqArgs* a, int n, hipStream_t st) {
         d.X = a[m].X; d.ldx = a[m].ldx; d.M = a[m].M; d.K = a[m].K; d.Qpack = a[m].Qpack; d.r = a[m].r;
         d.T = a[m].T; d.TpackT = a[m].TpackT; d.m_pad = a[m].m_pad;
         d.rows = a[m].TpackT ? a[m].m_pad : a[m].M;
+        d.Xext = a[m].Xext;
         d.ns = a[m].part ? xq_splits(a[m].m_pad, a[m].K) : 1;
         d.part = d.ns > 1 ? a[m].part : nullptr;
         const uint32_t gx = (uint32_t)((d.rows + XQ_TOK - 1) / XQ_TOK);
@@ -338,8 +384,8 @@ hipError_t launch_xq_bf16_many(const XqArgs* a, int n, hipStream_t st) {
 }
 
 hipError_t launch_xq_bf16(const bf16_t* X, int64_t ldx, int64_t M, int64_t K, const bf16_t* Qpack, int r, int rp,
-                          float* T, bf16_t* TpackT, int64_t m_pad, float* part, hipStream_t st) {
-    const XqArgs a{X, ldx, M, K, Qpack, r, rp, T, TpackT, m_pad, part};
+                          float* T, bf16_t* TpackT, int64_t m_pad, float* part, bf16_t* Xext, hipStream_t st) {
+    const XqArgs a{X, ldx, M, K, Qpack, r, rp, T, TpackT, m_pad, part, Xext};
     return launch_xq_bf16_many(&a, 1, st);
 }
 
