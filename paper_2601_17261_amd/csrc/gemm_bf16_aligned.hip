@@ -688,8 +688,10 @@ static hipError_t launch_aligned_variant(const GemmParams& p, hipStream_t st) {
         if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         if (e != hipSuccess) return e;
         if (cus < 1) return hipErrorInvalidDevice;
-        if (G > cus) G = cus;
-        if (G >= 8) G -= G % 8;
+        // (rounded up: workgroups without a tile leave at once, while one short of a workgroup per tile 190 or 250 tiles took
+        // the time of two)
+        G = (G + 7) / 8 * 8;
+        if (G > cus) G = cus >= 8 ? cus - cus % 8 : cus;
     }
     dim3 grid((unsigned)G);
     hipLaunchKernelGGL((gemm_bf16_aligned_kernel<OUT, T_F32, PHASES, RAGGED>), grid, dim3(256), smem, st, p);
