@@ -113,7 +113,7 @@ inline int64_t round32(int64_t n) { return (n + 31) / 32 * 32; }
 
 // carve-out of the ctx workspace for one layer; everything a step can need at the same time
 struct Plan {
-    size_t off_S, off_Q, off_B, off_pack, off_T, off_TpackT, off_xtt, off_qr, off_part, off_Ybuf, off_ce_ms, off_ce_tl, off_upd, off_ext, off_xqpart, total;
+    size_t off_S, off_Q, off_B, off_pack, off_T, off_TpackT, off_xtt, off_qr, off_part, off_Ybuf, off_ce_ms, off_ce_tl, off_upd, off_ext, off_xqpart, off_split, total;
     int rp, nsplit;
     int64_t m_pad;
     int n_part;
@@ -153,7 +153,19 @@ Plan make_plan(const agzo_layer& L, bool need_ybuf, bool ce = false, bool shared
     p.off_ext = take(bf ? gemm_bf16_ext_bytes(L.n_tokens, L.d_out, L.r) : 0);
     p.off_xqpart = take(bf ? xq_part_bytes(L.n_tokens, L.d_in, p.rp) : 0);
     p.off_Ybuf = take(need_ybuf ? (size_t)L.n_tokens * L.d_out * 4 : 0);
+    p.off_split = 0;
     p.total = o;
+    return p;
+}
+
+// with the scratch of a lone stored output (the forwards that a model makes layer by layer)
+Plan make_forward_plan(const agzo_layer& L, bool need_ybuf, bool ce, bool fused_sketch, bool stored) {
+    Plan p = make_plan(L, need_ybuf, ce, false, 0, fused_sketch);
+    const size_t split = (stored && L.dtype == AGZO_BF16 && L.y_dtype == AGZO_BF16) ? gemm_bf16_split_bytes(L.n_tokens, L.d_out, L.d_in) : 0;
+    if (split) {
+        p.off_split = p.total;
+        p.total += align_up(split);
+    }
     return p;
 }
 
@@ -306,6 +318,7 @@ GemmBf16Args forward_bf16_args(agzo_ctx* ctx, const agzo_layer& L, const Plan& p
     a.shared = shared;
     a.large_tiles = (L.tiling == AGZO_TILING_LARGE);
     a.ext_ws = P ? ctx->ws + p.off_ext : nullptr;
+    a.split_ws = p.off_split ? ctx->ws + p.off_split : nullptr;
     if (((ctx->prof >> AGZO_PROF_GEMM) & 1u) && ctx->clk_used < kClkSlots) a.clk = ctx->clk + 4 * ctx->clk_used++;
     return a;
 }
@@ -808,7 +821,7 @@ int agzo_layer_forward_sketch(agzo_ctx* ctx, const agzo_layer* L, const void* W,
         TRY(check_y(ctx, L, Y));
         TRY(check_loss(ctx, L, loss, loss_dev));
     }
-    const Plan p = make_plan(*L, gemm && L->dtype == AGZO_F32 && !Y && loss && loss->kind == AGZO_LOSS_CE, loss && loss->kind == AGZO_LOSS_CE, false, 0, fused);
+    const Plan p = make_forward_plan(*L, gemm && L->dtype == AGZO_F32 && !Y && loss && loss->kind == AGZO_LOSS_CE, loss && loss->kind == AGZO_LOSS_CE, fused, gemm && Y);
     TRY(reserve(ctx, p.total));
     if (fused) {
         {
@@ -864,7 +877,7 @@ int agzo_perturbed_forward(agzo_ctx* ctx, const agzo_layer* L, const void* W, co
     TRY(check_operands(ctx, L, W, X));
     TRY(check_y(ctx, L, Y));
     TRY(check_loss(ctx, L, loss, loss_dev));
-    const Plan p = make_plan(*L, L->dtype == AGZO_F32 && !Y && loss && loss->kind == AGZO_LOSS_CE, loss && loss->kind == AGZO_LOSS_CE);
+    const Plan p = make_forward_plan(*L, L->dtype == AGZO_F32 && !Y && loss && loss->kind == AGZO_LOSS_CE, loss && loss->kind == AGZO_LOSS_CE, false, Y != nullptr);
     TRY(reserve(ctx, p.total));
     float* P = wsf(ctx, p.off_T);
     if (L->dtype != AGZO_BF16) {

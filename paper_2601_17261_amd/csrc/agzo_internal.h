@@ -163,6 +163,8 @@ struct GemmBf16Args {
     // planes [3][16][sk_mpad], sk_mpad = gemm_bf16_sketch_mpad(M); sk_partial receives gemm_bf16_sketch_splits(M)
     // partial sums [split][K][16], one per 128-token tile
     const bf16_t* sk_T = nullptr; int64_t sk_mpad = 0; float* sk_partial = nullptr;
+    // gemm_bf16_split_bytes() bytes of device scratch for a stored output whose few tiles share out d_in (NULL: they do not)
+    void* split_ws = nullptr;
     // telemetry (NULL: none): four 64-bit device words that workgroup 0 fills with the shader-clock counter and the
     // constant-rate counter at kernel entry and exit
     unsigned long long* clk = nullptr;
@@ -171,6 +173,7 @@ struct GemmBf16Args {
 // mode, no cross-entropy), which is then used for shapes with few 256 x 256 tiles
 int gemm_bf16_num_workgroups(int64_t M, int64_t N, bool small_ok);
 size_t gemm_bf16_ext_bytes(int64_t M, int64_t N, int r);
+size_t gemm_bf16_split_bytes(int64_t M, int64_t N, int64_t K);
 // true: a plain forward of this shape (no rank-r term, no shared-forward mode, no cross-entropy) runs in the 128 x 128
 // tiling, whose kernel can emit the range sketch from its LDS-staged X tiles (r <= 16, at most 64 token tiles)
 bool gemm_bf16_fuses_sketch(int64_t M, int64_t N, int r, bool large_tiles);

@@ -79,7 +79,10 @@ struct GemmItem {
     // fused range sketch (a launch of one problem; NULL: none): as in GemmParams
     const bf16_t* sk_T; int64_t sk_mpad; float* sk_partial;
     unsigned long long* clk;
+    // out 1 in a launch of one problem: so many shares of the slices, their sums in part (gemm_bf16_split_bytes(); NULL: one share)
+    int splits; float* part;
 };
+int gemm_bf16_mid_splits(int64_t M, int64_t N, int64_t K);
 // out 0: squared error (target_f32: of fp32 targets), 1: stored bf16 output
 bool gemm_bf16_mid_ok(const GemmItem& g, int out);
 hipError_t launch_gemm_bf16_mid(const GemmItem* a, int n, int out, bool target_f32, hipStream_t st);

@@ -1,6 +1,8 @@
 // Forward GEMM of the bf16 path in 128 x 128 tiles, for layers that give too few 256 x 256 tiles to fill the chip:
 //     OUT = 0:  f = sum over the tile of (X W^T (+ eps (X B) G^T) - Y*)^2     (f0, f+, f- of Sec. 4.1; Eq. 7 factored)
 //     OUT = 1:  Y = X W^T (+ eps (X B) G^T) stored as bf16
+//     OUT = 2:  the same sums over a share of the slices, stored as they are held; gemm_bf16_mid_finish_kernel adds the shares
+//               in order and stores Y
 // for d_in, tokens and outputs of at least 128, the rank-r extension as prepared operands.  Other shapes keep
 // gemm_bf16_small.hip.
 //
@@ -20,6 +22,8 @@
 // edge, so that no load needs a bound; the squared error leaves out what the tile before it has counted, a stored output is
 // stored twice with the same bits.  A last slice that d_in does not fill: its direct loads get a descriptor with a range and the
 // lanes past d_in an offset beyond it, which loads zeros.  Rows of target or output need no alignment.
+#include <algorithm>
+
 #include "gemm_bf16_common.h"
 
 namespace agzo {
@@ -62,24 +66,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
     // workgroup -> tile: ids are dealt round-robin over the 8 XCDs; each XCD takes a contiguous run of the problem's tiles, in
     // bands of eight token tiles per output tile
-    const int count = p.tiles_m * p.tiles_n, per = count / 8;
+    // (OUT = 2: the tiles once per share of the slices, share by share)
+    const int tiles = p.tiles_m * p.tiles_n, count = OUT == 2 ? tiles * p.splits : tiles, per = count / 8;
     int lin = (int)bx_;
     if (lin < per * 8) lin = (lin % 8) * per + lin / 8;
+    const int share = OUT == 2 ? __builtin_amdgcn_readfirstlane(lin / tiles) : 0;
+    if (OUT == 2) lin -= share * tiles;
     constexpr int BAND = 8;
     const int band = lin / (BAND * p.tiles_n), first = band * BAND;
     const int rows = min(BAND, p.tiles_m - first), in_band = lin - band * BAND * p.tiles_n;
     const int tm = __builtin_amdgcn_readfirstlane(first + in_band % rows), tn = __builtin_amdgcn_readfirstlane(in_band / rows);
     const int64_t m0 = min((int64_t)tm * MT, p.M - MT), n0 = min((int64_t)tn * MT, p.N - MT);
 
-    const bool has_ext = p.Xext != nullptr;
-    const bf16_t *xb = p.X + m0 * p.ldx, *wb_ = p.W + n0 * p.ldw;
+    // this workgroup's slices: all, or a share of the d_in slices (the last share: with the extension behind them)
+    const int nd_all = (int)((p.K + BK - 1) / BK);
+    const int kbeg = OUT == 2 ? nd_all * share / p.splits : 0, kend = OUT == 2 ? nd_all * (share + 1) / p.splits : nd_all;
+    const bool has_ext = p.Xext != nullptr && kend == nd_all;
+    const bf16_t *xb = p.X + m0 * p.ldx + (int64_t)kbeg * BK, *wb_ = p.W + n0 * p.ldw + (int64_t)kbeg * BK;
     const bf16_t *xb2 = has_ext ? p.Xext + m0 * p.ext_ld : xb, *wb2 = has_ext ? p.Wext + n0 * p.ext_ld : wb_;
     const int row0 = 8 * wave + (lane >> 3);
     const int chunk0 = (lane & 7) ^ ((row0 >> 1) & 7);
     const int vx = (int)(((int64_t)row0 * p.ldx + chunk0 * 8) * 2), vw = (int)(((int64_t)mid_perm(row0) * p.ldw + chunk0 * 8) * 2);
     const int vx2 = (row0 * p.ext_ld + chunk0 * 8) * 2, vw2 = (mid_perm(row0) * p.ext_ld + chunk0 * 8) * 2;
     const int gsx = (int)(64 * p.ldx), gsw = (int)(64 * p.ldw), gs2 = 64 * p.ext_ld;   // bytes between row groups
-    const int nfull = (int)(p.K / BK), nd = (int)((p.K + BK - 1) / BK);             // d_in slices: whole ones, all
+    const int nfull = min((int)(p.K / BK), kend) - kbeg, nd = kend - kbeg;          // d_in slices: whole ones, all
     const int npipe = nd + (has_ext ? p.ext_ld / BK : 0);
     const int tail_off = (chunk0 * 8 >= (int)(p.K % BK)) ? kPastEnd : 0;             // (of the slice that is not whole)
     typedef __attribute__((address_space(3))) void* lptr_t;
@@ -251,7 +261,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7");
     __builtin_amdgcn_s_waitcnt(0x0F70);                      // the slices fetched past the end
     const int64_t row_new = (int64_t)tm * MT, col_new = (int64_t)tn * MT;
-    if constexpr (OUT == 1) {
+    if constexpr (OUT == 2) {
+        floatx4* dst = reinterpret_cast<floatx4*>(p.part) + ((int64_t)(share * tiles + tm * p.tiles_n + tn) * 4 + wave) * 16 * 64 + lane;
+#pragma unroll
+        for (int J = 0; J < 4; ++J)
+#pragma unroll
+            for (int I = 0; I < 4; ++I) dst[(J * 4 + I) * 64] = acc[I][J];
+    } else if constexpr (OUT == 1) {
 #pragma unroll
         for (int J = 0; J < 4; ++J) {
             const int64_t row = m0 + wb * 64 + J * 16 + lc, col = n0 + wa * 64 + lg * 16;
@@ -305,6 +321,51 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (p.clk && bx_ == 0 && tid == 0) { p.clk[2] = __builtin_readcyclecounter(); p.clk[3] = wall_clock64(); }
 }
 
+// Y from the shares' sums: one workgroup per tile and token block of every wave, four shares' loads of a thread in flight (a
+// workgroup per tile took 7 us for 64 tiles of four shares: latency)
+__global__ __launch_bounds__(256) void gemm_bf16_mid_finish_kernel(const GemmItem p) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wa = wave >> 1, wb = wave & 1, lc = lane & 15, lg = lane >> 4;
+    const int tiles = p.tiles_m * p.tiles_n, tm = blockIdx.x / p.tiles_n, tn = blockIdx.x % p.tiles_n, J = blockIdx.y;
+    const int64_t m0 = min((int64_t)tm * MT, p.M - MT), n0 = min((int64_t)tn * MT, p.N - MT);
+    const floatx4* src = reinterpret_cast<const floatx4*>(p.part) + (((int64_t)blockIdx.x * 4 + wave) * 16 + J * 4) * 64 + lane;
+    floatx4 sum[4] = {};
+    for (int s0 = 0; s0 < p.splits; s0 += 4) {
+        floatx4 v[4][4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int I = 0; I < 4; ++I) v[s][I] = s0 + s < p.splits ? src[(int64_t)(s0 + s) * tiles * 4096 + I * 64] : floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int I = 0; I < 4; ++I) sum[I] += v[s][I];
+    }
+    uint32_t w[8];
+#pragma unroll
+    for (int I = 0; I < 4; ++I) {
+        w[2 * I] = pack_bf16x2(sum[I][0], sum[I][1]);
+        w[2 * I + 1] = pack_bf16x2(sum[I][2], sum[I][3]);
+    }
+    bf16_t* dst = reinterpret_cast<bf16_t*>(p.Y) + (m0 + wb * 64 + J * 16 + lc) * p.ldy + n0 + wa * 64 + lg * 16;
+    store16_any(dst, make_uint4(w[0], w[1], w[2], w[3]));
+    store16_any(dst + 8, make_uint4(w[4], w[5], w[6], w[7]));
+}
+
+// Shares of the d_in slices for a stored output.  A lone launch of few tiles leaves compute units idle while each tile walks all
+// of d_in at 0.5 us a slice (one workgroup per compute unit: bound by LDS reads): as many shares as fill the chip, of eight
+// slices at least, for the adding costs a launch of some 4 us.  The seven projections of a decoder layer on 385 tokens (32, 64 and 192
+// tiles; d_in 2048 and 6144): 191 us in one share each, 139 so.  Not for losses, whose tiles several layers usually share a
+// launch with
+int gemm_bf16_mid_splits(int64_t M, int64_t N, int64_t K) {
+    const int64_t tiles = ((M + MT - 1) / MT) * ((N + MT - 1) / MT), slices = K / BK;
+    if (M < MT || N < MT || tiles > 128) return 1;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(256 / tiles, slices / 8));
+}
+size_t gemm_bf16_split_bytes(int64_t M, int64_t N, int64_t K) {
+    const int s = gemm_bf16_mid_splits(M, N, K);
+    return s > 1 ? (size_t)s * ((M + MT - 1) / MT) * ((N + MT - 1) / MT) * MT * MT * sizeof(float) : 0;
+}
+
 template <int OUT, bool T_F32, bool SK, bool DEEP, int CAP>
 static hipError_t launch_mid_ring(const KBatch<GemmItem, CAP>& tb, unsigned blocks, hipStream_t st) {
     const int smem = (DEEP ? 10 : 5) * MTILE_BYTES + (SK ? MSK_SMEM : 0);
@@ -341,6 +402,19 @@ hipError_t launch_gemm_bf16_mid(const GemmItem* a, int n, int out, bool target_f
         int at = i;             // deepest first, so that the launch does not end on a few long tiles
         for (; at > 0 && a[order[at - 1]].K < a[i].K; --at) order[at] = order[at - 1];
         order[at] = i;
+    }
+    if (n == 1 && a[0].part && out == 1 && a[0].splits > 1) {
+        KBatch<GemmItem, 1> one{1, {0}, {0}, {a[0]}};
+        GemmItem& g = one.a[0];
+        g.tiles_m = (int)((g.M + MT - 1) / MT);
+        g.tiles_n = (int)((g.N + MT - 1) / MT);
+        if (g.sk_T || g.splits > g.K / BK) return hipErrorInvalidValue;
+        const unsigned tiles = (unsigned)(g.tiles_m * g.tiles_n);
+        one.gx[0] = tiles * (unsigned)g.splits;
+        hipError_t e = launch_mid_ring<2, false, false, true>(one, one.gx[0], st);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(gemm_bf16_mid_finish_kernel, dim3(tiles, 4), dim3(256), 0, st, g);
+        return hipGetLastError();
     }
     for (int i = 0; i < n; ++i) {
         GemmItem g = a[order[i]];
