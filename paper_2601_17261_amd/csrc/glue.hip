@@ -80,62 +80,78 @@ __global__ __launch_bounds__(256) void glue_add_kernel(bf16_t* __restrict__ h, i
 
 // ---------------------------------------------------------------------------
 // Attention core of a decoder layer (grouped-query, causal, 128-wide heads, per-head RMS normalisation of queries and
-// keys, rotary embedding): the model between the q / k / v projections and the o projection.  Two kernels.
+// keys, rotary embedding): the model between the q / k / v projections and the o projection.  Three kernels.
 //
 // prep: q, k <- rope(rmsnorm_per_head(.)), head-major [seq][head][t][128]; v transposed to [seq][kv head][128][t_pad]
-//       (t_pad = seq_len rounded up to 32, the padding zero) so that the second product reads keys contiguously.
-// attention: one wave = 32 queries of one head (two groups of 16).  Scores are computed transposed, S^T = K Q^T (keys x queries), with
+//       (t_pad = seq_len rounded up to 64, the padding zero) so that the second product reads keys contiguously.
+// attention: four waves of 32 queries of one head (two groups of 16) against tiles of 64 keys that they share in LDS.  Scores are
+//       computed transposed, S^T = K Q^T (keys x queries), with
 //       v_mfma_f32_16x16x32_bf16: a lane then holds, for ONE query (column lane % 16), the scores of keys 4 g + e of each
 //       16-key block (g = lane / 16), so the softmax's running maximum and sum are per-lane scalars up to a reduction
 //       over the four g, and the rescaling of the output accumulators (out^T = V^T P^T, same column = query) is a
-//       per-lane scalar too.  The eight probabilities a lane holds per 32-key step (two 16-key blocks) go straight into
+//       per-lane scalar too.  The eight probabilities a lane holds per 32 keys (two 16-key blocks) go straight into
 //       the second product as its operand: a sum over keys does not care about their order, so instead of re-laying P
-//       out, V^T is read in the order P is held (keys 4 g .. 4 g + 3 of both blocks: two 8-byte loads).  No LDS.
+//       out, V^T is stored in the order P is held (of every 32 keys, those at 4 g .. 4 g + 3 of both blocks side by side).
+//       Per tile and group of queries a wave has 512 cycles of matrix work, about as much exponential and other vector work (the
+//       mask only on tiles that reach past the group, the rescaling only where a maximum moved) and 8 KB of LDS reads; two
+//       workgroups per compute unit overlap them.  With every wave fetching its own K and V^T fragments from memory 16 x 512
+//       tokens of 16 heads took 160 us, now 50 (345 TFLOP/s of causal work); prep with a thread's own angles per head 34, now 21.
 // ---------------------------------------------------------------------------
 constexpr int HEAD_DIM = 128;
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
 
-// grid.x covers (token, head) pairs of q and k, 16 lanes each; the rotary pair (i, i + 64) sits 8 lanes apart
+// 16 lanes per item: PREP_HEADS heads of q or of k at one token, which share the angles; the rotary pair (i, i + 64) sits 8 lanes
+// apart
+constexpr int PREP_HEADS = 4;
 __global__ __launch_bounds__(256) void glue_qk_prep_kernel(const bf16_t* __restrict__ q, int64_t ldq, const bf16_t* __restrict__ k,
                                                            int64_t ldk, bf16_t* __restrict__ Qr, bf16_t* __restrict__ Kr, int n_seq,
                                                            int seq_len, int n_heads, int n_kv, float log2_theta) {
     const int64_t item = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 4;
     const int j = threadIdx.x & 15;
-    const int64_t n_q = (int64_t)n_seq * seq_len * n_heads, n_k = (int64_t)n_seq * seq_len * n_kv;
-    if (item >= n_q + n_k) return;                   // whole 16-lane groups leave together
-    const bool is_q = item < n_q;
-    const int64_t it = is_q ? item : item - n_q;
-    const int heads = is_q ? n_heads : n_kv;
-    const int64_t tok = it / heads;
-    const int head = (int)(it - tok * heads);
+    const int gq = (n_heads + PREP_HEADS - 1) / PREP_HEADS, gk = (n_kv + PREP_HEADS - 1) / PREP_HEADS;
+    if (item >= (int64_t)n_seq * seq_len * (gq + gk)) return;              // whole 16-lane groups leave together
+    const int64_t tok = item / (gq + gk);
+    const int grp = (int)(item - tok * (gq + gk));
+    const bool is_q = grp < gq;
+    const int heads = is_q ? n_heads : n_kv, h0 = (is_q ? grp : grp - gq) * PREP_HEADS;
     const int seq = (int)(tok / seq_len), t = (int)(tok - (int64_t)seq * seq_len);
-    const bf16_t* src = (is_q ? q + tok * ldq : k + tok * ldk) + head * HEAD_DIM + 8 * j;
-    float f[8];
-    unpack8(*reinterpret_cast<const uint4*>(src), f);
-    float ss = 0.f;
+    const bf16_t* src = (is_q ? q + tok * ldq : k + tok * ldk) + h0 * HEAD_DIM + 8 * j;
+    uint4 raw[PREP_HEADS];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) ss = fmaf(f[i], f[i], ss);
-#pragma unroll
-    for (int off = 8; off > 0; off >>= 1) ss += __shfl_xor(ss, off);      // the 16 lanes of this head
-    const float scale = rsqrtf(ss / (float)HEAD_DIM + 1e-6f);
-    float o[8];
+    for (int h = 0; h < PREP_HEADS; ++h) raw[h] = h0 + h < heads ? *reinterpret_cast<const uint4*>(src + h * HEAD_DIM) : make_uint4(0, 0, 0, 0);
+    float sn[8], cs[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        const float mine = f[i] * scale;
-        const float other = __shfl_xor(mine, 8);
         const int idx = 8 * (j & 7) + i;                                   // pair index 0..63
         const float inv = exp2f(-(float)idx * (2.0f / HEAD_DIM) * log2_theta);
-        float sn, cs;
-        sincosf((float)t * inv, &sn, &cs);
-        o[i] = (j < 8) ? mine * cs - other * sn : mine * cs + other * sn;  // first half: x1 c - x2 s; second: x2 c + x1 s
+        sincosf((float)t * inv, &sn[i], &cs[i]);
     }
-    bf16_t* dst = (is_q ? Qr : Kr) + (((int64_t)seq * heads + head) * seq_len + t) * HEAD_DIM + 8 * j;
-    *reinterpret_cast<uint4*>(dst) = pack8(o);
+    bf16_t* dst = (is_q ? Qr : Kr) + (((int64_t)seq * heads + h0) * seq_len + t) * HEAD_DIM + 8 * j;
+#pragma unroll
+    for (int h = 0; h < PREP_HEADS; ++h) {
+        float f[8];
+        unpack8(raw[h], f);
+        float ss = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) ss = fmaf(f[i], f[i], ss);
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) ss += __shfl_xor(ss, off);  // the 16 lanes of this head
+        const float scale = rsqrtf(ss / (float)HEAD_DIM + 1e-6f);
+        float o[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float mine = f[i] * scale;
+            const float other = __shfl_xor(mine, 8);
+            o[i] = (j < 8) ? mine * cs[i] - other * sn[i] : mine * cs[i] + other * sn[i];  // first half: x1 c - x2 s; second: x2 c + x1 s
+        }
+        if (h0 + h < heads) *reinterpret_cast<uint4*>(dst + (int64_t)h * seq_len * HEAD_DIM) = pack8(o);
+    }
 }
 
 // Vt[seq][kv head][d][t_pad]: a thread takes 8 values of one token (16-byte load) and stores them to 8 rows; the lanes of
 // a wave are consecutive tokens, so every store instruction writes 128 contiguous bytes.  Tokens >= seq_len write zeros.
+// Of every 32 tokens, token 16 b + 4 g + e is stored at 8 g + 4 b + e.
 __global__ __launch_bounds__(256) void glue_v_transpose_kernel(const bf16_t* __restrict__ v, int64_t ldv, bf16_t* __restrict__ Vt,
                                                                int n_seq, int seq_len, int t_pad, int n_kv) {
     const int t = blockIdx.x * 256 + threadIdx.x;
@@ -144,29 +160,55 @@ __global__ __launch_bounds__(256) void glue_v_transpose_kernel(const bf16_t* __r
     uint4 raw = make_uint4(0, 0, 0, 0);
     if (t < seq_len) raw = *reinterpret_cast<const uint4*>(v + ((int64_t)seq * seq_len + t) * ldv + head * HEAD_DIM + 8 * c);
     const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
-    bf16_t* dst = Vt + (((int64_t)seq * n_kv + head) * HEAD_DIM + 8 * c) * t_pad + t;
+    const int at = (t & ~31) | ((t >> 2) & 3) * 8 | ((t >> 4) & 1) * 4 | (t & 3);
+    bf16_t* dst = Vt + (((int64_t)seq * n_kv + head) * HEAD_DIM + 8 * c) * t_pad + at;
 #pragma unroll
     for (int i = 0; i < 8; ++i) dst[(int64_t)i * t_pad] = (bf16_t)((i & 1) ? (w[i >> 1] >> 16) : (w[i >> 1] & 0xFFFFu));
 }
 
-// QG 16-query groups per wave: every K and V^T fragment a wave loads serves QG matrix instructions
+// QG 16-query groups per wave: every K and V^T fragment a wave reads serves QG matrix instructions
 constexpr int ATT_QG = 2;
 constexpr int ATT_WAVE_Q = 16 * ATT_QG;     // queries per wave
 constexpr int ATT_WG_Q = 4 * ATT_WAVE_Q;    // queries per workgroup
+constexpr int ATT_KEYS = 64;                // keys per tile
+constexpr int ATT_TILE = ATT_KEYS * HEAD_DIM * 2;        // bytes of a K or V^T tile
+constexpr int ATT_SMEM = 4 * ATT_TILE;      // two stages of both
 
-__global__ __launch_bounds__(256) void glue_attention_kernel(const bf16_t* __restrict__ Qr, const bf16_t* __restrict__ Kr,
-                                                             const bf16_t* __restrict__ Vt, bf16_t* __restrict__ out, int64_t ldo,
-                                                             int seq_len, int t_pad, int n_heads, int n_kv) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void glue_attention_kernel(
+        const bf16_t* __restrict__ Qr, const bf16_t* __restrict__ Kr, const bf16_t* __restrict__ Vt, bf16_t* __restrict__ out, int64_t ldo,
+        int seq_len, int t_pad, int n_heads, int n_kv) {
+    extern __shared__ __align__(16) char att_smem[];
+    typedef __attribute__((address_space(3))) void* lptr_t;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, g = lane >> 4;
     const int head = blockIdx.y, seq = blockIdx.z, kvh = head / (n_heads / n_kv);
     // heavy tiles first: the last queries of a sequence see the most keys
-    const int q0 = ((int)(gridDim.x - 1 - blockIdx.x) * 4 + wave) * ATT_WAVE_Q;
-    if (q0 >= seq_len) return;                                         // wave-uniform
+    const int wg_q0 = (int)(gridDim.x - 1 - blockIdx.x) * ATT_WG_Q, q0 = wg_q0 + wave * ATT_WAVE_Q;
     const bf16_t* Qh = Qr + ((int64_t)seq * n_heads + head) * seq_len * HEAD_DIM;
-    const bf16_t* Kh = Kr + ((int64_t)seq * n_kv + kvh) * seq_len * HEAD_DIM;
-    const bf16_t* Vh = Vt + ((int64_t)seq * n_kv + kvh) * HEAD_DIM * t_pad;
+    auto rsrc = [](const bf16_t* base) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, (int)0xFFFFFFFFu, 0x00020000); };
+    const __amdgpu_buffer_rsrc_t rk = rsrc(Kr + ((int64_t)seq * n_kv + kvh) * seq_len * HEAD_DIM);
+    const __amdgpu_buffer_rsrc_t rv = rsrc(Vt + ((int64_t)seq * n_kv + kvh) * HEAD_DIM * t_pad);
     union Frag { uint4 u; bf16x8_t v; };
+    const int tiles = (min(wg_q0 + ATT_WG_Q, seq_len) + ATT_KEYS - 1) / ATT_KEYS;      // that any query of this workgroup may see
+    // direct loads of tile j into stage j & 1: K rows of 256 bytes (16-byte chunk c of row r at c ^ (r mod 16)), V^T rows of 128
+    // bytes (chunk c at c ^ (r / 2 mod 8)); four of each per wave.  Keys past the end repeat the last one, masked
+    auto request = [&](int j) __attribute__((always_inline)) {
+        char* stage = att_smem + (j & 1) * (2 * ATT_TILE) + wave * 4096;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int row = 16 * wave + 4 * t + (lane >> 4);
+            const int off = min(j * ATT_KEYS + row, seq_len - 1) * (HEAD_DIM * 2) + (((lane & 15) ^ (row & 15)) << 4);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (lptr_t)(stage + t * 1024), 16, off, 0, 0, 0);
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int row = 32 * wave + 8 * t + (lane >> 3);
+            const int off = row * (t_pad * 2) + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lptr_t)(stage + ATT_TILE + t * 1024), 16, off, j * (ATT_KEYS * 2), 0, 0);
+        }
+    };
+    request(0);
     int qi[ATT_QG];                                                    // rows past the end repeat the last query, unstored
     Frag qf[ATT_QG][4];
 #pragma unroll
@@ -180,79 +222,87 @@ __global__ __launch_bounds__(256) void glue_attention_kernel(const bf16_t* __res
     for (int qg = 0; qg < ATT_QG; ++qg)
 #pragma unroll
         for (int db = 0; db < 8; ++db) acc[qg][db] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-    float m_run[ATT_QG], l_run[ATT_QG];
+    float m_run[ATT_QG], l_run[ATT_QG];                                // maximum of the raw scores
 #pragma unroll
     for (int qg = 0; qg < ATT_QG; ++qg) { m_run[qg] = -INFINITY; l_run[qg] = 0.f; }
     const float sc = 1.44269504088896341f * 0.08838834764831845f;      // log2(e) / sqrt(128)
-    const int k_end = min(q0 + ATT_WAVE_Q - 1, seq_len - 1);           // last key any query of this wave may see
-    // K operand of a 32-key step: this lane's rows are keys kb + 16 blk + n (clamped), its columns 32 ks + 8 g ..
-    auto load_k = [&](int kb, Frag (&kf)[2][4]) __attribute__((always_inline)) {
+    for (int j = 0; j < tiles; ++j) {
+        // this wave's loads of tile j have landed, then everybody's; everybody is done with the other stage
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        if (j + 1 < tiles) request(j + 1);
+        const int kb = j * ATT_KEYS;
+        if (kb > q0 + ATT_WAVE_Q - 1) continue;                        // no query of this wave sees the tile (wave-uniform)
+        // (fragments are read as bf16x8_t: behind a read of another type the compiler waits for every direct load in flight)
+        const char* ks_ = att_smem + (j & 1) * (2 * ATT_TILE);
+        const char* vs_ = ks_ + ATT_TILE;
+        floatx4_t s[ATT_QG][4];
 #pragma unroll
-        for (int blk = 0; blk < 2; ++blk) {
-            const int krow = min(kb + 16 * blk + n, seq_len - 1);
+        for (int blk = 0; blk < 4; ++blk) {
+            Frag kf[4];
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) kf[blk][ks].u = *reinterpret_cast<const uint4*>(Kh + (int64_t)krow * HEAD_DIM + 32 * ks + 8 * g);
-        }
-    };
-    Frag kf[2][4];
-    load_k(0, kf);
-    for (int kb = 0; kb <= k_end; kb += 32) {
-        // V^T operands of this step: row = dim 16 db + n, the keys in the order the probabilities are held (4 g .. 4 g + 3
-        // of both 16-key blocks); requested before the scores so that they arrive under the first product and the softmax
-        Frag vf[8];
+            for (int ks = 0; ks < 4; ++ks) kf[ks].v = *reinterpret_cast<const bf16x8_t*>(ks_ + (16 * blk + n) * 256 + (((4 * ks + g) ^ n) << 4));
 #pragma unroll
-        for (int db = 0; db < 8; ++db) {
-            const bf16_t* vrow = Vh + (int64_t)(16 * db + n) * t_pad + kb + 4 * g;
-            const uint2 v0 = *reinterpret_cast<const uint2*>(vrow), v1 = *reinterpret_cast<const uint2*>(vrow + 16);
-            vf[db].u = make_uint4(v0.x, v0.y, v1.x, v1.y);
-        }
-        floatx4_t s[ATT_QG][2];
-#pragma unroll
-        for (int qg = 0; qg < ATT_QG; ++qg)
-#pragma unroll
-            for (int blk = 0; blk < 2; ++blk) {
+            for (int qg = 0; qg < ATT_QG; ++qg) {
                 s[qg][blk] = floatx4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int ks = 0; ks < 4; ++ks)
-                    s[qg][blk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[blk][ks].v, qf[qg][ks].v, s[qg][blk], 0, 0, 0);
+                    s[qg][blk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks].v, qf[qg][ks].v, s[qg][blk], 0, 0, 0);
             }
-        // the next step's K operands (the step after the last one re-reads clamped rows and is dropped)
-        load_k(kb + 32, kf);
+        }
+        Frag pf[ATT_QG][2];
+        const bool mask = kb + ATT_KEYS - 1 > q0;                      // wave-uniform: some query ends inside the tile
 #pragma unroll
         for (int qg = 0; qg < ATT_QG; ++qg) {
             // lane: query qi[qg] (column n), keys kb + 16 blk + 4 g + e
-            float p[8], mx = m_run[qg];
+            if (mask) {
+                const int last = qi[qg] - kb - 4 * g;
 #pragma unroll
-            for (int blk = 0; blk < 2; ++blk)
+                for (int blk = 0; blk < 4; ++blk)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int key = kb + 16 * blk + 4 * g + e;
-                    const float v = (key <= qi[qg] && key < seq_len) ? s[qg][blk][e] * sc : -INFINITY;
-                    p[4 * blk + e] = v;
-                    mx = fmaxf(mx, v);
-                }
+                    for (int e = 0; e < 4; ++e) s[qg][blk][e] = 16 * blk + e <= last ? s[qg][blk][e] : -INFINITY;
+            }
+            float mx = m_run[qg];
+#pragma unroll
+            for (int blk = 0; blk < 4; ++blk)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) mx = fmaxf(mx, s[qg][blk][e]);
             mx = fmaxf(mx, __shfl_xor(mx, 16));
             mx = fmaxf(mx, __shfl_xor(mx, 32));
-            // a group of queries that sees none of this step's keys (its rows all lie before kb) keeps its state:
-            // mx = m_run, alpha = 1, every p = 0.  On a group's first step m_run = -inf and mx is finite (key 0 is visible).
-            const float alpha = exp2f(m_run[qg] - mx);
-            float psum = 0.f;
+            // a group of queries that sees none of this tile's keys (its rows all lie before kb) keeps its state:
+            // mx = m_run, alpha = 1, every p = 0.  On a group's first tile m_run = -inf and mx is finite (key 0 is visible).
+            if (__any(mx != m_run[qg])) {
+                const float alpha = __builtin_amdgcn_exp2f((m_run[qg] - mx) * sc);
+                l_run[qg] *= alpha;
+                m_run[qg] = mx;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                p[i] = exp2f(p[i] - mx);
+                for (int db = 0; db < 8; ++db)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[qg][db][e] *= alpha;
+            }
+            const float top = mx * sc;
+            float p[16], psum = 0.f;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                p[i] = __builtin_amdgcn_exp2f(fmaf(s[qg][i >> 2][i & 3], sc, -top));
                 psum += p[i];
             }
-            l_run[qg] = l_run[qg] * alpha + psum;
-            m_run[qg] = mx;
-            Frag pf;
-            pf.u = make_uint4(pack_bf16x2(p[0], p[1]), pack_bf16x2(p[2], p[3]), pack_bf16x2(p[4], p[5]), pack_bf16x2(p[6], p[7]));
+            l_run[qg] += psum;
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                pf[qg][h].u = make_uint4(pack_bf16x2(p[8 * h], p[8 * h + 1]), pack_bf16x2(p[8 * h + 2], p[8 * h + 3]),
+                                         pack_bf16x2(p[8 * h + 4], p[8 * h + 5]), pack_bf16x2(p[8 * h + 6], p[8 * h + 7]));
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int db = 0; db < 8; ++db) {
+                Frag vf;                                               // dim 16 db + n, the keys in the order the probabilities are held
+                vf.v = *reinterpret_cast<const bf16x8_t*>(vs_ + (16 * db + n) * 128 + (((4 * h + g) ^ ((n >> 1) & 7)) << 4));
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[qg][db][e] *= alpha;
-                acc[qg][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[db].v, pf.v, acc[qg][db], 0, 0, 0);
+                for (int qg = 0; qg < ATT_QG; ++qg) acc[qg][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf.v, pf[qg][h].v, acc[qg][db], 0, 0, 0);
             }
-        }
     }
 #pragma unroll
     for (int qg = 0; qg < ATT_QG; ++qg) {
@@ -270,7 +320,7 @@ __global__ __launch_bounds__(256) void glue_attention_kernel(const bf16_t* __res
 }
 
 size_t glue_attention_workspace_bytes(int n_seq, int seq_len, int n_heads, int n_kv) {
-    const int64_t t_pad = (seq_len + 31) / 32 * 32;
+    const int64_t t_pad = (seq_len + ATT_KEYS - 1) / ATT_KEYS * ATT_KEYS;
     return (size_t)n_seq * ((int64_t)(n_heads + n_kv) * seq_len + (int64_t)n_kv * t_pad) * HEAD_DIM * sizeof(bf16_t) + 256;
 }
 
@@ -278,11 +328,11 @@ hipError_t launch_glue_attention(const bf16_t* q, int64_t ldq, const bf16_t* k, 
                                  bf16_t* out, int64_t ldo, int n_seq, int seq_len, int n_heads, int n_kv, float rope_theta,
                                  void* workspace, hipStream_t st) {
     if (n_seq == 0 || seq_len == 0) return hipSuccess;
-    const int t_pad = (seq_len + 31) / 32 * 32;
+    const int t_pad = (seq_len + ATT_KEYS - 1) / ATT_KEYS * ATT_KEYS;
     bf16_t* Qr = static_cast<bf16_t*>(workspace);
     bf16_t* Kr = Qr + (int64_t)n_seq * n_heads * seq_len * HEAD_DIM;
     bf16_t* Vt = Kr + (int64_t)n_seq * n_kv * seq_len * HEAD_DIM;
-    const int64_t items = (int64_t)n_seq * seq_len * (n_heads + n_kv) * 16;
+    const int64_t items = (int64_t)n_seq * seq_len * ((n_heads + PREP_HEADS - 1) / PREP_HEADS + (n_kv + PREP_HEADS - 1) / PREP_HEADS) * 16;
     hipLaunchKernelGGL(glue_qk_prep_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, q, ldq, k, ldk, Qr, Kr, n_seq,
                        seq_len, n_heads, n_kv, log2f(rope_theta));
     hipError_t e = hipGetLastError();
@@ -291,7 +341,13 @@ hipError_t launch_glue_attention(const bf16_t* q, int64_t ldq, const bf16_t* k, 
                        dim3(256), 0, st, v, ldv, Vt, n_seq, seq_len, t_pad, n_kv);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(glue_attention_kernel, dim3((unsigned)((seq_len + ATT_WG_Q - 1) / ATT_WG_Q), (unsigned)n_heads, (unsigned)n_seq), dim3(256), 0, st,
+    static bool attr_set = false;
+    if (!attr_set) {
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(glue_attention_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, ATT_SMEM);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    hipLaunchKernelGGL(glue_attention_kernel, dim3((unsigned)((seq_len + ATT_WG_Q - 1) / ATT_WG_Q), (unsigned)n_heads, (unsigned)n_seq), dim3(256), ATT_SMEM, st,
                        Qr, Kr, Vt, out, ldo, seq_len, t_pad, n_heads, n_kv);
     return hipGetLastError();
 }
