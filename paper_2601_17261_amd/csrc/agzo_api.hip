@@ -172,6 +172,8 @@ Plan make_forward_plan(const agzo_layer& L, bool need_ybuf, bool ce, bool fused_
 int reserve(agzo_ctx* ctx, size_t bytes) {
     if (bytes <= ctx->ws_bytes) return 0;
     HIPCHK(hipStreamSynchronize(ctx->stream));
+    // a context that needs more once will need more again (the layers of a model, one after the other): half as much again
+    if (ctx->ws) bytes = std::max(bytes, ctx->ws_bytes + ctx->ws_bytes / 2);
     if (ctx->ws) HIPCHK(hipFree(ctx->ws));
     ctx->ws = nullptr;
     ctx->ws_bytes = 0;
