@@ -143,6 +143,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         if (f < p.K) *reinterpret_cast<float4*>(p.sk_partial + ((int64_t)tm * p.K + f) * MSK_RP + 4 * g) = make_float4(s[0], s[1], s[2], s[3]);
     };
 
+    // a stored output has the bits of one whose shares of d_in are added by gemm_bf16_mid_finish_kernel: the sums of a share are
+    // moved to `tot` behind its last slice
+    constexpr bool FOLD = SK && OUT == 1;
+    floatx4 tot[FOLD ? 4 : 1][4];
+    int fold_share = 0;
+    auto fold = [&]() __attribute__((always_inline)) {
+        asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7");
+#pragma unroll
+        for (int I = 0; I < 4; ++I)
+#pragma unroll
+            for (int J = 0; J < 4; ++J) {
+                tot[FOLD ? I : 0][J] = fold_share == 0 ? acc[I][J] : tot[FOLD ? I : 0][J] + acc[I][J];
+                acc[I][J] = floatx4{0.f, 0.f, 0.f, 0.f};
+            }
+        // (named, so that the zeros are written in front of it: the next matrix instructions read them)
+        asm volatile("s_nop 7" : "+v"(acc[0][0]), "+v"(acc[0][1]), "+v"(acc[0][2]), "+v"(acc[0][3]), "+v"(acc[1][0]), "+v"(acc[1][1]), "+v"(acc[1][2]), "+v"(acc[1][3]),
+                                 "+v"(acc[2][0]), "+v"(acc[2][1]), "+v"(acc[2][2]), "+v"(acc[2][3]), "+v"(acc[3][0]), "+v"(acc[3][1]), "+v"(acc[3][2]), "+v"(acc[3][3]));
+        ++fold_share;
+    };
+
     // ---- source of a slice: d_in slices, then the extension operands ----
     __amdgpu_buffer_rsrc_t src_rsx = mid_rsrc(xb), src_rsw = mid_rsrc(wb_);
     int src_so = 0, src_vxt[4], src_vwt[4];
@@ -256,10 +276,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         block(IC<1>{}, wcur, xcur, IC<2>{}, xput);
         wput = (wput == WS - 1) ? 0 : wput + 1;
         xput = (xput == XS - 1) ? 0 : xput + 1;
+        if constexpr (FOLD)
+            if (fold_share + 1 < p.splits && kt + 1 == nd * (fold_share + 1) / p.splits) fold();
     }
     // 24 wait states before the first read of a result: the compiler does not know of the instructions above
     asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7");
     __builtin_amdgcn_s_waitcnt(0x0F70);                      // the slices fetched past the end
+    if constexpr (FOLD) {
+        if (fold_share > 0) {
+#pragma unroll
+            for (int I = 0; I < 4; ++I)
+#pragma unroll
+                for (int J = 0; J < 4; ++J) acc[I][J] = tot[I][J] + acc[I][J];
+        }
+    }
     const int64_t row_new = (int64_t)tm * MT, col_new = (int64_t)tn * MT;
     if constexpr (OUT == 2) {
         floatx4* dst = reinterpret_cast<floatx4*>(p.part) + ((int64_t)(share * tiles + tm * p.tiles_n + tn) * 4 + wave) * 16 * 64 + lane;
