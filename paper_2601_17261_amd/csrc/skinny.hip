@@ -390,7 +390,10 @@ hipError_t launch_xq_bf16(const bf16_t* X, int64_t ldx, int64_t M, int64_t K, co
 }
 
 // ---------------------------------------------------------------------------
-// xtt: workgroup = (panel of 128 features) x (token range); waves interleave 32-token steps.
+// xtt: r <= 16: workgroup = (panel of 128 features) x (token range); waves interleave 32-token steps and add their sums in LDS.
+// r > 16: a wave has a panel and a token range of its own.  Its steps carry 48 to 96 matrix instructions, so a range of a few
+// steps is work enough, while adding four waves' sums (one after the other, 128 rows of up to 64 columns) took longer than the
+// three steps each of them had: r = 64, 4096 tokens of seven 4B-sized layers 161 us, now 109.
 // MFMA roles: A = T^T planes (rows = k, K = tokens), B = X^T (K = tokens, cols = features).
 // X is row-major in features, so a lane loads 8 features x 8 tokens as eight 16-byte rows and
 // transposes them in registers (byte permutes) into eight token-contiguous operands.
@@ -422,7 +425,9 @@ __device__ __forceinline__ void xtt_bf16_body(const bf16_t* __restrict__ X, int6
     extern __shared__ __align__(16) float sbuf[];   // [XTT_PANEL][RP]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lc = lane & 15, lg = lane >> 4;
-    const int64_t db = (int64_t)bx * XTT_PANEL;
+    constexpr bool ALONE = NB > 1;                 // a wave with a panel of its own
+    const int64_t db = ((int64_t)bx * (ALONE ? 4 : 1) + (ALONE ? wave : 0)) * XTT_PANEL;
+    if (ALONE && db >= K) return;
     const int split = (int)by;
     const int64_t ts = (int64_t)split * tok_per_split;
     const int64_t te = min(ts + tok_per_split, m_pad);
@@ -435,6 +440,7 @@ __device__ __forceinline__ void xtt_bf16_body(const bf16_t* __restrict__ X, int6
 
     const int64_t dcol = db + lc * 8;
     const bool din = dcol < K;
+    const int64_t dload = min(dcol, K - 8);        // (features past the end repeat the last, unstored)
     // one 32-token step: 8 KB of X and the T planes per wave.  The next step's loads are issued before this step's
     // matrix work (twice the bytes in flight: with one step in flight the sweep ran at memory latency); they are
     // unconditional, the step after the last one re-reads the last (clamped) and is dropped.
@@ -442,7 +448,7 @@ __device__ __forceinline__ void xtt_bf16_body(const bf16_t* __restrict__ X, int6
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int64_t t = min(tb + lg * 8 + i, M - 1);   // rows past M meet zero planes
-            v[i] = din ? *reinterpret_cast<const uint4*>(X + t * ldx + dcol) : make_uint4(0, 0, 0, 0);
+            v[i] = *reinterpret_cast<const uint4*>(X + t * ldx + dload);
         }
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
@@ -450,42 +456,51 @@ __device__ __forceinline__ void xtt_bf16_body(const bf16_t* __restrict__ X, int6
             for (int pl = 0; pl < 3; ++pl)
                 a[nb][pl].u = *reinterpret_cast<const uint4*>(TpackT + ((int64_t)(pl * RP + nb * 16 + lc)) * m_pad + tb + lg * 8);
     };
-    int64_t tb = ts + wave * XTT_STEP;
-    if (tb < te) {
-        uint4 v[8];
-        Frag a[NB][3];
-        load_step(tb, v, a);
-        for (; tb < te; tb += 4 * XTT_STEP) {
-            uint4 vn[8];
-            Frag an[NB][3];
-            load_step(min(tb + 4 * XTT_STEP, te - XTT_STEP), vn, an);
+    constexpr int STRIDE = (ALONE ? 1 : 4) * XTT_STEP;
+    int64_t tb = ts + (ALONE ? 0 : wave * XTT_STEP);
+    auto multiply = [&](const uint4 (&v)[8], const Frag (&a)[NB][3]) __attribute__((always_inline)) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                // word q of v[i] holds features 2q (low half) and 2q+1 (high half) of token i
-                const uint32_t sel = (j & 1) ? 0x07060302u : 0x05040100u;
-                const int q = j >> 1;
-                Frag b;
-                const uint32_t* w0 = reinterpret_cast<const uint32_t*>(&v[0]);
-                uint32_t o[4];
+        for (int j = 0; j < 8; ++j) {
+            // word q of v[i] holds features 2q (low half) and 2q+1 (high half) of token i
+            const uint32_t sel = (j & 1) ? 0x07060302u : 0x05040100u;
+            const int q = j >> 1;
+            Frag b;
+            const uint32_t* w0 = reinterpret_cast<const uint32_t*>(&v[0]);
+            uint32_t o[4];
 #pragma unroll
-                for (int pp = 0; pp < 4; ++pp)
-                    o[pp] = __builtin_amdgcn_perm(w0[(2 * pp + 1) * 4 + q], w0[(2 * pp) * 4 + q], sel);
-                b.u = make_uint4(o[0], o[1], o[2], o[3]);
+            for (int pp = 0; pp < 4; ++pp)
+                o[pp] = __builtin_amdgcn_perm(w0[(2 * pp + 1) * 4 + q], w0[(2 * pp) * 4 + q], sel);
+            b.u = make_uint4(o[0], o[1], o[2], o[3]);
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl)
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                    for (int pl = 0; pl < 3; ++pl)
-                        acc[nb][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[nb][pl].v, b.v, acc[nb][j], 0, 0, 0);
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = vn[i];
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                for (int pl = 0; pl < 3; ++pl) a[nb][pl] = an[nb][pl];
+                    acc[nb][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[nb][pl].v, b.v, acc[nb][j], 0, 0, 0);
+        }
+    };
+    if (tb < te) {
+        // two register sets in turn: moved from one to the other at the end of a step, the loads would be waited for there
+        uint4 v0[8], v1[8];
+        Frag a0[NB][3], a1[NB][3];
+        load_step(tb, v0, a0);
+        for (; tb < te; tb += 2 * STRIDE) {
+            load_step(min(tb + STRIDE, te - XTT_STEP), v1, a1);
+            multiply(v0, a0);
+            if (tb + STRIDE >= te) break;
+            load_step(min(tb + 2 * STRIDE, te - XTT_STEP), v0, a0);
+            multiply(v1, a1);
         }
     }
     // D layout: row (k within block) = 4*(lane/16) + e, col = lane%16 -> feature db + 8*lc + j
+    if constexpr (ALONE) {
+        if (!din) return;                          // (d_in is a multiple of 8: a lane's features are all in or all out)
+        float* dst = partial + ((int64_t)split * K + dcol) * RP + lg * 4;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) *reinterpret_cast<floatx4*>(dst + j * RP + nb * 16) = acc[nb][j];
+        return;
+    }
     for (int w = 0; w < 4; ++w) {
         if (wave == w) {
 #pragma unroll
@@ -525,7 +540,7 @@ static int64_t xtt_tokens_per_split(int64_t m_pad, int nsplit) {
 
 template <int CAP>
 static hipError_t launch_xtt_cap(const KBatch<XttDev, CAP>& tb, unsigned blocks, int rp, hipStream_t st) {
-    const size_t smem = (size_t)XTT_PANEL * rp * sizeof(float);
+    const size_t smem = rp == 16 ? (size_t)XTT_PANEL * rp * sizeof(float) : 0;
     const dim3 grid(blocks);
     switch (rp / 16) {
         case 1: hipLaunchKernelGGL((xtt_bf16_many_kernel<1, CAP>), grid, dim3(256), smem, st, tb); break;
@@ -550,7 +565,8 @@ hipError_t launch_xtt_bf16_many(const XttArgs* a, int n, hipStream_t st) {
         XttDev d;
         d.X = a[m].X; d.ldx = a[m].ldx; d.M = a[m].M; d.K = a[m].K; d.TpackT = a[m].TpackT; d.m_pad = a[m].m_pad;
         d.partial = a[m].partial; d.tok_per_split = xtt_tokens_per_split(a[m].m_pad, a[m].nsplit);
-        const uint32_t gx = (uint32_t)((a[m].K + XTT_PANEL - 1) / XTT_PANEL);
+        const int panel = (rp > 16 ? 4 : 1) * XTT_PANEL;
+        const uint32_t gx = (uint32_t)((a[m].K + panel - 1) / panel);
         tb.first[tb.n] = (uint32_t)blocks; tb.gx[tb.n] = gx; tb.a[tb.n++] = d;
         blocks += (uint64_t)gx * (uint32_t)a[m].nsplit;
     }
