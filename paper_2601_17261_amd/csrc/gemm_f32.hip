@@ -153,11 +153,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void f
                 const int c = (tid & 3) * 2 + i, k = k0 + 4 * c;
                 float4 pv = make_float4(0.f, 0.f, 0.f, 0.f), gv = pv;
                 if (k < a.r) {
-                    const float* p = a.P + min(m0 + row_t, a.M - 1) * a.r + k;
-                    pv.x = p[0];
-                    if (k + 1 < a.r) pv.y = p[1];
-                    if (k + 2 < a.r) pv.z = p[2];
-                    if (k + 3 < a.r) pv.w = p[3];
+                    const float* p = a.P + min(m0 + row_t, a.M - 1) * a.r;
+                    pv = make_float4(p[k], p[min(k + 1, a.r - 1)], p[min(k + 2, a.r - 1)], p[min(k + 3, a.r - 1)]);
+                    if (k + 1 >= a.r) pv.y = 0.f;
+                    if (k + 2 >= a.r) pv.z = 0.f;
+                    if (k + 3 >= a.r) pv.w = 0.f;
                     gv = philox_normal4(a.s_lo, a.s_hi, AGZO_TAG_G, (uint32_t)min(n0 + row_t, a.N - 1), (uint32_t)(k >> 2));
                     if (k + 1 >= a.r) gv.y = 0.f;
                     if (k + 2 >= a.r) gv.z = 0.f;
@@ -174,7 +174,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void f
     auto evaluate = [&](int phase) {
         double part = 0.0;
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < 2; ++i) {
+            // eight targets requested before the first is used; rows and columns past the end repeat the last (conditional on
+            // uniform values only: around a lane's condition the compiler waits for each load before the next)
+            float tv[2][4];
+            auto targets = [&](auto read) __attribute__((always_inline)) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        tv[j][e] = read(min(m0 + wt * 32 + i * 16 + 4 * e + lg, a.M - 1) * a.ldt + min(n0 + wo * 32 + j * 16 + lc, a.N - 1));
+            };
+            if (a.target != nullptr) {
+                if (a.target_dtype == AGZO_BF16) targets([&](int64_t at) { return bf16_to_f32(reinterpret_cast<const bf16_t*>(a.target)[at]); });
+                else targets([&](int64_t at) { return reinterpret_cast<const float*>(a.target)[at]; });
+            }
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const int64_t col = n0 + wo * 32 + j * 16 + lc;
@@ -185,13 +199,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void f
                     const double y = acc[i][j][e];
                     if (a.Y != nullptr) a.Y[row * a.ldy + col] = (float)y;
                     if (a.target != nullptr) {
-                        const float t = (a.target_dtype == AGZO_BF16) ? bf16_to_f32(reinterpret_cast<const bf16_t*>(a.target)[row * a.ldt + col])
-                                                                      : reinterpret_cast<const float*>(a.target)[row * a.ldt + col];
-                        const double r = y - (double)t;
+                        const double r = y - (double)tv[j][e];
                         part = fma(r, r, part);
                     }
                 }
             }
+        }
         if (a.target == nullptr) return;
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
@@ -299,7 +312,7 @@ hipError_t launch_rank_term_f32(float* Y, int64_t ldy, int64_t M, int64_t N, con
 // result rows and split the contraction between them, so that the whole chip has loads in flight after one launch and no
 // second one is needed to add partial sums (they meet in LDS, in wave order).  The result has up to four blocks of 16 columns.
 // (The generic 64 x 64 tile kernel that these replace walked the contraction alone, with r of its 64 columns in use: 50 us at
-// 512 x 256 and r = 4, now 5 (xq) and 8 (xtt); the seven layers of 1000 x 1024 .. 3072 in one launch take 34 and 29 us.)
+// 512 x 256 and r = 4, now 5 (xq) and 5.5 (xtt); the seven layers of 1000 x 1024 .. 3072 in one launch take 34 and 17 us.)
 // ---------------------------------------------------------------------------
 constexpr int SK_WAVES = 16;
 
@@ -396,10 +409,19 @@ __global__ __launch_bounds__(64 * SK_WAVES) void xtt_f32_kernel(const KBatch<F32
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t t = 4 * (int64_t)(g0 + u * SK_WAVES) + lg;
-            const bool in = t < a.M;
-            x[u] = in ? xc[t * a.ldx] : 0.f;
+            // (conditional on uniform values only: around a lane's condition the compiler waits for each load before the next)
+            if (g0 + u * SK_WAVES >= ngroup) break;
+            const int64_t tc = min(t, a.M - 1);
+            x[u] = xc[tc * a.ldx];
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) v[u][nb] = (in && nb * 16 + lc < a.r) ? a.V[t * a.r + nb * 16 + lc] : 0.f;
+            for (int nb = 0; nb < NB; ++nb) v[u][nb] = a.V[tc * a.r + min(nb * 16 + lc, a.r - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool in = 4 * (int64_t)(g0 + u * SK_WAVES) + lg < a.M;
+            x[u] = in ? x[u] : 0.f;
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) v[u][nb] = in && nb * 16 + lc < a.r ? v[u][nb] : 0.f;
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {

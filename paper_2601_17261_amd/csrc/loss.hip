@@ -97,9 +97,12 @@ __global__ __launch_bounds__(256) void ce_combine_kernel(const float2* __restric
             float2 v[CE_FLIGHT];
 #pragma unroll
             for (int u = 0; u < CE_FLIGHT; ++u) {
-                const int c = c0 + u * CE_LANES;
-                v[u] = c < nchunk ? m[(int64_t)c * M] : make_float2(-INFINITY, 0.f);
+                // (never conditional: around a condition the compiler waits for each load before the next)
+                v[u] = m[(int64_t)min(c0 + u * CE_LANES, nchunk - 1) * M];
             }
+#pragma unroll
+            for (int u = 1; u < CE_FLIGHT; ++u)
+                if (c0 + u * CE_LANES >= nchunk) v[u] = make_float2(-INFINITY, 0.f);
             float top = v[0].x;                                // (the first of the eight exists)
 #pragma unroll
             for (int u = 1; u < CE_FLIGHT; ++u) top = fmaxf(top, v[u].x);

@@ -19,7 +19,7 @@
 // in registers (its inverse along with it, no barrier), everything else - panels, trailing blocks, the inverse's other blocks,
 // Y R^-1 - is 16 x 16 products on the fp64 matrix cores.  A column-by-column factorisation by the whole workgroup (two
 // barriers a column) and a substitution with a thread per row took 159 us where this takes 42 (the single pass of seven 4B-sized
-// layers, r = 64) and 10.9 where it takes 8.3 (0.6B-sized, r = 8); launch 1 at r = 64 65 and 35 us.
+// layers, r = 64) and 10.9 where it takes 8.3 (0.6B-sized, r = 8); launch 1 at r = 64 65 and 22 us.
 #include <type_traits>
 
 #include "agzo_internal.h"
@@ -283,9 +283,14 @@ __device__ __forceinline__ void load_rows(const Tin* __restrict__ Y, int64_t i0,
 #pragma unroll
         for (int s = 0; s < RP / 4; ++s) {
             const int col = 4 * s + (lane >> 4);
-            y[b][s] = (row < rows && col < r) ? Y[(i0 + row) * r + col] : (Tin)0;
+            y[b][s] = Y[(i0 + min(row, rows - 1)) * r + min(col, r - 1)];
         }
     }
+#pragma unroll
+    for (int b = 0; b < Q::RB; ++b)
+#pragma unroll
+        for (int s = 0; s < RP / 4; ++s)
+            if ((wave * Q::RB + b) * 16 + (lane & 15) >= rows || 4 * s + (lane >> 4) >= r) y[b][s] = (Tin)0;
 }
 // column block q of a 16-row block of Y R^-1 (rows and columns as D lays them out)
 template <int RP, typename Tin>
@@ -347,25 +352,31 @@ __global__ __launch_bounds__(QrShape<RP>::THREADS) void qr_gram_kernel(const KBa
         constexpr int VPT = Q::NB == 1 ? 2 : 1;
         for (int v0 = tid; v0 < total_vec; v0 += VPT * Q::THREADS) {
             double acc[VPT][4] = {};
-            for (int sp0 = 0; sp0 < nsplit; sp0 += 16) {
-                float4 x[VPT][16];
+            // N splits' loads at once; those past the last repeat it and are left out (never conditional: around a condition the
+            // compiler waits for each load before the next, 14 us instead of 6 for seven 0.6B-sized layers)
+            auto add = [&](auto NS) __attribute__((always_inline)) {
+                constexpr int N = decltype(NS)::value;
+                for (int sp0 = 0; sp0 < nsplit; sp0 += N) {
+                    float4 x[VPT][N];
 #pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    const float4* src = reinterpret_cast<const float4*>(base + (int64_t)(sp0 + u) * d * RP);
+                    for (int u = 0; u < N; ++u) {
+                        const float4* src = reinterpret_cast<const float4*>(base + (int64_t)min(sp0 + u, nsplit - 1) * d * RP);
 #pragma unroll
-                    for (int k = 0; k < VPT; ++k) {
-                        const int v = v0 + k * Q::THREADS;
-                        x[k][u] = (v < nvec && sp0 + u < nsplit) ? src[v] : make_float4(0.f, 0.f, 0.f, 0.f);
+                        for (int k = 0; k < VPT; ++k) x[k][u] = src[min(v0 + k * Q::THREADS, nvec - 1)];
+                    }
+#pragma unroll
+                    for (int u = 0; u < N; ++u) {
+                        const bool in = sp0 + u < nsplit;
+#pragma unroll
+                        for (int k = 0; k < VPT; ++k) {
+                            acc[k][0] += in ? (double)x[k][u].x : 0.0; acc[k][1] += in ? (double)x[k][u].y : 0.0;
+                            acc[k][2] += in ? (double)x[k][u].z : 0.0; acc[k][3] += in ? (double)x[k][u].w : 0.0;
+                        }
                     }
                 }
-#pragma unroll
-                for (int u = 0; u < 16; ++u)
-#pragma unroll
-                    for (int k = 0; k < VPT; ++k) {
-                        acc[k][0] += (double)x[k][u].x; acc[k][1] += (double)x[k][u].y;
-                        acc[k][2] += (double)x[k][u].z; acc[k][3] += (double)x[k][u].w;
-                    }
-            }
+            };
+            if (nsplit <= 8) add(std::integral_constant<int, 8>{});
+            else add(std::integral_constant<int, 16>{});
 #pragma unroll
             for (int k = 0; k < VPT; ++k)
                 if (v0 + k * Q::THREADS < total_vec) finish(v0 + k * Q::THREADS, acc[k]);

@@ -278,9 +278,18 @@ __device__ __forceinline__ void xq_finish_body(const float* __restrict__ part, i
     if (idx >= rows * rp) return;
     const int64_t t = idx / rp;
     const int k = (int)(idx - t * rp);
+    // (eight splits' loads in flight; conditional on uniform values only - around a lane's condition the compiler waits for each
+    // load before the next - and what lies behind the last token or column is left out below)
     float v = 0.f;
-    if (t < M && k < r)
-        for (int s = 0; s < nsplit; ++s) v += part[((int64_t)s * m_pad + t) * rp + k];
+    const float* src = part + (t < m_pad ? t : m_pad - 1) * rp + k;
+    for (int s0 = 0; s0 < nsplit; s0 += 8) {
+        float x[8];
+#pragma unroll
+        for (int s = 0; s < 8; ++s) x[s] = s0 + s < nsplit ? src[(int64_t)(s0 + s) * m_pad * rp] : 0.f;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) v += x[s];
+    }
+    if (!(t < M && k < r)) v = 0.f;
     if (t < M && k < r && T != nullptr) T[t * r + k] = v;
     if (t < M && Xext != nullptr) store_ext(Xext, t, k, rp, v);
     if (TpackT != nullptr && t < m_pad) {

@@ -78,23 +78,35 @@ __global__ __launch_bounds__(256) void update_kernel(float* __restrict__ Wf, int
     }
 
     if (jc >= d_in) return;
-    const bool full = (jc + 8 <= d_in);
+    if (jc + 8 <= d_in && ldw % 4 == 0 && (reinterpret_cast<uintptr_t>(Wf + jc) & 15) == 0) {
+        // every row's values requested before the first is used; rows past the end repeat the last, unstored
+        float4 lo[UP_TR], hi[UP_TR];
+#pragma unroll
+        for (int s = 0; s < UP_TR; ++s) {
+            const float* w = Wf + min(i0 + ty + 8 * s, d_out - 1) * ldw + jc;
+            lo[s] = *reinterpret_cast<const float4*>(w);
+            hi[s] = *reinterpret_cast<const float4*>(w + 4);
+        }
+#pragma unroll
+        for (int s = 0; s < UP_TR; ++s) {
+            lo[s].x = fmaf(coef, acc[s][0], lo[s].x); lo[s].y = fmaf(coef, acc[s][1], lo[s].y);
+            lo[s].z = fmaf(coef, acc[s][2], lo[s].z); lo[s].w = fmaf(coef, acc[s][3], lo[s].w);
+            hi[s].x = fmaf(coef, acc[s][4], hi[s].x); hi[s].y = fmaf(coef, acc[s][5], hi[s].y);
+            hi[s].z = fmaf(coef, acc[s][6], hi[s].z); hi[s].w = fmaf(coef, acc[s][7], hi[s].w);
+            const int64_t i = i0 + ty + 8 * s;
+            if (i >= d_out) continue;
+            float* w = Wf + i * ldw + jc;
+            *reinterpret_cast<float4*>(w) = lo[s];
+            *reinterpret_cast<float4*>(w + 4) = hi[s];
+        }
+        return;
+    }
 #pragma unroll
     for (int s = 0; s < UP_TR; ++s) {
         const int64_t i = i0 + ty + 8 * s;
         if (i >= d_out) continue;
         float* w = Wf + i * ldw + jc;
-        if (full && ((reinterpret_cast<uintptr_t>(w) & 15) == 0)) {
-            float4 a = *reinterpret_cast<const float4*>(w), c4 = *reinterpret_cast<const float4*>(w + 4);
-            a.x = fmaf(coef, acc[s][0], a.x); a.y = fmaf(coef, acc[s][1], a.y);
-            a.z = fmaf(coef, acc[s][2], a.z); a.w = fmaf(coef, acc[s][3], a.w);
-            c4.x = fmaf(coef, acc[s][4], c4.x); c4.y = fmaf(coef, acc[s][5], c4.y);
-            c4.z = fmaf(coef, acc[s][6], c4.z); c4.w = fmaf(coef, acc[s][7], c4.w);
-            *reinterpret_cast<float4*>(w) = a;
-            *reinterpret_cast<float4*>(w + 4) = c4;
-        } else {
-            for (int c = 0; c < 8 && jc + c < d_in; ++c) w[c] = fmaf(coef, acc[s][c], w[c]);
-        }
+        for (int c = 0; c < 8 && jc + c < d_in; ++c) w[c] = fmaf(coef, acc[s][c], w[c]);
     }
 }
 
