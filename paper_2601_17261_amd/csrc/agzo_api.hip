@@ -173,12 +173,18 @@ int reserve(agzo_ctx* ctx, size_t bytes) {
     if (bytes <= ctx->ws_bytes) return 0;
     HIPCHK(hipStreamSynchronize(ctx->stream));
     // a context that needs more once will need more again (the layers of a model, one after the other): half as much again
+    const size_t need = bytes;
     if (ctx->ws) bytes = std::max(bytes, ctx->ws_bytes + ctx->ws_bytes / 2);
     if (ctx->ws) HIPCHK(hipFree(ctx->ws));
     ctx->ws = nullptr;
     ctx->ws_bytes = 0;
     void* p = nullptr;
     hipError_t e = hipMalloc(&p, bytes);
+    if (e != hipSuccess && bytes > need) {      // not that much left: what the call needs
+        (void)hipGetLastError();
+        bytes = need;
+        e = hipMalloc(&p, bytes);
+    }
     if (e != hipSuccess) return fail(ctx, AGZO_ENOMEM, "workspace of %zu bytes: %s", bytes, hipGetErrorString(e));
     ctx->ws = static_cast<char*>(p);
     ctx->ws_bytes = bytes;
