@@ -13,7 +13,7 @@
 // counted, stored outputs are stored twice with the same bits.  A last slice that d_in does not fill gets a descriptor with a
 // range, and the lanes past d_in an offset beyond it: they load zeros.  gemm_bf16.hip, which bounded every access and drained
 // its loads at every slice, ran 3001 x 2560 -> 9728 (both signs and none, with the smaller projections beside it) at 820
-// TFLOP/s and the cross-entropy head 3001 x 2048 -> 32000 at 937; this kernel at 1240 and 1290.
+// TFLOP/s and the cross-entropy head 3001 x 2048 -> 32000 at 937; this kernel at 1130 and 1105.
 //
 // Matrix instruction.
 // v_mfma_f32_16x16x32_bf16, 8 x 8 blocks per wave, two k steps of 32 per slice, where gemm_bf16.hip has 4 x 4 blocks of

@@ -39,8 +39,7 @@ def bf(a):
 
 @pytest.mark.parametrize("n_seq,T,H,Hkv", [(2, 13, 2, 1), (3, 100, 4, 2), (1, 200, 8, 8), (2, 64, 2, 2), (1, 1, 2, 1),
                                            (2, 512, 16, 8),      # the decoder workload's sequence length and heads
-                                           (1, 129, 4, 1),       # one query past a workgroup's 128, four query heads per kv head
-                                           (2, 63, 1, 1), (1, 65, 6, 3), (1, 321, 5, 1)])      # around a tile of 64 keys, head counts that four does not divide
+                                           (1, 129, 4, 1)])      # one query past a workgroup's 128, four query heads per kv head
 def test_attention_core_matches_oracle(ctx, n_seq, T, H, Hkv):
     rng = np.random.default_rng(100 * T + H)
     N = n_seq * T
