@@ -343,23 +343,41 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
             }
         }
     };
-    // a slice whose operands are complete in buffer `buf`, unpipelined
-    auto multiply_slice = [&](int buf, bool) __attribute__((always_inline)) {
+    // The matrix instructions are written out, so the compiler does not know of them and keeps no distance between them and what
+    // touches their results (8 wait states).  Behind a tile's slices: these 24, and then from_acc(), for such statements stay in
+    // order where an ordinary read could come in front.  In the shared-forward schedule, which multiplies on between evaluations
+    // and would copy what it read by hand, the wait is part of what multiplies: the last statement of a slice, below and in the
+    // loop over the slices
+    auto settle = [&]() __attribute__((always_inline)) { asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7"); };
+    // a slice whose operands are complete in buffer `buf`, unpipelined; each k step is one statement, from the wait between a
+    // value's last write and the first instruction to the one behind the last
+#define MM(I, J) "v_mfma_f32_16x16x32_bf16 %[c" #I #J "], %[w" #I "], %[x" #J "], %[c" #I #J "]\n\t"
+#define MM_TOKENS(A, B, C, D, J) MM(A, J) MM(B, J) MM(C, J) MM(D, J)
+#define MM_SET(A, B, C, D)                                                                                                       \
+    MM_TOKENS(A, B, C, D, 0) MM_TOKENS(A, B, C, D, 1) MM_TOKENS(A, B, C, D, 2) MM_TOKENS(A, B, C, D, 3)                          \
+    MM_TOKENS(A, B, C, D, 4) MM_TOKENS(A, B, C, D, 5) MM_TOKENS(A, B, C, D, 6) MM_TOKENS(A, B, C, D, 7)
+#define ACC(I, J) [c##I##J] "+a"(acc[I][J])
+#define ACC_ROW(I) ACC(I, 0), ACC(I, 1), ACC(I, 2), ACC(I, 3), ACC(I, 4), ACC(I, 5), ACC(I, 6), ACC(I, 7)
+    auto multiply_slice = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
 #pragma unroll
             for (int J = 0; J < 8; ++J) read_x(buf, ks, J);
 #pragma unroll
-            for (int set = 0; set < 2; ++set) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) read_w(buf, ks, set, i);
-#pragma unroll
-                for (int J = 0; J < 8; ++J)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) mfma1(set, i, J);
-            }
+            for (int I = 0; I < 8; ++I) read_w(buf, ks, I >> 2, I & 3);
+            asm volatile("s_nop 1\n\t" MM_SET(0, 1, 2, 3) MM_SET(4, 5, 6, 7) "s_nop 7"
+                         : ACC_ROW(0), ACC_ROW(1), ACC_ROW(2), ACC_ROW(3), ACC_ROW(4), ACC_ROW(5), ACC_ROW(6), ACC_ROW(7)
+                         : [w0] "v"(aw[0][0]), [w1] "v"(aw[0][1]), [w2] "v"(aw[0][2]), [w3] "v"(aw[0][3]),
+                           [w4] "v"(aw[1][0]), [w5] "v"(aw[1][1]), [w6] "v"(aw[1][2]), [w7] "v"(aw[1][3]),
+                           [x0] "v"(bx[0]), [x1] "v"(bx[1]), [x2] "v"(bx[2]), [x3] "v"(bx[3]),
+                           [x4] "v"(bx[4]), [x5] "v"(bx[5]), [x6] "v"(bx[6]), [x7] "v"(bx[7]));
         }
     };
+#undef MM
+#undef MM_TOKENS
+#undef MM_SET
+#undef ACC
+#undef ACC_ROW
 
     // ---- sum of squares of the accumulators: fp32 squares four at a time, summed in fp64; lanes, then waves, in a
     // fixed order ----
@@ -369,9 +387,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
     // last 256 rows or columns instead of hanging over the edge)
     auto eval_sum = [&](int rs, int cs) __attribute__((always_inline)) {
         double part = 0.0;
-        // 24 wait states between the last matrix instruction and the first read of a result: the matrix instructions are
-        // written out, so the compiler does not know of them and keeps no distance itself
-        asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7");
+        if constexpr (PHASES == 1) settle();
         auto sum = [&](auto MASK) __attribute__((always_inline)) {
             constexpr bool mask = decltype(MASK)::value != 0;
 #pragma clang loop unroll(full)
@@ -483,6 +499,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
             __builtin_amdgcn_sched_barrier(0);
             // every wave has read this slice's X: X of slice g + 2 goes into its stage, three blocks ahead
             block(IC<1>{}, IC<0>{}, IC<1>{}, cur ^ 1, wst1, IC<2>{}, cur);
+            // (half of the time that the last matrix instruction takes anyway)
+            if constexpr (PHASES != 1) asm volatile("s_nop 7");
             wst = wst1;
         }
         // the tile's last matrix instruction has issued; the stages of slice g hold the next tile's first slice, fragment
@@ -494,7 +512,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
             // quarter of the W stage that is idle between two tiles: written as held (16-byte chunk c of row t at
             // c ^ (t mod 16): the lanes of one write spread over all banks), read back 16 lanes to a 256-byte row, and
             // stored four whole rows to an instruction.
-            asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7");     // (the matrix instructions are written out: their results' wait states too)
+            settle();
             char* stg = smem + W_BASE + ((wst == 0) ? 2 : wst - 1) * TILE_BYTES + wave * 8192;
 #pragma clang loop unroll(full)
             for (int r2 = 0; r2 < 4; ++r2) {
@@ -507,8 +525,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
 #pragma clang loop unroll(full)
                         for (int t = 0; t < 4; ++t) {
                             const floatx4 v = acc[i4 * 4 + t][J];
-                            w[2 * t] = pack_bf16x2(v[0], v[1]);
-                            w[2 * t + 1] = pack_bf16x2(v[2], v[3]);
+                            w[2 * t] = pack_bf16x2(from_acc(v[0]), from_acc(v[1]));
+                            w[2 * t + 1] = pack_bf16x2(from_acc(v[2]), from_acc(v[3]));
                         }
                         const int c0 = i4 * 8 + lg * 2;
                         *reinterpret_cast<uint4*>(stg + trow * 256 + ((c0 ^ (trow & 15)) << 4)) = make_uint4(w[0], w[1], w[2], w[3]);
@@ -530,7 +548,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
         } else if constexpr (OUT == 2) {
             // a lane holds 32 of the 128 logits of the wave's columns for each of eight tokens; the lanes lane ^ 16, ^ 32, ^ 48
             // hold the others.  Online softmax over the wave's 128 columns, per token
-            asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7");
+            settle();
             // columns that the tile before this one has counted stay out (rows that it has counted get the same values again);
             // cskip: how many of the lane's 16 columns per group those are
             const int cs = RAGGED ? (int)(tn * BT - n0) : 0;
@@ -548,7 +566,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
                     for (int t = 0; t < 4; ++t)
 #pragma clang loop unroll(full)
                         for (int e = 0; e < 4; ++e) {
-                            const float y = acc[i4 * 4 + t][J][e];
+                            const float y = from_acc(acc[i4 * 4 + t][J][e]);
                             if (!RAGGED || 4 * t + e >= cskip[i4]) mx = fmaxf(mx, y);
                             if (4 * t + e == trel) { tl = y; has_tl = true; }
                         }
@@ -562,7 +580,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
                 for (int I = 0; I < 8; ++I)
 #pragma clang loop unroll(full)
                     for (int e = 0; e < 4; ++e) {
-                        const float ex = __builtin_amdgcn_exp2f((acc[I][J][e] - mx) * 1.44269504088896341f);
+                        const float ex = __builtin_amdgcn_exp2f((from_acc(acc[I][J][e]) - mx) * 1.44269504088896341f);
                         sm += (!RAGGED || (I & 3) * 4 + e >= cskip[I >> 2]) ? ex : 0.f;
                     }
                 sm += __shfl_xor(sm, 16);
@@ -616,7 +634,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
             if (next > 0) ext_dma(rw2, 0, 0);
             double* red = reinterpret_cast<double*>(smem + W_BASE + 2 * TILE_BYTES);
             if constexpr (LATE_T) {                          // from here on the accumulators hold residuals
-                asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7");
                 request_target();
 #pragma clang loop unroll(full)
                 for (int J = 0; J < 8; ++J) {
@@ -632,26 +649,26 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
                 ext_dma(rw3, 0, 1);
                 __builtin_amdgcn_s_waitcnt(0x0F70 | 16);     // the +eps slice has landed (the -2 eps one may be in flight)
                 __syncthreads();
-                multiply_slice(0, true);
+                multiply_slice(0);
                 for (int e = 1; e < next; ++e) {
                     __syncthreads();
                     ext_dma(rw2, e, 0);
                     __builtin_amdgcn_s_waitcnt(0x0F70);
                     __syncthreads();
-                    multiply_slice(0, true);
+                    multiply_slice(0);
                 }
             }
             evaluate(1, tm, tn, red);
             if (next > 0) {
                 __builtin_amdgcn_s_waitcnt(0x0F70);
                 __syncthreads();
-                multiply_slice(1, true);
+                multiply_slice(1);
                 for (int e = 1; e < next; ++e) {
                     __syncthreads();
                     ext_dma(rw3, e, 1);
                     __builtin_amdgcn_s_waitcnt(0x0F70);
                     __syncthreads();
-                    multiply_slice(1, true);
+                    multiply_slice(1);
                 }
             }
             evaluate(2, tm, tn, red);

@@ -143,13 +143,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         if (f < p.K) *reinterpret_cast<float4*>(p.sk_partial + ((int64_t)tm * p.K + f) * MSK_RP + 4 * g) = make_float4(s[0], s[1], s[2], s[3]);
     };
 
+    // The matrix instructions below are written out and the compiler keeps no distance between them and what reads or writes
+    // their accumulators: 24 wait states, which name the accumulators so that nothing that touches one comes on the wrong side
+    auto settle = [&]() __attribute__((always_inline)) {
+        asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7"
+                     : "+v"(acc[0][0]), "+v"(acc[0][1]), "+v"(acc[0][2]), "+v"(acc[0][3]), "+v"(acc[1][0]), "+v"(acc[1][1]), "+v"(acc[1][2]), "+v"(acc[1][3]),
+                       "+v"(acc[2][0]), "+v"(acc[2][1]), "+v"(acc[2][2]), "+v"(acc[2][3]), "+v"(acc[3][0]), "+v"(acc[3][1]), "+v"(acc[3][2]), "+v"(acc[3][3]));
+    };
     // a stored output has the bits of one whose shares of d_in are added by gemm_bf16_mid_finish_kernel: the sums of a share are
     // moved to `tot` behind its last slice
     constexpr bool FOLD = SK && OUT == 1;
     floatx4 tot[FOLD ? 4 : 1][4];
     int fold_share = 0;
     auto fold = [&]() __attribute__((always_inline)) {
-        asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7");
+        settle();
 #pragma unroll
         for (int I = 0; I < 4; ++I)
 #pragma unroll
@@ -157,9 +164,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 tot[FOLD ? I : 0][J] = fold_share == 0 ? acc[I][J] : tot[FOLD ? I : 0][J] + acc[I][J];
                 acc[I][J] = floatx4{0.f, 0.f, 0.f, 0.f};
             }
-        // (named, so that the zeros are written in front of it: the next matrix instructions read them)
-        asm volatile("s_nop 7" : "+v"(acc[0][0]), "+v"(acc[0][1]), "+v"(acc[0][2]), "+v"(acc[0][3]), "+v"(acc[1][0]), "+v"(acc[1][1]), "+v"(acc[1][2]), "+v"(acc[1][3]),
-                                 "+v"(acc[2][0]), "+v"(acc[2][1]), "+v"(acc[2][2]), "+v"(acc[2][3]), "+v"(acc[3][0]), "+v"(acc[3][1]), "+v"(acc[3][2]), "+v"(acc[3][3]));
+        settle();
         ++fold_share;
     };
 
@@ -248,8 +253,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    // (the instructions that start from the accumulators' first values read registers that vector instructions have just written)
-    asm volatile("s_nop 7");
+    settle();
     // slice 0 has landed
     constexpr int W0 = 8 * (AHEAD - 1), W1 = 8 * (AHEAD - 2) + 4;
     __builtin_amdgcn_s_waitcnt(0x0F70 | (W0 & 15) | ((W0 >> 4) << 14));
@@ -279,8 +283,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         if constexpr (FOLD)
             if (fold_share + 1 < p.splits && kt + 1 == nd * (fold_share + 1) / p.splits) fold();
     }
-    // 24 wait states before the first read of a result: the compiler does not know of the instructions above
-    asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7");
+    settle();
     __builtin_amdgcn_s_waitcnt(0x0F70);                      // the slices fetched past the end
     if constexpr (FOLD) {
         if (fold_share > 0) {

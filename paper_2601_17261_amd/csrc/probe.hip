@@ -51,6 +51,8 @@ __global__ __launch_bounds__(256) void probe_mfma_kernel(const uint4* __restrict
                     // builtin these accumulators land in the ordinary registers, where the instruction issues at 0.81 of
                     // its rate)
                     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c[i]) : "v"(a2[((i >> 3) + g) & 7]), "v"(b2[((i & 7) + g) & 7]));
+            // (the distance to the first read of a result, which the compiler does not keep for these; the last instruction takes longer)
+            asm volatile("s_nop 7");
         }
 #pragma unroll
         for (int i = 0; i < 64; ++i) acc[i & 15][i >> 4] += c[i][0] + c[i][1] + c[i][2] + c[i][3];

@@ -74,3 +74,26 @@ def test_stored_outputs_and_cross_entropy(n, d_out, d_in, r, pad):
     y, keep = torch.from_numpy(Yo), (ids >= 0).cpu()
     want = (torch.logsumexp(y, 1)[keep] - y[keep, ids.cpu()[keep].long()]).mean().item()
     assert abs(out.item() - want) < 1e-5 * max(1.0, abs(want)), (out.item(), want)
+
+
+@pytest.mark.parametrize("target", ["bf16", "f32"])
+@pytest.mark.parametrize("r", [16, 64])
+def test_shared_schedule_sums_every_term_of_the_perturbation(r, target):
+    """L+ and L- of the shared schedule against those of three forwards, with an eps that makes the rank-r term most of the
+    output: both add the same fp32 terms, in another order and with the target subtracted at another point.  Rounding: 2^-24 of an
+    output for each of some twenty additions, independent over 131072 outputs, so some 1e-9 of a loss.  One lo term (2^-9 of the
+    perturbation) left out in one of a wave's 64 blocks: 1e-6."""
+    n, d_out, d_in = 512, 257, 136
+    _, X, T = synth.single_layer_problem(n + r, n, d_in, d_out, kind="rmsnorm", storage="bf16", target_storage=target)
+    W, _, _ = synth.single_layer_problem(r, n, d_in, d_out, kind="rmsnorm", storage="bf16")
+    Xd, Td = _dev(X, torch.bfloat16, 0), _dev(T, torch.bfloat16 if target == "bf16" else torch.float32, 0)
+    ctx = binding.Context()
+    got = []
+    for flags in (0, binding.SHARED_FORWARD):
+        Wd = _dev(W, torch.bfloat16, 0)
+        out = torch.zeros(4, dtype=torch.float64, device="cuda")
+        ctx.step(_large(binding.make_layer(Wd, Xd, r)), Wd, Xd, binding.make_loss(Td), 1, 1.0, 0.0, 31, flags, out)
+        ctx.check()
+        got.append(out.cpu().numpy())
+    for i in range(3):
+        assert abs(got[1][i] - got[0][i]) < 1e-7 * got[0][i], (i, got)
