@@ -254,9 +254,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         }
     };
     settle();
-    // slice 0 has landed
+    // slice 0 has landed (SK: and this wave's part of the Omega^T planes is written, which a bare barrier does not wait for)
     constexpr int W0 = 8 * (AHEAD - 1), W1 = 8 * (AHEAD - 2) + 4;
-    __builtin_amdgcn_s_waitcnt(0x0F70 | (W0 & 15) | ((W0 >> 4) << 14));
+    __builtin_amdgcn_s_waitcnt((SK ? 0x0070 : 0x0F70) | (W0 & 15) | ((W0 >> 4) << 14));
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll

@@ -1,8 +1,9 @@
 """Orderings that the compiler does not keep by itself, checked in the assembly of the kernels that rely on them.
 
 Matrix instructions written as inline assembly are opaque to the compiler's hazard bookkeeping: the code keeps the distance to
-the instructions that touch their accumulators, and the compiler may move those unless something ties them down.  That does not
-show in a result reliably, so the instruction streams are walked instead (every path, a few wait states deep).
+the instructions that touch their accumulators, and the compiler may move those unless something ties them down.  A bare
+s_barrier does not wait for LDS writes: the code puts the wait in front of it.  Neither shows in a result reliably, so the
+instruction streams are walked instead (every path, a few wait states deep).
 """
 import concurrent.futures
 import os
@@ -13,7 +14,7 @@ import pytest
 
 from paper_2601_17261_amd import build as B
 
-SOURCES = ["gemm_bf16_aligned.hip", "gemm_bf16_mid.hip", "probe.hip"]
+SOURCES = ["gemm_bf16_aligned.hip", "gemm_bf16_mid.hip", "skinny.hip", "glue.hip", "probe.hip"]
 # wait states this compiler keeps on gfx950 around v_mfma_f32_16x16x32_bf16 when it knows the instruction (through the
 # builtin): 8 from the instruction to anything else that reads or writes its result, 2 from a vector instruction's result to it
 AFTER_MFMA, BEFORE_MFMA = 8, 2
@@ -99,6 +100,24 @@ def wait_state_faults(body, succ):
     return faults
 
 
+def barrier_faults(body, succ):
+    """LDS writes that may be under way at an s_barrier (no wait for them on some path between)"""
+    faults, seen = [], set()
+    todo = [(t, i) for i, ins in enumerate(body) if ins.op.startswith(("ds_write", "ds_add")) for t in succ[i]]
+    while todo:
+        i, src = todo.pop()
+        if i in seen:
+            continue
+        seen.add(i)
+        if body[i].op == "s_barrier":
+            faults.append("%s  -->  s_barrier (instruction %d)" % (body[src].text, i))
+            continue
+        if body[i].op == "s_waitcnt" and "lgkmcnt(0)" in body[i].text:
+            continue
+        todo += [(t, src) for t in succ[i]]
+    return faults
+
+
 @pytest.fixture(scope="module")
 def kernels(tmp_path_factory):
     d = tmp_path_factory.mktemp("asm")
@@ -115,21 +134,31 @@ def kernels(tmp_path_factory):
 @pytest.mark.parametrize("src", SOURCES)
 def test_results_of_written_out_matrix_instructions(kernels, src):
     found = {name: wait_state_faults(*f) for name, f in kernels[src].items()}
-    assert any(ins.mfma and ins.in_asm for body, _ in kernels[src].values() for ins in body)
+    written = any(ins.mfma and ins.in_asm for body, _ in kernels[src].values() for ins in body)
+    assert written == (src in ("gemm_bf16_aligned.hip", "gemm_bf16_mid.hip", "probe.hip"))
     assert not any(found.values()), "\n".join("%s: %d, e.g. %s" % (n, len(v), v[0]) for n, v in found.items() if v)
+
+
+@pytest.mark.parametrize("src", SOURCES)
+def test_lds_writes_are_complete_at_barriers(kernels, src):
+    found = {name: barrier_faults(*f) for name, f in kernels[src].items()}
+    assert found
+    assert not any(found.values()), "\n".join("%s: %s" % (n, v[0]) for n, v in found.items() if v)
 
 
 def test_the_walk_finds_planted_faults():
     head, tail = "_Zk:\n", "\ts_endpgm\n.Lfunc_end0:\n"
     mfma = "\t;;#ASMSTART\n\tv_mfma_f32_16x16x32_bf16 a[0:3], v[4:7], v[8:11], a[0:3]\n\t;;#ASMEND\n"
 
-    def walk(text):
+    def walk(text, check):
         (f,) = functions(head + text + tail).values()
-        return wait_state_faults(*f)
+        return check(*f)
     read = "\tv_accvgpr_read_b32 v20, a2\n"
-    assert len(walk(mfma + read)) == 1
-    assert len(walk(mfma + "\ts_nop 6\n" + read)) == 1
-    assert not walk(mfma + "\ts_nop 7\n" + read)
-    assert len(walk(mfma + "\ts_cbranch_scc1 .LBB0_2\n\ts_nop 7\n.LBB0_2:\n" + read)) == 1      # by the branch
-    assert not walk(mfma + "\tv_accvgpr_read_b32 v20, a4\n")
-    assert len(walk("\tv_accvgpr_write_b32 a1, v3\n" + mfma)) == 1
+    assert len(walk(mfma + read, wait_state_faults)) == 1
+    assert len(walk(mfma + "\ts_nop 6\n" + read, wait_state_faults)) == 1
+    assert not walk(mfma + "\ts_nop 7\n" + read, wait_state_faults)
+    assert len(walk(mfma + "\ts_cbranch_scc1 .LBB0_2\n\ts_nop 7\n.LBB0_2:\n" + read, wait_state_faults)) == 1      # by the branch
+    assert not walk(mfma + "\tv_accvgpr_read_b32 v20, a4\n", wait_state_faults)
+    assert len(walk("\tv_accvgpr_write_b32 a1, v3\n" + mfma, wait_state_faults)) == 1
+    assert len(walk("\tds_write_b16 v1, v2\n\ts_waitcnt vmcnt(8)\n\ts_barrier\n", barrier_faults)) == 1
+    assert not walk("\tds_write_b16 v1, v2\n\ts_waitcnt vmcnt(8) lgkmcnt(0)\n\ts_barrier\n", barrier_faults)
