@@ -756,7 +756,7 @@ hipError_t choose(const GemmBf16Args& a, Choice& c) {
     GemmItem& g = c.g;
     g.X = p.X; g.W = p.W; g.ldx = p.ldx; g.ldw = p.ldw; g.M = p.M; g.N = p.N; g.K = p.K;
     g.Xext = p.Xext; g.Wext = p.Wext; g.ext_ld = p.ext_ld;
-    g.target = p.target; g.ldt = p.ldt; g.partials = p.partials; g.Y = p.Y; g.ldy = p.ldy; g.clk = p.clk;
+    g.target = p.target; g.ldt = p.ldt; g.partials = p.partials; g.wide = !p.vec_ok; g.Y = p.Y; g.ldy = p.ldy; g.clk = p.clk;
     g.splits = 1; g.part = nullptr;
     if (a.split_ws) {      // (with a fused sketch one workgroup adds up the same shares: the same bits)
         g.splits = gemm_bf16_mid_splits(p.M, p.N, p.K);

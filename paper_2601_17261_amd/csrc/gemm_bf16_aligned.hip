@@ -384,33 +384,46 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
     // The four waves' sums meet in LDS, in `red`: the head of a W stage that nothing reads or fills at that moment
     // (the operand stages take all of the LDS)
     // rs, cs: rows and columns of the tile that the tile before it has counted (the last tile of a direction starts at the
-    // last 256 rows or columns instead of hanging over the edge)
+    // last 256 rows or columns instead of hanging over the edge).  Such tiles, and all of a layer whose target rows do not start
+    // on 16 bytes, are squared in fp64 as well: what gemm_bf16.hip squares so keeps its precision here
     auto eval_sum = [&](int rs, int cs) __attribute__((always_inline)) {
         double part = 0.0;
         if constexpr (PHASES == 1) settle();
-        auto sum = [&](auto MASK) __attribute__((always_inline)) {
-            constexpr bool mask = decltype(MASK)::value != 0;
+        auto sum = [&](auto WIDE) __attribute__((always_inline)) {
+            constexpr bool wide = decltype(WIDE)::value != 0;
 #pragma clang loop unroll(full)
             for (int J = 0; J < 8; ++J) {
                 if (LATE_T && PHASES == 1 && T_F32 && J == 4) { tload(IC<4>{}); tload(IC<5>{}); tload(IC<6>{}); tload(IC<7>{}); }
+                // the first of the lane's 16 columns per group that counts
+                int from[2] = {0, 0};
+                if (wide) {
+                    const bool in = wb * 128 + J * 16 + lc >= rs;
+                    from[0] = in ? cs - (wa * 128 + lg * 16) : 16;
+                    from[1] = in ? cs - (wa * 128 + 64 + lg * 16) : 16;
+                    // (or the compiler works out all 256 conditions ahead and keeps them)
+                    asm volatile("" : "+v"(from[0]), "+v"(from[1]));
+                }
 #pragma clang loop unroll(full)
                 for (int I = 0; I < 8; ++I) {
                     const floatx4 v = acc[I][J];
                     float s4 = 0.f;
-                    const int left = mask ? ((wb * 128 + J * 16 + lc >= rs) ? cs - (wa * 128 + (I >> 2) * 64 + lg * 16 + (I & 3) * 4) : 4) : 0;
 #pragma clang loop unroll(full)
                     for (int u = 0; u < 4; ++u) {
                         // (the shared-forward schedule multiplies on after an evaluation and nothing else is live there)
                         float x = (PHASES == 1) ? from_acc(v[u]) : v[u];
                         if (LATE_T && PHASES == 1) x -= target_value(J, I, u);
-                        if (mask) x = u >= left ? x : 0.f;
-                        s4 = fmaf(x, x, s4);
+                        if (wide) {
+                            const double xd = (I & 3) * 4 + u >= from[I >> 2] ? (double)x : 0.0;
+                            part = fma(xd, xd, part);
+                        } else {
+                            s4 = fmaf(x, x, s4);
+                        }
                     }
-                    part += (double)s4;
+                    if (!wide) part += (double)s4;
                 }
             }
         };
-        if (RAGGED && __builtin_expect((rs | cs) != 0, 0)) sum(IC<1>{});
+        if (RAGGED && ((rs | cs) != 0 || !p.vec_ok)) sum(IC<1>{});
         else sum(IC<0>{});
         return part;
     };
@@ -644,34 +657,24 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
                         for (int u = 0; u < 4; ++u) acc[I][J][u] -= target_value(J, I, u);
                 }
             }
-            evaluate(0, tm, tn, red);
-            if (next > 0) {
-                ext_dma(rw3, 0, 1);
-                __builtin_amdgcn_s_waitcnt(0x0F70 | 16);     // the +eps slice has landed (the -2 eps one may be in flight)
-                __syncthreads();
-                multiply_slice(0);
-                for (int e = 1; e < next; ++e) {
-                    __syncthreads();
-                    ext_dma(rw2, e, 0);
+            // (rolled: the accumulators of three evaluations in a row end up in scratch memory)
+#pragma clang loop unroll(disable)
+            for (int ph = 0;; ++ph) {
+                evaluate(ph, tm, tn, red);
+                if (ph == 2) break;
+                const __amdgpu_buffer_rsrc_t rwp = rsrc(ph == 0 ? wb2 : wb3);
+                if (ph == 0) ext_dma(rw3, 0, 1);
+#pragma clang loop unroll(disable)
+                for (int e = 0; e < next; ++e) {
+                    if (e > 0) {
+                        __syncthreads();
+                        ext_dma(rwp, e, ph);
+                    }
                     __builtin_amdgcn_s_waitcnt(0x0F70);
                     __syncthreads();
-                    multiply_slice(0);
+                    multiply_slice(ph);
                 }
             }
-            evaluate(1, tm, tn, red);
-            if (next > 0) {
-                __builtin_amdgcn_s_waitcnt(0x0F70);
-                __syncthreads();
-                multiply_slice(1);
-                for (int e = 1; e < next; ++e) {
-                    __syncthreads();
-                    ext_dma(rw3, e, 1);
-                    __builtin_amdgcn_s_waitcnt(0x0F70);
-                    __syncthreads();
-                    multiply_slice(1);
-                }
-            }
-            evaluate(2, tm, tn, red);
             break;
         }
         // ---- hand the accumulators to the next tile ----

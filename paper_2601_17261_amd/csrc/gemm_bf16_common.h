@@ -74,6 +74,7 @@ struct GemmItem {
     int64_t ldx, ldw, M, N, K;
     const bf16_t* Xext; const bf16_t* Wext; int ext_ld;   // prepared rank-r extension operands (NULL: none)
     const void* target; int64_t ldt; double* partials;    // squared error: [ceil(M / 128) * ceil(N / 128)] partial sums
+    int wide;                                              // (squares in fp64 everywhere)
     void* Y; int64_t ldy;                                  // stored bf16 output
     int tiles_m, tiles_n;                                  // (set by the launch)
     // fused range sketch (a launch of one problem; NULL: none): as in GemmParams

@@ -315,7 +315,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             store16_any(dst + 8, make_uint4(w[4], w[5], w[6], w[7]));
         }
     } else {
-        // squares in fp32 four at a time, summed in fp64; lanes, then waves, in a fixed order
+        // squares in fp32 four at a time, summed in fp64; lanes, then waves, in a fixed order.  Tiles that overlap the one before
+        // them, and all of a layer whose target rows do not start on 16 bytes, are squared in fp64 as well: what
+        // gemm_bf16_small.hip squares so keeps its precision here
         double part = 0.0;
         // value of element e of block (I, J) among the raw vectors
         auto target_value = [&](int J, int I, int e) __attribute__((always_inline)) {
@@ -329,20 +331,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             return __uint_as_float((e & 1) ? w & 0xFFFF0000u : w << 16);
         };
         const int skip = (int)(col_new - (n0 + wa * 64 + lg * 16));      // so many of the lane's 16 columns are counted already
+        auto sum = [&](auto WIDE) __attribute__((always_inline)) {
+            constexpr bool wide = decltype(WIDE)::value != 0;
 #pragma unroll
-        for (int J = 0; J < 4; ++J) {
-            const int from = m0 + wb * 64 + J * 16 + lc >= row_new ? skip : 16;
+            for (int J = 0; J < 4; ++J) {
+                const int from = m0 + wb * 64 + J * 16 + lc >= row_new ? skip : 16;
 #pragma unroll
-            for (int I = 0; I < 4; ++I) {
-                float s4 = 0.f;
+                for (int I = 0; I < 4; ++I) {
+                    float s4 = 0.f;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float x = 4 * I + e >= from ? acc[I][J][e] - target_value(J, I, e) : 0.f;
-                    s4 = fmaf(x, x, s4);
+                    for (int e = 0; e < 4; ++e) {
+                        const float x = acc[I][J][e] - target_value(J, I, e);
+                        if (wide) {
+                            const double xd = 4 * I + e >= from ? (double)x : 0.0;
+                            part = fma(xd, xd, part);
+                        } else {
+                            s4 = fmaf(x, x, s4);
+                        }
+                    }
+                    if (!wide) part += (double)s4;
                 }
-                part += (double)s4;
             }
-        }
+        };
+        if (p.wide || m0 != row_new || n0 != col_new) sum(IC<1>{});
+        else sum(IC<0>{});
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
         double* red = reinterpret_cast<double*>(smem);
