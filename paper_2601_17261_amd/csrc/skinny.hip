@@ -399,10 +399,10 @@ hipError_t launch_xq_bf16(const bf16_t* X, int64_t ldx, int64_t M, int64_t K, co
 }
 
 // ---------------------------------------------------------------------------
-// xtt: r <= 16: workgroup = (panel of 128 features) x (token range); waves interleave 32-token steps and add their sums in LDS.
-// r > 16: a wave has a panel and a token range of its own.  Its steps carry 48 to 96 matrix instructions, so a range of a few
-// steps is work enough, while adding four waves' sums (one after the other, 128 rows of up to 64 columns) took longer than the
-// three steps each of them had: r = 64, 4096 tokens of seven 4B-sized layers 161 us, now 109.
+// xtt: workgroup = (panel of 128 features) x (token range); its four waves take 32-token steps in turn and add their sums in LDS.
+// ALONE (r > 16 only): a wave has a panel of its own and takes the four waves' steps one wave after the other: the same sums in the
+// same order, a quarter of the workgroups, and no adding of 128 rows of up to 64 columns in LDS, which takes longer than the few
+// steps it follows.
 // MFMA roles: A = T^T planes (rows = k, K = tokens), B = X^T (K = tokens, cols = features).
 // X is row-major in features, so a lane loads 8 features x 8 tokens as eight 16-byte rows and
 // transposes them in registers (byte permutes) into eight token-contiguous operands.
@@ -426,7 +426,7 @@ int xtt_num_splits(int64_t M, int64_t K) {
 }
 
 // bx: panel of features, by: token range
-template <int NB>
+template <int NB, bool ALONE>
 __device__ __forceinline__ void xtt_bf16_body(const bf16_t* __restrict__ X, int64_t ldx, int64_t M, int64_t K,
                                               const bf16_t* __restrict__ TpackT, int64_t m_pad,
                                               float* __restrict__ partial, int64_t tok_per_split, uint32_t bx, uint32_t by) {
@@ -434,7 +434,6 @@ __device__ __forceinline__ void xtt_bf16_body(const bf16_t* __restrict__ X, int6
     extern __shared__ __align__(16) float sbuf[];   // [XTT_PANEL][RP]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lc = lane & 15, lg = lane >> 4;
-    constexpr bool ALONE = NB > 1;                 // a wave with a panel of its own
     const int64_t db = ((int64_t)bx * (ALONE ? 4 : 1) + (ALONE ? wave : 0)) * XTT_PANEL;
     if (ALONE && db >= K) return;
     const int split = (int)by;
@@ -465,8 +464,7 @@ __device__ __forceinline__ void xtt_bf16_body(const bf16_t* __restrict__ X, int6
             for (int pl = 0; pl < 3; ++pl)
                 a[nb][pl].u = *reinterpret_cast<const uint4*>(TpackT + ((int64_t)(pl * RP + nb * 16 + lc)) * m_pad + tb + lg * 8);
     };
-    constexpr int STRIDE = (ALONE ? 1 : 4) * XTT_STEP;
-    int64_t tb = ts + (ALONE ? 0 : wave * XTT_STEP);
+    constexpr int STRIDE = 4 * XTT_STEP;
     auto multiply = [&](const uint4 (&v)[8], const Frag (&a)[NB][3]) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -487,18 +485,45 @@ __device__ __forceinline__ void xtt_bf16_body(const bf16_t* __restrict__ X, int6
                     acc[nb][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[nb][pl].v, b.v, acc[nb][j], 0, 0, 0);
         }
     };
+    // A wave's steps: every fourth of the range, from its own number on; ALONE: the four waves' steps one wave after the other, and
+    // their sums added in that order (tot).  Either way the same bits
+    floatx4 tot[ALONE ? NB : 1][8] = {};
+    int w = ALONE ? 0 : wave;
+    int64_t tb = ts + w * XTT_STEP;
     if (tb < te) {
+        bool first = true;
+        // the step behind the one at tb, which may belong to the next wave's share; `more`: there is one
+        int wn;
+        int64_t tn;
+        auto find = [&]() __attribute__((always_inline)) -> bool {
+            wn = w;
+            tn = tb + STRIDE;
+            if (ALONE && tn >= te) tn = (++wn < 4) ? ts + wn * XTT_STEP : te;
+            return tn < te;
+        };
+        auto step = [&](uint4 (&v)[8], Frag (&a)[NB][3], uint4 (&v2)[8], Frag (&a2)[NB][3]) __attribute__((always_inline)) -> bool {
+            const bool more = find();
+            load_step(more ? tn : tb, v2, a2);
+            multiply(v, a);
+            if (ALONE && (wn != w || !more)) {
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        tot[ALONE ? nb : 0][j] = first ? acc[nb][j] : tot[ALONE ? nb : 0][j] + acc[nb][j];
+                        acc[nb][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+                    }
+                first = false;
+            }
+            tb = tn;
+            w = wn;
+            return more;
+        };
         // two register sets in turn: moved from one to the other at the end of a step, the loads would be waited for there
         uint4 v0[8], v1[8];
         Frag a0[NB][3], a1[NB][3];
         load_step(tb, v0, a0);
-        for (; tb < te; tb += 2 * STRIDE) {
-            load_step(min(tb + STRIDE, te - XTT_STEP), v1, a1);
-            multiply(v0, a0);
-            if (tb + STRIDE >= te) break;
-            load_step(min(tb + 2 * STRIDE, te - XTT_STEP), v0, a0);
-            multiply(v1, a1);
-        }
+        while (step(v0, a0, v1, a1) && step(v1, a1, v0, a0)) {}
     }
     // D layout: row (k within block) = 4*(lane/16) + e, col = lane%16 -> feature db + 8*lc + j
     if constexpr (ALONE) {
@@ -507,7 +532,7 @@ __device__ __forceinline__ void xtt_bf16_body(const bf16_t* __restrict__ X, int6
 #pragma unroll
         for (int j = 0; j < 8; ++j)
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) *reinterpret_cast<floatx4*>(dst + j * RP + nb * 16) = acc[nb][j];
+            for (int nb = 0; nb < NB; ++nb) *reinterpret_cast<floatx4*>(dst + j * RP + nb * 16) = tot[nb][j];
         return;
     }
     for (int w = 0; w < 4; ++w) {
@@ -535,11 +560,11 @@ struct XttDev {
     const bf16_t* TpackT; int64_t m_pad;
     float* partial; int64_t tok_per_split;
 };
-template <int NB, int CAP>
-__global__ __launch_bounds__(256) void xtt_bf16_many_kernel(const KBatch<XttDev, CAP> tb) {
+template <int NB, bool ALONE, int CAP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NB <= 2 ? 2 : 1))) void xtt_bf16_many_kernel(const KBatch<XttDev, CAP> tb) {
     uint32_t bx, by;
     const XttDev& a = tb.a[kbatch_find(tb, bx, by)];
-    xtt_bf16_body<NB>(a.X, a.ldx, a.M, a.K, a.TpackT, a.m_pad, a.partial, a.tok_per_split, bx, by);
+    xtt_bf16_body<NB, ALONE>(a.X, a.ldx, a.M, a.K, a.TpackT, a.m_pad, a.partial, a.tok_per_split, bx, by);
 }
 
 static int64_t xtt_tokens_per_split(int64_t m_pad, int nsplit) {
@@ -547,41 +572,62 @@ static int64_t xtt_tokens_per_split(int64_t m_pad, int nsplit) {
     return (t + 4 * XTT_STEP - 1) / (4 * XTT_STEP) * (4 * XTT_STEP);
 }
 
+// ALONE or not, from the workgroups that the other form would have work for and their steps: where they fill the chip less than
+// once, a quarter of them leaves it idle (r = 32, 16384 tokens of a 4096-wide layer, 256 workgroups of 64 steps: 65 us against 33), and
+// beyond that the adding is worth avoiding for short ranges (seven 4B-sized layers, 512 tokens, 832 of 4 steps: 15 us against 25 at
+// r = 32, 28 against 55 at r = 64) and, where it allows one workgroup per compute unit (r > 32), for long ones too once
+// there are many (4096 tokens, 1860 of some 16 steps: 139 us against 163 at r = 64, 103 against 130 at r = 48, but 78
+// against 70 at r = 32; one 9728-wide layer, 304 of 32 steps: 67 against 52 at r = 64)
+static bool xtt_alone(int rp, int64_t workgroups, int64_t steps) {
+    return workgroups > 256 && (steps <= 8 * workgroups || (rp > 32 && workgroups >= 1024));
+}
+template <int NB, bool ALONE, int CAP>
+static hipError_t launch_xtt_nb(const KBatch<XttDev, CAP>& tb, unsigned blocks, hipStream_t st) {
+    const size_t smem = ALONE ? 0 : (size_t)XTT_PANEL * NB * 16 * sizeof(float);
+    hipLaunchKernelGGL((xtt_bf16_many_kernel<NB, ALONE, CAP>), dim3(blocks), dim3(256), smem, st, tb);
+    return hipGetLastError();
+}
 template <int CAP>
-static hipError_t launch_xtt_cap(const KBatch<XttDev, CAP>& tb, unsigned blocks, int rp, hipStream_t st) {
-    const size_t smem = rp == 16 ? (size_t)XTT_PANEL * rp * sizeof(float) : 0;
-    const dim3 grid(blocks);
+static hipError_t launch_xtt_cap(const KBatch<XttDev, CAP>& tb, unsigned blocks, int rp, bool alone, hipStream_t st) {
     switch (rp / 16) {
-        case 1: hipLaunchKernelGGL((xtt_bf16_many_kernel<1, CAP>), grid, dim3(256), smem, st, tb); break;
-        case 2: hipLaunchKernelGGL((xtt_bf16_many_kernel<2, CAP>), grid, dim3(256), smem, st, tb); break;
-        case 3: hipLaunchKernelGGL((xtt_bf16_many_kernel<3, CAP>), grid, dim3(256), smem, st, tb); break;
-        case 4: hipLaunchKernelGGL((xtt_bf16_many_kernel<4, CAP>), grid, dim3(256), smem, st, tb); break;
+        case 1: return launch_xtt_nb<1, false>(tb, blocks, st);
+        case 2: return alone ? launch_xtt_nb<2, true>(tb, blocks, st) : launch_xtt_nb<2, false>(tb, blocks, st);
+        case 3: return alone ? launch_xtt_nb<3, true>(tb, blocks, st) : launch_xtt_nb<3, false>(tb, blocks, st);
+        case 4: return alone ? launch_xtt_nb<4, true>(tb, blocks, st) : launch_xtt_nb<4, false>(tb, blocks, st);
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 hipError_t launch_xtt_bf16_many(const XttArgs* a, int n, hipStream_t st) {
     if (n < 0 || n > kBatchMax) return hipErrorInvalidValue;
     KBatch<XttDev> tb;
     tb.n = 0;
-    uint64_t blocks = 0;
+    int64_t busy = 0, steps = 0;
     int rp = 0;
     for (int m = 0; m < n; ++m) {
         if (a[m].M == 0 || a[m].K == 0) continue;
         if (rp == 0) rp = a[m].rp;
         if (a[m].rp != rp || a[m].nsplit < 1) return hipErrorInvalidValue;
+        // (ranges that hold tokens, and their steps)
+        const int64_t panels = (a[m].K + XTT_PANEL - 1) / XTT_PANEL, tok = xtt_tokens_per_split(a[m].m_pad, a[m].nsplit);
+        busy += panels * ((a[m].m_pad + tok - 1) / tok);
+        steps += panels * (a[m].m_pad / XTT_STEP);
+    }
+    const bool alone = rp > 16 && xtt_alone(rp, busy, steps);
+    const int panel = (alone ? 4 : 1) * XTT_PANEL;
+    uint64_t blocks = 0;
+    for (int m = 0; m < n; ++m) {
+        if (a[m].M == 0 || a[m].K == 0) continue;
         XttDev d;
         d.X = a[m].X; d.ldx = a[m].ldx; d.M = a[m].M; d.K = a[m].K; d.TpackT = a[m].TpackT; d.m_pad = a[m].m_pad;
         d.partial = a[m].partial; d.tok_per_split = xtt_tokens_per_split(a[m].m_pad, a[m].nsplit);
-        const int panel = (rp > 16 ? 4 : 1) * XTT_PANEL;
         const uint32_t gx = (uint32_t)((a[m].K + panel - 1) / panel);
         tb.first[tb.n] = (uint32_t)blocks; tb.gx[tb.n] = gx; tb.a[tb.n++] = d;
         blocks += (uint64_t)gx * (uint32_t)a[m].nsplit;
     }
     if (tb.n == 0) return hipSuccess;
     if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    return tb.n == 1 ? launch_xtt_cap(kbatch_one(tb), (unsigned)blocks, rp, st) : launch_xtt_cap(tb, (unsigned)blocks, rp, st);
+    return tb.n == 1 ? launch_xtt_cap(kbatch_one(tb), (unsigned)blocks, rp, alone, st) : launch_xtt_cap(tb, (unsigned)blocks, rp, alone, st);
 }
 
 hipError_t launch_xtt_bf16(const bf16_t* X, int64_t ldx, int64_t M, int64_t K, const bf16_t* TpackT, int64_t m_pad,
