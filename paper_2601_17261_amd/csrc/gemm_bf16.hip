@@ -758,9 +758,9 @@ hipError_t choose(const GemmBf16Args& a, Choice& c) {
     g.Xext = p.Xext; g.Wext = p.Wext; g.ext_ld = p.ext_ld;
     g.target = p.target; g.ldt = p.ldt; g.partials = p.partials; g.wide = !p.vec_ok; g.Y = p.Y; g.ldy = p.ldy; g.clk = p.clk;
     g.splits = 1; g.part = nullptr;
-    if (a.split_ws) {      // (with a fused sketch one workgroup adds up the same shares: the same bits)
+    if (a.split_ws) {
         g.splits = gemm_bf16_mid_splits(p.M, p.N, p.K);
-        if (!p.sk_T) g.part = static_cast<float*>(a.split_ws);
+        g.part = static_cast<float*>(a.split_ws);
     }
     g.sk_T = p.sk_T; g.sk_mpad = p.sk_mpad; g.sk_partial = p.sk_partial;
     c.out = (p.Y && p.loss_kind == AGZO_LOSS_NONE && p.y_dtype == AGZO_BF16) ? 1 : (!p.Y && p.loss_kind == AGZO_LOSS_MSE) ? 0 : -1;

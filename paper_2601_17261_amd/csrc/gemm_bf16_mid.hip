@@ -45,16 +45,21 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t mid_rsrc(const bf16_t* base, u
 }
 
 // SK: also emits the range sketch of Alg. 1 from the X slices in LDS, as gemm_bf16_small.hip describes; the planes of Omega^T
-// take another 12.75 KiB of LDS, which leaves one workgroup per compute unit
+// take another 12.75 KiB of LDS, so that the rings are shorter: two stages of both operands where two workgroups share a compute
+// unit (the W of a slice is then requested with its X), four with DEEP.  A stored output in shares: each sketches its own slices.
+// 3001 x 2048 -> 2048 stored and sketched 52 us in gemm_bf16_small.hip, 72 with the longer ring, one workgroup per compute unit and
+// a full wait at every slice, 40 so; 130 x 9728 -> 2560 104, 122 and 29
 // DEEP: five stages of both operands and one workgroup per compute unit, for launches that give a compute unit no second
 // workgroup anyway: 16 us a launch against 17.1 on the 0.6B-sized layers, 35.8 against 39.3 at 512 tokens on the 4B-sized ones
 // (with two workgroups for every compute unit it is the slower one, 42.6 against 34.7 us at 8192 x 2048 -> 1024).  Same bits
+constexpr int mid_w_stages(bool sk, bool deep) { return deep ? (sk ? 4 : 5) : (sk ? 2 : 3); }
+constexpr int mid_x_stages(bool sk, bool deep) { return deep ? (sk ? 4 : 5) : 2; }
 template <int OUT, bool T_F32, bool SK, bool DEEP, int CAP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_bf16_mid_kernel(const KBatch<GemmItem, CAP> tb) {
-    constexpr int WS = DEEP ? 5 : 3, XS = DEEP ? 5 : 2;      // stages
-    constexpr int AHEAD = DEEP ? 4 : 2;                       // slices between a request and its use
+    constexpr int WS = mid_w_stages(SK, DEEP), XS = mid_x_stages(SK, DEEP);
+    constexpr int AHEAD = DEEP ? XS - 1 : 2;                  // slices between a request and its use
+    constexpr bool LATE_W = WS == AHEAD;                      // no stage is free for the W of a slice before the barrier
     constexpr int X_BASE = WS * MTILE_BYTES;
-    static_assert(!(SK && DEEP), "the sketch planes share the LDS of the shallow ring");
     extern __shared__ __align__(16) char smem[];
     uint32_t bx_, by_;
     const GemmItem& p = tb.a[kbatch_find(tb, bx_, by_)];
@@ -112,12 +117,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
     // ---- fused range sketch: this tile contracts its tokens for the d_in slices tn, tn + tiles_n, ... ----
     char* const Ts = smem + (WS + XS) * MTILE_BYTES;              // Omega^T planes [3][16][128 tokens]
-    int sk_next = tn;
+    int sk_next = tn + max(0, kbeg - tn + p.tiles_n - 1) / p.tiles_n * p.tiles_n;      // (of this workgroup's slices)
     if constexpr (SK) {
-        for (int e = tid; e < 3 * MSK_RP * MT; e += 256) {
-            const int row = e / MT, t = e % MT;
-            // (tokens that the tile before this one has covered add nothing)
-            *reinterpret_cast<bf16_t*>(Ts + row * MSK_ROW + 2 * t) = (m0 + t >= (int64_t)tm * MT) ? p.sk_T[(int64_t)row * p.sk_mpad + m0 + t] : (bf16_t)0;
+        const int skip = (int)((int64_t)tm * MT - m0);            // tokens that the tile before this one has covered add nothing
+#pragma unroll
+        for (int i = 0; i < 3 * MSK_RP * (MT / 8) / 256; ++i) {
+            const int v = tid + 256 * i, row = v / (MT / 8), t = v % (MT / 8) * 8;
+            const uint4 raw = load16_any(p.sk_T + (int64_t)row * p.sk_mpad + m0 + t);
+            uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+#pragma unroll
+            for (int u = 0; u < 4; ++u) w[u] &= (t + 2 * u >= skip ? 0xFFFFu : 0u) | (t + 2 * u + 1 >= skip ? 0xFFFF0000u : 0u);
+            *reinterpret_cast<uint4*>(Ts + row * MSK_ROW + 2 * t) = make_uint4(w[0], w[1], w[2], w[3]);
         }
     }
     auto sketch = [&](int buf, int it) __attribute__((always_inline)) {
@@ -150,24 +160,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                      : "+v"(acc[0][0]), "+v"(acc[0][1]), "+v"(acc[0][2]), "+v"(acc[0][3]), "+v"(acc[1][0]), "+v"(acc[1][1]), "+v"(acc[1][2]), "+v"(acc[1][3]),
                        "+v"(acc[2][0]), "+v"(acc[2][1]), "+v"(acc[2][2]), "+v"(acc[2][3]), "+v"(acc[3][0]), "+v"(acc[3][1]), "+v"(acc[3][2]), "+v"(acc[3][3]));
     };
-    // a stored output has the bits of one whose shares of d_in are added by gemm_bf16_mid_finish_kernel: the sums of a share are
-    // moved to `tot` behind its last slice
-    constexpr bool FOLD = SK && OUT == 1;
-    floatx4 tot[FOLD ? 4 : 1][4];
-    int fold_share = 0;
-    auto fold = [&]() __attribute__((always_inline)) {
-        settle();
-#pragma unroll
-        for (int I = 0; I < 4; ++I)
-#pragma unroll
-            for (int J = 0; J < 4; ++J) {
-                tot[FOLD ? I : 0][J] = fold_share == 0 ? acc[I][J] : tot[FOLD ? I : 0][J] + acc[I][J];
-                acc[I][J] = floatx4{0.f, 0.f, 0.f, 0.f};
-            }
-        settle();
-        ++fold_share;
-    };
-
     // ---- source of a slice: d_in slices, then the extension operands ----
     __amdgpu_buffer_rsrc_t src_rsx = mid_rsrc(xb), src_rsw = mid_rsrc(wb_);
     int src_so = 0, src_vxt[4], src_vwt[4];
@@ -233,7 +225,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc[I][J]) : "v"(aw[ks][I]), "v"(bx[ks][J]));
     };
     // 16 instructions of k step KS; rides along: the eight fragments of k step 1 - KS (of W stage rw, X stage rx), one per other
-    // instruction, and four direct loads (LOADS 1: W, 2: X)
+    // instruction, and four direct loads (LOADS 1: W, 2: X) or eight (3: both)
     auto block = [&](auto KS, int rw, int rx, auto LOADS, int lbuf) __attribute__((always_inline)) {
         constexpr int ks = decltype(KS)::value, loads = decltype(LOADS)::value;
 #pragma unroll
@@ -247,15 +239,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 else read_x(rx, ks ^ 1, f - 4);
             }
             if ((q & 3) == 1) {
-                if (loads == 1) dma_w(lbuf, q >> 2);
+                if (loads == 1 || loads == 3) dma_w(lbuf, q >> 2);
                 if (loads == 2) dma_x(lbuf, q >> 2);
             }
+            if ((q & 3) == 3 && loads == 3) dma_x(lbuf, q >> 2);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
     settle();
     // slice 0 has landed (SK: and this wave's part of the Omega^T planes is written, which a bare barrier does not wait for)
-    constexpr int W0 = 8 * (AHEAD - 1), W1 = 8 * (AHEAD - 2) + 4;
+    constexpr int W0 = 8 * (AHEAD - 1), W1 = 8 * (AHEAD - 2) + (LATE_W ? 0 : 4);
     __builtin_amdgcn_s_waitcnt((SK ? 0x0070 : 0x0F70) | (W0 & 15) | ((W0 >> 4) << 14));
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
@@ -265,34 +258,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int kt = 0; kt < npipe; ++kt) {
         if (__builtin_expect(kt + AHEAD >= nfull, 0)) select_slice(kt + AHEAD);
         else src_so = (kt + AHEAD) * (BK * 2);
-        block(IC<0>{}, wcur, xcur, IC<1>{}, wput);
-        if constexpr (SK) {
-            if (kt == sk_next && kt < nd) { sketch(xcur, kt); sk_next += p.tiles_n; }
-            __builtin_amdgcn_s_waitcnt(0x0070);              // (its stores count as well)
-        }
-        // lgkmcnt(0) and all but the youngest loads: the whole next slice has landed (loads return in the order issued), this
-        // wave's reads of the current one are done
+        block(IC<0>{}, wcur, xcur, IC<LATE_W ? 0 : 1>{}, wput);
+        if constexpr (SK)
+            if (kbeg + kt == sk_next && kt < nd) { sketch(xcur, kbeg + kt); sk_next += p.tiles_n; }
+        // lgkmcnt(0) and all but the youngest loads: the whole next slice has landed (loads return in the order issued; a sketch's
+        // stores, which count too, can only make this wait longer), this wave's reads of the current one are done
         __builtin_amdgcn_s_waitcnt(0x0070 | (W1 & 15) | ((W1 >> 4) << 14));
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         wcur = (wcur == WS - 1) ? 0 : wcur + 1;
         xcur = (xcur == XS - 1) ? 0 : xcur + 1;
-        block(IC<1>{}, wcur, xcur, IC<2>{}, xput);
+        block(IC<1>{}, wcur, xcur, IC<LATE_W ? 3 : 2>{}, xput);      // (LATE_W: wput = xput)
         wput = (wput == WS - 1) ? 0 : wput + 1;
         xput = (xput == XS - 1) ? 0 : xput + 1;
-        if constexpr (FOLD)
-            if (fold_share + 1 < p.splits && kt + 1 == nd * (fold_share + 1) / p.splits) fold();
     }
     settle();
     __builtin_amdgcn_s_waitcnt(0x0F70);                      // the slices fetched past the end
-    if constexpr (FOLD) {
-        if (fold_share > 0) {
-#pragma unroll
-            for (int I = 0; I < 4; ++I)
-#pragma unroll
-                for (int J = 0; J < 4; ++J) acc[I][J] = tot[I][J] + acc[I][J];
-        }
-    }
     const int64_t row_new = (int64_t)tm * MT, col_new = (int64_t)tn * MT;
     if constexpr (OUT == 2) {
         floatx4* dst = reinterpret_cast<floatx4*>(p.part) + ((int64_t)(share * tiles + tm * p.tiles_n + tn) * 4 + wave) * 16 * 64 + lane;
@@ -413,7 +394,8 @@ size_t gemm_bf16_split_bytes(int64_t M, int64_t N, int64_t K) {
 
 template <int OUT, bool T_F32, bool SK, bool DEEP, int CAP>
 static hipError_t launch_mid_ring(const KBatch<GemmItem, CAP>& tb, unsigned blocks, hipStream_t st) {
-    const int smem = (DEEP ? 10 : 5) * MTILE_BYTES + (SK ? MSK_SMEM : 0);
+    constexpr int smem = (mid_w_stages(SK, DEEP) + mid_x_stages(SK, DEEP)) * MTILE_BYTES + (SK ? MSK_SMEM : 0);
+    static_assert(smem <= (DEEP ? 160 : 80) * 1024, "workgroups per compute unit");
     static bool attr_set = false;
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_bf16_mid_kernel<OUT, T_F32, SK, DEEP, CAP>),
@@ -427,7 +409,7 @@ static hipError_t launch_mid_ring(const KBatch<GemmItem, CAP>& tb, unsigned bloc
 template <int OUT, bool T_F32>
 static hipError_t launch_mid_variant(const KBatch<GemmItem>& tb, unsigned blocks, bool sk, hipStream_t st) {
     // (256: a workgroup per compute unit)
-    if (sk) return launch_mid_ring<OUT, T_F32, true, false>(kbatch_one(tb), blocks, st);
+    if (sk) return blocks <= 256 ? launch_mid_ring<OUT, T_F32, true, true>(kbatch_one(tb), blocks, st) : launch_mid_ring<OUT, T_F32, true, false>(kbatch_one(tb), blocks, st);
     if (tb.n == 1) return blocks <= 256 ? launch_mid_ring<OUT, T_F32, false, true>(kbatch_one(tb), blocks, st) : launch_mid_ring<OUT, T_F32, false, false>(kbatch_one(tb), blocks, st);
     return blocks <= 256 ? launch_mid_ring<OUT, T_F32, false, true>(tb, blocks, st) : launch_mid_ring<OUT, T_F32, false, false>(tb, blocks, st);
 }
@@ -448,15 +430,17 @@ hipError_t launch_gemm_bf16_mid(const GemmItem* a, int n, int out, bool target_f
         for (; at > 0 && a[order[at - 1]].K < a[i].K; --at) order[at] = order[at - 1];
         order[at] = i;
     }
+    const bool sk = n > 0 && a[0].sk_T != nullptr;
+    if (sk && (n != 1 || !a[0].sk_partial || a[0].sk_mpad < (a[0].M + MT - 1) / MT * MT)) return hipErrorInvalidValue;
     if (n == 1 && a[0].part && out == 1 && a[0].splits > 1) {
         KBatch<GemmItem, 1> one{1, {0}, {0}, {a[0]}};
         GemmItem& g = one.a[0];
         g.tiles_m = (int)((g.M + MT - 1) / MT);
         g.tiles_n = (int)((g.N + MT - 1) / MT);
-        if (g.sk_T || g.splits > g.K / BK) return hipErrorInvalidValue;
+        if (g.splits > g.K / BK) return hipErrorInvalidValue;
         const unsigned tiles = (unsigned)(g.tiles_m * g.tiles_n);
         one.gx[0] = tiles * (unsigned)g.splits;
-        hipError_t e = launch_mid_ring<2, false, false, true>(one, one.gx[0], st);
+        hipError_t e = sk ? launch_mid_ring<2, false, true, true>(one, one.gx[0], st) : launch_mid_ring<2, false, false, true>(one, one.gx[0], st);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(gemm_bf16_mid_finish_kernel, dim3(tiles, 4), dim3(256), 0, st, g);
         return hipGetLastError();
@@ -472,8 +456,6 @@ hipError_t launch_gemm_bf16_mid(const GemmItem* a, int n, int out, bool target_f
     }
     if (tb.n == 0) return hipSuccess;
     if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    const bool sk = a[0].sk_T != nullptr;
-    if (sk && (n != 1 || !a[0].sk_partial || a[0].sk_mpad < (int64_t)tb.a[0].tiles_m * MT)) return hipErrorInvalidValue;
     if (out == 1) return launch_mid_variant<1, false>(tb, (unsigned)blocks, sk, st);
     return target_f32 ? launch_mid_variant<0, true>(tb, (unsigned)blocks, sk, st) : launch_mid_variant<0, false>(tb, (unsigned)blocks, sk, st);
 }
