@@ -64,13 +64,15 @@ int fail(agzo_ctx* c, int code, const char* fmt, ...) {
         if (rc__ != 0) return rc__; \
     } while (0)
 
+inline bool timed(const agzo_ctx* c, int kind) { return ((c->prof >> kind) & 1u) != 0; }
+
 // Optional timing of one kernel class with HIP events recorded on the ctx stream around each launch.
 struct ProfScope {
     agzo_ctx* c;
     int kind;
     hipEvent_t stop = nullptr;
     ProfScope(agzo_ctx* ctx, int k) : c(ctx), kind(k) {
-        if (!((c->prof >> kind) & 1u)) return;
+        if (!timed(c, kind)) return;
         ProfClass& pc = c->pc[kind];
         if (pc.used == pc.start.size()) {
             hipEvent_t a, b;
@@ -327,7 +329,7 @@ GemmBf16Args forward_bf16_args(agzo_ctx* ctx, const agzo_layer& L, const Plan& p
     a.large_tiles = (L.tiling == AGZO_TILING_LARGE);
     a.ext_ws = P ? ctx->ws + p.off_ext : nullptr;
     a.split_ws = p.off_split ? ctx->ws + p.off_split : nullptr;
-    if (((ctx->prof >> AGZO_PROF_GEMM) & 1u) && ctx->clk_used < kClkSlots) a.clk = ctx->clk + 4 * ctx->clk_used++;
+    if (timed(ctx, AGZO_PROF_GEMM) && ctx->clk_used < kClkSlots) a.clk = ctx->clk + 4 * ctx->clk_used++;
     return a;
 }
 
@@ -893,6 +895,15 @@ int agzo_perturbed_forward(agzo_ctx* ctx, const agzo_layer* L, const void* W, co
         HIPCHK(launch_xq_f32_many(&a, 1, ctx->stream));
         return op_forward(ctx, *L, p, W, X, P, eps_signed, seed, Y, loss, loss_dev);
     }
+    if (timed(ctx, AGZO_PROF_GEMM)) {      // the operands are prepared inside the forward's time
+        HIPCHK(launch_pack_planes(B, L->d_in, L->r, p.rp, wsh(ctx, p.off_pack), ctx->stream));
+        {
+            ProfScope ps(ctx, AGZO_PROF_XQ);
+            HIPCHK(launch_xq_bf16(static_cast<const bf16_t*>(X), L->ldx, L->n_tokens, L->d_in, wsh(ctx, p.off_pack), L->r, p.rp, P, nullptr, p.m_pad,
+                                  wsf(ctx, p.off_xqpart), nullptr, ctx->stream));
+        }
+        return op_forward(ctx, *L, p, W, X, P, eps_signed, seed, Y, loss, loss_dev);
+    }
     // the W side of the extension operands and the planes of B in one launch, then the projection writes the X side: a model's
     // step makes this chain once per linear layer and sign
     const GemmExtArgs ext{ctx->ws + p.off_ext, L->n_tokens, L->d_out, nullptr, L->r, eps_signed, 0.f, false, seed, B, wsh(ctx, p.off_pack), L->d_in};
@@ -1033,7 +1044,8 @@ int step_many_impl(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
             GemmLossArgs la;
             la.kind = AGZO_LOSS_MSE; la.target_dtype = it.loss.target_dtype; la.target = it.loss.target; la.ldt = it.loss.ldt;
             const float* P = perturbed ? wsf(ctx, j.p.off_T) : nullptr;
-            const bool pair = perturbed && !shared && j.L.dtype == AGZO_BF16;      // both signs' operands in one preparation
+            // both signs' operands in one preparation (timed: each forward's own, inside its time)
+            const bool pair = perturbed && !shared && j.L.dtype == AGZO_BF16 && !timed(ctx, AGZO_PROF_GEMM);
             if (pair) ext.push_back(GemmExtArgs{ctx->ws + j.p.off_ext, j.L.n_tokens, j.L.d_out, P, j.L.r, eps, -eps, ph1 > 2, it.seed});
             for (int ph = ph0; ph < ph1; ++ph) {
                 la.partials = reinterpret_cast<double*>(ctx->ws + j.p.off_part) + (size_t)ph * j.p.n_part;
@@ -1052,7 +1064,7 @@ int step_many_impl(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
         if (bf.empty()) return 0;
         for (size_t b = 0; b < ext.size(); b += kBatchMax)
             HIPCHK(launch_gemm_ext_prep_many(ext.data() + b, (int)std::min(ext.size() - b, (size_t)kBatchMax), st));
-        if (!((ctx->prof >> AGZO_PROF_GEMM) & 1u)) {
+        if (!timed(ctx, AGZO_PROF_GEMM)) {
             HIPCHK(launch_gemm_bf16_many(bf.data(), (int)bf.size(), st));
             return 0;
         }
