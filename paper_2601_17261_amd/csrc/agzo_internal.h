@@ -180,8 +180,8 @@ bool gemm_bf16_fuses_sketch(int64_t M, int64_t N, int r, bool large_tiles);
 inline int64_t gemm_bf16_sketch_mpad(int64_t M) { return (M + 127) / 128 * 128; }
 inline int gemm_bf16_sketch_splits(int64_t M) { return (int)((M + 127) / 128); }
 hipError_t launch_gemm_bf16(const GemmBf16Args& a, hipStream_t st);
-// several independent forwards: those that the kernel of gemm_bf16_mid.hip takes share launches, the others run one by one.
-// Every result has the bits of a launch of its own.  Workspaces (ext_ws unless ext_ready, loss partials) must not overlap.
+// several independent forwards: the squared errors that the kernel of gemm_bf16_mid.hip takes share launches, the others run one by
+// one.  Every result has the bits of a launch of its own.  Workspaces (ext_ws unless ext_ready, loss partials) must not overlap.
 hipError_t launch_gemm_bf16_many(const GemmBf16Args* a, int n, hipStream_t st);
 // extension operands of several layers in one launch: the W side times coef and, with two = true, once more times coef2
 // P = NULL: without the X side (launch_xq_bf16 writes it).  planes != NULL: also the bf16 planes [3][rp][d] of B fp32 [d][r]

@@ -798,18 +798,20 @@ hipError_t launch_gemm_bf16_many(const GemmBf16Args* a, int n, hipStream_t st) {
         }
         hipError_t e = launch_gemm_ext_prep_many(ext, next, st);
         if (e != hipSuccess) return e;
-        // the mid kernel's forwards by what they produce: squared error of bf16 or fp32 targets, stored outputs
-        for (int kind = 0; kind < 3; ++kind) {
+        // squared errors of the mid kernel together, bf16 and fp32 targets apart.  (A stored output may take shares of d_in, which
+        // only a launch of its own does)
+        auto shared_launch = [&](int i) { return c[i].kernel == Kernel::mid && c[i].out == 0 && !c[i].g.sk_T; };
+        for (int f32 = 0; f32 < 2; ++f32) {
             GemmItem g[kBatchMax];
             int ng = 0;
             for (int i = 0; i < nb; ++i)
-                if (c[i].kernel == Kernel::mid && !c[i].g.sk_T && (c[i].out == 1 ? 2 : c[i].p.target_dtype != AGZO_BF16 ? 1 : 0) == kind) g[ng++] = c[i].g;
+                if (shared_launch(i) && (c[i].p.target_dtype != AGZO_BF16) == (f32 != 0)) g[ng++] = c[i].g;
             if (ng == 0) continue;
-            e = launch_gemm_bf16_mid(g, ng, kind == 2 ? 1 : 0, kind == 1, st);
+            e = launch_gemm_bf16_mid(g, ng, 0, f32 != 0, st);
             if (e != hipSuccess) return e;
         }
         for (int i = 0; i < nb; ++i) {
-            if (a[b + i].M == 0 || a[b + i].N == 0 || (c[i].kernel == Kernel::mid && !c[i].g.sk_T)) continue;
+            if (a[b + i].M == 0 || a[b + i].N == 0 || shared_launch(i)) continue;
             e = launch_one(c[i], st);
             if (e != hipSuccess) return e;
         }

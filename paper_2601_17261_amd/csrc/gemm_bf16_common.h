@@ -84,7 +84,7 @@ struct GemmItem {
     int splits; float* part;
 };
 int gemm_bf16_mid_splits(int64_t M, int64_t N, int64_t K);
-// out 0: squared error (target_f32: of fp32 targets), 1: stored bf16 output
+// out 0: squared error (target_f32: of fp32 targets), 1: stored bf16 output (one problem a launch)
 bool gemm_bf16_mid_ok(const GemmItem& g, int out);
 hipError_t launch_gemm_bf16_mid(const GemmItem* a, int n, int out, bool target_f32, hipStream_t st);
 

@@ -410,8 +410,9 @@ template <int OUT, bool T_F32>
 static hipError_t launch_mid_variant(const KBatch<GemmItem>& tb, unsigned blocks, bool sk, hipStream_t st) {
     // (256: a workgroup per compute unit)
     if (sk) return blocks <= 256 ? launch_mid_ring<OUT, T_F32, true, true>(kbatch_one(tb), blocks, st) : launch_mid_ring<OUT, T_F32, true, false>(kbatch_one(tb), blocks, st);
-    if (tb.n == 1) return blocks <= 256 ? launch_mid_ring<OUT, T_F32, false, true>(kbatch_one(tb), blocks, st) : launch_mid_ring<OUT, T_F32, false, false>(kbatch_one(tb), blocks, st);
-    return blocks <= 256 ? launch_mid_ring<OUT, T_F32, false, true>(tb, blocks, st) : launch_mid_ring<OUT, T_F32, false, false>(tb, blocks, st);
+    if constexpr (OUT == 0)
+        if (tb.n > 1) return blocks <= 256 ? launch_mid_ring<OUT, T_F32, false, true>(tb, blocks, st) : launch_mid_ring<OUT, T_F32, false, false>(tb, blocks, st);
+    return blocks <= 256 ? launch_mid_ring<OUT, T_F32, false, true>(kbatch_one(tb), blocks, st) : launch_mid_ring<OUT, T_F32, false, false>(kbatch_one(tb), blocks, st);
 }
 
 bool gemm_bf16_mid_ok(const GemmItem& g, int out) {
@@ -419,7 +420,7 @@ bool gemm_bf16_mid_ok(const GemmItem& g, int out) {
 }
 
 hipError_t launch_gemm_bf16_mid(const GemmItem* a, int n, int out, bool target_f32, hipStream_t st) {
-    if (n < 0 || n > kBatchMax) return hipErrorInvalidValue;
+    if (n < 0 || n > (out == 1 ? 1 : kBatchMax)) return hipErrorInvalidValue;
     KBatch<GemmItem> tb;
     tb.n = 0;
     uint64_t blocks = 0;
@@ -432,7 +433,7 @@ hipError_t launch_gemm_bf16_mid(const GemmItem* a, int n, int out, bool target_f
     }
     const bool sk = n > 0 && a[0].sk_T != nullptr;
     if (sk && (n != 1 || !a[0].sk_partial || a[0].sk_mpad < (a[0].M + MT - 1) / MT * MT)) return hipErrorInvalidValue;
-    if (n == 1 && a[0].part && out == 1 && a[0].splits > 1) {
+    if (out == 1 && n == 1 && a[0].part && a[0].splits > 1) {
         KBatch<GemmItem, 1> one{1, {0}, {0}, {a[0]}};
         GemmItem& g = one.a[0];
         g.tiles_m = (int)((g.M + MT - 1) / MT);
