@@ -295,7 +295,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                                          pack_bf16x2(p[8 * h + 4], p[8 * h + 5]), pack_bf16x2(p[8 * h + 6], p[8 * h + 7]));
         }
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < 2; ++h) {
+            // (the second 32 keys may lie behind every query of the wave (wave-uniform): their probabilities are 0, but a value
+            // there that is not finite would still make NaNs of sums that it is no part of)
+            if (kb + 32 * h > q0 + ATT_WAVE_Q - 1) break;
 #pragma unroll
             for (int db = 0; db < 8; ++db) {
                 Frag vf;                                               // dim 16 db + n, the keys in the order the probabilities are held
@@ -303,6 +306,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
                 for (int qg = 0; qg < ATT_QG; ++qg) acc[qg][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf.v, pf[qg][h].v, acc[qg][db], 0, 0, 0);
             }
+        }
     }
 #pragma unroll
     for (int qg = 0; qg < ATT_QG; ++qg) {
