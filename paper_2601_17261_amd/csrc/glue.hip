@@ -187,25 +187,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int wg_q0 = (int)(gridDim.x - 1 - blockIdx.x) * ATT_WG_Q, q0 = wg_q0 + wave * ATT_WAVE_Q;
     const bf16_t* Qh = Qr + ((int64_t)seq * n_heads + head) * seq_len * HEAD_DIM;
     auto rsrc = [](const bf16_t* base) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, (int)0xFFFFFFFFu, 0x00020000); };
-    const __amdgpu_buffer_rsrc_t rk = rsrc(Kr + ((int64_t)seq * n_kv + kvh) * seq_len * HEAD_DIM);
-    const __amdgpu_buffer_rsrc_t rv = rsrc(Vt + ((int64_t)seq * n_kv + kvh) * HEAD_DIM * t_pad);
+    const bf16_t* Kh = Kr + ((int64_t)seq * n_kv + kvh) * seq_len * HEAD_DIM;
+    const bf16_t* Vh = Vt + ((int64_t)seq * n_kv + kvh) * HEAD_DIM * t_pad;
     union Frag { uint4 u; bf16x8_t v; };
     const int tiles = (min(wg_q0 + ATT_WG_Q, seq_len) + ATT_KEYS - 1) / ATT_KEYS;      // that any query of this workgroup may see
     // direct loads of tile j into stage j & 1: K rows of 256 bytes (16-byte chunk c of row r at c ^ (r mod 16)), V^T rows of 128
-    // bytes (chunk c at c ^ (r / 2 mod 8)); four of each per wave.  Keys past the end repeat the last one, masked
+    // bytes (chunk c at c ^ (r / 2 mod 8)); four of each per wave.  Keys past the end repeat the last one, masked.  (Lanes' offsets
+    // have 32 bits: the tile and, in V^T, whose rows are as long as the sequence, the row group are part of the base)
     auto request = [&](int j) __attribute__((always_inline)) {
         char* stage = att_smem + (j & 1) * (2 * ATT_TILE) + wave * 4096;
+        const __amdgpu_buffer_rsrc_t rk = rsrc(Kh + (int64_t)j * (ATT_KEYS * HEAD_DIM));
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             const int row = 16 * wave + 4 * t + (lane >> 4);
-            const int off = min(j * ATT_KEYS + row, seq_len - 1) * (HEAD_DIM * 2) + (((lane & 15) ^ (row & 15)) << 4);
+            const int off = min(row, seq_len - 1 - j * ATT_KEYS) * (HEAD_DIM * 2) + (((lane & 15) ^ (row & 15)) << 4);
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (lptr_t)(stage + t * 1024), 16, off, 0, 0, 0);
         }
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             const int row = 32 * wave + 8 * t + (lane >> 3);
-            const int off = row * (t_pad * 2) + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lptr_t)(stage + ATT_TILE + t * 1024), 16, off, j * (ATT_KEYS * 2), 0, 0);
+            const __amdgpu_buffer_rsrc_t rv = rsrc(Vh + (int64_t)(32 * wave + 8 * t) * t_pad + (int64_t)j * ATT_KEYS);
+            const uint32_t off = (uint32_t)(lane >> 3) * (2u * (uint32_t)t_pad) + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lptr_t)(stage + ATT_TILE + t * 1024), 16, (int)off, 0, 0, 0);
         }
     };
     request(0);
