@@ -1005,7 +1005,7 @@ namespace {
 // bit).  Squared-error layers run every stage together: the evaluations of part 1 (f0, or all three in the shared schedule) and
 // of part 2 (f+ and f-) go to the launch functions as one list, and one launch finishes every loss and scalar.  Cross-entropy
 // layers evaluate one by one (every evaluation is finished by launches of its own).
-int step_many_impl(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, float eps, float lr, int flags) {
+int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, float eps, float lr, int flags) {
     const bool shared = (flags & AGZO_SHARED_FORWARD) != 0, one_sided = (flags & AGZO_ONE_SIDED) != 0;
     std::vector<LayerJob> jobs((size_t)n);
     size_t total = 0;
@@ -1124,6 +1124,13 @@ int step_many_impl(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
     if (upd.empty()) return AGZO_OK;
     // the update's factor fragments go behind the layers' carve-outs, which still hold the bases
     return update_many_at(ctx, upd.data(), (int)upd.size(), total);
+}
+int step_many_impl(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, float eps, float lr, int flags) {
+    try {
+        return step_many_body(ctx, items, n, K, eps, lr, flags);
+    } catch (const std::bad_alloc&) {      // (a C entry)
+        return fail(ctx, AGZO_ENOMEM, "no host memory for the lists of %d layers", n);
+    }
 }
 }  // namespace
 
