@@ -225,9 +225,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int qg = 0; qg < ATT_QG; ++qg)
 #pragma unroll
         for (int db = 0; db < 8; ++db) acc[qg][db] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-    float m_run[ATT_QG], l_run[ATT_QG];                                // maximum of the raw scores
+    float m_run[ATT_QG], t_run[ATT_QG], l_run[ATT_QG];                 // maximum of the raw scores, the same scaled and rounded
 #pragma unroll
-    for (int qg = 0; qg < ATT_QG; ++qg) { m_run[qg] = -INFINITY; l_run[qg] = 0.f; }
+    for (int qg = 0; qg < ATT_QG; ++qg) { m_run[qg] = t_run[qg] = -INFINITY; l_run[qg] = 0.f; }
     const float sc = 1.44269504088896341f * 0.08838834764831845f;      // log2(e) / sqrt(128)
     for (int j = 0; j < tiles; ++j) {
         // this wave's loads of tile j have landed, then everybody's; everybody is done with the other stage
@@ -254,7 +254,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                     s[qg][blk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks].v, qf[qg][ks].v, s[qg][blk], 0, 0, 0);
             }
         }
+        // The probabilities are rounded to bf16 around the maximum so far, the tile's two groups of 32 keys one after the other: the
+        // largest of a group is then exact more often than around one maximum of 64 (0.5 % of the outputs' error, and no less than
+        // with steps of 32 keys)
         Frag pf[ATT_QG][2];
+        float back[ATT_QG];                                            // what the second group's maximum scales the first by
+        bool moved[ATT_QG];
         const bool mask = kb + ATT_KEYS - 1 > q0;                      // wave-uniform: some query ends inside the tile
 #pragma unroll
         for (int qg = 0; qg < ATT_QG; ++qg) {
@@ -266,32 +271,42 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
                     for (int e = 0; e < 4; ++e) s[qg][blk][e] = 16 * blk + e <= last ? s[qg][blk][e] : -INFINITY;
             }
-            float mx = m_run[qg];
+            float mx[2] = {m_run[qg], -INFINITY};
 #pragma unroll
             for (int blk = 0; blk < 4; ++blk)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) mx = fmaxf(mx, s[qg][blk][e]);
-            mx = fmaxf(mx, __shfl_xor(mx, 16));
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
-            // a group of queries that sees none of this tile's keys (its rows all lie before kb) keeps its state:
-            // mx = m_run, alpha = 1, every p = 0.  On a group's first tile m_run = -inf and mx is finite (key 0 is visible).
-            if (__any(mx != m_run[qg])) {
-                const float alpha = __builtin_amdgcn_exp2f((m_run[qg] - mx) * sc);
+                for (int e = 0; e < 4; ++e) mx[blk >> 1] = fmaxf(mx[blk >> 1], s[qg][blk][e]);
+#pragma unroll
+            for (int off = 16; off < 64; off *= 2) {
+                const float o0 = __shfl_xor(mx[0], off), o1 = __shfl_xor(mx[1], off);
+                mx[0] = fmaxf(mx[0], o0);
+                mx[1] = fmaxf(mx[1], o1);
+            }
+            mx[1] = fmaxf(mx[1], mx[0]);
+            // a group of queries that sees none of these keys (its rows all lie before kb) keeps its state: mx = m_run,
+            // alpha = 1, every p = 0.  On a group's first tile m_run = -inf and mx is finite (key 0 is visible).
+            float top[2] = {t_run[qg], t_run[qg]};
+            if (__any(mx[0] != m_run[qg])) {
+                top[0] = top[1] = mx[0] * sc;
+                const float alpha = __builtin_amdgcn_exp2f(t_run[qg] - top[0]);
                 l_run[qg] *= alpha;
-                m_run[qg] = mx;
 #pragma unroll
                 for (int db = 0; db < 8; ++db)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) acc[qg][db][e] *= alpha;
             }
-            const float top = mx * sc;
-            float p[16], psum = 0.f;
+            moved[qg] = __any(mx[1] != mx[0]);
+            if (moved[qg]) top[1] = mx[1] * sc;
+            back[qg] = __builtin_amdgcn_exp2f(top[0] - top[1]);
+            m_run[qg] = mx[1];
+            t_run[qg] = top[1];
+            float p[16], psum[2] = {0.f, 0.f};
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                p[i] = __builtin_amdgcn_exp2f(fmaf(s[qg][i >> 2][i & 3], sc, -top));
-                psum += p[i];
+                p[i] = __builtin_amdgcn_exp2f(fmaf(s[qg][i >> 2][i & 3], sc, -top[i >> 3]));
+                psum[i >> 3] += p[i];
             }
-            l_run[qg] += psum;
+            l_run[qg] = fmaf(l_run[qg] + psum[0], back[qg], psum[1]);
 #pragma unroll
             for (int h = 0; h < 2; ++h)
                 pf[qg][h].u = make_uint4(pack_bf16x2(p[8 * h], p[8 * h + 1]), pack_bf16x2(p[8 * h + 2], p[8 * h + 3]),
@@ -302,6 +317,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             // (the second 32 keys may lie behind every query of the wave (wave-uniform): their probabilities are 0, but a value
             // there that is not finite would still make NaNs of sums that it is no part of)
             if (kb + 32 * h > q0 + ATT_WAVE_Q - 1) break;
+            if (h == 1) {
+#pragma unroll
+                for (int qg = 0; qg < ATT_QG; ++qg)
+                    if (moved[qg]) {
+#pragma unroll
+                        for (int db = 0; db < 8; ++db)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) acc[qg][db][e] *= back[qg];
+                    }
+            }
 #pragma unroll
             for (int db = 0; db < 8; ++db) {
                 Frag vf;                                               // dim 16 db + n, the keys in the order the probabilities are held
