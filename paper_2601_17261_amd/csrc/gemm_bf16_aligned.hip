@@ -384,8 +384,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
     // The four waves' sums meet in LDS, in `red`: the head of a W stage that nothing reads or fills at that moment
     // (the operand stages take all of the LDS)
     // rs, cs: rows and columns of the tile that the tile before it has counted (the last tile of a direction starts at the
-    // last 256 rows or columns instead of hanging over the edge).  Such tiles, and all of a layer whose target rows do not start
-    // on 16 bytes, are squared in fp64 as well: what gemm_bf16.hip squares so keeps its precision here
+    // last 256 rows or columns instead of hanging over the edge).  A column tile that overlaps by no multiple of 16, and all tiles of
+    // a layer whose target rows do not start on 16 bytes, are squared in fp64 as well: what gemm_bf16.hip squares so keeps its
+    // precision here.  (Otherwise a lane's 16 columns of a group count or do not count together; the wide form takes some 2 us more
+    // a tile)
     auto eval_sum = [&](int rs, int cs) __attribute__((always_inline)) {
         double part = 0.0;
         if constexpr (PHASES == 1) settle();
@@ -396,11 +398,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
                 if (LATE_T && PHASES == 1 && T_F32 && J == 4) { tload(IC<4>{}); tload(IC<5>{}); tload(IC<6>{}); tload(IC<7>{}); }
                 // the first of the lane's 16 columns per group that counts
                 int from[2] = {0, 0};
-                if (wide) {
+                if (RAGGED) {
                     const bool in = wb * 128 + J * 16 + lc >= rs;
                     from[0] = in ? cs - (wa * 128 + lg * 16) : 16;
                     from[1] = in ? cs - (wa * 128 + 64 + lg * 16) : 16;
-                    // (or the compiler works out all 256 conditions ahead and keeps them)
+                    // (or the compiler works out all conditions ahead and keeps them)
                     asm volatile("" : "+v"(from[0]), "+v"(from[1]));
                 }
 #pragma clang loop unroll(full)
@@ -419,11 +421,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
                             s4 = fmaf(x, x, s4);
                         }
                     }
-                    if (!wide) part += (double)s4;
+                    if (!wide) part += (double)(!RAGGED || from[I >> 2] <= 0 ? s4 : 0.f);
                 }
             }
         };
-        if (RAGGED && ((rs | cs) != 0 || !p.vec_ok)) sum(IC<1>{});
+        if (RAGGED && ((cs & 15) != 0 || !p.vec_ok)) sum(IC<1>{});
         else sum(IC<0>{});
         return part;
     };

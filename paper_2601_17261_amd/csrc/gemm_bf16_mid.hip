@@ -296,9 +296,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             store16_any(dst + 8, make_uint4(w[4], w[5], w[6], w[7]));
         }
     } else {
-        // squares in fp32 four at a time, summed in fp64; lanes, then waves, in a fixed order.  Tiles that overlap the one before
-        // them, and all of a layer whose target rows do not start on 16 bytes, are squared in fp64 as well: what
-        // gemm_bf16_small.hip squares so keeps its precision here
+        // squares in fp32 four at a time, summed in fp64; lanes, then waves, in a fixed order.  A column tile that overlaps the one
+        // before it by no multiple of 16, and all tiles of a layer whose target rows do not start on 16 bytes, are squared in fp64 as
+        // well: what gemm_bf16_small.hip squares so keeps its precision here.  (Otherwise a lane's 16 columns count or do not count
+        // together)
         double part = 0.0;
         // value of element e of block (I, J) among the raw vectors
         auto target_value = [&](int J, int I, int e) __attribute__((always_inline)) {
@@ -330,11 +331,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                             s4 = fmaf(x, x, s4);
                         }
                     }
-                    if (!wide) part += (double)s4;
+                    if (!wide) part += (double)(from <= 0 ? s4 : 0.f);
                 }
             }
         };
-        if (p.wide || m0 != row_new || n0 != col_new) sum(IC<1>{});
+        if (p.wide || ((int)(col_new - n0) & 15) != 0) sum(IC<1>{});
         else sum(IC<0>{});
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
