@@ -486,44 +486,49 @@ __device__ __forceinline__ void xtt_bf16_body(const bf16_t* __restrict__ X, int6
         }
     };
     // A wave's steps: every fourth of the range, from its own number on; ALONE: the four waves' steps one wave after the other, and
-    // their sums added in that order (tot).  Either way the same bits
+    // their sums added in that order (tot).  Either way the same bits.  Two register sets in turn: moved from one to the other at the
+    // end of a step, the loads would be waited for there
     floatx4 tot[ALONE ? NB : 1][8] = {};
-    int w = ALONE ? 0 : wave;
-    int64_t tb = ts + w * XTT_STEP;
+    int64_t tb = ts + (ALONE ? 0 : wave * XTT_STEP);
     if (tb < te) {
-        bool first = true;
-        // the step behind the one at tb, which may belong to the next wave's share; `more`: there is one
-        int wn;
-        int64_t tn;
-        auto find = [&]() __attribute__((always_inline)) -> bool {
-            wn = w;
-            tn = tb + STRIDE;
-            if (ALONE && tn >= te) tn = (++wn < 4) ? ts + wn * XTT_STEP : te;
-            return tn < te;
-        };
-        auto step = [&](uint4 (&v)[8], Frag (&a)[NB][3], uint4 (&v2)[8], Frag (&a2)[NB][3]) __attribute__((always_inline)) -> bool {
-            const bool more = find();
-            load_step(more ? tn : tb, v2, a2);
-            multiply(v, a);
-            if (ALONE && (wn != w || !more)) {
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        tot[ALONE ? nb : 0][j] = first ? acc[nb][j] : tot[ALONE ? nb : 0][j] + acc[nb][j];
-                        acc[nb][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-                    }
-                first = false;
-            }
-            tb = tn;
-            w = wn;
-            return more;
-        };
-        // two register sets in turn: moved from one to the other at the end of a step, the loads would be waited for there
         uint4 v0[8], v1[8];
         Frag a0[NB][3], a1[NB][3];
         load_step(tb, v0, a0);
-        while (step(v0, a0, v1, a1) && step(v1, a1, v0, a0)) {}
+        if constexpr (!ALONE) {
+            for (; tb < te; tb += 2 * STRIDE) {
+                load_step(min(tb + STRIDE, te - XTT_STEP), v1, a1);
+                multiply(v0, a0);
+                if (tb + STRIDE >= te) break;
+                load_step(min(tb + 2 * STRIDE, te - XTT_STEP), v0, a0);
+                multiply(v1, a1);
+            }
+        } else {
+            int w = 0;
+            bool first = true;
+            // the step at tb, with the loads of the one behind it, which may be the first of the next wave's; false: there is none
+            auto step = [&](uint4 (&v)[8], Frag (&a)[NB][3], uint4 (&v2)[8], Frag (&a2)[NB][3]) __attribute__((always_inline)) -> bool {
+                int wn = w;
+                int64_t tn = tb + STRIDE;
+                if (tn >= te) tn = (++wn < 4) ? ts + wn * XTT_STEP : te;
+                const bool more = tn < te;
+                load_step(more ? tn : tb, v2, a2);
+                multiply(v, a);
+                if (wn != w || !more) {
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) {
+                            tot[nb][j] = first ? acc[nb][j] : tot[nb][j] + acc[nb][j];
+                            acc[nb][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+                        }
+                    first = false;
+                }
+                tb = tn;
+                w = wn;
+                return more;
+            };
+            while (step(v0, a0, v1, a1) && step(v1, a1, v0, a0)) {}
+        }
     }
     // D layout: row (k within block) = 4*(lane/16) + e, col = lane%16 -> feature db + 8*lc + j
     if constexpr (ALONE) {
@@ -561,7 +566,7 @@ struct XttDev {
     float* partial; int64_t tok_per_split;
 };
 template <int NB, bool ALONE, int CAP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NB <= 2 ? 2 : 1))) void xtt_bf16_many_kernel(const KBatch<XttDev, CAP> tb) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NB == 2 ? 2 : 1))) void xtt_bf16_many_kernel(const KBatch<XttDev, CAP> tb) {
     uint32_t bx, by;
     const XttDev& a = tb.a[kbatch_find(tb, bx, by)];
     xtt_bf16_body<NB, ALONE>(a.X, a.ldx, a.M, a.K, a.TpackT, a.m_pad, a.partial, a.tok_per_split, bx, by);
@@ -576,7 +581,7 @@ static int64_t xtt_tokens_per_split(int64_t m_pad, int nsplit) {
 // once, a quarter of them leaves it idle (r = 32, 16384 tokens of a 4096-wide layer, 256 workgroups of 64 steps: 65 us against 33), and
 // beyond that the adding is worth avoiding for short ranges (seven 4B-sized layers, 512 tokens, 832 of 4 steps: 15 us against 25 at
 // r = 32, 28 against 55 at r = 64) and, where it allows one workgroup per compute unit (r > 32), for long ones too once
-// there are many (4096 tokens, 1860 of some 16 steps: 139 us against 163 at r = 64, 103 against 130 at r = 48, but 78
+// there are many (4096 tokens, 1860 of some 16 steps: 129 us against 163 at r = 64, 103 against 130 at r = 48, but 78
 // against 70 at r = 32; one 9728-wide layer, 304 of 32 steps: 67 against 52 at r = 64)
 static bool xtt_alone(int rp, int64_t workgroups, int64_t steps) {
     return workgroups > 256 && (steps <= 8 * workgroups || (rp > 32 && workgroups >= 1024));
