@@ -156,8 +156,8 @@ int agzo_basis(agzo_ctx* ctx, const agzo_layer* L, const void* X, int32_t K, uin
 
 /* Alg. 1 for n layers at once (Alg. 2, first loop: the base forward computes every layer's basis; the extractions are
  * independent of each other).  Per item the arguments of agzo_basis; every stage of the algorithm (test matrix,
- * sketches, orthonormalisations, power steps) is one launch for up to 16 bf16 layers whose ranks round up to the same
- * multiple of 16, instead of one per layer, which is what a set of small layers is bound by.  Every B is bit-identical
+ * sketches, orthonormalisations, power steps) is one launch for up to 16 layers of one storage type whose ranks round up to the
+ * same multiple of 16, instead of one per layer, which is what a set of small layers is bound by.  Every B is bit-identical
  * to what agzo_basis gives for the same item.  items: host array, read during the call only; the B of different items
  * must not overlap.  n = 0 is a no-op.  Errors: AGZO_EINVAL for n < 0, NULL items, or an item agzo_basis would reject
  * (nothing is enqueued then). */

@@ -1,5 +1,6 @@
-// Shared between the two tilings of the bf16 forward GEMM (gemm_bf16.hip: 256 x 256 tiles for shapes that fill the
-// chip with them; gemm_bf16_small.hip: 128 x 128 tiles for the others): launch parameters and the LDS tile layout.
+// Shared between the kernels of the bf16 forward GEMM: launch parameters and the LDS tile layout.  256 x 256 tiles for shapes that
+// fill the chip with them (gemm_bf16_aligned.hip; gemm_bf16.hip for what that one has no output form for or does not fit into a layer),
+// 128 x 128 tiles for the others (gemm_bf16_mid.hip; gemm_bf16_small.hip likewise).
 #pragma once
 #include "agzo_internal.h"
 

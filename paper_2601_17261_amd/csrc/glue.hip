@@ -95,7 +95,7 @@ __global__ __launch_bounds__(256) void glue_add_kernel(bf16_t* __restrict__ h, i
 //       Per tile and group of queries a wave has 512 cycles of matrix work, about as much exponential and other vector work (the
 //       mask only on tiles that reach past the group, the rescaling only where a maximum moved) and 8 KB of LDS reads; two
 //       workgroups per compute unit overlap them.  With every wave fetching its own K and V^T fragments from memory 16 x 512
-//       tokens of 16 heads took 160 us, now 50 (345 TFLOP/s of causal work); prep with a thread's own angles per head 34, now 21.
+//       tokens of 16 heads took 160 us, now 51 (340 TFLOP/s of causal work); prep with a thread's own angles per head 34, now 21.
 // ---------------------------------------------------------------------------
 constexpr int HEAD_DIM = 128;
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
