@@ -810,8 +810,16 @@ hipError_t launch_gemm_bf16_many(const GemmBf16Args* a, int n, hipStream_t st) {
             e = launch_gemm_bf16_mid(g, ng, 0, f32 != 0, st);
             if (e != hipSuccess) return e;
         }
+        // the shared schedule's tiles together
+        auto one_pass = [&](int i) { return c[i].kernel == Kernel::aligned && c[i].p.shared; };
+        const GemmParams* sh[kBatchMax];
+        int ns = 0;
+        for (int i = 0; i < nb; ++i)
+            if (one_pass(i)) sh[ns++] = &c[i].p;
+        e = launch_gemm_bf16_aligned_shared(sh, ns, st);
+        if (e != hipSuccess) return e;
         for (int i = 0; i < nb; ++i) {
-            if (a[b + i].M == 0 || a[b + i].N == 0 || shared_launch(i)) continue;
+            if (a[b + i].M == 0 || a[b + i].N == 0 || shared_launch(i) || one_pass(i)) continue;
             e = launch_one(c[i], st);
             if (e != hipSuccess) return e;
         }

@@ -62,7 +62,9 @@
 // PHASES = 3 is the shared-forward schedule for a single layer: the d_in slices are multiplied once, f0 is the sum of
 // squares of the accumulators as they stand, the extension slices with +eps make them the residual of f+, the same
 // slices with -2 eps that of f-.  The extension operands of both passes are requested before the evaluation that
-// precedes them, so their latency runs under it.
+// precedes them, so their latency runs under it.  A workgroup takes one tile, and a launch the tiles of up to kBatchMax
+// layers, the deepest first: a launch per layer ends on a round that is partly idle, seven times for a set (4096 tokens
+// of the 4B-sized layers, 64 to 608 tiles each, r = 64: 1031 us in seven launches, 775 in one).
 #include "gemm_bf16_common.h"
 
 namespace agzo {
@@ -98,15 +100,30 @@ __device__ __forceinline__ float from_acc(float x) {
     return r;
 }
 
-template <int OUT, bool T_F32, int PHASES, bool RAGGED>
-__global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
+// what the kernel needs of one problem (GemmParams without the fields of the other kernels: sixteen fit a launch's arguments)
+struct AlignedItem {
+    const bf16_t *X, *W, *Xext, *Wext, *Wext2;
+    int64_t ldx, ldw, M, N, K, ldt, ldy;
+    const void* target;
+    double* partials;
+    void* Y;
+    const int32_t* ce_target; float2* ce_ms; float* ce_tl;
+    unsigned long long* clk;
+    int ext_ld, tiles_m, tiles_n, group_m, vec_ok;
+};
+
+template <int OUT, bool T_F32, int PHASES, bool RAGGED, int CAP>
+__global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const KBatch<AlignedItem, CAP> tb) {
+    static_assert(CAP == 1 || PHASES == 3, "tile lists are lists of one problem's tiles");
     static_assert(OUT == 0 || (PHASES == 1 && !T_F32), "the kernels without a squared-error target have one evaluation");
     constexpr bool LATE_T = RAGGED && OUT == 0;    // the target is subtracted after the last slice
     constexpr int NT = 256, BA = 4, BB = 4;
     constexpr int W_BASE = 0, X_BASE = 3 * TILE_BYTES;       // LDS: three W stages, then two X stages (all 160 KiB)
     extern __shared__ __align__(16) char smem[];
+    uint32_t wgid, unused;                                   // this problem's workgroups count from 0
+    const AlignedItem& p = tb.a[kbatch_find(tb, wgid, unused)];
     const int tid = threadIdx.x, lane = tid & 63;
-    if (p.clk && blockIdx.x == 0 && tid == 0) { p.clk[0] = __builtin_readcyclecounter(); p.clk[1] = wall_clock64(); }
+    if (p.clk && wgid == 0 && tid == 0) { p.clk[0] = __builtin_readcyclecounter(); p.clk[1] = wall_clock64(); }
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wa = wave >> 1, wb = wave & 1;
     const int lc = lane & 15, lg = lane >> 4;      // matrix instruction 16x16x32: column (token) / row of a fragment, k group
@@ -117,10 +134,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
     // run, tiles are ordered in bands of group_m token tiles per output tile, so that the tiles an XCD works on at any
     // moment share a few W tiles and a band of X tiles.
     const int nwg = p.tiles_m * p.tiles_n;
-    const int G = (int)gridDim.x;
+    const int G = (int)tb.gx[CAP == 1 ? 0 : &p - tb.a];
     const bool by_xcd = (G % 8 == 0);
     const int S = by_xcd ? G / 8 : G;
-    const int xcd = by_xcd ? (int)blockIdx.x % 8 : 0, slot = by_xcd ? (int)blockIdx.x / 8 : (int)blockIdx.x;
+    const int xcd = by_xcd ? (int)wgid % 8 : 0, slot = by_xcd ? (int)wgid / 8 : (int)wgid;
     const int per = by_xcd ? nwg / 8 : nwg;
     const int n_run = slot < per ? (per - slot + S - 1) / S : 0;
     const int n_tiles = __builtin_amdgcn_readfirstlane(n_run + ((by_xcd && slot == S - 1 && xcd < nwg - 8 * per) ? 1 : 0));
@@ -688,57 +705,109 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(GemmParams p) {
         next_sources(it + 2);
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);                      // the slices fetched past the end of the list
-    if (p.clk && blockIdx.x == 0 && tid == 0) { p.clk[2] = __builtin_readcyclecounter(); p.clk[3] = wall_clock64(); }
+    if (p.clk && wgid == 0 && tid == 0) { p.clk[2] = __builtin_readcyclecounter(); p.clk[3] = wall_clock64(); }
 }
 
-template <int OUT, bool T_F32, int PHASES, bool RAGGED>
-static hipError_t launch_aligned_variant(const GemmParams& p, hipStream_t st) {
+template <int OUT, bool T_F32, int PHASES, bool RAGGED, int CAP>
+static hipError_t launch_aligned_grid(const KBatch<AlignedItem, CAP>& tb, unsigned blocks, hipStream_t st) {
     static bool attr_set = false;
     const int smem = 5 * TILE_BYTES;           // three W stages and two X stages: all 160 KiB of a compute unit's LDS
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_bf16_aligned_kernel<OUT, T_F32, PHASES, RAGGED>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_bf16_aligned_kernel<OUT, T_F32, PHASES, RAGGED, CAP>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, smem);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    // one workgroup per compute unit, each with a list of tiles (a multiple of 8 workgroups: one share per XCD); the
-    // shared-forward schedule needs both LDS stages between its evaluations and takes one tile per workgroup
-    int64_t G = (int64_t)p.tiles_m * p.tiles_n;
-    if (PHASES == 1) {
-        int dev = 0, cus = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e != hipSuccess) return e;
-        if (cus < 1) return hipErrorInvalidDevice;
-        // (rounded up: workgroups without a tile leave at once, while one short of a workgroup per tile 190 or 250 tiles took
-        // the time of two)
-        G = (G + 7) / 8 * 8;
-        if (G > cus) G = cus >= 8 ? cus - cus % 8 : cus;
-    }
-    dim3 grid((unsigned)G);
-    hipLaunchKernelGGL((gemm_bf16_aligned_kernel<OUT, T_F32, PHASES, RAGGED>), grid, dim3(256), smem, st, p);
+    hipLaunchKernelGGL((gemm_bf16_aligned_kernel<OUT, T_F32, PHASES, RAGGED, CAP>), dim3(blocks), dim3(256), smem, st, tb);
     return hipGetLastError();
+}
+
+static AlignedItem aligned_item(const GemmParams& p) {
+    AlignedItem a;
+    a.X = p.X; a.W = p.W; a.Xext = p.Xext; a.Wext = p.Wext; a.Wext2 = p.Wext2;
+    a.ldx = p.ldx; a.ldw = p.ldw; a.M = p.M; a.N = p.N; a.K = p.K; a.ldt = p.ldt; a.ldy = p.ldy;
+    a.target = p.target; a.partials = p.partials; a.Y = p.Y;
+    a.ce_target = p.ce_target; a.ce_ms = p.ce_ms; a.ce_tl = p.ce_tl; a.clk = p.clk;
+    a.ext_ld = p.ext_ld; a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n; a.group_m = p.group_m; a.vec_ok = p.vec_ok;
+    return a;
+}
+
+// one workgroup per compute unit, each with a list of tiles (a multiple of 8 workgroups: one share per XCD)
+template <int OUT, bool T_F32, bool RAGGED>
+static hipError_t launch_aligned_lists(const GemmParams& p, hipStream_t st) {
+    int dev = 0, cus = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    if (cus < 1) return hipErrorInvalidDevice;
+    // (rounded up: workgroups without a tile leave at once, while one short of a workgroup per tile 190 or 250 tiles took
+    // the time of two)
+    int64_t G = ((int64_t)p.tiles_m * p.tiles_n + 7) / 8 * 8;
+    if (G > cus) G = cus >= 8 ? cus - cus % 8 : cus;
+    const KBatch<AlignedItem, 1> tb{1, {0}, {(uint32_t)G}, {aligned_item(p)}};
+    return launch_aligned_grid<OUT, T_F32, 1, RAGGED>(tb, (unsigned)G, st);
 }
 
 template <bool RAGGED>
 static hipError_t launch_aligned(const GemmParams& p, hipStream_t st) {
     if (p.Y != nullptr) {       // stored output, no loss
-        if (p.loss_kind != AGZO_LOSS_NONE || p.y_dtype != AGZO_BF16 || p.shared) return hipErrorInvalidValue;
-        return launch_aligned_variant<1, false, 1, RAGGED>(p, st);
+        if (p.loss_kind != AGZO_LOSS_NONE || p.y_dtype != AGZO_BF16) return hipErrorInvalidValue;
+        return launch_aligned_lists<1, false, RAGGED>(p, st);
     }
     if (p.loss_kind == AGZO_LOSS_CE) {
-        if (p.shared || !p.ce_target || !p.ce_ms || !p.ce_tl) return hipErrorInvalidValue;
-        return launch_aligned_variant<2, false, 1, RAGGED>(p, st);
+        if (!p.ce_target || !p.ce_ms || !p.ce_tl) return hipErrorInvalidValue;
+        return launch_aligned_lists<2, false, RAGGED>(p, st);
     }
-    if (p.loss_kind != AGZO_LOSS_MSE || (p.shared && p.Wext2 == nullptr)) return hipErrorInvalidValue;
-    const bool f32 = p.target_dtype != AGZO_BF16;
-    if (p.shared) return f32 ? launch_aligned_variant<0, true, 3, RAGGED>(p, st) : launch_aligned_variant<0, false, 3, RAGGED>(p, st);
-    return f32 ? launch_aligned_variant<0, true, 1, RAGGED>(p, st) : launch_aligned_variant<0, false, 1, RAGGED>(p, st);
+    if (p.loss_kind != AGZO_LOSS_MSE) return hipErrorInvalidValue;
+    return p.target_dtype != AGZO_BF16 ? launch_aligned_lists<0, true, RAGGED>(p, st) : launch_aligned_lists<0, false, RAGGED>(p, st);
 }
 
+static bool aligned_fits(const GemmParams& p) { return p.M >= BT && p.N >= BT && p.K >= 2 * BK && (p.P == nullptr || p.Xext != nullptr); }
+static bool aligned_ragged(const GemmParams& p) { return !(p.vec_ok && p.M % BT == 0 && p.N % BT == 0 && p.K % BK == 0); }
+
 hipError_t launch_gemm_bf16_aligned(const GemmParams& p, hipStream_t st) {
-    if (p.M < BT || p.N < BT || p.K < 2 * BK || (p.P != nullptr && p.Xext == nullptr)) return hipErrorInvalidValue;
-    return p.vec_ok && p.M % BT == 0 && p.N % BT == 0 && p.K % BK == 0 ? launch_aligned<false>(p, st) : launch_aligned<true>(p, st);
+    if (!aligned_fits(p) || p.shared) return hipErrorInvalidValue;
+    return aligned_ragged(p) ? launch_aligned<true>(p, st) : launch_aligned<false>(p, st);
+}
+
+template <bool T_F32, bool RAGGED>
+static hipError_t launch_shared(const KBatch<AlignedItem>& tb, unsigned blocks, hipStream_t st) {
+    if (tb.n == 1) return launch_aligned_grid<0, T_F32, 3, RAGGED>(kbatch_one(tb), blocks, st);
+    return launch_aligned_grid<0, T_F32, 3, RAGGED>(tb, blocks, st);
+}
+
+hipError_t launch_gemm_bf16_aligned_shared(const GemmParams* const* a, int n, hipStream_t st) {
+    if (n < 0 || n > kBatchMax) return hipErrorInvalidValue;
+    int order[kBatchMax];
+    for (int i = 0; i < n; ++i) {
+        const GemmParams& p = *a[i];
+        if (!aligned_fits(p) || !p.shared || p.Y || p.loss_kind != AGZO_LOSS_MSE || !p.Wext2) return hipErrorInvalidValue;
+        int at = i;
+        for (; at > 0 && a[order[at - 1]]->K < p.K; --at) order[at] = order[at - 1];
+        order[at] = i;
+    }
+    for (int kind = 0; kind < 4; ++kind) {
+        const bool f32 = kind & 1, ragged = kind & 2;
+        KBatch<AlignedItem> tb;
+        tb.n = 0;
+        uint64_t blocks = 0;
+        for (int i = 0; i < n; ++i) {
+            const GemmParams& p = *a[order[i]];
+            if ((p.target_dtype != AGZO_BF16) != f32 || aligned_ragged(p) != ragged) continue;
+            // (a multiple of 8: workgroups of every problem start at the first XCD; those without a tile leave at once)
+            tb.first[tb.n] = (uint32_t)blocks;
+            tb.gx[tb.n] = (uint32_t)(((int64_t)p.tiles_m * p.tiles_n + 7) / 8 * 8);
+            blocks += tb.gx[tb.n];
+            tb.a[tb.n++] = aligned_item(p);
+        }
+        if (tb.n == 0) continue;
+        if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+        const unsigned g = (unsigned)blocks;
+        const hipError_t e = ragged ? (f32 ? launch_shared<true, true>(tb, g, st) : launch_shared<false, true>(tb, g, st))
+                                    : (f32 ? launch_shared<true, false>(tb, g, st) : launch_shared<false, false>(tb, g, st));
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace agzo

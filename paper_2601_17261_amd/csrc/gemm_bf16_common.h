@@ -90,8 +90,9 @@ bool gemm_bf16_mid_ok(const GemmItem& g, int out);
 hipError_t launch_gemm_bf16_mid(const GemmItem* a, int n, int out, bool target_f32, hipStream_t st);
 
 // persistent kernel in 256 x 256 tiles (gemm_bf16_aligned.hip): M, N >= 256, d_in >= 128, the rank-r term as prepared operands;
-// either the squared-error loss without a stored Y (p.shared: f0, f+, f- in one pass, needs Wext2, partials [3][tiles]), the
-// cross-entropy statistics without a stored Y, or a bf16 Y without a loss
+// either the squared-error loss without a stored Y, the cross-entropy statistics without a stored Y, or a bf16 Y without a loss
 hipError_t launch_gemm_bf16_aligned(const GemmParams& p, hipStream_t st);
+// squared error with p.shared (f0, f+, f- in one pass, needs Wext2, partials [3][tiles]): up to kBatchMax layers together
+hipError_t launch_gemm_bf16_aligned_shared(const GemmParams* const* a, int n, hipStream_t st);
 
 }  // namespace agzo
