@@ -44,12 +44,57 @@ __device__ __forceinline__ void store_ext(bf16_t* Xext, int64_t t, int k, int rp
     if (3 * rp < ld) dst[3 * rp] = 0;          // (ld - 3 rp is 0 or rp)
 }
 
+// the results of tokens t .. t + 3 (t and m_pad multiples of 4), column k
+__device__ __forceinline__ void xq_emit(floatx4 v, int64_t M, int r, int rp, float* __restrict__ T, bf16_t* __restrict__ TpackT, int64_t m_pad,
+                                        bf16_t* __restrict__ Xext, int64_t t, int k) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        if (!(t + e < M && k < r)) v[e] = 0.f;
+        if (t + e < M && k < r && T != nullptr) T[(t + e) * r + k] = v[e];
+        if (t + e < M && Xext != nullptr) store_ext(Xext, t + e, k, rp, v[e]);
+    }
+    if (TpackT == nullptr || t >= m_pad) return;
+    uint32_t w[3][2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        bf16_t h[2], m[2], l[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) split3_bf16(v[2 * u + i], h[i], m[i], l[i]);
+        w[0][u] = (uint32_t)h[0] | ((uint32_t)h[1] << 16);
+        w[1][u] = (uint32_t)m[0] | ((uint32_t)m[1] << 16);
+        w[2][u] = (uint32_t)l[0] | ((uint32_t)l[1] << 16);
+    }
+#pragma unroll
+    for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<uint2*>(TpackT + ((int64_t)pl * rp + k) * m_pad + t) = make_uint2(w[pl][0], w[pl][1]);
+}
+// what a wave's accumulators become.  D layout: row (token) = 4*(lane/16) + e, col (k) = lane%16.  part: partial sums, column by
+// column where planes are to be written, [split][RP][m_pad], token by token otherwise, [split][m_pad][RP]
+template <int NB, int MB>
+__device__ __forceinline__ void xq_store(const floatx4 (&acc)[MB][NB], int64_t M, int r, float* __restrict__ T, bf16_t* __restrict__ TpackT, int64_t m_pad,
+                                         float* __restrict__ part, bf16_t* __restrict__ Xext, int64_t t0, int split, int wave, int lm, int lg) {
+    constexpr int RP = NB * 16;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+        const int64_t t = t0 + (wave * MB + mb) * 16 + lg * 4;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const int k = nb * 16 + lm;
+            if (part == nullptr) xq_emit(acc[mb][nb], M, r, RP, T, TpackT, m_pad, Xext, t, k);
+            else if (t >= m_pad) continue;
+            else if (TpackT != nullptr) *reinterpret_cast<floatx4*>(part + ((int64_t)split * RP + k) * m_pad + t) = acc[mb][nb];
+            else
+#pragma unroll
+                for (int e = 0; e < 4; ++e) part[((int64_t)split * m_pad + t + e) * RP + k] = acc[mb][nb][e];
+        }
+    }
+}
+
 // bx: token block, by / ny: this workgroup's share of d_in (ny = 1: all of it)
 // ring depth: DEEP = one workgroup per CU with as many slices in flight as LDS holds; otherwise a shallower ring that
 // lets two workgroups share a CU, for launches with at least two workgroups per CU (several layers at once): while one
 // waits at its barrier or on its fragment reads the other multiplies
 template <int NB, bool DEEP>
-struct XqRing { static constexpr int STAGES = DEEP ? ((NB == 1) ? 8 : (NB == 2) ? 6 : 4) : ((NB == 1) ? 5 : (NB == 2) ? 3 : 4); };
+struct XqRing { static constexpr int STAGES = DEEP ? (NB == 1 ? 8 : 6) : (NB == 1 ? 5 : 3); };
 
 // a slot holds the rows of a slice and, where four waves do not share their groups evenly, groups that nobody reads: every wave
 // then issues the same number of loads and waits by constants (a wait chosen among a dozen cases and a branch around each load
@@ -74,9 +119,9 @@ __device__ __forceinline__ void xq_bf16_body(const bf16_t* __restrict__ X, int64
     const int lm = lane & 15, lg = lane >> 4;
     const int64_t t0 = (int64_t)bx * XQ_TOK;
 
-    floatx4 acc[NB];
+    floatx4 acc[1][NB];
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) acc[nb] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int nb = 0; nb < NB; ++nb) acc[0][nb] = floatx4{0.f, 0.f, 0.f, 0.f};
 
     // this wave's row groups g = wave, wave + 4, ...: per-lane source pointers (row of the group, swizzled chunk)
     constexpr int MAXG = (NGROUP + 3) / 4;
@@ -90,7 +135,7 @@ __device__ __forceinline__ void xq_bf16_body(const bf16_t* __restrict__ X, int64
         else src[i] = Qpack + (int64_t)(row - XQ_TOK) * K + c * 8;
     }
     // few tokens: gridDim.y workgroups share a token block, each taking a contiguous run of d_in slices, and leave
-    // partial sums in `part` for xq_finish_kernel (a single workgroup per block would walk d_in alone, bound by latency)
+    // partial sums in `part` for xq_finish_many_kernel (a single workgroup per block would walk d_in alone, bound by latency)
     const int nsplit = (int)ny, split = (int)by;
     const int nfull_all = (int)(K / XQ_BK);
     const int kbeg = (int)((int64_t)nfull_all * split / nsplit);
@@ -119,6 +164,7 @@ __device__ __forceinline__ void xq_bf16_body(const bf16_t* __restrict__ X, int64
         u32x4 a[2], b[2][NB][3];
         const uint32_t xaddr0 = (uint32_t)(uintptr_t)(lptr_t)(xs + xq_lds_off(wave * 16 + lm, lg)), xaddr1 = (uint32_t)(uintptr_t)(lptr_t)(xs + xq_lds_off(wave * 16 + lm, 4 + lg));
         const uint32_t qaddr0 = (uint32_t)(uintptr_t)(lptr_t)(qs + xq_lds_off(lm, lg)), qaddr1 = (uint32_t)(uintptr_t)(lptr_t)(qs + xq_lds_off(lm, 4 + lg));
+        static_assert(NB <= 2, "wider ones read X directly");
         if constexpr (NB == 1)
             asm volatile("ds_read_b128 %0, %8\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %10 offset:2048\n\t"
                          "ds_read_b128 %4, %10 offset:4096\n\tds_read_b128 %1, %9\n\tds_read_b128 %5, %11\n\t"
@@ -126,7 +172,7 @@ __device__ __forceinline__ void xq_bf16_body(const bf16_t* __restrict__ X, int64
                          : "=&v"(a[0]), "=&v"(a[1]), "=&v"(b[0][0][0]), "=&v"(b[0][0][1]), "=&v"(b[0][0][2]),
                            "=&v"(b[1][0][0]), "=&v"(b[1][0][1]), "=&v"(b[1][0][2])
                          : "v"(xaddr0), "v"(xaddr1), "v"(qaddr0), "v"(qaddr1) : "memory");
-        else if constexpr (NB == 2)
+        else
             asm volatile("ds_read_b128 %0, %14\n\tds_read_b128 %2, %16\n\tds_read_b128 %3, %16 offset:2048\n\t"
                          "ds_read_b128 %4, %16 offset:4096\n\tds_read_b128 %5, %16 offset:6144\n\t"
                          "ds_read_b128 %6, %16 offset:8192\n\tds_read_b128 %7, %16 offset:10240\n\tds_read_b128 %1, %15\n\t"
@@ -137,49 +183,14 @@ __device__ __forceinline__ void xq_bf16_body(const bf16_t* __restrict__ X, int64
                            "=&v"(b[0][1][1]), "=&v"(b[0][0][2]), "=&v"(b[0][1][2]), "=&v"(b[1][0][0]), "=&v"(b[1][1][0]),
                            "=&v"(b[1][0][1]), "=&v"(b[1][1][1]), "=&v"(b[1][0][2]), "=&v"(b[1][1][2])
                          : "v"(xaddr0), "v"(xaddr1), "v"(qaddr0), "v"(qaddr1) : "memory");
-        else if constexpr (NB == 3)
-            asm volatile("ds_read_b128 %0, %20\n\tds_read_b128 %2, %22\n\tds_read_b128 %3, %22 offset:2048\n\t"
-                         "ds_read_b128 %4, %22 offset:4096\n\tds_read_b128 %5, %22 offset:6144\n\t"
-                         "ds_read_b128 %6, %22 offset:8192\n\tds_read_b128 %7, %22 offset:10240\n\t"
-                         "ds_read_b128 %8, %22 offset:12288\n\tds_read_b128 %9, %22 offset:14336\n\t"
-                         "ds_read_b128 %10, %22 offset:16384\n\tds_read_b128 %1, %21\n\tds_read_b128 %11, %23\n\t"
-                         "ds_read_b128 %12, %23 offset:2048\n\tds_read_b128 %13, %23 offset:4096\n\t"
-                         "ds_read_b128 %14, %23 offset:6144\n\tds_read_b128 %15, %23 offset:8192\n\t"
-                         "ds_read_b128 %16, %23 offset:10240\n\tds_read_b128 %17, %23 offset:12288\n\t"
-                         "ds_read_b128 %18, %23 offset:14336\n\tds_read_b128 %19, %23 offset:16384\n\ts_waitcnt lgkmcnt(0)"
-                         : "=&v"(a[0]), "=&v"(a[1]), "=&v"(b[0][0][0]), "=&v"(b[0][1][0]), "=&v"(b[0][2][0]),
-                           "=&v"(b[0][0][1]), "=&v"(b[0][1][1]), "=&v"(b[0][2][1]), "=&v"(b[0][0][2]), "=&v"(b[0][1][2]),
-                           "=&v"(b[0][2][2]), "=&v"(b[1][0][0]), "=&v"(b[1][1][0]), "=&v"(b[1][2][0]), "=&v"(b[1][0][1]),
-                           "=&v"(b[1][1][1]), "=&v"(b[1][2][1]), "=&v"(b[1][0][2]), "=&v"(b[1][1][2]), "=&v"(b[1][2][2])
-                         : "v"(xaddr0), "v"(xaddr1), "v"(qaddr0), "v"(qaddr1) : "memory");
-        else
-            asm volatile("ds_read_b128 %0, %26\n\tds_read_b128 %2, %28\n\tds_read_b128 %3, %28 offset:2048\n\t"
-                         "ds_read_b128 %4, %28 offset:4096\n\tds_read_b128 %5, %28 offset:6144\n\t"
-                         "ds_read_b128 %6, %28 offset:8192\n\tds_read_b128 %7, %28 offset:10240\n\t"
-                         "ds_read_b128 %8, %28 offset:12288\n\tds_read_b128 %9, %28 offset:14336\n\t"
-                         "ds_read_b128 %10, %28 offset:16384\n\tds_read_b128 %11, %28 offset:18432\n\t"
-                         "ds_read_b128 %12, %28 offset:20480\n\tds_read_b128 %13, %28 offset:22528\n\tds_read_b128 %1, %27\n\t"
-                         "ds_read_b128 %14, %29\n\tds_read_b128 %15, %29 offset:2048\n\tds_read_b128 %16, %29 offset:4096\n\t"
-                         "ds_read_b128 %17, %29 offset:6144\n\tds_read_b128 %18, %29 offset:8192\n\t"
-                         "ds_read_b128 %19, %29 offset:10240\n\tds_read_b128 %20, %29 offset:12288\n\t"
-                         "ds_read_b128 %21, %29 offset:14336\n\tds_read_b128 %22, %29 offset:16384\n\t"
-                         "ds_read_b128 %23, %29 offset:18432\n\tds_read_b128 %24, %29 offset:20480\n\t"
-                         "ds_read_b128 %25, %29 offset:22528\n\ts_waitcnt lgkmcnt(0)"
-                         : "=&v"(a[0]), "=&v"(a[1]), "=&v"(b[0][0][0]), "=&v"(b[0][1][0]), "=&v"(b[0][2][0]),
-                           "=&v"(b[0][3][0]), "=&v"(b[0][0][1]), "=&v"(b[0][1][1]), "=&v"(b[0][2][1]), "=&v"(b[0][3][1]),
-                           "=&v"(b[0][0][2]), "=&v"(b[0][1][2]), "=&v"(b[0][2][2]), "=&v"(b[0][3][2]), "=&v"(b[1][0][0]),
-                           "=&v"(b[1][1][0]), "=&v"(b[1][2][0]), "=&v"(b[1][3][0]), "=&v"(b[1][0][1]), "=&v"(b[1][1][1]),
-                           "=&v"(b[1][2][1]), "=&v"(b[1][3][1]), "=&v"(b[1][0][2]), "=&v"(b[1][1][2]), "=&v"(b[1][2][2]),
-                           "=&v"(b[1][3][2])
-                         : "v"(xaddr0), "v"(xaddr1), "v"(qaddr0), "v"(qaddr1) : "memory");
 #pragma unroll
         for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
             for (int pl = 0; pl < 3; ++pl)
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb)
-                    acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[sub]), __builtin_bit_cast(bf16x8, b[sub][nb][pl]),
-                                                                      acc[nb], 0, 0, 0);
+                    acc[0][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[sub]), __builtin_bit_cast(bf16x8, b[sub][nb][pl]),
+                                                                         acc[0][nb], 0, 0, 0);
     };
     // ring: slices kt .. kt + STAGES - 2 in flight while slice kt is multiplied
 #pragma unroll
@@ -224,35 +235,168 @@ __device__ __forceinline__ void xq_bf16_body(const bf16_t* __restrict__ X, int64
         __syncthreads();
         multiply(0);
     }
-    // D layout: row (token) = 4*(lane/16) + e, col (k) = lane%16
-    if (part != nullptr) {
+    xq_store<NB, 1>(acc, M, r, T, TpackT, m_pad, part, Xext, t0, split, wave, lm, lg);
+}
+
+// 48 and 64 columns.  The rows of X, which one wave alone reads, go to its registers, and only the planes through LDS: three
+// slices of them leave room for two workgroups on a compute unit.  A slice's 32-wide sub-steps take 16-byte chunks 2 lg and
+// 2 lg + 1 of a row, so that a row's line is asked for at once.  MB = 2, a wave with 32 tokens, reads the planes half as often: at 64
+// columns every wave reads 24 KB of them from LDS a slice against 2 KB of its own 16 tokens (4096 tokens of seven 4B-sized layers, r =
+// 64: 86 us through the ring above, 74 and 62 here with MB = 1 and 2)
+constexpr int XQD_STAGES = 3;
+constexpr int xqd_loads(int nb) { return (6 * nb + 3) / 4; }
+template <int NB, int MB>
+__device__ __forceinline__ void xq_direct_body(const bf16_t* __restrict__ X, int64_t ldx, int64_t M, int64_t K,
+                                               const bf16_t* __restrict__ Qpack, int r, float* __restrict__ T,
+                                               bf16_t* __restrict__ TpackT, int64_t m_pad, float* __restrict__ part,
+                                               bf16_t* __restrict__ Xext, uint32_t bx, uint32_t by, uint32_t ny) {
+    constexpr int RP = NB * 16, TOK = MB * XQ_TOK;
+    constexpr int QROWS = 3 * RP, LOADS = xqd_loads(NB);                // plane rows; a wave's direct loads of a slice
+    constexpr int STAGES = XQD_STAGES, SLOT = LOADS * 4096;
+    extern __shared__ __align__(16) char xq_smem[];
+    typedef __attribute__((address_space(3))) void* lptr_t;
+    typedef const __attribute__((address_space(1))) void* gptr_t;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lm = lane & 15, lg = lane >> 4;
+    const int64_t t0 = (int64_t)bx * TOK;
+
+    floatx4 acc[MB][NB];
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int64_t t = t0 + wave * 16 + lg * 4 + e;
-                if (t < m_pad) part[((int64_t)split * m_pad + t) * RP + nb * 16 + lm] = acc[nb][e];
-            }
-        return;
+        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+    const int nsplit = (int)ny, split = (int)by;
+    const int nfull_all = (int)(K / XQ_BK);
+    const int kbeg = (int)((int64_t)nfull_all * split / nsplit);
+    const int nfull = (int)((int64_t)nfull_all * (split + 1) / nsplit) - kbeg;      // this workgroup's slices
+    const bool tail = (K % XQ_BK) != 0 && split == nsplit - 1;
+    // plane rows: groups of eight, wave w takes w, w + 4, ... (past the last: the last once more, into rows nobody reads)
+    const bf16_t* src[LOADS];
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+        const int row = 8 * (wave + 4 * i) + (lane >> 3);
+        src[i] = Qpack + (int64_t)min(row, QROWS - 8 + (lane >> 3)) * K + ((lane & 7) ^ ((row >> 1) & 7)) * 8 + (int64_t)kbeg * XQ_BK;
     }
+    const bf16_t* xsrc[MB];
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        const int k = nb * 16 + lm;
+    for (int mb = 0; mb < MB; ++mb) xsrc[mb] = X + min(t0 + (wave * MB + mb) * 16 + lm, M - 1) * ldx + lg * 16 + (int64_t)kbeg * XQ_BK;
+    u32x4 x[STAGES][MB][2];
+    auto issue = [&](auto SET) __attribute__((always_inline)) {
+        constexpr int set = decltype(SET)::value;
+        char* base = xq_smem + set * SLOT + wave * 1024;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int64_t t = t0 + wave * 16 + lg * 4 + e;
-            const float v = (t < M && k < r) ? acc[nb][e] : 0.f;
-            if (t < M && k < r && T != nullptr) T[t * r + k] = v;
-            if (t < M && Xext != nullptr) store_ext(Xext, t, k, RP, v);
-            if (TpackT != nullptr && t < m_pad) {
-                bf16_t hi, mid, lo;
-                split3_bf16(v, hi, mid, lo);
-                TpackT[((int64_t)0 * RP + k) * m_pad + t] = hi;
-                TpackT[((int64_t)1 * RP + k) * m_pad + t] = mid;
-                TpackT[((int64_t)2 * RP + k) * m_pad + t] = lo;
-            }
+        for (int i = 0; i < LOADS; ++i) {
+            __builtin_amdgcn_global_load_lds((gptr_t)src[i], (lptr_t)(base + i * 4096), 16, 0, 0);
+            src[i] += XQ_BK;
         }
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+#pragma unroll
+            for (int sub = 0; sub < 2; ++sub) x[set][mb][sub] = *reinterpret_cast<const u32x4*>(xsrc[mb] + sub * 8);
+            xsrc[mb] += XQ_BK;
+        }
+    };
+    auto multiply = [&](int slot, u32x4 (&xa)[MB][2]) __attribute__((always_inline)) {
+        const char* qs = xq_smem + slot * SLOT;
+        u32x4 b[2][NB][3];
+        const uint32_t qaddr0 = (uint32_t)(uintptr_t)(lptr_t)(qs + xq_lds_off(lm, 2 * lg)), qaddr1 = (uint32_t)(uintptr_t)(lptr_t)(qs + xq_lds_off(lm, 2 * lg + 1));
+        static_assert(NB == 3 || NB == 4, "column blocks");
+        if constexpr (NB == 3)
+            asm volatile("ds_read_b128 %0, %18\n\tds_read_b128 %1, %18 offset:2048\n\tds_read_b128 %2, %18 offset:4096\n\t"
+                                     "ds_read_b128 %3, %18 offset:6144\n\tds_read_b128 %4, %18 offset:8192\n\tds_read_b128 %5, %18 offset:10240\n\t"
+                                     "ds_read_b128 %6, %18 offset:12288\n\tds_read_b128 %7, %18 offset:14336\n\tds_read_b128 %8, %18 offset:16384\n\t"
+                                     "ds_read_b128 %9, %19\n\tds_read_b128 %10, %19 offset:2048\n\tds_read_b128 %11, %19 offset:4096\n\t"
+                                     "ds_read_b128 %12, %19 offset:6144\n\tds_read_b128 %13, %19 offset:8192\n\tds_read_b128 %14, %19 offset:10240\n\t"
+                                     "ds_read_b128 %15, %19 offset:12288\n\tds_read_b128 %16, %19 offset:14336\n\tds_read_b128 %17, %19 offset:16384\n\t"
+                                     "s_waitcnt lgkmcnt(0)"
+                                     : "=&v"(b[0][0][0]), "=&v"(b[0][1][0]), "=&v"(b[0][2][0]), "=&v"(b[0][0][1]), "=&v"(b[0][1][1]),
+                                       "=&v"(b[0][2][1]), "=&v"(b[0][0][2]), "=&v"(b[0][1][2]), "=&v"(b[0][2][2]), "=&v"(b[1][0][0]),
+                                       "=&v"(b[1][1][0]), "=&v"(b[1][2][0]), "=&v"(b[1][0][1]), "=&v"(b[1][1][1]), "=&v"(b[1][2][1]),
+                                       "=&v"(b[1][0][2]), "=&v"(b[1][1][2]), "=&v"(b[1][2][2])
+                                     : "v"(qaddr0), "v"(qaddr1) : "memory");
+        else
+            asm volatile("ds_read_b128 %0, %24\n\tds_read_b128 %1, %24 offset:2048\n\tds_read_b128 %2, %24 offset:4096\n\t"
+                                     "ds_read_b128 %3, %24 offset:6144\n\tds_read_b128 %4, %24 offset:8192\n\tds_read_b128 %5, %24 offset:10240\n\t"
+                                     "ds_read_b128 %6, %24 offset:12288\n\tds_read_b128 %7, %24 offset:14336\n\tds_read_b128 %8, %24 offset:16384\n\t"
+                                     "ds_read_b128 %9, %24 offset:18432\n\tds_read_b128 %10, %24 offset:20480\n\tds_read_b128 %11, %24 offset:22528\n\t"
+                                     "ds_read_b128 %12, %25\n\tds_read_b128 %13, %25 offset:2048\n\tds_read_b128 %14, %25 offset:4096\n\t"
+                                     "ds_read_b128 %15, %25 offset:6144\n\tds_read_b128 %16, %25 offset:8192\n\tds_read_b128 %17, %25 offset:10240\n\t"
+                                     "ds_read_b128 %18, %25 offset:12288\n\tds_read_b128 %19, %25 offset:14336\n\tds_read_b128 %20, %25 offset:16384\n\t"
+                                     "ds_read_b128 %21, %25 offset:18432\n\tds_read_b128 %22, %25 offset:20480\n\tds_read_b128 %23, %25 offset:22528\n\t"
+                                     "s_waitcnt lgkmcnt(0)"
+                                     : "=&v"(b[0][0][0]), "=&v"(b[0][1][0]), "=&v"(b[0][2][0]), "=&v"(b[0][3][0]), "=&v"(b[0][0][1]),
+                                       "=&v"(b[0][1][1]), "=&v"(b[0][2][1]), "=&v"(b[0][3][1]), "=&v"(b[0][0][2]), "=&v"(b[0][1][2]),
+                                       "=&v"(b[0][2][2]), "=&v"(b[0][3][2]), "=&v"(b[1][0][0]), "=&v"(b[1][1][0]), "=&v"(b[1][2][0]),
+                                       "=&v"(b[1][3][0]), "=&v"(b[1][0][1]), "=&v"(b[1][1][1]), "=&v"(b[1][2][1]), "=&v"(b[1][3][1]),
+                                       "=&v"(b[1][0][2]), "=&v"(b[1][1][2]), "=&v"(b[1][2][2]), "=&v"(b[1][3][2])
+                                     : "v"(qaddr0), "v"(qaddr1) : "memory");
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl)
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+                        acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, xa[mb][sub]), __builtin_bit_cast(bf16x8, b[sub][nb][pl]),
+                                                                              acc[mb][nb], 0, 0, 0);
+    };
+    // slices kt .. kt + 2: one being multiplied, two in flight
+    std::integral_constant<int, 0> c0; std::integral_constant<int, 1> c1; std::integral_constant<int, 2> c2;
+    auto step = [&](auto SET, auto YOUNGER, bool more) __attribute__((always_inline)) {
+        constexpr int set = decltype(SET)::value;
+        wait_vmcnt<decltype(YOUNGER)::value * (LOADS + 2 * MB)>();
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        if (more) issue(std::integral_constant<int, (set + 2) % 3>{});
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(set, x[set]);
+    };
+    if (nfull >= 2) {
+        issue(c0);
+        __builtin_amdgcn_sched_barrier(0);
+        issue(c1);
+        __builtin_amdgcn_sched_barrier(0);
+        int left = nfull;
+        for (; left >= 5; left -= 3) {
+            step(c0, c1, true);
+            step(c1, c1, true);
+            step(c2, c1, true);
+        }
+        if (left == 4) { step(c0, c1, true); step(c1, c1, true); step(c2, c1, false); step(c0, c0, false); }
+        else if (left == 3) { step(c0, c1, true); step(c1, c1, false); step(c2, c0, false); }
+        else { step(c0, c1, false); step(c1, c0, false); }
+    } else if (nfull == 1) {
+        issue(c0);
+        step(c0, c0, false);
     }
+    if (tail) {
+        // ragged end of d_in: the threads copy it themselves, zero past d_in
+        __syncthreads();
+        const int64_t k0 = (int64_t)nfull_all * XQ_BK;
+        for (int e = tid; e < QROWS * 8; e += 256) {
+            const int row = e >> 3, c = e & 7;
+            uint4 v = make_uint4(0, 0, 0, 0);
+            if (k0 + c * 8 < K) v = *reinterpret_cast<const uint4*>(Qpack + (int64_t)row * K + k0 + c * 8);
+            *reinterpret_cast<uint4*>(xq_smem + xq_lds_off(row, c)) = v;
+        }
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int sub = 0; sub < 2; ++sub) {
+                const int64_t k = k0 + lg * 16 + sub * 8;
+                u32x4 v = {0, 0, 0, 0};
+                if (k < K) v = *reinterpret_cast<const u32x4*>(X + min(t0 + (wave * MB + mb) * 16 + lm, M - 1) * ldx + k);
+                x[0][mb][sub] = v;
+            }
+        __syncthreads();
+        multiply(0, x[0]);
+    }
+    xq_store<NB, MB>(acc, M, r, T, TpackT, m_pad, part, Xext, t0, split, wave, lm, lg);
 }
 
 // what a launch needs per product (the layers of a model)
@@ -260,7 +404,7 @@ struct XqDev {
     const bf16_t* X; int64_t ldx, M, K;
     const bf16_t* Qpack; int r;
     float* T; bf16_t* TpackT; int64_t m_pad; float* part;   // part: NULL unless ns > 1
-    int ns; int64_t rows;
+    int ns;
     bf16_t* Xext;
 };
 template <int NB, bool DEEP, int CAP>
@@ -270,18 +414,46 @@ __global__ __launch_bounds__(256) void xq_bf16_many_kernel(const KBatch<XqDev, C
     xq_bf16_body<NB, DEEP>(a.X, a.ldx, a.M, a.K, a.Qpack, a.r, a.T, a.TpackT, a.m_pad, a.part, a.Xext, bx, by, (uint32_t)a.ns);
 }
 
-// sums the d_in splits of xq in fixed order and writes what the unsplit kernel's epilogue writes; one thread per (t, k)
-__device__ __forceinline__ void xq_finish_body(const float* __restrict__ part, int nsplit, int64_t rows, int64_t M,
-                                               int64_t m_pad, int r, int rp, float* __restrict__ T,
-                                               bf16_t* __restrict__ TpackT, bf16_t* __restrict__ Xext, uint32_t bx) {
-    const int64_t idx = (int64_t)bx * 256 + threadIdx.x;
-    if (idx >= rows * rp) return;
-    const int64_t t = idx / rp;
-    const int k = (int)(idx - t * rp);
+template <int NB, int MB, int CAP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void xq_direct_many_kernel(const KBatch<XqDev, CAP> tb) {
+    uint32_t bx, by;
+    const XqDev& a = tb.a[kbatch_find(tb, bx, by)];
+    xq_direct_body<NB, MB>(a.X, a.ldx, a.M, a.K, a.Qpack, a.r, a.T, a.TpackT, a.m_pad, a.part, a.Xext, bx, by, (uint32_t)a.ns);
+}
+
+// sums the d_in splits of xq in fixed order and writes what the unsplit kernel's epilogue writes.  For the planes a workgroup takes
+// 64 tokens of 16 columns and a thread four tokens of a column, so that the stores of a wave are whole rows (with a thread per value,
+// columns side by side, every plane was written in 2-byte pieces: 28 us for 4096 tokens of seven layers at r = 64, 9 so).  T and the
+// extension operands are token by token, as their partial sums are: 16 tokens of 16 columns, a thread a value
+constexpr int XQF_TOK = 64, XQF_TOK_ROWS = 16;
+template <int CAP>
+__global__ __launch_bounds__(256) void xq_finish_many_kernel(const KBatch<XqDev, CAP> tb, int rp) {
+    uint32_t bx, by;
+    const XqDev& a = tb.a[kbatch_find(tb, bx, by)];
+    const int tid = threadIdx.x, nsplit = a.ns, r = a.r;
+    const int64_t m_pad = a.m_pad, M = a.M;
     // (eight splits' loads in flight; conditional on uniform values only - around a lane's condition the compiler waits for each
     // load before the next - and what lies behind the last token or column is left out below)
+    if (a.TpackT != nullptr) {
+        const int k = (int)by * 16 + (tid >> 4);
+        const int64_t t = (int64_t)bx * XQF_TOK + 4 * (tid & 15);
+        const float* src = a.part + (int64_t)k * m_pad + min(t, m_pad - 4);
+        floatx4 v = {0.f, 0.f, 0.f, 0.f};
+        for (int s0 = 0; s0 < nsplit; s0 += 8) {
+            floatx4 x[8];
+#pragma unroll
+            for (int s = 0; s < 8; ++s)
+                x[s] = s0 + s < nsplit ? *reinterpret_cast<const floatx4*>(src + (int64_t)(s0 + s) * rp * m_pad) : floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < 8; ++s) v += x[s];
+        }
+        xq_emit(v, M, r, rp, a.T, a.TpackT, m_pad, a.Xext, t, k);
+        return;
+    }
+    const int64_t t = (int64_t)bx * XQF_TOK_ROWS + (tid >> 4);
+    const int k = (int)by * 16 + (tid & 15);
     float v = 0.f;
-    const float* src = part + (t < m_pad ? t : m_pad - 1) * rp + k;
+    const float* src = a.part + min(t, m_pad - 1) * rp + k;
     for (int s0 = 0; s0 < nsplit; s0 += 8) {
         float x[8];
 #pragma unroll
@@ -289,23 +461,9 @@ __device__ __forceinline__ void xq_finish_body(const float* __restrict__ part, i
 #pragma unroll
         for (int s = 0; s < 8; ++s) v += x[s];
     }
-    if (!(t < M && k < r)) v = 0.f;
-    if (t < M && k < r && T != nullptr) T[t * r + k] = v;
-    if (t < M && Xext != nullptr) store_ext(Xext, t, k, rp, v);
-    if (TpackT != nullptr && t < m_pad) {
-        bf16_t hi, mid, lo;
-        split3_bf16(v, hi, mid, lo);
-        TpackT[((int64_t)0 * rp + k) * m_pad + t] = hi;
-        TpackT[((int64_t)1 * rp + k) * m_pad + t] = mid;
-        TpackT[((int64_t)2 * rp + k) * m_pad + t] = lo;
-    }
-}
-
-template <int CAP>
-__global__ __launch_bounds__(256) void xq_finish_many_kernel(const KBatch<XqDev, CAP> tb, int rp) {
-    uint32_t bx, by;
-    const XqDev& a = tb.a[kbatch_find(tb, bx, by)];
-    xq_finish_body(a.part, a.ns, a.rows, a.M, a.m_pad, a.r, rp, a.T, a.TpackT, a.Xext, bx);
+    if (k >= r) v = 0.f;
+    if (t < M && k < r && a.T != nullptr) a.T[t * r + k] = v;
+    if (t < M && a.Xext != nullptr) store_ext(a.Xext, t, k, rp, v);
 }
 
 // number of d_in splits for M tokens (1 = the token blocks alone fill the chip, or d_in is too short to share)
@@ -326,65 +484,88 @@ size_t xq_part_bytes(int64_t M, int64_t K, int rp) {
 }
 
 template <int NB, bool DEEP, int CAP>
-static hipError_t launch_xq_many_ring(const KBatch<XqDev, CAP>& tb, unsigned blocks, hipStream_t st) {
+static hipError_t launch_xq_ring(const KBatch<XqDev, CAP>& tb, unsigned blocks, hipStream_t st) {
     const int smem = XqRing<NB, DEEP>::STAGES * xq_slot_bytes(NB);
     static bool set = false;
     if (!set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(xq_bf16_many_kernel<NB, DEEP, CAP>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(xq_bf16_many_kernel<NB, DEEP, CAP>), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
         if (e != hipSuccess) return e;
         set = true;
     }
     hipLaunchKernelGGL((xq_bf16_many_kernel<NB, DEEP, CAP>), dim3(blocks), dim3(256), smem, st, tb);
     return hipGetLastError();
 }
+template <int NB, int MB, int CAP>
+static hipError_t launch_xq_direct(const KBatch<XqDev, CAP>& tb, unsigned blocks, hipStream_t st) {
+    const int smem = XQD_STAGES * xqd_loads(NB) * 4096;
+    static bool set = false;
+    if (!set) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(xq_direct_many_kernel<NB, MB, CAP>), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+        if (e != hipSuccess) return e;
+        set = true;
+    }
+    hipLaunchKernelGGL((xq_direct_many_kernel<NB, MB, CAP>), dim3(blocks), dim3(256), smem, st, tb);
+    return hipGetLastError();
+}
+// (the result depends neither on the ring's depth nor on the tokens of a workgroup: same slices, same order)
 template <int NB, int CAP>
-static hipError_t launch_xq_many_nb(const KBatch<XqDev, CAP>& tb, unsigned blocks, hipStream_t st) {
-    // (the result does not depend on the ring's depth: same slices, same order)
-    if (NB <= 2 && blocks >= 512) return launch_xq_many_ring<NB, false>(tb, blocks, st);
-    return launch_xq_many_ring<NB, true>(tb, blocks, st);
+static hipError_t launch_xq_many_nb(const KBatch<XqDev, CAP>& tb, unsigned blocks, int mb, hipStream_t st) {
+    if constexpr (NB >= 3) return mb == 2 ? launch_xq_direct<NB, 2>(tb, blocks, st) : launch_xq_direct<NB, 1>(tb, blocks, st);
+    else return blocks >= 512 ? launch_xq_ring<NB, false>(tb, blocks, st) : launch_xq_ring<NB, true>(tb, blocks, st);
 }
 
 template <int CAP>
-static hipError_t launch_xq_cap(const KBatch<XqDev, CAP>& tb, unsigned blocks, int rp, hipStream_t st) {
+static hipError_t launch_xq_cap(const KBatch<XqDev, CAP>& tb, unsigned blocks, int rp, int mb, hipStream_t st) {
     switch (rp / 16) {
-        case 1: return launch_xq_many_nb<1>(tb, blocks, st);
-        case 2: return launch_xq_many_nb<2>(tb, blocks, st);
-        case 3: return launch_xq_many_nb<3>(tb, blocks, st);
-        case 4: return launch_xq_many_nb<4>(tb, blocks, st);
+        case 1: return launch_xq_many_nb<1>(tb, blocks, mb, st);
+        case 2: return launch_xq_many_nb<2>(tb, blocks, mb, st);
+        case 3: return launch_xq_many_nb<3>(tb, blocks, mb, st);
+        case 4: return launch_xq_many_nb<4>(tb, blocks, mb, st);
         default: return hipErrorInvalidValue;
     }
 }
 
 hipError_t launch_xq_bf16_many(const XqArgs* a, int n, hipStream_t st) {
     if (n < 0 || n > kBatchMax) return hipErrorInvalidValue;
+    int rp = 0;
+    uint64_t half = 0;                         // workgroups of 128 tokens
+    // the deepest first, so that the launch does not end on a few long workgroups
+    int order[kBatchMax], count = 0;
+    for (int m = 0; m < n; ++m) {
+        if (a[m].M == 0) continue;
+        int at = count++;
+        for (; at > 0 && a[order[at - 1]].K < a[m].K; --at) order[at] = order[at - 1];
+        order[at] = m;
+        if (rp == 0) rp = a[m].rp;
+        if (a[m].rp != rp || a[m].m_pad % 4) return hipErrorInvalidValue;       // one padded rank per launch
+        half += (uint64_t)((a[m].M + 2 * XQ_TOK - 1) / (2 * XQ_TOK)) * (uint64_t)(a[m].part ? xq_splits(a[m].m_pad, a[m].K) : 1);
+    }
+    if (rp == 0) return hipSuccess;
+    const int mb = rp >= 48 && half >= 256 ? 2 : 1;      // (where that leaves no compute unit without a workgroup)
     KBatch<XqDev> tb, fin;
     tb.n = fin.n = 0;
     uint64_t blocks = 0, fin_blocks = 0;
-    int rp = 0;
-    for (int m = 0; m < n; ++m) {
-        if (a[m].M == 0) continue;
-        if (rp == 0) rp = a[m].rp;
-        if (a[m].rp != rp) return hipErrorInvalidValue;       // one padded rank per launch
+    for (int i = 0; i < count; ++i) {
+        const int m = order[i];
         XqDev d;
         d.X = a[m].X; d.ldx = a[m].ldx; d.M = a[m].M; d.K = a[m].K; d.Qpack = a[m].Qpack; d.r = a[m].r;
         d.T = a[m].T; d.TpackT = a[m].TpackT; d.m_pad = a[m].m_pad;
-        d.rows = a[m].TpackT ? a[m].m_pad : a[m].M;
         d.Xext = a[m].Xext;
         d.ns = a[m].part ? xq_splits(a[m].m_pad, a[m].K) : 1;
         d.part = d.ns > 1 ? a[m].part : nullptr;
-        const uint32_t gx = (uint32_t)((d.rows + XQ_TOK - 1) / XQ_TOK);
+        const int64_t rows = a[m].TpackT ? a[m].m_pad : a[m].M;
+        const uint32_t gx = (uint32_t)((rows + mb * XQ_TOK - 1) / (mb * XQ_TOK));
         tb.first[tb.n] = (uint32_t)blocks; tb.gx[tb.n] = gx; tb.a[tb.n++] = d;
         blocks += (uint64_t)gx * (uint32_t)d.ns;
         if (d.ns > 1) {
-            const uint32_t fx = (uint32_t)((d.rows * rp + 255) / 256);
+            const int ftok = d.TpackT ? XQF_TOK : XQF_TOK_ROWS;
+            const uint32_t fx = (uint32_t)((rows + ftok - 1) / ftok);
             fin.first[fin.n] = (uint32_t)fin_blocks; fin.gx[fin.n] = fx; fin.a[fin.n++] = d;
-            fin_blocks += fx;
+            fin_blocks += (uint64_t)fx * (uint32_t)(rp / 16);
         }
     }
-    if (tb.n == 0) return hipSuccess;
     if (blocks > 0x7FFFFFFFull || fin_blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    hipError_t e = tb.n == 1 ? launch_xq_cap(kbatch_one(tb), (unsigned)blocks, rp, st) : launch_xq_cap(tb, (unsigned)blocks, rp, st);
+    hipError_t e = tb.n == 1 ? launch_xq_cap(kbatch_one(tb), (unsigned)blocks, rp, mb, st) : launch_xq_cap(tb, (unsigned)blocks, rp, mb, st);
     if (e != hipSuccess || fin.n == 0) return e;
     const dim3 fin_grid((unsigned)fin_blocks);
     if (fin.n == 1) hipLaunchKernelGGL(xq_finish_many_kernel<1>, fin_grid, dim3(256), 0, st, kbatch_one(fin), rp);
@@ -400,9 +581,8 @@ hipError_t launch_xq_bf16(const bf16_t* X, int64_t ldx, int64_t M, int64_t K, co
 
 // ---------------------------------------------------------------------------
 // xtt: workgroup = (panel of 128 features) x (token range); its four waves take 32-token steps in turn and add their sums in LDS.
-// ALONE (r > 16 only): a wave has a panel of its own and takes the four waves' steps one wave after the other: the same sums in the
-// same order, a quarter of the workgroups, and no adding of 128 rows of up to 64 columns in LDS, which takes longer than the few
-// steps it follows.
+// ALONE (r > 16 only): a wave takes the four waves' steps one wave after the other: the same sums in the same order, a quarter of
+// the workgroups, and no adding of 128 rows of up to 64 columns in LDS, which takes longer than the few steps it follows.
 // MFMA roles: A = T^T planes (rows = k, K = tokens), B = X^T (K = tokens, cols = features).
 // X is row-major in features, so a lane loads 8 features x 8 tokens as eight 16-byte rows and
 // transposes them in registers (byte permutes) into eight token-contiguous operands.
@@ -426,7 +606,7 @@ int xtt_num_splits(int64_t M, int64_t K) {
 }
 
 // bx: panel of features, by: token range
-template <int NB, bool ALONE>
+template <int NB>
 __device__ __forceinline__ void xtt_bf16_body(const bf16_t* __restrict__ X, int64_t ldx, int64_t M, int64_t K,
                                               const bf16_t* __restrict__ TpackT, int64_t m_pad,
                                               float* __restrict__ partial, int64_t tok_per_split, uint32_t bx, uint32_t by) {
@@ -434,8 +614,7 @@ __device__ __forceinline__ void xtt_bf16_body(const bf16_t* __restrict__ X, int6
     extern __shared__ __align__(16) float sbuf[];   // [XTT_PANEL][RP]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lc = lane & 15, lg = lane >> 4;
-    const int64_t db = ((int64_t)bx * (ALONE ? 4 : 1) + (ALONE ? wave : 0)) * XTT_PANEL;
-    if (ALONE && db >= K) return;
+    const int64_t db = (int64_t)bx * XTT_PANEL;
     const int split = (int)by;
     const int64_t ts = (int64_t)split * tok_per_split;
     const int64_t te = min(ts + tok_per_split, m_pad);
@@ -447,7 +626,6 @@ __device__ __forceinline__ void xtt_bf16_body(const bf16_t* __restrict__ X, int6
         for (int j = 0; j < 8; ++j) acc[nb][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
     const int64_t dcol = db + lc * 8;
-    const bool din = dcol < K;
     const int64_t dload = min(dcol, K - 8);        // (features past the end repeat the last, unstored)
     // one 32-token step: 8 KB of X and the T planes per wave.  The next step's loads are issued before this step's
     // matrix work (twice the bytes in flight: with one step in flight the sweep ran at memory latency); they are
@@ -485,61 +663,22 @@ __device__ __forceinline__ void xtt_bf16_body(const bf16_t* __restrict__ X, int6
                     acc[nb][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[nb][pl].v, b.v, acc[nb][j], 0, 0, 0);
         }
     };
-    // A wave's steps: every fourth of the range, from its own number on; ALONE: the four waves' steps one wave after the other, and
-    // their sums added in that order (tot).  Either way the same bits.  Two register sets in turn: moved from one to the other at the
-    // end of a step, the loads would be waited for there
-    floatx4 tot[ALONE ? NB : 1][8] = {};
-    int64_t tb = ts + (ALONE ? 0 : wave * XTT_STEP);
+    // A wave's steps: every fourth of the range, from its own number on.  Two register sets in turn: moved from one to the other at
+    // the end of a step, the loads would be waited for there
+    int64_t tb = ts + wave * XTT_STEP;
     if (tb < te) {
         uint4 v0[8], v1[8];
         Frag a0[NB][3], a1[NB][3];
         load_step(tb, v0, a0);
-        if constexpr (!ALONE) {
-            for (; tb < te; tb += 2 * STRIDE) {
-                load_step(min(tb + STRIDE, te - XTT_STEP), v1, a1);
-                multiply(v0, a0);
-                if (tb + STRIDE >= te) break;
-                load_step(min(tb + 2 * STRIDE, te - XTT_STEP), v0, a0);
-                multiply(v1, a1);
-            }
-        } else {
-            int w = 0;
-            bool first = true;
-            // the step at tb, with the loads of the one behind it, which may be the first of the next wave's; false: there is none
-            auto step = [&](uint4 (&v)[8], Frag (&a)[NB][3], uint4 (&v2)[8], Frag (&a2)[NB][3]) __attribute__((always_inline)) -> bool {
-                int wn = w;
-                int64_t tn = tb + STRIDE;
-                if (tn >= te) tn = (++wn < 4) ? ts + wn * XTT_STEP : te;
-                const bool more = tn < te;
-                load_step(more ? tn : tb, v2, a2);
-                multiply(v, a);
-                if (wn != w || !more) {
-#pragma unroll
-                    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                        for (int j = 0; j < 8; ++j) {
-                            tot[nb][j] = first ? acc[nb][j] : tot[nb][j] + acc[nb][j];
-                            acc[nb][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-                        }
-                    first = false;
-                }
-                tb = tn;
-                w = wn;
-                return more;
-            };
-            while (step(v0, a0, v1, a1) && step(v1, a1, v0, a0)) {}
+        for (; tb < te; tb += 2 * STRIDE) {
+            load_step(min(tb + STRIDE, te - XTT_STEP), v1, a1);
+            multiply(v0, a0);
+            if (tb + STRIDE >= te) break;
+            load_step(min(tb + 2 * STRIDE, te - XTT_STEP), v0, a0);
+            multiply(v1, a1);
         }
     }
     // D layout: row (k within block) = 4*(lane/16) + e, col = lane%16 -> feature db + 8*lc + j
-    if constexpr (ALONE) {
-        if (!din) return;                          // (d_in is a multiple of 8: a lane's features are all in or all out)
-        float* dst = partial + ((int64_t)split * K + dcol) * RP + lg * 4;
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) *reinterpret_cast<floatx4*>(dst + j * RP + nb * 16) = tot[nb][j];
-        return;
-    }
     for (int w = 0; w < 4; ++w) {
         if (wave == w) {
 #pragma unroll
@@ -560,16 +699,162 @@ __device__ __forceinline__ void xtt_bf16_body(const bf16_t* __restrict__ X, int6
         if (idx < nvalid) out[idx] = sbuf[idx];
 }
 
+// ALONE: a workgroup is four panels of one token range.  The planes of a step are the same for all of them (from memory to each wave, at
+// r = 64 they were 12 KB a step against 8 KB of X) and come through LDS, X with them, two steps ahead.  A wave has 16 columns of a
+// panel, 32 at r > 48: two or three waves to a SIMD, one of which multiplies while the others read, and accumulators and the sums of
+// finished shares that fit the registers without moves (a wave with all 64 columns spent 330 of a step's instructions on those).
+// 4096 tokens of seven 4B-sized layers: 70 -> 52 us at r = 32, 103 -> 66 at 48, 130 -> 75 at 64
+template <int NB>
+struct XttAlone {
+    static constexpr int NBW = NB == 4 ? 2 : 1, WAVES = 4 * NB / NBW;                                      // column blocks of a wave
+    static constexpr int LOADS = (3 * NB + WAVES - 1) / WAVES, XLOADS = (32 + WAVES - 1) / WAVES;        // a wave's direct loads of a step
+    static constexpr int STAGE = (LOADS * WAVES + 32) * 1024;
+};
+template <int NB>
+__device__ __forceinline__ void xtt_alone_body(const bf16_t* __restrict__ X, int64_t ldx, int64_t M, int64_t K,
+                                               const bf16_t* __restrict__ TpackT, int64_t m_pad,
+                                               float* __restrict__ partial, int64_t tok_per_split, uint32_t bx, uint32_t by) {
+    typedef XttAlone<NB> S;
+    constexpr int RP = NB * 16, SEGS = 3 * NB, NBW = S::NBW;  // 16-row segments of the planes: a direct load each, 1 KiB
+    constexpr int WAVES = S::WAVES, LOADS = S::LOADS, XLOADS = S::XLOADS, STAGE = S::STAGE, X_AT = LOADS * WAVES * 1024;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    extern __shared__ __align__(16) char xtt_smem[];          // [3 stages]: [segments][16 rows][32 tokens], [4 panels][32 tokens][128 features]
+    typedef __attribute__((address_space(3))) void* lptr_t;
+    typedef const __attribute__((address_space(1))) void* gptr_t;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lc = lane & 15, lg = lane >> 4, panel = wave & 3, nb0 = (wave >> 2) * NBW;
+    const int split = (int)by;
+    const int64_t ts = (int64_t)split * tok_per_split, te = min(ts + tok_per_split, m_pad);
+    const int64_t dcol = ((int64_t)bx * 4 + panel) * XTT_PANEL + lc * 8;
+    // (features past the end repeat the last, unstored)
+    const bf16_t* xcol = X + min(((int64_t)bx * 4 + panel) * XTT_PANEL + lc * 8, K - 8);
+
+    // this wave's segments of a step: segment wave + WAVES i (past the last: the last once more, into rows nobody reads)
+    const bf16_t* tsrc[LOADS];
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) tsrc[i] = TpackT + (int64_t)(16 * min(wave + WAVES * i, SEGS - 1) + (lane >> 2)) * m_pad + (lane & 3) * 8;
+
+    // the step behind that at tb, of share w: the shares are every fourth step, taken one share after the other
+    auto next = [&](int64_t& tb, int& w) __attribute__((always_inline)) {
+        tb += 4 * XTT_STEP;
+        if (tb >= te) tb = ++w < 4 ? ts + w * XTT_STEP : te;
+    };
+    auto issue = [&](int set, int64_t tb) __attribute__((always_inline)) {
+        tb = min(tb, te - XTT_STEP);                          // (past the last step: that once more)
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i)
+            __builtin_amdgcn_global_load_lds((gptr_t)(tsrc[i] + tb), (lptr_t)(xtt_smem + set * STAGE + (wave + WAVES * i) * 1024), 16, 0, 0);
+#pragma unroll
+        for (int i = 0; i < XLOADS; ++i) {                    // (rows past M meet zero planes)
+            const int q = min((wave >> 2) * XLOADS + i, 7);       // (three waves to a panel: the last once more)
+            __builtin_amdgcn_global_load_lds((gptr_t)(xcol + min(tb + 4 * q + lg, M - 1) * ldx), (lptr_t)(xtt_smem + set * STAGE + X_AT + panel * 8192 + q * 1024), 16, 0, 0);
+        }
+    };
+    floatx4 acc[NBW][8], tot[NBW][8];
+    auto multiply = [&](int set) __attribute__((always_inline)) {
+        u32x4 a[NBW][3], x[8];
+        const uint32_t addr = (uint32_t)(uintptr_t)(lptr_t)(xtt_smem + set * STAGE + nb0 * 1024 + lc * 64 + lg * 16);
+        const uint32_t xaddr = (uint32_t)(uintptr_t)(lptr_t)(xtt_smem + set * STAGE + X_AT + panel * 8192 + lg * 2048 + lc * 16);
+        if constexpr (NB == 2)
+            asm volatile("ds_read_b128 %0, %11\n\tds_read_b128 %1, %11 offset:2048\n\tds_read_b128 %2, %11 offset:4096\n\t"
+                                     "ds_read_b128 %3, %12\n\tds_read_b128 %4, %12 offset:256\n\tds_read_b128 %5, %12 offset:512\n\t"
+                                     "ds_read_b128 %6, %12 offset:768\n\tds_read_b128 %7, %12 offset:1024\n\tds_read_b128 %8, %12 offset:1280\n\t"
+                                     "ds_read_b128 %9, %12 offset:1536\n\tds_read_b128 %10, %12 offset:1792\n\ts_waitcnt lgkmcnt(0)"
+                                     : "=&v"(a[0][0]), "=&v"(a[0][1]), "=&v"(a[0][2]), "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]),
+                                       "=&v"(x[3]), "=&v"(x[4]), "=&v"(x[5]), "=&v"(x[6]), "=&v"(x[7])
+                                     : "v"(addr), "v"(xaddr) : "memory");
+        else if constexpr (NB == 3)
+            asm volatile("ds_read_b128 %0, %11\n\tds_read_b128 %1, %11 offset:3072\n\tds_read_b128 %2, %11 offset:6144\n\t"
+                                     "ds_read_b128 %3, %12\n\tds_read_b128 %4, %12 offset:256\n\tds_read_b128 %5, %12 offset:512\n\t"
+                                     "ds_read_b128 %6, %12 offset:768\n\tds_read_b128 %7, %12 offset:1024\n\tds_read_b128 %8, %12 offset:1280\n\t"
+                                     "ds_read_b128 %9, %12 offset:1536\n\tds_read_b128 %10, %12 offset:1792\n\ts_waitcnt lgkmcnt(0)"
+                                     : "=&v"(a[0][0]), "=&v"(a[0][1]), "=&v"(a[0][2]), "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]),
+                                       "=&v"(x[3]), "=&v"(x[4]), "=&v"(x[5]), "=&v"(x[6]), "=&v"(x[7])
+                                     : "v"(addr), "v"(xaddr) : "memory");
+        else
+            asm volatile("ds_read_b128 %0, %14\n\tds_read_b128 %1, %14 offset:1024\n\tds_read_b128 %2, %14 offset:4096\n\t"
+                                     "ds_read_b128 %3, %14 offset:5120\n\tds_read_b128 %4, %14 offset:8192\n\tds_read_b128 %5, %14 offset:9216\n\t"
+                                     "ds_read_b128 %6, %15\n\tds_read_b128 %7, %15 offset:256\n\tds_read_b128 %8, %15 offset:512\n\t"
+                                     "ds_read_b128 %9, %15 offset:768\n\tds_read_b128 %10, %15 offset:1024\n\tds_read_b128 %11, %15 offset:1280\n\t"
+                                     "ds_read_b128 %12, %15 offset:1536\n\tds_read_b128 %13, %15 offset:1792\n\ts_waitcnt lgkmcnt(0)"
+                                     : "=&v"(a[0][0]), "=&v"(a[1][0]), "=&v"(a[0][1]), "=&v"(a[1][1]), "=&v"(a[0][2]), "=&v"(a[1][2]),
+                                       "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(x[4]), "=&v"(x[5]),
+                                       "=&v"(x[6]), "=&v"(x[7])
+                                     : "v"(addr), "v"(xaddr) : "memory");
+        // (two features at a time: a lone column block would multiply three times in a row into one accumulator)
+#pragma unroll
+        for (int j = 0; j < 8; j += 2) {
+            u32x4 b[2];                                       // word q of x[i] holds features 2q (low half) and 2q+1 (high half) of token i
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int pp = 0; pp < 4; ++pp) b[h][pp] = __builtin_amdgcn_perm(x[2 * pp + 1][j >> 1], x[2 * pp][j >> 1], h ? 0x07060302u : 0x05040100u);
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int nb = 0; nb < NBW; ++nb)
+                        acc[nb][j + h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[nb][pl]), __builtin_bit_cast(bf16x8, b[h]),
+                                                                                 acc[nb][j + h], 0, 0, 0);
+        }
+    };
+#pragma unroll
+    for (int nb = 0; nb < NBW; ++nb)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) tot[nb][j] = floatx4{-0.f, -0.f, -0.f, -0.f};      // (plus the first share: that share)
+    if (ts < te) {
+        int64_t ahead = ts;                                   // the step to be requested next
+        int wa = 0, set = 0;
+        issue(0, ahead);
+        next(ahead, wa);
+        issue(1, ahead);
+        next(ahead, wa);
+        for (int w = 0; w < 4 && ts + w * XTT_STEP < te; ++w) {
+#pragma unroll
+            for (int nb = 0; nb < NBW; ++nb)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) acc[nb][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+            for (int64_t tb = ts + w * XTT_STEP; tb < te; tb += 4 * XTT_STEP) {
+                wait_vmcnt<LOADS + XLOADS>();                      // this wave's loads of the step have landed
+                __builtin_amdgcn_sched_barrier(0);
+                __builtin_amdgcn_s_barrier();                 // everybody's have, and the stage of the step before is free
+                __builtin_amdgcn_sched_barrier(0);
+                issue(set == 0 ? 2 : set - 1, ahead);
+                next(ahead, wa);
+                multiply(set);
+                set = set == 2 ? 0 : set + 1;
+            }
+#pragma unroll
+            for (int nb = 0; nb < NBW; ++nb)
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) tot[nb][j][e] += acc[nb][j][e];
+        }
+        wait_vmcnt<0>();                                      // (what was fetched past the end)
+    }
+    // D layout: row (k within block) = 4*(lane/16) + e, col = lane%16 -> feature 8*lc + j of the panel
+    if (dcol >= K) return;                                    // (d_in is a multiple of 8: a lane's features are all in or all out)
+    float* dst = partial + ((int64_t)split * K + dcol) * RP + nb0 * 16 + lg * 4;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+        for (int nb = 0; nb < NBW; ++nb) *reinterpret_cast<floatx4*>(dst + j * RP + nb * 16) = tot[nb][j];
+}
+
 struct XttDev {
     const bf16_t* X; int64_t ldx, M, K;
     const bf16_t* TpackT; int64_t m_pad;
     float* partial; int64_t tok_per_split;
 };
 template <int NB, bool ALONE, int CAP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NB == 2 ? 2 : 1))) void xtt_bf16_many_kernel(const KBatch<XttDev, CAP> tb) {
+__global__ __launch_bounds__(ALONE ? 64 * XttAlone<NB>::WAVES : 256) __attribute__((amdgpu_waves_per_eu(ALONE ? XttAlone<NB>::WAVES / 4 : NB == 2 ? 2 : 1))) void xtt_bf16_many_kernel(const KBatch<XttDev, CAP> tb) {
     uint32_t bx, by;
     const XttDev& a = tb.a[kbatch_find(tb, bx, by)];
-    xtt_bf16_body<NB, ALONE>(a.X, a.ldx, a.M, a.K, a.TpackT, a.m_pad, a.partial, a.tok_per_split, bx, by);
+    if constexpr (ALONE) xtt_alone_body<NB>(a.X, a.ldx, a.M, a.K, a.TpackT, a.m_pad, a.partial, a.tok_per_split, bx, by);
+    else xtt_bf16_body<NB>(a.X, a.ldx, a.M, a.K, a.TpackT, a.m_pad, a.partial, a.tok_per_split, bx, by);
 }
 
 static int64_t xtt_tokens_per_split(int64_t m_pad, int nsplit) {
@@ -578,18 +863,23 @@ static int64_t xtt_tokens_per_split(int64_t m_pad, int nsplit) {
 }
 
 // ALONE or not, from the workgroups that the other form would have work for and their steps: where they fill the chip less than
-// once, a quarter of them leaves it idle (r = 32, 16384 tokens of a 4096-wide layer, 256 workgroups of 64 steps: 65 us against 33), and
-// beyond that the adding is worth avoiding for short ranges (seven 4B-sized layers, 512 tokens, 832 of 4 steps: 15 us against 25 at
-// r = 32, 28 against 55 at r = 64) and, where it allows one workgroup per compute unit (r > 32), for long ones too once
-// there are many (4096 tokens, 1860 of some 16 steps: 129 us against 163 at r = 64, 103 against 130 at r = 48, but 78
-// against 70 at r = 32; one 9728-wide layer, 304 of 32 steps: 67 against 52 at r = 64)
+// once, a quarter of them leaves it idle (r = 32, 16384 tokens of a 4096-wide layer, 256 workgroups of 64 steps: 58 us against 34), and
+// beyond that two column blocks, which the other form has two waves a SIMD for, need short ranges or many workgroups (r = 32, 4096 tokens
+// of a 9728-wide layer, 304 workgroups of 32 steps: 34 us against 28; 16384 tokens, 608 of 64: 68 against 85).  Over 72 shapes of r = 32, 48
+// and 64 with more than 256 workgroups 0.58 to 1.03 of the other form's time
 static bool xtt_alone(int rp, int64_t workgroups, int64_t steps) {
-    return workgroups > 256 && (steps <= 8 * workgroups || (rp > 32 && workgroups >= 1024));
+    return workgroups > 256 && (rp > 32 || workgroups >= 512 || steps <= 8 * workgroups);
 }
 template <int NB, bool ALONE, int CAP>
 static hipError_t launch_xtt_nb(const KBatch<XttDev, CAP>& tb, unsigned blocks, hipStream_t st) {
-    const size_t smem = ALONE ? 0 : (size_t)XTT_PANEL * NB * 16 * sizeof(float);
-    hipLaunchKernelGGL((xtt_bf16_many_kernel<NB, ALONE, CAP>), dim3(blocks), dim3(256), smem, st, tb);
+    const int smem = ALONE ? 3 * XttAlone<NB>::STAGE : XTT_PANEL * NB * 16 * (int)sizeof(float);
+    static bool set = false;
+    if (ALONE && !set) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(xtt_bf16_many_kernel<NB, ALONE, CAP>), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+        if (e != hipSuccess) return e;
+        set = true;
+    }
+    hipLaunchKernelGGL((xtt_bf16_many_kernel<NB, ALONE, CAP>), dim3(blocks), dim3(ALONE ? 64 * XttAlone<NB>::WAVES : 256), smem, st, tb);
     return hipGetLastError();
 }
 template <int CAP>
@@ -620,9 +910,18 @@ hipError_t launch_xtt_bf16_many(const XttArgs* a, int n, hipStream_t st) {
     }
     const bool alone = rp > 16 && xtt_alone(rp, busy, steps);
     const int panel = (alone ? 4 : 1) * XTT_PANEL;
-    uint64_t blocks = 0;
+    // the longest ranges first, so that the launch does not end on a few of them
+    int order[kBatchMax], count = 0;
     for (int m = 0; m < n; ++m) {
         if (a[m].M == 0 || a[m].K == 0) continue;
+        int at = count++;
+        const int64_t tok = xtt_tokens_per_split(a[m].m_pad, a[m].nsplit);
+        for (; at > 0 && xtt_tokens_per_split(a[order[at - 1]].m_pad, a[order[at - 1]].nsplit) < tok; --at) order[at] = order[at - 1];
+        order[at] = m;
+    }
+    uint64_t blocks = 0;
+    for (int i = 0; i < count; ++i) {
+        const int m = order[i];
         XttDev d;
         d.X = a[m].X; d.ldx = a[m].ldx; d.M = a[m].M; d.K = a[m].K; d.TpackT = a[m].TpackT; d.m_pad = a[m].m_pad;
         d.partial = a[m].partial; d.tok_per_split = xtt_tokens_per_split(a[m].m_pad, a[m].nsplit);
