@@ -34,6 +34,10 @@ struct agzo_ctx {
     int* flag;   // device int: deferred numeric failure
     uint32_t prof;      // mask of timed kernel classes (bit = AGZO_PROF_* value)
     ProfClass pc[AGZO_PROF_KINDS];
+    // base forwards of a set of layers run on a stream of the context's own beside the extraction (step_many_body)
+    hipStream_t side;
+    hipEvent_t fork, join;
+    bool beside;           // forwards on `side` may hold half of every compute unit: launches on `stream` should fit the other half
     // clock telemetry: kClkSlots records of four 64-bit words (one per timed GEMM launch), then the probe's record
     unsigned long long* clk;
     size_t clk_used;
@@ -246,6 +250,33 @@ int check_loss(agzo_ctx* ctx, const agzo_layer* L, const agzo_loss_spec* loss, c
         return fail(ctx, AGZO_EINVAL, "target dtype %d", loss->target_dtype);
     return 0;
 }
+
+// Work on `side` between what is on the context's stream when it is opened and what comes there after close(), which also every
+// return in between makes wait: to the caller all of it is work on the context's stream
+struct Beside {
+    agzo_ctx* ctx;
+    bool open = false;
+    explicit Beside(agzo_ctx* c) : ctx(c) {}
+    template <typename F>
+    int run(F launches) {
+        HIPCHK(hipEventRecord(ctx->fork, ctx->stream));
+        HIPCHK(hipStreamWaitEvent(ctx->side, ctx->fork, 0));
+        open = ctx->beside = true;
+        const hipError_t e = launches(ctx->side);
+        HIPCHK(hipEventRecord(ctx->join, ctx->side));
+        HIPCHK(e);
+        return 0;
+    }
+    int close() {
+        if (!open) return 0;
+        open = ctx->beside = false;
+        HIPCHK(hipStreamWaitEvent(ctx->stream, ctx->join, 0));
+        return 0;
+    }
+    ~Beside() {
+        if (open) (void)close();
+    }
+};
 
 // ---- internal building blocks; all take a ready workspace plan --------------------------------
 inline float* wsf(agzo_ctx* c, size_t off) { return reinterpret_cast<float*>(c->ws + off); }
@@ -516,7 +547,7 @@ int stage_sketch_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, const in
                           nullptr, wsh(ctx, j.p.off_TpackT), j.p.m_pad, wsf(ctx, j.p.off_xqpart)};
         }
         ProfScope ps(ctx, AGZO_PROF_XQ);
-        HIPCHK(launch_xq_bf16_many(q, n, st));
+        HIPCHK(launch_xq_bf16_many(q, n, ctx->beside, st));
     }
     XttArgs t[kBatchMax];
     for (int i = 0; i < n; ++i) {
@@ -611,7 +642,7 @@ int project_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs) {
             done[b] = 1;
         }
         ProfScope ps(ctx, AGZO_PROF_XQ);
-        HIPCHK(launch_xq_bf16_many(q, n, ctx->stream));
+        HIPCHK(launch_xq_bf16_many(q, n, ctx->beside, ctx->stream));
     }
     return 0;
 }
@@ -672,6 +703,9 @@ int agzo_create(agzo_ctx** out, void* hip_stream) {
     ctx->prof = 0;
     ctx->clk = nullptr;
     ctx->clk_used = 0;
+    ctx->side = nullptr;
+    ctx->fork = ctx->join = nullptr;
+    ctx->beside = false;
     ctx->device = -1;
     ctx->static_scratch = nullptr;
     hipError_t e = hipGetDevice(&ctx->device);
@@ -680,9 +714,15 @@ int agzo_create(agzo_ctx** out, void* hip_stream) {
     if (e == hipSuccess) e = hipMemset(ctx->flag, 0, 256);
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&ctx->clk), kClkBytes);
     if (e == hipSuccess) e = hipMemset(ctx->clk, 0, kClkBytes);
+    // (non-blocking: the context's stream may be the default stream, which others would otherwise wait for)
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->fork, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->join, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking);
     if (e != hipSuccess) {
         if (ctx->flag) (void)hipFree(ctx->flag);
         if (ctx->clk) (void)hipFree(ctx->clk);
+        if (ctx->fork) (void)hipEventDestroy(ctx->fork);
+        if (ctx->join) (void)hipEventDestroy(ctx->join);
         delete ctx;
         return AGZO_EHIP;
     }
@@ -692,7 +732,10 @@ int agzo_create(agzo_ctx** out, void* hip_stream) {
 
 void agzo_destroy(agzo_ctx* ctx) {
     if (!ctx) return;
-    (void)hipStreamSynchronize(ctx->stream);
+    (void)hipStreamSynchronize(ctx->stream);      // (what ran on `side` has been waited for there)
+    if (ctx->side) (void)hipStreamDestroy(ctx->side);
+    if (ctx->fork) (void)hipEventDestroy(ctx->fork);
+    if (ctx->join) (void)hipEventDestroy(ctx->join);
     if (ctx->ws) (void)hipFree(ctx->ws);
     if (ctx->flag) (void)hipFree(ctx->flag);
     if (ctx->clk) (void)hipFree(ctx->clk);
@@ -1004,6 +1047,13 @@ int agzo_basis_many(agzo_ctx* ctx, const agzo_basis_item* items, int32_t n, int3
 }
 
 namespace {
+// The base forwards need nothing of the extraction nor it of them, and the extraction is a chain of some twenty launches that are bound by
+// latency or by memory: for a set of layers they run beside it, those in 128 x 128 tiles on half of every compute unit.  The two streams
+// wait for each other twice, some 20 us.  Measured (us a step, one stream and two): seven layers 0.6B-sized on 512 tokens (16 GFLOP) 233
+// and 233, on 1024 299 and 290, on 2048 428 and 416, 4B-sized on 128 383 and 360, on 512 617 and 570, on 3001 2075 and 1935; four
+// of them on 512 272 and 265, on 4096 790 and 750; two on 4096 444 and 452; one 4096 x 4096 layer on 1024 tokens 232 and 249
+constexpr int kBesideLayers = 4;
+constexpr double kBesideFlops = 20e9;
 // Alg. 2 for n single-layer problems (agzo_step_many; agzo_step is the same with n = 1, so that their results agree bit for
 // bit).  Squared-error layers run every stage together: the evaluations of part 1 (f0, or all three in the shared schedule) and
 // of part 2 (f+ and f-) go to the launch functions as one list, and one launch finishes every loss and scalar.  Cross-entropy
@@ -1031,6 +1081,7 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
     TRY(reserve(ctx, total + upd_bytes));
     for (int m = 0; m < n; ++m) jobs[(size_t)m].B = items[m].B_out ? items[m].B_out : wsf(ctx, jobs[(size_t)m].p.off_B);
     hipStream_t st = ctx->stream;
+    Beside beside(ctx);
 
     // the squared-error evaluations of phases [ph0, ph1): 0 = f0 (or, shared, all three from one pass), 1 = f+, 2 = f-; the
     // loss partials of phase ph go to slot ph of the layer's region
@@ -1039,6 +1090,7 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
         std::vector<F32FwdArgs> f32;
         std::vector<GemmExtArgs> ext;
         const bool perturbed = shared || ph0 > 0;
+        double flops = 0.0;
         for (int m = 0; m < n; ++m) {
             const agzo_step_item& it = items[m];
             if (it.loss.kind != AGZO_LOSS_MSE) continue;
@@ -1058,6 +1110,7 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
                 } else {
                     bf.push_back(forward_bf16_args(ctx, j.L, j.p, it.W, it.X, P, e, it.seed, nullptr, la, shared));
                     bf.back().ext_ready = pair;
+                    flops += 2.0 * (double)j.L.n_tokens * (double)j.L.d_in * (double)j.L.d_out;
                     bf.back().ext_side = ph == 2 ? 1 : 0;
                 }
             }
@@ -1065,10 +1118,12 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
         for (size_t b = 0; b < f32.size(); b += kBatchMax)
             HIPCHK(launch_forward_f32_many(f32.data() + b, (int)std::min(f32.size() - b, (size_t)kBatchMax), st));
         if (bf.empty()) return 0;
+        if (ph1 == 1 && !shared && ctx->prof == 0 && ctx->side && n >= kBesideLayers && flops >= kBesideFlops)
+            return beside.run([&](hipStream_t side) { return launch_gemm_bf16_many(bf.data(), (int)bf.size(), true, side); });
         for (size_t b = 0; b < ext.size(); b += kBatchMax)
             HIPCHK(launch_gemm_ext_prep_many(ext.data() + b, (int)std::min(ext.size() - b, (size_t)kBatchMax), st));
         if (!timed(ctx, AGZO_PROF_GEMM)) {
-            HIPCHK(launch_gemm_bf16_many(bf.data(), (int)bf.size(), st));
+            HIPCHK(launch_gemm_bf16_many(bf.data(), (int)bf.size(), false, st));
             return 0;
         }
         for (const GemmBf16Args& a : bf) {      // timed: a launch of its own for every forward (the results are the same)
@@ -1102,6 +1157,7 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
             if (!one_sided) TRY(forward_ce(m, P, -eps, items[m].out_dev + 2, false, 2));
         }
     }
+    TRY(beside.close());
     // the scalars, then every update in one batched call
     std::vector<agzo_update_item> upd;
     std::vector<FinishTwoPointArgs> fin;

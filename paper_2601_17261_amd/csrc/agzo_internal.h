@@ -182,7 +182,8 @@ inline int gemm_bf16_sketch_splits(int64_t M) { return (int)((M + 127) / 128); }
 hipError_t launch_gemm_bf16(const GemmBf16Args& a, hipStream_t st);
 // several independent forwards: the squared errors that the kernel of gemm_bf16_mid.hip takes share launches, the others run one by
 // one.  Every result has the bits of a launch of its own.  Workspaces (ext_ws unless ext_ready, loss partials) must not overlap.
-hipError_t launch_gemm_bf16_many(const GemmBf16Args* a, int n, hipStream_t st);
+// half_cu: those that share launches leave half of every compute unit to what runs on other streams
+hipError_t launch_gemm_bf16_many(const GemmBf16Args* a, int n, bool half_cu, hipStream_t st);
 // extension operands of several layers in one launch: the W side times coef and, with two = true, once more times coef2
 // P = NULL: without the X side (launch_xq_bf16 writes it).  planes != NULL: also the bf16 planes [3][rp][d] of B fp32 [d][r]
 struct GemmExtArgs {
@@ -227,8 +228,9 @@ struct XqArgs {
     const bf16_t* X; int64_t ldx, M, K; const bf16_t* Qpack; int r, rp; float* T; bf16_t* TpackT; int64_t m_pad; float* part;
     bf16_t* Xext = nullptr;
 };
-// up to kBatchMax products with the same rp in one launch (plus one finishing launch if any of them splits d_in)
-hipError_t launch_xq_bf16_many(const XqArgs* a, int n, hipStream_t st);
+// up to kBatchMax products with the same rp in one launch (plus one finishing launch if any of them splits d_in); m_pad is a multiple of 4
+// half_cu: forwards on another stream hold half of every compute unit
+hipError_t launch_xq_bf16_many(const XqArgs* a, int n, bool half_cu, hipStream_t st);
 int xtt_num_splits(int64_t M, int64_t K);
 // partial[s][d][rp] = sum over token range s of X[t][d] * T[t][k]
 hipError_t launch_xtt_bf16(const bf16_t* X, int64_t ldx, int64_t M, int64_t K, const bf16_t* TpackT, int64_t m_pad,

@@ -772,7 +772,7 @@ hipError_t choose(const GemmBf16Args& a, Choice& c) {
 hipError_t launch_one(const Choice& c, hipStream_t st) {
     const GemmParams& p = c.p;
     switch (c.kernel) {
-        case Kernel::mid: return launch_gemm_bf16_mid(&c.g, 1, c.out, p.target_dtype != AGZO_BF16, st);
+        case Kernel::mid: return launch_gemm_bf16_mid(&c.g, 1, c.out, p.target_dtype != AGZO_BF16, false, st);
         case Kernel::small: return launch_gemm_bf16_small(p, st);
         case Kernel::aligned: return launch_gemm_bf16_aligned(p, st);
         case Kernel::general: break;
@@ -783,7 +783,7 @@ hipError_t launch_one(const Choice& c, hipStream_t st) {
 }
 }  // namespace
 
-hipError_t launch_gemm_bf16_many(const GemmBf16Args* a, int n, hipStream_t st) {
+hipError_t launch_gemm_bf16_many(const GemmBf16Args* a, int n, bool half_cu, hipStream_t st) {
     Choice c[kBatchMax];
     for (int b = 0; b < n; b += kBatchMax) {
         const int nb = n - b < kBatchMax ? n - b : kBatchMax;
@@ -807,7 +807,7 @@ hipError_t launch_gemm_bf16_many(const GemmBf16Args* a, int n, hipStream_t st) {
             for (int i = 0; i < nb; ++i)
                 if (shared_launch(i) && (c[i].p.target_dtype != AGZO_BF16) == (f32 != 0)) g[ng++] = c[i].g;
             if (ng == 0) continue;
-            e = launch_gemm_bf16_mid(g, ng, 0, f32 != 0, st);
+            e = launch_gemm_bf16_mid(g, ng, 0, f32 != 0, half_cu, st);
             if (e != hipSuccess) return e;
         }
         // the shared schedule's tiles together
@@ -827,6 +827,6 @@ hipError_t launch_gemm_bf16_many(const GemmBf16Args* a, int n, hipStream_t st) {
     return hipSuccess;
 }
 
-hipError_t launch_gemm_bf16(const GemmBf16Args& a, hipStream_t st) { return launch_gemm_bf16_many(&a, 1, st); }
+hipError_t launch_gemm_bf16(const GemmBf16Args& a, hipStream_t st) { return launch_gemm_bf16_many(&a, 1, false, st); }
 
 }  // namespace agzo

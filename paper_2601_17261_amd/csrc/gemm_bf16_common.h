@@ -87,7 +87,8 @@ struct GemmItem {
 int gemm_bf16_mid_splits(int64_t M, int64_t N, int64_t K);
 // out 0: squared error (target_f32: of fp32 targets), 1: stored bf16 output (one problem a launch)
 bool gemm_bf16_mid_ok(const GemmItem& g, int out);
-hipError_t launch_gemm_bf16_mid(const GemmItem* a, int n, int out, bool target_f32, hipStream_t st);
+// half_cu (out 0): at most one workgroup to a compute unit, and 72 KiB of its LDS left
+hipError_t launch_gemm_bf16_mid(const GemmItem* a, int n, int out, bool target_f32, bool half_cu, hipStream_t st);
 
 // persistent kernel in 256 x 256 tiles (gemm_bf16_aligned.hip): M, N >= 256, d_in >= 128, the rank-r term as prepared operands;
 // either the squared-error loss without a stored Y, the cross-entropy statistics without a stored Y, or a bf16 Y without a loss

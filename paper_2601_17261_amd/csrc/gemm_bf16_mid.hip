@@ -393,26 +393,30 @@ size_t gemm_bf16_split_bytes(int64_t M, int64_t N, int64_t K) {
     return s > 1 ? (size_t)s * ((M + MT - 1) / MT) * ((N + MT - 1) / MT) * MT * MT * sizeof(float) : 0;
 }
 
+// pad: LDS asked for beyond what the kernel uses, which keeps a second workgroup off the compute unit
+constexpr int MID_HALF_CU = 8 * 1024;
 template <int OUT, bool T_F32, bool SK, bool DEEP, int CAP>
-static hipError_t launch_mid_ring(const KBatch<GemmItem, CAP>& tb, unsigned blocks, hipStream_t st) {
+static hipError_t launch_mid_ring(const KBatch<GemmItem, CAP>& tb, unsigned blocks, hipStream_t st, int pad = 0) {
     constexpr int smem = (mid_w_stages(SK, DEEP) + mid_x_stages(SK, DEEP)) * MTILE_BYTES + (SK ? MSK_SMEM : 0);
     static_assert(smem <= (DEEP ? 160 : 80) * 1024, "workgroups per compute unit");
     static bool attr_set = false;
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_bf16_mid_kernel<OUT, T_F32, SK, DEEP, CAP>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, smem + (DEEP ? 0 : MID_HALF_CU));
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    hipLaunchKernelGGL((gemm_bf16_mid_kernel<OUT, T_F32, SK, DEEP, CAP>), dim3(blocks), dim3(256), smem, st, tb);
+    hipLaunchKernelGGL((gemm_bf16_mid_kernel<OUT, T_F32, SK, DEEP, CAP>), dim3(blocks), dim3(256), smem + pad, st, tb);
     return hipGetLastError();
 }
 template <int OUT, bool T_F32>
-static hipError_t launch_mid_variant(const KBatch<GemmItem>& tb, unsigned blocks, bool sk, hipStream_t st) {
+static hipError_t launch_mid_variant(const KBatch<GemmItem>& tb, unsigned blocks, bool sk, bool half_cu, hipStream_t st) {
     // (256: a workgroup per compute unit)
     if (sk) return blocks <= 256 ? launch_mid_ring<OUT, T_F32, true, true>(kbatch_one(tb), blocks, st) : launch_mid_ring<OUT, T_F32, true, false>(kbatch_one(tb), blocks, st);
-    if constexpr (OUT == 0)
+    if constexpr (OUT == 0) {
+        if (half_cu) return launch_mid_ring<OUT, T_F32, false, false>(tb, blocks, st, MID_HALF_CU);
         if (tb.n > 1) return blocks <= 256 ? launch_mid_ring<OUT, T_F32, false, true>(tb, blocks, st) : launch_mid_ring<OUT, T_F32, false, false>(tb, blocks, st);
+    }
     return blocks <= 256 ? launch_mid_ring<OUT, T_F32, false, true>(kbatch_one(tb), blocks, st) : launch_mid_ring<OUT, T_F32, false, false>(kbatch_one(tb), blocks, st);
 }
 
@@ -420,8 +424,8 @@ bool gemm_bf16_mid_ok(const GemmItem& g, int out) {
     return g.M >= MT && g.N >= MT && g.K >= 2 * BK && (out == 1 ? g.Y != nullptr : g.target != nullptr);
 }
 
-hipError_t launch_gemm_bf16_mid(const GemmItem* a, int n, int out, bool target_f32, hipStream_t st) {
-    if (n < 0 || n > (out == 1 ? 1 : kBatchMax)) return hipErrorInvalidValue;
+hipError_t launch_gemm_bf16_mid(const GemmItem* a, int n, int out, bool target_f32, bool half_cu, hipStream_t st) {
+    if ((half_cu && out != 0) || n < 0 || n > (out == 1 ? 1 : kBatchMax)) return hipErrorInvalidValue;
     KBatch<GemmItem> tb;
     tb.n = 0;
     uint64_t blocks = 0;
@@ -458,8 +462,8 @@ hipError_t launch_gemm_bf16_mid(const GemmItem* a, int n, int out, bool target_f
     }
     if (tb.n == 0) return hipSuccess;
     if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    if (out == 1) return launch_mid_variant<1, false>(tb, (unsigned)blocks, sk, st);
-    return target_f32 ? launch_mid_variant<0, true>(tb, (unsigned)blocks, sk, st) : launch_mid_variant<0, false>(tb, (unsigned)blocks, sk, st);
+    if (out == 1) return launch_mid_variant<1, false>(tb, (unsigned)blocks, sk, false, st);
+    return target_f32 ? launch_mid_variant<0, true>(tb, (unsigned)blocks, sk, half_cu, st) : launch_mid_variant<0, false>(tb, (unsigned)blocks, sk, half_cu, st);
 }
 
 }  // namespace agzo

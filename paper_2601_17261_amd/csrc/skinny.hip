@@ -90,18 +90,18 @@ __device__ __forceinline__ void xq_store(const floatx4 (&acc)[MB][NB], int64_t M
 }
 
 // bx: token block, by / ny: this workgroup's share of d_in (ny = 1: all of it)
-// ring depth: DEEP = one workgroup per CU with as many slices in flight as LDS holds; otherwise a shallower ring that
+// ring depth: DEEP = 1, one workgroup per CU with as many slices in flight as LDS holds; 0, a shallower ring that
 // lets two workgroups share a CU, for launches with at least two workgroups per CU (several layers at once): while one
-// waits at its barrier or on its fragment reads the other multiplies
-template <int NB, bool DEEP>
-struct XqRing { static constexpr int STAGES = DEEP ? (NB == 1 ? 8 : 6) : (NB == 1 ? 5 : 3); };
+// waits at its barrier or on its fragment reads the other multiplies; 2, what a workgroup of the forwards leaves of the LDS
+template <int NB, int DEEP>
+struct XqRing { static constexpr int STAGES = DEEP == 1 ? (NB == 1 ? 8 : 6) : NB == 2 ? 3 : DEEP == 2 ? 4 : 5; };
 
 // a slot holds the rows of a slice and, where four waves do not share their groups evenly, groups that nobody reads: every wave
 // then issues the same number of loads and waits by constants (a wait chosen among a dozen cases and a branch around each load
 // cost more than the slice's matrix work)
 constexpr int xq_slot_bytes(int nb) { return (XQ_TOK / 8 + 6 * nb + 3) / 4 * 4096; }
 
-template <int NB, bool DEEP>
+template <int NB, int DEEP>
 __device__ __forceinline__ void xq_bf16_body(const bf16_t* __restrict__ X, int64_t ldx, int64_t M, int64_t K,
                                              const bf16_t* __restrict__ Qpack, int r, float* __restrict__ T,
                                              bf16_t* __restrict__ TpackT, int64_t m_pad, float* __restrict__ part,
@@ -407,7 +407,7 @@ struct XqDev {
     int ns;
     bf16_t* Xext;
 };
-template <int NB, bool DEEP, int CAP>
+template <int NB, int DEEP, int CAP>
 __global__ __launch_bounds__(256) void xq_bf16_many_kernel(const KBatch<XqDev, CAP> tb) {
     uint32_t bx, by;
     const XqDev& a = tb.a[kbatch_find(tb, bx, by)];
@@ -483,7 +483,7 @@ size_t xq_part_bytes(int64_t M, int64_t K, int rp) {
     return ns > 1 ? (size_t)ns * m_pad * rp * sizeof(float) : 0;
 }
 
-template <int NB, bool DEEP, int CAP>
+template <int NB, int DEEP, int CAP>
 static hipError_t launch_xq_ring(const KBatch<XqDev, CAP>& tb, unsigned blocks, hipStream_t st) {
     const int smem = XqRing<NB, DEEP>::STAGES * xq_slot_bytes(NB);
     static bool set = false;
@@ -509,23 +509,24 @@ static hipError_t launch_xq_direct(const KBatch<XqDev, CAP>& tb, unsigned blocks
 }
 // (the result depends neither on the ring's depth nor on the tokens of a workgroup: same slices, same order)
 template <int NB, int CAP>
-static hipError_t launch_xq_many_nb(const KBatch<XqDev, CAP>& tb, unsigned blocks, int mb, hipStream_t st) {
+static hipError_t launch_xq_many_nb(const KBatch<XqDev, CAP>& tb, unsigned blocks, int mb, bool half_cu, hipStream_t st) {
     if constexpr (NB >= 3) return mb == 2 ? launch_xq_direct<NB, 2>(tb, blocks, st) : launch_xq_direct<NB, 1>(tb, blocks, st);
-    else return blocks >= 512 ? launch_xq_ring<NB, false>(tb, blocks, st) : launch_xq_ring<NB, true>(tb, blocks, st);
+    else if (half_cu) return launch_xq_ring<NB, 2>(tb, blocks, st);
+    else return blocks >= 512 ? launch_xq_ring<NB, 0>(tb, blocks, st) : launch_xq_ring<NB, 1>(tb, blocks, st);
 }
 
 template <int CAP>
-static hipError_t launch_xq_cap(const KBatch<XqDev, CAP>& tb, unsigned blocks, int rp, int mb, hipStream_t st) {
+static hipError_t launch_xq_cap(const KBatch<XqDev, CAP>& tb, unsigned blocks, int rp, int mb, bool half_cu, hipStream_t st) {
     switch (rp / 16) {
-        case 1: return launch_xq_many_nb<1>(tb, blocks, mb, st);
-        case 2: return launch_xq_many_nb<2>(tb, blocks, mb, st);
-        case 3: return launch_xq_many_nb<3>(tb, blocks, mb, st);
-        case 4: return launch_xq_many_nb<4>(tb, blocks, mb, st);
+        case 1: return launch_xq_many_nb<1>(tb, blocks, mb, half_cu, st);
+        case 2: return launch_xq_many_nb<2>(tb, blocks, mb, half_cu, st);
+        case 3: return launch_xq_many_nb<3>(tb, blocks, mb, half_cu, st);
+        case 4: return launch_xq_many_nb<4>(tb, blocks, mb, half_cu, st);
         default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_xq_bf16_many(const XqArgs* a, int n, hipStream_t st) {
+hipError_t launch_xq_bf16_many(const XqArgs* a, int n, bool half_cu, hipStream_t st) {
     if (n < 0 || n > kBatchMax) return hipErrorInvalidValue;
     int rp = 0;
     uint64_t half = 0;                         // workgroups of 128 tokens
@@ -565,7 +566,7 @@ hipError_t launch_xq_bf16_many(const XqArgs* a, int n, hipStream_t st) {
         }
     }
     if (blocks > 0x7FFFFFFFull || fin_blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    hipError_t e = tb.n == 1 ? launch_xq_cap(kbatch_one(tb), (unsigned)blocks, rp, mb, st) : launch_xq_cap(tb, (unsigned)blocks, rp, mb, st);
+    hipError_t e = tb.n == 1 ? launch_xq_cap(kbatch_one(tb), (unsigned)blocks, rp, mb, half_cu, st) : launch_xq_cap(tb, (unsigned)blocks, rp, mb, half_cu, st);
     if (e != hipSuccess || fin.n == 0) return e;
     const dim3 fin_grid((unsigned)fin_blocks);
     if (fin.n == 1) hipLaunchKernelGGL(xq_finish_many_kernel<1>, fin_grid, dim3(256), 0, st, kbatch_one(fin), rp);
@@ -576,7 +577,7 @@ hipError_t launch_xq_bf16_many(const XqArgs* a, int n, hipStream_t st) {
 hipError_t launch_xq_bf16(const bf16_t* X, int64_t ldx, int64_t M, int64_t K, const bf16_t* Qpack, int r, int rp,
                           float* T, bf16_t* TpackT, int64_t m_pad, float* part, bf16_t* Xext, hipStream_t st) {
     const XqArgs a{X, ldx, M, K, Qpack, r, rp, T, TpackT, m_pad, part, Xext};
-    return launch_xq_bf16_many(&a, 1, st);
+    return launch_xq_bf16_many(&a, 1, false, st);
 }
 
 // ---------------------------------------------------------------------------

@@ -1,0 +1,87 @@
+"""Sets of layers large enough for their base forwards to run on the context's second stream: to the caller all of it is work on the
+context's stream (inputs written there just before, weights and inputs overwritten just after), the results are those of a call per
+layer, bit for bit, and a captured step replays."""
+import pytest
+import torch
+
+from paper_2601_17261_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+EPS, LR = 1e-3, 1e-3
+# d_in, d_out of five layers: 24 GFLOP a forward on 900 tokens (no tile divides them), squared errors in both tilings
+SHAPES = [(1024, 2048), (1536, 1024), (1024, 1024), (512, 3072), (2048, 2560)]
+
+
+def _inputs(n, seed):
+    X = [synth.device_powerlaw_x(seed + i, n, d_in) for i, (d_in, _) in enumerate(SHAPES)]
+    return [(x,) + synth.device_weights_and_target(seed + 50 + i, x, d_out) for i, (x, (_, d_out)) in enumerate(zip(X, SHAPES))]
+
+
+def _items(layers, out, r):
+    return [(binding.make_layer(w, x, r), w, x, binding.make_loss(t), 30 + i, out[i], None) for i, (x, w, t) in enumerate(layers)]
+
+
+@pytest.mark.parametrize("flags", [0, binding.ONE_SIDED])
+@pytest.mark.parametrize("n,r", [(900, 1), (900, 8), (2600, 40)])
+def test_same_as_a_call_per_layer(n, r, flags):
+    stream = torch.cuda.Stream()
+    ctx = binding.Context(stream=stream)
+    given = _inputs(n, 3)
+    assert sum(2 * n * i * o for i, o in SHAPES) > 20e9
+    want, out1 = [], torch.zeros(len(given), 4, dtype=torch.float64, device="cuda")
+    out = torch.zeros_like(out1)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        for i, (x, w, t) in enumerate(given):
+            w = w.clone()
+            ctx.step(binding.make_layer(w, x, r), w, x, binding.make_loss(t), 3, EPS, LR, 30 + i, flags, out1[i])
+            want.append(w)
+        layers = [tuple(torch.full_like(a, float("nan")) for a in one) for one in given]
+        for k in range(3):
+            for one, src in zip(layers, given):          # written on the stream, right before
+                for a, s in zip(one, src):
+                    a.copy_(s)
+            ctx.step_many(_items(layers, out, r), 3, EPS, LR, flags)
+            got = [w.clone() for _, w, _ in layers]
+            for one in layers:                           # and overwritten right after
+                for a in one:
+                    a.fill_(float("nan"))
+            stream.synchronize()
+            assert torch.equal(out, out1), k
+            assert all(torch.equal(a, b) for a, b in zip(got, want)), k
+    ctx.check()
+    ctx.close()
+
+
+def test_captured():
+    r, stream = 8, torch.cuda.Stream()
+    ctx = binding.Context(stream=stream)
+    layers = _inputs(900, 9)
+    w0 = [w.clone() for _, w, _ in layers]
+    out = torch.zeros(len(layers), 4, dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
+    ref = []
+    with torch.cuda.stream(stream):
+        for _ in range(3):
+            ctx.step_many(_items(layers, out, r), 3, EPS, LR, 0)
+            stream.synchronize()
+            ref.append(([w.clone() for _, w, _ in layers], out.clone()))
+        for (_, w, _), s in zip(layers, w0):
+            w.copy_(s)
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            ctx.step_many(_items(layers, out, r), 3, EPS, LR, 0)
+    torch.cuda.synchronize()
+    assert all(torch.equal(w, s) for (_, w, _), s in zip(layers, w0))
+    for k in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref[k][1]), k
+        assert all(torch.equal(w, s) for (_, w, _), s in zip(layers, ref[k][0])), k
+        scratch = torch.empty(1 << 20, device="cuda").normal_()
+        assert torch.isfinite(scratch.sum()).item()
+    with torch.cuda.stream(stream):
+        ctx.step_many(_items(layers, out, r), 3, EPS, LR, 0)      # the context's own streams are as before
+        ctx.check()
+    ctx.close()
