@@ -585,24 +585,21 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const KBatch<Ali
             // cskip: how many of the lane's 16 columns per group those are
             const int cs = RAGGED ? (int)(tn * BT - n0) : 0;
             const int cskip[2] = {cs - (wa * 128 + lg * 16), cs - (wa * 128 + 64 + lg * 16)};
-#pragma clang loop unroll(full)
-            for (int J = 0; J < 8; ++J) {
+            // one token block; SKIP: some of the wave's columns may have been counted
+            auto statistics = [&](int J, auto SKIP) __attribute__((always_inline)) {
+                constexpr bool skip = decltype(SKIP)::value != 0;
                 const int64_t row = m0 + wb * 128 + J * 16 + lc;
                 const int tgt = p.ce_target[row];
-                float mx = -INFINITY, tl = 0.f;
-                bool has_tl = false;
+                float mx = -INFINITY;
 #pragma clang loop unroll(full)
-                for (int i4 = 0; i4 < 2; ++i4) {
-                    const int trel = (tgt >= 0) ? (int)((int64_t)tgt - (n0 + wa * 128 + i4 * 64 + lg * 16)) : -1;
+                for (int i4 = 0; i4 < 2; ++i4)
 #pragma clang loop unroll(full)
                     for (int t = 0; t < 4; ++t)
 #pragma clang loop unroll(full)
                         for (int e = 0; e < 4; ++e) {
                             const float y = from_acc(acc[i4 * 4 + t][J][e]);
-                            if (!RAGGED || 4 * t + e >= cskip[i4]) mx = fmaxf(mx, y);
-                            if (4 * t + e == trel) { tl = y; has_tl = true; }
+                            if (!skip || 4 * t + e >= cskip[i4]) mx = fmaxf(mx, y);
                         }
-                }
                 mx = fmaxf(mx, __shfl_xor(mx, 16));
                 mx = fmaxf(mx, __shfl_xor(mx, 32));
                 // exp(y - mx) as 2^((y - mx) log2 e) on the hardware exponential: the difference is exact enough in fp32
@@ -613,14 +610,38 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const KBatch<Ali
 #pragma clang loop unroll(full)
                     for (int e = 0; e < 4; ++e) {
                         const float ex = __builtin_amdgcn_exp2f((from_acc(acc[I][J][e]) - mx) * 1.44269504088896341f);
-                        sm += (!RAGGED || (I & 3) * 4 + e >= cskip[I >> 2]) ? ex : 0.f;
+                        sm += (!skip || (I & 3) * 4 + e >= cskip[I >> 2]) ? ex : 0.f;
                     }
                 sm += __shfl_xor(sm, 16);
                 sm += __shfl_xor(sm, 32);
                 const int64_t chunk = tn * 2 + wa;           // of tiles_n x 2 chunks per token
                 if (lg == 0) p.ce_ms[chunk * p.M + row] = make_float2(mx, sm);
-                if (has_tl) p.ce_tl[row] = tl;
-            }
+                // the target's logit: one token in d_out / 128 has its target among the wave's columns, so most waves have none in
+                // the block's sixteen, and nothing to look for (looked for along with the maximum it was two instructions a logit)
+                const int64_t trel = (int64_t)tgt - (n0 + wa * 128);
+                const bool mine = tgt >= 0 && trel >= 0 && trel < 128 && (((int)trel >> 4) & 3) == lg;
+                if (__builtin_amdgcn_ballot_w64(mine) != 0) {
+                    float tl = 0.f;
+                    const int at = (int)trel & 15, grp = (int)trel >> 6;
+#pragma clang loop unroll(full)
+                    for (int i4 = 0; i4 < 2; ++i4)
+#pragma clang loop unroll(full)
+                        for (int t = 0; t < 4; ++t)
+#pragma clang loop unroll(full)
+                            for (int e = 0; e < 4; ++e) {
+                                const float y = from_acc(acc[i4 * 4 + t][J][e]);
+                                if (grp == i4 && at == 4 * t + e) tl = y;
+                            }
+                    if (mine) p.ce_tl[row] = tl;
+                }
+            };
+            auto tile_statistics = [&](auto SKIP) __attribute__((always_inline)) {
+                statistics(0, SKIP); statistics(1, SKIP); statistics(2, SKIP); statistics(3, SKIP);
+                statistics(4, SKIP); statistics(5, SKIP); statistics(6, SKIP); statistics(7, SKIP);
+            };
+            // (only the last column tile overlaps the one before it)
+            if (RAGGED && cs != 0) tile_statistics(IC<1>{});
+            else tile_statistics(IC<0>{});
             if (!more) break;
         } else if constexpr (PHASES == 1) {
             const int64_t tm_done = tm, tn_done = tn;
