@@ -23,9 +23,14 @@ template <int V> struct IC { static constexpr int value = V; };
 // conversions.  The vector-unit version it replaces (a 4 x 4 register tile per thread) converted eight values from LDS for
 // every 16 multiplications, loaded without a prefetch, and ran at 7 TFLOP/s.  The small tile is for few tokens: 1000 x 1024
 // outputs give one wave to each of the 1024 SIMDs.
+// Layers of fewer than F32_SMALL such tiles take 32 x 32 ones, four waves of 16 x 16, with four slices in flight: the work of a tile is a
+// quarter, and what bounds it is no longer the matrix rate of a few compute units but the latency of its loads (512 tokens,
+// 256 x 256: 32 workgroups and 17.6 us a forward, 128 and 7.6 us).  At 128 to 255 tiles a lone layer would gain 7 to 10 % of its step
+// too, but a set of such layers, which fills the chip anyway, loses 8 % (seven 0.6B-sized ones on 500 tokens).
 // ---------------------------------------------------------------------------
-constexpr int FT = 64;      // tile edge
+constexpr int F32_SMALL = 128;
 constexpr int FK = 32;      // slice of d_in: a tile row is 128 bytes in LDS
+static int f32_tile(int64_t M, int64_t N) { return ((M + 63) / 64) * ((N + 63) / 64) < F32_SMALL ? 32 : 64; }
 
 struct F32FwdDev {
     F32FwdArgs a;
@@ -37,8 +42,9 @@ __device__ __forceinline__ int f32_lds_off(int row, int c) { return row * 128 + 
 
 // (at least two waves per SIMD: the accumulators then stay in ordinary registers; with the whole file to itself the compiler moves
 // all of them to the accumulation half and back around every slice)
-template <bool VEC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void forward_f32_kernel(const KBatch<F32FwdDev> tb) {
+template <bool VEC, int FT, int CAP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void forward_f32_kernel(const KBatch<F32FwdDev, CAP> tb) {
+    constexpr int FB = FT / 32, AHEAD = FT == 64 ? 1 : 4;    // 16 x 16 blocks of a wave in either direction; slices in flight
     __shared__ __align__(16) char smem[2 * 2 * FT * FK * 4];
     __shared__ double red[4];
     uint32_t bx, by;
@@ -46,7 +52,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void f
     const F32FwdArgs& a = d.a;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lc = lane & 15, lg = lane >> 4;
-    const int wt = wave & 1, wo = wave >> 1;               // the wave's half of the tokens and of the outputs
+    const int wt = (wave & 1) * 16 * FB, wo = (wave >> 1) * 16 * FB;               // the wave's tokens and outputs
     // each XCD (workgroup id mod 8) takes a contiguous run of tiles, in bands of eight token tiles per output tile
     const int count = d.tiles_m * d.tiles_n, per = count / 8;
     int lin = (int)bx;
@@ -59,98 +65,121 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void f
     char* const Xs = smem;                                 // [2 buffers][FT][FK]
     char* const Ws = smem + 2 * FT * FK * 4;
 
-    doublex4 acc[2][2];
+    doublex4 acc[FB][FB];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < FB; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
+        for (int j = 0; j < FB; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
 
-    // staging: two 16-byte chunks per thread and operand.  Rows past the end repeat the last one (they only feed outputs that
+    // staging: a 16-byte chunk per thread, operand and 32 rows.  Rows past the end repeat the last one (they only feed outputs that
     // the epilogue masks), columns past d_in are zero
-    const int ch = tid & 7, r0 = tid >> 3;                 // rows r0 and r0 + 32
-    const float *xr[2], *wr[2];
+    const int ch = tid & 7, r0 = tid >> 3;                 // rows r0 (and r0 + 32)
+    const float *xr[FB], *wr[FB];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < FB; ++i) {
         xr[i] = a.X + min(m0 + r0 + 32 * i, a.M - 1) * a.ldx;
         wr[i] = a.W + min(n0 + r0 + 32 * i, a.N - 1) * a.ldw;
     }
-    float4 rx[2], rw[2];
-    // MASK: the slice may reach past d_in
+    float4 rx[AHEAD][FB], rw[AHEAD][FB];
+    // MASK: the slice may reach past d_in (with several slices in flight its end is loaded instead and left out: around a lane's
+    // condition the compiler waits for each load before the next)
     auto load4 = [&](const float* p, int64_t k, auto MASK) __attribute__((always_inline)) -> float4 {
         constexpr bool mask = decltype(MASK)::value != 0;
         if constexpr (VEC) {
             if constexpr (!mask) return *reinterpret_cast<const float4*>(p + k);
-            return (k < a.K) ? *reinterpret_cast<const float4*>(p + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+            if constexpr (AHEAD == 1) return (k < a.K) ? *reinterpret_cast<const float4*>(p + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+            const float4 v = *reinterpret_cast<const float4*>(p + min(k, a.K - 4));
+            return (k < a.K) ? v : make_float4(0.f, 0.f, 0.f, 0.f);
         } else {
             float v[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = (!mask || k + e < a.K) ? p[k + e] : 0.f;
+            for (int e = 0; e < 4; ++e) v[e] = (AHEAD > 1 || !mask || k + e < a.K) ? p[AHEAD > 1 ? min(k + e, a.K - 1) : k + e] : 0.f;
+            if constexpr (AHEAD > 1) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = k + e < a.K ? v[e] : 0.f;
+            }
             return make_float4(v[0], v[1], v[2], v[3]);
         }
     };
-    auto gload = [&](int64_t k0, auto MASK) __attribute__((always_inline)) {
+    auto gload = [&](float4 (&x)[FB], float4 (&w)[FB], int64_t k0, auto MASK) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            rx[i] = load4(xr[i], k0 + ch * 4, MASK);
-            rw[i] = load4(wr[i], k0 + ch * 4, MASK);
+        for (int i = 0; i < FB; ++i) {
+            x[i] = load4(xr[i], k0 + ch * 4, MASK);
+            w[i] = load4(wr[i], k0 + ch * 4, MASK);
         }
     };
-    auto sstore = [&](int buf) {
+    auto sstore = [&](const float4 (&x)[FB], const float4 (&w)[FB], int buf) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < FB; ++i) {
             const int off = buf * FT * FK * 4 + f32_lds_off(r0 + 32 * i, ch);
-            *reinterpret_cast<float4*>(Xs + off) = rx[i];
-            *reinterpret_cast<float4*>(Ws + off) = rw[i];
+            *reinterpret_cast<float4*>(Xs + off) = x[i];
+            *reinterpret_cast<float4*>(Ws + off) = w[i];
         }
     };
     // scale: factor on the W side in fp64 (1 for the d_in slices)
     auto multiply = [&](int buf, double scale) {
 #pragma unroll
         for (int c = 0; c < FK / 16; ++c) {
-            float av[2][4], bv[2][4];
+            float av[FB][4], bv[FB][4];
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const float4 x = *reinterpret_cast<const float4*>(Xs + buf * FT * FK * 4 + f32_lds_off(wt * 32 + i * 16 + lc, 4 * c + lg));
-                const float4 w = *reinterpret_cast<const float4*>(Ws + buf * FT * FK * 4 + f32_lds_off(wo * 32 + i * 16 + lc, 4 * c + lg));
+            for (int i = 0; i < FB; ++i) {
+                const float4 x = *reinterpret_cast<const float4*>(Xs + buf * FT * FK * 4 + f32_lds_off(wt + i * 16 + lc, 4 * c + lg));
+                const float4 w = *reinterpret_cast<const float4*>(Ws + buf * FT * FK * 4 + f32_lds_off(wo + i * 16 + lc, 4 * c + lg));
                 av[i][0] = x.x; av[i][1] = x.y; av[i][2] = x.z; av[i][3] = x.w;
                 bv[i][0] = w.x; bv[i][1] = w.y; bv[i][2] = w.z; bv[i][3] = w.w;
             }
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
-                double ad[2], bd[2];
+                double ad[FB], bd[FB];
 #pragma unroll
-                for (int i = 0; i < 2; ++i) { ad[i] = (double)av[i][s]; bd[i] = (double)bv[i][s] * scale; }
+                for (int i = 0; i < FB; ++i) { ad[i] = (double)av[i][s]; bd[i] = (double)bv[i][s] * scale; }
 #pragma unroll
-                for (int i = 0; i < 2; ++i)
+                for (int i = 0; i < FB; ++i)
 #pragma unroll
-                    for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ad[i], bd[j], acc[i][j], 0, 0, 0);
+                    for (int j = 0; j < FB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ad[i], bd[j], acc[i][j], 0, 0, 0);
             }
         }
     };
     const int nfull = (int)(a.K / FK), nk = (int)((a.K + FK - 1) / FK);
-    gload(0, IC<1>{});
-    sstore(0);
-    __syncthreads();
-    int kt = 0;
-    for (; kt + 1 < nfull; ++kt) {
-        gload((int64_t)(kt + 1) * FK, IC<0>{});
-        multiply(kt & 1, 1.0);
-        sstore((kt + 1) & 1);
+    if constexpr (AHEAD == 1) {
+        gload(rx[0], rw[0], 0, IC<1>{});
+        sstore(rx[0], rw[0], 0);
         __syncthreads();
-    }
-    for (; kt < nk; ++kt) {                                // the last one or two slices
-        if (kt + 1 < nk) gload((int64_t)(kt + 1) * FK, IC<1>{});
-        multiply(kt & 1, 1.0);
-        if (kt + 1 < nk) sstore((kt + 1) & 1);
+        int kt = 0;
+        for (; kt + 1 < nfull; ++kt) {
+            gload(rx[0], rw[0], (int64_t)(kt + 1) * FK, IC<0>{});
+            multiply(kt & 1, 1.0);
+            sstore(rx[0], rw[0], (kt + 1) & 1);
+            __syncthreads();
+        }
+        for (; kt < nk; ++kt) {                            // the last one or two slices
+            if (kt + 1 < nk) gload(rx[0], rw[0], (int64_t)(kt + 1) * FK, IC<1>{});
+            multiply(kt & 1, 1.0);
+            if (kt + 1 < nk) sstore(rx[0], rw[0], (kt + 1) & 1);
+            __syncthreads();
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) gload(rx[i], rw[i], (int64_t)i * FK, IC<1>{});
+        for (int k0 = 0; k0 < nk; k0 += AHEAD)
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) {
+                if (k0 + i >= nk) break;
+                sstore(rx[i], rw[i], i & 1);
+                gload(rx[i], rw[i], (int64_t)(k0 + i + AHEAD) * FK, IC<1>{});
+                __syncthreads();                           // (the buffer was read two slices ago: everyone is past that)
+                multiply(i & 1, 1.0);
+            }
         __syncthreads();
     }
     // the rank-r term as more slices: P rows against G rows regenerated from the seed, eps applied in fp64
     auto rank_term = [&](double coef) {
         for (int k0 = 0; k0 < a.r; k0 += FK) {
-            const int row_t = tid >> 2;                    // 64 rows, four threads each
+            constexpr int TR = 256 / FT;                   // threads to a row of the tile
+            const int row_t = tid / TR;
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int c = (tid & 3) * 2 + i, k = k0 + 4 * c;
+            for (int i = 0; i < 8 / TR; ++i) {
+                const int c = (tid % TR) * (8 / TR) + i, k = k0 + 4 * c;
                 float4 pv = make_float4(0.f, 0.f, 0.f, 0.f), gv = pv;
                 if (k < a.r) {
                     const float* p = a.P + min(m0 + row_t, a.M - 1) * a.r;
@@ -174,27 +203,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void f
     auto evaluate = [&](int phase) {
         double part = 0.0;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < FB; ++i) {
             // eight targets requested before the first is used; rows and columns past the end repeat the last (conditional on
             // uniform values only: around a lane's condition the compiler waits for each load before the next)
-            float tv[2][4];
+            float tv[FB][4];
             auto targets = [&](auto read) __attribute__((always_inline)) {
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
+                for (int j = 0; j < FB; ++j)
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        tv[j][e] = read(min(m0 + wt * 32 + i * 16 + 4 * e + lg, a.M - 1) * a.ldt + min(n0 + wo * 32 + j * 16 + lc, a.N - 1));
+                        tv[j][e] = read(min(m0 + wt + i * 16 + 4 * e + lg, a.M - 1) * a.ldt + min(n0 + wo + j * 16 + lc, a.N - 1));
             };
             if (a.target != nullptr) {
                 if (a.target_dtype == AGZO_BF16) targets([&](int64_t at) { return bf16_to_f32(reinterpret_cast<const bf16_t*>(a.target)[at]); });
                 else targets([&](int64_t at) { return reinterpret_cast<const float*>(a.target)[at]; });
             }
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int64_t col = n0 + wo * 32 + j * 16 + lc;
+            for (int j = 0; j < FB; ++j) {
+                const int64_t col = n0 + wo + j * 16 + lc;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const int64_t row = m0 + wt * 32 + i * 16 + 4 * e + lg;
+                    const int64_t row = m0 + wt + i * 16 + 4 * e + lg;
                     if (row >= a.M || col >= a.N) continue;
                     const double y = acc[i][j][e];
                     if (a.Y != nullptr) a.Y[row * a.ldy + col] = (float)y;
@@ -226,26 +255,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void f
     }
 }
 
-int forward_f32_num_workgroups(int64_t M, int64_t N) { return (int)(((M + FT - 1) / FT) * ((N + FT - 1) / FT)); }
+int forward_f32_num_workgroups(int64_t M, int64_t N) {
+    const int t = f32_tile(M, N);
+    return (int)(((M + t - 1) / t) * ((N + t - 1) / t));
+}
 
-hipError_t launch_forward_f32_many(const F32FwdArgs* a, int n, hipStream_t st) {
-    if (n < 0 || n > kBatchMax) return hipErrorInvalidValue;
+template <int FT>
+static hipError_t launch_forward_f32_tiles(const F32FwdArgs* const* a, int n, hipStream_t st) {
+    if (n == 0) return hipSuccess;
     KBatch<F32FwdDev> tb;
     tb.n = 0;
     uint64_t blocks = 0;
-    int order[kBatchMax], m = 0;
     bool vec = true;            // every row starts on 16 bytes
     for (int i = 0; i < n; ++i) {
-        if (a[i].M == 0 || a[i].N == 0) continue;
-        if (a[i].K < 1 || (a[i].shared && (!a[i].P || a[i].Y || !a[i].target))) return hipErrorInvalidValue;
-        // deepest first, so that the launch does not end on a few long tiles
-        int at = m++;
-        for (; at > 0 && a[order[at - 1]].K < a[i].K; --at) order[at] = order[at - 1];
-        order[at] = i;
-    }
-    for (int i = 0; i < m; ++i) {
         F32FwdDev d;
-        d.a = a[order[i]];
+        d.a = *a[i];
         d.tiles_m = (int)((d.a.M + FT - 1) / FT);
         d.tiles_n = (int)((d.a.N + FT - 1) / FT);
         vec = vec && d.a.K % 4 == 0 && d.a.ldx % 4 == 0 && d.a.ldw % 4 == 0 && ((reinterpret_cast<uintptr_t>(d.a.X) | reinterpret_cast<uintptr_t>(d.a.W)) & 15) == 0;
@@ -254,11 +278,39 @@ hipError_t launch_forward_f32_many(const F32FwdArgs* a, int n, hipStream_t st) {
         blocks += tb.gx[tb.n];
         tb.a[tb.n++] = d;
     }
-    if (tb.n == 0) return hipSuccess;
     if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    if (vec) hipLaunchKernelGGL(forward_f32_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, st, tb);
-    else hipLaunchKernelGGL(forward_f32_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, st, tb);
+    const dim3 grid((unsigned)blocks), block(256);
+    if constexpr (FT == 32)      // (the larger tile, at its limit of registers, spills more with one argument set and is 2 % slower)
+        if (tb.n == 1) {
+            if (vec) hipLaunchKernelGGL((forward_f32_kernel<true, FT, 1>), grid, block, 0, st, kbatch_one(tb));
+            else hipLaunchKernelGGL((forward_f32_kernel<false, FT, 1>), grid, block, 0, st, kbatch_one(tb));
+            return hipGetLastError();
+        }
+    if (vec) hipLaunchKernelGGL((forward_f32_kernel<true, FT, kBatchMax>), grid, block, 0, st, tb);
+    else hipLaunchKernelGGL((forward_f32_kernel<false, FT, kBatchMax>), grid, block, 0, st, tb);
     return hipGetLastError();
+}
+
+hipError_t launch_forward_f32_many(const F32FwdArgs* a, int n, hipStream_t st) {
+    if (n < 0 || n > kBatchMax) return hipErrorInvalidValue;
+    int order[kBatchMax], m = 0;
+    for (int i = 0; i < n; ++i) {
+        if (a[i].M == 0 || a[i].N == 0) continue;
+        if (a[i].K < 1 || (a[i].shared && (!a[i].P || a[i].Y || !a[i].target))) return hipErrorInvalidValue;
+        // deepest first, so that the launch does not end on a few long tiles
+        int at = m++;
+        for (; at > 0 && a[order[at - 1]].K < a[i].K; --at) order[at] = order[at - 1];
+        order[at] = i;
+    }
+    const F32FwdArgs *large[kBatchMax], *small[kBatchMax];
+    int nl = 0, ns = 0;
+    for (int i = 0; i < m; ++i) {
+        const F32FwdArgs& p = a[order[i]];
+        if (f32_tile(p.M, p.N) == 64) large[nl++] = &p;
+        else small[ns++] = &p;
+    }
+    const hipError_t e = launch_forward_f32_tiles<64>(large, nl, st);
+    return e != hipSuccess ? e : launch_forward_f32_tiles<32>(small, ns, st);
 }
 
 // Y[t][j] += eps_signed sum_k P[t][k] G[j][k] on stored outputs: the shared-forward schedule with a cross-entropy loss, which
