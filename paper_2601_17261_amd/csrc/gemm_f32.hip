@@ -441,6 +441,76 @@ __global__ __launch_bounds__(64 * SK_WAVES) void xq_f32_kernel(const KBatch<F32S
     skinny_f32_finish<NB>(acc, red, t0, a.M, a.r, a.out);
 }
 
+// T = X Q for one to four columns, of which the form above uses as many lanes in sixteen to load Q: a workgroup is four tokens, its four
+// waves share d_in in chunks of 256, a lane multiplies four consecutive values of each token with the rows of Q that belong to them, on
+// the vector units (whose fp64 rate is that of the matrix cores and far from what bounds this: the bytes of X and their latency; two
+// chunks in flight).  Seven layers of 1000 x 1024 .. 3072 at r = 1: 34 us a launch above, 18 here.  Shorter rows leave waves without a chunk
+// and loads for nothing (512 x 256, r = 4: 5.1 us above, 7.8 here; 512-wide 4 % of a step slower, 1024-wide 0 to 4 % faster)
+constexpr int XQN_TOK = 4, XQN_MIN = 1024;
+template <int R>
+__global__ __launch_bounds__(256) void xq_f32_narrow_kernel(const KBatch<F32SkinnyDev> tb) {
+    __shared__ double red[4][XQN_TOK * R];
+    uint32_t bx, by;
+    const F32SkinnyDev& d = tb.a[kbatch_find(tb, bx, by)];
+    const F32SkinnyArgs& a = d.a;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t t0 = (int64_t)bx * XQN_TOK, K = a.K;
+    const float* xr[XQN_TOK];
+#pragma unroll
+    for (int t = 0; t < XQN_TOK; ++t) xr[t] = a.X + min(t0 + t, a.M - 1) * a.ldx;
+    double acc[XQN_TOK][R] = {};
+    const int64_t nchunk = (K + 255) / 256;
+    constexpr int U = 2;
+    for (int64_t c0 = wave; c0 < nchunk; c0 += 4 * U) {
+        // (never conditional on the lane: what lies past the end is read from the last place and left out)
+        float x[U][XQN_TOK][4], q[U][4][R];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t k = 256 * (c0 + 4 * u) + 4 * lane;
+            if (d.vec) {
+                const int64_t kc = min(k, K - 4);
+#pragma unroll
+                for (int t = 0; t < XQN_TOK; ++t) {
+                    const float4 v = *reinterpret_cast<const float4*>(xr[t] + kc);
+                    x[u][t][0] = v.x; x[u][t][1] = v.y; x[u][t][2] = v.z; x[u][t][3] = v.w;
+                }
+            } else {
+#pragma unroll
+                for (int t = 0; t < XQN_TOK; ++t)
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) x[u][t][s] = xr[t][min(k + s, K - 1)];
+            }
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int j = 0; j < R; ++j) q[u][s][j] = a.V[min(k + s, K - 1) * R + j];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t k = 256 * (c0 + 4 * u) + 4 * lane;
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int j = 0; j < R; ++j) {
+                    const double qd = (double)q[u][s][j];
+#pragma unroll
+                    for (int t = 0; t < XQN_TOK; ++t) acc[t][j] = fma(k + s < K ? (double)x[u][t][s] : 0.0, k + s < K ? qd : 0.0, acc[t][j]);
+                }
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < XQN_TOK; ++t)
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) acc[t][j] += __shfl_xor(acc[t][j], off);
+            if (lane == 0) red[wave][t * R + j] = acc[t][j];
+        }
+    __syncthreads();
+    const int e = threadIdx.x;
+    if (e < XQN_TOK * R && t0 + e / R < a.M) a.out[t0 * R + e] = (float)((red[0][e] + red[1][e]) + (red[2][e] + red[3][e]));
+}
+
 // S = X^T T: rows = features, groups of four tokens dealt to the waves
 template <int NB>
 __global__ __launch_bounds__(64 * SK_WAVES) void xtt_f32_kernel(const KBatch<F32SkinnyDev> tb) {
@@ -485,25 +555,58 @@ __global__ __launch_bounds__(64 * SK_WAVES) void xtt_f32_kernel(const KBatch<F32
     skinny_f32_finish<NB>(acc, red, f0, a.K, a.r, a.out);
 }
 
+static bool skinny_f32_vec(const F32SkinnyArgs& a) { return a.K % 4 == 0 && a.ldx % 4 == 0 && (reinterpret_cast<uintptr_t>(a.X) & 15) == 0; }
+
+static hipError_t launch_xq_f32_narrow(const F32SkinnyArgs* a, const int* idx, int n, int r, hipStream_t st) {
+    if (n == 0) return hipSuccess;
+    KBatch<F32SkinnyDev> tb;
+    tb.n = 0;
+    uint64_t blocks = 0;
+    for (int i = 0; i < n; ++i) {
+        const F32SkinnyArgs& s = a[idx[i]];
+        tb.first[tb.n] = (uint32_t)blocks;
+        tb.gx[tb.n] = (uint32_t)((s.M + XQN_TOK - 1) / XQN_TOK);
+        blocks += tb.gx[tb.n];
+        tb.a[tb.n++] = F32SkinnyDev{s, skinny_f32_vec(s)};
+    }
+    if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)blocks), block(256);
+    switch (r) {
+        case 1: hipLaunchKernelGGL(xq_f32_narrow_kernel<1>, grid, block, 0, st, tb); break;
+        case 2: hipLaunchKernelGGL(xq_f32_narrow_kernel<2>, grid, block, 0, st, tb); break;
+        case 3: hipLaunchKernelGGL(xq_f32_narrow_kernel<3>, grid, block, 0, st, tb); break;
+        default: hipLaunchKernelGGL(xq_f32_narrow_kernel<4>, grid, block, 0, st, tb); break;
+    }
+    return hipGetLastError();
+}
+
 static hipError_t launch_skinny_f32(const F32SkinnyArgs* a, int n, bool transposed, hipStream_t st) {
     if (n < 0 || n > kBatchMax) return hipErrorInvalidValue;
     KBatch<F32SkinnyDev> tb;
     tb.n = 0;
     uint64_t blocks = 0;
-    int nb = 0;
+    int nb = 0, narrow[4][kBatchMax], n_narrow[4] = {};
     for (int i = 0; i < n; ++i) {
         if (a[i].M == 0 || a[i].K == 0) continue;
         if (a[i].r < 1 || a[i].r > kMaxRank) return hipErrorInvalidValue;
         const int want = (a[i].r + 15) / 16;
         if (nb == 0) nb = want;
         if (nb != want) return hipErrorInvalidValue;        // one padded rank per launch
+        if (!transposed && a[i].r <= 4 && a[i].K >= XQN_MIN) {
+            narrow[a[i].r - 1][n_narrow[a[i].r - 1]++] = i;
+            continue;
+        }
         F32SkinnyDev d;
         d.a = a[i];
-        d.vec = (a[i].K % 4 == 0 && a[i].ldx % 4 == 0 && (reinterpret_cast<uintptr_t>(a[i].X) & 15) == 0);
+        d.vec = skinny_f32_vec(a[i]);
         tb.first[tb.n] = (uint32_t)blocks;
         tb.gx[tb.n] = (uint32_t)(((transposed ? a[i].K : a[i].M) + 15) / 16);
         blocks += tb.gx[tb.n];
         tb.a[tb.n++] = d;
+    }
+    for (int r = 1; r <= 4; ++r) {
+        const hipError_t e = launch_xq_f32_narrow(a, narrow[r - 1], n_narrow[r - 1], r, st);
+        if (e != hipSuccess) return e;
     }
     if (tb.n == 0) return hipSuccess;
     if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
