@@ -312,8 +312,9 @@ int sketch_power(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* 
     if (L.dtype == AGZO_BF16) {
         {
             ProfScope ps(ctx, AGZO_PROF_XQ);
-            HIPCHK(launch_xq_bf16(static_cast<const bf16_t*>(X), L.ldx, L.n_tokens, L.d_in, wsh(ctx, p.off_pack), L.r,
-                                  p.rp, nullptr, wsh(ctx, p.off_TpackT), p.m_pad, wsf(ctx, p.off_xqpart), nullptr, st));
+            const XqArgs q{static_cast<const bf16_t*>(X), L.ldx, L.n_tokens, L.d_in, wsh(ctx, p.off_pack), L.r, p.rp, nullptr,
+                           wsh(ctx, p.off_TpackT), p.m_pad, wsf(ctx, p.off_xqpart), nullptr, Q};
+            HIPCHK(launch_xq_bf16_many(&q, 1, ctx->beside, st));
         }
         ProfScope ps(ctx, AGZO_PROF_XTT);
         HIPCHK(launch_xtt_bf16(static_cast<const bf16_t*>(X), L.ldx, L.n_tokens, L.d_in, wsh(ctx, p.off_TpackT),
@@ -544,7 +545,7 @@ int stage_sketch_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, const in
         for (int i = 0; i < n; ++i) {
             const LayerJob& j = jobs[idx[i]];
             q[i] = XqArgs{static_cast<const bf16_t*>(j.X), j.L.ldx, j.L.n_tokens, j.L.d_in, wsh(ctx, j.p.off_pack), j.L.r, j.p.rp,
-                          nullptr, wsh(ctx, j.p.off_TpackT), j.p.m_pad, wsf(ctx, j.p.off_xqpart)};
+                          nullptr, wsh(ctx, j.p.off_TpackT), j.p.m_pad, wsf(ctx, j.p.off_xqpart), nullptr, wsf(ctx, j.p.off_Q)};
         }
         ProfScope ps(ctx, AGZO_PROF_XQ);
         HIPCHK(launch_xq_bf16_many(q, n, ctx->beside, st));
@@ -638,7 +639,7 @@ int project_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs) {
             const LayerJob& j = jobs[b];
             if (done[b] || j.L.dtype != AGZO_BF16 || j.p.rp != ja.p.rp) continue;
             q[n++] = XqArgs{static_cast<const bf16_t*>(j.X), j.L.ldx, j.L.n_tokens, j.L.d_in, wsh(ctx, j.p.off_pack), j.L.r, j.p.rp,
-                            wsf(ctx, j.p.off_T), nullptr, j.p.m_pad, wsf(ctx, j.p.off_xqpart)};
+                            wsf(ctx, j.p.off_T), nullptr, j.p.m_pad, wsf(ctx, j.p.off_xqpart), nullptr, j.B};
             done[b] = 1;
         }
         ProfScope ps(ctx, AGZO_PROF_XQ);
@@ -941,23 +942,29 @@ int agzo_perturbed_forward(agzo_ctx* ctx, const agzo_layer* L, const void* W, co
         HIPCHK(launch_xq_f32_many(&a, 1, ctx->stream));
         return op_forward(ctx, *L, p, W, X, P, eps_signed, seed, Y, loss, loss_dev);
     }
+    const bool narrow = xq_narrow(L->n_tokens, L->d_in, L->r);
+    XqArgs q{static_cast<const bf16_t*>(X), L->ldx, L->n_tokens, L->d_in, wsh(ctx, p.off_pack), L->r, p.rp, P, nullptr, p.m_pad, wsf(ctx, p.off_xqpart), nullptr, B};
     if (timed(ctx, AGZO_PROF_GEMM)) {      // the operands are prepared inside the forward's time
-        HIPCHK(launch_pack_planes(B, L->d_in, L->r, p.rp, wsh(ctx, p.off_pack), ctx->stream));
+        if (!narrow) HIPCHK(launch_pack_planes(B, L->d_in, L->r, p.rp, wsh(ctx, p.off_pack), ctx->stream));
         {
             ProfScope ps(ctx, AGZO_PROF_XQ);
-            HIPCHK(launch_xq_bf16(static_cast<const bf16_t*>(X), L->ldx, L->n_tokens, L->d_in, wsh(ctx, p.off_pack), L->r, p.rp, P, nullptr, p.m_pad,
-                                  wsf(ctx, p.off_xqpart), nullptr, ctx->stream));
+            HIPCHK(launch_xq_bf16_many(&q, 1, false, ctx->stream));
         }
         return op_forward(ctx, *L, p, W, X, P, eps_signed, seed, Y, loss, loss_dev);
     }
     // the W side of the extension operands and the planes of B in one launch, then the projection writes the X side: a model's
-    // step makes this chain once per linear layer and sign
-    const GemmExtArgs ext{ctx->ws + p.off_ext, L->n_tokens, L->d_out, nullptr, L->r, eps_signed, 0.f, false, seed, B, wsh(ctx, p.off_pack), L->d_in};
-    HIPCHK(launch_gemm_ext_prep_many(&ext, 1, ctx->stream));
-    {
+    // step makes this chain once per linear layer and sign.  A narrow projection needs no planes and shares a launch with the W side
+    q.T = nullptr;
+    q.Xext = wsh(ctx, p.off_ext);
+    GemmExtArgs ext{ctx->ws + p.off_ext, L->n_tokens, L->d_out, nullptr, L->r, eps_signed, 0.f, false, seed, B, wsh(ctx, p.off_pack), L->d_in};
+    if (narrow) {
+        ext.planes = nullptr;
         ProfScope ps(ctx, AGZO_PROF_XQ);
-        HIPCHK(launch_xq_bf16(static_cast<const bf16_t*>(X), L->ldx, L->n_tokens, L->d_in, wsh(ctx, p.off_pack), L->r, p.rp, nullptr, nullptr,
-                              p.m_pad, wsf(ctx, p.off_xqpart), wsh(ctx, p.off_ext), ctx->stream));
+        HIPCHK(launch_xq_narrow_ext(q, ext, ctx->stream));
+    } else {
+        HIPCHK(launch_gemm_ext_prep_many(&ext, 1, ctx->stream));
+        ProfScope ps(ctx, AGZO_PROF_XQ);
+        HIPCHK(launch_xq_bf16_many(&q, 1, false, ctx->stream));
     }
     return op_forward(ctx, *L, p, W, X, P, eps_signed, seed, Y, loss, loss_dev, false, 0, false, false, true);
 }

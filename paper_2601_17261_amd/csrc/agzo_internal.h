@@ -221,15 +221,19 @@ hipError_t launch_xtt_f32_many(const F32SkinnyArgs* a, int n, hipStream_t st);
 // part: xq_part_bytes() bytes of scratch for the split over d_in that small token counts take (NULL: never split)
 // Xext: T as the X side of a forward's extension operands, [M][gemm_bf16_ext_width(r)] (nullable)
 size_t xq_part_bytes(int64_t M, int64_t K, int rp);
-hipError_t launch_xq_bf16(const bf16_t* X, int64_t ldx, int64_t M, int64_t K, const bf16_t* Qpack, int r, int rp,
-                          float* T, bf16_t* TpackT, int64_t m_pad, float* part, bf16_t* Xext, hipStream_t st);
 struct XqArgs {
     const bf16_t* X; int64_t ldx, M, K; const bf16_t* Qpack; int r, rp; float* T; bf16_t* TpackT; int64_t m_pad; float* part;
     bf16_t* Xext = nullptr;
+    const float* Q = nullptr;      // the fp32 [K][r] of which Qpack are the planes: what xq_narrow() products read instead
 };
+// true: a product that multiplies the fp32 factor itself (one column, few tokens); Qpack may then be NULL
+bool xq_narrow(int64_t M, int64_t K, int r);
 // up to kBatchMax products with the same rp in one launch (plus one finishing launch if any of them splits d_in); m_pad is a multiple of 4
 // half_cu: forwards on another stream hold half of every compute unit
 hipError_t launch_xq_bf16_many(const XqArgs* a, int n, bool half_cu, hipStream_t st);
+// one narrow product and, in the same launch, the W side of a forward's extension operands
+struct GemmExtArgs;
+hipError_t launch_xq_narrow_ext(const XqArgs& a, const GemmExtArgs& ext, hipStream_t st);
 int xtt_num_splits(int64_t M, int64_t K);
 // partial[s][d][rp] = sum over token range s of X[t][d] * T[t][k]
 hipError_t launch_xtt_bf16(const bf16_t* X, int64_t ldx, int64_t M, int64_t K, const bf16_t* TpackT, int64_t m_pad,

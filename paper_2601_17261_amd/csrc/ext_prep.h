@@ -1,0 +1,102 @@
+// Extension operands of perturbed forwards: device code of the launches that write them (gemm_bf16.hip; skinny.hip, which writes the W side
+// beside a narrow projection).
+#pragma once
+#include "agzo_internal.h"
+
+namespace agzo {
+
+// Extension operands of perturbed forwards, written once per layer instead of once per tile: eight columns per thread.
+// Rows 0..M-1 are the X side ([Ph | Ph | Pl | 0], P = X B split hi + lo in bf16), rows M..M+N-1 the W side
+// ([Gh | Gl | Gh | 0], G regenerated from the Philox seed, times coef: the signed eps); n_w = 2 adds rows M+N..M+2N-1, the
+// W side once more with coef2 (the other sign's, or the shared-forward kernel's second pass, -2 eps).  Several layers per
+// launch (fourteen launches of one operand set each took 62 us of a layer set's step).  M = 0 where the projection writes
+// the X side itself; then the threads behind the W side split B into planes for that projection.
+struct ExtDev {
+    bf16_t* Xext; bf16_t* Wext;
+    int64_t M, N; int ext_ld;
+    const float* P; int r, rp;
+    float coef, coef2; int n_w;
+    uint32_t s_lo, s_hi;
+    const float* B; bf16_t* planes; int64_t d;
+};
+// workgroup bx of 256 threads
+__device__ __forceinline__ void ext_prep_body(const ExtDev& a, uint32_t bx) {
+    const int ext_ld = a.ext_ld, r = a.r, rp = a.rp;
+    const int64_t M = a.M, N = a.N;
+    const int chunks = ext_ld / 8;
+    const int64_t idx = (int64_t)bx * 256 + threadIdx.x;
+    if (idx >= (M + a.n_w * N) * chunks) {
+        // eight rows of one column of B
+        const int64_t e = idx - (M + a.n_w * N) * chunks;
+        if (a.planes == nullptr || e >= a.d / 8 * rp) return;
+        const int64_t i = e % (a.d / 8) * 8;
+        const int k = (int)(e / (a.d / 8));
+        uint32_t w[3][4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            bf16_t h[2], m[2], l[2];
+#pragma unroll
+            for (int v = 0; v < 2; ++v) split3_bf16(k < r ? a.B[(i + 2 * u + v) * r + k] : 0.f, h[v], m[v], l[v]);
+            w[0][u] = (uint32_t)h[0] | ((uint32_t)h[1] << 16);
+            w[1][u] = (uint32_t)m[0] | ((uint32_t)m[1] << 16);
+            w[2][u] = (uint32_t)l[0] | ((uint32_t)l[1] << 16);
+        }
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<uint4*>(a.planes + ((int64_t)pl * rp + k) * a.d + i) = make_uint4(w[pl][0], w[pl][1], w[pl][2], w[pl][3]);
+        return;
+    }
+    int64_t row = idx / chunks;
+    const bool second = row >= M + N;
+    if (second) row -= N;
+    const float coef = second ? a.coef2 : a.coef;
+    const int col0 = (int)(idx % chunks) * 8;
+    const int seg = col0 / rp, k0 = col0 % rp;
+    uint32_t hi[4] = {0, 0, 0, 0}, lo[4] = {0, 0, 0, 0};
+    if (seg < 3) {
+        float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        if (row < M) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (k0 + i < r) v[i] = a.P[row * r + k0 + i];
+        } else {
+            const int64_t j = row - M;
+            if (k0 < r) {
+                const float4 z = philox_normal4(a.s_lo, a.s_hi, AGZO_TAG_G, (uint32_t)j, (uint32_t)(k0 >> 2));
+                v[0] = z.x; v[1] = z.y; v[2] = z.z; v[3] = z.w;
+            }
+            if (k0 + 4 < r) {
+                const float4 z = philox_normal4(a.s_lo, a.s_hi, AGZO_TAG_G, (uint32_t)j, (uint32_t)((k0 >> 2) + 1));
+                v[4] = z.x; v[5] = z.y; v[6] = z.z; v[7] = z.w;
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = (k0 + i < r) ? coef * v[i] : 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            hi[i] = pack_bf16x2(v[2 * i], v[2 * i + 1]);
+            lo[i] = pack_bf16x2(v[2 * i] - __uint_as_float(hi[i] << 16), v[2 * i + 1] - __uint_as_float(hi[i] & 0xFFFF0000u));
+        }
+    }
+    // X side: [hi | hi | lo]; W side: [hi | lo | hi]
+    const bool use_lo = (row < M) ? (seg == 2) : (seg == 1);
+    const uint4 out = use_lo ? make_uint4(lo[0], lo[1], lo[2], lo[3]) : make_uint4(hi[0], hi[1], hi[2], hi[3]);
+    bf16_t* dst = (row < M) ? a.Xext + row * ext_ld + col0 : a.Wext + (row - M + (second ? N : 0)) * ext_ld + col0;
+    *reinterpret_cast<uint4*>(dst) = out;
+}
+
+// the W side of args (and the X side, from P, unless that is NULL) as the kernels take it, and the workgroups for it
+inline ExtDev ext_dev(const GemmExtArgs& a, uint64_t& workgroups) {
+    ExtDev d;
+    d.M = a.M; d.N = a.N; d.ext_ld = gemm_bf16_ext_width(a.r);
+    d.Xext = static_cast<bf16_t*>(a.ext_ws); d.Wext = d.Xext + d.M * d.ext_ld;
+    if (!a.P) d.M = 0;
+    d.B = a.B; d.planes = a.planes; d.d = a.d;
+    d.P = a.P; d.r = a.r; d.rp = (a.r + 15) / 16 * 16;
+    d.coef = a.coef; d.coef2 = a.coef2; d.n_w = a.two ? 2 : 1;
+    d.s_lo = (uint32_t)a.seed; d.s_hi = (uint32_t)(a.seed >> 32);
+    const int64_t items = (d.M + d.n_w * d.N) * (d.ext_ld / 8) + (d.planes ? d.d / 8 * d.rp : 0);
+    workgroups = (uint64_t)((items + 255) / 256);
+    return d;
+}
+
+}  // namespace agzo

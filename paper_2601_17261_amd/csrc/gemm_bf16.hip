@@ -17,6 +17,7 @@
 // The rank-r term is accumulated by the same MFMA blocks as a few extra K slices appended after the d_in slices:
 // one operand is eps * P split in bf16 hi/lo, the other is G regenerated from the Philox seed and split
 // likewise, so both signs share bit-identical X W^T accumulators.
+#include "ext_prep.h"
 #include "gemm_bf16_common.h"
 
 namespace agzo {
@@ -560,85 +561,11 @@ __global__ __launch_bounds__(64 * WA * WB) void gemm_bf16_kernel(GemmParams p) {
 
 
 
-// Extension operands of perturbed forwards, written once per layer instead of once per tile: eight columns per thread.
-// Rows 0..M-1 are the X side ([Ph | Ph | Pl | 0], P = X B split hi + lo in bf16), rows M..M+N-1 the W side
-// ([Gh | Gl | Gh | 0], G regenerated from the Philox seed, times coef: the signed eps); n_w = 2 adds rows M+N..M+2N-1, the
-// W side once more with coef2 (the other sign's, or the shared-forward kernel's second pass, -2 eps).  Several layers per
-// launch (fourteen launches of one operand set each took 62 us of a layer set's step).  M = 0 where the projection writes
-// the X side itself; then the threads behind the W side split B into planes for that projection.
-struct ExtDev {
-    bf16_t* Xext; bf16_t* Wext;
-    int64_t M, N; int ext_ld;
-    const float* P; int r, rp;
-    float coef, coef2; int n_w;
-    uint32_t s_lo, s_hi;
-    const float* B; bf16_t* planes; int64_t d;
-};
 template <int CAP>
 __global__ __launch_bounds__(256) void gemm_ext_prep_kernel(const KBatch<ExtDev, CAP> tb) {
     uint32_t bx, by;
     const ExtDev& a = tb.a[kbatch_find(tb, bx, by)];
-    const int ext_ld = a.ext_ld, r = a.r, rp = a.rp;
-    const int64_t M = a.M, N = a.N;
-    const int chunks = ext_ld / 8;
-    const int64_t idx = (int64_t)bx * 256 + threadIdx.x;
-    if (idx >= (M + a.n_w * N) * chunks) {
-        // eight rows of one column of B
-        const int64_t e = idx - (M + a.n_w * N) * chunks;
-        if (a.planes == nullptr || e >= a.d / 8 * rp) return;
-        const int64_t i = e % (a.d / 8) * 8;
-        const int k = (int)(e / (a.d / 8));
-        uint32_t w[3][4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            bf16_t h[2], m[2], l[2];
-#pragma unroll
-            for (int v = 0; v < 2; ++v) split3_bf16(k < r ? a.B[(i + 2 * u + v) * r + k] : 0.f, h[v], m[v], l[v]);
-            w[0][u] = (uint32_t)h[0] | ((uint32_t)h[1] << 16);
-            w[1][u] = (uint32_t)m[0] | ((uint32_t)m[1] << 16);
-            w[2][u] = (uint32_t)l[0] | ((uint32_t)l[1] << 16);
-        }
-#pragma unroll
-        for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<uint4*>(a.planes + ((int64_t)pl * rp + k) * a.d + i) = make_uint4(w[pl][0], w[pl][1], w[pl][2], w[pl][3]);
-        return;
-    }
-    int64_t row = idx / chunks;
-    const bool second = row >= M + N;
-    if (second) row -= N;
-    const float coef = second ? a.coef2 : a.coef;
-    const int col0 = (int)(idx % chunks) * 8;
-    const int seg = col0 / rp, k0 = col0 % rp;
-    uint32_t hi[4] = {0, 0, 0, 0}, lo[4] = {0, 0, 0, 0};
-    if (seg < 3) {
-        float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        if (row < M) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (k0 + i < r) v[i] = a.P[row * r + k0 + i];
-        } else {
-            const int64_t j = row - M;
-            if (k0 < r) {
-                const float4 z = philox_normal4(a.s_lo, a.s_hi, AGZO_TAG_G, (uint32_t)j, (uint32_t)(k0 >> 2));
-                v[0] = z.x; v[1] = z.y; v[2] = z.z; v[3] = z.w;
-            }
-            if (k0 + 4 < r) {
-                const float4 z = philox_normal4(a.s_lo, a.s_hi, AGZO_TAG_G, (uint32_t)j, (uint32_t)((k0 >> 2) + 1));
-                v[4] = z.x; v[5] = z.y; v[6] = z.z; v[7] = z.w;
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = (k0 + i < r) ? coef * v[i] : 0.f;
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            hi[i] = pack_bf16x2(v[2 * i], v[2 * i + 1]);
-            lo[i] = pack_bf16x2(v[2 * i] - __uint_as_float(hi[i] << 16), v[2 * i + 1] - __uint_as_float(hi[i] & 0xFFFF0000u));
-        }
-    }
-    // X side: [hi | hi | lo]; W side: [hi | lo | hi]
-    const bool use_lo = (row < M) ? (seg == 2) : (seg == 1);
-    const uint4 out = use_lo ? make_uint4(lo[0], lo[1], lo[2], lo[3]) : make_uint4(hi[0], hi[1], hi[2], hi[3]);
-    bf16_t* dst = (row < M) ? a.Xext + row * ext_ld + col0 : a.Wext + (row - M + (second ? N : 0)) * ext_ld + col0;
-    *reinterpret_cast<uint4*>(dst) = out;
+    ext_prep_body(a, bx);
 }
 
 static_assert(BK == 64, "the extension operands' width");
@@ -649,23 +576,16 @@ hipError_t launch_gemm_ext_prep_many(const GemmExtArgs* a, int n, hipStream_t st
     tb.n = 0;
     uint64_t blocks = 0;
     for (int m = 0; m < n; ++m) {
-        ExtDev d;
-        d.M = a[m].M; d.N = a[m].N; d.ext_ld = gemm_bf16_ext_width(a[m].r);
-        d.Xext = static_cast<bf16_t*>(a[m].ext_ws); d.Wext = d.Xext + d.M * d.ext_ld;
-        if (!a[m].P) d.M = 0;
-        d.B = a[m].B; d.planes = a[m].planes; d.d = a[m].d;
-        if (d.planes && d.d % 8) return hipErrorInvalidValue;
-        d.P = a[m].P; d.r = a[m].r; d.rp = (a[m].r + 15) / 16 * 16;
-        d.coef = a[m].coef; d.coef2 = a[m].coef2; d.n_w = a[m].two ? 2 : 1;
-        d.s_lo = (uint32_t)a[m].seed; d.s_hi = (uint32_t)(a[m].seed >> 32);
-        const int64_t items = (d.M + d.n_w * d.N) * (d.ext_ld / 8) + (d.planes ? d.d / 8 * d.rp : 0);
+        if (a[m].planes && a[m].d % 8) return hipErrorInvalidValue;
+        uint64_t wgs;
+        const ExtDev d = ext_dev(a[m], wgs);
+        if (blocks + wgs > 0x7FFFFFFFull) return hipErrorInvalidValue;
         tb.first[tb.n] = (uint32_t)blocks;
-        tb.gx[tb.n] = (uint32_t)((items + 255) / 256);
-        blocks += tb.gx[tb.n];
+        tb.gx[tb.n] = (uint32_t)wgs;
+        blocks += wgs;
         tb.a[tb.n++] = d;
     }
     if (blocks == 0) return hipSuccess;
-    if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
     if (tb.n == 1) hipLaunchKernelGGL(gemm_ext_prep_kernel<1>, dim3((unsigned)blocks), dim3(256), 0, st, kbatch_one(tb));
     else hipLaunchKernelGGL(gemm_ext_prep_kernel<kBatchMax>, dim3((unsigned)blocks), dim3(256), 0, st, tb);
     return hipGetLastError();

@@ -6,7 +6,7 @@
 // kernels stay bound by the single read of X.  v_mfma_f32_16x16x32_bf16 throughout.
 #include <type_traits>
 
-#include "agzo_internal.h"
+#include "ext_prep.h"
 
 namespace agzo {
 
@@ -466,6 +466,131 @@ __global__ __launch_bounds__(256) void xq_finish_many_kernel(const KBatch<XqDev,
     if (t < M && a.Xext != nullptr) store_ext(a.Xext, t, k, rp, v);
 }
 
+// ---------------------------------------------------------------------------
+// xq for one column (the paper's rank) and few tokens: on the vector units, from the fp32 column itself.  A lane multiplies eight
+// consecutive values of four tokens with the values of Q that belong to them (fp32 products and sums, a lane's in order, then lanes and
+// waves pairwise: fewer roundings than a sum over d_in of three planes); the waves of a workgroup share d_in in chunks of 512, as many
+// as it has, and tokens otherwise.  The kernels above pad Q to 16 columns of three planes, and few tokens leave them to share d_in
+// among workgroups, whose sums take a launch of their own: 432 tokens of a 1024-wide layer 5.1 + 3.1 us there and 4.4 here.  For four columns
+// (the rows of Q are then twice the bytes of the four tokens) a step is 0 to 12 % slower this way
+// ---------------------------------------------------------------------------
+constexpr int XQN_TOK = 4, XQN_CHUNK = 512;
+bool xq_narrow(int64_t M, int64_t K, int r) { return r == 1 && M < 8192 && K >= 8; }
+struct XqNarrowDev {
+    const bf16_t* X; const float* Q; int64_t ldx, M, K, m_pad;
+    float* T; bf16_t* TpackT; bf16_t* Xext;
+    int kw, vec;                 // waves that share d_in; 16-byte loads of Q
+};
+static int xqn_waves(int64_t K) { return K > 3 * XQN_CHUNK ? 4 : K > XQN_CHUNK ? 2 : 1; }
+
+__device__ __forceinline__ void xq_narrow_body(const XqNarrowDev& a, uint32_t bx) {
+    constexpr int U = 2;                                        // chunks in flight
+    __shared__ float part[4][XQN_TOK];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kw = a.kw, wk = wave % kw, wt = wave / kw;
+    const int64_t K = a.K, tw = ((int64_t)bx * (4 / kw) + wt) * XQN_TOK;        // the wave's first token
+    const bf16_t* xr[XQN_TOK];
+#pragma unroll
+    for (int t = 0; t < XQN_TOK; ++t) xr[t] = a.X + min(tw + t, a.M - 1) * a.ldx;
+    float acc[XQN_TOK] = {};
+    const int64_t nchunk = (K + XQN_CHUNK - 1) / XQN_CHUNK;
+    for (int64_t c0 = wk; c0 < nchunk; c0 += kw * U) {
+        // (never conditional on the lane: what lies past the end, in whole eights, is read from the last place and left out)
+        uint4 x[U][XQN_TOK];
+        float q[U][8];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t k = min((c0 + u * kw) * XQN_CHUNK + 8 * lane, K - 8);
+#pragma unroll
+            for (int t = 0; t < XQN_TOK; ++t) x[u][t] = *reinterpret_cast<const uint4*>(xr[t] + k);
+            const float* src = a.Q + k;
+            if (a.vec) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const float4 v = reinterpret_cast<const float4*>(src)[i];
+                    q[u][4 * i] = v.x; q[u][4 * i + 1] = v.y; q[u][4 * i + 2] = v.z; q[u][4 * i + 3] = v.w;
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) q[u][i] = src[i];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if ((c0 + u * kw) * XQN_CHUNK + 8 * lane >= K) continue;
+#pragma unroll
+            for (int t = 0; t < XQN_TOK; ++t) {
+                const uint32_t w[4] = {x[u][t].x, x[u][t].y, x[u][t].z, x[u][t].w};
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[t] = fmaf(__uint_as_float((e & 1) ? w[e >> 1] & 0xFFFF0000u : w[e >> 1] << 16), q[u][e], acc[t]);
+            }
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < XQN_TOK; ++t) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) acc[t] += __shfl_xor(acc[t], off);
+        if (lane == 0) part[wave][t] = acc[t];
+    }
+    __syncthreads();
+    // a thread four tokens and a column of the outputs' sixteen: all but the first are zero
+    const int g = tid >> 4, k = tid & 15;
+    if (g >= 4 / kw) return;
+    floatx4 v = {0.f, 0.f, 0.f, 0.f};
+    if (k == 0) {
+#pragma unroll
+        for (int t = 0; t < XQN_TOK; ++t) {
+            v[t] = part[g * kw][t];
+            if (kw == 2) v[t] += part[g * kw + 1][t];
+            if (kw == 4) v[t] = (v[t] + part[1][t]) + (part[2][t] + part[3][t]);
+        }
+    }
+    xq_emit(v, a.M, 1, 16, a.T, a.TpackT, a.m_pad, a.Xext, ((int64_t)bx * (4 / kw) + g) * XQN_TOK, k);
+}
+template <int CAP>
+__global__ __launch_bounds__(256) void xq_narrow_many_kernel(const KBatch<XqNarrowDev, CAP> tb) {
+    uint32_t bx, by;
+    const XqNarrowDev& a = tb.a[kbatch_find(tb, bx, by)];
+    xq_narrow_body(a, bx);
+}
+__global__ __launch_bounds__(256) void xq_narrow_ext_kernel(const XqNarrowDev a, uint32_t blocks, const ExtDev ext) {
+    if (blockIdx.x < blocks) xq_narrow_body(a, blockIdx.x);
+    else ext_prep_body(ext, blockIdx.x - blocks);
+}
+
+static XqNarrowDev xqn_dev(const XqArgs& a, uint64_t& workgroups) {
+    XqNarrowDev d{a.X, a.Q, a.ldx, a.M, a.K, a.m_pad, a.T, a.TpackT, a.Xext, xqn_waves(a.K), (reinterpret_cast<uintptr_t>(a.Q) & 15) == 0};
+    const int64_t tok = XQN_TOK * (4 / d.kw);
+    workgroups = (uint64_t)(((a.TpackT ? a.m_pad : a.M) + tok - 1) / tok);
+    return d;
+}
+static hipError_t launch_xq_narrow(const XqArgs* const* a, int n, hipStream_t st) {
+    KBatch<XqNarrowDev> tb;
+    tb.n = n;
+    uint64_t blocks = 0;
+    for (int i = 0; i < n; ++i) {
+        uint64_t wgs;
+        tb.a[i] = xqn_dev(*a[i], wgs);
+        tb.first[i] = (uint32_t)blocks;
+        tb.gx[i] = (uint32_t)wgs;
+        blocks += wgs;
+    }
+    if (n == 0) return hipSuccess;
+    if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    if (n == 1) hipLaunchKernelGGL(xq_narrow_many_kernel<1>, dim3((unsigned)blocks), dim3(256), 0, st, kbatch_one(tb));
+    else hipLaunchKernelGGL(xq_narrow_many_kernel<kBatchMax>, dim3((unsigned)blocks), dim3(256), 0, st, tb);
+    return hipGetLastError();
+}
+hipError_t launch_xq_narrow_ext(const XqArgs& a, const GemmExtArgs& ext, hipStream_t st) {
+    if (!xq_narrow(a.M, a.K, a.r) || !a.Q || a.rp != 16 || a.m_pad % 4 || ext.planes) return hipErrorInvalidValue;
+    uint64_t wgs, ext_wgs;
+    const XqNarrowDev d = xqn_dev(a, wgs);
+    const ExtDev e = ext_dev(ext, ext_wgs);
+    if (wgs + ext_wgs > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(xq_narrow_ext_kernel, dim3((unsigned)(wgs + ext_wgs)), dim3(256), 0, st, d, (uint32_t)wgs, e);
+    return hipGetLastError();
+}
+
 // number of d_in splits for M tokens (1 = the token blocks alone fill the chip, or d_in is too short to share)
 static int xq_splits(int64_t rows, int64_t K) {
     const int64_t blocks = (rows + XQ_TOK - 1) / XQ_TOK;
@@ -532,16 +657,24 @@ hipError_t launch_xq_bf16_many(const XqArgs* a, int n, bool half_cu, hipStream_t
     uint64_t half = 0;                         // workgroups of 128 tokens
     // the deepest first, so that the launch does not end on a few long workgroups
     int order[kBatchMax], count = 0;
+    const XqArgs* narrow[kBatchMax];
+    int n_narrow = 0;
     for (int m = 0; m < n; ++m) {
         if (a[m].M == 0) continue;
+        if (rp == 0) rp = a[m].rp;
+        if (a[m].rp != rp || a[m].m_pad % 4) return hipErrorInvalidValue;       // one padded rank per launch
+        if (xq_narrow(a[m].M, a[m].K, a[m].r)) {
+            if (!a[m].Q) return hipErrorInvalidValue;
+            narrow[n_narrow++] = &a[m];
+            continue;
+        }
         int at = count++;
         for (; at > 0 && a[order[at - 1]].K < a[m].K; --at) order[at] = order[at - 1];
         order[at] = m;
-        if (rp == 0) rp = a[m].rp;
-        if (a[m].rp != rp || a[m].m_pad % 4) return hipErrorInvalidValue;       // one padded rank per launch
         half += (uint64_t)((a[m].M + 2 * XQ_TOK - 1) / (2 * XQ_TOK)) * (uint64_t)(a[m].part ? xq_splits(a[m].m_pad, a[m].K) : 1);
     }
-    if (rp == 0) return hipSuccess;
+    const hipError_t en = launch_xq_narrow(narrow, n_narrow, st);
+    if (en != hipSuccess || count == 0) return en;
     const int mb = rp >= 48 && half >= 256 ? 2 : 1;      // (where that leaves no compute unit without a workgroup)
     KBatch<XqDev> tb, fin;
     tb.n = fin.n = 0;
@@ -572,12 +705,6 @@ hipError_t launch_xq_bf16_many(const XqArgs* a, int n, bool half_cu, hipStream_t
     if (fin.n == 1) hipLaunchKernelGGL(xq_finish_many_kernel<1>, fin_grid, dim3(256), 0, st, kbatch_one(fin), rp);
     else hipLaunchKernelGGL(xq_finish_many_kernel<kBatchMax>, fin_grid, dim3(256), 0, st, fin, rp);
     return hipGetLastError();
-}
-
-hipError_t launch_xq_bf16(const bf16_t* X, int64_t ldx, int64_t M, int64_t K, const bf16_t* Qpack, int r, int rp,
-                          float* T, bf16_t* TpackT, int64_t m_pad, float* part, bf16_t* Xext, hipStream_t st) {
-    const XqArgs a{X, ldx, M, K, Qpack, r, rp, T, TpackT, m_pad, part, Xext};
-    return launch_xq_bf16_many(&a, 1, false, st);
 }
 
 // ---------------------------------------------------------------------------

@@ -1,0 +1,57 @@
+"""X Q for a single column on the vector units: widths below, at and past the chunks that waves share, tokens that waves and workgroups
+do not divide, unaligned factors, every output form."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import agzo as oagzo
+from paper_2601_17261_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(1, 8), (3, 64), (17, 504), (33, 512), (66, 520), (5, 1024), (129, 1032), (7, 1536), (9, 1544), (40, 2560), (21, 4104), (8191, 16), (8192, 16)]
+
+
+def _offset(a, k):
+    """the same values k floats behind a 16-byte boundary"""
+    flat = torch.empty(a.numel() + 4, device="cuda")
+    v = flat[k:k + a.numel()].view(a.shape)
+    v.copy_(a)
+    return v
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("n,d", SHAPES)
+def test_sketch_and_perturbed_forward(n, d, shift):
+    """T = X q in fp32 sums of at most d terms: sqrt(d) 2^-24 of |x| |q|; the sketch adds n of them"""
+    ctx = binding.Context()
+    X = torch.randn(n, d + 8, device="cuda").bfloat16()[:, :d]
+    q = _offset(torch.randn(d, 1, device="cuda"), shift)
+    S = torch.empty(d, 1, device="cuda")
+    ctx.layer_forward_sketch(binding.make_layer(torch.empty(16, d, device="cuda", dtype=torch.bfloat16), X, 1), None, X, None, binding.SKETCH_POWER, q, 0, S, None, None)
+    T = X.double() @ q.double()
+    want = X.double().T @ T
+    tol = 4 * 2.0 ** -24 * ((d ** 0.5) * X.double().abs().T @ (X.double().norm(dim=1, keepdim=True) * q.double().norm() / d ** 0.5) + n ** 0.5 * (X.double().abs().T @ T.abs()))
+    assert ((S.double() - want).abs() <= tol + 1e-30).all()
+    # the projection inside a forward: Y = eps (X q) G^T with W = 0, rank-r term as bf16 hi / lo pairs (2^-16 of it), stored as bf16
+    W = torch.zeros(140, d, device="cuda", dtype=torch.bfloat16)
+    Y = torch.full((n, 140), 7.0, device="cuda", dtype=torch.bfloat16)
+    ctx.perturbed_forward(binding.make_layer(W, X, 1, Y=Y), W, X, q, 9, 0.5, Y, None, None)
+    ctx.check()
+    G = torch.from_numpy(oagzo.gaussian_factor(9, 140, 1)).cuda().double()
+    want = 0.5 * T @ G.T
+    err = (Y.double() - want).abs()
+    assert (err <= (2.0 ** -8 + 2.0 ** -14) * want.abs() + 2e-6 * X.double().norm(dim=1, keepdim=True) * q.double().norm() * G.abs().max()).all()
+
+
+def test_many_layers_as_one_by_one():
+    ctx = binding.Context()
+    X = [torch.randn(n, d, device="cuda").bfloat16() for n, d in SHAPES]
+    lay = [binding.make_layer(torch.empty(16, x.shape[1], device="cuda", dtype=torch.bfloat16), x, 1) for x in X]
+    many = [torch.empty(x.shape[1], 1, device="cuda") for x in X]
+    ctx.basis_many([(l, x, 3 + i, None, b) for i, (l, x, b) in enumerate(zip(lay, X, many))], 2, 0)
+    for i, (l, x, b) in enumerate(zip(lay, X, many)):
+        one = torch.empty_like(b)
+        ctx.basis(l, x, 2, 3 + i, None, 0, one)
+        assert torch.equal(one, b), i
+    ctx.check()
