@@ -343,14 +343,6 @@ int op_qr(agzo_ctx* ctx, size_t off_qr, const float* S, int64_t d, int r, int rp
     return 0;
 }
 
-// Q = qr(sum of the pending splits); the summed sketch is left in the workspace S
-int op_qr_from_splits(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, float* Q, bf16_t* planes, bool refine) {
-    ProfScope ps(ctx, AGZO_PROF_QR);
-    HIPCHK(launch_qr(nullptr, wsf(ctx, p.off_xtt), p.nsplit, p.rp, wsf(ctx, p.off_S), L.d_in, L.r, Q, planes,
-                     ctx->ws + p.off_qr, ctx->flag, refine, ctx->stream));
-    return 0;
-}
-
 GemmBf16Args forward_bf16_args(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* W, const void* X, const float* P,
                                float eps_signed, uint64_t seed, void* Y, const GemmLossArgs& loss, bool shared) {
     GemmBf16Args a;
@@ -466,40 +458,6 @@ int op_update(agzo_ctx* ctx, const agzo_layer& L, size_t off_upd, void* W, const
     return 0;
 }
 
-// Alg. 1.  On return (bf16) the workspace planes hold B.
-int op_basis(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* X, int K, uint64_t seed, const float* S0,
-             int flags, float* B) {
-    const bool bf = (L.dtype == AGZO_BF16);
-    float* S = wsf(ctx, p.off_S);
-    float* Q = wsf(ctx, p.off_Q);
-    bf16_t* planes = bf ? wsh(ctx, p.off_pack) : nullptr;
-    const float* given = S0;      // an explicit first sketch, if any
-    if (flags & AGZO_INIT_FEATURE) {
-        HIPCHK(launch_fill_normal(Q, L.d_in, L.r, seed, AGZO_TAG_Q0, ctx->stream));
-        if (bf) HIPCHK(launch_pack_planes(Q, L.d_in, L.r, p.rp, planes, ctx->stream));
-        TRY(sketch_power(ctx, L, p, X, Q, S));
-        given = nullptr;
-    } else if (!given) {
-        TRY(sketch_range(ctx, L, p, X, seed, S));
-    }
-    for (int k = 0; k <= K; ++k) {
-        float* out = (k == K) ? B : Q;
-        // iterates that are sketched again need a well-conditioned basis of the same span, not full orthonormality:
-        // one Cholesky pass (same final QR factor, see qr.hip); the returned basis gets both passes
-        const bool refine = (k == K);
-        if (given) {
-            TRY(op_qr(ctx, p.off_qr, given, L.d_in, L.r, p.rp, out, planes, refine));
-            given = nullptr;
-        } else if (bf) {
-            TRY(op_qr_from_splits(ctx, L, p, out, planes, refine));
-        } else {
-            TRY(op_qr(ctx, p.off_qr, S, L.d_in, L.r, p.rp, out, nullptr, refine));
-        }
-        if (k < K) TRY(sketch_power(ctx, L, p, X, Q, S));
-    }
-    return 0;
-}
-
 // ---- several layers at once (Alg. 2: the base forward computes every layer's basis before the perturbed passes; the
 // extractions are independent, so every stage of Alg. 1 is one launch for all layers) ----
 struct LayerJob {
@@ -529,7 +487,8 @@ int stage_sketch_many_f32(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, cons
 }
 
 // one stage for the jobs idx[0..n) (one dtype): Omega^T planes + range sketch, or T = X Q planes + power sketch
-int stage_sketch_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, const int* idx, int n, bool range) {
+// raw (power sketch; nullable): per job of idx the column that the last factorisation left to be normalised, NULL where Q is ready
+int stage_sketch_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, const int* idx, int n, bool range, const float* const* raw = nullptr) {
     if (n > 0 && jobs[idx[0]].L.dtype != AGZO_BF16) return stage_sketch_many_f32(ctx, jobs, idx, n, range);
     hipStream_t st = ctx->stream;
     if (range) {
@@ -546,6 +505,12 @@ int stage_sketch_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, const in
             const LayerJob& j = jobs[idx[i]];
             q[i] = XqArgs{static_cast<const bf16_t*>(j.X), j.L.ldx, j.L.n_tokens, j.L.d_in, wsh(ctx, j.p.off_pack), j.L.r, j.p.rp,
                           nullptr, wsh(ctx, j.p.off_TpackT), j.p.m_pad, wsf(ctx, j.p.off_xqpart), nullptr, wsf(ctx, j.p.off_Q)};
+            if (raw && raw[i]) {
+                q[i].Q = raw[i];
+                q[i].norm2 = reinterpret_cast<const double*>(ctx->ws + j.p.off_qr);
+                q[i].norm_blocks = qr_norm_blocks(j.L.d_in);
+                q[i].flag = ctx->flag;
+            }
         }
         ProfScope ps(ctx, AGZO_PROF_XQ);
         HIPCHK(launch_xq_bf16_many(q, n, ctx->beside, st));
@@ -595,6 +560,7 @@ int basis_many_impl(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, int K, int
         if (n_need) TRY(stage_sketch_many(ctx, jobs, need_idx, n_need, !(flags & AGZO_INIT_FEATURE)));
         for (int k = 0; k <= K; ++k) {
             QrArgs q[kBatchMax];
+            const float* raw[kBatchMax];
             for (int i = 0; i < n; ++i) {
                 const LayerJob& j = jobs[idx[i]];
                 float* out = (k == K) ? j.B : wsf(ctx, j.p.off_Q);
@@ -604,15 +570,27 @@ int basis_many_impl(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, int K, int
                 else
                     q[i] = QrArgs{nullptr, wsf(ctx, j.p.off_xtt), j.p.nsplit, j.p.rp, wsf(ctx, j.p.off_S), j.L.d_in, j.L.r, out,
                                   wsh(ctx, j.p.off_pack), ctx->ws + j.p.off_qr};
+                // a single column between power steps: the projection that follows normalises its result, one launch less
+                q[i].defer = bf && k < K && xq_narrow(j.L.n_tokens, j.L.d_in, j.L.r);
+                raw[i] = !q[i].defer ? nullptr : q[i].splits ? q[i].S_out : q[i].S;
             }
             {
                 ProfScope ps(ctx, AGZO_PROF_QR);
                 HIPCHK(launch_qr_many(q, n, ctx->flag, k == K, ctx->stream));
             }
-            if (k < K) TRY(stage_sketch_many(ctx, jobs, idx, n, false));
+            if (k < K) TRY(stage_sketch_many(ctx, jobs, idx, n, false, raw));
         }
     }
     return 0;
+}
+
+// Alg. 1 for one layer.  On return (bf16) the workspace planes hold B.
+int op_basis(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* X, int K, uint64_t seed, const float* S0, int flags, float* B) {
+    try {
+        return basis_many_impl(ctx, {LayerJob{L, p, X, seed, S0, B}}, K, flags);
+    } catch (const std::bad_alloc&) {      // (below a C entry)
+        return fail(ctx, AGZO_ENOMEM, "no host memory for the list of one layer");
+    }
 }
 
 // P = X B for every job (one launch per kBatchMax jobs of a dtype and padded rank); bf16: the planes hold its basis

@@ -225,6 +225,8 @@ struct XqArgs {
     const bf16_t* X; int64_t ldx, M, K; const bf16_t* Qpack; int r, rp; float* T; bf16_t* TpackT; int64_t m_pad; float* part;
     bf16_t* Xext = nullptr;
     const float* Q = nullptr;      // the fp32 [K][r] of which Qpack are the planes: what xq_narrow() products read instead
+    // xq_narrow() products: Q is still to be normalised, by the root of the sum of norm_blocks values; *flag = 1 if that is not positive
+    const double* norm2 = nullptr; int norm_blocks = 0; int* flag = nullptr;
 };
 // true: a product that multiplies the fp32 factor itself (one column, few tokens); Qpack may then be NULL
 bool xq_narrow(int64_t M, int64_t K, int r);
@@ -251,7 +253,12 @@ size_t qr_workspace_bytes(int64_t d, int r);
 hipError_t launch_qr(const float* S, const float* splits, int nsplit, int rp, float* S_out, int64_t d, int r, float* Q,
                      bf16_t* planes, void* workspace, int* numeric_flag, bool refine, hipStream_t st);
 
-struct QrArgs { const float* S; const float* splits; int nsplit; int rp; float* S_out; int64_t d; int r; float* Q; bf16_t* planes; void* workspace; };
+struct QrArgs { const float* S; const float* splits; int nsplit; int rp; float* S_out; int64_t d; int r; float* Q; bf16_t* planes; void* workspace;
+    // r = 1: the column is left as it is (in S, or S_out), and its squared norm as qr_norm_blocks(d) partial sums at the workspace's
+    // start, for a product that normalises its result instead (XqArgs::norm2); Q and planes are not written
+    bool defer = false;
+};
+int qr_norm_blocks(int64_t d);
 // up to kBatchMax factorisations with the same rp, each launch of the sequence serving all of them
 hipError_t launch_qr_many(const QrArgs* a, int n, int* numeric_flag, bool refine, hipStream_t st);
 

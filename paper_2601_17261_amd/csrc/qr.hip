@@ -553,14 +553,16 @@ __global__ __launch_bounds__(256) void qr1_scale_kernel(const KBatch<QrDev, CAP>
         if (col < a.d) *reinterpret_cast<uint4*>(a.planes + ((int64_t)pl * rp + 1 + row - pl * rest) * a.d + col) = make_uint4(0, 0, 0, 0);
     }
 }
-static inline int64_t qr1_blocks(int64_t d) { return (d + QR1_ROWS - 1) / QR1_ROWS; }
+int qr_norm_blocks(int64_t d) { return (int)((d + QR1_ROWS - 1) / QR1_ROWS); }
 
+// tb: every column; scaled: those that this factorisation normalises itself
 template <int CAP>
-static hipError_t launch_qr1(const KBatch<QrDev, CAP>& tb, unsigned blocks, int rp, int* flag, hipStream_t st) {
+static hipError_t launch_qr1(const KBatch<QrDev, CAP>& tb, unsigned blocks, const KBatch<QrDev, CAP>& scaled, unsigned scaled_blocks, int rp, int* flag,
+                             hipStream_t st) {
     hipLaunchKernelGGL(qr1_sumsq_kernel<CAP>, dim3(blocks), dim3(256), 0, st, tb, rp);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;      // the launch below consumes what this one would have written
-    hipLaunchKernelGGL(qr1_scale_kernel<CAP>, dim3(blocks), dim3(256), 0, st, tb, rp, flag);
+    if (e != hipSuccess || scaled_blocks == 0) return e;      // the launch below consumes what this one would have written
+    hipLaunchKernelGGL(qr1_scale_kernel<CAP>, dim3(scaled_blocks), dim3(256), 0, st, scaled, rp, flag);
     return hipGetLastError();
 }
 
@@ -593,8 +595,7 @@ static hipError_t launch_qr_rp(const KBatch<QrDev, CAP>& tb, unsigned blocks, in
 }
 
 template <int CAP>
-static hipError_t launch_qr_cap(const KBatch<QrDev, CAP>& tb, unsigned blocks, int rp, bool rank1, int* flag, bool refine, hipStream_t st) {
-    if (rank1) return launch_qr1(tb, blocks, rp, flag, st);
+static hipError_t launch_qr_cap(const KBatch<QrDev, CAP>& tb, unsigned blocks, int rp, int* flag, bool refine, hipStream_t st) {
     switch (rp) {
         case 16: return launch_qr_rp<16>(tb, blocks, flag, refine, st);
         case 32: return launch_qr_rp<32>(tb, blocks, flag, refine, st);
@@ -606,16 +607,16 @@ static hipError_t launch_qr_cap(const KBatch<QrDev, CAP>& tb, unsigned blocks, i
 
 hipError_t launch_qr_many(const QrArgs* a, int n, int* numeric_flag, bool refine, hipStream_t st) {
     if (n < 0 || n > kBatchMax) return hipErrorInvalidValue;
-    KBatch<QrDev> tb;
-    tb.n = 0;
-    uint64_t blocks = 0;
+    KBatch<QrDev> tb, scaled;
+    tb.n = scaled.n = 0;
+    uint64_t blocks = 0, scaled_blocks = 0;
     int rp = 0, rank1 = -1;
     for (int m = 0; m < n; ++m) {
         if (a[m].d == 0) continue;
         if (rp == 0) rp = a[m].rp;
         if (rank1 < 0) rank1 = (a[m].r == 1);
         // one padded rank per launch, and single columns (normalised, not factored) apart from the others
-        if (a[m].rp != rp || (a[m].r == 1) != (rank1 == 1)) return hipErrorInvalidValue;
+        if (a[m].rp != rp || (a[m].r == 1) != (rank1 == 1) || (a[m].defer && a[m].r != 1)) return hipErrorInvalidValue;
         QrDev q;
         q.S = a[m].S; q.splits = a[m].splits; q.nsplit = a[m].nsplit; q.S_out = a[m].S_out;
         q.Sin = a[m].splits ? a[m].S_out : a[m].S;
@@ -625,14 +626,22 @@ hipError_t launch_qr_many(const QrArgs* a, int n, int* numeric_flag, bool refine
         q.partial2 = q.partial1 + (size_t)q.nblk * rp * rp;
         q.Q1 = q.partial2 + (size_t)q.nblk * rp * rp;
         q.Q = a[m].Q; q.planes = a[m].planes;
-        if (rank1 == 1) q.nblk = (int)qr1_blocks(a[m].d);        // (partials: fewer than those reserved)
+        if (rank1 == 1) q.nblk = qr_norm_blocks(a[m].d);        // (partials: fewer than those reserved)
+        if (rank1 == 1 && !a[m].defer) {
+            scaled.first[scaled.n] = (uint32_t)scaled_blocks; scaled.gx[scaled.n] = (uint32_t)q.nblk; scaled.a[scaled.n++] = q;
+            scaled_blocks += (uint64_t)q.nblk;
+        }
         tb.first[tb.n] = (uint32_t)blocks; tb.gx[tb.n] = (uint32_t)q.nblk; tb.a[tb.n++] = q;
         blocks += (uint64_t)q.nblk;
     }
     if (tb.n == 0) return hipSuccess;
     if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    if (tb.n == 1) return launch_qr_cap(kbatch_one(tb), (unsigned)blocks, rp, rank1 == 1, numeric_flag, refine, st);
-    return launch_qr_cap(tb, (unsigned)blocks, rp, rank1 == 1, numeric_flag, refine, st);
+    if (rank1 == 1) {
+        if (tb.n == 1) return launch_qr1(kbatch_one(tb), (unsigned)blocks, kbatch_one(tb), (unsigned)scaled_blocks, rp, numeric_flag, st);
+        return launch_qr1(tb, (unsigned)blocks, scaled, (unsigned)scaled_blocks, rp, numeric_flag, st);
+    }
+    if (tb.n == 1) return launch_qr_cap(kbatch_one(tb), (unsigned)blocks, rp, numeric_flag, refine, st);
+    return launch_qr_cap(tb, (unsigned)blocks, rp, numeric_flag, refine, st);
 }
 
 hipError_t launch_qr(const float* S, const float* splits, int nsplit, int rp, float* S_out, int64_t d, int r, float* Q,

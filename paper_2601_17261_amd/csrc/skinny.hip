@@ -480,6 +480,7 @@ struct XqNarrowDev {
     const bf16_t* X; const float* Q; int64_t ldx, M, K, m_pad;
     float* T; bf16_t* TpackT; bf16_t* Xext;
     int kw, vec;                 // waves that share d_in; 16-byte loads of Q
+    const double* norm2; int norm_blocks; int* flag;
 };
 static int xqn_waves(int64_t K) { return K > 3 * XQN_CHUNK ? 4 : K > XQN_CHUNK ? 2 : 1; }
 
@@ -533,6 +534,23 @@ __device__ __forceinline__ void xq_narrow_body(const XqNarrowDev& a, uint32_t bx
         if (lane == 0) part[wave][t] = acc[t];
     }
     __syncthreads();
+    // a column that is still to be normalised: the result is, as the columns between power steps are by qr1_scale_kernel
+    double scale = 1.0;
+    if (a.norm2 != nullptr) {
+        double sum = 0.0;
+        for (int b0 = 0; b0 < a.norm_blocks; b0 += 16) {           // uniform: every thread adds the same values
+            double v[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) v[u] = b0 + u < a.norm_blocks ? a.norm2[b0 + u] : 0.0;
+#pragma unroll
+            for (int u = 0; u < 16; ++u) sum += v[u];
+        }
+        if (!(sum > 0.0)) {
+            if (tid == 0 && bx == 0) *a.flag = 1;
+            sum = 1.0;
+        }
+        scale = 1.0 / sqrt(sum);
+    }
     // a thread four tokens and a column of the outputs' sixteen: all but the first are zero
     const int g = tid >> 4, k = tid & 15;
     if (g >= 4 / kw) return;
@@ -543,6 +561,7 @@ __device__ __forceinline__ void xq_narrow_body(const XqNarrowDev& a, uint32_t bx
             v[t] = part[g * kw][t];
             if (kw == 2) v[t] += part[g * kw + 1][t];
             if (kw == 4) v[t] = (v[t] + part[1][t]) + (part[2][t] + part[3][t]);
+            v[t] = (float)((double)v[t] * scale);
         }
     }
     xq_emit(v, a.M, 1, 16, a.T, a.TpackT, a.m_pad, a.Xext, ((int64_t)bx * (4 / kw) + g) * XQN_TOK, k);
@@ -559,7 +578,8 @@ __global__ __launch_bounds__(256) void xq_narrow_ext_kernel(const XqNarrowDev a,
 }
 
 static XqNarrowDev xqn_dev(const XqArgs& a, uint64_t& workgroups) {
-    XqNarrowDev d{a.X, a.Q, a.ldx, a.M, a.K, a.m_pad, a.T, a.TpackT, a.Xext, xqn_waves(a.K), (reinterpret_cast<uintptr_t>(a.Q) & 15) == 0};
+    XqNarrowDev d{a.X, a.Q, a.ldx, a.M, a.K, a.m_pad, a.T, a.TpackT, a.Xext, xqn_waves(a.K), (reinterpret_cast<uintptr_t>(a.Q) & 15) == 0,
+                  a.norm2, a.norm_blocks, a.flag};
     const int64_t tok = XQN_TOK * (4 / d.kw);
     workgroups = (uint64_t)(((a.TpackT ? a.m_pad : a.M) + tok - 1) / tok);
     return d;

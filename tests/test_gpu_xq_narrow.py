@@ -55,3 +55,36 @@ def test_many_layers_as_one_by_one():
         ctx.basis(l, x, 2, 3 + i, None, 0, one)
         assert torch.equal(one, b), i
     ctx.check()
+
+
+@pytest.mark.parametrize("scale", [1.0, 1e-12, 1e12])
+@pytest.mark.parametrize("n,d,K", [(300, 1032, 1), (300, 1032, 3), (65, 8, 2), (8191, 264, 2)])
+def test_normalised_by_the_projection(n, d, K, scale):
+    """Between power steps the column stays as the sketch left it and the projection normalises its result.  From a given first sketch
+    of any size, against fp64: each step rounds the column and T to fp32"""
+    ctx = binding.Context()
+    X = torch.randn(n, d, device="cuda").bfloat16()
+    S0 = scale * torch.randn(d, 1, device="cuda")
+    B = torch.empty(d, 1, device="cuda")
+    ctx.basis(binding.make_layer(torch.empty(16, d, device="cuda", dtype=torch.bfloat16), X, 1), X, K, 3, S0, 0, B)
+    ctx.check()
+    q = S0.double() / S0.double().norm()
+    for _ in range(K):
+        q = X.double().T @ (X.double() @ q)
+        q = q / q.norm()
+    assert (B.double() - q).norm() <= (K + 1) * 4e-6
+
+
+def test_zero_column_is_reported():
+    ctx = binding.Context()
+    X = torch.randn(100, 64, device="cuda").bfloat16()
+    B = torch.empty(64, 1, device="cuda")
+    L = binding.make_layer(torch.empty(16, 64, device="cuda", dtype=torch.bfloat16), X, 1)
+    ctx.basis(L, X, 0, 3, torch.zeros(64, 1, device="cuda"), 0, B)
+    with pytest.raises(binding.AgzoError):
+        ctx.check()
+    ctx.basis(L, X, 2, 3, torch.zeros(64, 1, device="cuda"), 0, B)
+    with pytest.raises(binding.AgzoError):
+        ctx.check()
+    ctx.basis(L, X, 2, 3, None, 0, B)
+    ctx.check()
