@@ -21,7 +21,9 @@
  *     operands ldw, ldx and d_in must be multiples of 8 and below 2^22, and
  *     W and X must be 16-byte aligned (16-byte rows).
  *   - Calls only enqueue work on the ctx stream (no host synchronisation)
- *     unless stated.  Calls on one ctx must not overlap from several threads.
+ *     unless stated; agzo_step_many may fork a stream of the context's own
+ *     off it and joins it again before the call's last launches.  Calls on
+ *     one ctx must not overlap from several threads.
  *   - Return value: 0 on success, a negative agzo_status otherwise; the text
  *     of the last error is available from agzo_last_error().
  */
