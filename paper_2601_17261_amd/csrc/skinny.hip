@@ -493,6 +493,11 @@ __device__ __forceinline__ void xq_narrow_body(const XqNarrowDev& a, uint32_t bx
     const bf16_t* xr[XQN_TOK];
 #pragma unroll
     for (int t = 0; t < XQN_TOK; ++t) xr[t] = a.X + min(tw + t, a.M - 1) * a.ldx;
+    // A column that is still to be normalised: the result is, in fp64, as the columns between power steps are by qr1_scale_kernel.  The
+    // column is X^T T of the step before, of size |X|^2, and multiplied as it stands would make sums of size |X|^3: it is read times the
+    // power of two that brings its norm to [1, 2), which is exact, so the bits are the same wherever such sums are normal numbers
+    double scale = 1.0;                        // (set in the waves that have a chunk: wave 0, which writes the results, among them)
+    int down = 0;
     float acc[XQN_TOK] = {};
     const int64_t nchunk = (K + XQN_CHUNK - 1) / XQN_CHUNK;
     for (int64_t c0 = wk; c0 < nchunk; c0 += kw * U) {
@@ -516,9 +521,27 @@ __device__ __forceinline__ void xq_narrow_body(const XqNarrowDev& a, uint32_t bx
                 for (int i = 0; i < 8; ++i) q[u][i] = src[i];
             }
         }
+        if (a.norm2 != nullptr && c0 == wk) {                      // (behind the first chunks' loads: ahead of them the bases of 12288-wide layers take 1 to 4 % longer)
+            double sum = 0.0;
+            for (int b0 = 0; b0 < a.norm_blocks; b0 += 16) {       // uniform: every thread adds the same values
+                double v[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) v[i] = b0 + i < a.norm_blocks ? a.norm2[b0 + i] : 0.0;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) sum += v[i];
+            }
+            if (!(sum > 0.0)) {
+                if (tid == 0 && bx == 0) *a.flag = 1;
+                sum = 1.0;
+            }
+            down = ((__double2hiint(sum) >> 20) - 1023) >> 1;      // (squares of fp32 values: never subnormal)
+            scale = ldexp(1.0 / sqrt(sum), down);
+        }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if ((c0 + u * kw) * XQN_CHUNK + 8 * lane >= K) continue;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) q[u][i] = ldexpf(q[u][i], -down);
 #pragma unroll
             for (int t = 0; t < XQN_TOK; ++t) {
                 const uint32_t w[4] = {x[u][t].x, x[u][t].y, x[u][t].z, x[u][t].w};
@@ -534,23 +557,6 @@ __device__ __forceinline__ void xq_narrow_body(const XqNarrowDev& a, uint32_t bx
         if (lane == 0) part[wave][t] = acc[t];
     }
     __syncthreads();
-    // a column that is still to be normalised: the result is, as the columns between power steps are by qr1_scale_kernel
-    double scale = 1.0;
-    if (a.norm2 != nullptr) {
-        double sum = 0.0;
-        for (int b0 = 0; b0 < a.norm_blocks; b0 += 16) {           // uniform: every thread adds the same values
-            double v[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) v[u] = b0 + u < a.norm_blocks ? a.norm2[b0 + u] : 0.0;
-#pragma unroll
-            for (int u = 0; u < 16; ++u) sum += v[u];
-        }
-        if (!(sum > 0.0)) {
-            if (tid == 0 && bx == 0) *a.flag = 1;
-            sum = 1.0;
-        }
-        scale = 1.0 / sqrt(sum);
-    }
     // a thread four tokens and a column of the outputs' sixteen: all but the first are zero
     const int g = tid >> 4, k = tid & 15;
     if (g >= 4 / kw) return;

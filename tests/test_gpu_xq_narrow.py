@@ -75,6 +75,39 @@ def test_normalised_by_the_projection(n, d, K, scale):
     assert (B.double() - q).norm() <= (K + 1) * 4e-6
 
 
+@pytest.mark.parametrize("of_x,of_s0", [(1e-16, 1.0), (1e-12, 1.0), (1e12, 1.0), (1e16, 1.0), (1.0, 1e-37), (1.0, 1e37), (1e16, 1e37), (1e-16, 1e-37)])
+@pytest.mark.parametrize("n,d,K", [(300, 1032, 1), (65, 8, 3), (8191, 264, 2)])
+def test_range_of_a_column_left_to_be_normalised(n, d, K, of_x, of_s0):
+    """A sketch is of size |X|^2, and so is the column between power steps: activations and first sketches whose squares fp32 holds
+    lose nothing, though the product of such a column with X is of size |X|^3.  Bound as above"""
+    ctx = binding.Context()
+    X = (of_x * torch.randn(n, d, device="cuda")).bfloat16()
+    S0 = of_s0 * torch.randn(d, 1, device="cuda")
+    B = torch.empty(d, 1, device="cuda")
+    L = binding.make_layer(torch.empty(16, d, device="cuda", dtype=torch.bfloat16), X, 1)
+    ctx.basis(L, X, K, 3, S0, 0, B)
+    ctx.check()
+    q = S0.double() / S0.double().norm()
+    for _ in range(K):
+        q = X.double().T @ (X.double() @ q)
+        q = q / q.norm()
+    assert (B.double() - q).norm() <= (K + 1) * 4e-6
+
+
+@pytest.mark.parametrize("e", [-54, -40, 40, 50])
+def test_powers_of_two_give_the_same_bits(e):
+    """every rounding of a basis scales with a power of two"""
+    ctx = binding.Context()
+    n, d = 300, 1032
+    X = torch.randn(n, d, device="cuda").bfloat16()
+    L = binding.make_layer(torch.empty(16, d, device="cuda", dtype=torch.bfloat16), X, 1)
+    got = torch.empty(2, d, 1, device="cuda")
+    ctx.basis(L, X, 3, 3, None, 0, got[0])
+    ctx.basis(L, X * 2.0 ** e, 3, 3, None, 0, got[1])
+    ctx.check()
+    assert torch.equal(got[0], got[1])
+
+
 def test_zero_column_is_reported():
     ctx = binding.Context()
     X = torch.randn(100, 64, device="cuda").bfloat16()
