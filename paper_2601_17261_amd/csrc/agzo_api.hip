@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "agzo_internal.h"
+#include "fork.h"
 
 using namespace agzo;
 
@@ -37,7 +38,6 @@ struct agzo_ctx {
     // base forwards of a set of layers run on a stream of the context's own beside the extraction (step_many_body)
     hipStream_t side;
     hipEvent_t fork, join;
-    bool beside;           // forwards on `side` may hold half of every compute unit: launches on `stream` should fit the other half
     // clock telemetry: kClkSlots records of four 64-bit words (one per timed GEMM launch), then the probe's record
     unsigned long long* clk;
     size_t clk_used;
@@ -179,6 +179,7 @@ constexpr size_t kMapBytes = (size_t)2 << 20;
 int reserve(agzo_ctx* ctx, size_t bytes) {
     if (bytes <= ctx->ws_bytes) return 0;
     HIPCHK(hipStreamSynchronize(ctx->stream));
+    if (ctx->side) HIPCHK(hipStreamSynchronize(ctx->side));      // (joined to the above, unless joining failed)
     // a context that needs more once will need more again (the layers of a model, one after the other): half as much again, up to the
     // 2 MiB that device memory is mapped by.  (A growth is up to 0.5 ms of a first pass: the dense estimator's over seven 0.6B-sized
     // layers on 1131 tokens takes 0.97 ms growing by what a call needs, 1.24 by half, 0.77 so)
@@ -251,31 +252,13 @@ int check_loss(agzo_ctx* ctx, const agzo_layer* L, const agzo_loss_spec* loss, c
     return 0;
 }
 
-// Work on `side` between what is on the context's stream when it is opened and what comes there after close(), which also every
-// return in between makes wait: to the caller all of it is work on the context's stream
-struct Beside {
-    agzo_ctx* ctx;
-    bool open = false;
-    explicit Beside(agzo_ctx* c) : ctx(c) {}
-    template <typename F>
-    int run(F launches) {
-        HIPCHK(hipEventRecord(ctx->fork, ctx->stream));
-        HIPCHK(hipStreamWaitEvent(ctx->side, ctx->fork, 0));
-        open = ctx->beside = true;
-        const hipError_t e = launches(ctx->side);
-        HIPCHK(hipEventRecord(ctx->join, ctx->side));
-        HIPCHK(e);
-        return 0;
-    }
-    int close() {
-        if (!open) return 0;
-        open = ctx->beside = false;
-        HIPCHK(hipStreamWaitEvent(ctx->stream, ctx->join, 0));
-        return 0;
-    }
-    ~Beside() {
-        if (open) (void)close();
-    }
+struct HipApi {
+    typedef hipStream_t stream_t;
+    typedef hipEvent_t event_t;
+    typedef hipError_t error_t;
+    static hipError_t record(hipEvent_t e, hipStream_t s) { return hipEventRecord(e, s); }
+    static hipError_t wait(hipStream_t s, hipEvent_t e) { return hipStreamWaitEvent(s, e, 0); }
+    static hipError_t synchronize(hipStream_t s) { return hipStreamSynchronize(s); }
 };
 
 // ---- internal building blocks; all take a ready workspace plan --------------------------------
@@ -314,7 +297,7 @@ int sketch_power(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* 
             ProfScope ps(ctx, AGZO_PROF_XQ);
             const XqArgs q{static_cast<const bf16_t*>(X), L.ldx, L.n_tokens, L.d_in, wsh(ctx, p.off_pack), L.r, p.rp, nullptr,
                            wsh(ctx, p.off_TpackT), p.m_pad, wsf(ctx, p.off_xqpart), nullptr, Q};
-            HIPCHK(launch_xq_bf16_many(&q, 1, ctx->beside, st));
+            HIPCHK(launch_xq_bf16_many(&q, 1, false, st));
         }
         ProfScope ps(ctx, AGZO_PROF_XTT);
         HIPCHK(launch_xtt_bf16(static_cast<const bf16_t*>(X), L.ldx, L.n_tokens, L.d_in, wsh(ctx, p.off_TpackT),
@@ -488,7 +471,8 @@ int stage_sketch_many_f32(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, cons
 
 // one stage for the jobs idx[0..n) (one dtype): Omega^T planes + range sketch, or T = X Q planes + power sketch
 // raw (power sketch; nullable): per job of idx the column that the last factorisation left to be normalised, NULL where Q is ready
-int stage_sketch_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, const int* idx, int n, bool range, const float* const* raw = nullptr) {
+// half_cu (here and below): forwards on another stream may hold half of every compute unit
+int stage_sketch_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, const int* idx, int n, bool range, bool half_cu, const float* const* raw = nullptr) {
     if (n > 0 && jobs[idx[0]].L.dtype != AGZO_BF16) return stage_sketch_many_f32(ctx, jobs, idx, n, range);
     hipStream_t st = ctx->stream;
     if (range) {
@@ -513,7 +497,7 @@ int stage_sketch_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, const in
             }
         }
         ProfScope ps(ctx, AGZO_PROF_XQ);
-        HIPCHK(launch_xq_bf16_many(q, n, ctx->beside, st));
+        HIPCHK(launch_xq_bf16_many(q, n, half_cu, st));
     }
     XttArgs t[kBatchMax];
     for (int i = 0; i < n; ++i) {
@@ -528,7 +512,7 @@ int stage_sketch_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, const in
 
 // Alg. 1 for every job.  Jobs that share a dtype and a padded rank go through the batched kernels, at most kBatchMax per
 // launch.  On return every bf16 job's workspace planes hold its basis.
-int basis_many_impl(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, int K, int flags) {
+int basis_many_impl(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, int K, int flags, bool half_cu = false) {
     std::vector<char> done(jobs.size(), 0);
     for (size_t a = 0; a < jobs.size(); ++a) {
         if (done[a]) continue;
@@ -557,7 +541,7 @@ int basis_many_impl(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, int K, int
                 need_idx[n_need++] = idx[i];
             }
         }
-        if (n_need) TRY(stage_sketch_many(ctx, jobs, need_idx, n_need, !(flags & AGZO_INIT_FEATURE)));
+        if (n_need) TRY(stage_sketch_many(ctx, jobs, need_idx, n_need, !(flags & AGZO_INIT_FEATURE), half_cu));
         for (int k = 0; k <= K; ++k) {
             QrArgs q[kBatchMax];
             const float* raw[kBatchMax];
@@ -578,7 +562,7 @@ int basis_many_impl(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, int K, int
                 ProfScope ps(ctx, AGZO_PROF_QR);
                 HIPCHK(launch_qr_many(q, n, ctx->flag, k == K, ctx->stream));
             }
-            if (k < K) TRY(stage_sketch_many(ctx, jobs, idx, n, false, raw));
+            if (k < K) TRY(stage_sketch_many(ctx, jobs, idx, n, false, half_cu, raw));
         }
     }
     return 0;
@@ -594,7 +578,7 @@ int op_basis(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* X, i
 }
 
 // P = X B for every job (one launch per kBatchMax jobs of a dtype and padded rank); bf16: the planes hold its basis
-int project_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs) {
+int project_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, bool half_cu) {
     std::vector<char> done(jobs.size(), 0);
     for (size_t a = 0; a < jobs.size(); ++a) {
         if (done[a]) continue;
@@ -621,7 +605,7 @@ int project_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs) {
             done[b] = 1;
         }
         ProfScope ps(ctx, AGZO_PROF_XQ);
-        HIPCHK(launch_xq_bf16_many(q, n, ctx->beside, ctx->stream));
+        HIPCHK(launch_xq_bf16_many(q, n, half_cu, ctx->stream));
     }
     return 0;
 }
@@ -684,7 +668,6 @@ int agzo_create(agzo_ctx** out, void* hip_stream) {
     ctx->clk_used = 0;
     ctx->side = nullptr;
     ctx->fork = ctx->join = nullptr;
-    ctx->beside = false;
     ctx->device = -1;
     ctx->static_scratch = nullptr;
     hipError_t e = hipGetDevice(&ctx->device);
@@ -711,8 +694,11 @@ int agzo_create(agzo_ctx** out, void* hip_stream) {
 
 void agzo_destroy(agzo_ctx* ctx) {
     if (!ctx) return;
-    (void)hipStreamSynchronize(ctx->stream);      // (what ran on `side` has been waited for there)
-    if (ctx->side) (void)hipStreamDestroy(ctx->side);
+    (void)hipStreamSynchronize(ctx->stream);
+    if (ctx->side) {
+        (void)hipStreamSynchronize(ctx->side);    // (joined to the above, unless joining failed)
+        (void)hipStreamDestroy(ctx->side);
+    }
     if (ctx->fork) (void)hipEventDestroy(ctx->fork);
     if (ctx->join) (void)hipEventDestroy(ctx->join);
     if (ctx->ws) (void)hipFree(ctx->ws);
@@ -1066,7 +1052,7 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
     TRY(reserve(ctx, total + upd_bytes));
     for (int m = 0; m < n; ++m) jobs[(size_t)m].B = items[m].B_out ? items[m].B_out : wsf(ctx, jobs[(size_t)m].p.off_B);
     hipStream_t st = ctx->stream;
-    Beside beside(ctx);
+    Fork<HipApi> beside(st, ctx->side, ctx->fork, ctx->join);
 
     // the squared-error evaluations of phases [ph0, ph1): 0 = f0 (or, shared, all three from one pass), 1 = f+, 2 = f-; the
     // loss partials of phase ph go to slot ph of the layer's region
@@ -1103,8 +1089,10 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
         for (size_t b = 0; b < f32.size(); b += kBatchMax)
             HIPCHK(launch_forward_f32_many(f32.data() + b, (int)std::min(f32.size() - b, (size_t)kBatchMax), st));
         if (bf.empty()) return 0;
-        if (ph1 == 1 && !shared && ctx->prof == 0 && ctx->side && n >= kBesideLayers && flops >= kBesideFlops)
-            return beside.run([&](hipStream_t side) { return launch_gemm_bf16_many(bf.data(), (int)bf.size(), true, side); });
+        if (ph1 == 1 && !shared && ctx->prof == 0 && ctx->side && n >= kBesideLayers && flops >= kBesideFlops) {
+            HIPCHK(beside.run([&](hipStream_t side) { return launch_gemm_bf16_many(bf.data(), (int)bf.size(), true, side); }));
+            return 0;
+        }
         for (size_t b = 0; b < ext.size(); b += kBatchMax)
             HIPCHK(launch_gemm_ext_prep_many(ext.data() + b, (int)std::min(ext.size() - b, (size_t)kBatchMax), st));
         if (!timed(ctx, AGZO_PROF_GEMM)) {
@@ -1128,9 +1116,9 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
         TRY(forward_mse(0, 1));
         for (int m = 0; m < n; ++m) TRY(forward_ce(m, nullptr, 0.f, items[m].out_dev, false, 0));
     }
-    TRY(basis_many_impl(ctx, jobs, K, flags & AGZO_INIT_FEATURE));
+    TRY(basis_many_impl(ctx, jobs, K, flags & AGZO_INIT_FEATURE, beside.open()));
     // parts 2-3: the perturbed evaluations
-    TRY(project_many(ctx, jobs));
+    TRY(project_many(ctx, jobs, beside.open()));
     if (shared) TRY(forward_mse(0, 1));
     else TRY(forward_mse(1, one_sided ? 2 : 3));
     for (int m = 0; m < n; ++m) {
@@ -1142,7 +1130,7 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
             if (!one_sided) TRY(forward_ce(m, P, -eps, items[m].out_dev + 2, false, 2));
         }
     }
-    TRY(beside.close());
+    HIPCHK(beside.close());
     // the scalars, then every update in one batched call
     std::vector<agzo_update_item> upd;
     std::vector<FinishTwoPointArgs> fin;
