@@ -1020,9 +1020,15 @@ int agzo_basis_many(agzo_ctx* ctx, const agzo_basis_item* items, int32_t n, int3
 namespace {
 // The base forwards need nothing of the extraction nor it of them, and the extraction is a chain of some twenty launches that are bound by
 // latency or by memory: for a set of layers they run beside it, those in 128 x 128 tiles on half of every compute unit.  The two streams
-// wait for each other twice, some 20 us.  Measured (us a step, one stream and two): seven layers 0.6B-sized on 512 tokens (16 GFLOP) 233
+// wait for each other twice, some 20 us, and what counts is the layers whose forwards run there (bf16, squared error), not those of the
+// call (one 4096 x 4096 layer on 1024 tokens among three small fp32 ones: 349 us a step, 389 with two streams).  Measured (us a step, one
+// stream and two): seven layers 0.6B-sized on 512 tokens (16 GFLOP) 233
 // and 233, on 1024 299 and 290, on 2048 428 and 416, 4B-sized on 128 383 and 360, on 512 617 and 570, on 3001 2075 and 1935; four
-// of them on 512 272 and 265, on 4096 790 and 750; two on 4096 444 and 452; one 4096 x 4096 layer on 1024 tokens 232 and 249
+// of them on 512 272 and 265, on 4096 790 and 750; two on 4096 444 and 452; one 4096 x 4096 layer on 1024 tokens 232 and 249.
+// The rule has no line for the rank or the tiles of the forwards.  At r > 16 the second form of X^T T needs more LDS than forwards in
+// 128 x 128 tiles leave, and starts where those end; forwards in 256 x 256 tiles hold whole compute units, and the extraction fills the
+// rounds that they do not: 4B-sized on 512 tokens 682 and 642 at r = 32, 899 and 887 at 64, on 4096 2786 and 2676, 3183 and 3005 (with
+// their large tiles on the context's stream 2779 and 3177), 8B-sized on 16384, r = 16, 15173 and 14976
 constexpr int kBesideLayers = 4;
 constexpr double kBesideFlops = 20e9;
 // Alg. 2 for n single-layer problems (agzo_step_many; agzo_step is the same with n = 1, so that their results agree bit for
@@ -1089,7 +1095,7 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
         for (size_t b = 0; b < f32.size(); b += kBatchMax)
             HIPCHK(launch_forward_f32_many(f32.data() + b, (int)std::min(f32.size() - b, (size_t)kBatchMax), st));
         if (bf.empty()) return 0;
-        if (ph1 == 1 && !shared && ctx->prof == 0 && ctx->side && n >= kBesideLayers && flops >= kBesideFlops) {
+        if (ph1 == 1 && !shared && ctx->prof == 0 && ctx->side && (int)bf.size() >= kBesideLayers && flops >= kBesideFlops) {
             HIPCHK(beside.run([&](hipStream_t side) { return launch_gemm_bf16_many(bf.data(), (int)bf.size(), true, side); }));
             return 0;
         }

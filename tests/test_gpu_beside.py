@@ -1,6 +1,8 @@
 """Sets of layers large enough for their base forwards to run on the context's second stream: to the caller all of it is work on the
 context's stream (inputs written there just before, weights and inputs overwritten just after), the results are those of a call per
 layer, bit for bit, and a captured step replays."""
+import ctypes
+
 import pytest
 import torch
 
@@ -84,4 +86,55 @@ def test_captured():
     with torch.cuda.stream(stream):
         ctx.step_many(_items(layers, out, r), 3, EPS, LR, 0)      # the context's own streams are as before
         ctx.check()
+    ctx.close()
+
+
+def _forks(stream, call):
+    """whether the launches of a call are no single chain: a captured chain has one edge less than nodes"""
+    graph, before = torch.cuda.CUDAGraph(keep_graph=True), torch.zeros(1, device="cuda")
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        before.add_(1)          # what the fork follows
+        call()
+    lib, raw = binding.load(), ctypes.c_void_p(graph.raw_cuda_graph())
+    nodes, edges = ctypes.c_size_t(0), ctypes.c_size_t(0)
+    assert lib.hipGraphGetNodes(raw, None, ctypes.byref(nodes)) == 0
+    assert lib.hipGraphGetEdges(raw, None, None, ctypes.byref(edges)) == 0
+    assert nodes.value > 10 and edges.value >= nodes.value - 1
+    return edges.value >= nodes.value
+
+
+def _mixed(n_bf16, n_f32, n_ce, tokens=900, r=4):
+    """(W, X, loss with its target) of squared-error layers in bf16, each of 24 GFLOP a forward on 900 tokens, in fp32, and of heads"""
+    got = []
+    for i in range(n_bf16):
+        x = synth.device_powerlaw_x(i, tokens, 2600)
+        w, t = synth.device_weights_and_target(50 + i, x, 5200)
+        got.append((w, x, t, binding.make_loss(t)))
+    for i in range(n_f32):
+        w, x, t = (torch.randn(s, device="cuda") for s in ((96, 200), (333, 200), (333, 96)))
+        got.append((w, x, t, binding.make_loss(t)))
+    for i in range(n_ce):
+        w, x = (torch.randn(s, device="cuda").bfloat16() for s in ((1000, 264), (300, 264)))
+        t = torch.randint(0, 1000, (300,), device="cuda", dtype=torch.int32)
+        got.append((w, x, t, binding.make_loss(t, kind=binding.LOSS_CE)))
+    out = torch.zeros(len(got), 4, dtype=torch.float64, device="cuda")
+    return got, out, [(binding.make_layer(w, x, r), w, x, loss, 30 + i, out[i], None) for i, (w, x, _, loss) in enumerate(got)]
+
+
+@pytest.mark.parametrize("n_bf16,n_f32,n_ce,forks", [(4, 0, 0, True), (1, 3, 0, False), (1, 0, 3, False), (2, 2, 2, False), (3, 1, 0, False), (4, 1, 1, True)])
+def test_the_layers_that_count(n_bf16, n_f32, n_ce, forks):
+    """two streams pay from four layers on whose forwards run on the second one; other layers of the list are not among them"""
+    stream = torch.cuda.Stream()
+    ctx = binding.Context(stream=stream)
+    _, _, items = _mixed(n_bf16, n_f32, n_ce)
+    torch.cuda.synchronize()
+
+    def call():
+        ctx.step_many(items, 3, EPS, LR, 0)
+    with torch.cuda.stream(stream):
+        call()
+        stream.synchronize()
+    assert _forks(stream, call) == forks
+    ctx.check()
     ctx.close()
