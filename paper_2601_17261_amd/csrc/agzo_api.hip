@@ -1029,8 +1029,26 @@ namespace {
 // 128 x 128 tiles leave, and starts where those end; forwards in 256 x 256 tiles hold whole compute units, and the extraction fills the
 // rounds that they do not: 4B-sized on 512 tokens 682 and 642 at r = 32, 899 and 887 at 64, on 4096 2786 and 2676, 3183 and 3005 (with
 // their large tiles on the context's stream 2779 and 3177), 8B-sized on 16384, r = 16, 15173 and 14976
+// Forwards in 128 x 128 tiles should not outlast the extraction: they would stay on half of every compute unit, and the perturbed ones
+// that follow find no room beside them (8B-sized, r = 1, on 768 tokens 1122 and 1231, on 2304 2647 and 2774).  The extraction takes time
+// for its launches (more with a factorisation than with a norm), the rank and the sweeps over X: with K = 3 and up to
+// 200 + 60 [r > 1] + r GFLOP and 800 per value of X, two streams were never more than 1.2 % slower over the three sets' sizes, 256
+// to 16384 tokens and r = 1 to 64, and no more than 0.7 % faster beyond
 constexpr int kBesideLayers = 4;
 constexpr double kBesideFlops = 20e9;
+bool beside_fits(const std::vector<GemmBf16Args>& forwards, int K) {
+    double half_cu = 0.0, values = 0.0, flops = 0.0;
+    int r = 1;
+    for (const GemmBf16Args& a : forwards) {
+        const double f = 2.0 * (double)a.M * (double)a.N * (double)a.K;
+        flops += f;
+        if (gemm_bf16_small_tiles(a.M, a.N, a.large_tiles)) half_cu += f;
+        values += (double)a.M * (double)a.K;
+        r = std::max(r, a.r);
+    }
+    return (int)forwards.size() >= kBesideLayers && flops >= kBesideFlops &&
+           half_cu <= (1e9 * (200 + (r > 1 ? 60 : 0) + r) + 800.0 * values) * ((2 * K + 2) / 8.0);
+}
 // Alg. 2 for n single-layer problems (agzo_step_many; agzo_step is the same with n = 1, so that their results agree bit for
 // bit).  Squared-error layers run every stage together: the evaluations of part 1 (f0, or all three in the shared schedule) and
 // of part 2 (f+ and f-) go to the launch functions as one list, and one launch finishes every loss and scalar.  Cross-entropy
@@ -1067,7 +1085,6 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
         std::vector<F32FwdArgs> f32;
         std::vector<GemmExtArgs> ext;
         const bool perturbed = shared || ph0 > 0;
-        double flops = 0.0;
         for (int m = 0; m < n; ++m) {
             const agzo_step_item& it = items[m];
             if (it.loss.kind != AGZO_LOSS_MSE) continue;
@@ -1087,7 +1104,6 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
                 } else {
                     bf.push_back(forward_bf16_args(ctx, j.L, j.p, it.W, it.X, P, e, it.seed, nullptr, la, shared));
                     bf.back().ext_ready = pair;
-                    flops += 2.0 * (double)j.L.n_tokens * (double)j.L.d_in * (double)j.L.d_out;
                     bf.back().ext_side = ph == 2 ? 1 : 0;
                 }
             }
@@ -1095,7 +1111,7 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
         for (size_t b = 0; b < f32.size(); b += kBatchMax)
             HIPCHK(launch_forward_f32_many(f32.data() + b, (int)std::min(f32.size() - b, (size_t)kBatchMax), st));
         if (bf.empty()) return 0;
-        if (ph1 == 1 && !shared && ctx->prof == 0 && ctx->side && (int)bf.size() >= kBesideLayers && flops >= kBesideFlops) {
+        if (ph1 == 1 && !shared && ctx->prof == 0 && ctx->side && beside_fits(bf, K)) {
             HIPCHK(beside.run([&](hipStream_t side) { return launch_gemm_bf16_many(bf.data(), (int)bf.size(), true, side); }));
             return 0;
         }

@@ -173,6 +173,8 @@ struct GemmBf16Args {
 int gemm_bf16_num_workgroups(int64_t M, int64_t N, bool small_ok);
 size_t gemm_bf16_ext_bytes(int64_t M, int64_t N, int r);
 size_t gemm_bf16_split_bytes(int64_t M, int64_t N, int64_t K);
+// true: a squared-error forward of this shape (not in shared-forward mode) runs in the 128 x 128 tiling
+bool gemm_bf16_small_tiles(int64_t M, int64_t N, bool large_tiles);
 // true: a plain forward of this shape (no rank-r term, no shared-forward mode, no cross-entropy) runs in the 128 x 128
 // tiling, whose kernel can emit the range sketch from its LDS-staged X tiles (r <= 16, at most 64 token tiles)
 bool gemm_bf16_fuses_sketch(int64_t M, int64_t N, int r, bool large_tiles);

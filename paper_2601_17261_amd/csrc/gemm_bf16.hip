@@ -28,8 +28,10 @@ static bool small_shape(int64_t M, int64_t N) {
     return ((M + BT - 1) / BT) * ((N + BT - 1) / BT) < 160;
 }
 
+bool gemm_bf16_small_tiles(int64_t M, int64_t N, bool large_tiles) { return !large_tiles && small_shape(M, N); }
+
 bool gemm_bf16_fuses_sketch(int64_t M, int64_t N, int r, bool large_tiles) {
-    return !large_tiles && small_shape(M, N) && r <= 16 && gemm_bf16_sketch_splits(M) <= 64;
+    return gemm_bf16_small_tiles(M, N, large_tiles) && r <= 16 && gemm_bf16_sketch_splits(M) <= 64;
 }
 
 int gemm_bf16_ce_chunks(int64_t N) { return (int)((N + BT - 1) / BT) * 2; }   // 128-column chunks (2 per tile)

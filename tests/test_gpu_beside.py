@@ -138,3 +138,28 @@ def test_the_layers_that_count(n_bf16, n_f32, n_ce, forks):
     assert _forks(stream, call) == forks
     ctx.check()
     ctx.close()
+
+
+# four layers of 77 GFLOP a forward, in 128 x 128 tiles: longer than one column's extraction, not than 64 columns'; in the other tiling
+# nothing is left waiting on half of the compute units
+@pytest.mark.parametrize("r,K,large,forks", [(1, 3, False, False), (1, 6, False, True), (64, 3, False, True), (64, 0, False, False), (1, 3, True, True)])
+def test_forwards_that_outlast_the_extraction(r, K, large, forks):
+    stream = torch.cuda.Stream()
+    ctx = binding.Context(stream=stream)
+    x = torch.randn(768, 4096, device="cuda").bfloat16()
+    w, t = torch.randn(12288, 4096, device="cuda").bfloat16(), torch.randn(768, 12288, device="cuda").bfloat16()
+    layer = binding.make_layer(w, x, r)
+    layer.tiling = binding.TILING_LARGE if large else binding.TILING_AUTO
+    out = torch.zeros(4, 4, dtype=torch.float64, device="cuda")
+    b = torch.empty(4, 4096, r, device="cuda")
+    items = [(layer, w, x, binding.make_loss(t), i, out[i], b[i]) for i in range(4)]
+    torch.cuda.synchronize()
+
+    def call():
+        ctx.step_many(items, K, EPS, LR, 0)
+    with torch.cuda.stream(stream):
+        call()
+        stream.synchronize()
+    assert _forks(stream, call) == forks
+    ctx.check()
+    ctx.close()
