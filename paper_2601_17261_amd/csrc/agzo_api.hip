@@ -35,7 +35,7 @@ struct agzo_ctx {
     int* flag;   // device int: deferred numeric failure
     uint32_t prof;      // mask of timed kernel classes (bit = AGZO_PROF_* value)
     ProfClass pc[AGZO_PROF_KINDS];
-    // base forwards of a set of layers run on a stream of the context's own beside the extraction (step_many_body)
+    // base forwards of a set of layers run on a stream of the context's own beside the extraction (step_many_body); NULL: not made yet
     hipStream_t side;
     hipEvent_t fork, join;
     // clock telemetry: kClkSlots records of four 64-bit words (one per timed GEMM launch), then the probe's record
@@ -260,6 +260,33 @@ struct HipApi {
     static hipError_t wait(hipStream_t s, hipEvent_t e) { return hipStreamWaitEvent(s, e, 0); }
     static hipError_t synchronize(hipStream_t s) { return hipStreamSynchronize(s); }
 };
+
+void drop_side(agzo_ctx* ctx) {
+    if (ctx->side) (void)hipStreamDestroy(ctx->side);
+    if (ctx->fork) (void)hipEventDestroy(ctx->fork);
+    if (ctx->join) (void)hipEventDestroy(ctx->join);
+    ctx->side = nullptr;
+    ctx->fork = ctx->join = nullptr;
+}
+// The second stream and its events, made by the first call that takes them: most contexts never do, and they took longer than
+// all else of agzo_create (33 us with them, 10 without).  false: a call that cannot have them - the current device is not the context's,
+// or its stream is being captured and they are not there yet - runs in one stream, with the same results
+bool have_side(agzo_ctx* ctx) {
+    if (ctx->side) return true;
+    int dev = -1;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusActive;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipStreamIsCapturing(ctx->stream, &capture);
+    if (e == hipSuccess && (dev != ctx->device || capture != hipStreamCaptureStatusNone)) return false;
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->fork, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->join, hipEventDisableTiming);
+    // (non-blocking: the context's stream may be the default stream, which others would otherwise wait for)
+    if (e == hipSuccess) e = hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking);
+    if (e == hipSuccess) return true;
+    (void)hipGetLastError();
+    drop_side(ctx);
+    return false;
+}
 
 // ---- internal building blocks; all take a ready workspace plan --------------------------------
 inline float* wsf(agzo_ctx* c, size_t off) { return reinterpret_cast<float*>(c->ws + off); }
@@ -676,15 +703,9 @@ int agzo_create(agzo_ctx** out, void* hip_stream) {
     if (e == hipSuccess) e = hipMemset(ctx->flag, 0, 256);
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&ctx->clk), kClkBytes);
     if (e == hipSuccess) e = hipMemset(ctx->clk, 0, kClkBytes);
-    // (non-blocking: the context's stream may be the default stream, which others would otherwise wait for)
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->fork, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->join, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking);
     if (e != hipSuccess) {
         if (ctx->flag) (void)hipFree(ctx->flag);
         if (ctx->clk) (void)hipFree(ctx->clk);
-        if (ctx->fork) (void)hipEventDestroy(ctx->fork);
-        if (ctx->join) (void)hipEventDestroy(ctx->join);
         delete ctx;
         return AGZO_EHIP;
     }
@@ -695,12 +716,8 @@ int agzo_create(agzo_ctx** out, void* hip_stream) {
 void agzo_destroy(agzo_ctx* ctx) {
     if (!ctx) return;
     (void)hipStreamSynchronize(ctx->stream);
-    if (ctx->side) {
-        (void)hipStreamSynchronize(ctx->side);    // (joined to the above, unless joining failed)
-        (void)hipStreamDestroy(ctx->side);
-    }
-    if (ctx->fork) (void)hipEventDestroy(ctx->fork);
-    if (ctx->join) (void)hipEventDestroy(ctx->join);
+    if (ctx->side) (void)hipStreamSynchronize(ctx->side);      // (joined to the above, unless joining failed)
+    drop_side(ctx);
     if (ctx->ws) (void)hipFree(ctx->ws);
     if (ctx->flag) (void)hipFree(ctx->flag);
     if (ctx->clk) (void)hipFree(ctx->clk);
@@ -1033,7 +1050,8 @@ namespace {
 // that follow find no room beside them (8B-sized, r = 1, on 768 tokens 1122 and 1231, on 2304 2647 and 2774).  The extraction takes time
 // for its launches (more with a factorisation than with a norm), the rank and the sweeps over X: with K = 3 and up to
 // 200 + 60 [r > 1] + r GFLOP and 800 per value of X, two streams were never more than 1.2 % slower over the three sets' sizes, 256
-// to 16384 tokens and r = 1 to 64, and no more than 0.7 % faster beyond
+// to 16384 tokens and r = 1 to 64, and no more than 0.7 % faster beyond; with K from 0 to 6 the line taken as the number of sweeps
+// never more than 3 % slower (without it up to 13)
 constexpr int kBesideLayers = 4;
 constexpr double kBesideFlops = 20e9;
 bool beside_fits(const std::vector<GemmBf16Args>& forwards, int K) {
@@ -1076,7 +1094,7 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
     TRY(reserve(ctx, total + upd_bytes));
     for (int m = 0; m < n; ++m) jobs[(size_t)m].B = items[m].B_out ? items[m].B_out : wsf(ctx, jobs[(size_t)m].p.off_B);
     hipStream_t st = ctx->stream;
-    Fork<HipApi> beside(st, ctx->side, ctx->fork, ctx->join);
+    Fork<HipApi> beside(st);
 
     // the squared-error evaluations of phases [ph0, ph1): 0 = f0 (or, shared, all three from one pass), 1 = f+, 2 = f-; the
     // loss partials of phase ph go to slot ph of the layer's region
@@ -1111,8 +1129,8 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
         for (size_t b = 0; b < f32.size(); b += kBatchMax)
             HIPCHK(launch_forward_f32_many(f32.data() + b, (int)std::min(f32.size() - b, (size_t)kBatchMax), st));
         if (bf.empty()) return 0;
-        if (ph1 == 1 && !shared && ctx->prof == 0 && ctx->side && beside_fits(bf, K)) {
-            HIPCHK(beside.run([&](hipStream_t side) { return launch_gemm_bf16_many(bf.data(), (int)bf.size(), true, side); }));
+        if (ph1 == 1 && !shared && ctx->prof == 0 && beside_fits(bf, K) && have_side(ctx)) {
+            HIPCHK(beside.run(ctx->side, ctx->fork, ctx->join, [&](hipStream_t side) { return launch_gemm_bf16_many(bf.data(), (int)bf.size(), true, side); }));
             return 0;
         }
         for (size_t b = 0; b < ext.size(); b += kBatchMax)
