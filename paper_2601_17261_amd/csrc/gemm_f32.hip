@@ -23,18 +23,23 @@ template <int V> struct IC { static constexpr int value = V; };
 // conversions.  The vector-unit version it replaces (a 4 x 4 register tile per thread) converted eight values from LDS for
 // every 16 multiplications, loaded without a prefetch, and ran at 7 TFLOP/s.  The small tile is for few tokens: 1000 x 1024
 // outputs give one wave to each of the 1024 SIMDs.
-// Layers of fewer than F32_SMALL such tiles take 32 x 32 ones, four waves of 16 x 16, with four slices in flight: the work of a tile is a
-// quarter, and what bounds it is no longer the matrix rate of a few compute units but the latency of its loads (512 tokens,
-// 256 x 256: 32 workgroups and 17.6 us a forward, 128 and 7.6 us).  At 128 to 255 tiles a lone layer would gain 7 to 10 % of its step
-// too, but a set of such layers, which fills the chip anyway, loses 8 % (seven 0.6B-sized ones on 500 tokens).
+// Launches of fewer than F32_SMALL_LAUNCH such tiles take 32 x 32 ones, four waves of 16 x 16, with four slices in flight, for layers
+// of fewer than F32_SMALL: the work of a tile is a quarter, and what bounds it is no longer the matrix rate of a few compute units but the
+// latency of its loads (512 tokens, 256 x 256: 32 workgroups and 17.6 us a forward, 128 and 7.6 us).  Where the large tiles fill the chip
+// once and a half they are the faster ones (steps of K = 0, us with the small, the large tiles: eight layers of 64 tiles 607 and 570, sixteen
+// of 32 704 and 673, two of 120 320 and 308; below, three of 64 121 and 138, seven 0.6B-sized ones on 128 tokens 376 and 463)
 // ---------------------------------------------------------------------------
-constexpr int F32_SMALL = 128;
+constexpr int F32_SMALL = 128, F32_SMALL_LAUNCH = 400;      // both in 64 x 64 tiles
 constexpr int FK = 32;      // slice of d_in: a tile row is 128 bytes in LDS
-static int f32_tile(int64_t M, int64_t N) { return ((M + 63) / 64) * ((N + 63) / 64) < F32_SMALL ? 32 : 64; }
+static int64_t f32_tiles(int64_t M, int64_t N) { return ((M + 63) / 64) * ((N + 63) / 64); }
+// loss partials of a layer: one for every 32 x 32 or every 64 x 64 outputs, by its shape alone, so that a layer's losses have the same bits
+// in every launch
+static int f32_part(int64_t M, int64_t N) { return f32_tiles(M, N) < F32_SMALL ? 32 : 64; }
 
 struct F32FwdDev {
     F32FwdArgs a;
     int tiles_m, tiles_n;
+    bool fine;               // 64 x 64 tiles, but a partial for every 32 x 32 outputs, with the bits of the 32 x 32 tile
 };
 
 // byte offset of 16-byte chunk c of tile row `row` (the XOR spreads the rows of one read over the banks)
@@ -201,7 +206,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void f
         }
     };
     auto evaluate = [&](int phase) {
-        double part = 0.0;
+        double part = 0.0, quarter[2] = {0.0, 0.0};
+        auto across = [&](double v) __attribute__((always_inline)) -> double {
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+            return v;
+        };
 #pragma unroll
         for (int i = 0; i < FB; ++i) {
             // eight targets requested before the first is used; rows and columns past the end repeat the last (conditional on
@@ -232,11 +242,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void f
                         part = fma(r, r, part);
                     }
                 }
+                if constexpr (FT == 64)
+                    if (d.fine) {                          // as four waves of the small tile add up theirs
+                        quarter[j] += across(part);
+                        part = 0.0;
+                    }
             }
         }
         if (a.target == nullptr) return;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
+        if constexpr (FT == 64)
+            if (d.fine) {
+                const int64_t bm = (m0 + wt) / 32, bn = (n0 + wo) / 32, rows = (a.M + 31) / 32, cols = (a.N + 31) / 32;
+                if (lane == 0 && bm < rows && bn < cols) a.partials[(phase * rows + bm) * cols + bn] = quarter[0] + quarter[1];
+                return;
+            }
+        part = across(part);
         if (lane == 0) red[wave] = part;
         __syncthreads();
         if (tid == 0) a.partials[(int64_t)phase * count + tm * d.tiles_n + tn] = (red[0] + red[1]) + (red[2] + red[3]);
@@ -256,7 +276,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void f
 }
 
 int forward_f32_num_workgroups(int64_t M, int64_t N) {
-    const int t = f32_tile(M, N);
+    const int t = f32_part(M, N);
     return (int)(((M + t - 1) / t) * ((N + t - 1) / t));
 }
 
@@ -272,6 +292,7 @@ static hipError_t launch_forward_f32_tiles(const F32FwdArgs* const* a, int n, hi
         d.a = *a[i];
         d.tiles_m = (int)((d.a.M + FT - 1) / FT);
         d.tiles_n = (int)((d.a.N + FT - 1) / FT);
+        d.fine = FT == 64 && d.a.target && f32_part(d.a.M, d.a.N) == 32;
         vec = vec && d.a.K % 4 == 0 && d.a.ldx % 4 == 0 && d.a.ldw % 4 == 0 && ((reinterpret_cast<uintptr_t>(d.a.X) | reinterpret_cast<uintptr_t>(d.a.W)) & 15) == 0;
         tb.first[tb.n] = (uint32_t)blocks;
         tb.gx[tb.n] = (uint32_t)((int64_t)d.tiles_m * d.tiles_n);
@@ -302,12 +323,14 @@ hipError_t launch_forward_f32_many(const F32FwdArgs* a, int n, hipStream_t st) {
         for (; at > 0 && a[order[at - 1]].K < a[i].K; --at) order[at] = order[at - 1];
         order[at] = i;
     }
+    int64_t tiles = 0;
+    for (int i = 0; i < m; ++i) tiles += f32_tiles(a[order[i]].M, a[order[i]].N);
     const F32FwdArgs *large[kBatchMax], *small[kBatchMax];
     int nl = 0, ns = 0;
     for (int i = 0; i < m; ++i) {
         const F32FwdArgs& p = a[order[i]];
-        if (f32_tile(p.M, p.N) == 64) large[nl++] = &p;
-        else small[ns++] = &p;
+        if (tiles < F32_SMALL_LAUNCH && f32_part(p.M, p.N) == 32) small[ns++] = &p;
+        else large[nl++] = &p;
     }
     const hipError_t e = launch_forward_f32_tiles<64>(large, nl, st);
     return e != hipSuccess ? e : launch_forward_f32_tiles<32>(small, ns, st);
