@@ -316,7 +316,10 @@ int sketch_range(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* 
     return 0;
 }
 
-// S = X^T (X Q)  (Alg. 1: Y <- H (H^T Q)).  bf16: Q must already sit in the workspace as planes.
+// whether the products X Q of a layer read Q as planes
+bool reads_planes(const agzo_layer& L) { return L.dtype == AGZO_BF16 && !xq_narrow(L.n_tokens, L.d_in, L.r); }
+
+// S = X^T (X Q)  (Alg. 1: Y <- H (H^T Q)).  Where it is read as planes, Q must already sit in the workspace as such.
 int sketch_power(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* X, const float* Q, float* S) {
     hipStream_t st = ctx->stream;
     if (L.dtype == AGZO_BF16) {
@@ -345,11 +348,10 @@ int reduce_to_S(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, float* S) {
     return 0;
 }
 
-// Q = qr(S) for an explicit S; planes (nullable) also receive Q as bf16 planes
-int op_qr(agzo_ctx* ctx, size_t off_qr, const float* S, int64_t d, int r, int rp, float* Q, bf16_t* planes,
-          bool refine = true) {
+// Q = qr(S) for an explicit S
+int op_qr(agzo_ctx* ctx, size_t off_qr, const float* S, int64_t d, int r, int rp, float* Q) {
     ProfScope ps(ctx, AGZO_PROF_QR);
-    HIPCHK(launch_qr(S, nullptr, 0, rp, nullptr, d, r, Q, planes, ctx->ws + off_qr, ctx->flag, refine, ctx->stream));
+    HIPCHK(launch_qr(S, nullptr, 0, rp, nullptr, d, r, Q, nullptr, ctx->ws + off_qr, ctx->flag, true, ctx->stream));
     return 0;
 }
 
@@ -538,7 +540,7 @@ int stage_sketch_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, const in
 }
 
 // Alg. 1 for every job.  Jobs that share a dtype and a padded rank go through the batched kernels, at most kBatchMax per
-// launch.  On return every bf16 job's workspace planes hold its basis.
+// launch.  On return the workspace planes of every job that reads them hold its basis.
 int basis_many_impl(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, int K, int flags, bool half_cu = false) {
     std::vector<char> done(jobs.size(), 0);
     for (size_t a = 0; a < jobs.size(); ++a) {
@@ -560,7 +562,7 @@ int basis_many_impl(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, int K, int
             given[i] = false;
             if (flags & AGZO_INIT_FEATURE) {
                 HIPCHK(launch_fill_normal(wsf(ctx, j.p.off_Q), j.L.d_in, j.L.r, j.seed, AGZO_TAG_Q0, ctx->stream));
-                if (bf) HIPCHK(launch_pack_planes(wsf(ctx, j.p.off_Q), j.L.d_in, j.L.r, j.p.rp, wsh(ctx, j.p.off_pack), ctx->stream));
+                if (reads_planes(j.L)) HIPCHK(launch_pack_planes(wsf(ctx, j.p.off_Q), j.L.d_in, j.L.r, j.p.rp, wsh(ctx, j.p.off_pack), ctx->stream));
                 need_idx[n_need++] = idx[i];
             } else if (j.S0) {
                 given[i] = true;
@@ -575,12 +577,13 @@ int basis_many_impl(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, int K, int
             for (int i = 0; i < n; ++i) {
                 const LayerJob& j = jobs[idx[i]];
                 float* out = (k == K) ? j.B : wsf(ctx, j.p.off_Q);
+                bf16_t* planes = reads_planes(j.L) ? wsh(ctx, j.p.off_pack) : nullptr;
                 if ((k == 0 && given[i]) || !bf)
                     q[i] = QrArgs{(k == 0 && given[i]) ? j.S0 : wsf(ctx, j.p.off_S), nullptr, 0, j.p.rp, nullptr, j.L.d_in, j.L.r, out,
-                                  bf ? wsh(ctx, j.p.off_pack) : nullptr, ctx->ws + j.p.off_qr};
+                                  planes, ctx->ws + j.p.off_qr};
                 else
                     q[i] = QrArgs{nullptr, wsf(ctx, j.p.off_xtt), j.p.nsplit, j.p.rp, wsf(ctx, j.p.off_S), j.L.d_in, j.L.r, out,
-                                  wsh(ctx, j.p.off_pack), ctx->ws + j.p.off_qr};
+                                  planes, ctx->ws + j.p.off_qr};
                 // a single column between power steps: the projection that follows normalises its result, one launch less
                 q[i].defer = bf && k < K && xq_narrow(j.L.n_tokens, j.L.d_in, j.L.r);
                 raw[i] = !q[i].defer ? nullptr : q[i].splits ? q[i].S_out : q[i].S;
@@ -595,7 +598,7 @@ int basis_many_impl(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, int K, int
     return 0;
 }
 
-// Alg. 1 for one layer.  On return (bf16) the workspace planes hold B.
+// Alg. 1 for one layer
 int op_basis(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* X, int K, uint64_t seed, const float* S0, int flags, float* B) {
     try {
         return basis_many_impl(ctx, {LayerJob{L, p, X, seed, S0, B}}, K, flags);
@@ -604,7 +607,7 @@ int op_basis(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* X, i
     }
 }
 
-// P = X B for every job (one launch per kBatchMax jobs of a dtype and padded rank); bf16: the planes hold its basis
+// P = X B for every job (one launch per kBatchMax jobs of a dtype and padded rank), behind basis_many_impl
 int project_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, bool half_cu) {
     std::vector<char> done(jobs.size(), 0);
     for (size_t a = 0; a < jobs.size(); ++a) {
@@ -881,8 +884,7 @@ int agzo_layer_forward_sketch(agzo_ctx* ctx, const agzo_layer* L, const void* W,
             HIPCHK(launch_fill_normal(Q0, L->d_in, L->r, seed, AGZO_TAG_Q0, ctx->stream));
             Q = Q0;
         }
-        if (L->dtype == AGZO_BF16)
-            HIPCHK(launch_pack_planes(Q, L->d_in, L->r, p.rp, wsh(ctx, p.off_pack), ctx->stream));
+        if (reads_planes(*L)) HIPCHK(launch_pack_planes(Q, L->d_in, L->r, p.rp, wsh(ctx, p.off_pack), ctx->stream));
         TRY(sketch_power(ctx, *L, p, X, Q, S));
         TRY(reduce_to_S(ctx, *L, p, S));
     }
@@ -894,7 +896,7 @@ int agzo_qr(agzo_ctx* ctx, const float* S, int64_t d_in, int32_t r, float* Q) {
     if (!S || !Q) return fail(ctx, AGZO_EINVAL, "S or Q is NULL");
     if (r < 1 || r > kMaxRank || d_in < r) return fail(ctx, AGZO_EINVAL, "need 1 <= r <= min(64, d_in)");
     TRY(reserve(ctx, qr_workspace_bytes(d_in, r)));
-    return op_qr(ctx, 0, S, d_in, r, round16(r), Q, nullptr);
+    return op_qr(ctx, 0, S, d_in, r, round16(r), Q);
 }
 
 int agzo_basis(agzo_ctx* ctx, const agzo_layer* L, const void* X, int32_t K, uint64_t seed, const float* S0,
@@ -923,7 +925,7 @@ int agzo_perturbed_forward(agzo_ctx* ctx, const agzo_layer* L, const void* W, co
         HIPCHK(launch_xq_f32_many(&a, 1, ctx->stream));
         return op_forward(ctx, *L, p, W, X, P, eps_signed, seed, Y, loss, loss_dev);
     }
-    const bool narrow = xq_narrow(L->n_tokens, L->d_in, L->r);
+    const bool narrow = !reads_planes(*L);
     XqArgs q{static_cast<const bf16_t*>(X), L->ldx, L->n_tokens, L->d_in, wsh(ctx, p.off_pack), L->r, p.rp, P, nullptr, p.m_pad, wsf(ctx, p.off_xqpart), nullptr, B};
     if (timed(ctx, AGZO_PROF_GEMM)) {      // the operands are prepared inside the forward's time
         if (!narrow) HIPCHK(launch_pack_planes(B, L->d_in, L->r, p.rp, wsh(ctx, p.off_pack), ctx->stream));

@@ -186,7 +186,7 @@ hipError_t launch_gemm_bf16(const GemmBf16Args& a, hipStream_t st);
 // half_cu: those that share launches leave half of every compute unit to what runs on other streams
 hipError_t launch_gemm_bf16_many(const GemmBf16Args* a, int n, bool half_cu, hipStream_t st);
 // extension operands of several layers in one launch: the W side times coef and, with two = true, once more times coef2
-// P = NULL: without the X side (launch_xq_bf16 writes it).  planes != NULL: also the bf16 planes [3][rp][d] of B fp32 [d][r]
+// P = NULL: without the X side (the projection writes it).  planes != NULL: also the bf16 planes [3][rp][d] of B fp32 [d][r]
 struct GemmExtArgs {
     void* ext_ws; int64_t M, N; const float* P; int r; float coef, coef2; bool two; uint64_t seed;
     const float* B = nullptr; bf16_t* planes = nullptr; int64_t d = 0;

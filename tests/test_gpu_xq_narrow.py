@@ -1,5 +1,7 @@
 """X Q for a single column on the vector units: widths below, at and past the chunks that waves share, tokens that waves and workgroups
 do not divide, unaligned factors, every output form."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -121,3 +123,42 @@ def test_zero_column_is_reported():
         ctx.check()
     ctx.basis(L, X, 2, 3, None, 0, B)
     ctx.check()
+
+
+def _launches(ctx, call):
+    call()
+    ctx.stream.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph, stream=ctx.stream):
+        call()
+    n = ctypes.c_size_t(0)
+    assert binding.load().hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("seed", [3, 11])
+def test_no_planes_where_the_column_is_read(seed):
+    """a power sketch, and the feature-space start of a basis, of few tokens: a launch less than of many, whose products read planes; and
+    the start's result against fp64, beside a layer that does read them"""
+    ctx = binding.Context(stream=torch.cuda.Stream())
+    few, many = (torch.randn(n, 264, device="cuda").bfloat16() for n in (8191, 8192))
+    q, s = torch.randn(264, 1, device="cuda"), torch.empty(264, 1, device="cuda")
+    b = torch.empty(2, 264, 1, device="cuda")
+    q0 = torch.empty(264, 1, device="cuda")
+    lay = [binding.make_layer(torch.empty(16, 264, device="cuda", dtype=torch.bfloat16), x, 1) for x in (few, many)]
+    torch.cuda.synchronize()
+    with torch.cuda.stream(ctx.stream):
+        sketch = [_launches(ctx, lambda: ctx.layer_forward_sketch(l, None, x, None, binding.SKETCH_POWER, q, 0, s, None, None)) for l, x in zip(lay, (few, many))]
+        basis = [_launches(ctx, lambda: ctx.basis(l, x, 1, seed, None, binding.INIT_FEATURE, o)) for l, x, o in zip(lay, (few, many), b)]
+        assert sketch[0] == sketch[1] - 1
+        assert basis[0] == basis[1] - 2                # (and one that the projection saves by normalising its result)
+        ctx.basis_many([(l, x, seed, None, o) for l, x, o in zip(lay, (few, many), b)], 2, binding.INIT_FEATURE)
+        ctx.fill_normal(q0, seed, binding.TAG_Q0)
+        ctx.check()
+    for x, o in zip((few, many), b):
+        y = q0.double()
+        for _ in range(3):
+            y = x.double().T @ (x.double() @ y)
+            y = y / y.norm()
+        assert (o.double() - y).norm() <= 4 * 4e-6
+    ctx.close()
