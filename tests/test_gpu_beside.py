@@ -197,3 +197,39 @@ def test_a_first_call_that_is_captured():
     assert _forks(stream, call)          # it is there now
     ctx.check()
     ctx.close()
+
+
+@pytest.mark.parametrize("n_bf16,n_f32,n_ce,tokens,r", [(4, 1, 1, 900, 4), (5, 2, 3, 900, 1), (18, 1, 1, 400, 8), (17, 0, 0, 400, 40)])
+def test_beside_layers_of_other_kinds(n_bf16, n_f32, n_ce, tokens, r):
+    """base forwards on the second stream while those of fp32 layers and heads, and the extraction of all, run on the context's; also more
+    of them than a launch takes.  Written right before, overwritten right after: the bits of a call per layer"""
+    stream = torch.cuda.Stream()
+    ctx = binding.Context(stream=stream)
+    layers, out, items = _mixed(n_bf16, n_f32, n_ce, tokens, r)
+    given = [(w.clone(), x.clone(), t.clone()) for w, x, t, _ in layers]
+    want, out1 = [], torch.zeros_like(out)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        for i, ((w, x, t), (_, _, _, loss)) in enumerate(zip(given, layers)):
+            w = w.clone()
+            own = binding.make_loss(t, kind=loss.kind)
+            ctx.step(binding.make_layer(w, x, r), w, x, own, 3, EPS, LR, 30 + i, 0, out1[i])
+            want.append(w)
+        ctx.step_many(items, 3, EPS, LR, 0)
+        for _ in range(3):
+            for (w, x, t, _), src in zip(layers, given):
+                for a, s in zip((w, x, t), src):
+                    a.copy_(s)
+            out.fill_(float("nan"))
+            ctx.step_many(items, 3, EPS, LR, 0)
+            got = [w.clone() for w, _, _, _ in layers]
+            for w, x, t, _ in layers:
+                w.fill_(float("nan"))
+                x.fill_(float("nan"))
+                t.fill_(-1 if t.dtype == torch.int32 else float("nan"))
+            stream.synchronize()
+            assert torch.equal(out, out1)
+            assert all(torch.equal(a, b) for a, b in zip(got, want))
+    ctx.check()
+    assert _forks(stream, lambda: ctx.step_many(items, 3, EPS, LR, 0))
+    ctx.close()
