@@ -35,7 +35,7 @@ struct agzo_ctx {
     int* flag;   // device int: deferred numeric failure
     uint32_t prof;      // mask of timed kernel classes (bit = AGZO_PROF_* value)
     ProfClass pc[AGZO_PROF_KINDS];
-    // base forwards of a set of layers run on a stream of the context's own beside the extraction (step_many_body); NULL: not made yet
+    // base forwards of a set of layers run on a stream of the context's own beside the extraction (step_many_body)
     hipStream_t side;
     hipEvent_t fork, join;
     // clock telemetry: kClkSlots records of four 64-bit words (one per timed GEMM launch), then the probe's record
@@ -260,33 +260,6 @@ struct HipApi {
     static hipError_t wait(hipStream_t s, hipEvent_t e) { return hipStreamWaitEvent(s, e, 0); }
     static hipError_t synchronize(hipStream_t s) { return hipStreamSynchronize(s); }
 };
-
-void drop_side(agzo_ctx* ctx) {
-    if (ctx->side) (void)hipStreamDestroy(ctx->side);
-    if (ctx->fork) (void)hipEventDestroy(ctx->fork);
-    if (ctx->join) (void)hipEventDestroy(ctx->join);
-    ctx->side = nullptr;
-    ctx->fork = ctx->join = nullptr;
-}
-// The second stream and its events, made by the first call that takes them: most contexts never do, and they took longer than
-// all else of agzo_create (33 us with them, 10 without).  false: a call that cannot have them - the current device is not the context's,
-// or its stream is being captured and they are not there yet - runs in one stream, with the same results
-bool have_side(agzo_ctx* ctx) {
-    if (ctx->side) return true;
-    int dev = -1;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusActive;
-    hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipStreamIsCapturing(ctx->stream, &capture);
-    if (e == hipSuccess && (dev != ctx->device || capture != hipStreamCaptureStatusNone)) return false;
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->fork, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->join, hipEventDisableTiming);
-    // (non-blocking: the context's stream may be the default stream, which others would otherwise wait for)
-    if (e == hipSuccess) e = hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking);
-    if (e == hipSuccess) return true;
-    (void)hipGetLastError();
-    drop_side(ctx);
-    return false;
-}
 
 // ---- internal building blocks; all take a ready workspace plan --------------------------------
 inline float* wsf(agzo_ctx* c, size_t off) { return reinterpret_cast<float*>(c->ws + off); }
@@ -706,9 +679,17 @@ int agzo_create(agzo_ctx** out, void* hip_stream) {
     if (e == hipSuccess) e = hipMemset(ctx->flag, 0, 256);
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&ctx->clk), kClkBytes);
     if (e == hipSuccess) e = hipMemset(ctx->clk, 0, kClkBytes);
+    // (Non-blocking: the context's stream may be the default stream, which others would otherwise wait for.  Made here although few
+    // contexts use it, 23 us of 33, and not by the first call that does: what follows the making of a stream is faster on the context's own
+    // too, the dense estimator over seven 0.6B-sized layers 426 us a pass and 434 without, its first pass 0.9 ms and 1.35)
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->fork, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->join, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking);
     if (e != hipSuccess) {
         if (ctx->flag) (void)hipFree(ctx->flag);
         if (ctx->clk) (void)hipFree(ctx->clk);
+        if (ctx->fork) (void)hipEventDestroy(ctx->fork);
+        if (ctx->join) (void)hipEventDestroy(ctx->join);
         delete ctx;
         return AGZO_EHIP;
     }
@@ -719,8 +700,12 @@ int agzo_create(agzo_ctx** out, void* hip_stream) {
 void agzo_destroy(agzo_ctx* ctx) {
     if (!ctx) return;
     (void)hipStreamSynchronize(ctx->stream);
-    if (ctx->side) (void)hipStreamSynchronize(ctx->side);      // (joined to the above, unless joining failed)
-    drop_side(ctx);
+    if (ctx->side) {
+        (void)hipStreamSynchronize(ctx->side);    // (joined to the above, unless joining failed)
+        (void)hipStreamDestroy(ctx->side);
+    }
+    if (ctx->fork) (void)hipEventDestroy(ctx->fork);
+    if (ctx->join) (void)hipEventDestroy(ctx->join);
     if (ctx->ws) (void)hipFree(ctx->ws);
     if (ctx->flag) (void)hipFree(ctx->flag);
     if (ctx->clk) (void)hipFree(ctx->clk);
@@ -1096,7 +1081,7 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
     TRY(reserve(ctx, total + upd_bytes));
     for (int m = 0; m < n; ++m) jobs[(size_t)m].B = items[m].B_out ? items[m].B_out : wsf(ctx, jobs[(size_t)m].p.off_B);
     hipStream_t st = ctx->stream;
-    Fork<HipApi> beside(st);
+    Fork<HipApi> beside(st, ctx->side, ctx->fork, ctx->join);
 
     // the squared-error evaluations of phases [ph0, ph1): 0 = f0 (or, shared, all three from one pass), 1 = f+, 2 = f-; the
     // loss partials of phase ph go to slot ph of the layer's region
@@ -1131,8 +1116,8 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
         for (size_t b = 0; b < f32.size(); b += kBatchMax)
             HIPCHK(launch_forward_f32_many(f32.data() + b, (int)std::min(f32.size() - b, (size_t)kBatchMax), st));
         if (bf.empty()) return 0;
-        if (ph1 == 1 && !shared && ctx->prof == 0 && beside_fits(bf, K) && have_side(ctx)) {
-            HIPCHK(beside.run(ctx->side, ctx->fork, ctx->join, [&](hipStream_t side) { return launch_gemm_bf16_many(bf.data(), (int)bf.size(), true, side); }));
+        if (ph1 == 1 && !shared && ctx->prof == 0 && ctx->side && beside_fits(bf, K)) {
+            HIPCHK(beside.run([&](hipStream_t side) { return launch_gemm_bf16_many(bf.data(), (int)bf.size(), true, side); }));
             return 0;
         }
         for (size_t b = 0; b < ext.size(); b += kBatchMax)

@@ -12,18 +12,16 @@ class Fork {
     typedef typename Api::event_t event_t;
     typedef typename Api::error_t error_t;
 
-    explicit Fork(stream_t main) : main_(main) {}
+    Fork(stream_t main, stream_t side, event_t fork, event_t join) : main_(main), side_(side), fork_(fork), join_(join) {}
     Fork(const Fork&) = delete;
     Fork& operator=(const Fork&) = delete;
     ~Fork() { (void)close(); }
 
-    // once
+    // once per fork
     template <typename F>
-    error_t run(stream_t side, event_t fork, event_t join, F launches) {
-        side_ = side;
-        join_ = join;
-        error_t e = Api::record(fork, main_);
-        if (e == error_t(0)) e = Api::wait(side_, fork);
+    error_t run(F launches) {
+        error_t e = Api::record(fork_, main_);
+        if (e == error_t(0)) e = Api::wait(side_, fork_);
         if (e != error_t(0)) return e;
         open_ = true;            // whatever follows, also an exception: something may be under way on the second stream
         return launches(side_);
@@ -41,8 +39,8 @@ class Fork {
     bool open() const { return open_; }
 
   private:
-    stream_t main_, side_{};
-    event_t join_{};
+    stream_t main_, side_;
+    event_t fork_, join_;
     bool open_ = false;
 };
 

@@ -36,8 +36,8 @@ int main(int argc, char** argv) {
     int rc = 0, closed = 0;
     bool enqueued = false;
     try {
-        agzo::Fork<Fake> f(&main_);
-        rc = f.run(&side, &fork, &join, [&](Stream* s) {
+        agzo::Fork<Fake> f(&main_, &side, &fork, &join);
+        rc = f.run([&](Stream* s) {
             s->work += 1;
             enqueued = true;
             if (how == "throws") throw std::runtime_error("no memory");

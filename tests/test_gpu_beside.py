@@ -165,40 +165,6 @@ def test_forwards_that_outlast_the_extraction(r, K, large, forks):
     ctx.close()
 
 
-def test_a_first_call_that_is_captured():
-    """the second stream is made by the first call that takes it, not while the context's stream is being captured: in one stream, with the
-    same results"""
-    stream = torch.cuda.Stream()
-    ctx = binding.Context(stream=stream)
-    layers, out, items = _mixed(4, 0, 0)
-    w0 = [one[0].clone() for one in layers]
-    x = torch.randn(8192, 2600, device="cuda").bfloat16()
-    w, t = torch.randn(5200, 2600, device="cuda").bfloat16(), torch.randn(8192, 5200, device="cuda").bfloat16()
-    torch.cuda.synchronize()
-
-    def call():
-        ctx.step_many(items, 3, EPS, LR, 0)
-    with torch.cuda.stream(stream):
-        ctx.step(binding.make_layer(w, x, 64), w, x, binding.make_loss(t), 3, EPS, LR, 1, 0, out[0])      # a workspace for all of it
-        stream.synchronize()
-        graph = torch.cuda.CUDAGraph()
-        with torch.cuda.graph(graph, stream=stream):
-            call()
-    assert not _forks(stream, call)
-    graph.replay()
-    torch.cuda.synchronize()
-    got = [one[0].clone() for one in layers], out.clone()
-    with torch.cuda.stream(stream):
-        for one, s in zip(layers, w0):
-            one[0].copy_(s)
-        call()
-        stream.synchronize()
-    assert torch.equal(got[1], out) and all(torch.equal(a, one[0]) for a, one in zip(got[0], layers))
-    assert _forks(stream, call)          # it is there now
-    ctx.check()
-    ctx.close()
-
-
 @pytest.mark.parametrize("n_bf16,n_f32,n_ce,tokens,r", [(4, 1, 1, 900, 4), (5, 2, 3, 900, 1), (18, 1, 1, 400, 8), (17, 0, 0, 400, 40)])
 def test_beside_layers_of_other_kinds(n_bf16, n_f32, n_ce, tokens, r):
     """base forwards on the second stream while those of fp32 layers and heads, and the extraction of all, run on the context's; also more
