@@ -538,12 +538,14 @@ int update_many_max() { return UPD_MAX; }
 // update lines): theta[i][j] += coef * z(i, j), z from Philox stream AGZO_TAG_DENSE, coef = scale * (*g_dev or 1).
 // A thread takes the same four columns of DENSE_ROWS rows, a Philox call each, with what it reads requested before the first.  The
 // generator bounds this kernel, not the 4 - 8 bytes per value it moves.  (A 64-bit division a thread for its place, one row a thread
-// and the two halves of every Philox product by themselves: the estimator over seven 0.6B-sized layers 419 us a step, 408 so)
-constexpr int DENSE_ROWS = 2;
-template <typename T>
+// and the two halves of every Philox product by themselves: the estimator over seven 0.6B-sized layers 419 us a step, 408 so.)  Rows
+// that four columns do not divide are read and written value by value, each load in its place: there half the threads hide less of that
+// latency than they save of the generator's (fp32, 982 x 1183: 5.1 us with a row a thread, 6.2 with two; 1024 x 2047 6.8 and 7.2; 8192 x
+// 4095 62 and 62), except in large bf16 blocks (8192 x 4095: 49 and 47)
+template <typename T, bool VEC, int DENSE_ROWS>
 __global__ __launch_bounds__(256) void dense_axpy_kernel(T* __restrict__ theta, int64_t rows, int64_t cols, int64_t ld,
                                                          int64_t nquad, int64_t items, uint32_t s_lo, uint32_t s_hi, float scale,
-                                                         const double* __restrict__ g_dev, int vec_ok) {
+                                                         const double* __restrict__ g_dev) {
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (idx >= items) return;
     int64_t group, quad;
@@ -560,7 +562,7 @@ __global__ __launch_bounds__(256) void dense_axpy_kernel(T* __restrict__ theta, 
     T* p = theta + row * ld + quad * 4;
     typedef typename std::conditional<sizeof(T) == 4, float4, uint2>::type vec_t;
     vec_t v[DENSE_ROWS];
-    if (vec_ok) {
+    if constexpr (VEC) {
 #pragma unroll
         for (int i = 0; i < DENSE_ROWS; ++i) v[i] = *reinterpret_cast<const vec_t*>(p + min(i, n - 1) * ld);
     }
@@ -571,7 +573,7 @@ __global__ __launch_bounds__(256) void dense_axpy_kernel(T* __restrict__ theta, 
         const float4 z4 = philox_normal4(s_lo, s_hi, AGZO_TAG_DENSE, (uint32_t)(row + i), (uint32_t)quad);
         const float z[4] = {z4.x, z4.y, z4.z, z4.w};
         T* pi = p + i * ld;
-        if (vec_ok) {
+        if constexpr (VEC) {
             if constexpr (sizeof(T) == 4) {
                 v[i].x = fmaf(coef, z[0], v[i].x); v[i].y = fmaf(coef, z[1], v[i].y);
                 v[i].z = fmaf(coef, z[2], v[i].z); v[i].w = fmaf(coef, z[3], v[i].w);
@@ -592,23 +594,28 @@ __global__ __launch_bounds__(256) void dense_axpy_kernel(T* __restrict__ theta, 
     }
 }
 
-hipError_t launch_dense_axpy(void* theta, int dtype, int64_t rows, int64_t cols, int64_t ld, uint64_t seed, float scale,
-                             const double* g_dev, hipStream_t st) {
-    if (rows == 0 || cols == 0) return hipSuccess;
+template <typename T, bool VEC, int DENSE_ROWS>
+static hipError_t launch_dense_rows(T* theta, int64_t rows, int64_t cols, int64_t ld, uint64_t seed, float scale, const double* g_dev, hipStream_t st) {
     const int64_t nquad = (cols + 3) / 4;
     const int64_t items = (rows + DENSE_ROWS - 1) / DENSE_ROWS * nquad;
     const dim3 grid((unsigned)((items + 255) / 256));
-    const uintptr_t addr = reinterpret_cast<uintptr_t>(theta);
-    if (dtype == AGZO_BF16) {
-        const int vec = (cols % 4 == 0) && (ld % 4 == 0) && (addr % 8 == 0);
-        hipLaunchKernelGGL(dense_axpy_kernel<bf16_t>, grid, dim3(256), 0, st, static_cast<bf16_t*>(theta), rows, cols, ld, nquad, items,
-                           (uint32_t)seed, (uint32_t)(seed >> 32), scale, g_dev, vec);
-    } else {
-        const int vec = (cols % 4 == 0) && (ld % 4 == 0) && (addr % 16 == 0);
-        hipLaunchKernelGGL(dense_axpy_kernel<float>, grid, dim3(256), 0, st, static_cast<float*>(theta), rows, cols, ld, nquad, items,
-                           (uint32_t)seed, (uint32_t)(seed >> 32), scale, g_dev, vec);
-    }
+    hipLaunchKernelGGL((dense_axpy_kernel<T, VEC, DENSE_ROWS>), grid, dim3(256), 0, st, theta, rows, cols, ld, nquad, items,
+                       (uint32_t)seed, (uint32_t)(seed >> 32), scale, g_dev);
     return hipGetLastError();
+}
+template <typename T>
+static hipError_t launch_dense_typed(T* theta, int64_t rows, int64_t cols, int64_t ld, uint64_t seed, float scale, const double* g_dev, hipStream_t st) {
+    if (cols % 4 == 0 && ld % 4 == 0 && reinterpret_cast<uintptr_t>(theta) % (4 * sizeof(T)) == 0)
+        return launch_dense_rows<T, true, 2>(theta, rows, cols, ld, seed, scale, g_dev, st);
+    if constexpr (sizeof(T) == 2)
+        if ((double)rows * (double)cols >= 8e6) return launch_dense_rows<T, false, 2>(theta, rows, cols, ld, seed, scale, g_dev, st);
+    return launch_dense_rows<T, false, 1>(theta, rows, cols, ld, seed, scale, g_dev, st);
+}
+hipError_t launch_dense_axpy(void* theta, int dtype, int64_t rows, int64_t cols, int64_t ld, uint64_t seed, float scale,
+                             const double* g_dev, hipStream_t st) {
+    if (rows == 0 || cols == 0) return hipSuccess;
+    if (dtype == AGZO_BF16) return launch_dense_typed(static_cast<bf16_t*>(theta), rows, cols, ld, seed, scale, g_dev, st);
+    return launch_dense_typed(static_cast<float*>(theta), rows, cols, ld, seed, scale, g_dev, st);
 }
 
 }  // namespace agzo

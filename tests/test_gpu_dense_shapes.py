@@ -26,3 +26,19 @@ def test_against_the_generator(rows, cols, pad, dtype):
     assert torch.equal(whole[:, cols:], before[:, cols:])
     half_ulp = want.abs() * (2.0 ** -24 if dtype == torch.float32 else 2.0 ** -8)      # 24 and 8 significant bits
     assert ((theta.double() - want).abs() <= half_ulp * 1.01 + 2.0 ** -24 * (want.abs() + 1e-30)).all()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("rows,cols", [(2731, 2929), (2731, 2930), (8000001, 1), (3, 2666667)])
+def test_large_blocks_of_odd_rows(rows, cols, dtype):
+    """on both sides of the size from which a thread takes two rows: the bound of the test above"""
+    ctx = binding.Context()
+    theta = torch.randn(rows, cols, device="cuda").to(dtype)
+    z = torch.empty(rows, cols, device="cuda")
+    ctx.fill_normal(z, 5, TAG_DENSE)
+    c = torch.tensor(0.25, device="cuda").item()
+    want = torch.addcmul(theta.double(), z.double(), torch.full_like(z, c, dtype=torch.float64))
+    ctx.dense_perturb(theta, 5, c)
+    ctx.check()
+    half_ulp = want.abs() * (2.0 ** -24 if dtype == torch.float32 else 2.0 ** -8)
+    assert ((theta.double() - want).abs() <= half_ulp * 1.01 + 2.0 ** -24 * (want.abs() + 1e-30)).all()
