@@ -27,9 +27,12 @@ template <int V> struct IC { static constexpr int value = V; };
 // of fewer than F32_SMALL: the work of a tile is a quarter, and what bounds it is no longer the matrix rate of a few compute units but the
 // latency of its loads (512 tokens, 256 x 256: 32 workgroups and 17.6 us a forward, 128 and 7.6 us).  Where the large tiles fill the chip
 // once and a half they are the faster ones (steps of K = 0, us with the small, the large tiles: eight layers of 64 tiles 607 and 570, sixteen
-// of 32 704 and 673, two of 120 320 and 308; below, three of 64 121 and 138, seven 0.6B-sized ones on 128 tokens 376 and 463)
+// of 32 704 and 673, two of 120 320 and 308; below, three of 64 121 and 138, seven 0.6B-sized ones on 128 tokens 376 and 463).
+// Where rows are no 16-byte vectors, value-by-value loads are four times the instructions and the small tile has twice as many for its
+// work: there it is launches of fewer than F32_SMALL_SCALAR (four layers of 64 tiles, 2047 wide: 478 and 386; two of 126, 198 wide: 131 and
+// 120; below, one of 64 189 and 243)
 // ---------------------------------------------------------------------------
-constexpr int F32_SMALL = 128, F32_SMALL_LAUNCH = 400;      // both in 64 x 64 tiles
+constexpr int F32_SMALL = 128, F32_SMALL_LAUNCH = 400, F32_SMALL_SCALAR = 192;      // in 64 x 64 tiles
 constexpr int FK = 32;      // slice of d_in: a tile row is 128 bytes in LDS
 static int64_t f32_tiles(int64_t M, int64_t N) { return ((M + 63) / 64) * ((N + 63) / 64); }
 // loss partials of a layer: one for every 32 x 32 or every 64 x 64 outputs, by its shape alone, so that a layer's losses have the same bits
@@ -206,7 +209,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void f
         }
     };
     auto evaluate = [&](int phase) {
-        double part = 0.0, quarter[2] = {0.0, 0.0};
+        double part = 0.0, quarter[FB][FB];
         auto across = [&](double v) __attribute__((always_inline)) -> double {
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
@@ -244,7 +247,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void f
                 }
                 if constexpr (FT == 64)
                     if (d.fine) {                          // as four waves of the small tile add up theirs
-                        quarter[j] += across(part);
+                        quarter[i][j] = part;
                         part = 0.0;
                     }
             }
@@ -252,8 +255,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void f
         if (a.target == nullptr) return;
         if constexpr (FT == 64)
             if (d.fine) {
+#pragma unroll
+                for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) quarter[q >> 1][q & 1] += __shfl_xor(quarter[q >> 1][q & 1], off);
                 const int64_t bm = (m0 + wt) / 32, bn = (n0 + wo) / 32, rows = (a.M + 31) / 32, cols = (a.N + 31) / 32;
-                if (lane == 0 && bm < rows && bn < cols) a.partials[(phase * rows + bm) * cols + bn] = quarter[0] + quarter[1];
+                if (lane == 0 && bm < rows && bn < cols) a.partials[(phase * rows + bm) * cols + bn] = (quarter[0][0] + quarter[1][0]) + (quarter[0][1] + quarter[1][1]);
                 return;
             }
         part = across(part);
@@ -280,20 +287,25 @@ int forward_f32_num_workgroups(int64_t M, int64_t N) {
     return (int)(((M + t - 1) / t) * ((N + t - 1) / t));
 }
 
+// every row of X and W starts on 16 bytes
+static bool f32_vec(const F32FwdArgs& a) {
+    return a.K % 4 == 0 && a.ldx % 4 == 0 && a.ldw % 4 == 0 && ((reinterpret_cast<uintptr_t>(a.X) | reinterpret_cast<uintptr_t>(a.W)) & 15) == 0;
+}
+
 template <int FT>
 static hipError_t launch_forward_f32_tiles(const F32FwdArgs* const* a, int n, hipStream_t st) {
     if (n == 0) return hipSuccess;
     KBatch<F32FwdDev> tb;
     tb.n = 0;
     uint64_t blocks = 0;
-    bool vec = true;            // every row starts on 16 bytes
+    bool vec = true;
     for (int i = 0; i < n; ++i) {
         F32FwdDev d;
         d.a = *a[i];
         d.tiles_m = (int)((d.a.M + FT - 1) / FT);
         d.tiles_n = (int)((d.a.N + FT - 1) / FT);
         d.fine = FT == 64 && d.a.target && f32_part(d.a.M, d.a.N) == 32;
-        vec = vec && d.a.K % 4 == 0 && d.a.ldx % 4 == 0 && d.a.ldw % 4 == 0 && ((reinterpret_cast<uintptr_t>(d.a.X) | reinterpret_cast<uintptr_t>(d.a.W)) & 15) == 0;
+        vec = vec && f32_vec(d.a);
         tb.first[tb.n] = (uint32_t)blocks;
         tb.gx[tb.n] = (uint32_t)((int64_t)d.tiles_m * d.tiles_n);
         blocks += tb.gx[tb.n];
@@ -324,12 +336,16 @@ hipError_t launch_forward_f32_many(const F32FwdArgs* a, int n, hipStream_t st) {
         order[at] = i;
     }
     int64_t tiles = 0;
-    for (int i = 0; i < m; ++i) tiles += f32_tiles(a[order[i]].M, a[order[i]].N);
+    bool vec = true;
+    for (int i = 0; i < m; ++i) {
+        tiles += f32_tiles(a[order[i]].M, a[order[i]].N);
+        vec = vec && f32_vec(a[order[i]]);
+    }
     const F32FwdArgs *large[kBatchMax], *small[kBatchMax];
     int nl = 0, ns = 0;
     for (int i = 0; i < m; ++i) {
         const F32FwdArgs& p = a[order[i]];
-        if (tiles < F32_SMALL_LAUNCH && f32_part(p.M, p.N) == 32) small[ns++] = &p;
+        if (tiles < (vec ? F32_SMALL_LAUNCH : F32_SMALL_SCALAR) && f32_part(p.M, p.N) == 32) small[ns++] = &p;
         else large[nl++] = &p;
     }
     const hipError_t e = launch_forward_f32_tiles<64>(large, nl, st);
