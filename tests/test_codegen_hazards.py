@@ -146,6 +146,21 @@ def test_lds_writes_are_complete_at_barriers(kernels, src):
     assert not any(found.values()), "\n".join("%s: %s" % (n, v[0]) for n, v in found.items() if v)
 
 
+def test_accumulators_stay_in_place(kernels):
+    """X Q up to 32 columns: no moves between the halves of the register file in a loop over slices (a block of matrix instructions that
+    branches back to its own start)"""
+    found = 0
+    for name, (body, succ) in kernels["skinny.hip"].items():
+        if "xq_bf16_many_kernel" not in name:
+            continue
+        loops = [body[t:i + 1] for i, s in enumerate(succ) for t in s if t <= i]
+        inner = [l for l in loops if sum(ins.mfma for ins in l) in (6, 12) and not any(ins.target for ins in l[:-1])]
+        assert inner, name
+        found += 1
+        assert not [ins.text for l in inner for ins in l if ins.op.startswith("v_accvgpr")], name
+    assert found == 12
+
+
 def test_the_walk_finds_planted_faults():
     head, tail = "_Zk:\n", "\ts_endpgm\n.Lfunc_end0:\n"
     mfma = "\t;;#ASMSTART\n\tv_mfma_f32_16x16x32_bf16 a[0:3], v[4:7], v[8:11], a[0:3]\n\t;;#ASMEND\n"
