@@ -661,7 +661,7 @@ def main():
                             "unit": "GB/s", "frac": upd_gbs / PEAK_HBM_GBS, "traffic": upd_traffic,
                             "algorithmic_bytes": upd_bytes_per_launch, "launches": n_upd, "avg_ms": upd_avg_ms},
         "stage_ms_per_step": {"gemm": st_gemm, "update": st_upd, "xq": ms_xq, "xtt": ms_xtt, "qr": ms_qr,
-                              "note": "from %d extra steps with every kernel class timed" % nstage},
+                              "note": "from %d extra steps with every kernel class timed: forwards one by one, in one stream" % nstage},
     }
     if not args.no_extras:
         # the single-matrix update (agzo_update) per projection shape: prep + sweep, bytes = W read + written + the basis;
@@ -840,7 +840,7 @@ def main():
                                  "unit": "GB/s", "frac": fill_gbs / PEAK_HBM_GBS, "launches": n_fill,
                                  "normals_per_s": fill_gbs * 1e9 / 4.0,
                                  "note": "4 bytes written per value; 59 vector instructions per value (Philox4x32-10 + "
-                                         "Box-Muller; profiles/generator_valu_instructions.txt): bound by its arithmetic"}
+                                         "Box-Muller; profiles/generator_valu_instructions.txt): the rate follows these, not the bytes"}
     # the dense Gaussian sweep of Eq. 7's other branch on a bf16 block of the same size (read + write 2 bytes each)
     theta = gbuf.view(torch.bfloat16)[:, :16]
     theta.zero_()
@@ -888,7 +888,8 @@ def main():
         ctx.check()
         res["qwen3_0p6b_layer_set"] = {"value": n_small / dt3, "unit": "steps/s", "ms_per_step": 1e3 * dt3 / n_small,
                                        "tokens": 2048, "rank": 8, "steps": n_small, "stage_ms_per_step": st,
-                                       "note": "launch- and latency-bound: 7 projections of 1-3 M parameters each"}
+                                       "note": "launch- and latency-bound: 7 projections of 1-3 M parameters each; the stages are of steps in "
+                                               "one stream, with forwards one by one, and sum to more than ms_per_step"}
         # the same step recorded once in a HIP graph on a stream of its own and replayed (the calls enqueue kernels only);
         # the seeds are part of the recorded arguments, so every replay repeats one step's seeds: the work is the same
         try:

@@ -111,7 +111,9 @@ int agzo_check(agzo_ctx* ctx);
  * mask: bit (1 << AGZO_PROF_x) selects class x, AGZO_PROF_ALL all of them, 0 switches timing off.  The events
  * cost a few microseconds of stream time each, so a timed region should select only what it reports.  While AGZO_PROF_GEMM
  * is selected every bf16 forward is timed by itself, together with the preparation of its rank-r operands; otherwise forwards of
- * several layers, and their preparations, share launches.  The results are the same bits. */
+ * several layers, and their preparations, share launches.  While any class is selected a set of layers runs in one stream, without
+ * its base forwards beside the extraction.  AGZO_PROF_XQ contains the Gaussian factor's preparation where a projection shares its
+ * launch (agzo_perturbed_forward, one column).  The results are the same bits. */
 enum { AGZO_PROF_GEMM = 0, AGZO_PROF_UPDATE = 1, AGZO_PROF_XQ = 2, AGZO_PROF_XTT = 3, AGZO_PROF_QR = 4,
        AGZO_PROF_FILL = 5, AGZO_PROF_KINDS = 6, AGZO_PROF_ALL = 63 };
 int agzo_profile_enable(agzo_ctx* ctx, int32_t mask);
