@@ -484,7 +484,12 @@ __global__ __launch_bounds__(256) void xq_finish_many_kernel(const KBatch<XqDev,
 // waves pairwise: fewer roundings than a sum over d_in of three planes); the waves of a workgroup share d_in in chunks of 512, as many
 // as it has, and tokens otherwise.  The kernels above pad Q to 16 columns of three planes, and few tokens leave them to share d_in
 // among workgroups, whose sums take a launch of their own: 432 tokens of a 1024-wide layer 5.1 + 3.1 us there and 4.4 here.  For four columns
-// (the rows of Q are then twice the bytes of the four tokens) a step is 0 to 12 % slower this way
+// (the rows of Q are then twice the bytes of the four tokens) a step is 0 to 12 % slower this way.
+// The line at 8192 tokens is a cautious one: of a lone layer's basis (K = 3, us with the planes, this way) it keeps out 92 and 83 at 512
+// wide, 147 and 127 at 4096, 308 and 256 at 12288 on 8192 tokens, and 109 and 101, 203 and 194, 578 and 557 on 16384; below it, 512 to 12288
+// wide, it lets in 72 and 59 to 96 and 75 on 432 tokens and 93 and 83 to 278 and 255 on 8064.  Errors against 64 bits are the same to 5 %
+// or smaller (385 tokens of 2048: 4.6e-8 and 4.5e-8; 432 of 1024: 4.1e-8 and 3.4e-8).  The waves that share d_in: one, two and four of them 59, 58
+// and 59 at 512 wide on 432 tokens (79, 80 and 83 on 6144), 65, 62 and 62 at 2560, 90, 80 and 74 at 12288
 // ---------------------------------------------------------------------------
 constexpr int XQN_TOK = 4, XQN_CHUNK = 512;
 bool xq_narrow(int64_t M, int64_t K, int r) { return r == 1 && M < 8192 && K >= 8; }
