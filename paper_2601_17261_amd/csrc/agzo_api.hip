@@ -1039,6 +1039,8 @@ namespace {
 // 200 + 60 [r > 1] + r GFLOP and 800 per value of X, two streams were never more than 1.2 % slower over the three sets' sizes, 256
 // to 16384 tokens and r = 1 to 64, and no more than 0.7 % faster beyond; with K from 0 to 6 the line taken as the number of sweeps
 // never more than 3 % slower (without it up to 13)
+// Where 256 x 256 tiles in lists take every layer they get compute units of their own, as many as let both be done first
+// (launch_gemm_bf16_beside()): the 4B-sized layers on 1500 tokens 1097 and 1005, 8B-sized on 1000 1284 and 1209
 constexpr int kBesideLayers = 4;
 constexpr double kBesideFlops = 20e9;
 bool beside_fits(const std::vector<GemmBf16Args>& forwards, int K) {
@@ -1053,6 +1055,16 @@ bool beside_fits(const std::vector<GemmBf16Args>& forwards, int K) {
     }
     return (int)forwards.size() >= kBesideLayers && flops >= kBesideFlops &&
            half_cu <= (1e9 * (200 + (r > 1 ? 60 : 0) + r) + 800.0 * values) * ((2 * K + 2) / 8.0);
+}
+// What the extraction takes by itself: the latencies of its launches, and two sweeps over X a step at 5.7 TB/s
+GemmBeside extraction_us(const std::vector<GemmBf16Args>& forwards, int K) {
+    double bytes = 0.0;
+    int r = 1;
+    for (const GemmBf16Args& a : forwards) {
+        bytes += 2.0 * (double)a.M * (double)a.K;
+        r = std::max(r, a.r);
+    }
+    return GemmBeside{(r > 1 ? 37.0 : 28.0) * (K + 1), bytes * (2 * K + 2) / 5.7e6};
 }
 // Alg. 2 for n single-layer problems (agzo_step_many; agzo_step is the same with n = 1, so that their results agree bit for
 // bit).  Squared-error layers run every stage together: the evaluations of part 1 (f0, or all three in the shared schedule) and
@@ -1082,6 +1094,7 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
     for (int m = 0; m < n; ++m) jobs[(size_t)m].B = items[m].B_out ? items[m].B_out : wsf(ctx, jobs[(size_t)m].p.off_B);
     hipStream_t st = ctx->stream;
     Fork<HipApi> beside(st, ctx->side, ctx->fork, ctx->join);
+    bool half_cu = false;          // forwards on the other stream hold half of every compute unit
 
     // the squared-error evaluations of phases [ph0, ph1): 0 = f0 (or, shared, all three from one pass), 1 = f+, 2 = f-; the
     // loss partials of phase ph go to slot ph of the layer's region
@@ -1117,7 +1130,11 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
             HIPCHK(launch_forward_f32_many(f32.data() + b, (int)std::min(f32.size() - b, (size_t)kBatchMax), st));
         if (bf.empty()) return 0;
         if (ph1 == 1 && !shared && ctx->prof == 0 && ctx->side && beside_fits(bf, K)) {
-            HIPCHK(beside.run([&](hipStream_t side) { return launch_gemm_bf16_many(bf.data(), (int)bf.size(), true, side); }));
+            const int count = (int)bf.size();
+            half_cu = !gemm_bf16_listed(bf.data(), count);
+            HIPCHK(beside.run([&](hipStream_t side) {
+                return half_cu ? launch_gemm_bf16_many(bf.data(), count, true, side) : launch_gemm_bf16_beside(bf.data(), count, extraction_us(bf, K), side);
+            }));
             return 0;
         }
         for (size_t b = 0; b < ext.size(); b += kBatchMax)
@@ -1143,9 +1160,9 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
         TRY(forward_mse(0, 1));
         for (int m = 0; m < n; ++m) TRY(forward_ce(m, nullptr, 0.f, items[m].out_dev, false, 0));
     }
-    TRY(basis_many_impl(ctx, jobs, K, flags & AGZO_INIT_FEATURE, beside.open()));
+    TRY(basis_many_impl(ctx, jobs, K, flags & AGZO_INIT_FEATURE, half_cu));
     // parts 2-3: the perturbed evaluations
-    TRY(project_many(ctx, jobs, beside.open()));
+    TRY(project_many(ctx, jobs, half_cu));
     if (shared) TRY(forward_mse(0, 1));
     else TRY(forward_mse(1, one_sided ? 2 : 3));
     for (int m = 0; m < n; ++m) {

@@ -183,8 +183,13 @@ inline int gemm_bf16_sketch_splits(int64_t M) { return (int)((M + 127) / 128); }
 hipError_t launch_gemm_bf16(const GemmBf16Args& a, hipStream_t st);
 // several independent forwards: the squared errors that the kernel of gemm_bf16_mid.hip takes share launches, the others run one by
 // one.  Every result has the bits of a launch of its own.  Workspaces (ext_ws unless ext_ready, loss partials) must not overlap.
-// half_cu: those that share launches leave half of every compute unit to what runs on other streams
+// half_cu: those that share launches in 128 x 128 tiles leave half of every compute unit to what runs on other streams
 hipError_t launch_gemm_bf16_many(const GemmBf16Args* a, int n, bool half_cu, hipStream_t st);
+// the same for forwards of which gemm_bf16_listed() says that their 256 x 256 tiles can share launches, beside work on another stream
+// that takes latency_us + sweep_us by itself, of which only the second depends on how many compute units it has
+struct GemmBeside { double latency_us, sweep_us; };
+bool gemm_bf16_listed(const GemmBf16Args* a, int n);
+hipError_t launch_gemm_bf16_beside(const GemmBf16Args* a, int n, const GemmBeside& beside, hipStream_t st);
 // extension operands of several layers in one launch: the W side times coef and, with two = true, once more times coef2
 // P = NULL: without the X side (the projection writes it).  planes != NULL: also the bf16 planes [3][rp][d] of B fp32 [d][r]
 struct GemmExtArgs {

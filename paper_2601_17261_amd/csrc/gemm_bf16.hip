@@ -723,15 +723,46 @@ hipError_t launch_gemm_bf16_many(const GemmBf16Args* a, int n, bool half_cu, hip
         // squared errors of the mid kernel together, bf16 and fp32 targets apart.  (A stored output may take shares of d_in, which
         // only a launch of its own does)
         auto shared_launch = [&](int i) { return c[i].kernel == Kernel::mid && c[i].out == 0 && !c[i].g.sk_T; };
+        // Squared errors in 256 x 256 tiles together, and with them those that take 128 x 128 tiles alone, where that should be the faster
+        // way by 5 %: a 128 x 128 tile takes 0.48 us a slice and compute unit, 256 x 256 ones as launch_gemm_bf16_aligned_lists()
+        // reckons, and a launch more 10 us.  (Predicted and measured gain of both signs, us: 4B-sized on 3001 tokens 125 and 114, on
+        // 1500 75 and 63, on 512 -18 and 0, 8B-sized on 1000 69 and 64, on 300 -9 and -20, 0.6B-sized on 2048 -1 and -16, on 1000 -11 and -3)
+        const GemmParams* big[kBatchMax];
+        bool sub[kBatchMax], listed[kBatchMax] = {};
+        int nbig = 0, nsub = 0;
+        for (int i = 0; nb > 1 && !half_cu && i < nb; ++i)
+            if (c[i].kernel == Kernel::aligned && gemm_bf16_aligned_listed(c[i].p)) {
+                listed[i] = true;
+                sub[nbig] = false;
+                big[nbig++] = &c[i].p;
+            }
+        double mid_us = 0.0;
+        for (int i = 0; nb > 1 && !half_cu && i < nb; ++i)
+            if (shared_launch(i) && gemm_bf16_aligned_listed(c[i].p)) {
+                sub[nbig + nsub] = true;
+                big[nbig + nsub++] = &c[i].p;
+                mid_us += 0.48 / 256 * c[i].p.tiles_m * c[i].p.tiles_n * (double)((c[i].p.K + BK - 1) / BK + (c[i].p.Xext ? c[i].p.ext_ld / BK : 0));
+            }
+        if (nsub > 0) {
+            double alone = 0.0, together = 0.0;
+            e = launch_gemm_bf16_aligned_lists(big, sub, nbig, nullptr, &alone, st);
+            if (e == hipSuccess) e = launch_gemm_bf16_aligned_lists(big, sub, nbig + nsub, nullptr, &together, st);
+            if (e != hipSuccess) return e;
+            if (together < 0.0 || alone < 0.0 || 1.05 * together > alone + mid_us + (nbig > 0 ? 10.0 : 0.0)) nsub = 0;
+            for (int i = 0; i < nb && nsub > 0; ++i)
+                if (shared_launch(i) && gemm_bf16_aligned_listed(c[i].p)) listed[i] = true;
+        }
         for (int f32 = 0; f32 < 2; ++f32) {
             GemmItem g[kBatchMax];
             int ng = 0;
             for (int i = 0; i < nb; ++i)
-                if (shared_launch(i) && (c[i].p.target_dtype != AGZO_BF16) == (f32 != 0)) g[ng++] = c[i].g;
+                if (shared_launch(i) && !listed[i] && (c[i].p.target_dtype != AGZO_BF16) == (f32 != 0)) g[ng++] = c[i].g;
             if (ng == 0) continue;
             e = launch_gemm_bf16_mid(g, ng, 0, f32 != 0, half_cu, st);
             if (e != hipSuccess) return e;
         }
+        e = launch_gemm_bf16_aligned_lists(big, sub, nbig + nsub, nullptr, nullptr, st);
+        if (e != hipSuccess) return e;
         // the shared schedule's tiles together
         auto one_pass = [&](int i) { return c[i].kernel == Kernel::aligned && c[i].p.shared; };
         const GemmParams* sh[kBatchMax];
@@ -741,10 +772,38 @@ hipError_t launch_gemm_bf16_many(const GemmBf16Args* a, int n, bool half_cu, hip
         e = launch_gemm_bf16_aligned_shared(sh, ns, st);
         if (e != hipSuccess) return e;
         for (int i = 0; i < nb; ++i) {
-            if (a[b + i].M == 0 || a[b + i].N == 0 || shared_launch(i) || one_pass(i)) continue;
+            if (a[b + i].M == 0 || a[b + i].N == 0 || shared_launch(i) || listed[i] || one_pass(i)) continue;
             e = launch_one(c[i], st);
             if (e != hipSuccess) return e;
         }
+    }
+    return hipSuccess;
+}
+
+bool gemm_bf16_listed(const GemmBf16Args* a, int n) {
+    for (int i = 0; i < n; ++i) {
+        Choice c;
+        if (choose(a[i], c) != hipSuccess || c.prep || (c.kernel != Kernel::aligned && c.kernel != Kernel::mid) || !gemm_bf16_aligned_listed(c.p)) return false;
+    }
+    return true;
+}
+
+hipError_t launch_gemm_bf16_beside(const GemmBf16Args* a, int n, const GemmBeside& beside, hipStream_t st) {
+    for (int b = 0; b < n; b += kBatchMax) {
+        const int nb = n - b < kBatchMax ? n - b : kBatchMax;
+        Choice c[kBatchMax];
+        const GemmParams* big[kBatchMax];
+        bool sub[kBatchMax];
+        for (int i = 0; i < nb; ++i) {
+            hipError_t e = choose(a[b + i], c[i]);
+            if (e != hipSuccess) return e;
+            if (c[i].prep) return hipErrorInvalidValue;
+            big[i] = &c[i].p;
+            sub[i] = c[i].kernel == Kernel::mid;
+        }
+        const GemmBeside share{beside.latency_us * nb / n, beside.sweep_us * nb / n};
+        hipError_t e = launch_gemm_bf16_aligned_lists(big, sub, nb, &share, nullptr, st);
+        if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }

@@ -9,8 +9,10 @@
 //
 // RAGGED = false takes tile-aligned layers: M and N multiples of 256, d_in a multiple of 64, 16-byte aligned target / output
 // rows.  RAGGED = true takes the others.  The last tile of a direction starts at the last 256 rows (or columns) instead of
-// hanging over the edge, so no load needs a bound; squared error and softmax statistics leave out what the tile before it has
-// counted, stored outputs are stored twice with the same bits.  A last slice that d_in does not fill gets a descriptor with a
+// hanging over the edge, so no load needs a bound; softmax statistics leave out what the tile before it has counted, stored
+// outputs are stored twice with the same bits.  For the squared error the two halves of a tile do so each by itself (a tile's second
+// 128 rows start at the last 128 of the matrix at the latest), so that a wave's 128 x 128 outputs are those of a tile of
+// gemm_bf16_mid.hip, and leave out what the half before them has counted.  A last slice that d_in does not fill gets a descriptor with a
 // range, and the lanes past d_in an offset beyond it: they load zeros.  gemm_bf16.hip, which bounded every access and drained
 // its loads at every slice, ran 3001 x 2560 -> 9728 (both signs and none, with the smaller projections beside it) at 820
 // TFLOP/s and the cross-entropy head 3001 x 2048 -> 32000 at 937; this kernel at 1130 and 1105.
@@ -58,6 +60,10 @@
 // (or stored) while it travels, and the accumulators restart from minus the new target.  The tile list keeps the
 // order that makes an XCD's 32 workgroups share operand slices in its L2: XCD x (workgroup id mod 8) owns a contiguous
 // run of tiles, and its workgroups take them 32 at a time.
+//
+// CAP > 1: the lists go through the tiles of several problems (layers of a set, both signs); see TileLists and
+// launch_gemm_bf16_aligned_lists().  The operands of the next tile are another problem's then, so the choice of a slice's source works
+// out its offsets from that problem's row lengths.
 //
 // PHASES = 3 is the shared-forward schedule for a single layer: the d_in slices are multiplied once, f0 is the sum of
 // squares of the accumulators as they stand, the extension slices with +eps make them the residual of f+, the same
@@ -110,20 +116,44 @@ struct AlignedItem {
     const int32_t* ce_target; float2* ce_ms; float* ce_tl;
     unsigned long long* clk;
     int ext_ld, tiles_m, tiles_n, group_m, vec_ok;
+    int sub;                                       // partials are those of gemm_bf16_mid.hip: one per 128 x 128 outputs
 };
 
+// Tile lists over the tiles of several problems (one evaluation, squared error).  The tiles of a problem are dealt to the XCDs in runs
+// of equal length, the runs that are one longer starting at XCD long_at[q].  An XCD's workgroups (its slots) take full[q] rounds of
+// problem q together, problem after problem, and then what is left of the runs, slot s take[q][s] tiles of problem q.  (Operand slices
+// are shared through an XCD's L2 by workgroups that walk them in step: lists dealt without the rounds, each problem's tiles to whoever
+// is done first, took 2.4 % longer than launches of their own for the 8B-sized layers on 15028 tokens)
+constexpr int kListSlots = 32;                    // workgroups per XCD
+struct TileLists {
+    int n, slots;
+    uint8_t long_at[kBatchMax];
+    int full[kBatchMax];
+    uint32_t take[kBatchMax][kListSlots / 4];      // bytes
+    AlignedItem a[kBatchMax];
+};
+static_assert(sizeof(TileLists) <= 4096, "kernel arguments");
+
+template <int PHASES, int CAP>
+using AlignedArgs = typename std::conditional<(PHASES == 1 && CAP > 1), TileLists, KBatch<AlignedItem, CAP>>::type;
+
 template <int OUT, bool T_F32, int PHASES, bool RAGGED, int CAP>
-__global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const KBatch<AlignedItem, CAP> tb) {
-    static_assert(CAP == 1 || PHASES == 3, "tile lists are lists of one problem's tiles");
+__global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArgs<PHASES, CAP> tb) {
     static_assert(OUT == 0 || (PHASES == 1 && !T_F32), "the kernels without a squared-error target have one evaluation");
+    constexpr bool LISTS = PHASES == 1 && CAP > 1;
     constexpr bool LATE_T = RAGGED && OUT == 0;    // the target is subtracted after the last slice
+    // ... and the two 128-row halves of a tile end at the last row by themselves, as the tiles of gemm_bf16_mid.hip do
+    constexpr bool HALVES = RAGGED && OUT == 0;
     constexpr int NT = 256, BA = 4, BB = 4;
     constexpr int W_BASE = 0, X_BASE = 3 * TILE_BYTES;       // LDS: three W stages, then two X stages (all 160 KiB)
     extern __shared__ __align__(16) char smem[];
-    uint32_t wgid, unused;                                   // this problem's workgroups count from 0
-    const AlignedItem& p = tb.a[kbatch_find(tb, wgid, unused)];
+    uint32_t wgid = blockIdx.x, unused;                      // this problem's workgroups count from 0
+    // the problems of the current and of the next tile, by their places in the arguments (as pointers the compiler copies all of them
+    // to scratch memory)
+    int cq = 0, nq = 0;
+    if constexpr (!LISTS) cq = kbatch_find(tb, wgid, unused);
     const int tid = threadIdx.x, lane = tid & 63;
-    if (p.clk && wgid == 0 && tid == 0) { p.clk[0] = __builtin_readcyclecounter(); p.clk[1] = wall_clock64(); }
+    if (!LISTS && tb.a[cq].clk && wgid == 0 && tid == 0) { tb.a[cq].clk[0] = __builtin_readcyclecounter(); tb.a[cq].clk[1] = wall_clock64(); }
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wa = wave >> 1, wb = wave & 1;
     const int lc = lane & 15, lg = lane >> 4;      // matrix instruction 16x16x32: column (token) / row of a fragment, k group
@@ -133,50 +163,128 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const KBatch<Ali
     // its S workgroups S at a time; the up to 7 tiles left over go to the last workgroup of the first XCDs.  Inside a
     // run, tiles are ordered in bands of group_m token tiles per output tile, so that the tiles an XCD works on at any
     // moment share a few W tiles and a band of X tiles.
-    const int nwg = p.tiles_m * p.tiles_n;
-    const int G = (int)tb.gx[CAP == 1 ? 0 : &p - tb.a];
+    // LISTS: the same over the runs of several problems; the lists are the launch's, which knows what a tile of each takes.
+    int64_t tm = 0, tn = 0;
+    auto tile_of = [&](const AlignedItem& a, int lin, int64_t& tm_, int64_t& tn_) __attribute__((always_inline)) {
+        const int group = lin / (a.group_m * a.tiles_n);
+        const int first_m = group * a.group_m;
+        const int gsz = min(a.group_m, a.tiles_m - first_m);
+        const int in_group = lin - group * a.group_m * a.tiles_n;
+        tm_ = __builtin_amdgcn_readfirstlane(first_m + in_group % gsz);
+        tn_ = __builtin_amdgcn_readfirstlane(in_group / gsz);
+    };
+    // lists of one problem's tiles
+    int G = 0;
+    if constexpr (!LISTS) G = (int)tb.gx[CAP == 1 ? 0 : cq];
+    const int nwg = LISTS ? 0 : tb.a[cq].tiles_m * tb.a[cq].tiles_n;
     const bool by_xcd = (G % 8 == 0);
     const int S = by_xcd ? G / 8 : G;
     const int xcd = by_xcd ? (int)wgid % 8 : 0, slot = by_xcd ? (int)wgid / 8 : (int)wgid;
     const int per = by_xcd ? nwg / 8 : nwg;
     const int n_run = slot < per ? (per - slot + S - 1) / S : 0;
     const int n_tiles = __builtin_amdgcn_readfirstlane(n_run + ((by_xcd && slot == S - 1 && xcd < nwg - 8 * per) ? 1 : 0));
-    const int GROUP_M = p.group_m;
-    int64_t tm = 0, tn = 0;
     auto tile_at = [&](int i, int64_t& tm_, int64_t& tn_) __attribute__((always_inline)) {
-        const int lin = (i < n_run) ? xcd * per + slot + i * S : 8 * per + xcd;
-        const int group = lin / (GROUP_M * p.tiles_n);
-        const int first_m = group * GROUP_M;
-        const int gsz = min(GROUP_M, p.tiles_m - first_m);
-        const int in_group = lin - group * GROUP_M * p.tiles_n;
-        tm_ = __builtin_amdgcn_readfirstlane(first_m + in_group % gsz);
-        tn_ = __builtin_amdgcn_readfirstlane(in_group / gsz);
+        tile_of(tb.a[cq], (i < n_run) ? xcd * per + slot + i * S : 8 * per + xcd, tm_, tn_);
     };
-    if (n_tiles == 0) return;
-    tile_at(0, tm, tn);
+    // lists over several problems: problem (l_rest: what is left of it) and round of this workgroup's next tile, the tiles of the run
+    // taken in earlier rounds, and, lane by lane, how many tiles the slots of the XCD take of the problem
+    int l_q = -1, l_rest = 0, l_base = 0, l_round = 0, l_run = 0, l_begin = 0, l_take = 0;
+    int l_ext = 0, l_ldx = 0, l_ldw = 0, l_ldxn = 0, l_ldwn = 0;      // row lengths of the current and the next tile's problem
+    bool l_more = true;
+    // nq, tmn, tnn <- the next tile of the list; left alone behind its end
+    int64_t tmn = 0, tnn = 0;
+    auto advance = [&]() __attribute__((always_inline)) {
+        if constexpr (LISTS) {
+            const int lxcd = (int)(blockIdx.x % 8), lslot = (int)(blockIdx.x / 8);
+            for (;;) {
+                const uint32_t m = (uint32_t)__builtin_amdgcn_ballot_w64(l_take > l_round);
+                if ((m >> lslot) & 1) {
+                    const int at = l_base + __builtin_popcount(m & ((1u << lslot) - 1));
+                    l_base += __builtin_popcount(m);
+                    ++l_round;
+                    if (at < l_run) {
+                        nq = l_q;
+                        tile_of(tb.a[l_q], l_begin + at, tmn, tnn);
+                        return;
+                    }
+                }
+                ++l_q;
+                if (l_q == tb.n) {
+                    if (l_rest) { l_more = false; return; }
+                    l_rest = 1;
+                    l_q = 0;
+                }
+                const int q = l_q;
+                const int tiles = tb.a[q].tiles_m * tb.a[q].tiles_n, share = tiles / 8, longer = tiles - 8 * share;
+                const int at8 = (lxcd - (int)tb.long_at[q]) & 7;      // this XCD's place among the runs
+                l_begin = at8 * share + min(at8, longer);
+                l_run = share + (at8 < longer ? 1 : 0);
+                l_round = 0;
+                l_base = l_rest * tb.full[q] * tb.slots;
+                uint32_t w = tb.take[q][0];
+#pragma unroll
+                for (int k = 1; k < kListSlots / 4; ++k) w = ((lane >> 2) & 7) == k ? tb.take[q][k] : w;
+                l_take = (int)((w >> (8 * (lane & 3))) & 255u);
+                l_take = l_rest ? l_take : (lane & 31) < tb.slots ? tb.full[q] : 0;
+            }
+        }
+    };
+    if constexpr (LISTS) {
+        advance();
+        if (!l_more) return;
+        cq = nq; tm = tmn; tn = tnn;
+        advance();
+    } else {
+        if (n_tiles == 0) return;
+        tile_at(0, tm, tn);
+    }
     // first row and column of a tile
-    auto origin_m = [&](int64_t t) __attribute__((always_inline)) { return RAGGED ? min(t * BT, p.M - BT) : t * BT; };
-    auto origin_n = [&](int64_t t) __attribute__((always_inline)) { return RAGGED ? min(t * BT, p.N - BT) : t * BT; };
-    int64_t m0 = origin_m(tm), n0 = origin_n(tn);
+    auto origin = [&](int64_t t, int64_t size) __attribute__((always_inline)) {
+        return HALVES ? min(t * BT, size - BT / 2) : RAGGED ? min(t * BT, size - BT) : t * BT;
+    };
+    // HALVES: rows between the first row of the second half and where it would be in a tile that lies inside the matrix (<= 0)
+    auto second_half = [&](int64_t t, int64_t size) __attribute__((always_inline)) {
+        return HALVES ? (int)(min(t * BT + BT / 2, size - BT / 2) - (origin(t, size) + BT / 2)) : 0;
+    };
+    int64_t m0 = origin(tm, tb.a[cq].M), n0 = origin(tn, tb.a[cq].N);
+    int hm = second_half(tm, tb.a[cq].M), hn = second_half(tn, tb.a[cq].N), hmn = 0, hnn = 0;
 
     // ---- operand sources: X / W slices, then the prepared extension operands ----------------------
-    const bool has_ext = p.Xext != nullptr;
     // operand bases of the current tile (d_in slices, extension slices) and of the next tile's d_in slices
     const bf16_t *xb, *wb_, *xb2, *wb2, *wb3, *xbn, *wbn;
     auto tile_sources = [&]() __attribute__((always_inline)) {
-        xb = p.X + m0 * p.ldx;
-        wb_ = p.W + n0 * p.ldw;
-        xb2 = has_ext ? p.Xext + m0 * p.ext_ld : xb;
-        wb2 = has_ext ? p.Wext + n0 * p.ext_ld : wb_;
-        wb3 = (has_ext && PHASES == 3) ? p.Wext2 + n0 * p.ext_ld : wb_;
+        const bool has_ext = tb.a[cq].Xext != nullptr;
+        xb = tb.a[cq].X + m0 * tb.a[cq].ldx;
+        wb_ = tb.a[cq].W + n0 * tb.a[cq].ldw;
+        xb2 = has_ext ? tb.a[cq].Xext + m0 * tb.a[cq].ext_ld : xb;
+        wb2 = has_ext ? tb.a[cq].Wext + n0 * tb.a[cq].ext_ld : wb_;
+        wb3 = (has_ext && PHASES == 3) ? tb.a[cq].Wext2 + n0 * tb.a[cq].ext_ld : wb_;
     };
-    // i: index of the tile after the current one; past the list: the current tile once more (its first slices are
-    // fetched again into the stage nobody reads)
+    // the tile after the current one (i: its index; LISTS: the list's next); past the list: the current tile once more (its first
+    // slices are fetched again into the stage nobody reads)
     auto next_sources = [&](int i) __attribute__((always_inline)) {
-        int64_t tmn = tm, tnn = tn;
-        if (i < n_tiles) tile_at(i, tmn, tnn);
-        xbn = p.X + origin_m(tmn) * p.ldx;
-        wbn = p.W + origin_n(tnn) * p.ldw;
+        if constexpr (LISTS) {
+            if (!l_more) { nq = cq; tmn = tm; tnn = tn; }
+        } else {
+            nq = cq; tmn = tm; tnn = tn;
+            if (i < n_tiles) tile_at(i, tmn, tnn);
+        }
+        xbn = tb.a[nq].X + origin(tmn, tb.a[nq].M) * tb.a[nq].ldx;
+        wbn = tb.a[nq].W + origin(tnn, tb.a[nq].N) * tb.a[nq].ldw;
+        hmn = second_half(tmn, tb.a[nq].M);
+        hnn = second_half(tnn, tb.a[nq].N);
+        if (LISTS) { l_ldxn = (int)tb.a[nq].ldx; l_ldwn = (int)tb.a[nq].ldw; }
+    };
+    // on to the next tile
+    auto next_tile = [&](int it) __attribute__((always_inline)) {
+        if constexpr (LISTS) {
+            cq = nq; tm = tmn; tn = tnn;
+            advance();
+        } else {
+            tile_at(it + 1, tm, tn);
+        }
+        m0 = origin(tm, tb.a[cq].M);   n0 = origin(tn, tb.a[cq].N);
+        hm = second_half(tm, tb.a[cq].M);   hn = second_half(tn, tb.a[cq].N);
     };
     tile_sources();
     next_sources(1);
@@ -184,15 +292,23 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const KBatch<Ali
     // further on is 8 more)
     const int row0 = 8 * wave + (lane >> 3);
     const int chunk0 = (lane & 7) ^ ((row0 >> 1) & 7);       // the swizzle term does not depend on t
-    const int vx = (int)(((int64_t)row0 * p.ldx + chunk0 * 8) * 2), vw = (int)(((int64_t)w_perm64(row0) * p.ldw + chunk0 * 8) * 2);
-    const int vx2 = (row0 * p.ext_ld + chunk0 * 8) * 2, vw2 = (w_perm64(row0) * p.ext_ld + chunk0 * 8) * 2;
-    const int gsx = (int)(64 * p.ldx), gsw = (int)(64 * p.ldw), gs2 = 64 * p.ext_ld;   // bytes between row groups
-    const int nfull = (int)(p.K / BK), nd = RAGGED ? (int)((p.K + BK - 1) / BK) : nfull;      // d_in slices: whole ones, all
-    const int tail_off = (RAGGED && chunk0 * 8 >= (int)(p.K % BK)) ? kPastEnd : 0;               // (of the slice that is not whole)
-    const int next = has_ext ? p.ext_ld / BK : 0;
-    // slices that ride the load pipeline: the d_in slices, and in the one-evaluation kernel the extension behind them
-    // (at least two: the first two slices of a tile are always d_in slices)
-    const int npipe = nd + (PHASES == 1 ? next : 0);
+    const int wrow0 = w_perm64(row0);
+    const int vx = (int)(((int64_t)row0 * tb.a[cq].ldx + chunk0 * 8) * 2), vw = (int)(((int64_t)wrow0 * tb.a[cq].ldw + chunk0 * 8) * 2);
+    const int vx2 = (row0 * tb.a[cq].ext_ld + chunk0 * 8) * 2, vw2 = (wrow0 * tb.a[cq].ext_ld + chunk0 * 8) * 2;
+    const int gsx = (int)(64 * tb.a[cq].ldx), gsw = (int)(64 * tb.a[cq].ldw), gs2 = 64 * tb.a[cq].ext_ld;   // bytes between row groups
+    int nfull = 0, nd = 0, next = 0, npipe = 0, ktail = 0;
+    // d_in slices (whole ones, all) and extension slices of the current tile's problem; npipe: slices that ride the load
+    // pipeline, the d_in slices and in the one-evaluation kernel the extension behind them (at least two: the first two slices of a
+    // tile are always d_in slices)
+    auto count_slices = [&]() __attribute__((always_inline)) {
+        nfull = (int)(tb.a[cq].K / BK);
+        nd = RAGGED ? (int)((tb.a[cq].K + BK - 1) / BK) : nfull;
+        next = tb.a[cq].Xext != nullptr ? tb.a[cq].ext_ld / BK : 0;
+        npipe = nd + (PHASES == 1 ? next : 0);
+        if (RAGGED) ktail = (int)(tb.a[cq].K % BK);
+        if (LISTS) { l_ext = tb.a[cq].ext_ld; l_ldx = (int)tb.a[cq].ldx; l_ldw = (int)tb.a[cq].ldw; }
+    };
+    count_slices();
     typedef __attribute__((address_space(3))) void* lptr_t;
 
     // ---- accumulators <- minus the target tile ----------------------------------------------------
@@ -204,16 +320,16 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const KBatch<Ali
     uint4 traw[32];
     auto tload = [&](auto JJ) __attribute__((always_inline)) {
         constexpr int J = decltype(JJ)::value;
-        const int64_t row = m0 + wb * 128 + J * 16 + lc;
-        const int64_t colw = n0 + wa * 128 + lg * 16;
+        const int64_t row = m0 + wb * (128 + hm) + J * 16 + lc;
+        const int64_t colw = n0 + wa * (128 + hn) + lg * 16;
         if (T_F32) {
-            const uint4* src = reinterpret_cast<const uint4*>(reinterpret_cast<const float*>(p.target) + row * p.ldt + colw);
+            const uint4* src = reinterpret_cast<const uint4*>(reinterpret_cast<const float*>(tb.a[cq].target) + row * tb.a[cq].ldt + colw);
 #pragma clang loop unroll(full)
             for (int i4 = 0; i4 < 2; ++i4)
 #pragma clang loop unroll(full)
                 for (int q = 0; q < 4; ++q) traw[(J & 3) * 8 + i4 * 4 + q] = RAGGED ? load16_any(src + i4 * 16 + q) : src[i4 * 16 + q];
         } else {
-            const uint4* src = reinterpret_cast<const uint4*>(reinterpret_cast<const bf16_t*>(p.target) + row * p.ldt + colw);
+            const uint4* src = reinterpret_cast<const uint4*>(reinterpret_cast<const bf16_t*>(tb.a[cq].target) + row * tb.a[cq].ldt + colw);
 #pragma clang loop unroll(full)
             for (int i4 = 0; i4 < 2; ++i4)
 #pragma clang loop unroll(full)
@@ -295,11 +411,14 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const KBatch<Ali
     // vector offsets of a lane's eight row groups per operand, kept in registers: worked out in front of each load they
     // put an add and its latency between a matrix instruction and the load behind it
     int src_vxt[8], src_vwt[8];
-    auto set_offsets = [&](int v0x, int gx, int v0w, int gw) __attribute__((always_inline)) {
+    // (hx, hw: bytes that the second half's rows lie further on)
+    auto set_offsets = [&](int v0x, int gx, int hx, int v0w, int gw, int hw) __attribute__((always_inline)) {
 #pragma unroll
-        for (int t = 0; t < 8; ++t) { src_vxt[t] = v0x + t * gx; src_vwt[t] = v0w + (t >> 1) * (2 * gw) + (t & 1) * (gw >> 2); }
+        for (int t = 0; t < 8; ++t) {
+            src_vxt[t] = v0x + t * gx + (HALVES && t >= 4 ? hx : 0);
+            src_vwt[t] = v0w + (t >> 1) * (2 * gw) + (t & 1) * (gw >> 2) + (HALVES && t >= 4 ? hw : 0);
+        }
     };
-    set_offsets(vx, gsx, vw, gsw);
     // kt counts from the current tile's first slice; npipe and npipe + 1 are the first two slices of the next tile.
     // Two rounds of selects, each on one condition, between values (a select between captured references becomes a
     // computed address into the closure, which then stays in memory with everything it points to; and selects on
@@ -307,26 +426,40 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const KBatch<Ali
     auto select_slice = [&](int kt) __attribute__((always_inline)) {
         // (copies first: the selects then see values, not addresses of captured variables)
         const bf16_t *cxb = xb, *cwb = wb_, *cxb2 = xb2, *cwb2 = wb2, *cxbn = xbn, *cwbn = wbn;
-        const int cvx = vx, cvw = vw, cvx2 = vx2, cvw2 = vw2, cgsx = gsx, cgsw = gsw, cgs2 = gs2;
         const bool e = kt >= nd;                             // extension operands (or, past npipe, the next tile)
         const bf16_t* xs = e ? cxb2 : cxb;
         const bf16_t* ws = e ? cwb2 : cwb;
-        int svx = e ? cvx2 : cvx, svw = e ? cvw2 : cvw, sgx = e ? cgs2 : cgsx, sgw = e ? cgs2 : cgsw;
         int so = e ? kt - nd : kt;
         const bool nxt = kt >= npipe;
         xs = nxt ? cxbn : xs;
         ws = nxt ? cwbn : ws;
-        svx = nxt ? cvx : svx;   svw = nxt ? cvw : svw;   sgx = nxt ? cgsx : sgx;   sgw = nxt ? cgsw : sgw;
         so = nxt ? kt - npipe : so;
+        int svx, svw, sgx, sgw, hx = 0, hw = 0;
+        if constexpr (LISTS) {
+            // (the next tile may be another problem's: its offsets from its row lengths)
+            const int cle = l_ext, clx = l_ldx, clw = l_ldw, cnx = l_ldxn, cnw = l_ldwn;
+            int lx = e ? cle : clx, lw = e ? cle : clw;
+            lx = nxt ? cnx : lx;   lw = nxt ? cnw : lw;
+            svx = (row0 * lx + chunk0 * 8) * 2;   svw = (wrow0 * lw + chunk0 * 8) * 2;
+            sgx = 64 * lx;   sgw = 64 * lw;
+        } else {
+            const int cvx = vx, cvw = vw, cvx2 = vx2, cvw2 = vw2, cgsx = gsx, cgsw = gsw, cgs2 = gs2;
+            svx = e ? cvx2 : cvx;   svw = e ? cvw2 : cvw;   sgx = e ? cgs2 : cgsx;   sgw = e ? cgs2 : cgsw;
+            svx = nxt ? cvx : svx;   svw = nxt ? cvw : svw;   sgx = nxt ? cgsx : sgx;   sgw = nxt ? cgsw : sgw;
+        }
+        if constexpr (HALVES) {
+            const int chm = hm, chn = hn, chmn = hmn, chnn = hnn;
+            hx = (nxt ? chmn : chm) * (sgx / 32);   hw = (nxt ? chnn : chn) * (sgw / 32);
+        }
         uint32_t bytes = 0xFFFFFFFFu;
         if constexpr (RAGGED) {
             const bool last = kt == nfull && kt < nd;        // the slice that d_in does not fill
-            const int past = last ? tail_off : 0;
+            const int past = (last && chunk0 * 8 >= ktail) ? kPastEnd : 0;
             svx += past;   svw += past;
             bytes = last ? (uint32_t)kPastEnd : bytes;
         }
         src_rsx = rsrc(xs, bytes);   src_rsw = rsrc(ws, bytes);
-        set_offsets(svx, sgx, svw, sgw);
+        set_offsets(svx, sgx, hx, svw, sgw, hw);
         src_so = so * (BK * 2);
     };
     // direct load of row group t (0..7) of the selected slice: X into X stage buf (0..1), W into W stage buf (0..2)
@@ -400,14 +533,16 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const KBatch<Ali
     // fixed order ----
     // The four waves' sums meet in LDS, in `red`: the head of a W stage that nothing reads or fills at that moment
     // (the operand stages take all of the LDS)
-    // rs, cs: rows and columns of the tile that the tile before it has counted (the last tile of a direction starts at the
-    // last 256 rows or columns instead of hanging over the edge).  A column tile that overlaps by no multiple of 16, and all tiles of
+    // HALVES: rows and columns of the wave's half that the half before it has counted are left out (a half beyond the last row or
+    // column has nothing that counts).  A column tile that overlaps the one before it by no multiple of 16, and all tiles of
     // a layer whose target rows do not start on 16 bytes, are squared in fp64 as well: what gemm_bf16.hip squares so keeps its
     // precision here.  (Otherwise a lane's 16 columns of a group count or do not count together; the wide form takes some 2 us more
     // a tile)
-    auto eval_sum = [&](int rs, int cs) __attribute__((always_inline)) {
-        double part = 0.0;
+    // The sums of the wave's four 64 x 64 blocks: outputs, tokens
+    auto eval_sum = [&](double (&part)[2][2]) __attribute__((always_inline)) {
+        part[0][0] = part[0][1] = part[1][0] = part[1][1] = 0.0;
         if constexpr (PHASES == 1) settle();
+        const int rs = HALVES ? (int)(tm * BT - m0) - wb * hm : 0, cs0 = HALVES ? (int)(tn * BT - n0) : 0, cs = cs0 - wa * hn;
         auto sum = [&](auto WIDE) __attribute__((always_inline)) {
             constexpr bool wide = decltype(WIDE)::value != 0;
 #pragma clang loop unroll(full)
@@ -415,16 +550,17 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const KBatch<Ali
                 if (LATE_T && PHASES == 1 && T_F32 && J == 4) { tload(IC<4>{}); tload(IC<5>{}); tload(IC<6>{}); tload(IC<7>{}); }
                 // the first of the lane's 16 columns per group that counts
                 int from[2] = {0, 0};
-                if (RAGGED) {
-                    const bool in = wb * 128 + J * 16 + lc >= rs;
-                    from[0] = in ? cs - (wa * 128 + lg * 16) : 16;
-                    from[1] = in ? cs - (wa * 128 + 64 + lg * 16) : 16;
+                if (HALVES) {
+                    const bool in = J * 16 + lc >= rs;
+                    from[0] = in ? cs - lg * 16 : 16;
+                    from[1] = in ? cs - (64 + lg * 16) : 16;
                     // (or the compiler works out all conditions ahead and keeps them)
                     asm volatile("" : "+v"(from[0]), "+v"(from[1]));
                 }
 #pragma clang loop unroll(full)
                 for (int I = 0; I < 8; ++I) {
                     const floatx4 v = acc[I][J];
+                    double& sum64 = part[HALVES ? I >> 2 : 0][HALVES ? J >> 2 : 0];
                     float s4 = 0.f;
 #pragma clang loop unroll(full)
                     for (int u = 0; u < 4; ++u) {
@@ -433,33 +569,51 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const KBatch<Ali
                         if (LATE_T && PHASES == 1) x -= target_value(J, I, u);
                         if (wide) {
                             const double xd = (I & 3) * 4 + u >= from[I >> 2] ? (double)x : 0.0;
-                            part = fma(xd, xd, part);
+                            sum64 = fma(xd, xd, sum64);
                         } else {
                             s4 = fmaf(x, x, s4);
                         }
                     }
-                    if (!wide) part += (double)(!RAGGED || from[I >> 2] <= 0 ? s4 : 0.f);
+                    if (!wide) sum64 += (double)(!HALVES || from[I >> 2] <= 0 ? s4 : 0.f);
                 }
             }
         };
-        if (RAGGED && ((cs & 15) != 0 || !p.vec_ok)) sum(IC<1>{});
+        if (HALVES && (((LISTS && tb.a[cq].sub ? cs : cs0 | (cs0 - hn)) & 15) != 0 || !tb.a[cq].vec_ok)) sum(IC<1>{});
         else sum(IC<0>{});
-        return part;
     };
-    auto eval_finish = [&](double part, int phase, int64_t tm_, int64_t tn_, double* red) __attribute__((always_inline)) {
+    // of one problem's tile
+    auto eval_finish = [&](const double (&part4)[2][2], const AlignedItem& a, int phase, int64_t tm_, int64_t tn_, double* red) __attribute__((always_inline)) {
+        if (LISTS && HALVES && a.sub) {
+            // the wave's half of the tile is a tile of gemm_bf16_mid.hip: its lanes, then its four blocks, in the order of that kernel's
+            // lanes and waves.  Each step of the sum over the lanes halves the blocks that a lane sums
+            const bool out1 = (lane & 32) != 0, tok1 = (lane & 16) != 0;
+            const double a0 = (out1 ? part4[1][0] : part4[0][0]) + __shfl_xor(out1 ? part4[0][0] : part4[1][0], 32);
+            const double a1 = (out1 ? part4[1][1] : part4[0][1]) + __shfl_xor(out1 ? part4[0][1] : part4[1][1], 32);
+            double b = (tok1 ? a1 : a0) + __shfl_xor(tok1 ? a0 : a1, 16);
+#pragma unroll
+            for (int off = 8; off > 0; off >>= 1) b += __shfl_xor(b, off);
+            b += __shfl_xor(b, 16);
+            b += __shfl_xor(b, 32);
+            const int64_t bm = 2 * tm_ + wb, bn = 2 * tn_ + wa, blocks_n = (a.N + BT / 2 - 1) / (BT / 2);
+            if (lane == 0 && bm * (BT / 2) < a.M && bn < blocks_n) a.partials[bm * blocks_n + bn] = b;
+            return;
+        }
+        double part = HALVES ? (part4[0][0] + part4[0][1]) + (part4[1][0] + part4[1][1]) : part4[0][0];
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) part += __shfl_xor(part, off);
         if (lane == 0) red[phase * 4 + wave] = part;
         __syncthreads();
         if (tid == 0)
-            p.partials[(int64_t)phase * p.tiles_m * p.tiles_n + tm_ * p.tiles_n + tn_] =
+            a.partials[(int64_t)phase * a.tiles_m * a.tiles_n + tm_ * a.tiles_n + tn_] =
                 (red[phase * 4] + red[phase * 4 + 1]) + (red[phase * 4 + 2] + red[phase * 4 + 3]);
         // (one-evaluation kernel: the next slice's loads go into this stage, and no wave may issue them before the sums
         // have been read)
         if constexpr (PHASES == 1) __syncthreads();
     };
-    auto evaluate = [&](int phase, int64_t tm_, int64_t tn_, double* red) __attribute__((always_inline)) {
-        eval_finish(eval_sum((int)(tm * BT - m0), (int)(tn * BT - n0)), phase, tm_, tn_, red);
+    auto evaluate = [&](int phase, double* red) __attribute__((always_inline)) {
+        double part[2][2];
+        eval_sum(part);
+        eval_finish(part, tb.a[cq], phase, tm, tn, red);
     };
 
     // accumulators <- minus the target tile (squared error) or zero (stored output)
@@ -537,7 +691,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const KBatch<Ali
         }
         // the tile's last matrix instruction has issued; the stages of slice g hold the next tile's first slice, fragment
         // set 0 its sub-step 0, and its second slice is in flight; W stage wst - 1 is idle until the next W loads
-        const bool more = it + 1 < n_tiles;
+        const bool more = LISTS ? l_more : it + 1 < n_tiles;
         if constexpr (OUT == 1) {
             // A lane holds 16 consecutive outputs of one token per group of four blocks, so stored from the registers every
             // store touches 16 rows.  Instead each wave passes its 128 x 128 block through LDS, 32 tokens at a time, in its
@@ -570,7 +724,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const KBatch<Ali
                 for (int n = 0; n < 8; ++n) {
                     const int t = 4 * n + (lane >> 4);
                     const uint4 v = *reinterpret_cast<const uint4*>(stg + t * 256 + ((cc ^ (t & 15)) << 4));
-                    bf16_t* dst = reinterpret_cast<bf16_t*>(p.Y) + (m0 + wb * 128 + r2 * 32 + t) * p.ldy + n0 + wa * 128 + cc * 8;
+                    bf16_t* dst = reinterpret_cast<bf16_t*>(tb.a[cq].Y) + (m0 + wb * 128 + r2 * 32 + t) * tb.a[cq].ldy + n0 + wa * 128 + cc * 8;
                     if (RAGGED) store16_any(dst, v);
                     else *reinterpret_cast<uint4*>(dst) = v;
                 }
@@ -589,7 +743,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const KBatch<Ali
             auto statistics = [&](int J, auto SKIP) __attribute__((always_inline)) {
                 constexpr bool skip = decltype(SKIP)::value != 0;
                 const int64_t row = m0 + wb * 128 + J * 16 + lc;
-                const int tgt = p.ce_target[row];
+                const int tgt = tb.a[cq].ce_target[row];
                 float mx = -INFINITY;
 #pragma clang loop unroll(full)
                 for (int i4 = 0; i4 < 2; ++i4)
@@ -615,7 +769,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const KBatch<Ali
                 sm += __shfl_xor(sm, 16);
                 sm += __shfl_xor(sm, 32);
                 const int64_t chunk = tn * 2 + wa;           // of tiles_n x 2 chunks per token
-                if (lg == 0) p.ce_ms[chunk * p.M + row] = make_float2(mx, sm);
+                if (lg == 0) tb.a[cq].ce_ms[chunk * tb.a[cq].M + row] = make_float2(mx, sm);
                 // the target's logit: one token in d_out / 128 has its target among the wave's columns, so most waves have none in
                 // the block's sixteen, and nothing to look for (looked for along with the maximum it was two instructions a logit)
                 const int64_t trel = (int64_t)tgt - (n0 + wa * 128);
@@ -632,7 +786,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const KBatch<Ali
                                 const float y = from_acc(acc[i4 * 4 + t][J][e]);
                                 if (grp == i4 && at == 4 * t + e) tl = y;
                             }
-                    if (mine) p.ce_tl[row] = tl;
+                    if (mine) tb.a[cq].ce_tl[row] = tl;
                 }
             };
             auto tile_statistics = [&](auto SKIP) __attribute__((always_inline)) {
@@ -645,28 +799,24 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const KBatch<Ali
             if (!more) break;
         } else if constexpr (PHASES == 1) {
             const int64_t tm_done = tm, tn_done = tn;
-            const int rs = RAGGED ? (int)(tm * BT - m0) : 0, cs = RAGGED ? (int)(tn * BT - n0) : 0;
-            double part;
+            const int q_done = cq;
+            double part[2][2];
             if constexpr (LATE_T) {
                 request_target();
-                part = eval_sum(rs, cs);
-                if (more) {
-                    tile_at(it + 1, tm, tn);
-                    m0 = origin_m(tm); n0 = origin_n(tn);
-                }
+                eval_sum(part);
+                if (more) next_tile(it);
             } else if (more) {
-                tile_at(it + 1, tm, tn);
-                m0 = origin_m(tm); n0 = origin_n(tn);
+                next_tile(it);
                 // The next tile's target is requested and the finished tile summed, in one order by two of the waves and in
                 // the other by the other two: a request keeps its wave's issue port for as long as the address unit takes
                 // over its 64 rows, and the address unit is the compute unit's one, so four waves requesting at once wait
                 // for each other while nobody sums
-                if (wave < 2) { request_target(); part = eval_sum(rs, cs); }
-                else { part = eval_sum(rs, cs); request_target(); }
+                if (wave < 2) { request_target(); eval_sum(part); }
+                else { eval_sum(part); request_target(); }
             } else {
-                part = eval_sum(rs, cs);
+                eval_sum(part);
             }
-            eval_finish(part, 0, tm_done, tn_done, reinterpret_cast<double*>(smem + W_BASE + ((wst == 0) ? 2 : wst - 1) * TILE_BYTES));
+            eval_finish(part, tb.a[q_done], 0, tm_done, tn_done, reinterpret_cast<double*>(smem + W_BASE + ((wst == 0) ? 2 : wst - 1) * TILE_BYTES));
             if (!more) break;
         } else {
             // shared forward: one tile per workgroup.  All LDS stages are free once the re-fetched slices have landed: the
@@ -680,8 +830,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const KBatch<Ali
                 for (int q = 0; q < 16; ++q) {
                     const int t = q >> 1;
                     char* dst = smem + buf * TILE_BYTES + wave * 1024 + t * 4096 + ((q & 1) ? W_BASE : X_BASE);
-                    if (q & 1) __builtin_amdgcn_raw_ptr_buffer_load_lds(rws, (lptr_t)dst, 16, vw2 + (t >> 1) * (2 * gs2) + (t & 1) * (gs2 >> 2), e * (BK * 2), 0, 0);
-                    else __builtin_amdgcn_raw_ptr_buffer_load_lds(rx2, (lptr_t)dst, 16, vx2 + t * gs2, e * (BK * 2), 0, 0);
+                    if (q & 1) __builtin_amdgcn_raw_ptr_buffer_load_lds(rws, (lptr_t)dst, 16, vw2 + (t >> 1) * (2 * gs2) + (t & 1) * (gs2 >> 2) + (HALVES && t >= 4 ? hn * (gs2 / 32) : 0), e * (BK * 2), 0, 0);
+                    else __builtin_amdgcn_raw_ptr_buffer_load_lds(rx2, (lptr_t)dst, 16, vx2 + t * gs2 + (HALVES && t >= 4 ? hm * (gs2 / 32) : 0), e * (BK * 2), 0, 0);
                 }
             };
             if (next > 0) ext_dma(rw2, 0, 0);
@@ -700,7 +850,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const KBatch<Ali
             // (rolled: the accumulators of three evaluations in a row end up in scratch memory)
 #pragma clang loop unroll(disable)
             for (int ph = 0;; ++ph) {
-                evaluate(ph, tm, tn, red);
+                evaluate(ph, red);
                 if (ph == 2) break;
                 const __amdgpu_buffer_rsrc_t rwp = rsrc(ph == 0 ? wb2 : wb3);
                 if (ph == 0) ext_dma(rw3, 0, 1);
@@ -718,19 +868,17 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const KBatch<Ali
             break;
         }
         // ---- hand the accumulators to the next tile ----
-        if constexpr (OUT != 0) {
-            tile_at(it + 1, tm, tn);
-            m0 = origin_m(tm); n0 = origin_n(tn);
-        }
+        if constexpr (OUT != 0) next_tile(it);
+        if constexpr (LISTS) count_slices();
         tile_sources();
         next_sources(it + 2);
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);                      // the slices fetched past the end of the list
-    if (p.clk && wgid == 0 && tid == 0) { p.clk[2] = __builtin_readcyclecounter(); p.clk[3] = wall_clock64(); }
+    if (!LISTS && tb.a[cq].clk && wgid == 0 && tid == 0) { tb.a[cq].clk[2] = __builtin_readcyclecounter(); tb.a[cq].clk[3] = wall_clock64(); }
 }
 
 template <int OUT, bool T_F32, int PHASES, bool RAGGED, int CAP>
-static hipError_t launch_aligned_grid(const KBatch<AlignedItem, CAP>& tb, unsigned blocks, hipStream_t st) {
+static hipError_t launch_aligned_grid(const AlignedArgs<PHASES, CAP>& tb, unsigned blocks, hipStream_t st) {
     static bool attr_set = false;
     const int smem = 5 * TILE_BYTES;           // three W stages and two X stages: all 160 KiB of a compute unit's LDS
     if (!attr_set) {
@@ -749,7 +897,8 @@ static AlignedItem aligned_item(const GemmParams& p) {
     a.ldx = p.ldx; a.ldw = p.ldw; a.M = p.M; a.N = p.N; a.K = p.K; a.ldt = p.ldt; a.ldy = p.ldy;
     a.target = p.target; a.partials = p.partials; a.Y = p.Y;
     a.ce_target = p.ce_target; a.ce_ms = p.ce_ms; a.ce_tl = p.ce_tl; a.clk = p.clk;
-    a.ext_ld = p.ext_ld; a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n; a.group_m = p.group_m; a.vec_ok = p.vec_ok;
+    a.ext_ld = p.ext_ld; a.tiles_m = (int)((p.M + BT - 1) / BT); a.tiles_n = (int)((p.N + BT - 1) / BT); a.group_m = p.group_m; a.vec_ok = p.vec_ok;
+    a.sub = 0;
     return a;
 }
 
@@ -766,7 +915,136 @@ static hipError_t launch_aligned_lists(const GemmParams& p, hipStream_t st) {
     int64_t G = ((int64_t)p.tiles_m * p.tiles_n + 7) / 8 * 8;
     if (G > cus) G = cus >= 8 ? cus - cus % 8 : cus;
     const KBatch<AlignedItem, 1> tb{1, {0}, {(uint32_t)G}, {aligned_item(p)}};
-    return launch_aligned_grid<OUT, T_F32, 1, RAGGED>(tb, (unsigned)G, st);
+    return launch_aligned_grid<OUT, T_F32, 1, RAGGED, 1>(tb, (unsigned)G, st);
+}
+
+static hipError_t list_slots(int* slots) {
+    int dev = 0, cus = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    *slots = cus / 8 < kListSlots ? cus / 8 : kListSlots;
+    return cus < 1 ? hipErrorInvalidDevice : hipSuccess;
+}
+
+// Microseconds that a slice and the change of tiles take, with all compute units at it
+constexpr double kSliceUs = 1.3, kTileUs = 8.0;
+static double tile_us(const AlignedItem& a) { return kSliceUs * (double)((a.K + BK - 1) / BK + (a.Xext ? a.ext_ld / BK : 0)) + kTileUs; }
+
+// Deals the tiles of an XCD's runs to its workgroups; the deepest problems come first, and what is left behind the rounds goes
+// tile by tile to the workgroup that is done first.  Returns when the last is done, in microseconds
+static double deal_tiles(const AlignedItem* const* a, int n, int slots, TileLists& tb) {
+    double busy[kListSlots] = {};
+    int long_at = 0;
+    tb.n = n;
+    tb.slots = slots;
+    for (int q = 0; q < n; ++q) {
+        const int64_t tiles = (int64_t)a[q]->tiles_m * a[q]->tiles_n;
+        const double cost = tile_us(*a[q]);
+        tb.full[q] = (int)(tiles / 8 / slots);
+        for (int s = 0; s < slots; ++s) busy[s] += (double)tb.full[q] * cost;
+        tb.long_at[q] = (uint8_t)long_at;
+        long_at = (int)((long_at + tiles % 8) % 8);
+    }
+    for (int q = 0; q < n; ++q) {
+        const int64_t tiles = (int64_t)a[q]->tiles_m * a[q]->tiles_n;
+        for (int w = 0; w < kListSlots / 4; ++w) tb.take[q][w] = 0;
+        for (int64_t left = (tiles + 7) / 8 - (int64_t)tb.full[q] * slots; left > 0; --left) {      // (at most one a slot, or one more)
+            int at = 0;
+            for (int s = 1; s < slots; ++s) at = busy[s] < busy[at] ? s : at;
+            tb.take[q][at / 4] += 1u << (8 * (at % 4));
+            busy[at] += tile_us(*a[q]);
+        }
+    }
+    double end = 0.0;
+    for (int s = 0; s < slots; ++s) end = busy[s] > end ? busy[s] : end;
+    return end;
+}
+
+// Forwards beside work on another stream, a chain of launches that is bound by its latencies and by the compute units it has: a
+// workgroup of the lists holds its compute unit to the end, so a launch on all of them keeps the chain waiting, and one on too few
+// outlasts it.  The number of workgroups per XCD for which both should be done first: the chain takes its latencies and its sweeps on
+// the compute units left (29 GB/s each, of the 22 that each has of the rate of all together), and goes on with all of them behind the
+// forwards.  Base forwards and extraction, us, in launches of their
+// own (start) and in lists on 256, 224, 192 and 160 compute units: 4B-sized layers on 3001 tokens 824, 801, 760, 734 and 686, on 4096 924,
+// 974, 933, 904 and 821 (but 68 more behind it), on 1500 556, 507, 472, 463 and 450, 8B-sized on 15028, r = 1, 5371, 5525, 5341 and
+// 4879 (but 850 more behind it)
+static int slots_beside(const GemmBeside& b, double total, double deepest, int slots) {
+    int best = slots;
+    double best_us = -1.0;
+    for (int s = slots; s >= 1; s = s > 4 ? (s - 1) / 4 * 4 : s - 1) {      // (in fours: rounds of 25 share operand slices less well than of 24)
+        const double forwards = total / (8.0 * s) > deepest ? total / (8.0 * s) : deepest;
+        const double left = s < slots ? 22.0 / 29.0 * slots / (slots - s) : -1.0;
+        const double all = b.latency_us + b.sweep_us, slow = left < 0.0 ? left : b.latency_us + b.sweep_us * (left > 1.0 ? left : 1.0);
+        const double done = slow < 0.0 ? 0.0 : forwards / slow;
+        const double us = done >= 1.0 ? forwards : forwards + (1.0 - done) * all;
+        if (best_us < 0.0 || us < best_us) { best_us = us; best = s; }
+    }
+    return best;
+}
+
+static bool aligned_fits(const GemmParams& p) { return p.M >= BT && p.N >= BT && p.K >= 2 * BK && (p.P == nullptr || p.Xext != nullptr); }
+static bool aligned_ragged(const GemmParams& p) { return !(p.vec_ok && p.M % BT == 0 && p.N % BT == 0 && p.K % BK == 0); }
+
+bool gemm_bf16_aligned_listed(const GemmParams& p) {
+    return aligned_fits(p) && !p.shared && !p.Y && p.loss_kind == AGZO_LOSS_MSE && p.target_dtype == AGZO_BF16;
+}
+
+// Several layers' squared errors.  Layers of few tiles leave compute units idle in the last round of a launch of their own, most of all
+// with few tokens; lists that go through the tiles of all of them do so once.  Where the rounds are full anyway (the 8B-sized layers on
+// 16384 tokens) launches of their own are as fast, so the lists have to be ahead by 3 % in what the tiles should take.  Both signs of
+// the seven 4B-sized layers, us, launches of their own and lists: on 3001 tokens 1055 (with those that 128 x 128 tiles took) and 868, on
+// 4096 1423 and 1137, on 14080 4537 and 3960, 8B-sized on 15028 8226 and 7944
+hipError_t launch_gemm_bf16_aligned_lists(const GemmParams* const* a, const bool* sub, int n, const GemmBeside* beside, double* us, hipStream_t st) {
+    if (n < 0 || n > kBatchMax) return hipErrorInvalidValue;
+    int slots = 0;
+    hipError_t e = list_slots(&slots);
+    if (e != hipSuccess) return e;
+    if (us) *us = 0.0;
+    AlignedItem items[kBatchMax];
+    double total = 0.0, deepest = 0.0;
+    for (int i = 0; i < n; ++i) {
+        if (!gemm_bf16_aligned_listed(*a[i])) return hipErrorInvalidValue;
+        items[i] = aligned_item(*a[i]);
+        items[i].sub = sub[i] ? 1 : 0;
+        total += (double)items[i].tiles_m * items[i].tiles_n * tile_us(items[i]);
+        deepest = tile_us(items[i]) > deepest ? tile_us(items[i]) : deepest;
+    }
+    if (beside && slots > 0) slots = slots_beside(*beside, total, deepest, slots);
+    for (int ragged = 0; ragged < 2; ++ragged) {
+        const AlignedItem* order[kBatchMax];
+        const GemmParams* own[kBatchMax];
+        int m = 0;
+        bool joined = beside != nullptr;
+        double alone = 0.0;
+        for (int i = 0; i < n; ++i) {
+            if ((sub[i] || aligned_ragged(*a[i])) != (ragged != 0)) continue;
+            joined = joined || sub[i];
+            if (slots > 0) alone += (double)(((int64_t)items[i].tiles_m * items[i].tiles_n + 8 * slots - 1) / (8 * slots)) * tile_us(items[i]);
+            own[m] = a[i];
+            int at = m++;
+            for (; at > 0 && order[at - 1]->K < items[i].K; --at) order[at] = order[at - 1];
+            order[at] = &items[i];
+        }
+        if (m == 0) continue;
+        TileLists tb;
+        const double span = slots > 0 ? deal_tiles(order, m, slots, tb) : -1.0;
+        const bool lists = span >= 0.0 && (joined || span < 0.97 * alone);
+        if (us) *us = *us < 0.0 || (joined && !lists) ? -1.0 : *us + (lists ? span : alone);
+        if (us) continue;
+        if (!lists) {
+            if (joined) return hipErrorInvalidValue;
+            for (int q = 0; q < m; ++q) {
+                e = launch_gemm_bf16_aligned(*own[q], st);
+                if (e != hipSuccess) return e;
+            }
+            continue;
+        }
+        for (int q = 0; q < m; ++q) tb.a[q] = *order[q];
+        e = ragged ? launch_aligned_grid<0, false, 1, true, kBatchMax>(tb, 8u * slots, st) : launch_aligned_grid<0, false, 1, false, kBatchMax>(tb, 8u * slots, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 template <bool RAGGED>
@@ -783,9 +1061,6 @@ static hipError_t launch_aligned(const GemmParams& p, hipStream_t st) {
     return p.target_dtype != AGZO_BF16 ? launch_aligned_lists<0, true, RAGGED>(p, st) : launch_aligned_lists<0, false, RAGGED>(p, st);
 }
 
-static bool aligned_fits(const GemmParams& p) { return p.M >= BT && p.N >= BT && p.K >= 2 * BK && (p.P == nullptr || p.Xext != nullptr); }
-static bool aligned_ragged(const GemmParams& p) { return !(p.vec_ok && p.M % BT == 0 && p.N % BT == 0 && p.K % BK == 0); }
-
 hipError_t launch_gemm_bf16_aligned(const GemmParams& p, hipStream_t st) {
     if (!aligned_fits(p) || p.shared) return hipErrorInvalidValue;
     return aligned_ragged(p) ? launch_aligned<true>(p, st) : launch_aligned<false>(p, st);
@@ -793,8 +1068,8 @@ hipError_t launch_gemm_bf16_aligned(const GemmParams& p, hipStream_t st) {
 
 template <bool T_F32, bool RAGGED>
 static hipError_t launch_shared(const KBatch<AlignedItem>& tb, unsigned blocks, hipStream_t st) {
-    if (tb.n == 1) return launch_aligned_grid<0, T_F32, 3, RAGGED>(kbatch_one(tb), blocks, st);
-    return launch_aligned_grid<0, T_F32, 3, RAGGED>(tb, blocks, st);
+    if (tb.n == 1) return launch_aligned_grid<0, T_F32, 3, RAGGED, 1>(kbatch_one(tb), blocks, st);
+    return launch_aligned_grid<0, T_F32, 3, RAGGED, kBatchMax>(tb, blocks, st);
 }
 
 hipError_t launch_gemm_bf16_aligned_shared(const GemmParams* const* a, int n, hipStream_t st) {

@@ -93,6 +93,12 @@ hipError_t launch_gemm_bf16_mid(const GemmItem* a, int n, int out, bool target_f
 // persistent kernel in 256 x 256 tiles (gemm_bf16_aligned.hip): M, N >= 256, d_in >= 128, the rank-r term as prepared operands;
 // either the squared-error loss without a stored Y, the cross-entropy statistics without a stored Y, or a bf16 Y without a loss
 hipError_t launch_gemm_bf16_aligned(const GemmParams& p, hipStream_t st);
+// squared errors of several layers (gemm_bf16_aligned_listed()) over tile lists that go through all of them.  sub[i]: the loss
+// partials of gemm_bf16_mid.hip, bit for bit (a layer that takes its 128 x 128 tiles when alone).  beside != NULL: in lists in any case, on
+// as many compute units as the work beside them leaves.  us != NULL: nothing is launched, *us is about what it would take, below 0
+// where the lists do not take the layers
+bool gemm_bf16_aligned_listed(const GemmParams& p);
+hipError_t launch_gemm_bf16_aligned_lists(const GemmParams* const* a, const bool* sub, int n, const GemmBeside* beside, double* us, hipStream_t st);
 // squared error with p.shared (f0, f+, f- in one pass, needs Wext2, partials [3][tiles]): up to kBatchMax layers together
 hipError_t launch_gemm_bf16_aligned_shared(const GemmParams* const* a, int n, hipStream_t st);
 
