@@ -910,25 +910,25 @@ int agzo_perturbed_forward(agzo_ctx* ctx, const agzo_layer* L, const void* W, co
         HIPCHK(launch_xq_f32_many(&a, 1, ctx->stream));
         return op_forward(ctx, *L, p, W, X, P, eps_signed, seed, Y, loss, loss_dev);
     }
-    const bool narrow = !reads_planes(*L);
+    const bool narrow = !reads_planes(*L), direct = !narrow && xq_ext_ok(L->d_in, L->r);
     XqArgs q{static_cast<const bf16_t*>(X), L->ldx, L->n_tokens, L->d_in, wsh(ctx, p.off_pack), L->r, p.rp, P, nullptr, p.m_pad, wsf(ctx, p.off_xqpart), nullptr, B};
     if (timed(ctx, AGZO_PROF_GEMM)) {      // the operands are prepared inside the forward's time
-        if (!narrow) HIPCHK(launch_pack_planes(B, L->d_in, L->r, p.rp, wsh(ctx, p.off_pack), ctx->stream));
+        if (!narrow && !direct) HIPCHK(launch_pack_planes(B, L->d_in, L->r, p.rp, wsh(ctx, p.off_pack), ctx->stream));
         {
             ProfScope ps(ctx, AGZO_PROF_XQ);
-            HIPCHK(launch_xq_bf16_many(&q, 1, false, ctx->stream));
+            HIPCHK(direct ? launch_xq_ext(q, nullptr, ctx->stream) : launch_xq_bf16_many(&q, 1, false, ctx->stream));
         }
         return op_forward(ctx, *L, p, W, X, P, eps_signed, seed, Y, loss, loss_dev);
     }
-    // the W side of the extension operands and the planes of B in one launch, then the projection writes the X side: a model's
-    // step makes this chain once per linear layer and sign.  A narrow projection needs no planes and shares a launch with the W side
+    // the projection writes the X side of the extension operands; up to 16 columns need no planes of B and share a launch with the W
+    // side, for more the planes and the W side are a launch ahead
     q.T = nullptr;
     q.Xext = wsh(ctx, p.off_ext);
     GemmExtArgs ext{ctx->ws + p.off_ext, L->n_tokens, L->d_out, nullptr, L->r, eps_signed, 0.f, false, seed, B, wsh(ctx, p.off_pack), L->d_in};
-    if (narrow) {
+    if (narrow || direct) {
         ext.planes = nullptr;
         ProfScope ps(ctx, AGZO_PROF_XQ);
-        HIPCHK(launch_xq_narrow_ext(q, ext, ctx->stream));
+        HIPCHK(narrow ? launch_xq_narrow_ext(q, ext, ctx->stream) : launch_xq_ext(q, &ext, ctx->stream));
     } else {
         HIPCHK(launch_gemm_ext_prep_many(&ext, 1, ctx->stream));
         ProfScope ps(ctx, AGZO_PROF_XQ);

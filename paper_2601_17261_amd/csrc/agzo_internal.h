@@ -243,6 +243,10 @@ hipError_t launch_xq_bf16_many(const XqArgs* a, int n, bool half_cu, hipStream_t
 // one narrow product and, in the same launch, the W side of a forward's extension operands
 struct GemmExtArgs;
 hipError_t launch_xq_narrow_ext(const XqArgs& a, const GemmExtArgs& ext, hipStream_t st);
+// a product of up to 16 columns from the fp32 factor (T, Xext) and, in the same launch, the W side of a forward's extension operands
+// (ext = NULL: without it)
+bool xq_ext_ok(int64_t K, int r);
+hipError_t launch_xq_ext(const XqArgs& a, const GemmExtArgs* ext, hipStream_t st);
 int xtt_num_splits(int64_t M, int64_t K);
 // partial[s][d][rp] = sum over token range s of X[t][d] * T[t][k]
 hipError_t launch_xtt_bf16(const bf16_t* X, int64_t ldx, int64_t M, int64_t K, const bf16_t* TpackT, int64_t m_pad,

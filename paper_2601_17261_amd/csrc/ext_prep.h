@@ -19,12 +19,11 @@ struct ExtDev {
     uint32_t s_lo, s_hi;
     const float* B; bf16_t* planes; int64_t d;
 };
-// workgroup bx of 256 threads
-__device__ __forceinline__ void ext_prep_body(const ExtDev& a, uint32_t bx) {
+// thread idx
+__device__ __forceinline__ void ext_prep_body(const ExtDev& a, int64_t idx) {
     const int ext_ld = a.ext_ld, r = a.r, rp = a.rp;
     const int64_t M = a.M, N = a.N;
     const int chunks = ext_ld / 8;
-    const int64_t idx = (int64_t)bx * 256 + threadIdx.x;
     if (idx >= (M + a.n_w * N) * chunks) {
         // eight rows of one column of B
         const int64_t e = idx - (M + a.n_w * N) * chunks;
@@ -84,8 +83,8 @@ __device__ __forceinline__ void ext_prep_body(const ExtDev& a, uint32_t bx) {
     *reinterpret_cast<uint4*>(dst) = out;
 }
 
-// the W side of args (and the X side, from P, unless that is NULL) as the kernels take it, and the workgroups for it
-inline ExtDev ext_dev(const GemmExtArgs& a, uint64_t& workgroups) {
+// the W side of args (and the X side, from P, unless that is NULL) as the kernels take it, and the workgroups of `threads` for it
+inline ExtDev ext_dev(const GemmExtArgs& a, uint64_t& workgroups, int threads = 256) {
     ExtDev d;
     d.M = a.M; d.N = a.N; d.ext_ld = gemm_bf16_ext_width(a.r);
     d.Xext = static_cast<bf16_t*>(a.ext_ws); d.Wext = d.Xext + d.M * d.ext_ld;
@@ -95,7 +94,7 @@ inline ExtDev ext_dev(const GemmExtArgs& a, uint64_t& workgroups) {
     d.coef = a.coef; d.coef2 = a.coef2; d.n_w = a.two ? 2 : 1;
     d.s_lo = (uint32_t)a.seed; d.s_hi = (uint32_t)(a.seed >> 32);
     const int64_t items = (d.M + d.n_w * d.N) * (d.ext_ld / 8) + (d.planes ? d.d / 8 * d.rp : 0);
-    workgroups = (uint64_t)((items + 255) / 256);
+    workgroups = (uint64_t)((items + threads - 1) / threads);
     return d;
 }
 

@@ -567,7 +567,7 @@ template <int CAP>
 __global__ __launch_bounds__(256) void gemm_ext_prep_kernel(const KBatch<ExtDev, CAP> tb) {
     uint32_t bx, by;
     const ExtDev& a = tb.a[kbatch_find(tb, bx, by)];
-    ext_prep_body(a, bx);
+    ext_prep_body(a, (int64_t)bx * 256 + threadIdx.x);
 }
 
 static_assert(BK == 64, "the extension operands' width");

@@ -597,7 +597,7 @@ __global__ __launch_bounds__(256) void xq_narrow_many_kernel(const KBatch<XqNarr
 }
 __global__ __launch_bounds__(256) void xq_narrow_ext_kernel(const XqNarrowDev a, uint32_t blocks, const ExtDev ext) {
     if (blockIdx.x < blocks) xq_narrow_body(a, blockIdx.x);
-    else ext_prep_body(ext, blockIdx.x - blocks);
+    else ext_prep_body(ext, (int64_t)(blockIdx.x - blocks) * 256 + threadIdx.x);
 }
 
 static XqNarrowDev xqn_dev(const XqArgs& a, uint64_t& workgroups) {
@@ -631,6 +631,118 @@ hipError_t launch_xq_narrow_ext(const XqArgs& a, const GemmExtArgs& ext, hipStre
     const ExtDev e = ext_dev(ext, ext_wgs);
     if (wgs + ext_wgs > 0x7FFFFFFFull) return hipErrorInvalidValue;
     hipLaunchKernelGGL(xq_narrow_ext_kernel, dim3((unsigned)(wgs + ext_wgs)), dim3(256), 0, st, d, (uint32_t)wgs, e);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// The projection P = X B of a perturbed forward (up to 16 columns) and the W side of its extension operands in one launch, from B as it
+// is: a model's program makes this chain once per linear layer and sign.  A workgroup has 32 tokens, its eight waves share d_in in
+// 64-wide slices, and nothing goes through LDS but the eight sums: a lane asks for its 16-byte chunks of X (two tokens, a line each)
+// and for sixteen values of its column of B, splits these into the planes and multiplies; two slices in flight.  Products and sums are
+// those of xq_bf16_many_kernel, the sums over d_in in eight parts that are added in order.
+// Bound by what a compute unit takes in, some 60 GB/s: a workgroup's rows of X and as many bytes of B.  (Three and four slices in flight, B in
+// 16-byte pieces through LDS, sixteen waves, another order of the chunks: the same time or 5 to 30 % more.)  With the planes of B and the
+// W side in a launch ahead, which is bound by its latency, and the projection in workgroups of 64 tokens it took, r = 16, us: 4.8 + 10.5
+// at 8192 x 2048 -> 2048 and 10.0 so; 4.8 + 44 at 8192 x 6144 and 33; 4.8 + 5 + 4.5 (shares of d_in, added by a third launch) at 385 x 2048
+// and 8.5.  A decoder on 8192 tokens 15268 a step and 14943, on 385 1929 and 1859
+// ---------------------------------------------------------------------------
+constexpr int XQE_TOK = 32, XQE_WAVES = 8;
+struct XqExtDev {
+    const bf16_t* X; const float* B; int64_t ldx, M, K; int r;
+    float* T; bf16_t* Xext;
+};
+__device__ __forceinline__ void xq_ext_body(const XqExtDev& a, uint32_t bx) {
+    __shared__ float part[XQE_WAVES][XQE_TOK][17];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lm = lane & 15, lg = lane >> 4, r = a.r;
+    const int64_t K = a.K, t0 = (int64_t)bx * XQE_TOK;
+    const bf16_t* xr[2];
+#pragma unroll
+    for (int m = 0; m < 2; ++m) xr[m] = a.X + min(t0 + m * 16 + lm, a.M - 1) * a.ldx;
+    const float* bc = a.B + min(lm, r - 1);
+    const bool col = lm < r;
+    struct Slice { uint4 x[2][2]; float b[2][8]; };
+    // lane (lm, lg): 16-byte chunks 2 lg and 2 lg + 1 of a row's slice, and column lm of the rows of B that belong to them.  (Never
+    // conditional on the lane: what lies past the end, in whole eights, is read from the last place and left out)
+    auto load = [&](Slice& s, int64_t slice) __attribute__((always_inline)) {
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub) {
+            const int64_t k = min(slice * XQ_BK + lg * 16 + sub * 8, K - 8);
+#pragma unroll
+            for (int m = 0; m < 2; ++m) s.x[m][sub] = *reinterpret_cast<const uint4*>(xr[m] + k);
+            const float* src = bc + k * r;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) s.b[sub][j] = src[j * r];
+        }
+    };
+    floatx4 acc[2] = {};
+    auto multiply = [&](const Slice& s, int64_t slice) __attribute__((always_inline)) {
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub) {
+            const bool in = slice * XQ_BK + lg * 16 + sub * 8 < K;
+            Frag x[2], q[3];
+#pragma unroll
+            for (int m = 0; m < 2; ++m) x[m].u = in ? s.x[m][sub] : make_uint4(0, 0, 0, 0);
+            uint32_t w[3][4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                float v0 = in && col ? s.b[sub][2 * j] : 0.f, v1 = in && col ? s.b[sub][2 * j + 1] : 0.f;
+#pragma unroll
+                for (int pl = 0; pl < 3; ++pl) {
+                    w[pl][j] = pack_bf16x2(v0, v1);
+                    v0 -= __uint_as_float(w[pl][j] << 16);
+                    v1 -= __uint_as_float(w[pl][j] & 0xFFFF0000u);
+                }
+            }
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) q[pl].u = make_uint4(w[pl][0], w[pl][1], w[pl][2], w[pl][3]);
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl)
+#pragma unroll
+                for (int m = 0; m < 2; ++m) acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[m].v, q[pl].v, acc[m], 0, 0, 0);
+        }
+    };
+    const int64_t slices = (K + XQ_BK - 1) / XQ_BK;
+    Slice s0, s1;
+    load(s0, wave);
+    for (int64_t sl = wave; sl < slices; sl += 2 * XQE_WAVES) {
+        load(s1, sl + XQE_WAVES);
+        multiply(s0, sl);
+        load(s0, sl + 2 * XQE_WAVES);
+        multiply(s1, sl + XQE_WAVES);          // (behind the last slice: nothing that counts)
+    }
+    // D layout: row (token) = 4 lg + e, column lm
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) part[wave][m * 16 + lg * 4 + e][lm] = acc[m][e];
+    __syncthreads();
+    const int k = tid & 15, tok = tid >> 4;
+    float v = part[0][tok][k];
+#pragma unroll
+    for (int w = 1; w < XQE_WAVES; ++w) v += part[w][tok][k];
+    const int64_t t = t0 + tok;
+    if (t >= a.M) return;
+    if (k >= r) v = 0.f;
+    if (a.T != nullptr && k < r) a.T[t * r + k] = v;
+    if (a.Xext != nullptr) store_ext(a.Xext, t, k, 16, v);
+}
+static_assert(XQE_TOK * 16 == XQE_WAVES * 64, "a thread a value");
+__global__ __launch_bounds__(64 * XQE_WAVES) void xq_ext_kernel(const XqExtDev a, uint32_t blocks, const ExtDev ext) {
+    if (blockIdx.x < blocks) xq_ext_body(a, blockIdx.x);
+    else ext_prep_body(ext, (int64_t)(blockIdx.x - blocks) * (64 * XQE_WAVES) + threadIdx.x);
+}
+bool xq_ext_ok(int64_t K, int r) { return r <= 16 && K >= 8; }
+hipError_t launch_xq_ext(const XqArgs& a, const GemmExtArgs* ext, hipStream_t st) {
+    if (!xq_ext_ok(a.K, a.r) || !a.Q || a.TpackT || (ext && (ext->planes || ext->P))) return hipErrorInvalidValue;
+    const uint64_t wgs = (uint64_t)((a.M + XQE_TOK - 1) / XQE_TOK);
+    uint64_t ext_wgs = 0;
+    ExtDev e{};
+    if (ext) e = ext_dev(*ext, ext_wgs, 64 * XQE_WAVES);
+    if (wgs + ext_wgs > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    if (wgs + ext_wgs == 0) return hipSuccess;
+    const XqExtDev d{a.X, a.Q, a.ldx, a.M, a.K, a.r, a.T, a.Xext};
+    hipLaunchKernelGGL(xq_ext_kernel, dim3((unsigned)(wgs + ext_wgs)), dim3(64 * XQE_WAVES), 0, st, d, (uint32_t)wgs, e);
     return hipGetLastError();
 }
 
