@@ -3,7 +3,8 @@
 // diagonal, which is the unique thin-QR factorisation of a full-rank Y.  A non-positive pivot
 // (rank-deficient sketch) raises a device flag instead of producing NaNs.
 //
-// Three launches per QR, coherence between them by kernel boundaries only (no device-scope fences):
+// Three launches per QR (and one ahead of the second and third that sums many partials), coherence between them by kernel boundaries
+// only (no device-scope fences):
 //   1. gram        : Gram partials of Y per 128-row block (v_mfma_f64_16x16x4_f64)
 //   2. apply_gram  : every block sums the partials in block order and factors the r x r matrix in LDS -> R1^-1;
 //                    Q1 = Y R1^-1 (fp64, stored), then the Gram partials of Q1
@@ -241,6 +242,8 @@ __device__ void gram_partial(const T* Ys, int rows_pad, double* partial, uint32_
     }
 }
 
+struct QrSumDev { double* partial; int nblk; };
+
 // Every block: sum over blocks of partial (block order, up to 32 loads of a thread in flight), then the workgroup factors
 // it -> R^-1.  Block 0 reports a bad pivot.  smem: FACTOR_SMEM bytes; returns R^-1's blocks in it
 template <int RP>
@@ -269,6 +272,25 @@ __device__ const double* reduce_and_factor(const double* partial, int nblk, doub
     if (bad && tid == 0 && bx == 0) *flag = 1;
     if (Q::NB == 1) __syncthreads();
     return Rinv;
+}
+
+// The sum of reduce_and_factor() ahead of it, into the first block's partial: every block of the launches that follow reads all partials,
+// and a compute unit takes in some 60 GB/s, so that 76 of 20 KB (r = 64, 9728 rows) are most of their time
+template <int RP, int CAP>
+__global__ __launch_bounds__(256) void qr_sum_kernel(const KBatch<QrSumDev, CAP> tb) {
+    typedef QrShape<RP> Q;
+    uint32_t bx, by;
+    const QrSumDev& a = tb.a[kbatch_find(tb, bx, by)];
+    double* at = a.partial + (int64_t)bx * 256 + threadIdx.x;
+    double sum = 0.0;
+    for (int b0 = 0; b0 < a.nblk; b0 += 32) {
+        double v[32];
+#pragma unroll
+        for (int u = 0; u < 32; ++u) v[u] = b0 + u < a.nblk ? at[(int64_t)(b0 + u) * (Q::PAIRS * 256)] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 32; ++u) sum += v[u];
+    }
+    *at = sum;
 }
 
 // the wave's rows of Y as operands (row l mod 16 of a 16-row block, columns l / 16 + 4 s of a column block), requested before
@@ -566,6 +588,10 @@ static hipError_t launch_qr1(const KBatch<QrDev, CAP>& tb, unsigned blocks, cons
     return hipGetLastError();
 }
 
+// Bytes of Gram partials from which on they are summed ahead.  agzo_qr, us, summed by every block and ahead: r = 64, 2048 rows (320 KB) 64.5
+// and 65.6, 2560 (400 KB) 66.1 and 65.9, 4096 (640 KB) 71 and 67, 9728 (1.5 MB) 90 and 72; r = 32, 9728 (456 KB) 37.8 and 37.2; r = 16, 40000
+// (626 KB) 58 and 50.  The single pass of seven 4B-sized layers, r = 64: 41 and 30 + 5.7
+constexpr int64_t kSumAhead = 448 * 1024;
 template <int RP, int CAP>
 static hipError_t launch_qr_rp(const KBatch<QrDev, CAP>& tb, unsigned blocks, int* flag, bool refine, hipStream_t st) {
     typedef QrShape<RP> Q;
@@ -580,17 +606,37 @@ static hipError_t launch_qr_rp(const KBatch<QrDev, CAP>& tb, unsigned blocks, in
         attr_set = true;
     }
     const dim3 grid(blocks), block(Q::THREADS);
+    // the partials summed ahead where a block would read many bytes of them
+    int64_t most = 0;
+    for (int m = 0; m < tb.n; ++m) most = tb.a[m].nblk > most ? tb.a[m].nblk : most;
+    const bool ahead = most * Q::PAIRS * 2048 > kSumAhead;
+    KBatch<QrDev, CAP> one = tb;                  // what the launches behind the sums take
+    for (int m = 0; ahead && m < one.n; ++m) one.a[m].nblk = 1;
+    auto sums = [&](bool second) -> hipError_t {
+        if (!ahead) return hipSuccess;
+        KBatch<QrSumDev, CAP> su;
+        su.n = tb.n;
+        for (int m = 0; m < tb.n; ++m) {
+            su.first[m] = (uint32_t)(m * Q::PAIRS);
+            su.gx[m] = Q::PAIRS;
+            su.a[m] = QrSumDev{second ? tb.a[m].partial2 : tb.a[m].partial1, tb.a[m].nblk};
+        }
+        hipLaunchKernelGGL((qr_sum_kernel<RP, CAP>), dim3((unsigned)(tb.n * Q::PAIRS)), dim3(256), 0, st, su);
+        return hipGetLastError();
+    };
     hipLaunchKernelGGL((qr_gram_kernel<RP, CAP>), grid, block, Q::GRAM_SMEM, st, tb);
     hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = sums(false);
     if (e != hipSuccess) return e;
     if (!refine) {
-        hipLaunchKernelGGL((qr_apply_final_kernel<RP, false, CAP>), grid, block, Q::APPLY_FINAL_SMEM, st, tb, flag);
+        hipLaunchKernelGGL((qr_apply_final_kernel<RP, false, CAP>), grid, block, Q::APPLY_FINAL_SMEM, st, one, flag);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL((qr_apply_gram_kernel<RP, CAP>), grid, block, Q::APPLY_GRAM_SMEM, st, tb, flag);
+    hipLaunchKernelGGL((qr_apply_gram_kernel<RP, CAP>), grid, block, Q::APPLY_GRAM_SMEM, st, one, flag);
     e = hipGetLastError();
+    if (e == hipSuccess) e = sums(true);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((qr_apply_final_kernel<RP, true, CAP>), grid, block, Q::APPLY_FINAL_SMEM, st, tb, flag);
+    hipLaunchKernelGGL((qr_apply_final_kernel<RP, true, CAP>), grid, block, Q::APPLY_FINAL_SMEM, st, one, flag);
     return hipGetLastError();
 }
 
