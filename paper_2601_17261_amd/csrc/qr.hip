@@ -445,6 +445,22 @@ __global__ __launch_bounds__(QrShape<RP>::THREADS) void qr_apply_gram_kernel(con
     gram_partial<RP>(Ys, (rows + 3) & ~3, a.partial2, bx);
 }
 
+// eight values of column c, rows i .. i + 7, as the planes [3][rp][d]
+__device__ __forceinline__ void store_planes(const float* src, bf16_t* planes, int rp, int c, int64_t d, int64_t i) {
+    uint32_t w[3][4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        bf16_t h[2], m[2], l[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) split3_bf16(src[2 * u + k], h[k], m[k], l[k]);
+        w[0][u] = (uint32_t)h[0] | ((uint32_t)h[1] << 16);
+        w[1][u] = (uint32_t)m[0] | ((uint32_t)m[1] << 16);
+        w[2][u] = (uint32_t)l[0] | ((uint32_t)l[1] << 16);
+    }
+#pragma unroll
+    for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<uint4*>(planes + ((int64_t)pl * rp + c) * d + i) = make_uint4(w[pl][0], w[pl][1], w[pl][2], w[pl][3]);
+}
+
 // launch 3: Q = Q1 R2^-1, rounded to fp32; planes (nullable, d % 8 == 0) receive the hi/mid/lo bf16 parts [3][rp][d].
 // DOUBLE_IN: second pass of CholeskyQR2 (input Q1, partials of Q1); otherwise the single-pass form, Q = Y R1^-1 straight from
 // launch 1's partials
@@ -482,20 +498,155 @@ __global__ __launch_bounds__(QrShape<RP>::THREADS) void qr_apply_final_kernel(co
     // eight rows of one column and plane per thread and pass: 16-byte stores
     for (int e = tid; e < RP * (QR_ROWS / 8); e += Q::THREADS) {
         const int i = (e % (QR_ROWS / 8)) * 8, c = e / (QR_ROWS / 8);
-        if (i >= rows) continue;
-        uint32_t w[3][4];
+        if (i < rows) store_planes(Qt + c * Q::PLANE_LD + i, a.planes, RP, c, d, i0 + i);
+    }
+}
+
+// ---- up to 512 rows and 16 columns: the launches above as one workgroup.  Bound by the latency of a launch each, they took 4.6 + 6.3 us
+// (single pass of 256 rows) and 4.6 + 7.5 + 6.2; this takes some 7.5 and 11, 2 of it for a factorisation.  Everything is added in the order of those launches, so the results are the same bits and a
+// call may take either way.  (A wave has 64 rows, two quarters of a Gram partial there: with all four in a row the matrix instructions took
+// a third of the time, and more rows than these take longer than the launches.)
+constexpr int QRS_BLOCKS = 4, QRS_WAVES = 2 * QRS_BLOCKS, QRS_ROWS = QRS_BLOCKS * QR_ROWS, QRS_LD = 17;
+constexpr size_t qrs_smem(int blocks) { return (size_t)blocks * QR_ROWS * QRS_LD * sizeof(double) + (4 * QRS_BLOCKS * 256 + 2 * QR_BLK) * sizeof(double); }
+template <int CAP>
+__global__ __launch_bounds__(64 * QRS_WAVES) void qr_small_kernel(const KBatch<QrDev, CAP> tb, int refine, int* flag) {
+    extern __shared__ __align__(16) char qr_smem[];
+    const QrDev& a = tb.a[CAP == 1 ? 0 : blockIdx.x];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lc = lane & 15, lg = lane >> 4;
+    const int r = a.r, d = (int)a.d, nblk = a.nblk, nsplit = a.nsplit;
+    double* parts = reinterpret_cast<double*>(qr_smem);                   // [blocks][4][256]
+    double *G = parts + 4 * QRS_BLOCKS * 256, *Rinv = G + QR_BLK;
+    char* rows_at = reinterpret_cast<char*>(Rinv + QR_BLK);               // rows in fp32, then in fp64, then Q transposed
+    float* Ys = reinterpret_cast<float*>(rows_at);
+    // (loads are never conditional on the lane: around a condition the compiler waits for each before the next)
+    if (a.splits != nullptr) {
+        const int nvec = d * 4, total = nblk * QR_ROWS * 4;
+        for (int v0 = tid; v0 < total; v0 += 2 * 64 * QRS_WAVES) {
+            double acc[2][4] = {};
+            for (int sp0 = 0; sp0 < nsplit; sp0 += 8) {
+                float4 x[2][8];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            bf16_t h[2], m[2], l[2];
+                for (int u = 0; u < 8; ++u)
 #pragma unroll
-            for (int k = 0; k < 2; ++k) split3_bf16(Qt[c * Q::PLANE_LD + i + 2 * u + k], h[k], m[k], l[k]);
-            w[0][u] = (uint32_t)h[0] | ((uint32_t)h[1] << 16);
-            w[1][u] = (uint32_t)m[0] | ((uint32_t)m[1] << 16);
-            w[2][u] = (uint32_t)l[0] | ((uint32_t)l[1] << 16);
+                    for (int k = 0; k < 2; ++k)
+                        x[k][u] = reinterpret_cast<const float4*>(a.splits + (int64_t)min(sp0 + u, nsplit - 1) * d * 16)[min(v0 + k * 64 * QRS_WAVES, nvec - 1)];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const bool in = sp0 + u < nsplit;
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        acc[k][0] += in ? (double)x[k][u].x : 0.0; acc[k][1] += in ? (double)x[k][u].y : 0.0;
+                        acc[k][2] += in ? (double)x[k][u].z : 0.0; acc[k][3] += in ? (double)x[k][u].w : 0.0;
+                    }
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int v = v0 + k * 64 * QRS_WAVES, i = v >> 2, k0 = (v & 3) * 4;
+                if (v >= total) continue;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const bool in = v < nvec && k0 + c < r;
+                    const float f = in ? (float)acc[k][c] : 0.f;
+                    if (in) a.S_out[(int64_t)i * r + k0 + c] = f;
+                    Ys[i * QRS_LD + k0 + c] = f;
+                }
+            }
         }
+    } else {
+        const int total = nblk * QR_ROWS * 16;                            // (four to a thread at least)
+        for (int e0 = tid; e0 < total; e0 += 4 * 64 * QRS_WAVES) {
+            float x[4];
 #pragma unroll
-        for (int pl = 0; pl < 3; ++pl)
-            *reinterpret_cast<uint4*>(a.planes + ((int64_t)pl * RP + c) * d + i0 + i) = make_uint4(w[pl][0], w[pl][1], w[pl][2], w[pl][3]);
+            for (int u = 0; u < 4; ++u) {
+                const int e = e0 + u * 64 * QRS_WAVES;
+                x[u] = a.S[(int64_t)min(e >> 4, d - 1) * r + min(e & 15, r - 1)];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int e = e0 + u * 64 * QRS_WAVES;
+                if (e < total) Ys[(e >> 4) * QRS_LD + (e & 15)] = ((e >> 4) < d && (e & 15) < r) ? x[u] : 0.f;
+            }
+        }
+    }
+    __syncthreads();
+    const int block = wave >> 1, half = wave & 1, row0 = block * QR_ROWS;
+    // the Gram matrix of the rows and R^-1: a wave's four quarters side by side, then the waves' sums
+    auto gram_factor = [&](const auto* Y) __attribute__((always_inline)) {
+        if (block < nblk) {
+            const int rows_pad = (min(QR_ROWS, d - row0) + 3) & ~3, chunk = ((rows_pad / 4 + 3) / 4) * 4;
+            doublex4 acc[2] = {};
+            for (int t = 0; t < chunk; t += 4)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const int at = (2 * half + q) * chunk + t;
+                    if (at < rows_pad) {
+                        const double y = (double)Y[(row0 + at + lg) * QRS_LD + lc];
+                        acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(y, y, acc[q], 0, 0, 0);
+                    }
+                }
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) parts[(block * 4 + 2 * half + q) * 256 + (4 * i + lg) * 16 + lc] = acc[q][i];
+        }
+        __syncthreads();
+        if (tid < 256) {
+            double sum = 0.0;
+            for (int b = 0; b < nblk; ++b) {
+                const double* p = parts + b * 4 * 256 + tid;
+                sum += (p[0] + p[256]) + (p[512] + p[768]);
+            }
+            G[(tid >> 4) * QR_LD + (tid & 15)] = sum;
+        }
+        if (factor_inverse<16>(G, Rinv, r) && tid == 0) *flag = 1;
+        __syncthreads();
+    };
+    constexpr int RB = QR_ROWS / 32;                                      // 16-row blocks of a wave
+    const int rw = row0 + half * (QR_ROWS / 2);
+    doublex4 v[RB];
+    auto apply = [&](const auto* Y) __attribute__((always_inline)) {
+        if (block < nblk) {
+#pragma unroll
+            for (int b = 0; b < RB; ++b) {
+                typename std::remove_const<typename std::remove_reference<decltype(*Y)>::type>::type y[4];
+#pragma unroll
+                for (int s = 0; s < 4; ++s) y[s] = Y[(rw + b * 16 + lc) * QRS_LD + 4 * s + lg];
+                v[b] = apply_rinv<16>(y, Rinv, 0);
+            }
+        }
+        __syncthreads();                                                  // what follows goes where the rows are
+    };
+    gram_factor(Ys);
+    apply(Ys);
+    if (refine) {
+        double* Y1 = reinterpret_cast<double*>(rows_at);
+        if (block < nblk)
+#pragma unroll
+            for (int b = 0; b < RB; ++b)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) Y1[(rw + b * 16 + 4 * i + lg) * QRS_LD + lc] = v[b][i];
+        __syncthreads();
+        gram_factor(Y1);
+        apply(Y1);
+    }
+    const int ld = nblk * QR_ROWS + 4;
+    float* Qt = reinterpret_cast<float*>(rows_at);                        // [16][ld]
+    if (block < nblk)
+#pragma unroll
+        for (int b = 0; b < RB; ++b)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int row = rw + b * 16 + 4 * i + lg;
+                const float f = lc < r ? (float)v[b][i] : 0.f;
+                Qt[lc * ld + row] = f;
+                if (row < d && lc < r) a.Q[(int64_t)row * r + lc] = f;
+            }
+    if (a.planes == nullptr) return;
+    __syncthreads();
+    for (int e = tid; e < 16 * nblk * (QR_ROWS / 8); e += 64 * QRS_WAVES) {
+        const int i = (e % (nblk * (QR_ROWS / 8))) * 8, c = e / (nblk * (QR_ROWS / 8));
+        if (i < d) store_planes(Qt + c * ld + i, a.planes, 16, c, a.d, i);
     }
 }
 
@@ -640,8 +791,33 @@ static hipError_t launch_qr_rp(const KBatch<QrDev, CAP>& tb, unsigned blocks, in
     return hipGetLastError();
 }
 
+// Whether one workgroup a problem does it: few rows, fewer where partial sketches are to be summed.  agzo_qr, us, three launches and one: 100
+// rows 15.4 and 10.6, 256 16.9 and 11.7, 384 17.1 and 13.8, 512 17.2 and 14.7, 1024 17.8 and 21.  A step of one layer: fp32, 256 wide on
+// 512 tokens 117 and 106, 512 on 300 142 and 137; bf16, 256 wide on 300 tokens 118 and 108, on 8000 (16 partial sketches) 216 and 207, but
+// 504 on 512 (4) 135 and 141
+template <int CAP>
+static bool qr_small(const KBatch<QrDev, CAP>& tb) {
+    for (int m = 0; m < tb.n; ++m)
+        if (tb.a[m].d > (tb.a[m].splits ? QRS_ROWS / 2 : QRS_ROWS)) return false;
+    return true;
+}
+template <int CAP>
+static hipError_t launch_qr_small(const KBatch<QrDev, CAP>& tb, int* flag, bool refine, hipStream_t st) {
+    static bool attr_set = false;
+    if (!attr_set) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(qr_small_kernel<CAP>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)qrs_smem(QRS_BLOCKS));
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    int most = 0;
+    for (int m = 0; m < tb.n; ++m) most = tb.a[m].nblk > most ? tb.a[m].nblk : most;
+    hipLaunchKernelGGL(qr_small_kernel<CAP>, dim3((unsigned)tb.n), dim3(64 * QRS_WAVES), qrs_smem(most), st, tb, refine ? 1 : 0, flag);
+    return hipGetLastError();
+}
+
 template <int CAP>
 static hipError_t launch_qr_cap(const KBatch<QrDev, CAP>& tb, unsigned blocks, int rp, int* flag, bool refine, hipStream_t st) {
+    if (rp == 16 && qr_small(tb)) return launch_qr_small(tb, flag, refine, st);
     switch (rp) {
         case 16: return launch_qr_rp<16>(tb, blocks, flag, refine, st);
         case 32: return launch_qr_rp<32>(tb, blocks, flag, refine, st);
