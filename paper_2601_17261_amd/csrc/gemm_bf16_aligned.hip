@@ -142,8 +142,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
     static_assert(OUT == 0 || (PHASES == 1 && !T_F32), "the kernels without a squared-error target have one evaluation");
     constexpr bool LISTS = PHASES == 1 && CAP > 1;
     constexpr bool LATE_T = RAGGED && OUT == 0;    // the target is subtracted after the last slice
-    // ... and the two 128-row halves of a tile end at the last row by themselves, as the tiles of gemm_bf16_mid.hip do
-    constexpr bool HALVES = RAGGED && OUT == 0;
+    // ... and the two 128-row halves of a tile end at the last row by themselves, as the tiles of gemm_bf16_mid.hip do.  (Not in the
+    // shared schedule, which no other kernel's layers join: its registers spill anyway, and halves took it 9 % longer)
+    constexpr bool HALVES = LATE_T && PHASES == 1;
     constexpr int NT = 256, BA = 4, BB = 4;
     constexpr int W_BASE = 0, X_BASE = 3 * TILE_BYTES;       // LDS: three W stages, then two X stages (all 160 KiB)
     extern __shared__ __align__(16) char smem[];
@@ -538,11 +539,13 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
     // a layer whose target rows do not start on 16 bytes, are squared in fp64 as well: what gemm_bf16.hip squares so keeps its
     // precision here.  (Otherwise a lane's 16 columns of a group count or do not count together; the wide form takes some 2 us more
     // a tile)
-    // The sums of the wave's four 64 x 64 blocks: outputs, tokens
+    // HALVES: the sums of the wave's four 64 x 64 blocks (outputs, tokens) by themselves
     auto eval_sum = [&](double (&part)[2][2]) __attribute__((always_inline)) {
-        part[0][0] = part[0][1] = part[1][0] = part[1][1] = 0.0;
+        part[0][0] = 0.0;
+        if (HALVES) part[0][1] = part[1][0] = part[1][1] = 0.0;
         if constexpr (PHASES == 1) settle();
-        const int rs = HALVES ? (int)(tm * BT - m0) - wb * hm : 0, cs0 = HALVES ? (int)(tn * BT - n0) : 0, cs = cs0 - wa * hn;
+        const int rs = RAGGED ? (int)(tm * BT - m0) - wb * (HALVES ? hm : BT / 2) : 0;
+        const int cs0 = RAGGED ? (int)(tn * BT - n0) : 0, cs = cs0 - wa * (HALVES ? hn : BT / 2);
         auto sum = [&](auto WIDE) __attribute__((always_inline)) {
             constexpr bool wide = decltype(WIDE)::value != 0;
 #pragma clang loop unroll(full)
@@ -550,7 +553,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
                 if (LATE_T && PHASES == 1 && T_F32 && J == 4) { tload(IC<4>{}); tload(IC<5>{}); tload(IC<6>{}); tload(IC<7>{}); }
                 // the first of the lane's 16 columns per group that counts
                 int from[2] = {0, 0};
-                if (HALVES) {
+                if (RAGGED) {
                     const bool in = J * 16 + lc >= rs;
                     from[0] = in ? cs - lg * 16 : 16;
                     from[1] = in ? cs - (64 + lg * 16) : 16;
@@ -574,16 +577,16 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
                             s4 = fmaf(x, x, s4);
                         }
                     }
-                    if (!wide) sum64 += (double)(!HALVES || from[I >> 2] <= 0 ? s4 : 0.f);
+                    if (!wide) sum64 += (double)(!RAGGED || from[I >> 2] <= 0 ? s4 : 0.f);
                 }
             }
         };
-        if (HALVES && (((LISTS && tb.a[cq].sub ? cs : cs0 | (cs0 - hn)) & 15) != 0 || !tb.a[cq].vec_ok)) sum(IC<1>{});
+        if (RAGGED && (((LISTS && tb.a[cq].sub ? cs : cs0 | (HALVES ? cs0 - hn : 0)) & 15) != 0 || !tb.a[cq].vec_ok)) sum(IC<1>{});
         else sum(IC<0>{});
     };
     // of one problem's tile
     auto eval_finish = [&](const double (&part4)[2][2], const AlignedItem& a, int phase, int64_t tm_, int64_t tn_, double* red) __attribute__((always_inline)) {
-        if (LISTS && HALVES && a.sub) {
+        if (HALVES && a.sub) {
             // the wave's half of the tile is a tile of gemm_bf16_mid.hip: its lanes, then its four blocks, in the order of that kernel's
             // lanes and waves.  Each step of the sum over the lanes halves the blocks that a lane sums
             const bool out1 = (lane & 32) != 0, tok1 = (lane & 16) != 0;
