@@ -363,7 +363,7 @@ F32FwdArgs forward_f32_args(const agzo_layer& L, const void* W, const void* X, c
 // shared = true: one pass over X and W evaluates the loss at W, W + eps Z, W - eps Z -> loss_dev[0..2]
 int op_forward(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* W, const void* X, const float* P,
                float eps_signed, uint64_t seed, void* Y, const agzo_loss_spec* loss, double* loss_dev,
-               bool shared = false, int part_slot = 0, bool defer_finish = false, bool fused_sketch = false, bool ext_ready = false) {
+               bool shared = false, int part_slot = 0, bool defer_finish = false, bool fused_sketch = false, bool ext_ready = false, int ext_side = 0) {
     hipStream_t st = ctx->stream;
     GemmLossArgs la;
     const bool has_loss = loss && loss->kind != AGZO_LOSS_NONE;
@@ -393,6 +393,7 @@ int op_forward(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* W,
     if (L.dtype == AGZO_BF16) {
         GemmBf16Args a = forward_bf16_args(ctx, L, p, W, X, P, eps_signed, seed, Y, la, shared);
         a.ext_ready = ext_ready;
+        a.ext_side = ext_side;
         if (fused_sketch) { a.sk_T = wsh(ctx, p.off_TpackT); a.sk_mpad = p.m_pad; a.sk_partial = wsf(ctx, p.off_xtt); }
         {
             ProfScope ps(ctx, AGZO_PROF_GEMM);
@@ -580,8 +581,11 @@ int op_basis(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* X, i
     }
 }
 
-// P = X B for every job (one launch per kBatchMax jobs of a dtype and padded rank), behind basis_many_impl
-int project_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, bool half_cu) {
+// whether the launches that project a job's activations write its extension operands too (timed: they are part of each forward's time)
+bool projects_ext(agzo_ctx* ctx, const agzo_layer& L) { return L.dtype == AGZO_BF16 && !timed(ctx, AGZO_PROF_GEMM); }
+// P = X B for every job (one launch per kBatchMax jobs of a dtype and padded rank, and one behind it), behind basis_many_impl.  ext: the
+// jobs' W sides (read where projects_ext())
+int project_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, const std::vector<GemmExtArgs>& ext, bool half_cu) {
     std::vector<char> done(jobs.size(), 0);
     for (size_t a = 0; a < jobs.size(); ++a) {
         if (done[a]) continue;
@@ -605,6 +609,10 @@ int project_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, bool half_cu)
             if (done[b] || j.L.dtype != AGZO_BF16 || j.p.rp != ja.p.rp) continue;
             q[n++] = XqArgs{static_cast<const bf16_t*>(j.X), j.L.ldx, j.L.n_tokens, j.L.d_in, wsh(ctx, j.p.off_pack), j.L.r, j.p.rp,
                             wsf(ctx, j.p.off_T), nullptr, j.p.m_pad, wsf(ctx, j.p.off_xqpart), nullptr, j.B};
+            if (projects_ext(ctx, j.L)) {
+                q[n - 1].Xext = wsh(ctx, j.p.off_ext);
+                q[n - 1].ext = &ext[b];
+            }
             done[b] = 1;
         }
         ProfScope ps(ctx, AGZO_PROF_XQ);
@@ -910,7 +918,7 @@ int agzo_perturbed_forward(agzo_ctx* ctx, const agzo_layer* L, const void* W, co
         HIPCHK(launch_xq_f32_many(&a, 1, ctx->stream));
         return op_forward(ctx, *L, p, W, X, P, eps_signed, seed, Y, loss, loss_dev);
     }
-    const bool narrow = !reads_planes(*L), direct = !narrow && xq_ext_ok(L->d_in, L->r);
+    const bool narrow = !reads_planes(*L), direct = !narrow && xq_ext_ok(L->n_tokens, L->d_in, L->r);
     XqArgs q{static_cast<const bf16_t*>(X), L->ldx, L->n_tokens, L->d_in, wsh(ctx, p.off_pack), L->r, p.rp, P, nullptr, p.m_pad, wsf(ctx, p.off_xqpart), nullptr, B};
     if (timed(ctx, AGZO_PROF_GEMM)) {      // the operands are prepared inside the forward's time
         if (!narrow && !direct) HIPCHK(launch_pack_planes(B, L->d_in, L->r, p.rp, wsh(ctx, p.off_pack), ctx->stream));
@@ -927,8 +935,9 @@ int agzo_perturbed_forward(agzo_ctx* ctx, const agzo_layer* L, const void* W, co
     GemmExtArgs ext{ctx->ws + p.off_ext, L->n_tokens, L->d_out, nullptr, L->r, eps_signed, 0.f, false, seed, B, wsh(ctx, p.off_pack), L->d_in};
     if (narrow || direct) {
         ext.planes = nullptr;
+        if (narrow) q.ext = &ext;
         ProfScope ps(ctx, AGZO_PROF_XQ);
-        HIPCHK(narrow ? launch_xq_narrow_ext(q, ext, ctx->stream) : launch_xq_ext(q, &ext, ctx->stream));
+        HIPCHK(narrow ? launch_xq_bf16_many(&q, 1, false, ctx->stream) : launch_xq_ext(q, &ext, ctx->stream));
     } else {
         HIPCHK(launch_gemm_ext_prep_many(&ext, 1, ctx->stream));
         ProfScope ps(ctx, AGZO_PROF_XQ);
@@ -1101,7 +1110,6 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
     auto forward_mse = [&](int ph0, int ph1) -> int {
         std::vector<GemmBf16Args> bf;
         std::vector<F32FwdArgs> f32;
-        std::vector<GemmExtArgs> ext;
         const bool perturbed = shared || ph0 > 0;
         for (int m = 0; m < n; ++m) {
             const agzo_step_item& it = items[m];
@@ -1111,9 +1119,8 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
             GemmLossArgs la;
             la.kind = AGZO_LOSS_MSE; la.target_dtype = it.loss.target_dtype; la.target = it.loss.target; la.ldt = it.loss.ldt;
             const float* P = perturbed ? wsf(ctx, j.p.off_T) : nullptr;
-            // both signs' operands in one preparation (timed: each forward's own, inside its time)
-            const bool pair = perturbed && !shared && j.L.dtype == AGZO_BF16 && !timed(ctx, AGZO_PROF_GEMM);
-            if (pair) ext.push_back(GemmExtArgs{ctx->ws + j.p.off_ext, j.L.n_tokens, j.L.d_out, P, j.L.r, eps, -eps, ph1 > 2, it.seed});
+            // the projection has written all operands (timed: each forward its own, inside its time)
+            const bool ready = perturbed && projects_ext(ctx, j.L);
             for (int ph = ph0; ph < ph1; ++ph) {
                 la.partials = reinterpret_cast<double*>(ctx->ws + j.p.off_part) + (size_t)ph * j.p.n_part;
                 const float e = ph == 2 ? -eps : eps;
@@ -1121,7 +1128,7 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
                     f32.push_back(forward_f32_args(j.L, it.W, it.X, P, e, it.seed, la, shared));
                 } else {
                     bf.push_back(forward_bf16_args(ctx, j.L, j.p, it.W, it.X, P, e, it.seed, nullptr, la, shared));
-                    bf.back().ext_ready = pair;
+                    bf.back().ext_ready = ready;
                     bf.back().ext_side = ph == 2 ? 1 : 0;
                 }
             }
@@ -1137,8 +1144,6 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
             }));
             return 0;
         }
-        for (size_t b = 0; b < ext.size(); b += kBatchMax)
-            HIPCHK(launch_gemm_ext_prep_many(ext.data() + b, (int)std::min(ext.size() - b, (size_t)kBatchMax), st));
         if (!timed(ctx, AGZO_PROF_GEMM)) {
             HIPCHK(launch_gemm_bf16_many(bf.data(), (int)bf.size(), false, st));
             return 0;
@@ -1153,7 +1158,7 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
         const agzo_step_item& it = items[m];
         if (it.loss.kind != AGZO_LOSS_CE) return 0;
         const LayerJob& j = jobs[(size_t)m];
-        return op_forward(ctx, j.L, j.p, it.W, it.X, P, e, it.seed, nullptr, &it.loss, dst, sh, slot, false);
+        return op_forward(ctx, j.L, j.p, it.W, it.X, P, e, it.seed, nullptr, &it.loss, dst, sh, slot, false, false, P && projects_ext(ctx, j.L), slot == 2 ? 1 : 0);
     };
     // Alg. 2, part 1: the base forward of every layer, and every layer's basis from the same activations
     if (!shared) {
@@ -1162,7 +1167,13 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
     }
     TRY(basis_many_impl(ctx, jobs, K, flags & AGZO_INIT_FEATURE, half_cu));
     // parts 2-3: the perturbed evaluations
-    TRY(project_many(ctx, jobs, half_cu));
+    // the Gaussian factors with the coefficients of both perturbed evaluations (shared: what each of them adds)
+    std::vector<GemmExtArgs> sides((size_t)n);
+    for (int m = 0; m < n; ++m) {
+        const LayerJob& j = jobs[(size_t)m];
+        sides[(size_t)m] = GemmExtArgs{ctx->ws + j.p.off_ext, j.L.n_tokens, j.L.d_out, nullptr, j.L.r, eps, shared ? -2.f * eps : -eps, shared || !one_sided, items[m].seed};
+    }
+    TRY(project_many(ctx, jobs, sides, half_cu));
     if (shared) TRY(forward_mse(0, 1));
     else TRY(forward_mse(1, one_sided ? 2 : 3));
     for (int m = 0; m < n; ++m) {

@@ -234,18 +234,17 @@ struct XqArgs {
     const float* Q = nullptr;      // the fp32 [K][r] of which Qpack are the planes: what xq_narrow() products read instead
     // xq_narrow() products: Q is still to be normalised, by the root of the sum of norm_blocks values; *flag = 1 if that is not positive
     const double* norm2 = nullptr; int norm_blocks = 0; int* flag = nullptr;
+    // the W side of a forward's extension operands, written by the product's last launch or one behind it (NULL: not)
+    const struct GemmExtArgs* ext = nullptr;
 };
 // true: a product that multiplies the fp32 factor itself (one column, few tokens); Qpack may then be NULL
 bool xq_narrow(int64_t M, int64_t K, int r);
 // up to kBatchMax products with the same rp in one launch (plus one finishing launch if any of them splits d_in); m_pad is a multiple of 4
 // half_cu: forwards on another stream hold half of every compute unit
 hipError_t launch_xq_bf16_many(const XqArgs* a, int n, bool half_cu, hipStream_t st);
-// one narrow product and, in the same launch, the W side of a forward's extension operands
-struct GemmExtArgs;
-hipError_t launch_xq_narrow_ext(const XqArgs& a, const GemmExtArgs& ext, hipStream_t st);
 // a product of up to 16 columns from the fp32 factor (T, Xext) and, in the same launch, the W side of a forward's extension operands
 // (ext = NULL: without it)
-bool xq_ext_ok(int64_t K, int r);
+bool xq_ext_ok(int64_t M, int64_t K, int r);
 hipError_t launch_xq_ext(const XqArgs& a, const GemmExtArgs* ext, hipStream_t st);
 int xtt_num_splits(int64_t M, int64_t K);
 // partial[s][d][rp] = sum over token range s of X[t][d] * T[t][k]

@@ -438,10 +438,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void x
 // columns side by side, every plane was written in 2-byte pieces: 28 us for 4096 tokens of seven layers at r = 64, 9 so).  T and the
 // extension operands are token by token, as their partial sums are: 16 tokens of 16 columns, a thread a value
 constexpr int XQF_TOK = 64, XQF_TOK_ROWS = 16;
-template <int CAP>
-__global__ __launch_bounds__(256) void xq_finish_many_kernel(const KBatch<XqDev, CAP> tb, int rp) {
-    uint32_t bx, by;
-    const XqDev& a = tb.a[kbatch_find(tb, bx, by)];
+__device__ __forceinline__ void xq_finish_body(const XqDev& a, int rp, uint32_t bx, uint32_t by) {
     const int tid = threadIdx.x, nsplit = a.ns, r = a.r;
     const int64_t m_pad = a.m_pad, M = a.M;
     // (eight splits' loads in flight; conditional on uniform values only - around a lane's condition the compiler waits for each
@@ -476,6 +473,23 @@ __global__ __launch_bounds__(256) void xq_finish_many_kernel(const KBatch<XqDev,
     if (k >= r) v = 0.f;
     if (t < M && k < r && a.T != nullptr) a.T[t * r + k] = v;
     if (t < M && a.Xext != nullptr) store_ext(a.Xext, t, k, rp, v);
+}
+template <int CAP>
+__global__ __launch_bounds__(256) void xq_finish_many_kernel(const KBatch<XqDev, CAP> tb, int rp) {
+    uint32_t bx, by;
+    const XqDev& a = tb.a[kbatch_find(tb, bx, by)];
+    xq_finish_body(a, rp, bx, by);
+}
+// with the W sides of forwards' extension operands: behind a projection both are bound by a launch's latency (4.7 + 5.6 us for 3001 tokens of
+// one 2048-wide layer, 11 + 26 for 4096 of the seven 4B-sized at r = 64)
+struct XqFinishExtDev { XqDev q; uint32_t fx, blocks; ExtDev ext; };
+static_assert(sizeof(KBatch<XqFinishExtDev>) <= 4096, "kernel arguments");
+template <int CAP>
+__global__ __launch_bounds__(256) void xq_finish_ext_kernel(const KBatch<XqFinishExtDev, CAP> tb, int rp) {
+    uint32_t bx, by;
+    const XqFinishExtDev& a = tb.a[kbatch_find(tb, bx, by)];
+    if (bx < a.blocks) xq_finish_body(a.q, rp, bx % a.fx, bx / a.fx);
+    else ext_prep_body(a.ext, (int64_t)(bx - a.blocks) * 256 + threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -595,9 +609,15 @@ __global__ __launch_bounds__(256) void xq_narrow_many_kernel(const KBatch<XqNarr
     const XqNarrowDev& a = tb.a[kbatch_find(tb, bx, by)];
     xq_narrow_body(a, bx);
 }
-__global__ __launch_bounds__(256) void xq_narrow_ext_kernel(const XqNarrowDev a, uint32_t blocks, const ExtDev ext) {
-    if (blockIdx.x < blocks) xq_narrow_body(a, blockIdx.x);
-    else ext_prep_body(ext, (int64_t)(blockIdx.x - blocks) * 256 + threadIdx.x);
+// with the W sides of forwards' extension operands
+struct XqNarrowExtDev { XqNarrowDev q; uint32_t blocks; ExtDev ext; };
+static_assert(sizeof(KBatch<XqNarrowExtDev>) <= 4096, "kernel arguments");
+template <int CAP>
+__global__ __launch_bounds__(256) void xq_narrow_ext_kernel(const KBatch<XqNarrowExtDev, CAP> tb) {
+    uint32_t bx, by;
+    const XqNarrowExtDev& a = tb.a[kbatch_find(tb, bx, by)];
+    if (bx < a.blocks) xq_narrow_body(a.q, bx);
+    else ext_prep_body(a.ext, (int64_t)(bx - a.blocks) * 256 + threadIdx.x);
 }
 
 static XqNarrowDev xqn_dev(const XqArgs& a, uint64_t& workgroups) {
@@ -609,28 +629,32 @@ static XqNarrowDev xqn_dev(const XqArgs& a, uint64_t& workgroups) {
 }
 static hipError_t launch_xq_narrow(const XqArgs* const* a, int n, hipStream_t st) {
     KBatch<XqNarrowDev> tb;
-    tb.n = n;
-    uint64_t blocks = 0;
+    KBatch<XqNarrowExtDev> eb;
+    tb.n = eb.n = 0;
+    uint64_t blocks = 0, eblocks = 0;
     for (int i = 0; i < n; ++i) {
-        uint64_t wgs;
-        tb.a[i] = xqn_dev(*a[i], wgs);
-        tb.first[i] = (uint32_t)blocks;
-        tb.gx[i] = (uint32_t)wgs;
-        blocks += wgs;
+        uint64_t wgs, ext_wgs = 0;
+        const XqNarrowDev d = xqn_dev(*a[i], wgs);
+        if (!a[i]->ext) {
+            tb.first[tb.n] = (uint32_t)blocks;
+            tb.gx[tb.n] = (uint32_t)wgs;
+            tb.a[tb.n++] = d;
+            blocks += wgs;
+        } else {
+            const ExtDev e = ext_dev(*a[i]->ext, ext_wgs);
+            eb.first[eb.n] = (uint32_t)eblocks;
+            eb.gx[eb.n] = (uint32_t)(wgs + ext_wgs);
+            eb.a[eb.n++] = XqNarrowExtDev{d, (uint32_t)wgs, e};
+            eblocks += wgs + ext_wgs;
+        }
+        if (blocks > 0x7FFFFFFFull || eblocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
     }
-    if (n == 0) return hipSuccess;
-    if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    if (n == 1) hipLaunchKernelGGL(xq_narrow_many_kernel<1>, dim3((unsigned)blocks), dim3(256), 0, st, kbatch_one(tb));
-    else hipLaunchKernelGGL(xq_narrow_many_kernel<kBatchMax>, dim3((unsigned)blocks), dim3(256), 0, st, tb);
-    return hipGetLastError();
-}
-hipError_t launch_xq_narrow_ext(const XqArgs& a, const GemmExtArgs& ext, hipStream_t st) {
-    if (!xq_narrow(a.M, a.K, a.r) || !a.Q || a.rp != 16 || a.m_pad % 4 || ext.planes) return hipErrorInvalidValue;
-    uint64_t wgs, ext_wgs;
-    const XqNarrowDev d = xqn_dev(a, wgs);
-    const ExtDev e = ext_dev(ext, ext_wgs);
-    if (wgs + ext_wgs > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(xq_narrow_ext_kernel, dim3((unsigned)(wgs + ext_wgs)), dim3(256), 0, st, d, (uint32_t)wgs, e);
+    if (tb.n == 1) hipLaunchKernelGGL(xq_narrow_many_kernel<1>, dim3((unsigned)blocks), dim3(256), 0, st, kbatch_one(tb));
+    else if (tb.n > 1) hipLaunchKernelGGL(xq_narrow_many_kernel<kBatchMax>, dim3((unsigned)blocks), dim3(256), 0, st, tb);
+    const hipError_t err = tb.n > 0 ? hipGetLastError() : hipSuccess;
+    if (err != hipSuccess || eb.n == 0) return err;
+    if (eb.n == 1) hipLaunchKernelGGL(xq_narrow_ext_kernel<1>, dim3((unsigned)eblocks), dim3(256), 0, st, kbatch_one(eb));
+    else hipLaunchKernelGGL(xq_narrow_ext_kernel<kBatchMax>, dim3((unsigned)eblocks), dim3(256), 0, st, eb);
     return hipGetLastError();
 }
 
@@ -732,9 +756,10 @@ __global__ __launch_bounds__(64 * XQE_WAVES) void xq_ext_kernel(const XqExtDev a
     if (blockIdx.x < blocks) xq_ext_body(a, blockIdx.x);
     else ext_prep_body(ext, (int64_t)(blockIdx.x - blocks) * (64 * XQE_WAVES) + threadIdx.x);
 }
-bool xq_ext_ok(int64_t K, int r) { return r <= 16 && K >= 8; }
+// (few tokens of a wide layer are a few workgroups that take in all of d_in each: 21 us for 300 x 8000 where the three launches take 17)
+bool xq_ext_ok(int64_t M, int64_t K, int r) { return r <= 16 && K >= 8 && (K <= 6144 || M >= 8192); }
 hipError_t launch_xq_ext(const XqArgs& a, const GemmExtArgs* ext, hipStream_t st) {
-    if (!xq_ext_ok(a.K, a.r) || !a.Q || a.TpackT || (ext && (ext->planes || ext->P))) return hipErrorInvalidValue;
+    if (!xq_ext_ok(a.M, a.K, a.r) || !a.Q || a.TpackT || (ext && (ext->planes || ext->P))) return hipErrorInvalidValue;
     const uint64_t wgs = (uint64_t)((a.M + XQE_TOK - 1) / XQE_TOK);
     uint64_t ext_wgs = 0;
     ExtDev e{};
@@ -819,7 +844,7 @@ hipError_t launch_xq_bf16_many(const XqArgs* a, int n, bool half_cu, hipStream_t
     for (int m = 0; m < n; ++m) {
         if (a[m].M == 0) continue;
         if (rp == 0) rp = a[m].rp;
-        if (a[m].rp != rp || a[m].m_pad % 4) return hipErrorInvalidValue;       // one padded rank per launch
+        if (a[m].rp != rp || a[m].m_pad % 4 || (a[m].ext && (a[m].ext->planes || a[m].ext->P))) return hipErrorInvalidValue;       // one padded rank per launch
         if (xq_narrow(a[m].M, a[m].K, a[m].r)) {
             if (!a[m].Q) return hipErrorInvalidValue;
             narrow[n_narrow++] = &a[m];
@@ -836,8 +861,9 @@ hipError_t launch_xq_bf16_many(const XqArgs* a, int n, bool half_cu, hipStream_t
     if (en != hipSuccess || count == 0) return en;
     const int mb = rp >= 48 && half >= 256 ? 2 : 1;      // (where that leaves no compute unit without a workgroup)
     KBatch<XqDev> tb, fin;
-    tb.n = fin.n = 0;
-    uint64_t blocks = 0, fin_blocks = 0;
+    KBatch<XqFinishExtDev> fext;
+    tb.n = fin.n = fext.n = 0;
+    uint64_t blocks = 0, fin_blocks = 0, fext_blocks = 0;
     for (int i = 0; i < count; ++i) {
         const int m = order[i];
         XqDev d;
@@ -850,15 +876,29 @@ hipError_t launch_xq_bf16_many(const XqArgs* a, int n, bool half_cu, hipStream_t
         const uint32_t gx = (uint32_t)((rows + mb * XQ_TOK - 1) / (mb * XQ_TOK));
         tb.first[tb.n] = (uint32_t)blocks; tb.gx[tb.n] = gx; tb.a[tb.n++] = d;
         blocks += (uint64_t)gx * (uint32_t)d.ns;
-        if (d.ns > 1) {
-            const int ftok = d.TpackT ? XQF_TOK : XQF_TOK_ROWS;
-            const uint32_t fx = (uint32_t)((rows + ftok - 1) / ftok);
+        const int ftok = d.TpackT ? XQF_TOK : XQF_TOK_ROWS;
+        const uint32_t fx = (uint32_t)((rows + ftok - 1) / ftok);
+        if (a[m].ext) {
+            uint64_t wgs;
+            XqFinishExtDev& x = fext.a[fext.n];
+            x.q = d; x.fx = fx; x.blocks = d.ns > 1 ? fx * (uint32_t)(rp / 16) : 0;
+            x.ext = ext_dev(*a[m].ext, wgs);
+            wgs += x.blocks;
+            if (wgs == 0) continue;
+            fext.first[fext.n] = (uint32_t)fext_blocks; fext.gx[fext.n++] = (uint32_t)wgs;
+            fext_blocks += wgs;
+        } else if (d.ns > 1) {
             fin.first[fin.n] = (uint32_t)fin_blocks; fin.gx[fin.n] = fx; fin.a[fin.n++] = d;
             fin_blocks += (uint64_t)fx * (uint32_t)(rp / 16);
         }
     }
-    if (blocks > 0x7FFFFFFFull || fin_blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    if (blocks > 0x7FFFFFFFull || fin_blocks > 0x7FFFFFFFull || fext_blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
     hipError_t e = tb.n == 1 ? launch_xq_cap(kbatch_one(tb), (unsigned)blocks, rp, mb, half_cu, st) : launch_xq_cap(tb, (unsigned)blocks, rp, mb, half_cu, st);
+    if (e == hipSuccess && fext.n > 0) {
+        if (fext.n == 1) hipLaunchKernelGGL(xq_finish_ext_kernel<1>, dim3((unsigned)fext_blocks), dim3(256), 0, st, kbatch_one(fext), rp);
+        else hipLaunchKernelGGL(xq_finish_ext_kernel<kBatchMax>, dim3((unsigned)fext_blocks), dim3(256), 0, st, fext, rp);
+        e = hipGetLastError();
+    }
     if (e != hipSuccess || fin.n == 0) return e;
     const dim3 fin_grid((unsigned)fin_blocks);
     if (fin.n == 1) hipLaunchKernelGGL(xq_finish_many_kernel<1>, fin_grid, dim3(256), 0, st, kbatch_one(fin), rp);
