@@ -747,16 +747,16 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
                 constexpr bool skip = decltype(SKIP)::value != 0;
                 const int64_t row = m0 + wb * 128 + J * 16 + lc;
                 const int tgt = tb.a[cq].ce_target[row];
+                // (the block's 32 values leave the accumulation registers once, for the maximum, the exponentials and the target)
+                float y[8][4];
                 float mx = -INFINITY;
 #pragma clang loop unroll(full)
-                for (int i4 = 0; i4 < 2; ++i4)
+                for (int I = 0; I < 8; ++I)
 #pragma clang loop unroll(full)
-                    for (int t = 0; t < 4; ++t)
-#pragma clang loop unroll(full)
-                        for (int e = 0; e < 4; ++e) {
-                            const float y = from_acc(acc[i4 * 4 + t][J][e]);
-                            if (!skip || 4 * t + e >= cskip[i4]) mx = fmaxf(mx, y);
-                        }
+                    for (int e = 0; e < 4; ++e) {
+                        y[I][e] = from_acc(acc[I][J][e]);
+                        if (!skip || 4 * (I & 3) + e >= cskip[I >> 2]) mx = fmaxf(mx, y[I][e]);
+                    }
                 mx = fmaxf(mx, __shfl_xor(mx, 16));
                 mx = fmaxf(mx, __shfl_xor(mx, 32));
                 // exp(y - mx) as 2^((y - mx) log2 e) on the hardware exponential: the difference is exact enough in fp32
@@ -766,7 +766,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
                 for (int I = 0; I < 8; ++I)
 #pragma clang loop unroll(full)
                     for (int e = 0; e < 4; ++e) {
-                        const float ex = __builtin_amdgcn_exp2f((from_acc(acc[I][J][e]) - mx) * 1.44269504088896341f);
+                        const float ex = __builtin_amdgcn_exp2f((y[I][e] - mx) * 1.44269504088896341f);
                         sm += (!skip || (I & 3) * 4 + e >= cskip[I >> 2]) ? ex : 0.f;
                     }
                 sm += __shfl_xor(sm, 16);
@@ -781,14 +781,10 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
                     float tl = 0.f;
                     const int at = (int)trel & 15, grp = (int)trel >> 6;
 #pragma clang loop unroll(full)
-                    for (int i4 = 0; i4 < 2; ++i4)
+                    for (int I = 0; I < 8; ++I)
 #pragma clang loop unroll(full)
-                        for (int t = 0; t < 4; ++t)
-#pragma clang loop unroll(full)
-                            for (int e = 0; e < 4; ++e) {
-                                const float y = from_acc(acc[i4 * 4 + t][J][e]);
-                                if (grp == i4 && at == 4 * t + e) tl = y;
-                            }
+                        for (int e = 0; e < 4; ++e)
+                            if (grp == (I >> 2) && at == 4 * (I & 3) + e) tl = y[I][e];
                     if (mine) tb.a[cq].ce_tl[row] = tl;
                 }
             };
