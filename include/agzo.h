@@ -207,8 +207,8 @@ int agzo_update_noalloc(agzo_ctx* ctx, const agzo_layer* L, void* W, const float
  * updates of a model arrive together).  items: host array, read during the call only; per item the arguments of
  * agzo_update: W device [d_out][ldw] of `dtype`, B device fp32 [d_in][r], g_dev device scalar or NULL (= 1), seed of
  * that layer's Gaussian factor, lr; reserved must be 0.  bf16 matrices whose ranks round up to the same multiple of 16
- * share one preparation launch and one sweep per 16 matrices (small matrices no longer pay two launches each); fp32
- * matrices are swept one by one.  Every matrix ends bit-identical to what agzo_update gives it.  The matrices must
+ * share one preparation launch and one sweep per 16 matrices (small matrices no longer pay two launches each); 16 fp32
+ * matrices share one launch.  Every matrix ends bit-identical to what agzo_update gives it.  The matrices must
  * not overlap.  n = 0 is a no-op.  Errors: AGZO_EINVAL for n < 0, NULL items, or an item agzo_update would reject
  * (nothing is enqueued then). */
 typedef struct {

@@ -317,6 +317,8 @@ struct UpdateDesc {
 int update_many_max();
 // bf16 matrices with r = 1 (at most kBatchMax): one launch, no scratch
 hipError_t launch_update_rank1_many(const UpdateDesc* d, int n, hipStream_t st);
+// fp32 matrices of any rank, n <= update_many_max(): one launch, no scratch
+hipError_t launch_update_f32_many(const UpdateDesc* d, int n, hipStream_t st, float shift = 0.f);
 hipError_t launch_update_many(const UpdateDesc* d, int n, int nk, void* workspace, hipStream_t st);
 
 // loss.hip

@@ -11,104 +11,144 @@
 
 namespace agzo {
 
-constexpr int UP_TI = 64;    // rows (d_out) per tile
+constexpr int UP_TI = 32;    // rows (d_out) per tile
 constexpr int UP_TJ = 256;   // cols (d_in) per tile
-constexpr int UP_TR = 8;     // rows per thread
+constexpr int UP_TR = 4;     // rows per thread
+constexpr int UP_BS = UP_TJ + 4;   // a row of the transposed B tile: 16 ranks of 4 columns in 64 banks
+constexpr int UPD_MAX = 16;  // matrices of one launch
 
-// KC = number of k handled per register chunk; nchunk chunks cover r (zero padded)
-template <int KC>
-__global__ __launch_bounds__(256) void update_kernel(float* __restrict__ Wf, int64_t ldw, int64_t d_out, int64_t d_in,
-                                                     const float* __restrict__ B, int r, int nchunk, uint32_t s_lo,
-                                                     uint32_t s_hi, float lr, float shift,
-                                                     const double* __restrict__ g_dev) {
+struct UpdF32Item {
+    float* W;
+    const float* B;
+    const double* g_dev;
+    int64_t ldw, d_out, d_in;
+    uint32_t blk0, njb;   // first workgroup of this matrix, its tiles across
+    uint32_t s_lo, s_hi;
+    float lr;
+    int r;
+};
+struct UpdF32Batch {
+    int n;
+    float shift;
+    UpdF32Item it[UPD_MAX];
+};
+
+// fp32 weights keep exact fp32 products on the vector units: a workgroup takes 32 x 256 elements, a lane two runs of four
+// columns in four rows.  HBM-bound, so the weights are requested before the generator and the products run (B's rows before
+// them: loads return in order).  B's tile is one run of floats, read as such and turned in LDS, a row padded by 4 so that 16
+// ranks of 4 columns fall on 64 banks; r is taken four at a time (the sum's order is k either way) and leaves the registers
+// for the weights.  The matrices of a model share one launch (workgroups find theirs from the running block counts).
+// The seven of a 1024-wide set, r = 16, 126 MB read and written, against 64 x 256 tiles that turned B through one bank, read W
+// last and took a launch each: 107 -> 24 us (5.2 TB/s); a 2560-wide set 299 -> 144 (5.6 TB/s); three matrices at r = 64
+// 101 -> 34 (generator and products); 1001 x 1003 and 777 x 2049, r = 7, 42 -> 13; 4096 x 12288, r = 1, 61 -> 59.  Tiles of
+// 64 rows (two waves a SIMD, not four): 29, 155, 43, 13, 60; of 16 rows: 25, 158, 45, 12, 59.
+template <bool VEC>   // rows of whole aligned runs of four
+__global__ __launch_bounds__(256) void update_f32_kernel(const UpdF32Batch tb) {
     extern __shared__ __align__(16) float up_smem[];
-    const int rp = KC * nchunk;
-    float* Gs = up_smem;                 // [UP_TI][rp]
-    float* Bt = up_smem + UP_TI * rp;    // [rp][UP_TJ]  (transposed: k-major)
+    int m = 0;
+    while (m + 1 < tb.n && blockIdx.x >= tb.it[m + 1].blk0) ++m;
+    const UpdF32Item& u = tb.it[m];
+    const int64_t ldw = u.ldw, d_out = u.d_out, d_in = u.d_in;
+    const int r = u.r, nquad = (r + 3) / 4;
+    const uint32_t local = blockIdx.x - u.blk0;
+    const int64_t i0 = (int64_t)(local / u.njb) * UP_TI, j0 = (int64_t)(local % u.njb) * UP_TJ;
+    float4* Gs = reinterpret_cast<float4*>(up_smem);        // [UP_TI][nquad]
+    float* Bt = up_smem + UP_TI * nquad * 4;                // [4 nquad][UP_BS]
     const int tid = threadIdx.x;
-    const int64_t i0 = (int64_t)blockIdx.y * UP_TI, j0 = (int64_t)blockIdx.x * UP_TJ;
+    const int tx = tid & 31;          // columns 4 tx + 128 h of the tile
+    const int ty = tid >> 5;          // rows ty + 8 s
+    const int64_t jc = j0 + tx * 4;
+    float* Wt = u.W + jc;
+    const int64_t jl = d_in - 1, jv = jl & ~(int64_t)3;   // the last column, the last whole run of four
+
+    // the tile's rows of B are one run of floats
+    const float* Bj = u.B + j0 * r;
+    const int n_b = (int)min((int64_t)UP_TJ, d_in - j0) * r;
+    const int step_j = 256 / r, step_k = 256 % r;
+    int bj = tid / r, bk = tid % r;
+#pragma unroll 4
+    for (int q = 0; q < r; ++q) {
+        Bt[bk * UP_BS + bj] = Bj[min(tid + q * 256, n_b - 1)];
+        bj += step_j;
+        bk += step_k;
+        if (bk >= r) { bk -= r; ++bj; }
+    }
+    for (int k = r; k < 4 * nquad; ++k) Bt[k * UP_BS + tid] = 0.f;
+    // rows and columns past the end read the last ones, which are not stored
+    float4 w[UP_TR][2];
+#pragma unroll
+    for (int s = 0; s < UP_TR; ++s) {
+        const float* p = u.W + min(i0 + ty + 8 * s, d_out - 1) * ldw;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int64_t j = jc + 128 * h;
+            if constexpr (VEC)
+                w[s][h] = *reinterpret_cast<const float4*>(p + min(j, jv));
+            else
+                w[s][h] = make_float4(p[min(j, jl)], p[min(j + 1, jl)], p[min(j + 2, jl)], p[min(j + 3, jl)]);
+        }
+    }
 
     // G tile from the seed: one Philox call = 4 columns of one row
-    const int nquad = (rp + 3) / 4;
     for (int e = tid; e < UP_TI * nquad; e += 256) {
         const int ii = e / nquad, q = e % nquad;
         float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (i0 + ii < d_out && q * 4 < r) z = philox_normal4(s_lo, s_hi, AGZO_TAG_G, (uint32_t)(i0 + ii), (uint32_t)q);
-        const float v[4] = {z.x, z.y, z.z, z.w};
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int k = q * 4 + c;
-            if (k < rp) Gs[ii * rp + k] = (k < r) ? v[c] : 0.f;
-        }
-    }
-    for (int e = tid; e < UP_TJ * rp; e += 256) {
-        const int jj = e / rp, k = e % rp;
-        Bt[k * UP_TJ + jj] = (j0 + jj < d_in && k < r) ? B[(j0 + jj) * r + k] : 0.f;
+        if (i0 + ii < d_out) z = philox_normal4(u.s_lo, u.s_hi, AGZO_TAG_G, (uint32_t)(i0 + ii), (uint32_t)q);
+        if (q * 4 + 1 >= r) z.y = 0.f;
+        if (q * 4 + 2 >= r) z.z = 0.f;
+        if (q * 4 + 3 >= r) z.w = 0.f;
+        Gs[e] = z;
     }
     __syncthreads();
 
-    const float coef = -fmaf(lr, g_dev ? (float)(*g_dev) : 1.0f, shift);
-    const int tx = tid & 31;          // 8 consecutive columns
-    const int ty = tid >> 5;          // rows ty + 8*s
-    const int64_t jc = j0 + tx * 8;
-
+    const float coef = -fmaf(u.lr, u.g_dev ? (float)(*u.g_dev) : 1.0f, tb.shift);
     float acc[UP_TR][8];
 #pragma unroll
     for (int s = 0; s < UP_TR; ++s)
 #pragma unroll
         for (int c = 0; c < 8; ++c) acc[s][c] = 0.f;
-
-    for (int ch = 0; ch < nchunk; ++ch) {
-        float b[KC][8];
+    for (int q = 0; q < nquad; ++q) {
+        float b[4][8];
 #pragma unroll
-        for (int k = 0; k < KC; ++k) {
-            const float4 lo = *reinterpret_cast<const float4*>(&Bt[(ch * KC + k) * UP_TJ + tx * 8]);
-            const float4 hi = *reinterpret_cast<const float4*>(&Bt[(ch * KC + k) * UP_TJ + tx * 8 + 4]);
-            b[k][0] = lo.x; b[k][1] = lo.y; b[k][2] = lo.z; b[k][3] = lo.w;
-            b[k][4] = hi.x; b[k][5] = hi.y; b[k][6] = hi.z; b[k][7] = hi.w;
-        }
+        for (int k = 0; k < 4; ++k)
 #pragma unroll
-        for (int s = 0; s < UP_TR; ++s) {
-            const float* g = &Gs[(ty + 8 * s) * rp + ch * KC];
-#pragma unroll
-            for (int k = 0; k < KC; ++k) {
-                const float gv = g[k];
-#pragma unroll
-                for (int c = 0; c < 8; ++c) acc[s][c] = fmaf(gv, b[k][c], acc[s][c]);
+            for (int h = 0; h < 2; ++h) {
+                const float4 v = *reinterpret_cast<const float4*>(&Bt[(q * 4 + k) * UP_BS + h * 128 + tx * 4]);
+                b[k][4 * h] = v.x; b[k][4 * h + 1] = v.y; b[k][4 * h + 2] = v.z; b[k][4 * h + 3] = v.w;
             }
+#pragma unroll
+        for (int s = 0; s < UP_TR; ++s) {
+            const float4 g4 = Gs[(ty + 8 * s) * nquad + q];
+            const float g[4] = {g4.x, g4.y, g4.z, g4.w};
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int c = 0; c < 8; ++c) acc[s][c] = fmaf(g[k], b[k][c], acc[s][c]);
         }
     }
 
-    if (jc >= d_in) return;
-    if (jc + 8 <= d_in && ldw % 4 == 0 && (reinterpret_cast<uintptr_t>(Wf + jc) & 15) == 0) {
-        // every row's values requested before the first is used; rows past the end repeat the last, unstored
-        float4 lo[UP_TR], hi[UP_TR];
-#pragma unroll
-        for (int s = 0; s < UP_TR; ++s) {
-            const float* w = Wf + min(i0 + ty + 8 * s, d_out - 1) * ldw + jc;
-            lo[s] = *reinterpret_cast<const float4*>(w);
-            hi[s] = *reinterpret_cast<const float4*>(w + 4);
-        }
-#pragma unroll
-        for (int s = 0; s < UP_TR; ++s) {
-            lo[s].x = fmaf(coef, acc[s][0], lo[s].x); lo[s].y = fmaf(coef, acc[s][1], lo[s].y);
-            lo[s].z = fmaf(coef, acc[s][2], lo[s].z); lo[s].w = fmaf(coef, acc[s][3], lo[s].w);
-            hi[s].x = fmaf(coef, acc[s][4], hi[s].x); hi[s].y = fmaf(coef, acc[s][5], hi[s].y);
-            hi[s].z = fmaf(coef, acc[s][6], hi[s].z); hi[s].w = fmaf(coef, acc[s][7], hi[s].w);
-            const int64_t i = i0 + ty + 8 * s;
-            if (i >= d_out) continue;
-            float* w = Wf + i * ldw + jc;
-            *reinterpret_cast<float4*>(w) = lo[s];
-            *reinterpret_cast<float4*>(w + 4) = hi[s];
-        }
-        return;
-    }
 #pragma unroll
     for (int s = 0; s < UP_TR; ++s) {
         const int64_t i = i0 + ty + 8 * s;
         if (i >= d_out) continue;
-        float* w = Wf + i * ldw + jc;
-        for (int c = 0; c < 8 && jc + c < d_in; ++c) w[c] = fmaf(coef, acc[s][c], w[c]);
+        float* p = Wt + i * ldw;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            float4 v = w[s][h];
+            v.x = fmaf(coef, acc[s][4 * h], v.x);
+            v.y = fmaf(coef, acc[s][4 * h + 1], v.y);
+            v.z = fmaf(coef, acc[s][4 * h + 2], v.z);
+            v.w = fmaf(coef, acc[s][4 * h + 3], v.w);
+            const int64_t left = d_in - jc - 128 * h;
+            if constexpr (VEC) {
+                if (left > 0) *reinterpret_cast<float4*>(p + 128 * h) = v;
+            } else {
+                if (left > 0) p[128 * h] = v.x;
+                if (left > 1) p[128 * h + 1] = v.y;
+                if (left > 2) p[128 * h + 2] = v.z;
+                if (left > 3) p[128 * h + 3] = v.w;
+            }
+        }
     }
 }
 
@@ -205,7 +245,6 @@ __global__ __launch_bounds__(256) void update_prep_kernel(uint4* __restrict__ Gf
 
 // Several matrices in one pair of launches (Alg. 2 updates every layer once the scalar g is known): the table is a
 // kernel argument, a workgroup finds its matrix from the running block counts (uniform, a handful of scalar compares).
-constexpr int UPD_MAX = 16;
 struct UpdItem {
     bf16_t* W;
     uint4 *Gf, *Bf;
@@ -406,23 +445,42 @@ static hipError_t launch_mfma(bf16_t* W, int64_t ldw, int64_t d_out, int64_t d_i
     return hipGetLastError();
 }
 
-template <int KC>
-static hipError_t launch_kc(float* W, int64_t ldw, int64_t d_out, int64_t d_in, const float* B, int r, int nchunk,
-                            uint64_t seed, float lr, float shift, const double* g_dev, hipStream_t st) {
-    dim3 grid((unsigned)((d_in + UP_TJ - 1) / UP_TJ), (unsigned)((d_out + UP_TI - 1) / UP_TI));
-    const int rp = KC * nchunk;
-    const size_t smem = (size_t)(UP_TI + UP_TJ) * rp * sizeof(float);
+template <bool VEC>
+static hipError_t launch_update_f32(const UpdateDesc* d, int n, hipStream_t st, float shift) {
+    UpdF32Batch tb;
+    tb.n = 0;
+    tb.shift = shift;
+    int64_t blocks = 0;
+    int rp = 0;
+    for (int m = 0; m < n; ++m) {
+        const bool whole = ((d[m].ldw | d[m].d_in) & 3) == 0 && (reinterpret_cast<uintptr_t>(d[m].W) & 15) == 0;
+        if (whole != VEC || d[m].d_out == 0 || d[m].d_in == 0) continue;
+        const int64_t njb = (d[m].d_in + UP_TJ - 1) / UP_TJ;
+        tb.it[tb.n++] = UpdF32Item{static_cast<float*>(d[m].W), d[m].B, d[m].g_dev, d[m].ldw, d[m].d_out, d[m].d_in,
+                                   (uint32_t)blocks, (uint32_t)njb, (uint32_t)d[m].seed, (uint32_t)(d[m].seed >> 32),
+                                   d[m].lr, d[m].r};
+        blocks += njb * ((d[m].d_out + UP_TI - 1) / UP_TI);
+        rp = max(rp, (d[m].r + 3) / 4 * 4);
+    }
+    if (tb.n == 0) return hipSuccess;
+    if (blocks > 0x7FFFFFFFLL) return hipErrorInvalidValue;
+    const size_t smem = (size_t)(UP_TI + UP_BS) * rp * sizeof(float);
     static bool set = false;
     if (!set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(update_kernel<KC>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(update_f32_kernel<VEC>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (UP_TI + UP_TJ) * kMaxRank * (int)sizeof(float));
+                                           (UP_TI + UP_BS) * kMaxRank * (int)sizeof(float));
         if (e != hipSuccess) return e;
         set = true;
     }
-    hipLaunchKernelGGL((update_kernel<KC>), grid, dim3(256), smem, st, W, ldw, d_out, d_in, B, r, nchunk, (uint32_t)seed,
-                       (uint32_t)(seed >> 32), lr, shift, g_dev);
+    hipLaunchKernelGGL(update_f32_kernel<VEC>, dim3((unsigned)blocks), dim3(256), smem, st, tb);
     return hipGetLastError();
+}
+
+hipError_t launch_update_f32_many(const UpdateDesc* d, int n, hipStream_t st, float shift) {
+    if (n < 1 || n > UPD_MAX) return hipErrorInvalidValue;
+    const hipError_t e = launch_update_f32<true>(d, n, st, shift);
+    return e != hipSuccess ? e : launch_update_f32<false>(d, n, st, shift);
 }
 
 hipError_t launch_update(void* W, int dtype, int64_t ldw, int64_t d_out, int64_t d_in, const float* B, int r,
@@ -430,12 +488,8 @@ hipError_t launch_update(void* W, int dtype, int64_t ldw, int64_t d_out, int64_t
     if (d_out == 0 || d_in == 0) return hipSuccess;
     // fp32 storage keeps exact fp32 products (VALU); bf16 storage takes the matrix-core outer product
     if (dtype != AGZO_BF16) {
-        float* Wf = static_cast<float*>(W);
-        if (r <= 1) return launch_kc<1>(Wf, ldw, d_out, d_in, B, r, 1, seed, lr, shift, g_dev, st);
-        if (r <= 2) return launch_kc<2>(Wf, ldw, d_out, d_in, B, r, 1, seed, lr, shift, g_dev, st);
-        if (r <= 4) return launch_kc<4>(Wf, ldw, d_out, d_in, B, r, 1, seed, lr, shift, g_dev, st);
-        if (r <= 8) return launch_kc<8>(Wf, ldw, d_out, d_in, B, r, 1, seed, lr, shift, g_dev, st);
-        return launch_kc<16>(Wf, ldw, d_out, d_in, B, r, (r + 15) / 16, seed, lr, shift, g_dev, st);
+        const UpdateDesc d{W, B, g_dev, ldw, d_out, d_in, seed, lr, r};
+        return launch_update_f32_many(&d, 1, st, shift);
     }
     if (r == 1) {
         const dim3 grid((unsigned)((d_in + U1_COLS - 1) / U1_COLS), (unsigned)((d_out + 4 * U1_ROWS - 1) / (4 * U1_ROWS)));
