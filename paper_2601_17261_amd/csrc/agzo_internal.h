@@ -59,40 +59,15 @@ __device__ __forceinline__ uint4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_
     return make_uint4(c0, c1, c2, c3);
 }
 
-// u(x) = ((x >> 9) + 1/2) 2^-23: 23 random bits plus a half, exact in fp32, strictly inside (0, 1)
-// The generator is bound by its instructions, so the map takes what the arguments allow.  Errors against 64 bits over all 2^23
-// arguments each (logf, sqrtf and sincospif in parentheses): the radius 1.28e-7 of it at most and 3.5e-8 rms (1.49e-7, 3.8e-8), sine and
-// cosine 4.6e-8 at most and 1.46e-8 rms (5.1e-8, 1.50e-8)
-// sqrt(-2 ln u), u never 0, subnormal or 1: the hardware logarithm times -2 ln 2 in two parts, and the square root
-// from the reciprocal one, corrected by its residual
-__device__ __forceinline__ float box_muller_radius(uint32_t x) {
-    constexpr double k = -1.38629436111989061883446424291635313615;
-    constexpr float hi = (float)k, lo = (float)(k - (double)hi);
-    const float l = __builtin_amdgcn_logf(fmaf((float)(x >> 9), 0x1p-23f, 0x1p-24f));
-    const float t = fmaf(l, hi, l * lo);
-    const float y = __builtin_amdgcn_rsqf(t), g = t * y;
-    return fmaf(fmaf(-g, g, t), 0.5f * y, g);
+__device__ __forceinline__ float philox_uniform(uint32_t x) {
+    // 23 random bits plus a half: exact in fp32, strictly inside (0, 1)
+    return ((float)(x >> 9) + 0.5f) * 1.1920928955078125e-07f;  // 2^-23
 }
-// sine and cosine of 2 pi u, u = w 2^-24: the nearest quarter turn in whole numbers, the rest, t quarter turns with
-// |t| <= 1/2, by polynomials (fitted to the largest relative error, 3e-9 and 6e-11) whose leading terms are in two parts
-__device__ __forceinline__ void box_muller_angle(uint32_t x, float& sine, float& cosine) {
-    const uint32_t w = (x >> 8) | 1u, q = (w + 0x200000u) >> 22;
-    const float t = (float)(int)(w - (q << 22)) * 0x1p-22f, z = t * t, zl = fmaf(t, t, -z);
-    constexpr double a0 = 1.5707963217083407, b0 = -1.2337005425976668;
-    constexpr float ah = (float)a0, al = (float)(a0 - (double)ah), bh = (float)b0, bl = (float)(b0 - (double)bh);
-    const float p = fmaf(z, fmaf(z, fmaf(z, -0.004601657887049992f, 0.07968003276843973f), -0.6459634602331893f), al);
-    const float s = fmaf(t, ah, t * p);
-    const float r = fmaf(z, fmaf(z, fmaf(z, 0.0009037665420705298f, -0.020860165110978122f), 0.25366922596544084f), bl);
-    const float m = fmaf(z, bh, 1.0f), rest = fmaf(z, r, zl * bh);
-    const float c = m + (fmaf(z, bh, 1.0f - m) + rest);
-    const bool odd = (q & 1u) != 0;
-    sine = __uint_as_float(__float_as_uint(odd ? c : s) ^ ((q << 30) & 0x80000000u));
-    cosine = __uint_as_float(__float_as_uint(odd ? s : c) ^ (((q + 1u) << 30) & 0x80000000u));
-}
+
 __device__ __forceinline__ void box_muller(uint32_t xa, uint32_t xb, float& z0, float& z1) {
+    float rad = sqrtf(-2.0f * logf(philox_uniform(xa)));
     float s, c;
-    const float rad = box_muller_radius(xa);
-    box_muller_angle(xb, s, c);
+    sincospif(2.0f * philox_uniform(xb), &s, &c);
     z0 = rad * c;
     z1 = rad * s;
 }
