@@ -839,7 +839,7 @@ def main():
     res["roofline_generator"] = {"bound": "hbm", "kernel": "fill_normal_kernel", "achieved": fill_gbs, "peak": PEAK_HBM_GBS,
                                  "unit": "GB/s", "frac": fill_gbs / PEAK_HBM_GBS, "launches": n_fill,
                                  "normals_per_s": fill_gbs * 1e9 / 4.0,
-                                 "note": "4 bytes written per value; 59 vector instructions per value (Philox4x32-10 + "
+                                 "note": "4 bytes written per value; 50 vector instructions per value (Philox4x32-10 + "
                                          "Box-Muller; profiles/generator_valu_instructions.txt): the rate follows these, not the bytes"}
     # the dense Gaussian sweep of Eq. 7's other branch on a bf16 block of the same size (read + write 2 bytes each)
     theta = gbuf.view(torch.bfloat16)[:, :16]

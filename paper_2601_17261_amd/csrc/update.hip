@@ -595,7 +595,8 @@ int update_many_max() { return UPD_MAX; }
 // and the two halves of every Philox product by themselves: the estimator over seven 0.6B-sized layers 419 us a step, 408 so.)  Rows
 // that four columns do not divide are read and written value by value, each load in its place: there half the threads hide less of that
 // latency than they save of the generator's (fp32, 982 x 1183: 5.1 us with a row a thread, 6.2 with two; 1024 x 2047 6.8 and 7.2; 8192 x
-// 4095 62 and 62), except in large bf16 blocks (8192 x 4095: 49 and 47)
+// 4095 62 and 62), except in large bf16 blocks (8192 x 4095: 49 and 47); all with a generator of 59 instructions a value.  With 50 a
+// value 8192 x 4096 in bf16 takes 39.0 us instead of 43.9
 template <typename T, bool VEC, int DENSE_ROWS>
 __global__ __launch_bounds__(256) void dense_axpy_kernel(T* __restrict__ theta, int64_t rows, int64_t cols, int64_t ld,
                                                          int64_t nquad, int64_t items, uint32_t s_lo, uint32_t s_hi, float scale,
