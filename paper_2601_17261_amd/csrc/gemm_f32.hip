@@ -403,7 +403,9 @@ hipError_t launch_rank_term_f32(float* Y, int64_t ldy, int64_t M, int64_t N, con
 // result rows and split the contraction between them, so that the whole chip has loads in flight after one launch and no
 // second one is needed to add partial sums (they meet in LDS, in wave order).  The result has up to four blocks of 16 columns.
 // (The generic 64 x 64 tile kernel that these replace walked the contraction alone, with r of its 64 columns in use: 50 us at
-// 512 x 256 and r = 4, now 5 (xq) and 5.5 (xtt); the seven layers of 1000 x 1024 .. 3072 in one launch take 34 and 17 us.)
+// 512 x 256 and r = 4, now 4.6 (xq) and 5.5 (xtt); the seven layers of 1000 x 1024 .. 3072 in one launch take 22 and 17 us.)  A
+// load of xq is conditional on nothing but uniform values: with conditions of a lane, and the forms for aligned and other rows
+// beside each other in the loop, the compiler waited for each (34 us, and 5.0 at 512 x 256).
 // ---------------------------------------------------------------------------
 constexpr int SK_WAVES = 16;
 
@@ -436,12 +438,8 @@ __device__ __forceinline__ void skinny_f32_finish(const doublex4 (&acc)[NB], dou
 }
 
 // T = X Q: rows = tokens, 16-wide chunks of d_in dealt to the waves
-template <int NB>
-__global__ __launch_bounds__(64 * SK_WAVES) void xq_f32_kernel(const KBatch<F32SkinnyDev> tb) {
-    __shared__ double red[SK_WAVES * 256];
-    uint32_t bx, by;
-    const F32SkinnyDev& d = tb.a[kbatch_find(tb, bx, by)];
-    const F32SkinnyArgs& a = d.a;
+template <int NB, bool VEC>
+__device__ __forceinline__ void xq_f32_rows(const F32SkinnyArgs& a, double* red, uint32_t bx) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lc = lane & 15, lg = lane >> 4;
     const int64_t t0 = (int64_t)bx * 16;
     const float* xr = a.X + min(t0 + lc, a.M - 1) * a.ldx;
@@ -455,17 +453,29 @@ __global__ __launch_bounds__(64 * SK_WAVES) void xq_f32_kernel(const KBatch<F32S
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t k = 16 * (int64_t)(c0 + u * SK_WAVES) + 4 * lg;
-            if (d.vec) {
-                const float4 v = (k < a.K) ? *reinterpret_cast<const float4*>(xr + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+            if (c0 + u * SK_WAVES >= nchunk) break;        // (wave-uniform)
+            if constexpr (VEC) {
+                const float4 v = *reinterpret_cast<const float4*>(xr + min(k, a.K - 4));
                 x[u][0] = v.x; x[u][1] = v.y; x[u][2] = v.z; x[u][3] = v.w;
             } else {
 #pragma unroll
-                for (int s = 0; s < 4; ++s) x[u][s] = (k + s < a.K) ? xr[k + s] : 0.f;
+                for (int s = 0; s < 4; ++s) x[u][s] = xr[min(k + s, a.K - 1)];
             }
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-                for (int s = 0; s < 4; ++s) q[u][nb][s] = (k + s < a.K && nb * 16 + lc < a.r) ? a.V[(k + s) * a.r + nb * 16 + lc] : 0.f;
+                for (int s = 0; s < 4; ++s) q[u][nb][s] = a.V[min(k + s, a.K - 1) * a.r + min(nb * 16 + lc, a.r - 1)];
+        }
+        // (never conditional on the lane: what lies past the end is read from the last place and left out)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t k = 16 * (int64_t)(c0 + u * SK_WAVES) + 4 * lg;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                x[u][s] = k + s < a.K ? x[u][s] : 0.f;
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) q[u][nb][s] = k + s < a.K && nb * 16 + lc < a.r ? q[u][nb][s] : 0.f;
+            }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -479,19 +489,26 @@ __global__ __launch_bounds__(64 * SK_WAVES) void xq_f32_kernel(const KBatch<F32S
     }
     skinny_f32_finish<NB>(acc, red, t0, a.M, a.r, a.out);
 }
+template <int NB>
+__global__ __launch_bounds__(64 * SK_WAVES) void xq_f32_kernel(const KBatch<F32SkinnyDev> tb) {
+    __shared__ double red[SK_WAVES * 256];
+    uint32_t bx, by;
+    const F32SkinnyDev& d = tb.a[kbatch_find(tb, bx, by)];
+    if (d.vec)      // (once, around everything: where two forms of a load meet, the compiler waits for it)
+        xq_f32_rows<NB, true>(d.a, red, bx);
+    else
+        xq_f32_rows<NB, false>(d.a, red, bx);
+}
 
 // T = X Q for one to four columns, of which the form above uses as many lanes in sixteen to load Q: a workgroup is four tokens, its four
 // waves share d_in in chunks of 256, a lane multiplies four consecutive values of each token with the rows of Q that belong to them, on
 // the vector units (whose fp64 rate is that of the matrix cores and far from what bounds this: the bytes of X and their latency; two
-// chunks in flight).  Seven layers of 1000 x 1024 .. 3072 at r = 1: 34 us a launch above, 18 here.  Shorter rows leave waves without a chunk
-// and loads for nothing (512 x 256, r = 4: 5.1 us above, 7.8 here; 512-wide 4 % of a step slower, 1024-wide 0 to 4 % faster)
+// chunks in flight).  Seven layers of 1000 x 1024 .. 3072 at r = 1: 22 us a launch above, 11 here (18 with both forms of the load of X inside
+// the loop).  Shorter rows leave waves without a chunk and loads for nothing: a step on 512 tokens at r = 1 / 4, above and here, 80 / 102 and
+// 86 / 114 us 256-wide, 92 / 124 and 94 / 134 512-wide, 116 / 149 and 103 / 148 1024-wide, 161 / 196 and 134 / 180 2048-wide
 constexpr int XQN_TOK = 4, XQN_MIN = 1024;
-template <int R>
-__global__ __launch_bounds__(256) void xq_f32_narrow_kernel(const KBatch<F32SkinnyDev> tb) {
-    __shared__ double red[4][XQN_TOK * R];
-    uint32_t bx, by;
-    const F32SkinnyDev& d = tb.a[kbatch_find(tb, bx, by)];
-    const F32SkinnyArgs& a = d.a;
+template <int R, bool VEC>
+__device__ __forceinline__ void xq_f32_narrow_rows(const F32SkinnyArgs& a, double (*red)[XQN_TOK * R], uint32_t bx) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t t0 = (int64_t)bx * XQN_TOK, K = a.K;
     const float* xr[XQN_TOK];
@@ -506,7 +523,7 @@ __global__ __launch_bounds__(256) void xq_f32_narrow_kernel(const KBatch<F32Skin
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t k = 256 * (c0 + 4 * u) + 4 * lane;
-            if (d.vec) {
+            if constexpr (VEC) {
                 const int64_t kc = min(k, K - 4);
 #pragma unroll
                 for (int t = 0; t < XQN_TOK; ++t) {
@@ -548,6 +565,16 @@ __global__ __launch_bounds__(256) void xq_f32_narrow_kernel(const KBatch<F32Skin
     __syncthreads();
     const int e = threadIdx.x;
     if (e < XQN_TOK * R && t0 + e / R < a.M) a.out[t0 * R + e] = (float)((red[0][e] + red[1][e]) + (red[2][e] + red[3][e]));
+}
+template <int R>
+__global__ __launch_bounds__(256) void xq_f32_narrow_kernel(const KBatch<F32SkinnyDev> tb) {
+    __shared__ double red[4][XQN_TOK * R];
+    uint32_t bx, by;
+    const F32SkinnyDev& d = tb.a[kbatch_find(tb, bx, by)];
+    if (d.vec)
+        xq_f32_narrow_rows<R, true>(d.a, red, bx);
+    else
+        xq_f32_narrow_rows<R, false>(d.a, red, bx);
 }
 
 // S = X^T T: rows = features, groups of four tokens dealt to the waves
