@@ -741,8 +741,9 @@ static hipError_t launch_qr1(const KBatch<QrDev, CAP>& tb, unsigned blocks, cons
 
 // Bytes of Gram partials from which on they are summed ahead.  agzo_qr, us, summed by every block and ahead: r = 64, 2048 rows (320 KB) 64.5
 // and 65.6, 2560 (400 KB) 66.1 and 65.9, 4096 (640 KB) 71 and 67, 9728 (1.5 MB) 90 and 72; r = 32, 9728 (456 KB) 37.8 and 37.2; r = 16, 40000
-// (626 KB) 58 and 50.  The single pass of seven 4B-sized layers, r = 64: 41 and 30 + 5.7
-constexpr int64_t kSumAhead = 448 * 1024;
+// (626 KB) 58 and 50.  The single pass of seven 4B-sized layers, r = 64: 41 and 30 + 5.7.  A step of them on 128 tokens, r = 26 (456 KB):
+// 438 and 445, 8B-sized (576 KB), before there were sums ahead and now: 695 and 684
+constexpr int64_t kSumAhead = 512 * 1024;
 template <int RP, int CAP>
 static hipError_t launch_qr_rp(const KBatch<QrDev, CAP>& tb, unsigned blocks, int* flag, bool refine, hipStream_t st) {
     typedef QrShape<RP> Q;

@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 # tokens, widths of the layers that are small alone, and of one that makes the call take the other launches
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("n,r,widths,other", [(300, 3, (8, 120, 128, 136, 256, 512), 520), (257, 16, (64, 248, 256, 500, 512), 2048), (2100, 9, (256, 264), 4096),
-                                              (300, 64, (640, 72), 4104), (300, 20, (9728, 64), 264)])
+                                              (300, 64, (640, 72), 4104), (300, 20, (9728, 64), 264), (300, 20, (12288, 64), 264)])
 def test_basis_in_any_company(n, r, widths, other, dtype):
     ctx = binding.Context()
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
