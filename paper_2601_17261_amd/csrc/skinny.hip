@@ -668,7 +668,7 @@ static hipError_t launch_xq_narrow(const XqArgs* const* a, int n, hipStream_t st
 // 16-byte pieces through LDS, sixteen waves, another order of the chunks: the same time or 5 to 30 % more.)  With the planes of B and the
 // W side in a launch ahead, which is bound by its latency, and the projection in workgroups of 64 tokens it took, r = 16, us: 4.8 + 10.5
 // at 8192 x 2048 -> 2048 and 10.0 so; 4.8 + 44 at 8192 x 6144 and 33; 4.8 + 5 + 4.5 (shares of d_in, added by a third launch) at 385 x 2048
-// and 8.5.  A decoder on 8192 tokens 15268 a step and 14943, on 385 1929 and 1859
+// and 8.5.  A decoder on 8192 tokens 15345 a step and 14988, on 385 1931 and 1834
 // ---------------------------------------------------------------------------
 constexpr int XQE_TOK = 32, XQE_WAVES = 8;
 struct XqExtDev {
@@ -756,8 +756,16 @@ __global__ __launch_bounds__(64 * XQE_WAVES) void xq_ext_kernel(const XqExtDev a
     if (blockIdx.x < blocks) xq_ext_body(a, blockIdx.x);
     else ext_prep_body(ext, (int64_t)(blockIdx.x - blocks) * (64 * XQE_WAVES) + threadIdx.x);
 }
-// (few tokens of a wide layer are a few workgroups that take in all of d_in each: 21 us for 300 x 8000 where the three launches take 17)
-bool xq_ext_ok(int64_t M, int64_t K, int r) { return r <= 16 && K >= 8 && (K <= 6144 || M >= 8192); }
+// One round of workgroups, and no more of d_in to a workgroup than the tokens make up for: few workgroups that take in all of a wide layer's d_in each
+// are slower than shares of d_in and a launch that adds them, and more workgroups than compute units slower than the 64-token ones of
+// xq_bf16_many_kernel.  A perturbed forward to 384 outputs, r = 16, us, those launches and this one: 385 tokens of 2048 20.8 and 18.6, of 3072
+// 22.4 and 22.0, of 4096 23.4 and 25.2, of 6144 27.0 and 32.6; 3001 of 2560 28.5 and 27.4, of 4096 31.8 and 31.4, of 6144 38.1 and 40.3; 6000
+// of 5120 54.9 and 52.0, 8192 of 2048 30.0 and 25.5, of 6144 66.7 and 59.4, of 8192 82.7 and 85.5; 9000 of 512 17.1 and 18.0, of 2048 30.8 and
+// 32.1, of 6144 69.4 and 76.3, 16384 of 4096 76.9 and 75.5, of 8192 171 and 188.  On this side of the line d_in has fewer than eight shares
+// there, so the sums here are the more exact ones (8192 of 6144: 3.1e-7 of the result against 8.6e-7; beyond it, 385 of 6144 in sixteen shares,
+// it was 3.0e-7 against 2.5e-7)
+constexpr int XQE_CUS = 256;
+bool xq_ext_ok(int64_t M, int64_t K, int r) { return r <= 16 && K >= 8 && M <= (int64_t)XQE_CUS * XQE_TOK && (K <= 2048 || M >= K + K / 8); }
 hipError_t launch_xq_ext(const XqArgs& a, const GemmExtArgs* ext, hipStream_t st) {
     if (!xq_ext_ok(a.M, a.K, a.r) || !a.Q || a.TpackT || (ext && (ext->planes || ext->P))) return hipErrorInvalidValue;
     const uint64_t wgs = (uint64_t)((a.M + XQE_TOK - 1) / XQE_TOK);
