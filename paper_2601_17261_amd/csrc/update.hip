@@ -26,6 +26,7 @@ struct UpdF32Item {
     uint32_t s_lo, s_hi;
     float lr;
     int r;
+    int vec;              // rows start on 16 bytes
 };
 struct UpdF32Batch {
     int n;
@@ -42,16 +43,14 @@ struct UpdF32Batch {
 // last and took a launch each: 107 -> 24 us (5.2 TB/s); a 2560-wide set 299 -> 144 (5.6 TB/s); three matrices at r = 64
 // 101 -> 34 (generator and products); 1001 x 1003 and 777 x 2049, r = 7, 42 -> 13; 4096 x 12288, r = 1, 61 -> 59.  Tiles of
 // 64 rows (two waves a SIMD, not four): 29, 155, 43, 13, 60; of 16 rows: 25, 158, 45, 12, 59.
-template <bool VEC>   // rows of whole aligned runs of four
-__global__ __launch_bounds__(256) void update_f32_kernel(const UpdF32Batch tb) {
+// Rows that start on 16 bytes but end inside a run of four are read value by value in their last tile only.  Tiles take one form or the
+// other around everything (where two forms of a load meet, the compiler waits for it): 4096 x 4094, rows of 4096, r = 1, 34.3 us with the
+// earlier tiles, 36.5 value by value, 33.7 so; 31 x 70001 7.1, 11.3 and 5.9.
+template <bool VEC>   // whole aligned runs of four
+__device__ __forceinline__ void update_f32_tile(const UpdF32Item& u, float shift, int64_t i0, int64_t j0) {
     extern __shared__ __align__(16) float up_smem[];
-    int m = 0;
-    while (m + 1 < tb.n && blockIdx.x >= tb.it[m + 1].blk0) ++m;
-    const UpdF32Item& u = tb.it[m];
     const int64_t ldw = u.ldw, d_out = u.d_out, d_in = u.d_in;
     const int r = u.r, nquad = (r + 3) / 4;
-    const uint32_t local = blockIdx.x - u.blk0;
-    const int64_t i0 = (int64_t)(local / u.njb) * UP_TI, j0 = (int64_t)(local % u.njb) * UP_TJ;
     float4* Gs = reinterpret_cast<float4*>(up_smem);        // [UP_TI][nquad]
     float* Bt = up_smem + UP_TI * nquad * 4;                // [4 nquad][UP_BS]
     const int tid = threadIdx.x;
@@ -101,7 +100,7 @@ __global__ __launch_bounds__(256) void update_f32_kernel(const UpdF32Batch tb) {
     }
     __syncthreads();
 
-    const float coef = -fmaf(u.lr, u.g_dev ? (float)(*u.g_dev) : 1.0f, tb.shift);
+    const float coef = -fmaf(u.lr, u.g_dev ? (float)(*u.g_dev) : 1.0f, shift);
     float acc[UP_TR][8];
 #pragma unroll
     for (int s = 0; s < UP_TR; ++s)
@@ -150,6 +149,16 @@ __global__ __launch_bounds__(256) void update_f32_kernel(const UpdF32Batch tb) {
             }
         }
     }
+}
+
+__global__ __launch_bounds__(256) void update_f32_kernel(const UpdF32Batch tb) {
+    int m = 0;
+    while (m + 1 < tb.n && blockIdx.x >= tb.it[m + 1].blk0) ++m;
+    const UpdF32Item& u = tb.it[m];
+    const uint32_t local = blockIdx.x - u.blk0;
+    const int64_t i0 = (int64_t)(local / u.njb) * UP_TI, j0 = (int64_t)(local % u.njb) * UP_TJ;
+    if (u.vec && ((u.d_in & 3) == 0 || j0 + UP_TJ <= u.d_in)) update_f32_tile<true>(u, tb.shift, i0, j0);
+    else update_f32_tile<false>(u, tb.shift, i0, j0);
 }
 
 // ---------------------------------------------------------------------------
@@ -445,20 +454,20 @@ static hipError_t launch_mfma(bf16_t* W, int64_t ldw, int64_t d_out, int64_t d_i
     return hipGetLastError();
 }
 
-template <bool VEC>
-static hipError_t launch_update_f32(const UpdateDesc* d, int n, hipStream_t st, float shift) {
+hipError_t launch_update_f32_many(const UpdateDesc* d, int n, hipStream_t st, float shift) {
+    if (n < 1 || n > UPD_MAX) return hipErrorInvalidValue;
     UpdF32Batch tb;
     tb.n = 0;
     tb.shift = shift;
     int64_t blocks = 0;
     int rp = 0;
     for (int m = 0; m < n; ++m) {
-        const bool whole = ((d[m].ldw | d[m].d_in) & 3) == 0 && (reinterpret_cast<uintptr_t>(d[m].W) & 15) == 0;
-        if (whole != VEC || d[m].d_out == 0 || d[m].d_in == 0) continue;
+        if (d[m].d_out == 0 || d[m].d_in == 0) continue;
+        const bool vec = (d[m].ldw & 3) == 0 && (reinterpret_cast<uintptr_t>(d[m].W) & 15) == 0;
         const int64_t njb = (d[m].d_in + UP_TJ - 1) / UP_TJ;
         tb.it[tb.n++] = UpdF32Item{static_cast<float*>(d[m].W), d[m].B, d[m].g_dev, d[m].ldw, d[m].d_out, d[m].d_in,
                                    (uint32_t)blocks, (uint32_t)njb, (uint32_t)d[m].seed, (uint32_t)(d[m].seed >> 32),
-                                   d[m].lr, d[m].r};
+                                   d[m].lr, d[m].r, vec ? 1 : 0};
         blocks += njb * ((d[m].d_out + UP_TI - 1) / UP_TI);
         rp = max(rp, (d[m].r + 3) / 4 * 4);
     }
@@ -467,20 +476,14 @@ static hipError_t launch_update_f32(const UpdateDesc* d, int n, hipStream_t st, 
     const size_t smem = (size_t)(UP_TI + UP_BS) * rp * sizeof(float);
     static bool set = false;
     if (!set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(update_f32_kernel<VEC>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(update_f32_kernel),
                                            hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (UP_TI + UP_BS) * kMaxRank * (int)sizeof(float));
         if (e != hipSuccess) return e;
         set = true;
     }
-    hipLaunchKernelGGL(update_f32_kernel<VEC>, dim3((unsigned)blocks), dim3(256), smem, st, tb);
+    hipLaunchKernelGGL(update_f32_kernel, dim3((unsigned)blocks), dim3(256), smem, st, tb);
     return hipGetLastError();
-}
-
-hipError_t launch_update_f32_many(const UpdateDesc* d, int n, hipStream_t st, float shift) {
-    if (n < 1 || n > UPD_MAX) return hipErrorInvalidValue;
-    const hipError_t e = launch_update_f32<true>(d, n, st, shift);
-    return e != hipSuccess ? e : launch_update_f32<false>(d, n, st, shift);
 }
 
 hipError_t launch_update(void* W, int dtype, int64_t ldw, int64_t d_out, int64_t d_in, const float* B, int r,

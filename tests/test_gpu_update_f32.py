@@ -5,12 +5,14 @@ import pytest
 import torch
 
 from oracle import agzo as oagzo
+from launches import kernels
 from paper_2601_17261_amd import binding
 
 pytestmark = pytest.mark.gpu
 
-# d_out, d_in, row stride, r
-SHAPES = [(1, 1, 1, 1), (31, 4, 8, 4), (32, 256, 256, 16), (33, 260, 260, 3), (65, 255, 256, 2), (64, 513, 513, 17), (7, 1028, 1032, 64), (300, 131, 131, 5)]
+# d_out, d_in, row stride, r (the last three: aligned rows that end inside a run of four)
+SHAPES = [(1, 1, 1, 1), (31, 4, 8, 4), (32, 256, 256, 16), (33, 260, 260, 3), (65, 255, 256, 2), (64, 513, 513, 17), (7, 1028, 1032, 64), (300, 131, 131, 5),
+          (40, 254, 256, 1), (33, 515, 520, 2), (5, 1021, 1024, 33)]
 
 
 @pytest.mark.parametrize("copies", [1, 3])
@@ -36,3 +38,17 @@ def test_sweeps_of_one_call(copies):
         assert (buf[:, d_in:] == 3.0).all()
         # G itself comes from fp32 logarithms and angles: 2^-20 of a value
         assert (np.abs(buf[:, :d_in].cpu().numpy().astype(np.float64) - want) <= bound * 8 + 1e-30).all()
+
+
+def test_rows_of_every_kind_share_a_launch():
+    """aligned rows of whole runs of four, aligned rows that end inside one, and others"""
+    stream = torch.cuda.Stream()
+    ctx = binding.Context(stream=stream)
+    items = [(torch.zeros(d_out, ld, device="cuda")[:, :d_in], torch.zeros(d_in, r, device="cuda"), 5, 0.1, None) for d_out, d_in, ld, r in SHAPES]
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        ctx.update_many(items)
+        stream.synchronize()
+    names, _ = kernels(stream, lambda: ctx.update_many(items))
+    assert len(names) == 1 and "update_f32_kernel" in names[0], names
+    ctx.close()
