@@ -10,7 +10,7 @@
 // RAGGED = false takes tile-aligned layers: M and N multiples of 256, d_in a multiple of 64, 16-byte aligned target / output
 // rows.  RAGGED = true takes the others.  The last tile of a direction starts at the last 256 rows (or columns) instead of
 // hanging over the edge, so no load needs a bound; softmax statistics leave out what the tile before it has counted, stored
-// outputs are stored twice with the same bits.  For the squared error the two halves of a tile do so each by itself (a tile's second
+// outputs are stored twice with the same bits.  For the squared error of bf16 targets the two halves of a tile do so each by itself (a tile's second
 // 128 rows start at the last 128 of the matrix at the latest), so that a wave's 128 x 128 outputs are those of a tile of
 // gemm_bf16_mid.hip, and leave out what the half before them has counted.  A last slice that d_in does not fill gets a descriptor with a
 // range, and the lanes past d_in an offset beyond it: they load zeros.  gemm_bf16.hip, which bounded every access and drained
@@ -137,24 +137,36 @@ static_assert(sizeof(TileLists) <= 4096, "kernel arguments");
 template <int PHASES, int CAP>
 using AlignedArgs = typename std::conditional<(PHASES == 1 && CAP > 1), TileLists, KBatch<AlignedItem, CAP>>::type;
 
+template <int CAP>
+__device__ __forceinline__ int own_problem(const KBatch<AlignedItem, CAP>& tb, uint32_t& wgid) {
+    uint32_t unused;
+    return kbatch_find(tb, wgid, unused);
+}
+__device__ __forceinline__ int own_problem(const TileLists&, uint32_t&) { return 0; }
+
 template <int OUT, bool T_F32, int PHASES, bool RAGGED, int CAP>
 __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArgs<PHASES, CAP> tb) {
     static_assert(OUT == 0 || (PHASES == 1 && !T_F32), "the kernels without a squared-error target have one evaluation");
     constexpr bool LISTS = PHASES == 1 && CAP > 1;
     constexpr bool LATE_T = RAGGED && OUT == 0;    // the target is subtracted after the last slice
-    // ... and the two 128-row halves of a tile end at the last row by themselves, as the tiles of gemm_bf16_mid.hip do.  (Not in the
-    // shared schedule, which no other kernel's layers join: its registers spill anyway, and halves took it 9 % longer)
-    constexpr bool HALVES = LATE_T && PHASES == 1;
+    // ... and the two 128-row halves of a tile end at the last row by themselves, as the tiles of gemm_bf16_mid.hip do.  (Only where lists
+    // may join layers of that kernel, that is for one evaluation and bf16 targets: in the shared schedule, whose registers spill anyway,
+    // halves took 9 % longer, with fp32 targets 128 registers spilled for 116, 1 % of a forward 8191 x 2048 -> 2048)
+    constexpr bool HALVES = LATE_T && PHASES == 1 && !T_F32;
     constexpr int NT = 256, BA = 4, BB = 4;
     constexpr int W_BASE = 0, X_BASE = 3 * TILE_BYTES;       // LDS: three W stages, then two X stages (all 160 KiB)
     extern __shared__ __align__(16) char smem[];
-    uint32_t wgid = blockIdx.x, unused;                      // this problem's workgroups count from 0
+    uint32_t wgid = blockIdx.x;                              // this problem's workgroups count from 0
     // the problems of the current and of the next tile, by their places in the arguments (as pointers the compiler copies all of them
-    // to scratch memory)
+    // to scratch memory; the only problem of a workgroup, whose place it would work out again, by reference)
     int cq = 0, nq = 0;
-    if constexpr (!LISTS) cq = kbatch_find(tb, wgid, unused);
+    const AlignedItem& only = tb.a[own_problem(tb, wgid)];
+    auto item = [&](int q) __attribute__((always_inline)) -> const AlignedItem& {
+        if constexpr (LISTS) return tb.a[q];
+        else return only;
+    };
     const int tid = threadIdx.x, lane = tid & 63;
-    if (!LISTS && tb.a[cq].clk && wgid == 0 && tid == 0) { tb.a[cq].clk[0] = __builtin_readcyclecounter(); tb.a[cq].clk[1] = wall_clock64(); }
+    if (!LISTS && item(cq).clk && wgid == 0 && tid == 0) { item(cq).clk[0] = __builtin_readcyclecounter(); item(cq).clk[1] = wall_clock64(); }
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wa = wave >> 1, wb = wave & 1;
     const int lc = lane & 15, lg = lane >> 4;      // matrix instruction 16x16x32: column (token) / row of a fragment, k group
@@ -176,8 +188,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
     };
     // lists of one problem's tiles
     int G = 0;
-    if constexpr (!LISTS) G = (int)tb.gx[CAP == 1 ? 0 : cq];
-    const int nwg = LISTS ? 0 : tb.a[cq].tiles_m * tb.a[cq].tiles_n;
+    if constexpr (!LISTS) G = (int)tb.gx[CAP == 1 ? 0 : &only - tb.a];
+    const int nwg = LISTS ? 0 : item(cq).tiles_m * item(cq).tiles_n;
     const bool by_xcd = (G % 8 == 0);
     const int S = by_xcd ? G / 8 : G;
     const int xcd = by_xcd ? (int)wgid % 8 : 0, slot = by_xcd ? (int)wgid / 8 : (int)wgid;
@@ -185,7 +197,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
     const int n_run = slot < per ? (per - slot + S - 1) / S : 0;
     const int n_tiles = __builtin_amdgcn_readfirstlane(n_run + ((by_xcd && slot == S - 1 && xcd < nwg - 8 * per) ? 1 : 0));
     auto tile_at = [&](int i, int64_t& tm_, int64_t& tn_) __attribute__((always_inline)) {
-        tile_of(tb.a[cq], (i < n_run) ? xcd * per + slot + i * S : 8 * per + xcd, tm_, tn_);
+        tile_of(item(cq), (i < n_run) ? xcd * per + slot + i * S : 8 * per + xcd, tm_, tn_);
     };
     // lists over several problems: problem (l_rest: what is left of it) and round of this workgroup's next tile, the tiles of the run
     // taken in earlier rounds, and, lane by lane, how many tiles the slots of the XCD take of the problem
@@ -205,7 +217,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
                     ++l_round;
                     if (at < l_run) {
                         nq = l_q;
-                        tile_of(tb.a[l_q], l_begin + at, tmn, tnn);
+                        tile_of(item(l_q), l_begin + at, tmn, tnn);
                         return;
                     }
                 }
@@ -216,7 +228,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
                     l_q = 0;
                 }
                 const int q = l_q;
-                const int tiles = tb.a[q].tiles_m * tb.a[q].tiles_n, share = tiles / 8, longer = tiles - 8 * share;
+                const int tiles = item(q).tiles_m * item(q).tiles_n, share = tiles / 8, longer = tiles - 8 * share;
                 const int at8 = (lxcd - (int)tb.long_at[q]) & 7;      // this XCD's place among the runs
                 l_begin = at8 * share + min(at8, longer);
                 l_run = share + (at8 < longer ? 1 : 0);
@@ -247,19 +259,19 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
     auto second_half = [&](int64_t t, int64_t size) __attribute__((always_inline)) {
         return HALVES ? (int)(min(t * BT + BT / 2, size - BT / 2) - (origin(t, size) + BT / 2)) : 0;
     };
-    int64_t m0 = origin(tm, tb.a[cq].M), n0 = origin(tn, tb.a[cq].N);
-    int hm = second_half(tm, tb.a[cq].M), hn = second_half(tn, tb.a[cq].N), hmn = 0, hnn = 0;
+    int64_t m0 = origin(tm, item(cq).M), n0 = origin(tn, item(cq).N);
+    int hm = second_half(tm, item(cq).M), hn = second_half(tn, item(cq).N), hmn = 0, hnn = 0;
 
     // ---- operand sources: X / W slices, then the prepared extension operands ----------------------
     // operand bases of the current tile (d_in slices, extension slices) and of the next tile's d_in slices
     const bf16_t *xb, *wb_, *xb2, *wb2, *wb3, *xbn, *wbn;
     auto tile_sources = [&]() __attribute__((always_inline)) {
-        const bool has_ext = tb.a[cq].Xext != nullptr;
-        xb = tb.a[cq].X + m0 * tb.a[cq].ldx;
-        wb_ = tb.a[cq].W + n0 * tb.a[cq].ldw;
-        xb2 = has_ext ? tb.a[cq].Xext + m0 * tb.a[cq].ext_ld : xb;
-        wb2 = has_ext ? tb.a[cq].Wext + n0 * tb.a[cq].ext_ld : wb_;
-        wb3 = (has_ext && PHASES == 3) ? tb.a[cq].Wext2 + n0 * tb.a[cq].ext_ld : wb_;
+        const bool has_ext = item(cq).Xext != nullptr;
+        xb = item(cq).X + m0 * item(cq).ldx;
+        wb_ = item(cq).W + n0 * item(cq).ldw;
+        xb2 = has_ext ? item(cq).Xext + m0 * item(cq).ext_ld : xb;
+        wb2 = has_ext ? item(cq).Wext + n0 * item(cq).ext_ld : wb_;
+        wb3 = (has_ext && PHASES == 3) ? item(cq).Wext2 + n0 * item(cq).ext_ld : wb_;
     };
     // the tile after the current one (i: its index; LISTS: the list's next); past the list: the current tile once more (its first
     // slices are fetched again into the stage nobody reads)
@@ -270,11 +282,11 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
             nq = cq; tmn = tm; tnn = tn;
             if (i < n_tiles) tile_at(i, tmn, tnn);
         }
-        xbn = tb.a[nq].X + origin(tmn, tb.a[nq].M) * tb.a[nq].ldx;
-        wbn = tb.a[nq].W + origin(tnn, tb.a[nq].N) * tb.a[nq].ldw;
-        hmn = second_half(tmn, tb.a[nq].M);
-        hnn = second_half(tnn, tb.a[nq].N);
-        if (LISTS) { l_ldxn = (int)tb.a[nq].ldx; l_ldwn = (int)tb.a[nq].ldw; }
+        xbn = item(nq).X + origin(tmn, item(nq).M) * item(nq).ldx;
+        wbn = item(nq).W + origin(tnn, item(nq).N) * item(nq).ldw;
+        hmn = second_half(tmn, item(nq).M);
+        hnn = second_half(tnn, item(nq).N);
+        if (LISTS) { l_ldxn = (int)item(nq).ldx; l_ldwn = (int)item(nq).ldw; }
     };
     // on to the next tile
     auto next_tile = [&](int it) __attribute__((always_inline)) {
@@ -284,8 +296,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
         } else {
             tile_at(it + 1, tm, tn);
         }
-        m0 = origin(tm, tb.a[cq].M);   n0 = origin(tn, tb.a[cq].N);
-        hm = second_half(tm, tb.a[cq].M);   hn = second_half(tn, tb.a[cq].N);
+        m0 = origin(tm, item(cq).M);   n0 = origin(tn, item(cq).N);
+        hm = second_half(tm, item(cq).M);   hn = second_half(tn, item(cq).N);
     };
     tile_sources();
     next_sources(1);
@@ -294,20 +306,21 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
     const int row0 = 8 * wave + (lane >> 3);
     const int chunk0 = (lane & 7) ^ ((row0 >> 1) & 7);       // the swizzle term does not depend on t
     const int wrow0 = w_perm64(row0);
-    const int vx = (int)(((int64_t)row0 * tb.a[cq].ldx + chunk0 * 8) * 2), vw = (int)(((int64_t)wrow0 * tb.a[cq].ldw + chunk0 * 8) * 2);
-    const int vx2 = (row0 * tb.a[cq].ext_ld + chunk0 * 8) * 2, vw2 = (wrow0 * tb.a[cq].ext_ld + chunk0 * 8) * 2;
-    const int gsx = (int)(64 * tb.a[cq].ldx), gsw = (int)(64 * tb.a[cq].ldw), gs2 = 64 * tb.a[cq].ext_ld;   // bytes between row groups
+    const int vx = (int)(((int64_t)row0 * item(cq).ldx + chunk0 * 8) * 2), vw = (int)(((int64_t)wrow0 * item(cq).ldw + chunk0 * 8) * 2);
+    const int vx2 = (row0 * item(cq).ext_ld + chunk0 * 8) * 2, vw2 = (wrow0 * item(cq).ext_ld + chunk0 * 8) * 2;
+    const int gsx = (int)(64 * item(cq).ldx), gsw = (int)(64 * item(cq).ldw), gs2 = 64 * item(cq).ext_ld;   // bytes between row groups
+    const int tail_off = (RAGGED && !LISTS && chunk0 * 8 >= (int)(item(cq).K % BK)) ? kPastEnd : 0;     // (of the slice that d_in does not fill)
     int nfull = 0, nd = 0, next = 0, npipe = 0, ktail = 0;
     // d_in slices (whole ones, all) and extension slices of the current tile's problem; npipe: slices that ride the load
     // pipeline, the d_in slices and in the one-evaluation kernel the extension behind them (at least two: the first two slices of a
     // tile are always d_in slices)
     auto count_slices = [&]() __attribute__((always_inline)) {
-        nfull = (int)(tb.a[cq].K / BK);
-        nd = RAGGED ? (int)((tb.a[cq].K + BK - 1) / BK) : nfull;
-        next = tb.a[cq].Xext != nullptr ? tb.a[cq].ext_ld / BK : 0;
+        nfull = (int)(item(cq).K / BK);
+        nd = RAGGED ? (int)((item(cq).K + BK - 1) / BK) : nfull;
+        next = item(cq).Xext != nullptr ? item(cq).ext_ld / BK : 0;
         npipe = nd + (PHASES == 1 ? next : 0);
-        if (RAGGED) ktail = (int)(tb.a[cq].K % BK);
-        if (LISTS) { l_ext = tb.a[cq].ext_ld; l_ldx = (int)tb.a[cq].ldx; l_ldw = (int)tb.a[cq].ldw; }
+        if (RAGGED && LISTS) ktail = (int)(item(cq).K % BK);
+        if (LISTS) { l_ext = item(cq).ext_ld; l_ldx = (int)item(cq).ldx; l_ldw = (int)item(cq).ldw; }
     };
     count_slices();
     typedef __attribute__((address_space(3))) void* lptr_t;
@@ -324,13 +337,13 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
         const int64_t row = m0 + wb * (128 + hm) + J * 16 + lc;
         const int64_t colw = n0 + wa * (128 + hn) + lg * 16;
         if (T_F32) {
-            const uint4* src = reinterpret_cast<const uint4*>(reinterpret_cast<const float*>(tb.a[cq].target) + row * tb.a[cq].ldt + colw);
+            const uint4* src = reinterpret_cast<const uint4*>(reinterpret_cast<const float*>(item(cq).target) + row * item(cq).ldt + colw);
 #pragma clang loop unroll(full)
             for (int i4 = 0; i4 < 2; ++i4)
 #pragma clang loop unroll(full)
                 for (int q = 0; q < 4; ++q) traw[(J & 3) * 8 + i4 * 4 + q] = RAGGED ? load16_any(src + i4 * 16 + q) : src[i4 * 16 + q];
         } else {
-            const uint4* src = reinterpret_cast<const uint4*>(reinterpret_cast<const bf16_t*>(tb.a[cq].target) + row * tb.a[cq].ldt + colw);
+            const uint4* src = reinterpret_cast<const uint4*>(reinterpret_cast<const bf16_t*>(item(cq).target) + row * item(cq).ldt + colw);
 #pragma clang loop unroll(full)
             for (int i4 = 0; i4 < 2; ++i4)
 #pragma clang loop unroll(full)
@@ -455,7 +468,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
         uint32_t bytes = 0xFFFFFFFFu;
         if constexpr (RAGGED) {
             const bool last = kt == nfull && kt < nd;        // the slice that d_in does not fill
-            const int past = (last && chunk0 * 8 >= ktail) ? kPastEnd : 0;
+            const int past = !LISTS ? (last ? tail_off : 0) : (last && chunk0 * 8 >= ktail) ? kPastEnd : 0;
             svx += past;   svw += past;
             bytes = last ? (uint32_t)kPastEnd : bytes;
         }
@@ -544,8 +557,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
         part[0][0] = 0.0;
         if (HALVES) part[0][1] = part[1][0] = part[1][1] = 0.0;
         if constexpr (PHASES == 1) settle();
-        const int rs = RAGGED ? (int)(tm * BT - m0) - wb * (HALVES ? hm : BT / 2) : 0;
-        const int cs0 = RAGGED ? (int)(tn * BT - n0) : 0, cs = cs0 - wa * (HALVES ? hn : BT / 2);
+        const int rs = RAGGED ? (int)(tm * BT - m0) - (HALVES ? wb * hm : 0) : 0;
+        const int cs0 = RAGGED ? (int)(tn * BT - n0) : 0, cs = cs0 - (HALVES ? wa * hn : 0);
         auto sum = [&](auto WIDE) __attribute__((always_inline)) {
             constexpr bool wide = decltype(WIDE)::value != 0;
 #pragma clang loop unroll(full)
@@ -554,9 +567,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
                 // the first of the lane's 16 columns per group that counts
                 int from[2] = {0, 0};
                 if (RAGGED) {
-                    const bool in = J * 16 + lc >= rs;
-                    from[0] = in ? cs - lg * 16 : 16;
-                    from[1] = in ? cs - (64 + lg * 16) : 16;
+                    const bool in = (HALVES ? 0 : wb * 128) + J * 16 + lc >= rs;
+                    from[0] = in ? cs - ((HALVES ? 0 : wa * 128) + lg * 16) : 16;
+                    from[1] = in ? cs - ((HALVES ? 0 : wa * 128) + 64 + lg * 16) : 16;
                     // (or the compiler works out all conditions ahead and keeps them)
                     asm volatile("" : "+v"(from[0]), "+v"(from[1]));
                 }
@@ -581,7 +594,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
                 }
             }
         };
-        if (RAGGED && (((LISTS && tb.a[cq].sub ? cs : cs0 | (HALVES ? cs0 - hn : 0)) & 15) != 0 || !tb.a[cq].vec_ok)) sum(IC<1>{});
+        if (RAGGED && (((LISTS && item(cq).sub ? cs : cs0 | (HALVES ? cs0 - hn : 0)) & 15) != 0 || !item(cq).vec_ok)) sum(IC<1>{});
         else sum(IC<0>{});
     };
     // of one problem's tile
@@ -616,7 +629,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
     auto evaluate = [&](int phase, double* red) __attribute__((always_inline)) {
         double part[2][2];
         eval_sum(part);
-        eval_finish(part, tb.a[cq], phase, tm, tn, red);
+        eval_finish(part, item(cq), phase, tm, tn, red);
     };
 
     // accumulators <- minus the target tile (squared error) or zero (stored output)
@@ -727,7 +740,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
                 for (int n = 0; n < 8; ++n) {
                     const int t = 4 * n + (lane >> 4);
                     const uint4 v = *reinterpret_cast<const uint4*>(stg + t * 256 + ((cc ^ (t & 15)) << 4));
-                    bf16_t* dst = reinterpret_cast<bf16_t*>(tb.a[cq].Y) + (m0 + wb * 128 + r2 * 32 + t) * tb.a[cq].ldy + n0 + wa * 128 + cc * 8;
+                    bf16_t* dst = reinterpret_cast<bf16_t*>(item(cq).Y) + (m0 + wb * 128 + r2 * 32 + t) * item(cq).ldy + n0 + wa * 128 + cc * 8;
                     if (RAGGED) store16_any(dst, v);
                     else *reinterpret_cast<uint4*>(dst) = v;
                 }
@@ -746,7 +759,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
             auto statistics = [&](int J, auto SKIP) __attribute__((always_inline)) {
                 constexpr bool skip = decltype(SKIP)::value != 0;
                 const int64_t row = m0 + wb * 128 + J * 16 + lc;
-                const int tgt = tb.a[cq].ce_target[row];
+                const int tgt = item(cq).ce_target[row];
                 // (the block's 32 values leave the accumulation registers once, for the maximum, the exponentials and the target)
                 float y[8][4];
                 float mx = -INFINITY;
@@ -772,7 +785,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
                 sm += __shfl_xor(sm, 16);
                 sm += __shfl_xor(sm, 32);
                 const int64_t chunk = tn * 2 + wa;           // of tiles_n x 2 chunks per token
-                if (lg == 0) tb.a[cq].ce_ms[chunk * tb.a[cq].M + row] = make_float2(mx, sm);
+                if (lg == 0) item(cq).ce_ms[chunk * item(cq).M + row] = make_float2(mx, sm);
                 // the target's logit: one token in d_out / 128 has its target among the wave's columns, so most waves have none in
                 // the block's sixteen, and nothing to look for (looked for along with the maximum it was two instructions a logit)
                 const int64_t trel = (int64_t)tgt - (n0 + wa * 128);
@@ -785,7 +798,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
 #pragma clang loop unroll(full)
                         for (int e = 0; e < 4; ++e)
                             if (grp == (I >> 2) && at == 4 * (I & 3) + e) tl = y[I][e];
-                    if (mine) tb.a[cq].ce_tl[row] = tl;
+                    if (mine) item(cq).ce_tl[row] = tl;
                 }
             };
             auto tile_statistics = [&](auto SKIP) __attribute__((always_inline)) {
@@ -815,7 +828,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
             } else {
                 eval_sum(part);
             }
-            eval_finish(part, tb.a[q_done], 0, tm_done, tn_done, reinterpret_cast<double*>(smem + W_BASE + ((wst == 0) ? 2 : wst - 1) * TILE_BYTES));
+            eval_finish(part, item(q_done), 0, tm_done, tn_done, reinterpret_cast<double*>(smem + W_BASE + ((wst == 0) ? 2 : wst - 1) * TILE_BYTES));
             if (!more) break;
         } else {
             // shared forward: one tile per workgroup.  All LDS stages are free once the re-fetched slices have landed: the
@@ -829,8 +842,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
                 for (int q = 0; q < 16; ++q) {
                     const int t = q >> 1;
                     char* dst = smem + buf * TILE_BYTES + wave * 1024 + t * 4096 + ((q & 1) ? W_BASE : X_BASE);
-                    if (q & 1) __builtin_amdgcn_raw_ptr_buffer_load_lds(rws, (lptr_t)dst, 16, vw2 + (t >> 1) * (2 * gs2) + (t & 1) * (gs2 >> 2) + (HALVES && t >= 4 ? hn * (gs2 / 32) : 0), e * (BK * 2), 0, 0);
-                    else __builtin_amdgcn_raw_ptr_buffer_load_lds(rx2, (lptr_t)dst, 16, vx2 + t * gs2 + (HALVES && t >= 4 ? hm * (gs2 / 32) : 0), e * (BK * 2), 0, 0);
+                    if (q & 1) __builtin_amdgcn_raw_ptr_buffer_load_lds(rws, (lptr_t)dst, 16, vw2 + (t >> 1) * (2 * gs2) + (t & 1) * (gs2 >> 2), e * (BK * 2), 0, 0);
+                    else __builtin_amdgcn_raw_ptr_buffer_load_lds(rx2, (lptr_t)dst, 16, vx2 + t * gs2, e * (BK * 2), 0, 0);
                 }
             };
             if (next > 0) ext_dma(rw2, 0, 0);
@@ -873,7 +886,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_aligned_kernel(const AlignedArg
         next_sources(it + 2);
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);                      // the slices fetched past the end of the list
-    if (!LISTS && tb.a[cq].clk && wgid == 0 && tid == 0) { tb.a[cq].clk[2] = __builtin_readcyclecounter(); tb.a[cq].clk[3] = wall_clock64(); }
+    if (!LISTS && item(cq).clk && wgid == 0 && tid == 0) { item(cq).clk[2] = __builtin_readcyclecounter(); item(cq).clk[3] = wall_clock64(); }
 }
 
 template <int OUT, bool T_F32, int PHASES, bool RAGGED, int CAP>

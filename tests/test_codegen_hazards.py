@@ -119,16 +119,21 @@ def barrier_faults(body, succ):
 
 
 @pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
+def assembly(tmp_path_factory):
     d = tmp_path_factory.mktemp("asm")
 
     def one(src):
         out = os.path.join(str(d), src.replace(".hip", ".s"))
         subprocess.run([B.HIPCC] + B.FLAGS + ["-S", "--cuda-device-only", os.path.join(B.CSRC, src), "-o", out], check=True, capture_output=True)
         with open(out) as f:
-            return functions(f.read())
+            return f.read()
     with concurrent.futures.ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
         return dict(zip(SOURCES, ex.map(one, SOURCES)))
+
+
+@pytest.fixture(scope="module")
+def kernels(assembly):
+    return {src: functions(text) for src, text in assembly.items()}
 
 
 @pytest.mark.parametrize("src", SOURCES)
@@ -159,6 +164,17 @@ def test_accumulators_stay_in_place(kernels):
         found += 1
         assert not [ins.text for l in inner for ins in l if ins.op.startswith("v_accvgpr")], name
     assert found == 12
+
+
+def test_registers_of_the_persistent_kernel(assembly):
+    """What the forms of gemm_bf16_aligned_kernel<OUT, T_F32, PHASES, RAGGED, CAP> spill: nothing for one evaluation, but for half an fp32
+    tile of a ragged layer, whose 128 registers wait beside the next tile's first fragments"""
+    limit = {("0", "1", "1", "1"): 118, ("0", "0", "3", "0"): 16, ("0", "1", "3", "0"): 16, ("0", "0", "3", "1"): 90, ("0", "1", "3", "1"): 90}
+    found = re.findall(r"\.name:\s+\S*gemm_bf16_aligned_kernelILi(\d)ELb(\d)ELi(\d)ELb(\d)ELi\d+E\S*$.*?\.vgpr_spill_count:\s+(\d+)", assembly["gemm_bf16_aligned.hip"],
+                       re.M | re.S)
+    assert len(found) == 18
+    for *form, spilled in found:
+        assert int(spilled) <= limit.get(tuple(form), 0), (form, spilled)
 
 
 def test_the_walk_finds_planted_faults():
