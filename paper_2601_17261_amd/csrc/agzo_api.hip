@@ -581,10 +581,8 @@ int op_basis(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* X, i
     }
 }
 
-// whether the launches that project a job's activations write its extension operands too (timed: they are part of each forward's time)
-bool projects_ext(agzo_ctx* ctx, const agzo_layer& L) { return L.dtype == AGZO_BF16 && !timed(ctx, AGZO_PROF_GEMM); }
 // P = X B for every job (one launch per kBatchMax jobs of a dtype and padded rank, and one behind it), behind basis_many_impl.  ext: the
-// jobs' W sides (read where projects_ext())
+// W sides of the jobs' extension operands, which the same launches write with the X sides (ext_ws = NULL: neither)
 int project_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, const std::vector<GemmExtArgs>& ext, bool half_cu) {
     std::vector<char> done(jobs.size(), 0);
     for (size_t a = 0; a < jobs.size(); ++a) {
@@ -609,8 +607,8 @@ int project_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, const std::ve
             if (done[b] || j.L.dtype != AGZO_BF16 || j.p.rp != ja.p.rp) continue;
             q[n++] = XqArgs{static_cast<const bf16_t*>(j.X), j.L.ldx, j.L.n_tokens, j.L.d_in, wsh(ctx, j.p.off_pack), j.L.r, j.p.rp,
                             wsf(ctx, j.p.off_T), nullptr, j.p.m_pad, wsf(ctx, j.p.off_xqpart), nullptr, j.B};
-            if (projects_ext(ctx, j.L)) {
-                q[n - 1].Xext = wsh(ctx, j.p.off_ext);
+            if (ext[b].ext_ws) {
+                q[n - 1].Xext = static_cast<bf16_t*>(ext[b].ext_ws);
                 q[n - 1].ext = &ext[b];
             }
             done[b] = 1;
@@ -1100,6 +1098,19 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
     hipStream_t st = ctx->stream;
     Fork<HipApi> beside(st, ctx->side, ctx->fork, ctx->join);
     bool half_cu = false;          // forwards on the other stream hold half of every compute unit
+    // the Gaussian factors with the coefficients of both perturbed evaluations (shared: what each of them adds), where the forwards read
+    // them from operands that the projection has written (timed: each forward prepares its own, inside its time)
+    std::vector<GemmExtArgs> sides((size_t)n);
+    for (int m = 0; m < n; ++m) {
+        const agzo_step_item& it = items[m];
+        const LayerJob& j = jobs[(size_t)m];
+        if (j.L.dtype != AGZO_BF16 || timed(ctx, AGZO_PROF_GEMM)) continue;
+        GemmLossArgs la;
+        la.kind = it.loss.kind;
+        const GemmBf16Args f = forward_bf16_args(ctx, j.L, j.p, it.W, it.X, wsf(ctx, j.p.off_T), eps, it.seed, nullptr, la, shared);
+        if (gemm_bf16_reads_ext(f))
+            sides[(size_t)m] = GemmExtArgs{f.ext_ws, f.M, f.N, nullptr, f.r, eps, shared ? -2.f * eps : -eps, shared || !one_sided, it.seed};
+    }
 
     // the squared-error evaluations of phases [ph0, ph1): 0 = f0 (or, shared, all three from one pass), 1 = f+, 2 = f-; the
     // loss partials of phase ph go to slot ph of the layer's region
@@ -1115,8 +1126,7 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
             GemmLossArgs la;
             la.kind = AGZO_LOSS_MSE; la.target_dtype = it.loss.target_dtype; la.target = it.loss.target; la.ldt = it.loss.ldt;
             const float* P = perturbed ? wsf(ctx, j.p.off_T) : nullptr;
-            // the projection has written all operands (timed: each forward its own, inside its time)
-            const bool ready = perturbed && projects_ext(ctx, j.L);
+            const bool ready = perturbed && sides[(size_t)m].ext_ws;
             for (int ph = ph0; ph < ph1; ++ph) {
                 la.partials = reinterpret_cast<double*>(ctx->ws + j.p.off_part) + (size_t)ph * j.p.n_part;
                 const float e = ph == 2 ? -eps : eps;
@@ -1154,7 +1164,7 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
         const agzo_step_item& it = items[m];
         if (it.loss.kind != AGZO_LOSS_CE) return 0;
         const LayerJob& j = jobs[(size_t)m];
-        return op_forward(ctx, j.L, j.p, it.W, it.X, P, e, it.seed, nullptr, &it.loss, dst, sh, slot, false, false, P && projects_ext(ctx, j.L), slot == 2 ? 1 : 0);
+        return op_forward(ctx, j.L, j.p, it.W, it.X, P, e, it.seed, nullptr, &it.loss, dst, sh, slot, false, false, P && sides[(size_t)m].ext_ws, slot == 2 ? 1 : 0);
     };
     // Alg. 2, part 1: the base forward of every layer, and every layer's basis from the same activations
     if (!shared) {
@@ -1163,12 +1173,6 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
     }
     TRY(basis_many_impl(ctx, jobs, K, flags & AGZO_INIT_FEATURE, half_cu));
     // parts 2-3: the perturbed evaluations
-    // the Gaussian factors with the coefficients of both perturbed evaluations (shared: what each of them adds)
-    std::vector<GemmExtArgs> sides((size_t)n);
-    for (int m = 0; m < n; ++m) {
-        const LayerJob& j = jobs[(size_t)m];
-        sides[(size_t)m] = GemmExtArgs{ctx->ws + j.p.off_ext, j.L.n_tokens, j.L.d_out, nullptr, j.L.r, eps, shared ? -2.f * eps : -eps, shared || !one_sided, items[m].seed};
-    }
     TRY(project_many(ctx, jobs, sides, half_cu));
     if (shared) TRY(forward_mse(0, 1));
     else TRY(forward_mse(1, one_sided ? 2 : 3));

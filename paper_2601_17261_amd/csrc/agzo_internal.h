@@ -193,6 +193,8 @@ bool gemm_bf16_fuses_sketch(int64_t M, int64_t N, int r, bool large_tiles);
 inline int64_t gemm_bf16_sketch_mpad(int64_t M) { return (M + 127) / 128 * 128; }
 inline int gemm_bf16_sketch_splits(int64_t M) { return (int)((M + 127) / 128); }
 hipError_t launch_gemm_bf16(const GemmBf16Args& a, hipStream_t st);
+// whether a perturbed forward multiplies prepared operands (in the shared schedule only the persistent kernel does; the others work from P)
+bool gemm_bf16_reads_ext(const GemmBf16Args& a);
 // several independent forwards: the squared errors that the kernel of gemm_bf16_mid.hip takes share launches, the others run one by
 // one.  Every result has the bits of a launch of its own.  Workspaces (ext_ws unless ext_ready, loss partials) must not overlap.
 // half_cu: those that share launches in 128 x 128 tiles leave half of every compute unit to what runs on other streams

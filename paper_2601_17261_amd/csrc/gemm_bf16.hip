@@ -624,6 +624,15 @@ struct Choice {
     bool prep;          // the extension operands still have to be written
 };
 
+bool takes_small(const GemmBf16Args& a) { return small_shape(a.M, a.N) && !a.large_tiles && !a.shared && a.loss.kind != AGZO_LOSS_CE; }
+// the persistent kernel of gemm_bf16_aligned.hip: squared error without a stored Y (also in shared-forward mode), the
+// cross-entropy statistics without a stored Y, or a stored bf16 Y without a loss, where a tile fits into the layer
+bool takes_persistent(const GemmBf16Args& a) {
+    return !takes_small(a) && a.M >= BT && a.N >= BT && a.K >= 2 * BK && (!a.P || a.ext_ws) &&
+           ((a.loss.kind == AGZO_LOSS_MSE && !a.Y) || (a.loss.kind == AGZO_LOSS_CE && !a.Y && !a.shared) ||
+            (a.loss.kind == AGZO_LOSS_NONE && a.Y && a.y_dtype == AGZO_BF16 && !a.shared));
+}
+
 hipError_t choose(const GemmBf16Args& a, Choice& c) {
     GemmParams& p = c.p;
     p.X = a.X; p.ldx = a.ldx; p.W = a.W; p.ldw = a.ldw;
@@ -649,15 +658,10 @@ hipError_t choose(const GemmBf16Args& a, Choice& c) {
     p.ce_tl = a.loss.ce_tl;
     p.clk = a.clk;
     p.sk_T = a.sk_T; p.sk_mpad = a.sk_T ? a.sk_mpad : 0; p.sk_partial = a.sk_T ? a.sk_partial : nullptr;
-    const bool small = small_shape(a.M, a.N) && !a.large_tiles && !a.shared && p.loss_kind != AGZO_LOSS_CE;
-    // the persistent kernel of gemm_bf16_aligned.hip: squared error without a stored Y (also in shared-forward mode), the
-    // cross-entropy statistics without a stored Y, or a stored bf16 Y without a loss, where a tile fits into the layer
-    const bool persistent = !small && a.M >= BT && a.N >= BT && a.K >= 2 * BK && (!a.P || a.ext_ws) &&
-                            ((a.loss.kind == AGZO_LOSS_MSE && !a.Y) || (a.loss.kind == AGZO_LOSS_CE && !a.Y && !a.shared) ||
-                             (a.loss.kind == AGZO_LOSS_NONE && a.Y && a.y_dtype == AGZO_BF16 && !a.shared));
+    const bool small = takes_small(a), persistent = takes_persistent(a);
     p.Xext = nullptr; p.Wext = nullptr; p.Wext2 = nullptr; p.ext_ld = 0;
     c.prep = false;
-    if (a.P && a.ext_ws && (!a.shared || persistent)) {
+    if (a.P && gemm_bf16_reads_ext(a)) {
         p.ext_ld = gemm_bf16_ext_width(a.r);
         bf16_t* xe = static_cast<bf16_t*>(a.ext_ws);
         bf16_t* we = xe + a.M * p.ext_ld;
@@ -704,6 +708,8 @@ hipError_t launch_one(const Choice& c, hipStream_t st) {
     return ce ? launch_variant<2, 2, false, 1>(p, st) : launch_variant<2, 2, false, 0>(p, st);
 }
 }  // namespace
+
+bool gemm_bf16_reads_ext(const GemmBf16Args& a) { return a.ext_ws && (!a.shared || takes_persistent(a)); }
 
 hipError_t launch_gemm_bf16_many(const GemmBf16Args* a, int n, bool half_cu, hipStream_t st) {
     Choice c[kBatchMax];

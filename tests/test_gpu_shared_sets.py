@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 import torch
 
+from launches import kernels
 from oracle import agzo as oagzo
 from paper_2601_17261_amd import binding, synth
 
@@ -41,3 +42,27 @@ def test_layers_share_a_launch(count):
         assert abs(got[3] - o["g"]) < 2e-2 * abs(o["g"]) + 1e-7 * o["L0"] / EPS, (i, got[3], o["g"])
     ctx.check()
     assert torch.equal(out[0], out[1])
+
+
+# a head; layers short of a tile in each direction; one that the persistent kernel takes
+@pytest.mark.parametrize("n,d_out,d_in,r,ce,reads", [(300, 1000, 264, 1, True, False), (700, 4000, 512, 16, True, False), (200, 512, 2048, 16, False, False), (512, 200, 512, 1, False, False),
+                                                     (512, 512, 64, 40, False, False), (512, 512, 128, 16, False, True), (257, 769, 1024, 1, False, True)])
+def test_operands_are_made_where_a_forward_reads_them(n, d_out, d_in, r, ce, reads):
+    stream = torch.cuda.Stream()
+    ctx = binding.Context(stream=stream)
+    w, x = (torch.randn(s, device="cuda").bfloat16() for s in ((d_out, d_in), (n, d_in)))
+    t = torch.randint(0, d_out, (n,), device="cuda", dtype=torch.int32) if ce else torch.randn(n, d_out, device="cuda").bfloat16()
+    out = torch.zeros(4, dtype=torch.float64, device="cuda")
+    item = (binding.make_layer(w, x, r), w, x, binding.make_loss(t, kind=binding.LOSS_CE if ce else binding.LOSS_MSE), 3, out, None)
+    torch.cuda.synchronize()
+
+    def call():
+        ctx.step_many([item], 1, EPS, LR, binding.SHARED_FORWARD)
+    with torch.cuda.stream(stream):
+        call()
+        stream.synchronize()
+    names, _ = kernels(stream, call)
+    assert any("_ext_kernel" in name or "ext_prep" in name for name in names) == reads, names
+    ctx.check()
+    assert torch.isfinite(out).all()
+    ctx.close()
