@@ -65,9 +65,12 @@ __device__ __forceinline__ float philox_uniform(uint32_t x, float scale) {
 }
 
 // sqrt(-2 ln u), the generator being bound by its instructions: u is never 0, subnormal or 1, so that the logarithm is the
-// hardware's times -2 ln 2 in two parts (the first cut, not rounded, to 24 bits) and the root comes from the reciprocal one and
-// its residual, without the scaling and the special values of logf and sqrtf.  The same bits as sqrtf(-2.0f * logf(u)) for all
-// 2^23 values of u (compared on the card, one by one); 50 instructions a value with the counter's, not 59: 2^28 normals 326 -> 303 us.
+// hardware's times -2 ln 2 and the root comes from the reciprocal one and its residual, without the scaling and the special values of
+// logf and sqrtf.  The same bits as sqrtf(-2.0f * logf(u)) for all 2^23 values of u (test_gpu_generator.py), because a seed stands for
+// its weights: another rounding of G changes every seeded update.  So the order of the logarithm's steps is the one to which the
+// compiler contracts logf: hi is -2 ln 2 cut to 24 bits and lo its rest, and the rounding of l * hi is added to a product that fmaf does not
+// round, that is twice (up to 1.07e-7 of t over all u, 6.0e-8 with fmaf(l, hi, l * lo), which is two instructions less and other
+// bits).  50 instructions a value with the counter's, not 59: 2^28 normals 326 -> 303 us.
 __device__ __forceinline__ float box_muller_radius(uint32_t x) {
     constexpr float hi = -2.0f * 0x1.62e42ep-1f, lo = -2.0f * 0x1.efa39ep-25f;
     const float l = __builtin_amdgcn_logf(philox_uniform(x, 1.0f));
