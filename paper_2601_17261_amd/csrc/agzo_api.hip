@@ -922,8 +922,8 @@ int agzo_perturbed_forward(agzo_ctx* ctx, const agzo_layer* L, const void* W, co
         }
         return op_forward(ctx, *L, p, W, X, P, eps_signed, seed, Y, loss, loss_dev);
     }
-    // the projection writes the X side of the extension operands; up to 16 columns need no planes of B and share a launch with the W
-    // side, for more the planes and the W side are a launch ahead
+    // the projection writes the X side of the extension operands; where it multiplies the fp32 basis itself (xq_narrow(), xq_ext_ok()) it needs
+    // no planes of B and shares a launch with the W side, else the planes and the W side are a launch ahead
     q.T = nullptr;
     q.Xext = wsh(ctx, p.off_ext);
     GemmExtArgs ext{ctx->ws + p.off_ext, L->n_tokens, L->d_out, nullptr, L->r, eps_signed, 0.f, false, seed, B, wsh(ctx, p.off_pack), L->d_in};
