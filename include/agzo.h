@@ -113,7 +113,8 @@ int agzo_check(agzo_ctx* ctx);
  * is selected every bf16 forward is timed by itself, together with the preparation of its rank-r operands; otherwise forwards of
  * several layers, and their preparations, share launches.  While any class is selected a set of layers runs in one stream, without
  * its base forwards beside the extraction.  AGZO_PROF_XQ contains the Gaussian factor's preparation where a projection shares its
- * launch (steps; agzo_perturbed_forward for up to 16 columns, but for wide layers of few tokens), unless AGZO_PROF_GEMM is selected too.  The results are the same bits. */
+ * launch (steps; agzo_perturbed_forward for up to 16 columns and 8192 tokens, but for wide layers of few tokens), unless AGZO_PROF_GEMM is
+ * selected too.  The results are the same bits. */
 enum { AGZO_PROF_GEMM = 0, AGZO_PROF_UPDATE = 1, AGZO_PROF_XQ = 2, AGZO_PROF_XTT = 3, AGZO_PROF_QR = 4,
        AGZO_PROF_FILL = 5, AGZO_PROF_KINDS = 6, AGZO_PROF_ALL = 63 };
 int agzo_profile_enable(agzo_ctx* ctx, int32_t mask);
