@@ -167,7 +167,7 @@ Plan make_plan(const agzo_layer& L, bool need_ybuf, bool ce = false, bool shared
 // with the scratch of a lone stored output (the forwards that a model makes layer by layer)
 Plan make_forward_plan(const agzo_layer& L, bool need_ybuf, bool ce, bool fused_sketch, bool stored) {
     Plan p = make_plan(L, need_ybuf, ce, false, 0, fused_sketch);
-    const size_t split = (stored && L.dtype == AGZO_BF16 && L.y_dtype == AGZO_BF16) ? gemm_bf16_split_bytes(L.n_tokens, L.d_out, L.d_in) : 0;
+    const size_t split = (stored && L.dtype == AGZO_BF16 && L.y_dtype == AGZO_BF16) ? gemm_bf16_split_bytes(L.n_tokens, L.d_out, L.d_in, fused_sketch) : 0;
     if (split) {
         p.off_split = p.total;
         p.total += align_up(split);

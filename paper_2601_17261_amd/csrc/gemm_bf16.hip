@@ -613,12 +613,12 @@ static hipError_t launch_variant(const GemmParams& p, hipStream_t st) {
 }
 
 namespace {
-enum class Kernel { small, mid, aligned, general };
+enum class Kernel { small, few, mid, aligned, general };
 
 // what a forward needs at its launch, and the kernel that takes it (by its own shape and operands alone)
 struct Choice {
     GemmParams p;
-    GemmItem g;         // mid
+    GemmItem g;         // mid, few
     int out;            // mid: 0 squared error, 1 stored bf16 output
     Kernel kernel;
     bool prep;          // the extension operands still have to be written
@@ -692,6 +692,7 @@ hipError_t choose(const GemmBf16Args& a, Choice& c) {
     c.out = (p.Y && p.loss_kind == AGZO_LOSS_NONE && p.y_dtype == AGZO_BF16) ? 1 : (!p.Y && p.loss_kind == AGZO_LOSS_MSE) ? 0 : -1;
     // one output or one loss and tiles that lie inside the layer: the pipelined kernel
     c.kernel = (c.out >= 0 && gemm_bf16_mid_ok(g, c.out)) ? Kernel::mid : Kernel::small;
+    if (c.kernel == Kernel::mid && c.out == 1 && !g.sk_T && gemm_bf16_few_shape(p.M, p.N, p.K)) c.kernel = Kernel::few;
     return hipSuccess;
 }
 
@@ -699,6 +700,7 @@ hipError_t launch_one(const Choice& c, hipStream_t st) {
     const GemmParams& p = c.p;
     switch (c.kernel) {
         case Kernel::mid: return launch_gemm_bf16_mid(&c.g, 1, c.out, p.target_dtype != AGZO_BF16, false, st);
+        case Kernel::few: return launch_gemm_bf16_few(c.g, st);
         case Kernel::small: return launch_gemm_bf16_small(p, st);
         case Kernel::aligned: return launch_gemm_bf16_aligned(p, st);
         case Kernel::general: break;

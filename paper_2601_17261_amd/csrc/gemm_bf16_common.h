@@ -1,6 +1,6 @@
 // Shared between the kernels of the bf16 forward GEMM: launch parameters and the LDS tile layout.  256 x 256 tiles for shapes that
 // fill the chip with them (gemm_bf16_aligned.hip; gemm_bf16.hip for what that one has no output form for or does not fit into a layer),
-// 128 x 128 tiles for the others (gemm_bf16_mid.hip; gemm_bf16_small.hip likewise).
+// 128 x 128 tiles for the others (gemm_bf16_mid.hip; gemm_bf16_small.hip likewise), 64 x 64 ones for stored outputs of few of these (gemm_bf16_few.hip).
 #pragma once
 #include "agzo_internal.h"
 
@@ -83,12 +83,19 @@ struct GemmItem {
     unsigned long long* clk;
     // out 1 in a launch of one problem: so many shares of the slices, their sums in part (gemm_bf16_split_bytes(); NULL: one share)
     int splits; float* part;
+    int fold, pairs;                                       // (set by the launch: shares summed as gemm_bf16_few.hip does)
 };
 int gemm_bf16_mid_splits(int64_t M, int64_t N, int64_t K);
 // out 0: squared error (target_f32: of fp32 targets), 1: stored bf16 output (one problem a launch)
 bool gemm_bf16_mid_ok(const GemmItem& g, int out);
 // half_cu (out 0): at most one workgroup to a compute unit, and 72 KiB of its LDS left
 hipError_t launch_gemm_bf16_mid(const GemmItem* a, int n, int out, bool target_f32, bool half_cu, hipStream_t st);
+
+// 64 x 64 tiles whose waves share d_in, for the stored outputs of few tiles (gemm_bf16_few.hip).  Sums over d_in in kFewShares shares,
+// slices nd i / kFewShares to nd (i + 1) / kFewShares, which are added in pairs
+constexpr int kFewShares = 4;
+bool gemm_bf16_few_shape(int64_t M, int64_t N, int64_t K);
+hipError_t launch_gemm_bf16_few(const GemmItem& a, hipStream_t st);
 
 // persistent kernel in 256 x 256 tiles (gemm_bf16_aligned.hip): M, N >= 256, d_in >= 128, the rank-r term as prepared operands;
 // either the squared-error loss without a stored Y, the cross-entropy statistics without a stored Y, or a bf16 Y without a loss

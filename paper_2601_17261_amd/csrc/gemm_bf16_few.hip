@@ -1,0 +1,198 @@
+// Forward GEMM of the bf16 path in 64 x 64 tiles whose four waves share d_in, for stored outputs of few tiles and no deep d_in:
+//     Y = X W^T (+ eps (X B) G^T) as bf16, tokens and outputs of at least 128, the rank-r term as prepared operands
+//
+// A program calls the layers of a model one by one, and few tokens leave such a launch a few dozen 128 x 128 tiles, whose time is latency:
+// a chain of slices with a barrier each, or shares of d_in that meet in memory and a second launch that adds them.  Here a wave has the
+// whole tile and a quarter of d_in, in a ring of its own that only it fills and reads: nothing in the loop over slices waits for
+// another wave.  A slice's fragments go to registers, then its slot is requested again, then they are multiplied.  The four sums meet
+// in LDS at the end.  Bound by what a compute unit takes in, some 85 GB/s of direct loads (16 KiB a slice): eight waves of one slot
+// each, loads spread between the matrix instructions and fragments read by hand take the same time.
+// us, weights from memory, 128 x 128 tiles (with the launch that adds their shares) and this kernel: 385 tokens of 2048 -> 2048
+// 18.2 and 9.2, -> 1024 14.0 and 8.8; 1000 of 2048 -> 1024 17.3 and 9.2, -> 2048 (two workgroups to a compute unit) 18.4 and 14.9; 432 of
+// 1024 -> 1024 11.5 and 6.4; 128 of 256 -> 256 5.5 and 4.0.  A decoder's step on 385 tokens: 1606 and 1493
+//
+// Rows, columns and a last slice that do not fill a tile as in gemm_bf16_mid.hip: the last tile of a direction starts at the last 64
+// rows, lanes past d_in load zeros.
+#include "gemm_bf16_common.h"
+
+namespace agzo {
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+constexpr int FT = 64;                              // tile edge
+constexpr int FSLOT = 2 * FT * BK * 2;              // a slice of both operands: 16 KiB, X rows first
+constexpr int WAVES = kFewShares;
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t few_rsrc(const bf16_t* base, uint32_t bytes = 0xFFFFFFFFu) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, (int)bytes, 0x00020000);
+}
+
+template <int STAGES>
+__device__ __forceinline__ void few_body(const GemmItem& p) {
+    extern __shared__ __align__(16) char smem[];
+    typedef __attribute__((address_space(3))) void* lptr_t;
+    const int tid = threadIdx.x, lane = tid & 63;
+    if (p.clk && blockIdx.x == 0 && tid == 0) { p.clk[0] = __builtin_readcyclecounter(); p.clk[1] = wall_clock64(); }
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lc = lane & 15, lg = lane >> 4;
+
+    // workgroup -> tile, as in gemm_bf16_mid.hip: each XCD takes a contiguous run of tiles, in bands of eight token tiles
+    const int tiles = p.tiles_m * p.tiles_n, per = tiles / 8;
+    int lin = (int)blockIdx.x;
+    if (lin < per * 8) lin = (lin % 8) * per + lin / 8;
+    constexpr int BAND = 8;
+    const int band = lin / (BAND * p.tiles_n), first = band * BAND;
+    const int rows = min(BAND, p.tiles_m - first), in_band = lin - band * BAND * p.tiles_n;
+    const int tm = __builtin_amdgcn_readfirstlane(first + in_band % rows), tn = __builtin_amdgcn_readfirstlane(in_band / rows);
+    const int64_t m0 = min((int64_t)tm * FT, p.M - FT), n0 = min((int64_t)tn * FT, p.N - FT);
+
+    // this wave's slices: its share of d_in's, the last wave's with the extension behind them
+    const int nd_all = (int)((p.K + BK - 1) / BK), nfull = (int)(p.K / BK);
+    const int kbeg = nd_all * wave / WAVES, nd = nd_all * (wave + 1) / WAVES - kbeg;
+    const int n = nd + (p.Xext != nullptr && wave == WAVES - 1 ? p.ext_ld / BK : 0);
+    char* const ring = smem + wave * STAGES * FSLOT;
+
+    // direct load t of an operand: LDS rows 8 t + lane / 8 (of W the permuted ones: a lane then holds 16 consecutive outputs), the
+    // chunks in the swizzled order, which turns by four between even and odd t
+    const int row0 = lane >> 3, chunk0 = (lane & 7) ^ (row0 >> 1);
+    auto w_row = [&](int t) __attribute__((always_inline)) { return (2 * (t & 1) + (row0 >> 2)) * 16 + (t >> 1) * 4 + (row0 & 3); };
+    auto chunk = [&](int t) __attribute__((always_inline)) { return chunk0 ^ (4 * (t & 1)); };
+    __amdgpu_buffer_rsrc_t rx = few_rsrc(p.X + m0 * p.ldx), rw = few_rsrc(p.W + n0 * p.ldw);
+    int vx[8], vw[8], so = 0;
+    auto offsets = [&](int64_t ldx, int64_t ldw) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            vx[t] = (int)(((int64_t)(8 * t + row0) * ldx + chunk(t) * 8) * 2);
+            vw[t] = (int)(((int64_t)w_row(t) * ldw + chunk(t) * 8) * 2);
+        }
+    };
+    offsets(p.ldx, p.ldw);
+    // the source of the wave's slice i
+    auto select = [&](int i) __attribute__((always_inline)) {
+        if (__builtin_expect(i < nd && kbeg + i < nfull, 1)) { so = (kbeg + i) * (BK * 2); return; }
+        if (i < nd) {                               // the slice that d_in does not fill: zeros past it
+            rx = few_rsrc(p.X + m0 * p.ldx, (uint32_t)kPastEnd); rw = few_rsrc(p.W + n0 * p.ldw, (uint32_t)kPastEnd);
+            so = nfull * (BK * 2);
+            const int left = (int)(p.K % BK);
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const int past = chunk(t) * 8 >= left ? kPastEnd : 0;
+                vx[t] += past; vw[t] += past;
+            }
+        } else {
+            rx = few_rsrc(p.Xext + m0 * p.ext_ld); rw = few_rsrc(p.Wext + n0 * p.ext_ld);
+            so = (i - nd) * (BK * 2);
+            offsets(p.ext_ld, p.ext_ld);
+        }
+    };
+    auto dma = [&](char* dst, int q) __attribute__((always_inline)) {
+        if (q < 8) __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lptr_t)(dst + q * 1024), 16, vx[q], so, 0, 0);
+        else __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lptr_t)(dst + q * 1024), 16, vw[q - 8], so, 0, 0);
+    };
+    floatx4 acc[4][4];
+    bf16x8 w[2][4], x[2][4];
+#pragma unroll
+    for (int I = 0; I < 4; ++I)
+#pragma unroll
+        for (int J = 0; J < 4; ++J) acc[I][J] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < STAGES; ++s)
+        if (s < n) {
+            select(s);
+#pragma unroll
+            for (int q = 0; q < 16; ++q) dma(ring + s * FSLOT, q);
+        }
+    const int off[2] = {lds_off(lc, lg), lds_off(lc, 4 + lg)};
+    int slot = 0;
+    for (int i = 0; i < n; ++i) {
+        // the slice has landed; this wave's reads of it are all there before its slot is filled again
+        if (STAGES == 2 && i + 1 < n) __builtin_amdgcn_s_waitcnt(0x4F70);      // vmcnt(16)
+        else __builtin_amdgcn_s_waitcnt(0x0F70);
+        __builtin_amdgcn_sched_barrier(0);
+        char* const at = ring + slot * FSLOT;
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+            for (int I = 0; I < 4; ++I) w[ks][I] = *reinterpret_cast<const bf16x8*>(at + 8192 + off[ks] + I * 2048);
+#pragma unroll
+            for (int J = 0; J < 4; ++J) x[ks][J] = *reinterpret_cast<const bf16x8*>(at + off[ks] + J * 2048);
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);         // lgkmcnt(0)
+        __builtin_amdgcn_sched_barrier(0);
+        if (i + STAGES < n) {
+            select(i + STAGES);
+#pragma unroll
+            for (int q = 0; q < 16; ++q) dma(at, q);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int J = 0; J < 4; ++J)
+#pragma unroll
+                for (int I = 0; I < 4; ++I) acc[I][J] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][I], x[ks][J], acc[I][J], 0, 0, 0);
+        slot = (slot + 1 == STAGES) ? 0 : slot + 1;
+    }
+    // the shares, added in pairs: wave w takes the tokens of block w
+    floatx4* mine = reinterpret_cast<floatx4*>(ring) + lane;
+#pragma unroll
+    for (int J = 0; J < 4; ++J)
+#pragma unroll
+        for (int I = 0; I < 4; ++I) mine[(J * 4 + I) * 64] = acc[I][J];
+    __syncthreads();
+    auto share = [&](int s, int I) __attribute__((always_inline)) { return reinterpret_cast<const floatx4*>(smem + s * STAGES * FSLOT)[(wave * 4 + I) * 64 + lane]; };
+    static_assert(WAVES == 4, "two pairs");
+    floatx4 sum[4];
+#pragma unroll
+    for (int I = 0; I < 4; ++I) sum[I] = (share(0, I) + share(1, I)) + (share(2, I) + share(3, I));
+    uint32_t o[8];
+#pragma unroll
+    for (int I = 0; I < 4; ++I) {
+        o[2 * I] = pack_bf16x2(sum[I][0], sum[I][1]);
+        o[2 * I + 1] = pack_bf16x2(sum[I][2], sum[I][3]);
+    }
+    bf16_t* dst = reinterpret_cast<bf16_t*>(p.Y) + (m0 + wave * 16 + lc) * p.ldy + n0 + lg * 16;
+    store16_any(dst, make_uint4(o[0], o[1], o[2], o[3]));
+    store16_any(dst + 8, make_uint4(o[4], o[5], o[6], o[7]));
+    if (p.clk && blockIdx.x == 0 && tid == 0) { p.clk[2] = __builtin_readcyclecounter(); p.clk[3] = wall_clock64(); }
+}
+
+template <int STAGES>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(STAGES == 1 ? 2 : 1))) void gemm_bf16_few_kernel(const GemmItem p) {
+    few_body<STAGES>(p);
+}
+
+template <int STAGES>
+static hipError_t launch_few(const GemmItem& g, unsigned tiles, hipStream_t st) {
+    constexpr int smem = WAVES * STAGES * FSLOT;
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_bf16_few_kernel<STAGES>), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    hipLaunchKernelGGL((gemm_bf16_few_kernel<STAGES>), dim3(tiles), dim3(64 * WAVES), smem, st, g);
+    return hipGetLastError();
+}
+
+// Up to two workgroups a compute unit, and a d_in that 128 x 128 tiles in shares do not walk as fast, for they take in half the bytes an output.  us,
+// those and this kernel: 2048 -> 1024 outputs 23.5 and 19.5 at d_in = 2560, 28.6 and 26.2 at 4096, 385 -> 2048 18.7 and 12.5, 19.6 and 17.1, but 128 ->
+// 4096 18.8 and 21.1 at 3064, 256 -> 2048 20.0 and 26.8 at 6144; of fewer than 64 tiles, which the shares spread over more compute units, 200 -> 256
+// 11.0 and 11.7 at 2560, 9.6 and 6.7 at 1024.  Rows of X and W that do not start on 128 bytes cost this kernel more (700 -> 2048, 2056:
+// 20.4 and 20.6).  More tiles: 1500 -> 2048, 768 of them, 16.4 and 23.2
+bool gemm_bf16_few_shape(int64_t M, int64_t N, int64_t K) {
+    const int64_t tiles = ((M + FT - 1) / FT) * ((N + FT - 1) / FT);
+    return M >= BT_SMALL && N >= BT_SMALL && tiles <= 512 && K >= WAVES * BK && K <= (tiles >= 64 ? 40 : 32) * BK;
+}
+
+hipError_t launch_gemm_bf16_few(const GemmItem& a, hipStream_t st) {
+    if (!gemm_bf16_few_shape(a.M, a.N, a.K) || !a.Y || a.sk_T) return hipErrorInvalidValue;
+    GemmItem g = a;
+    g.tiles_m = (int)((g.M + FT - 1) / FT);
+    g.tiles_n = (int)((g.N + FT - 1) / FT);
+    const int64_t tiles = (int64_t)g.tiles_m * g.tiles_n;
+    // (two slots a wave and one workgroup to a compute unit, or one slot and two)
+    return tiles <= 256 ? launch_few<2>(g, (unsigned)tiles, st) : launch_few<1>(g, (unsigned)tiles, st);
+}
+
+}  // namespace agzo

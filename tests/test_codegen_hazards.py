@@ -14,7 +14,7 @@ import pytest
 
 from paper_2601_17261_amd import build as B
 
-SOURCES = ["gemm_bf16_aligned.hip", "gemm_bf16_mid.hip", "skinny.hip", "glue.hip", "probe.hip"]
+SOURCES = ["gemm_bf16_aligned.hip", "gemm_bf16_mid.hip", "gemm_bf16_few.hip", "skinny.hip", "glue.hip", "probe.hip"]
 # wait states this compiler keeps on gfx950 around v_mfma_f32_16x16x32_bf16 when it knows the instruction (through the
 # builtin): 8 from the instruction to anything else that reads or writes its result, 2 from a vector instruction's result to it
 AFTER_MFMA, BEFORE_MFMA = 8, 2

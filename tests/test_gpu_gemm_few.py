@@ -1,0 +1,66 @@
+"""Stored outputs of few tiles whose waves share d_in (gemm_bf16_few.hip) at the edges of its range: one slice a wave and shares that differ,
+a slice that d_in does not fill, shifted last tiles, one and two workgroups to a compute unit, extension slices behind the last share; and
+that the sides of its line go where they should.  Tolerances as in test_gpu_gemm_mid.py."""
+import numpy as np
+import pytest
+import torch
+
+from launches import kernels
+from oracle import agzo as oagzo
+from paper_2601_17261_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+EPS = float(np.float32(1e-2))
+
+
+@pytest.mark.parametrize("n,d_out,d_in,r", [(128, 128, 256, 1), (129, 131, 264, 16), (191, 200, 328, 17), (1024, 1024, 320, 4), (1025, 1030, 712, 64),
+                                            (130, 2000, 2048, 33), (260, 1100, 2552, 8)])
+def test_stored_output(n, d_out, d_in, r):
+    W, X, _ = synth.single_layer_problem(5, n, d_in, d_out, kind="rmsnorm", storage="bf16")
+
+    def strided(a, pad):
+        t = torch.full((a.shape[0], a.shape[1] + pad), float("nan"), device="cuda", dtype=torch.bfloat16)[:, :a.shape[1]]
+        return t.copy_(torch.from_numpy(a))
+    Wd, Xd = strided(W, 16), strided(X, 8)
+    B = torch.linalg.qr(torch.randn(d_in, r, device="cuda"))[0].contiguous()
+    stream = torch.cuda.Stream()
+    ctx = binding.Context(stream)
+    torch.cuda.synchronize()
+    Y0 = X.astype(np.float64) @ W.astype(np.float64).T
+    D = (X.astype(np.float64) @ B.double().cpu().numpy()) @ oagzo.gaussian_factor(5, d_out, r).T
+    for eps in (0.0, EPS, -EPS):
+        buf = torch.full((n, d_out + 3), 7.0, device="cuda", dtype=torch.bfloat16)
+        Y = buf[:, :d_out]
+        L = binding.make_layer(Wd, Xd, r, Y=Y)
+
+        def call():
+            if eps == 0.0:
+                ctx.layer_forward_sketch(L, Wd, Xd, Y, binding.SKETCH_NONE, None, 0, None, None, None)
+            else:
+                ctx.perturbed_forward(L, Wd, Xd, B, 5, eps, Y, None, None)
+        torch.cuda.synchronize()
+        call()
+        ctx.check()
+        want = Y0 + eps * D
+        err = np.abs(Y.double().cpu().numpy() - want)
+        assert np.all(err <= 2.0 ** -8 * np.abs(want) + 1e-5 * np.sqrt(np.mean(want ** 2))), eps
+        assert bool((buf[:, d_out:] == 7.0).all())
+        names, _ = kernels(stream, call)
+        assert sum("gemm_bf16_few_kernel" in s for s in names) == 1 and not any("gemm_bf16_mid" in s for s in names), names
+
+
+@pytest.mark.parametrize("n,d_out,d_in", [(128, 128, 248), (1088, 1984, 512), (300, 300, 2056), (512, 512, 2568)])
+def test_beyond_the_line(n, d_out, d_in):
+    """d_in of fewer than four slices, 527 tiles, 25 tiles of more than 32 slices, 64 of more than 40: 128 x 128 tiles"""
+    x, w = torch.randn(n, d_in, device="cuda").bfloat16(), torch.randn(d_out, d_in, device="cuda").bfloat16()
+    stream = torch.cuda.Stream()
+    ctx, y = binding.Context(stream), torch.empty(n, d_out, device="cuda", dtype=torch.bfloat16)
+    L = binding.make_layer(w, x, 1, Y=y)
+
+    def call():
+        ctx.layer_forward_sketch(L, w, x, y, binding.SKETCH_NONE, None, 0, None, None, None)
+    torch.cuda.synchronize()
+    call()
+    ctx.check()
+    names, _ = kernels(stream, call)
+    assert any("gemm_bf16_mid_kernel" in s for s in names) and not any("gemm_bf16_few" in s for s in names), names
