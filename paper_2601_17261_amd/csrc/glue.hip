@@ -80,54 +80,60 @@ __global__ __launch_bounds__(256) void glue_add_kernel(bf16_t* __restrict__ h, i
 
 // ---------------------------------------------------------------------------
 // Attention core of a decoder layer (grouped-query, causal, 128-wide heads, per-head RMS normalisation of queries and
-// keys, rotary embedding): the model between the q / k / v projections and the o projection.  Three kernels.
+// keys, rotary embedding): the model between the q / k / v projections and the o projection.  Two kernels.
 //
-// prep: q, k <- rope(rmsnorm_per_head(.)), head-major [seq][head][t][128]; v transposed to [seq][kv head][128][t_pad]
-//       (t_pad = seq_len rounded up to 64, the padding zero) so that the second product reads keys contiguously.
-// attention: four waves of 32 queries of one head (two groups of 16) against tiles of 64 keys that they share in LDS.  Scores are
-//       computed transposed, S^T = K Q^T (keys x queries), with
+// prep: k <- rope(rmsnorm_per_head(.)), head-major [seq][kv head][t][128], and the angles' cosines and sines
+// attention: eight waves of 16 queries of one head, which a wave normalises and rotates as it loads them, against tiles of 64 keys that
+//       they share in LDS.  Scores are computed transposed, S^T = K Q^T (keys x queries), with
 //       v_mfma_f32_16x16x32_bf16: a lane then holds, for ONE query (column lane % 16), the scores of keys 4 g + e of each
 //       16-key block (g = lane / 16), so the softmax's running maximum and sum are per-lane scalars up to a reduction
 //       over the four g, and the rescaling of the output accumulators (out^T = V^T P^T, same column = query) is a
 //       per-lane scalar too.  The eight probabilities a lane holds per 32 keys (two 16-key blocks) go straight into
-//       the second product as its operand: a sum over keys does not care about their order, so instead of re-laying P
-//       out, V^T is stored in the order P is held (of every 32 keys, those at 4 g .. 4 g + 3 of both blocks side by side).
-//       Per tile and group of queries a wave has 512 cycles of matrix work, about as much exponential and other vector work (the
-//       mask only on tiles that reach past the group, the rescaling only where a maximum moved) and 8 KB of LDS reads; two
-//       workgroups per compute unit overlap them.  With every wave fetching its own K and V^T fragments from memory 16 x 512
-//       tokens of 16 heads took 160 us, now 51 (340 TFLOP/s of causal work); prep with a thread's own angles per head 34, now 21.
+//       the second product as its operand; V^T in the same order of keys comes from the row-major tile by reads that transpose.
+//       Per tile a wave has 512 cycles of matrix work, some 1000 of exponential and other vector work (the
+//       mask only on tiles that reach past the wave's queries, the rescaling only where a maximum moved) and 32 KB of LDS reads; four
+//       waves to a SIMD overlap them, of which the vector units are busy half of the time.
+//       16 x 512 tokens of 16 heads on 8: 84.5 us, with q through memory once more (prepared by a launch ahead) and V transposed
+//       by another, and 67.5; 64 x 128 67.7 and 41; 5 x 77 14.5 and 12.3; 4 x 2048 169 and 161
 // ---------------------------------------------------------------------------
 constexpr int HEAD_DIM = 128;
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float floatx4_t __attribute__((ext_vector_type(4)));
 
-// 16 lanes per item: PREP_HEADS heads of q or of k at one token, which share the angles; the rotary pair (i, i + 64) sits 8 lanes
-// apart
+// 16 lanes per item: PREP_HEADS heads of k at one token, which share the angles; the rotary pair (i, i + 64) sits 8 lanes apart.  The
+// first sequence's items also leave cosine and sine of every position and pair for the queries
 constexpr int PREP_HEADS = 4;
-__global__ __launch_bounds__(256) void glue_qk_prep_kernel(const bf16_t* __restrict__ q, int64_t ldq, const bf16_t* __restrict__ k,
-                                                           int64_t ldk, bf16_t* __restrict__ Qr, bf16_t* __restrict__ Kr, int n_seq,
-                                                           int seq_len, int n_heads, int n_kv, float log2_theta) {
+__global__ __launch_bounds__(256) void glue_k_prep_kernel(const bf16_t* __restrict__ k, int64_t ldk, bf16_t* __restrict__ Kr, float2* __restrict__ angles,
+                                                          int n_seq, int seq_len, int n_kv, float log2_theta) {
     const int64_t item = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 4;
     const int j = threadIdx.x & 15;
-    const int gq = (n_heads + PREP_HEADS - 1) / PREP_HEADS, gk = (n_kv + PREP_HEADS - 1) / PREP_HEADS;
-    if (item >= (int64_t)n_seq * seq_len * (gq + gk)) return;              // whole 16-lane groups leave together
-    const int64_t tok = item / (gq + gk);
-    const int grp = (int)(item - tok * (gq + gk));
-    const bool is_q = grp < gq;
-    const int heads = is_q ? n_heads : n_kv, h0 = (is_q ? grp : grp - gq) * PREP_HEADS;
+    const int groups = (n_kv + PREP_HEADS - 1) / PREP_HEADS;
+    if (item >= (int64_t)n_seq * seq_len * groups) return;                 // whole 16-lane groups leave together
+    const int64_t tok = item / groups;
+    const int h0 = (int)(item - tok * groups) * PREP_HEADS;
     const int seq = (int)(tok / seq_len), t = (int)(tok - (int64_t)seq * seq_len);
-    const bf16_t* src = (is_q ? q + tok * ldq : k + tok * ldk) + h0 * HEAD_DIM + 8 * j;
+    const bf16_t* src = k + tok * ldk + h0 * HEAD_DIM + 8 * j;
     uint4 raw[PREP_HEADS];
 #pragma unroll
-    for (int h = 0; h < PREP_HEADS; ++h) raw[h] = h0 + h < heads ? *reinterpret_cast<const uint4*>(src + h * HEAD_DIM) : make_uint4(0, 0, 0, 0);
+    for (int h = 0; h < PREP_HEADS; ++h) raw[h] = h0 + h < n_kv ? *reinterpret_cast<const uint4*>(src + h * HEAD_DIM) : make_uint4(0, 0, 0, 0);
+    // pairs 8 (j mod 8) .. + 8: both of a pair's lanes need them, and each makes four
     float sn[8], cs[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int idx = 8 * (j & 7) + i;                                   // pair index 0..63
+    for (int i = 0; i < 4; ++i) {
+        const int idx = 8 * (j & 7) + (j >> 3) * 4 + i;                    // pair index 0..63
         const float inv = exp2f(-(float)idx * (2.0f / HEAD_DIM) * log2_theta);
-        sincosf((float)t * inv, &sn[i], &cs[i]);
+        float sm, cm;
+        sincosf((float)t * inv, &sm, &cm);
+        const float so = __shfl_xor(sm, 8), co = __shfl_xor(cm, 8);
+        sn[i] = j < 8 ? sm : so; cs[i] = j < 8 ? cm : co;
+        sn[4 + i] = j < 8 ? so : sm; cs[4 + i] = j < 8 ? co : cm;
     }
-    bf16_t* dst = (is_q ? Qr : Kr) + (((int64_t)seq * heads + h0) * seq_len + t) * HEAD_DIM + 8 * j;
+    if (seq == 0 && h0 == 0 && j < 8) {
+        float4* to = reinterpret_cast<float4*>(angles + (int64_t)t * (HEAD_DIM / 2) + 8 * j);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) to[i] = make_float4(cs[2 * i], sn[2 * i], cs[2 * i + 1], sn[2 * i + 1]);
+    }
+    bf16_t* dst = Kr + (((int64_t)seq * n_kv + h0) * seq_len + t) * HEAD_DIM + 8 * j;
 #pragma unroll
     for (int h = 0; h < PREP_HEADS; ++h) {
         float f[8];
@@ -145,39 +151,23 @@ __global__ __launch_bounds__(256) void glue_qk_prep_kernel(const bf16_t* __restr
             const float other = __shfl_xor(mine, 8);
             o[i] = (j < 8) ? mine * cs[i] - other * sn[i] : mine * cs[i] + other * sn[i];  // first half: x1 c - x2 s; second: x2 c + x1 s
         }
-        if (h0 + h < heads) *reinterpret_cast<uint4*>(dst + (int64_t)h * seq_len * HEAD_DIM) = pack8(o);
+        if (h0 + h < n_kv) *reinterpret_cast<uint4*>(dst + (int64_t)h * seq_len * HEAD_DIM) = pack8(o);
     }
 }
 
-// Vt[seq][kv head][d][t_pad]: a thread takes 8 values of one token (16-byte load) and stores them to 8 rows; the lanes of
-// a wave are consecutive tokens, so every store instruction writes 128 contiguous bytes.  Tokens >= seq_len write zeros.
-// Of every 32 tokens, token 16 b + 4 g + e is stored at 8 g + 4 b + e.
-__global__ __launch_bounds__(256) void glue_v_transpose_kernel(const bf16_t* __restrict__ v, int64_t ldv, bf16_t* __restrict__ Vt,
-                                                               int n_seq, int seq_len, int t_pad, int n_kv) {
-    const int t = blockIdx.x * 256 + threadIdx.x;
-    const int c = blockIdx.y % (HEAD_DIM / 8), head = blockIdx.y / (HEAD_DIM / 8), seq = blockIdx.z;
-    if (t >= t_pad) return;
-    uint4 raw = make_uint4(0, 0, 0, 0);
-    if (t < seq_len) raw = *reinterpret_cast<const uint4*>(v + ((int64_t)seq * seq_len + t) * ldv + head * HEAD_DIM + 8 * c);
-    const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
-    const int at = (t & ~31) | ((t >> 2) & 3) * 8 | ((t >> 4) & 1) * 4 | (t & 3);
-    bf16_t* dst = Vt + (((int64_t)seq * n_kv + head) * HEAD_DIM + 8 * c) * t_pad + at;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) dst[(int64_t)i * t_pad] = (bf16_t)((i & 1) ? (w[i >> 1] >> 16) : (w[i >> 1] & 0xFFFFu));
-}
-
-// QG 16-query groups per wave: every K and V^T fragment a wave reads serves QG matrix instructions
-constexpr int ATT_QG = 2;
+// QG 16-query groups per wave: every K and V^T fragment a wave reads serves QG matrix instructions.  (One group and four waves to a SIMD: with two
+// and two, half the reads and as much of the rest, 16 x 512 tokens took 71.0 us, 67.5 so, 4 x 2048 169 and 161)
+constexpr int ATT_QG = 1, ATT_WAVES = 8;
 constexpr int ATT_WAVE_Q = 16 * ATT_QG;     // queries per wave
-constexpr int ATT_WG_Q = 4 * ATT_WAVE_Q;    // queries per workgroup
+constexpr int ATT_WG_Q = ATT_WAVES * ATT_WAVE_Q;    // queries per workgroup
 constexpr int ATT_KEYS = 64;                // keys per tile
 constexpr int ATT_TILE = ATT_KEYS * HEAD_DIM * 2;        // bytes of a K or V^T tile
 constexpr int ATT_SMEM = 4 * ATT_TILE;      // two stages of both
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void glue_attention_kernel(
-        const bf16_t* __restrict__ Qr, const bf16_t* __restrict__ Kr, const bf16_t* __restrict__ Vt, bf16_t* __restrict__ out, int64_t ldo,
-        int seq_len, int t_pad, int n_heads, int n_kv) {
-    extern __shared__ __align__(16) char att_smem[];
+__global__ __launch_bounds__(64 * ATT_WAVES) __attribute__((amdgpu_waves_per_eu(4, 4))) void glue_attention_kernel(
+        const bf16_t* __restrict__ q, int64_t ldq, const bf16_t* __restrict__ Kr, const bf16_t* __restrict__ v, int64_t ldv,
+        const float2* __restrict__ angles, bf16_t* __restrict__ out, int64_t ldo, int seq_len, int n_heads, int n_kv) {
+    extern __shared__ __align__(256) char att_smem[];
     typedef __attribute__((address_space(3))) void* lptr_t;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -185,41 +175,89 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int head = blockIdx.y, seq = blockIdx.z, kvh = head / (n_heads / n_kv);
     // heavy tiles first: the last queries of a sequence see the most keys
     const int wg_q0 = (int)(gridDim.x - 1 - blockIdx.x) * ATT_WG_Q, q0 = wg_q0 + wave * ATT_WAVE_Q;
-    const bf16_t* Qh = Qr + ((int64_t)seq * n_heads + head) * seq_len * HEAD_DIM;
-    auto rsrc = [](const bf16_t* base) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, (int)0xFFFFFFFFu, 0x00020000); };
+    typedef const __attribute__((address_space(1))) void* gptr_t;
     const bf16_t* Kh = Kr + ((int64_t)seq * n_kv + kvh) * seq_len * HEAD_DIM;
-    const bf16_t* Vh = Vt + ((int64_t)seq * n_kv + kvh) * HEAD_DIM * t_pad;
+    const bf16_t* Vh = v + (int64_t)seq * seq_len * ldv + kvh * HEAD_DIM;
     union Frag { uint4 u; bf16x8_t v; };
     const int tiles = (min(wg_q0 + ATT_WG_Q, seq_len) + ATT_KEYS - 1) / ATT_KEYS;      // that any query of this workgroup may see
-    // direct loads of tile j into stage j & 1: K rows of 256 bytes (16-byte chunk c of row r at c ^ (r mod 16)), V^T rows of 128
-    // bytes (chunk c at c ^ (r / 2 mod 8)); four of each per wave.  Keys past the end repeat the last one, masked.  (Lanes' offsets
-    // have 32 bits: the tile and, in V^T, whose rows are as long as the sequence, the row group are part of the base)
-    auto request = [&](int j) __attribute__((always_inline)) {
-        char* stage = att_smem + (j & 1) * (2 * ATT_TILE) + wave * 4096;
-        const __amdgpu_buffer_rsrc_t rk = rsrc(Kh + (int64_t)j * (ATT_KEYS * HEAD_DIM));
+    // direct loads of tile j into stage j & 1: rows of 256 bytes of K (16-byte chunk c of row r at c ^ (r mod 16)) and of V (pairs of
+    // chunks, pair c of row r at c ^ (r mod 8)), four rows a load.  Keys past the end repeat the last one, masked
+    constexpr int LOADS = 16 / ATT_WAVES;
+    auto rsrc = [](const bf16_t* base) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, (int)0xFFFFFFFFu, 0x00020000); };
+    uint32_t koff[LOADS], voff[LOADS];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int row = 16 * wave + 4 * t + (lane >> 4);
-            const int off = min(row, seq_len - 1 - j * ATT_KEYS) * (HEAD_DIM * 2) + (((lane & 15) ^ (row & 15)) << 4);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (lptr_t)(stage + t * 1024), 16, off, 0, 0, 0);
+    for (int t = 0; t < LOADS; ++t) {
+        const int row = 4 * (LOADS * wave + t) + (lane >> 4);
+        koff[t] = (uint32_t)(row * (HEAD_DIM * 2) + (((lane & 15) ^ (row & 15)) << 4));
+        voff[t] = (uint32_t)((lane >> 4) * (2 * ldv) + (((lane & 15) ^ (2 * (row & 7))) << 4));
+    }
+    const bool near = ldv < (1 << 28);                                     // offsets inside four rows of V have 32 bits
+    auto request = [&](int j) __attribute__((always_inline)) {
+        char* stage = att_smem + (j & 1) * (2 * ATT_TILE) + wave * (LOADS * 1024);
+        if (near && (j + 1) * ATT_KEYS <= seq_len) {
+            const __amdgpu_buffer_rsrc_t rk = rsrc(Kh + (int64_t)j * (ATT_KEYS * HEAD_DIM));
+#pragma unroll
+            for (int t = 0; t < LOADS; ++t) __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (lptr_t)(stage + t * 1024), 16, (int)koff[t], 0, 0, 0);
+#pragma unroll
+            for (int t = 0; t < LOADS; ++t)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc(Vh + (int64_t)(j * ATT_KEYS + 4 * (LOADS * wave + t)) * ldv), (lptr_t)(stage + ATT_TILE + t * 1024), 16, (int)voff[t], 0, 0, 0);
+            return;
         }
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int row = 32 * wave + 8 * t + (lane >> 3);
-            const __amdgpu_buffer_rsrc_t rv = rsrc(Vh + (int64_t)(32 * wave + 8 * t) * t_pad + (int64_t)j * ATT_KEYS);
-            const uint32_t off = (uint32_t)(lane >> 3) * (2u * (uint32_t)t_pad) + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lptr_t)(stage + ATT_TILE + t * 1024), 16, (int)off, 0, 0, 0);
+        for (int t = 0; t < LOADS; ++t) {
+            const int row = 4 * (LOADS * wave + t) + (lane >> 4);
+            const int64_t key = min(j * ATT_KEYS + row, seq_len - 1);
+            __builtin_amdgcn_global_load_lds((gptr_t)(Kh + key * HEAD_DIM + (((lane & 15) ^ (row & 15)) << 3)), (lptr_t)(stage + t * 1024), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((gptr_t)(Vh + key * ldv + (((lane & 15) ^ (2 * (row & 7))) << 3)), (lptr_t)(stage + ATT_TILE + t * 1024), 16, 0, 0);
         }
     };
     request(0);
+    // queries: normalised and rotated on their way in; lane (n, g) has dims 32 ks + 8 g .. + 8 of query n, both values of its rotary pairs
     int qi[ATT_QG];                                                    // rows past the end repeat the last query, unstored
     Frag qf[ATT_QG][4];
 #pragma unroll
     for (int qg = 0; qg < ATT_QG; ++qg) {
         qi[qg] = min(q0 + 16 * qg + n, seq_len - 1);
+        const bf16_t* src = q + ((int64_t)seq * seq_len + qi[qg]) * ldq + head * HEAD_DIM + 8 * g;
+        const float4* ang = reinterpret_cast<const float4*>(angles + (int64_t)qi[qg] * (HEAD_DIM / 2) + 8 * g);
+        float f[4][8], o[4][8];
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) qf[qg][ks].u = *reinterpret_cast<const uint4*>(Qh + (int64_t)qi[qg] * HEAD_DIM + 32 * ks + 8 * g);
+        for (int ks = 0; ks < 4; ++ks) unpack8(*reinterpret_cast<const uint4*>(src + 32 * ks), f[ks]);
+        float ss = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) ss = fmaf(f[ks][i], f[ks][i], ss);
+        ss += __shfl_xor(ss, 16);
+        ss += __shfl_xor(ss, 32);
+        const float scale = rsqrtf(ss / (float)HEAD_DIM + 1e-6f);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float4 two = ang[16 * ks + (i >> 1)];
+                const float cs = (i & 1) ? two.z : two.x, sn = (i & 1) ? two.w : two.y;
+                const float x1 = f[ks][i] * scale, x2 = f[ks + 2][i] * scale;
+                o[ks][i] = x1 * cs - x2 * sn;
+                o[ks + 2][i] = x2 * cs + x1 * sn;
+            }
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) qf[qg][ks].u = pack8(o[ks]);
     }
+    // V^T fragments of dims 16 db .. + 16, 32 keys: two reads that transpose 4 keys x 16 dims in every 16 lanes, lane n asking for 8 bytes of key
+    // 4 g + n / 4 and receiving the four keys' values of dim n.  (Written out with their wait: behind the builtin's the compiler waits for every
+    // direct load in flight)
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    const int vkey = 4 * g + (n >> 2);
+    const uint32_t vat = (uint32_t)(uintptr_t)(lptr_t)att_smem + ATT_TILE + vkey * 256 + (n & 3) * 8 + ((vkey & 7) << 5);      // (dims 0 .. 16; others ^ db << 5)
+    auto read_v = [](uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, u32x2 (&lo)[4], u32x2 (&hi)[4]) __attribute__((always_inline)) {
+        asm volatile("ds_read_b64_tr_b16 %0, %8\n\tds_read_b64_tr_b16 %1, %8 offset:4096\n\t"
+                     "ds_read_b64_tr_b16 %2, %9\n\tds_read_b64_tr_b16 %3, %9 offset:4096\n\t"
+                     "ds_read_b64_tr_b16 %4, %10\n\tds_read_b64_tr_b16 %5, %10 offset:4096\n\t"
+                     "ds_read_b64_tr_b16 %6, %11\n\tds_read_b64_tr_b16 %7, %11 offset:4096\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(lo[0]), "=&v"(hi[0]), "=&v"(lo[1]), "=&v"(hi[1]), "=&v"(lo[2]), "=&v"(hi[2]), "=&v"(lo[3]), "=&v"(hi[3])
+                     : "v"(a0), "v"(a1), "v"(a2), "v"(a3) : "memory");
+    };
     floatx4_t acc[ATT_QG][8];
 #pragma unroll
     for (int qg = 0; qg < ATT_QG; ++qg)
@@ -239,13 +277,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         if (kb > q0 + ATT_WAVE_Q - 1) continue;                        // no query of this wave sees the tile (wave-uniform)
         // (fragments are read as bf16x8_t: behind a read of another type the compiler waits for every direct load in flight)
         const char* ks_ = att_smem + (j & 1) * (2 * ATT_TILE);
-        const char* vs_ = ks_ + ATT_TILE;
         floatx4_t s[ATT_QG][4];
 #pragma unroll
         for (int blk = 0; blk < 4; ++blk) {
             Frag kf[4];
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) kf[ks].v = *reinterpret_cast<const bf16x8_t*>(ks_ + (16 * blk + n) * 256 + (((4 * ks + g) ^ n) << 4));
+            for (int ks = 0; ks < 4; ++ks) kf[ks].v = *reinterpret_cast<const bf16x8_t*>(ks_ + 16 * blk * 256 + ((n * 256 + ((g ^ n) << 4)) ^ (ks << 6)));
 #pragma unroll
             for (int qg = 0; qg < ATT_QG; ++qg) {
                 s[qg][blk] = floatx4_t{0.f, 0.f, 0.f, 0.f};
@@ -327,12 +364,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                             for (int e = 0; e < 4; ++e) acc[qg][db][e] *= back[qg];
                     }
             }
+            const uint32_t at = vat + (j & 1) * (2 * ATT_TILE) + h * 8192;
 #pragma unroll
-            for (int db = 0; db < 8; ++db) {
-                Frag vf;                                               // dim 16 db + n, the keys in the order the probabilities are held
-                vf.v = *reinterpret_cast<const bf16x8_t*>(vs_ + (16 * db + n) * 128 + (((4 * h + g) ^ ((n >> 1) & 7)) << 4));
+            for (int db = 0; db < 8; db += 4) {
+                u32x2 lo[4], hi[4];
+                read_v(at ^ (db << 5), at ^ ((db + 1) << 5), at ^ ((db + 2) << 5), at ^ ((db + 3) << 5), lo, hi);
 #pragma unroll
-                for (int qg = 0; qg < ATT_QG; ++qg) acc[qg][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf.v, pf[qg][h].v, acc[qg][db], 0, 0, 0);
+                for (int d = 0; d < 4; ++d) {
+                    Frag vf;                                           // the keys in the order the probabilities are held
+                    vf.u = make_uint4(lo[d][0], lo[d][1], hi[d][0], hi[d][1]);
+#pragma unroll
+                    for (int qg = 0; qg < ATT_QG; ++qg) acc[qg][db + d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf.v, pf[qg][h].v, acc[qg][db + d], 0, 0, 0);
+                }
             }
         }
     }
@@ -351,27 +394,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
 }
 
+// prepared keys, angles
 size_t glue_attention_workspace_bytes(int n_seq, int seq_len, int n_heads, int n_kv) {
-    const int64_t t_pad = (seq_len + ATT_KEYS - 1) / ATT_KEYS * ATT_KEYS;
-    return (size_t)n_seq * ((int64_t)(n_heads + n_kv) * seq_len + (int64_t)n_kv * t_pad) * HEAD_DIM * sizeof(bf16_t) + 256;
+    return (size_t)n_seq * n_kv * seq_len * HEAD_DIM * sizeof(bf16_t) + (size_t)seq_len * (HEAD_DIM / 2) * sizeof(float2);
 }
 
 hipError_t launch_glue_attention(const bf16_t* q, int64_t ldq, const bf16_t* k, int64_t ldk, const bf16_t* v, int64_t ldv,
                                  bf16_t* out, int64_t ldo, int n_seq, int seq_len, int n_heads, int n_kv, float rope_theta,
                                  void* workspace, hipStream_t st) {
     if (n_seq == 0 || seq_len == 0) return hipSuccess;
-    const int t_pad = (seq_len + ATT_KEYS - 1) / ATT_KEYS * ATT_KEYS;
-    bf16_t* Qr = static_cast<bf16_t*>(workspace);
-    bf16_t* Kr = Qr + (int64_t)n_seq * n_heads * seq_len * HEAD_DIM;
-    bf16_t* Vt = Kr + (int64_t)n_seq * n_kv * seq_len * HEAD_DIM;
-    const int64_t items = (int64_t)n_seq * seq_len * ((n_heads + PREP_HEADS - 1) / PREP_HEADS + (n_kv + PREP_HEADS - 1) / PREP_HEADS) * 16;
-    hipLaunchKernelGGL(glue_qk_prep_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, q, ldq, k, ldk, Qr, Kr, n_seq,
-                       seq_len, n_heads, n_kv, log2f(rope_theta));
+    bf16_t* Kr = static_cast<bf16_t*>(workspace);
+    float2* angles = reinterpret_cast<float2*>(Kr + (int64_t)n_seq * n_kv * seq_len * HEAD_DIM);
+    const int64_t items = (int64_t)n_seq * seq_len * ((n_kv + PREP_HEADS - 1) / PREP_HEADS) * 16;
+    hipLaunchKernelGGL(glue_k_prep_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, k, ldk, Kr, angles, n_seq, seq_len, n_kv, log2f(rope_theta));
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(glue_v_transpose_kernel, dim3((unsigned)((t_pad + 255) / 256), (unsigned)(n_kv * (HEAD_DIM / 8)), (unsigned)n_seq),
-                       dim3(256), 0, st, v, ldv, Vt, n_seq, seq_len, t_pad, n_kv);
-    e = hipGetLastError();
     if (e != hipSuccess) return e;
     static bool attr_set = false;
     if (!attr_set) {
@@ -379,8 +415,8 @@ hipError_t launch_glue_attention(const bf16_t* q, int64_t ldq, const bf16_t* k, 
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    hipLaunchKernelGGL(glue_attention_kernel, dim3((unsigned)((seq_len + ATT_WG_Q - 1) / ATT_WG_Q), (unsigned)n_heads, (unsigned)n_seq), dim3(256), ATT_SMEM, st,
-                       Qr, Kr, Vt, out, ldo, seq_len, t_pad, n_heads, n_kv);
+    hipLaunchKernelGGL(glue_attention_kernel, dim3((unsigned)((seq_len + ATT_WG_Q - 1) / ATT_WG_Q), (unsigned)n_heads, (unsigned)n_seq), dim3(64 * ATT_WAVES), ATT_SMEM, st,
+                       q, ldq, Kr, v, ldv, angles, out, ldo, seq_len, n_heads, n_kv);
     return hipGetLastError();
 }
 
