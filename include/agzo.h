@@ -21,9 +21,9 @@
  *     operands ldw, ldx and d_in must be multiples of 8 and below 2^22, and
  *     W and X must be 16-byte aligned (16-byte rows).
  *   - Calls only enqueue work on the ctx stream (no host synchronisation)
- *     unless stated; agzo_step_many may fork a stream of the context's own
- *     off it and joins it again before the call's last launches.  Calls on
- *     one ctx must not overlap from several threads.
+ *     unless stated; agzo_step and agzo_step_many may fork a stream of the
+ *     context's own off it and join it again before the call's last
+ *     launches.  Calls on one ctx must not overlap from several threads.
  *   - Return value: 0 on success, a negative agzo_status otherwise; the text
  *     of the last error is available from agzo_last_error().
  */
@@ -111,8 +111,8 @@ int agzo_check(agzo_ctx* ctx);
  * mask: bit (1 << AGZO_PROF_x) selects class x, AGZO_PROF_ALL all of them, 0 switches timing off.  The events
  * cost a few microseconds of stream time each, so a timed region should select only what it reports.  While AGZO_PROF_GEMM
  * is selected every bf16 forward is timed by itself, together with the preparation of its rank-r operands; otherwise forwards of
- * several layers, and their preparations, share launches.  While any class is selected a set of layers runs in one stream, without
- * its base forwards beside the extraction.  AGZO_PROF_XQ contains the Gaussian factor's preparation where a projection shares its
+ * several layers, and their preparations, share launches.  While any class is selected a step runs in one stream, without
+ * base forwards beside the extraction.  AGZO_PROF_XQ contains the Gaussian factor's preparation where a projection shares its
  * launch (steps; agzo_perturbed_forward for up to 16 columns and 8192 tokens, but for wide layers of few tokens), unless AGZO_PROF_GEMM is
  * selected too.  The results are the same bits. */
 enum { AGZO_PROF_GEMM = 0, AGZO_PROF_UPDATE = 1, AGZO_PROF_XQ = 2, AGZO_PROF_XTT = 3, AGZO_PROF_QR = 4,

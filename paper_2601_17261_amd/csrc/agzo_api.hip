@@ -359,12 +359,16 @@ F32FwdArgs forward_f32_args(const agzo_layer& L, const void* W, const void* X, c
     return a;
 }
 
+// a forward that is launched on another stream than the context's, on so many compute units of each XCD
+struct SideForward { hipStream_t stream; int slots; };
+
 // Y = X W^T (+ eps (P) G^T), loss
 // shared = true: one pass over X and W evaluates the loss at W, W + eps Z, W - eps Z -> loss_dev[0..2]
 int op_forward(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* W, const void* X, const float* P,
                float eps_signed, uint64_t seed, void* Y, const agzo_loss_spec* loss, double* loss_dev,
-               bool shared = false, int part_slot = 0, bool defer_finish = false, bool fused_sketch = false, bool ext_ready = false, int ext_side = 0) {
-    hipStream_t st = ctx->stream;
+               bool shared = false, int part_slot = 0, bool defer_finish = false, bool fused_sketch = false, bool ext_ready = false, int ext_side = 0,
+               const SideForward* side = nullptr) {
+    hipStream_t st = side ? side->stream : ctx->stream;
     GemmLossArgs la;
     const bool has_loss = loss && loss->kind != AGZO_LOSS_NONE;
     la.kind = has_loss ? loss->kind : AGZO_LOSS_NONE;
@@ -373,11 +377,12 @@ int op_forward(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* W,
     la.ldt = has_loss ? loss->ldt : 0;
     const bool ce = has_loss && loss->kind == AGZO_LOSS_CE;
     // squared error: a step keeps the tile partials of its forwards side by side (slot = 0, 1, 2) and finishes them in
-    // one launch.  Cross-entropy: every loss is finished by launches of its own right behind the forward, so all of
-    // them use the region from its start: (sum, count) per token (fp32 storage) or per kCeCombineTokens tokens and phase (bf16).
+    // one launch.  Cross-entropy: every loss is finished by launches of its own right behind the forward; with fp32 storage all of
+    // them use the region from its start, (sum, count) per token, with bf16, where a forward may run beside the others, slot by slot,
+    // (sum, count) per kCeCombineTokens tokens and phase.
     {
-        const size_t at = ce ? 0 : (size_t)part_slot * p.n_part;
         const size_t nblk = (size_t)((L.n_tokens + kCeCombineTokens - 1) / kCeCombineTokens);
+        const size_t at = !ce ? (size_t)part_slot * p.n_part : L.dtype == AGZO_BF16 ? 2 * nblk * part_slot : 0;
         const size_t need = !has_loss ? 0 : ce ? (L.dtype == AGZO_BF16 ? 2 * nblk * (shared ? 3 : 1) : 2 * (size_t)L.n_tokens)
                                                : (size_t)p.n_part * (shared ? 3 : 1);
         if (at + need > p.part_count)
@@ -387,13 +392,14 @@ int op_forward(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* W,
     }
     const int32_t* ids = ce ? static_cast<const int32_t*>(loss->target) : nullptr;
     if (ce && L.dtype == AGZO_BF16) {
-        la.ce_ms = ctx->ws + p.off_ce_ms;
-        la.ce_tl = wsf(ctx, p.off_ce_tl);
+        la.ce_ms = ctx->ws + p.off_ce_ms + (size_t)part_slot * gemm_bf16_ce_chunks(L.d_out) * L.n_tokens * 8;
+        la.ce_tl = wsf(ctx, p.off_ce_tl) + (size_t)part_slot * L.n_tokens;
     }
     if (L.dtype == AGZO_BF16) {
         GemmBf16Args a = forward_bf16_args(ctx, L, p, W, X, P, eps_signed, seed, Y, la, shared);
         a.ext_ready = ext_ready;
         a.ext_side = ext_side;
+        if (side) a.slots = side->slots;
         if (fused_sketch) { a.sk_T = wsh(ctx, p.off_TpackT); a.sk_mpad = p.m_pad; a.sk_partial = wsf(ctx, p.off_xtt); }
         {
             ProfScope ps(ctx, AGZO_PROF_GEMM);
@@ -1112,6 +1118,18 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
             sides[(size_t)m] = GemmExtArgs{f.ext_ws, f.M, f.N, nullptr, f.r, eps, shared ? -2.f * eps : -eps, shared || !one_sided, it.seed};
     }
 
+    // the base forward of a lone layer beside its extraction, in 256 x 256 tiles on compute units of its own where both are done sooner so.  (A
+    // factorisation takes longer with the rank: one layer 2048 wide, r = 64, about 200 us more than at 16)
+    int base_slots = 0;
+    if (n == 1 && !shared && items[0].layer.dtype == AGZO_BF16 && ctx->prof == 0 && ctx->side) {
+        GemmLossArgs la;
+        la.kind = items[0].loss.kind; la.target_dtype = items[0].loss.target_dtype; la.target = items[0].loss.target; la.ldt = items[0].loss.ldt;
+        const std::vector<GemmBf16Args> f(1, forward_bf16_args(ctx, jobs[0].L, jobs[0].p, items[0].W, items[0].X, nullptr, 0.f, 0, nullptr, la, false));
+        GemmBeside extraction = extraction_us(f, K);
+        extraction.latency_us += (K + 1) * std::max(0, f[0].r - 16);
+        base_slots = gemm_bf16_slots_beside(f[0], extraction);
+    }
+
     // the squared-error evaluations of phases [ph0, ph1): 0 = f0 (or, shared, all three from one pass), 1 = f+, 2 = f-; the
     // loss partials of phase ph go to slot ph of the layer's region
     auto forward_mse = [&](int ph0, int ph1) -> int {
@@ -1150,6 +1168,11 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
             }));
             return 0;
         }
+        if (ph1 == 1 && base_slots > 0) {
+            bf[0].slots = base_slots;
+            HIPCHK(beside.run([&](hipStream_t side) { return launch_gemm_bf16(bf[0], side); }));
+            return 0;
+        }
         if (!timed(ctx, AGZO_PROF_GEMM)) {
             HIPCHK(launch_gemm_bf16_many(bf.data(), (int)bf.size(), false, st));
             return 0;
@@ -1164,7 +1187,17 @@ int step_many_body(agzo_ctx* ctx, const agzo_step_item* items, int n, int K, flo
         const agzo_step_item& it = items[m];
         if (it.loss.kind != AGZO_LOSS_CE) return 0;
         const LayerJob& j = jobs[(size_t)m];
-        return op_forward(ctx, j.L, j.p, it.W, it.X, P, e, it.seed, nullptr, &it.loss, dst, sh, slot, false, false, P && sides[(size_t)m].ext_ws, slot == 2 ? 1 : 0);
+        auto forward = [&](const SideForward* side) {
+            return op_forward(ctx, j.L, j.p, it.W, it.X, P, e, it.seed, nullptr, &it.loss, dst, sh, slot, false, false, P && sides[(size_t)m].ext_ws, slot == 2 ? 1 : 0, side);
+        };
+        if (P || base_slots == 0) return forward(nullptr);
+        int rc = 0;
+        HIPCHK(beside.run([&](hipStream_t side) {
+            const SideForward s{side, base_slots};
+            rc = forward(&s);
+            return hipSuccess;
+        }));
+        return rc;
     };
     // Alg. 2, part 1: the base forward of every layer, and every layer's basis from the same activations
     if (!shared) {

@@ -182,6 +182,7 @@ struct GemmBf16Args {
     // telemetry (NULL: none): four 64-bit device words that workgroup 0 fills with the shader-clock counter and the
     // constant-rate counter at kernel entry and exit
     unsigned long long* clk = nullptr;
+    int slots = 0;              // gemm_bf16_slots_beside(): workgroups per XCD (0: all compute units)
 };
 // number of loss partials a launch writes; small_ok: the call is one the 128 x 128 tiling supports (no shared-forward
 // mode, no cross-entropy), which is then used for shapes with few 256 x 256 tiles
@@ -206,6 +207,8 @@ hipError_t launch_gemm_bf16_many(const GemmBf16Args* a, int n, bool half_cu, hip
 // that takes latency_us + sweep_us by itself, of which only the second depends on how many compute units it has
 struct GemmBeside { double latency_us, sweep_us; };
 bool gemm_bf16_listed(const GemmBf16Args* a, int n);
+// a lone forward: the workgroups per XCD with which it and such work on another stream are done sooner than one after the other (0: they are not)
+int gemm_bf16_slots_beside(const GemmBf16Args& a, const GemmBeside& beside);
 hipError_t launch_gemm_bf16_beside(const GemmBf16Args* a, int n, const GemmBeside& beside, hipStream_t st);
 // extension operands of several layers in one launch: the W side times coef and, with two = true, once more times coef2
 // P = NULL: without the X side (the projection writes it).  planes != NULL: also the bf16 planes [3][rp][d] of B fp32 [d][r]

@@ -657,6 +657,7 @@ hipError_t choose(const GemmBf16Args& a, Choice& c) {
     p.ce_ms = reinterpret_cast<float2*>(a.loss.ce_ms);
     p.ce_tl = a.loss.ce_tl;
     p.clk = a.clk;
+    p.slots = a.slots;
     p.sk_T = a.sk_T; p.sk_mpad = a.sk_T ? a.sk_mpad : 0; p.sk_partial = a.sk_T ? a.sk_partial : nullptr;
     const bool small = takes_small(a), persistent = takes_persistent(a);
     p.Xext = nullptr; p.Wext = nullptr; p.Wext2 = nullptr; p.ext_ld = 0;
@@ -794,6 +795,12 @@ bool gemm_bf16_listed(const GemmBf16Args* a, int n) {
         if (choose(a[i], c) != hipSuccess || c.prep || (c.kernel != Kernel::aligned && c.kernel != Kernel::mid) || !gemm_bf16_aligned_listed(c.p)) return false;
     }
     return true;
+}
+
+int gemm_bf16_slots_beside(const GemmBf16Args& a, const GemmBeside& beside) {
+    Choice c;
+    if (choose(a, c) != hipSuccess || c.prep || c.kernel != Kernel::aligned) return 0;
+    return gemm_bf16_aligned_slots(c.p, beside);
 }
 
 hipError_t launch_gemm_bf16_beside(const GemmBf16Args* a, int n, const GemmBeside& beside, hipStream_t st) {

@@ -926,6 +926,7 @@ static hipError_t launch_aligned_lists(const GemmParams& p, hipStream_t st) {
     // the time of two)
     int64_t G = ((int64_t)p.tiles_m * p.tiles_n + 7) / 8 * 8;
     if (G > cus) G = cus >= 8 ? cus - cus % 8 : cus;
+    if (p.slots > 0 && G > 8 * p.slots) G = 8 * p.slots;
     const KBatch<AlignedItem, 1> tb{1, {0}, {(uint32_t)G}, {aligned_item(p)}};
     return launch_aligned_grid<OUT, T_F32, 1, RAGGED, 1>(tb, (unsigned)G, st);
 }
@@ -941,6 +942,8 @@ static hipError_t list_slots(int* slots) {
 
 // Microseconds that a slice and the change of tiles take, with all compute units at it
 constexpr double kSliceUs = 1.3, kTileUs = 8.0;
+// ... the softmax statistics of a tile, and a fork of a stream with its join
+constexpr double kStatisticsUs = 6.0, kForkUs = 25.0;
 static double tile_us(const AlignedItem& a) { return kSliceUs * (double)((a.K + BK - 1) / BK + (a.Xext ? a.ext_ld / BK : 0)) + kTileUs; }
 
 // Deals the tiles of an XCD's runs to its workgroups; the deepest problems come first, and what is left behind the rounds goes
@@ -991,6 +994,28 @@ static int slots_beside(const GemmBeside& b, double total, double deepest, int s
         const double done = slow < 0.0 ? 0.0 : forwards / slow;
         const double us = done >= 1.0 ? forwards : forwards + (1.0 - done) * all;
         if (best_us < 0.0 || us < best_us) { best_us = us; best = s; }
+    }
+    return best;
+}
+
+// The same for one problem in a launch of its own, whose workgroups take whole rounds of tiles together, against both one after the other; four
+// compute units of each XCD at least are left (a chain on 16 in all took longer than its forward: 20000 outputs of 4096 on 1500 tokens, r =
+// 16, 735 and 755).  A step of one layer, us, one stream and two (K = 3): cross-entropy, 2048 -> 32000 on 3001 tokens, r = 16, 1105 and 1003, on
+// 8192 2522 and 2514, 1024 -> 9000 on 700 241 and 223, on 8192 629 and 531; squared error, 4096 -> 4096 on 3001 394 and 349, 1024 ->
+// 8192 on 8192 489 and 422, 8192 -> 8192 on 8192 2507 and 2391, r = 1 2427 and 2374, r = 64 3072 and 2876.  Of 19 shapes and r = 1, 16 and 64 none
+// was more than 0.5 % slower
+int gemm_bf16_aligned_slots(const GemmParams& p, const GemmBeside& b) {
+    int slots = 0;
+    if (list_slots(&slots) != hipSuccess) return 0;
+    const double tile = tile_us(aligned_item(p)) + (p.loss_kind == AGZO_LOSS_CE ? kStatisticsUs : 0.0), all = b.latency_us + b.sweep_us;
+    const int64_t run = ((int64_t)p.tiles_m * p.tiles_n + 7) / 8;
+    auto rounds = [&](int s) { return (double)((run + s - 1) / s) * tile; };
+    int best = 0;
+    double best_us = rounds(slots) + all - kForkUs;
+    for (int s = slots - 4; s >= 1; --s) {
+        const double left = 22.0 / 29.0 * slots / (slots - s), slow = b.latency_us + b.sweep_us * (left > 1.0 ? left : 1.0);
+        const double done = rounds(s) / slow, us = done >= 1.0 ? rounds(s) : rounds(s) + (1.0 - done) * all;
+        if (us <= best_us) { best_us = us; best = s; }      // (of equal ones the fewest)
     }
     return best;
 }

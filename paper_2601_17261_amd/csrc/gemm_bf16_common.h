@@ -61,6 +61,7 @@ struct GemmParams {
     const bf16_t* sk_T; int64_t sk_mpad; float* sk_partial;
     // optional telemetry: workgroup 0 leaves {shader clock, constant-rate clock} at entry and at exit
     unsigned long long* clk;
+    int slots;                  // workgroups per XCD of the persistent kernel at most (0: one to a compute unit)
 };
 
 
@@ -100,6 +101,8 @@ hipError_t launch_gemm_bf16_few(const GemmItem& a, hipStream_t st);
 // persistent kernel in 256 x 256 tiles (gemm_bf16_aligned.hip): M, N >= 256, d_in >= 128, the rank-r term as prepared operands;
 // either the squared-error loss without a stored Y, the cross-entropy statistics without a stored Y, or a bf16 Y without a loss
 hipError_t launch_gemm_bf16_aligned(const GemmParams& p, hipStream_t st);
+// p.slots for that launch beside other work, or 0 where it is done sooner one after the other
+int gemm_bf16_aligned_slots(const GemmParams& p, const GemmBeside& beside);
 // squared errors of several layers (gemm_bf16_aligned_listed()) over tile lists that go through all of them.  sub[i]: the loss
 // partials of gemm_bf16_mid.hip, bit for bit (a layer that takes its 128 x 128 tiles when alone).  beside != NULL: in lists in any case, on
 // as many compute units as the work beside them leaves.  us != NULL: nothing is launched, *us is about what it would take, below 0
