@@ -20,7 +20,10 @@ template <int V> struct IC { static constexpr int value = V; };
 // workgroup, up to four workgroups per compute unit), the next slice in flight in registers.
 // Bound by the fp64 rate (78.6 TFLOP/s, the same on the matrix cores and the vector units): one instruction takes 64 cycles
 // for two operand registers, so that a slice is 2048 cycles of matrix work per wave against eight LDS reads and 32
-// conversions.  The vector-unit version it replaces (a 4 x 4 register tile per thread) converted eight values from LDS for
+// conversions.  Vector instructions take turns with it, some four cycles each (the matrix unit was busy 83 % of the time at 50 vector
+// instructions a slice), so addresses are constants and 32-bit offsets from uniform bases: 34 a slice, the three forwards of
+// the 0.6B-sized set on 1000 tokens 1622 and 1580 us.  (Half of the conversions, with the slices in fp64 in LDS, were lost again to twice the
+// LDS reads and barriers: 1668.)  The vector-unit version it replaces (a 4 x 4 register tile per thread) converted eight values from LDS for
 // every 16 multiplications, loaded without a prefetch, and ran at 7 TFLOP/s.  The small tile is for few tokens: 1000 x 1024
 // outputs give one wave to each of the 1024 SIMDs.
 // Launches of fewer than F32_SMALL_LAUNCH such tiles take 32 x 32 ones, four waves of 16 x 16, with four slices in flight, for layers
@@ -83,10 +86,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void f
     // the epilogue masks), columns past d_in are zero
     const int ch = tid & 7, r0 = tid >> 3;                 // rows r0 (and r0 + 32)
     const float *xr[FB], *wr[FB];
+    uint32_t xo[FB], wo_[FB];                              // (VEC: bytes from the tile's first row, a uniform base)
+    const char *xb = reinterpret_cast<const char*>(a.X + m0 * a.ldx), *wb = reinterpret_cast<const char*>(a.W + n0 * a.ldw);
 #pragma unroll
     for (int i = 0; i < FB; ++i) {
-        xr[i] = a.X + min(m0 + r0 + 32 * i, a.M - 1) * a.ldx;
-        wr[i] = a.W + min(n0 + r0 + 32 * i, a.N - 1) * a.ldw;
+        const int64_t rx_ = min(m0 + r0 + 32 * i, a.M - 1), rw_ = min(n0 + r0 + 32 * i, a.N - 1);
+        xr[i] = a.X + rx_ * a.ldx;
+        wr[i] = a.W + rw_ * a.ldw;
+        xo[i] = (uint32_t)(((rx_ - m0) * a.ldx + ch * 4) * 4);
+        wo_[i] = (uint32_t)(((rw_ - n0) * a.ldw + ch * 4) * 4);
     }
     float4 rx[AHEAD][FB], rw[AHEAD][FB];
     // MASK: the slice may reach past d_in (with several slices in flight its end is loaded instead and left out: around a lane's
@@ -154,13 +162,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void f
         sstore(rx[0], rw[0], 0);
         __syncthreads();
         int kt = 0;
-        for (; kt + 1 < nfull; ++kt) {
-            gload(rx[0], rw[0], (int64_t)(kt + 1) * FK, IC<0>{});
-            multiply(kt & 1, 1.0);
-            sstore(rx[0], rw[0], (kt + 1) & 1);
+        auto whole = [&](int k, auto BUF) __attribute__((always_inline)) {
+            if constexpr (VEC) {
+#pragma unroll
+                for (int i = 0; i < FB; ++i) {
+                    rx[0][i] = *reinterpret_cast<const float4*>(xb + (int64_t)k * (FK * 4) + xo[i]);
+                    rw[0][i] = *reinterpret_cast<const float4*>(wb + (int64_t)k * (FK * 4) + wo_[i]);
+                }
+            } else {
+                gload(rx[0], rw[0], (int64_t)k * FK, IC<0>{});
+            }
+            multiply(decltype(BUF)::value, 1.0);
+            sstore(rx[0], rw[0], decltype(BUF)::value ^ 1);
             __syncthreads();
+        };
+        // (two slices at a time: the buffers' addresses are then constants.  Vector instructions take turns with the fp64 matrix ones)
+        for (; kt + 2 < nfull; kt += 2) {
+            whole(kt + 1, IC<0>{});
+            whole(kt + 2, IC<1>{});
         }
-        for (; kt < nk; ++kt) {                            // the last one or two slices
+        for (; kt < nk; ++kt) {                            // the last two or three slices
             if (kt + 1 < nk) gload(rx[0], rw[0], (int64_t)(kt + 1) * FK, IC<1>{});
             multiply(kt & 1, 1.0);
             if (kt + 1 < nk) sstore(rx[0], rw[0], (kt + 1) & 1);
@@ -287,9 +308,9 @@ int forward_f32_num_workgroups(int64_t M, int64_t N) {
     return (int)(((M + t - 1) / t) * ((N + t - 1) / t));
 }
 
-// every row of X and W starts on 16 bytes
+// every row of X and W starts on 16 bytes, and the rows of a tile lie within 32 bits of its first
 static bool f32_vec(const F32FwdArgs& a) {
-    return a.K % 4 == 0 && a.ldx % 4 == 0 && a.ldw % 4 == 0 && ((reinterpret_cast<uintptr_t>(a.X) | reinterpret_cast<uintptr_t>(a.W)) & 15) == 0;
+    return a.ldx < (1 << 24) && a.ldw < (1 << 24) && a.K % 4 == 0 && a.ldx % 4 == 0 && a.ldw % 4 == 0 && ((reinterpret_cast<uintptr_t>(a.X) | reinterpret_cast<uintptr_t>(a.W)) & 15) == 0;
 }
 
 template <int FT>
