@@ -5,7 +5,7 @@
 
 namespace agzo {
 
-// Extension operands of perturbed forwards, written once per layer instead of once per tile: eight columns per thread.
+// Extension operands of perturbed forwards, written once per layer instead of once per tile.
 // Rows 0..M-1 are the X side ([Ph | Ph | Pl | 0], P = X B split hi + lo in bf16), rows M..M+N-1 the W side
 // ([Gh | Gl | Gh | 0], G regenerated from the Philox seed, times coef: the signed eps); n_w = 2 adds rows M+N..M+2N-1, the
 // W side once more with coef2 (the other sign's, or the shared-forward kernel's second pass, -2 eps).  Several layers per
@@ -19,14 +19,34 @@ struct ExtDev {
     uint32_t s_lo, s_hi;
     const float* B; bf16_t* planes; int64_t d;
 };
-// thread idx
+// eight values as bf16 hi + lo
+__device__ __forceinline__ void ext_split(const float (&v)[8], uint4& hi, uint4& lo) {
+    uint32_t h[4], l[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        h[i] = pack_bf16x2(v[2 * i], v[2 * i + 1]);
+        l[i] = pack_bf16x2(v[2 * i] - __uint_as_float(h[i] << 16), v[2 * i + 1] - __uint_as_float(h[i] & 0xFFFF0000u));
+    }
+    hi = make_uint4(h[0], h[1], h[2], h[3]);
+    lo = make_uint4(l[0], l[1], l[2], l[3]);
+}
+// columns k0 .. k0 + 7 of the segments [first | second | third | 0] of a row (the last one of rp columns, or not there)
+__device__ __forceinline__ void ext_store(bf16_t* row, int ext_ld, int rp, int k0, uint4 first, uint4 second, uint4 third) {
+    *reinterpret_cast<uint4*>(row + k0) = first;
+    *reinterpret_cast<uint4*>(row + rp + k0) = second;
+    *reinterpret_cast<uint4*>(row + 2 * rp + k0) = third;
+    if (3 * rp < ext_ld) *reinterpret_cast<uint4*>(row + 3 * rp + k0) = make_uint4(0, 0, 0, 0);
+}
+// thread idx: eight columns of a row's segments, W side first; a row of the W side with both coefficients, so that its normals are made once
+// (a thread for every sixteen bytes written made them three times for each; beside the sums of a projection, seven 4B-sized layers on
+// 4096 tokens, r = 64, 30 us a launch and 20)
 __device__ __forceinline__ void ext_prep_body(const ExtDev& a, int64_t idx) {
     const int ext_ld = a.ext_ld, r = a.r, rp = a.rp;
     const int64_t M = a.M, N = a.N;
-    const int chunks = ext_ld / 8;
-    if (idx >= (M + a.n_w * N) * chunks) {
+    const int groups = rp / 8;
+    if (idx >= (M + N) * groups) {
         // eight rows of one column of B
-        const int64_t e = idx - (M + a.n_w * N) * chunks;
+        const int64_t e = idx - (M + N) * groups;
         if (a.planes == nullptr || e >= a.d / 8 * rp) return;
         const int64_t i = e % (a.d / 8) * 8;
         const int k = (int)(e / (a.d / 8));
@@ -44,43 +64,35 @@ __device__ __forceinline__ void ext_prep_body(const ExtDev& a, int64_t idx) {
         for (int pl = 0; pl < 3; ++pl) *reinterpret_cast<uint4*>(a.planes + ((int64_t)pl * rp + k) * a.d + i) = make_uint4(w[pl][0], w[pl][1], w[pl][2], w[pl][3]);
         return;
     }
-    int64_t row = idx / chunks;
-    const bool second = row >= M + N;
-    if (second) row -= N;
-    const float coef = second ? a.coef2 : a.coef;
-    const int col0 = (int)(idx % chunks) * 8;
-    const int seg = col0 / rp, k0 = col0 % rp;
-    uint32_t hi[4] = {0, 0, 0, 0}, lo[4] = {0, 0, 0, 0};
-    if (seg < 3) {
-        float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        if (row < M) {
+    const int64_t row = idx / groups;
+    const int k0 = (int)(idx - row * groups) * 8;
+    float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    uint4 hi, lo;
+    if (row >= N) {
+        const int64_t t = row - N;
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (k0 + i < r) v[i] = a.P[row * r + k0 + i];
-        } else {
-            const int64_t j = row - M;
-            if (k0 < r) {
-                const float4 z = philox_normal4(a.s_lo, a.s_hi, AGZO_TAG_G, (uint32_t)j, (uint32_t)(k0 >> 2));
-                v[0] = z.x; v[1] = z.y; v[2] = z.z; v[3] = z.w;
-            }
-            if (k0 + 4 < r) {
-                const float4 z = philox_normal4(a.s_lo, a.s_hi, AGZO_TAG_G, (uint32_t)j, (uint32_t)((k0 >> 2) + 1));
-                v[4] = z.x; v[5] = z.y; v[6] = z.z; v[7] = z.w;
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = (k0 + i < r) ? coef * v[i] : 0.f;
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            hi[i] = pack_bf16x2(v[2 * i], v[2 * i + 1]);
-            lo[i] = pack_bf16x2(v[2 * i] - __uint_as_float(hi[i] << 16), v[2 * i + 1] - __uint_as_float(hi[i] & 0xFFFF0000u));
-        }
+        for (int i = 0; i < 8; ++i)
+            if (k0 + i < r) v[i] = a.P[t * r + k0 + i];
+        ext_split(v, hi, lo);
+        ext_store(a.Xext + t * ext_ld, ext_ld, rp, k0, hi, hi, lo);
+        return;
     }
-    // X side: [hi | hi | lo]; W side: [hi | lo | hi]
-    const bool use_lo = (row < M) ? (seg == 2) : (seg == 1);
-    const uint4 out = use_lo ? make_uint4(lo[0], lo[1], lo[2], lo[3]) : make_uint4(hi[0], hi[1], hi[2], hi[3]);
-    bf16_t* dst = (row < M) ? a.Xext + row * ext_ld + col0 : a.Wext + (row - M + (second ? N : 0)) * ext_ld + col0;
-    *reinterpret_cast<uint4*>(dst) = out;
+    if (k0 < r) {
+        const float4 z = philox_normal4(a.s_lo, a.s_hi, AGZO_TAG_G, (uint32_t)row, (uint32_t)(k0 >> 2));
+        v[0] = z.x; v[1] = z.y; v[2] = z.z; v[3] = z.w;
+    }
+    if (k0 + 4 < r) {
+        const float4 z = philox_normal4(a.s_lo, a.s_hi, AGZO_TAG_G, (uint32_t)row, (uint32_t)((k0 >> 2) + 1));
+        v[4] = z.x; v[5] = z.y; v[6] = z.z; v[7] = z.w;
+    }
+    for (int w = 0; w < a.n_w; ++w) {
+        const float coef = w ? a.coef2 : a.coef;
+        float c[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) c[i] = (k0 + i < r) ? coef * v[i] : 0.f;
+        ext_split(c, hi, lo);
+        ext_store(a.Wext + (row + w * N) * ext_ld, ext_ld, rp, k0, hi, lo, hi);
+    }
 }
 
 // the W side of args (and the X side, from P, unless that is NULL) as the kernels take it, and the workgroups of `threads` for it
@@ -93,7 +105,7 @@ inline ExtDev ext_dev(const GemmExtArgs& a, uint64_t& workgroups, int threads = 
     d.P = a.P; d.r = a.r; d.rp = (a.r + 15) / 16 * 16;
     d.coef = a.coef; d.coef2 = a.coef2; d.n_w = a.two ? 2 : 1;
     d.s_lo = (uint32_t)a.seed; d.s_hi = (uint32_t)(a.seed >> 32);
-    const int64_t items = (d.M + d.n_w * d.N) * (d.ext_ld / 8) + (d.planes ? d.d / 8 * d.rp : 0);
+    const int64_t items = (d.M + d.N) * (d.rp / 8) + (d.planes ? d.d / 8 * d.rp : 0);
     workgroups = (uint64_t)((items + threads - 1) / threads);
     return d;
 }
