@@ -515,7 +515,7 @@ int stage_sketch_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, const in
                        wsf(ctx, j.p.off_xtt), j.p.nsplit};
     }
     ProfScope ps(ctx, AGZO_PROF_XTT);
-    HIPCHK(launch_xtt_bf16_many(t, n, st));
+    HIPCHK(launch_xtt_bf16_many(t, n, half_cu, st));
     return 0;
 }
 
@@ -1065,12 +1065,20 @@ bool beside_fits(const std::vector<GemmBf16Args>& forwards, int K) {
     return (int)forwards.size() >= kBesideLayers && flops >= kBesideFlops &&
            half_cu <= (1e9 * (200 + (r > 1 ? 60 : 0) + r) + 800.0 * values) * ((2 * K + 2) / 8.0);
 }
-// What the extraction takes by itself: the latencies of its launches, and two sweeps over X a step at 5.7 TB/s
+// What the extraction takes by itself: the latencies of its launches, and two sweeps over X a step at 5.7 TB/s (one for up to kProductsOfOneX layers
+// that share it)
 GemmBeside extraction_us(const std::vector<GemmBf16Args>& forwards, int K) {
     double bytes = 0.0;
     int r = 1;
-    for (const GemmBf16Args& a : forwards) {
-        bytes += 2.0 * (double)a.M * (double)a.K;
+    for (size_t i = 0; i < forwards.size(); ++i) {
+        const GemmBf16Args& a = forwards[i];
+        int before = 0;          // with the same activations
+        for (size_t j = 0; j < i; ++j) {
+            const GemmBf16Args& b = forwards[j];
+            before += b.X == a.X && b.ldx == a.ldx && b.M == a.M && b.K == a.K && b.r <= 16 && a.r <= 16;
+        }
+        const bool loads = before % kProductsOfOneX == 0;
+        bytes += (double)a.M * (double)a.K * ((loads ? 1.0 : 0.0) + (loads || xq_narrow(a.M, a.K, a.r) ? 1.0 : 0.0));
         r = std::max(r, a.r);
     }
     return GemmBeside{(r > 1 ? 37.0 : 28.0) * (K + 1), bytes * (2 * K + 2) / 5.7e6};

@@ -243,6 +243,8 @@ hipError_t launch_xq_f32_many(const F32SkinnyArgs* a, int n, hipStream_t st);
 hipError_t launch_xtt_f32_many(const F32SkinnyArgs* a, int n, hipStream_t st);
 
 // skinny.hip : bf16 tall-skinny products
+// so many products of a launch with the same X, up to 16 columns each, share its loads (as groups; a column's bits do not depend on it)
+constexpr int kProductsOfOneX = 4;
 // T = X Qp, Qp given as bf16 planes [3][rp][d_in]; writes T fp32 [M][r] (nullable) and
 // T^T planes bf16 [3][rp][m_pad] (nullable)
 // part: xq_part_bytes() bytes of scratch for the split over d_in that small token counts take (NULL: never split)
@@ -271,7 +273,8 @@ int xtt_num_splits(int64_t M, int64_t K);
 hipError_t launch_xtt_bf16(const bf16_t* X, int64_t ldx, int64_t M, int64_t K, const bf16_t* TpackT, int64_t m_pad,
                            int rp, float* partial, int nsplit, hipStream_t st);
 struct XttArgs { const bf16_t* X; int64_t ldx, M, K; const bf16_t* TpackT; int64_t m_pad; int rp; float* partial; int nsplit; };
-hipError_t launch_xtt_bf16_many(const XttArgs* a, int n, hipStream_t st);
+// (half_cu: as above)
+hipError_t launch_xtt_bf16_many(const XttArgs* a, int n, bool half_cu, hipStream_t st);
 hipError_t launch_reduce_splits(const float* partial, int nsplit, int64_t d, int rp, int r, float* S, hipStream_t st);
 // Q fp32 [d][r] -> bf16 planes [3][rp][d]
 hipError_t launch_pack_planes(const float* Q, int64_t d, int r, int rp, bf16_t* pack, hipStream_t st);

@@ -993,7 +993,7 @@ static int slots_beside(const GemmBeside& b, double total, double deepest, int s
         const double all = b.latency_us + b.sweep_us, slow = left < 0.0 ? left : b.latency_us + b.sweep_us * (left > 1.0 ? left : 1.0);
         const double done = slow < 0.0 ? 0.0 : forwards / slow;
         const double us = done >= 1.0 ? forwards : forwards + (1.0 - done) * all;
-        if (best_us < 0.0 || us < best_us) { best_us = us; best = s; }
+        if (best_us < 0.0 || us < 1.05 * best_us) { best = s; best_us = best_us < 0.0 || us < best_us ? us : best_us; }      // (of about equal ones the fewest)
     }
     return best;
 }

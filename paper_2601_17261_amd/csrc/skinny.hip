@@ -4,6 +4,7 @@
 // X is bf16; the small fp32 factor (Q, B, T, Omega) enters the matrix cores as three bf16 planes
 // hi + mid + lo, whose sum is the fp32 value, so the products carry fp32-level accuracy while the
 // kernels stay bound by the single read of X.  v_mfma_f32_16x16x32_bf16 throughout.
+#include <algorithm>
 #include <type_traits>
 
 #include "ext_prep.h"
@@ -25,6 +26,14 @@ union Frag {
 // slices (one 128-byte line per row and slice, XOR-swizzled chunks) through a ring of XQ_STAGES slots,
 // so that enough bytes are in flight per CU to cover the memory latency with four waves.
 // ---------------------------------------------------------------------------
+constexpr int kXShare = kProductsOfOneX;
+// Workgroups from which on a launch of products that share an X takes them in groups.  Fewer leave compute units idle that the products by
+// themselves, in smaller pieces, would use.  A step, us, without and with groups: 0.6B-sized layers on 512 tokens (56 and 112 workgroups) 226 and 254,
+// on 1000 (112 and 224) 274 and 278, on 1400 326 and 312, on 2048 (194 and 448) 392 and 376; 4B-sized on 200 (74 and 136) 384 and 393, on 400 503
+// and 489, on 512 (148 and 272) 535 and 521; 8B-sized on 300 (144 and 200) 711 and 683, on 16384 14749 and 14350.  2.3 layers of a
+// decoder, 2048 and 6144 wide, on 8192: 116 and 94 a launch of X^T T, 112 and 109 of X Q
+constexpr uint64_t XTT_GROUP_MIN = 128, XQ_GROUP_MIN = 192;
+
 constexpr int XQ_TOK = 64;
 constexpr int XQ_BK = 64;
 
@@ -432,6 +441,177 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void x
     const XqDev& a = tb.a[kbatch_find(tb, bx, by)];
     xq_direct_body<NB, MB>(a.X, a.ldx, a.M, a.K, a.Qpack, a.r, a.T, a.TpackT, a.m_pad, a.part, a.Xext, bx, by, (uint32_t)a.ns);
 }
+
+// Products of several layers that read the same activations, up to four with up to 16 columns each: X is read once for all of them.  As
+// xq_direct_body() with the planes of NB products side by side, in the slices' order of xq_bf16_body() (16-byte chunks lg and 4 + lg of a row's
+// line): sums and bits are those of a product by itself, in whose form (xq_bf16_body()) the same launch makes those that share theirs with none.
+// Bound by what a compute unit takes in, planes and X, and by the 16 rows that a load of X touches
+struct XqGroupDev {
+    const bf16_t* X; int64_t ldx, M, K, m_pad;
+    int ns, nb;
+    const bf16_t* Qpack[kXShare];
+    float* T[kXShare]; bf16_t* TpackT[kXShare]; float* part[kXShare]; bf16_t* Xext[kXShare];
+    int r[kXShare];
+};
+template <int NB, int MB>
+__device__ __forceinline__ void xq_group_body(const XqGroupDev& a, uint32_t bx, uint32_t by) {
+    constexpr int TOK = MB * XQ_TOK, QROWS = 48 * NB, LOADS = xqd_loads(NB);      // plane rows; a wave's direct loads of a slice
+    constexpr int STAGES = XQD_STAGES, SLOT = LOADS * 4096;
+    extern __shared__ __align__(16) char xq_smem[];
+    typedef __attribute__((address_space(3))) void* lptr_t;
+    typedef const __attribute__((address_space(1))) void* gptr_t;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lm = lane & 15, lg = lane >> 4;
+    const int64_t t0 = (int64_t)bx * TOK, M = a.M, K = a.K;
+
+    floatx4 acc[MB][NB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+    const int nsplit = a.ns, split = (int)by;
+    const int nfull_all = (int)(K / XQ_BK);
+    const int kbeg = (int)((int64_t)nfull_all * split / nsplit);
+    const int nfull = (int)((int64_t)nfull_all * (split + 1) / nsplit) - kbeg;      // this workgroup's slices
+    const bool tail = (K % XQ_BK) != 0 && split == nsplit - 1;
+    // plane rows, 16 of plane pl of product nb at 16 (pl NB + nb), in groups of eight: wave w takes w, w + 4, ... (past the last: the last once
+    // more, into rows nobody reads)
+    auto plane_row = [&](int row) __attribute__((always_inline)) { return a.Qpack[(row >> 4) % NB] + (int64_t)((row >> 4) / NB * 16 + (row & 15)) * K; };
+    const bf16_t* src[LOADS];
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+        const int group = min(wave + 4 * i, QROWS / 8 - 1), row = 8 * (wave + 4 * i) + (lane >> 3);
+        src[i] = a.Qpack[(group >> 1) % NB] + (int64_t)((group >> 1) / NB * 16 + 8 * (group & 1) + (lane >> 3)) * K + ((lane & 7) ^ ((row >> 1) & 7)) * 8 + (int64_t)kbeg * XQ_BK;
+    }
+    const bf16_t* xsrc[MB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) xsrc[mb] = a.X + min(t0 + (wave * MB + mb) * 16 + lm, M - 1) * a.ldx + lg * 8 + (int64_t)kbeg * XQ_BK;
+    u32x4 x[STAGES][MB][2];
+    auto issue = [&](auto SET) __attribute__((always_inline)) {
+        constexpr int set = decltype(SET)::value;
+        char* base = xq_smem + set * SLOT + wave * 1024;
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) {
+            __builtin_amdgcn_global_load_lds((gptr_t)src[i], (lptr_t)(base + i * 4096), 16, 0, 0);
+            src[i] += XQ_BK;
+        }
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+#pragma unroll
+            for (int sub = 0; sub < 2; ++sub) x[set][mb][sub] = *reinterpret_cast<const u32x4*>(xsrc[mb] + sub * 32);
+            xsrc[mb] += XQ_BK;
+        }
+    };
+    // (the fragments of one 32-wide sub-step at a time, reads and wait in one block)
+    auto multiply = [&](int slot, u32x4 (&xa)[MB][2]) __attribute__((always_inline)) {
+        const char* qs = xq_smem + slot * SLOT;
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub) {
+            u32x4 b[3][NB];
+            const uint32_t at = (uint32_t)(uintptr_t)(lptr_t)(qs + xq_lds_off(lm, 4 * sub + lg));
+            if constexpr (NB == 1)
+                asm volatile("ds_read_b128 %0, %3\n\tds_read_b128 %1, %3 offset:2048\n\tds_read_b128 %2, %3 offset:4096\n\ts_waitcnt lgkmcnt(0)"
+                             : "=&v"(b[0][0]), "=&v"(b[1][0]), "=&v"(b[2][0]) : "v"(at) : "memory");
+            else if constexpr (NB == 2)
+                asm volatile("ds_read_b128 %0, %6\n\tds_read_b128 %1, %6 offset:2048\n\tds_read_b128 %2, %6 offset:4096\n\t"
+                             "ds_read_b128 %3, %6 offset:6144\n\tds_read_b128 %4, %6 offset:8192\n\tds_read_b128 %5, %6 offset:10240\n\ts_waitcnt lgkmcnt(0)"
+                             : "=&v"(b[0][0]), "=&v"(b[0][1]), "=&v"(b[1][0]), "=&v"(b[1][1]), "=&v"(b[2][0]), "=&v"(b[2][1]) : "v"(at) : "memory");
+            else if constexpr (NB == 3)
+                asm volatile("ds_read_b128 %0, %9\n\tds_read_b128 %1, %9 offset:2048\n\tds_read_b128 %2, %9 offset:4096\n\t"
+                             "ds_read_b128 %3, %9 offset:6144\n\tds_read_b128 %4, %9 offset:8192\n\tds_read_b128 %5, %9 offset:10240\n\t"
+                             "ds_read_b128 %6, %9 offset:12288\n\tds_read_b128 %7, %9 offset:14336\n\tds_read_b128 %8, %9 offset:16384\n\ts_waitcnt lgkmcnt(0)"
+                             : "=&v"(b[0][0]), "=&v"(b[0][1]), "=&v"(b[0][2]), "=&v"(b[1][0]), "=&v"(b[1][1]), "=&v"(b[1][2]),
+                               "=&v"(b[2][0]), "=&v"(b[2][1]), "=&v"(b[2][2]) : "v"(at) : "memory");
+            else
+                asm volatile("ds_read_b128 %0, %12\n\tds_read_b128 %1, %12 offset:2048\n\tds_read_b128 %2, %12 offset:4096\n\t"
+                             "ds_read_b128 %3, %12 offset:6144\n\tds_read_b128 %4, %12 offset:8192\n\tds_read_b128 %5, %12 offset:10240\n\t"
+                             "ds_read_b128 %6, %12 offset:12288\n\tds_read_b128 %7, %12 offset:14336\n\tds_read_b128 %8, %12 offset:16384\n\t"
+                             "ds_read_b128 %9, %12 offset:18432\n\tds_read_b128 %10, %12 offset:20480\n\tds_read_b128 %11, %12 offset:22528\n\ts_waitcnt lgkmcnt(0)"
+                             : "=&v"(b[0][0]), "=&v"(b[0][1]), "=&v"(b[0][2]), "=&v"(b[0][3]), "=&v"(b[1][0]), "=&v"(b[1][1]),
+                               "=&v"(b[1][2]), "=&v"(b[1][3]), "=&v"(b[2][0]), "=&v"(b[2][1]), "=&v"(b[2][2]), "=&v"(b[2][3]) : "v"(at) : "memory");
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl)
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+                        acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, xa[mb][sub]), __builtin_bit_cast(bf16x8, b[pl][nb]),
+                                                                              acc[mb][nb], 0, 0, 0);
+        }
+    };
+    // the slices behind the one being multiplied are in flight, STAGES - 1 of them; at the end all that is left is waited for at once
+    auto step = [&](auto SET, int k) __attribute__((always_inline)) {
+        constexpr int set = decltype(SET)::value;
+        if (nfull - k > STAGES - 2) wait_vmcnt<(STAGES - 2) * (LOADS + 2 * MB)>();
+        else wait_vmcnt<0>();
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        if (nfull - k > STAGES - 1) issue(std::integral_constant<int, (set + STAGES - 1) % STAGES>{});
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(set, x[set]);
+    };
+    std::integral_constant<int, 0> c0; std::integral_constant<int, 1> c1; std::integral_constant<int, 2> c2;
+    static_assert(STAGES == 3, "sets");
+    if (nfull > 0) issue(c0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (nfull > 1) issue(c1);
+    __builtin_amdgcn_sched_barrier(0);
+    for (int k = 0; k < nfull; k += STAGES) {
+        step(c0, k);
+        if (k + 1 >= nfull) break;
+        step(c1, k + 1);
+        if (k + 2 < nfull) step(c2, k + 2);
+    }
+    if (tail) {
+        // ragged end of d_in: the threads copy it themselves, zero past d_in
+        __syncthreads();
+        const int64_t k0 = (int64_t)nfull_all * XQ_BK;
+        for (int e = tid; e < QROWS * 8; e += 256) {
+            const int row = e >> 3, c = e & 7;
+            uint4 v = make_uint4(0, 0, 0, 0);
+            if (k0 + c * 8 < K) v = *reinterpret_cast<const uint4*>(plane_row(row) + k0 + c * 8);
+            *reinterpret_cast<uint4*>(xq_smem + xq_lds_off(row, c)) = v;
+        }
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int sub = 0; sub < 2; ++sub) {
+                const int64_t k = k0 + lg * 8 + sub * 32;
+                u32x4 v = {0, 0, 0, 0};
+                if (k < K) v = *reinterpret_cast<const u32x4*>(a.X + min(t0 + (wave * MB + mb) * 16 + lm, M - 1) * a.ldx + k);
+                x[0][mb][sub] = v;
+            }
+        __syncthreads();
+        multiply(0, x[0]);
+    }
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        floatx4 one[MB][1];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) one[mb][0] = acc[mb][nb];
+        xq_store<1, MB>(one, M, a.r[nb], a.T[nb], a.TpackT[nb], a.m_pad, a.part[nb], a.Xext[nb], t0, split, wave, lm, lg);
+    }
+}
+// HALF_CU: within what forwards on another stream leave of the LDS
+template <bool HALF_CU>
+constexpr int xq_group_smem(int most) { return std::max(XqRing<1, HALF_CU ? 2 : 0>::STAGES * xq_slot_bytes(1), XQD_STAGES * xqd_loads(most) * 4096); }
+static_assert(xq_group_smem<false>(kXShare) <= 80 * 1024 && xq_group_smem<true>(kXShare) <= 72 * 1024, "two workgroups to a compute unit, one beside forwards");
+template <int MB, bool HALF_CU>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void xq_group_kernel(const KBatch<XqGroupDev> tb) {
+    uint32_t bx, by;
+    const XqGroupDev& a = tb.a[kbatch_find(tb, bx, by)];
+    switch (a.nb) {
+        case 1: xq_bf16_body<1, HALF_CU ? 2 : 0>(a.X, a.ldx, a.M, a.K, a.Qpack[0], a.r[0], a.T[0], a.TpackT[0], a.m_pad, a.part[0], a.Xext[0], bx, by, (uint32_t)a.ns); break;
+        case 2: xq_group_body<2, MB>(a, bx, by); break;
+        case 3: xq_group_body<3, MB>(a, bx, by); break;
+        default: xq_group_body<4, MB>(a, bx, by); break;
+    }
+}
+static_assert(sizeof(KBatch<XqGroupDev>) <= 4096, "kernel arguments");
 
 // sums the d_in splits of xq in fixed order and writes what the unsplit kernel's epilogue writes.  For the planes a workgroup takes
 // 64 tokens of 16 columns and a thread four tokens of a column, so that the stores of a wave are whole rows (with a thread per value,
@@ -854,6 +1034,64 @@ static hipError_t launch_xq_cap(const KBatch<XqDev, CAP>& tb, unsigned blocks, i
     }
 }
 
+template <int MB, bool HALF_CU>
+static hipError_t launch_xq_group(const KBatch<XqGroupDev>& tb, unsigned blocks, int most, hipStream_t st) {
+    static bool set = false;
+    if (!set) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(xq_group_kernel<MB, HALF_CU>), hipFuncAttributeMaxDynamicSharedMemorySize, xq_group_smem<HALF_CU>(kXShare));
+        if (e != hipSuccess) return e;
+        set = true;
+    }
+    hipLaunchKernelGGL((xq_group_kernel<MB, HALF_CU>), dim3(blocks), dim3(256), xq_group_smem<HALF_CU>(most), st, tb);
+    return hipGetLastError();
+}
+// the products of a launch in groups that share X: *done = false where there are none (or not up to 16 columns)
+static hipError_t launch_xq_groups(const KBatch<XqDev>& tb, int rp, bool half_cu, hipStream_t st, bool* done) {
+    *done = false;
+    if (rp != 16) return hipSuccess;
+    KBatch<XqGroupDev> gr;
+    gr.n = 0;
+    int most = 1;
+    int64_t widest = 0;                        // of those that share
+    uint64_t half = 0;                         // workgroups of 128 tokens
+    for (int i = 0; i < tb.n; ++i) {
+        const XqDev& p = tb.a[i];
+        int g = 0;
+        for (; g < gr.n; ++g) {
+            const XqGroupDev& d = gr.a[g];
+            if (d.nb < kXShare && d.X == p.X && d.ldx == p.ldx && d.M == p.M && d.K == p.K && d.m_pad == p.m_pad && d.ns == p.ns && (d.TpackT[0] != nullptr) == (p.TpackT != nullptr)) break;
+        }
+        XqGroupDev& d = gr.a[g];
+        if (g == gr.n) {
+            d.X = p.X; d.ldx = p.ldx; d.M = p.M; d.K = p.K; d.m_pad = p.m_pad; d.ns = p.ns; d.nb = 0;
+            gr.n++;
+            half += (uint64_t)((p.M + 2 * XQ_TOK - 1) / (2 * XQ_TOK)) * (uint64_t)p.ns;
+        }
+        d.Qpack[d.nb] = p.Qpack; d.T[d.nb] = p.T; d.TpackT[d.nb] = p.TpackT; d.part[d.nb] = p.part; d.Xext[d.nb] = p.Xext; d.r[d.nb] = p.r;
+        if (++d.nb > 1) widest = std::max(widest, d.K);
+        most = std::max(most, d.nb);
+    }
+    if (most == 1) return hipSuccess;
+    // Workgroups of 128 tokens read the planes half as often, but are fewer and longer: us a launch of all products of the 8B-sized layers on 16384
+    // tokens (beside their forwards) 524 with 64 tokens and 482 with 128, of 2.3 decoder layers (2048 wide) on 8192 109 and 116, 4B-sized (2560) on
+    // 3001 51.2 and 52.4
+    const int mb = half >= 256 && widest >= 4096 ? 2 : 1;
+    uint64_t blocks = 0;                       // (deepest first, as the products came)
+    for (int g = 0; g < gr.n; ++g) {
+        const int64_t rows = gr.a[g].TpackT[0] ? gr.a[g].m_pad : gr.a[g].M;
+        gr.first[g] = (uint32_t)blocks;
+        const int tok = gr.a[g].nb == 1 ? XQ_TOK : mb * XQ_TOK;
+        gr.gx[g] = (uint32_t)((rows + tok - 1) / tok);
+        blocks += (uint64_t)gr.gx[g] * (uint32_t)gr.a[g].ns;
+    }
+    if (blocks < XQ_GROUP_MIN) return hipSuccess;
+    const unsigned grid = (unsigned)blocks;
+    const hipError_t e = half_cu ? (mb == 2 ? launch_xq_group<2, true>(gr, grid, most, st) : launch_xq_group<1, true>(gr, grid, most, st))
+                                 : (mb == 2 ? launch_xq_group<2, false>(gr, grid, most, st) : launch_xq_group<1, false>(gr, grid, most, st));
+    *done = true;
+    return e;
+}
+
 hipError_t launch_xq_bf16_many(const XqArgs* a, int n, bool half_cu, hipStream_t st) {
     if (n < 0 || n > kBatchMax) return hipErrorInvalidValue;
     int rp = 0;
@@ -916,7 +1154,10 @@ hipError_t launch_xq_bf16_many(const XqArgs* a, int n, bool half_cu, hipStream_t
         }
     }
     if (blocks > 0x7FFFFFFFull || fin_blocks > 0x7FFFFFFFull || fext_blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    hipError_t e = tb.n == 1 ? launch_xq_cap(kbatch_one(tb), (unsigned)blocks, rp, mb, half_cu, st) : launch_xq_cap(tb, (unsigned)blocks, rp, mb, half_cu, st);
+    bool shared = false;
+    hipError_t e = launch_xq_groups(tb, rp, half_cu, st, &shared);
+    if (e != hipSuccess) return e;
+    if (!shared) e = tb.n == 1 ? launch_xq_cap(kbatch_one(tb), (unsigned)blocks, rp, mb, half_cu, st) : launch_xq_cap(tb, (unsigned)blocks, rp, mb, half_cu, st);
     if (e == hipSuccess && fext.n > 0) {
         if (fext.n == 1) hipLaunchKernelGGL(xq_finish_ext_kernel<1>, dim3((unsigned)fext_blocks), dim3(256), 0, st, kbatch_one(fext), rp);
         else hipLaunchKernelGGL(xq_finish_ext_kernel<kBatchMax>, dim3((unsigned)fext_blocks), dim3(256), 0, st, fext, rp);
@@ -1207,6 +1448,157 @@ __global__ __launch_bounds__(ALONE ? 64 * XttAlone<NB>::WAVES : 256) __attribute
     else xtt_bf16_body<NB>(a.X, a.ldx, a.M, a.K, a.TpackT, a.m_pad, a.partial, a.tok_per_split, bx, by);
 }
 
+// Products of several layers that read the same activations (q, k and v; gate and up), up to four with up to 16 columns each: X is read once
+// for all of them.  The form above with the column blocks of NB products; products of the same launch with an X of their own (NB = 1) take it too.  Eight
+// waves: four panels by two halves of the column blocks (NB = 1: the second half only loads).  Sums and bits are those of a product by itself
+struct XttGroupDev {
+    const bf16_t* X; int64_t ldx, M, K, m_pad, tok_per_split;
+    int nb;
+    const bf16_t* T[kXShare]; float* partial[kXShare];
+};
+template <int NB>
+struct XttGroup {
+    static constexpr int NBW = NB <= 2 ? 1 : 2, WAVES = 8;
+    static constexpr int LOADS = (3 * NB + WAVES - 1) / WAVES, XLOADS = 32 / WAVES;
+    static constexpr int STAGE = (LOADS * WAVES + 32) * 1024;
+};
+template <int NB>
+__device__ __forceinline__ void xtt_group_body(const XttGroupDev& a, uint32_t bx, uint32_t by) {
+    typedef XttGroup<NB> S;
+    constexpr int SEGS = 3 * NB, NBW = S::NBW, WAVES = S::WAVES, LOADS = S::LOADS, XLOADS = S::XLOADS, STAGE = S::STAGE, X_AT = LOADS * WAVES * 1024;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    extern __shared__ __align__(16) char xtt_smem[];          // [3 stages]: [segments][16 rows][32 tokens], [4 panels][32 tokens][128 features]
+    typedef __attribute__((address_space(3))) void* lptr_t;
+    typedef const __attribute__((address_space(1))) void* gptr_t;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lc = lane & 15, lg = lane >> 4, panel = wave & 3, half = wave >> 2;
+    const int64_t M = a.M, K = a.K, m_pad = a.m_pad, ldx = a.ldx;
+    const int split = (int)by;
+    const int64_t ts = (int64_t)split * a.tok_per_split, te = min(ts + a.tok_per_split, m_pad);
+    const int64_t dcol = ((int64_t)bx * 4 + panel) * XTT_PANEL + lc * 8;
+    const bf16_t* xcol = a.X + min(dcol, K - 8);              // (features past the end repeat the last, unstored)
+    // segment pl NB + nb: plane pl of product nb (past the last: that once more, into rows nobody reads)
+    const bf16_t* tsrc[LOADS];
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+        const int seg = min(wave + WAVES * i, SEGS - 1);
+        tsrc[i] = a.T[seg % NB] + (int64_t)(16 * (seg / NB) + (lane >> 2)) * m_pad + (lane & 3) * 8;
+    }
+    auto next = [&](int64_t& tb, int& w) __attribute__((always_inline)) {      // (the shares are every fourth step, one share after the other)
+        tb += 4 * XTT_STEP;
+        if (tb >= te) tb = ++w < 4 ? ts + w * XTT_STEP : te;
+    };
+    auto issue = [&](int set, int64_t tb) __attribute__((always_inline)) {
+        tb = min(tb, te - XTT_STEP);                          // (past the last step: that once more)
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i)
+            __builtin_amdgcn_global_load_lds((gptr_t)(tsrc[i] + tb), (lptr_t)(xtt_smem + set * STAGE + (wave + WAVES * i) * 1024), 16, 0, 0);
+#pragma unroll
+        for (int i = 0; i < XLOADS; ++i) {                    // (rows past M meet zero planes)
+            const int q = half * XLOADS + i;
+            __builtin_amdgcn_global_load_lds((gptr_t)(xcol + min(tb + 4 * q + lg, M - 1) * ldx), (lptr_t)(xtt_smem + set * STAGE + X_AT + panel * 8192 + q * 1024), 16, 0, 0);
+        }
+    };
+    // this wave's column blocks nb0, nb0 + 1 (of three the last one twice)
+    const int nb0 = half * NBW, nb1 = min(nb0 + 1, NB - 1);
+    floatx4 acc[NBW][8], tot[NBW][8];
+    auto multiply = [&](int set) __attribute__((always_inline)) {
+        u32x4 t[NBW][3], x[8];
+        const uint32_t at = (uint32_t)(uintptr_t)(lptr_t)(xtt_smem + set * STAGE + lc * 64 + lg * 16), addr0 = at + nb0 * 1024, addr1 = at + nb1 * 1024;
+        const uint32_t xaddr = (uint32_t)(uintptr_t)(lptr_t)(xtt_smem + set * STAGE + X_AT + panel * 8192 + lg * 2048 + lc * 16);
+        if constexpr (NBW == 1)
+            asm volatile("ds_read_b128 %0, %11\n\tds_read_b128 %1, %11 offset:%13\n\tds_read_b128 %2, %11 offset:%14\n\t"
+                                     "ds_read_b128 %3, %12\n\tds_read_b128 %4, %12 offset:256\n\tds_read_b128 %5, %12 offset:512\n\t"
+                                     "ds_read_b128 %6, %12 offset:768\n\tds_read_b128 %7, %12 offset:1024\n\tds_read_b128 %8, %12 offset:1280\n\t"
+                                     "ds_read_b128 %9, %12 offset:1536\n\tds_read_b128 %10, %12 offset:1792\n\ts_waitcnt lgkmcnt(0)"
+                                     : "=&v"(t[0][0]), "=&v"(t[0][1]), "=&v"(t[0][2]), "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]),
+                                       "=&v"(x[3]), "=&v"(x[4]), "=&v"(x[5]), "=&v"(x[6]), "=&v"(x[7])
+                                     : "v"(addr0), "v"(xaddr), "n"(NB * 1024), "n"(2 * NB * 1024) : "memory");
+        else
+            asm volatile("ds_read_b128 %0, %14\n\tds_read_b128 %1, %15\n\tds_read_b128 %2, %14 offset:%17\n\t"
+                                     "ds_read_b128 %3, %15 offset:%17\n\tds_read_b128 %4, %14 offset:%18\n\tds_read_b128 %5, %15 offset:%18\n\t"
+                                     "ds_read_b128 %6, %16\n\tds_read_b128 %7, %16 offset:256\n\tds_read_b128 %8, %16 offset:512\n\t"
+                                     "ds_read_b128 %9, %16 offset:768\n\tds_read_b128 %10, %16 offset:1024\n\tds_read_b128 %11, %16 offset:1280\n\t"
+                                     "ds_read_b128 %12, %16 offset:1536\n\tds_read_b128 %13, %16 offset:1792\n\ts_waitcnt lgkmcnt(0)"
+                                     : "=&v"(t[0][0]), "=&v"(t[NBW - 1][0]), "=&v"(t[0][1]), "=&v"(t[NBW - 1][1]), "=&v"(t[0][2]), "=&v"(t[NBW - 1][2]),
+                                       "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(x[4]), "=&v"(x[5]),
+                                       "=&v"(x[6]), "=&v"(x[7])
+                                     : "v"(addr0), "v"(addr1), "v"(xaddr), "n"(NB * 1024), "n"(2 * NB * 1024) : "memory");
+#pragma unroll
+        for (int j = 0; j < 8; j += 2) {
+            u32x4 b[2];                                       // word q of x[i] holds features 2q (low half) and 2q+1 (high half) of token i
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int pp = 0; pp < 4; ++pp) b[h][pp] = __builtin_amdgcn_perm(x[2 * pp + 1][j >> 1], x[2 * pp][j >> 1], h ? 0x07060302u : 0x05040100u);
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int nb = 0; nb < NBW; ++nb)
+                        acc[nb][j + h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, t[nb][pl]), __builtin_bit_cast(bf16x8, b[h]),
+                                                                                 acc[nb][j + h], 0, 0, 0);
+        }
+    };
+    const bool multiplies = NB > 1 || half == 0;
+#pragma unroll
+    for (int nb = 0; nb < NBW; ++nb)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) tot[nb][j] = floatx4{-0.f, -0.f, -0.f, -0.f};      // (plus the first share: that share)
+    if (ts < te) {
+        int64_t ahead = ts;                                   // the step to be requested next
+        int wa = 0, set = 0;
+        issue(0, ahead);
+        next(ahead, wa);
+        issue(1, ahead);
+        next(ahead, wa);
+        for (int w = 0; w < 4 && ts + w * XTT_STEP < te; ++w) {
+#pragma unroll
+            for (int nb = 0; nb < NBW; ++nb)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) acc[nb][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+            for (int64_t tb = ts + w * XTT_STEP; tb < te; tb += 4 * XTT_STEP) {
+                wait_vmcnt<LOADS + XLOADS>();                      // this wave's loads of the step have landed
+                __builtin_amdgcn_sched_barrier(0);
+                __builtin_amdgcn_s_barrier();                 // everybody's have, and the stage of the step before is free
+                __builtin_amdgcn_sched_barrier(0);
+                issue(set == 0 ? 2 : set - 1, ahead);
+                next(ahead, wa);
+                if (multiplies) multiply(set);
+                set = set == 2 ? 0 : set + 1;
+            }
+#pragma unroll
+            for (int nb = 0; nb < NBW; ++nb)
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) tot[nb][j][e] += acc[nb][j][e];
+        }
+        wait_vmcnt<0>();                                      // (what was fetched past the end)
+    }
+    // D layout: row (k within block) = 4*(lane/16) + e, col = lane%16 -> feature 8*lc + j of the panel
+    if (dcol >= K || !multiplies) return;                     // (d_in is a multiple of 8: a lane's features are all in or all out)
+#pragma unroll
+    for (int nb = 0; nb < NBW; ++nb) {
+        if (nb0 + nb >= NB) break;
+        float* dst = a.partial[nb0 + nb] + ((int64_t)split * K + dcol) * 16 + lg * 4;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) *reinterpret_cast<floatx4*>(dst + j * 16) = tot[nb][j];
+    }
+}
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void xtt_group_kernel(const KBatch<XttGroupDev> tb) {
+    uint32_t bx, by;
+    const XttGroupDev& a = tb.a[kbatch_find(tb, bx, by)];
+    switch (a.nb) {
+        case 1: xtt_group_body<1>(a, bx, by); break;
+        case 2: xtt_group_body<2>(a, bx, by); break;
+        case 3: xtt_group_body<3>(a, bx, by); break;
+        default: xtt_group_body<4>(a, bx, by); break;
+    }
+}
+
 static int64_t xtt_tokens_per_split(int64_t m_pad, int nsplit) {
     const int64_t t = (m_pad + nsplit - 1) / nsplit;
     return (t + 4 * XTT_STEP - 1) / (4 * XTT_STEP) * (4 * XTT_STEP);
@@ -1243,8 +1635,67 @@ static hipError_t launch_xtt_cap(const KBatch<XttDev, CAP>& tb, unsigned blocks,
     }
 }
 
-hipError_t launch_xtt_bf16_many(const XttArgs* a, int n, hipStream_t st) {
+// the same for a launch of up to 16 columns with products that share X: *done = false where there are none
+static hipError_t launch_xtt_groups(const XttArgs* a, int n, hipStream_t st, bool* done) {
+    *done = false;
+    KBatch<XttGroupDev> tb;
+    tb.n = 0;
+    int nsplit[kBatchMax], most = 1;
+    for (int m = 0; m < n; ++m) {
+        if (a[m].M == 0 || a[m].K == 0) continue;
+        if (a[m].rp != 16) return hipSuccess;
+        int g = 0;
+        for (; g < tb.n; ++g)
+            if (tb.a[g].nb < kXShare && tb.a[g].X == a[m].X && tb.a[g].ldx == a[m].ldx && tb.a[g].M == a[m].M && tb.a[g].K == a[m].K && tb.a[g].m_pad == a[m].m_pad &&
+                nsplit[g] == a[m].nsplit) break;
+        XttGroupDev& d = tb.a[g];
+        if (g == tb.n) {
+            d.X = a[m].X; d.ldx = a[m].ldx; d.M = a[m].M; d.K = a[m].K; d.m_pad = a[m].m_pad;
+            d.tok_per_split = xtt_tokens_per_split(a[m].m_pad, a[m].nsplit);
+            d.nb = 0;
+            nsplit[tb.n++] = a[m].nsplit;
+        }
+        d.T[d.nb] = a[m].TpackT;
+        d.partial[d.nb++] = a[m].partial;
+        most = d.nb > most ? d.nb : most;
+    }
+    if (most == 1) return hipSuccess;
+    // the longest ranges first, and of equal ones those with the most columns
+    KBatch<XttGroupDev> sorted;
+    sorted.n = 0;
+    uint64_t blocks = 0;
+    bool taken[kBatchMax] = {};
+    for (int i = 0; i < tb.n; ++i) {
+        int at = -1;
+        for (int g = 0; g < tb.n; ++g)
+            if (!taken[g] && (at < 0 || tb.a[g].tok_per_split > tb.a[at].tok_per_split || (tb.a[g].tok_per_split == tb.a[at].tok_per_split && tb.a[g].nb > tb.a[at].nb))) at = g;
+        taken[at] = true;
+        const uint32_t gx = (uint32_t)((tb.a[at].K + 4 * XTT_PANEL - 1) / (4 * XTT_PANEL));
+        sorted.first[i] = (uint32_t)blocks; sorted.gx[i] = gx; sorted.a[i] = tb.a[at];
+        sorted.n++;
+        blocks += (uint64_t)gx * (uint32_t)nsplit[at];
+    }
+    if (blocks < XTT_GROUP_MIN) return hipSuccess;
+    if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    static bool set = false;
+    if (!set) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(xtt_group_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 3 * XttGroup<4>::STAGE);
+        if (e != hipSuccess) return e;
+        set = true;
+    }
+    const int smem = 3 * (most <= 2 ? XttGroup<2>::STAGE : XttGroup<4>::STAGE);
+    hipLaunchKernelGGL(xtt_group_kernel, dim3((unsigned)blocks), dim3(512), smem, st, sorted);
+    *done = true;
+    return hipGetLastError();
+}
+
+hipError_t launch_xtt_bf16_many(const XttArgs* a, int n, bool half_cu, hipStream_t st) {
     if (n < 0 || n > kBatchMax) return hipErrorInvalidValue;
+    if (!half_cu) {
+        bool done;
+        const hipError_t e = launch_xtt_groups(a, n, st, &done);
+        if (e != hipSuccess || done) return e;
+    }
     KBatch<XttDev> tb;
     tb.n = 0;
     int64_t busy = 0, steps = 0;
@@ -1290,7 +1741,7 @@ hipError_t launch_xtt_bf16_many(const XttArgs* a, int n, hipStream_t st) {
 hipError_t launch_xtt_bf16(const bf16_t* X, int64_t ldx, int64_t M, int64_t K, const bf16_t* TpackT, int64_t m_pad,
                            int rp, float* partial, int nsplit, hipStream_t st) {
     const XttArgs a{X, ldx, M, K, TpackT, m_pad, rp, partial, nsplit};
-    return launch_xtt_bf16_many(&a, 1, st);
+    return launch_xtt_bf16_many(&a, 1, false, st);
 }
 
 // S[d][k] = sum over splits (fp64, fixed order) of partial[s][d][rp]
