@@ -479,9 +479,10 @@ int stage_sketch_many_f32(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, cons
 }
 
 // one stage for the jobs idx[0..n) (one dtype): Omega^T planes + range sketch, or T = X Q planes + power sketch
-// raw (power sketch; nullable): per job of idx the column that the last factorisation left to be normalised, NULL where Q is ready
+// raw (power sketch; nullable): per job of idx the column that the last factorisation left to be normalised, NULL where Q is ready.  summed: where the
+// partial sums of that column are all there is
 // half_cu (here and below): forwards on another stream may hold half of every compute unit
-int stage_sketch_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, const int* idx, int n, bool range, bool half_cu, const float* const* raw = nullptr) {
+int stage_sketch_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, const int* idx, int n, bool range, bool half_cu, const float* const* raw = nullptr, const bool* summed = nullptr) {
     if (n > 0 && jobs[idx[0]].L.dtype != AGZO_BF16) return stage_sketch_many_f32(ctx, jobs, idx, n, range);
     hipStream_t st = ctx->stream;
     if (range) {
@@ -498,7 +499,12 @@ int stage_sketch_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, const in
             const LayerJob& j = jobs[idx[i]];
             q[i] = XqArgs{static_cast<const bf16_t*>(j.X), j.L.ldx, j.L.n_tokens, j.L.d_in, wsh(ctx, j.p.off_pack), j.L.r, j.p.rp,
                           nullptr, wsh(ctx, j.p.off_TpackT), j.p.m_pad, wsf(ctx, j.p.off_xqpart), nullptr, wsf(ctx, j.p.off_Q)};
-            if (raw && raw[i]) {
+            if (summed && summed[i]) {
+                q[i].Q = nullptr;
+                q[i].splits = wsf(ctx, j.p.off_xtt);
+                q[i].nsplit = j.p.nsplit;
+                q[i].flag = ctx->flag;
+            } else if (raw && raw[i]) {
                 q[i].Q = raw[i];
                 q[i].norm2 = reinterpret_cast<const double*>(ctx->ws + j.p.off_qr);
                 q[i].norm_blocks = qr_norm_blocks(j.L.d_in);
@@ -512,7 +518,7 @@ int stage_sketch_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, const in
     for (int i = 0; i < n; ++i) {
         const LayerJob& j = jobs[idx[i]];
         t[i] = XttArgs{static_cast<const bf16_t*>(j.X), j.L.ldx, j.L.n_tokens, j.L.d_in, wsh(ctx, j.p.off_TpackT), j.p.m_pad, j.p.rp,
-                       wsf(ctx, j.p.off_xtt), j.p.nsplit};
+                       wsf(ctx, j.p.off_xtt), j.p.nsplit, j.L.r == 1};
     }
     ProfScope ps(ctx, AGZO_PROF_XTT);
     HIPCHK(launch_xtt_bf16_many(t, n, half_cu, st));
@@ -554,25 +560,32 @@ int basis_many_impl(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, int K, int
         for (int k = 0; k <= K; ++k) {
             QrArgs q[kBatchMax];
             const float* raw[kBatchMax];
+            bool summed[kBatchMax];
+            int nq = 0;
             for (int i = 0; i < n; ++i) {
                 const LayerJob& j = jobs[idx[i]];
+                // a single column between power steps: the projection that follows normalises its result, one launch less, and a short one it also adds up
+                const bool defer = bf && k < K && xq_narrow(j.L.n_tokens, j.L.d_in, j.L.r), partials = bf && !(k == 0 && given[i]);
+                summed[i] = n == 1 && defer && partials && xq_sums_column(j.L.n_tokens, j.L.d_in, j.p.nsplit);
+                raw[i] = nullptr;
+                if (summed[i]) continue;
                 float* out = (k == K) ? j.B : wsf(ctx, j.p.off_Q);
                 bf16_t* planes = reads_planes(j.L) ? wsh(ctx, j.p.off_pack) : nullptr;
-                if ((k == 0 && given[i]) || !bf)
-                    q[i] = QrArgs{(k == 0 && given[i]) ? j.S0 : wsf(ctx, j.p.off_S), nullptr, 0, j.p.rp, nullptr, j.L.d_in, j.L.r, out,
-                                  planes, ctx->ws + j.p.off_qr};
+                QrArgs& one = q[nq++];
+                if (!partials)
+                    one = QrArgs{(k == 0 && given[i]) ? j.S0 : wsf(ctx, j.p.off_S), nullptr, 0, j.p.rp, nullptr, j.L.d_in, j.L.r, out,
+                                 planes, ctx->ws + j.p.off_qr};
                 else
-                    q[i] = QrArgs{nullptr, wsf(ctx, j.p.off_xtt), j.p.nsplit, j.p.rp, wsf(ctx, j.p.off_S), j.L.d_in, j.L.r, out,
-                                  planes, ctx->ws + j.p.off_qr};
-                // a single column between power steps: the projection that follows normalises its result, one launch less
-                q[i].defer = bf && k < K && xq_narrow(j.L.n_tokens, j.L.d_in, j.L.r);
-                raw[i] = !q[i].defer ? nullptr : q[i].splits ? q[i].S_out : q[i].S;
+                    one = QrArgs{nullptr, wsf(ctx, j.p.off_xtt), j.p.nsplit, j.p.rp, wsf(ctx, j.p.off_S), j.L.d_in, j.L.r, out,
+                                 planes, ctx->ws + j.p.off_qr};
+                one.defer = defer;
+                if (defer) raw[i] = one.splits ? one.S_out : one.S;
             }
-            {
+            if (nq) {
                 ProfScope ps(ctx, AGZO_PROF_QR);
-                HIPCHK(launch_qr_many(q, n, ctx->flag, k == K, ctx->stream));
+                HIPCHK(launch_qr_many(q, nq, ctx->flag, k == K, ctx->stream));
             }
-            if (k < K) TRY(stage_sketch_many(ctx, jobs, idx, n, false, half_cu, raw));
+            if (k < K) TRY(stage_sketch_many(ctx, jobs, idx, n, false, half_cu, raw, summed));
         }
     }
     return 0;

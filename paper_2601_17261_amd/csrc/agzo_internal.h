@@ -256,11 +256,15 @@ struct XqArgs {
     const float* Q = nullptr;      // the fp32 [K][r] of which Qpack are the planes: what xq_narrow() products read instead
     // xq_narrow() products: Q is still to be normalised, by the root of the sum of norm_blocks values; *flag = 1 if that is not positive
     const double* norm2 = nullptr; int norm_blocks = 0; int* flag = nullptr;
+    // ... or still to be summed from nsplit partial columns [nsplit][K] (xq_sums_column()) and then normalised; *flag as above
+    const float* splits = nullptr; int nsplit = 0;
     // the W side of a forward's extension operands, written by the product's last launch or one behind it (NULL: not)
     const struct GemmExtArgs* ext = nullptr;
 };
 // true: a product that multiplies the fp32 factor itself (one column, few tokens); Qpack may then be NULL
 bool xq_narrow(int64_t M, int64_t K, int r);
+// true: such a product, alone in its launch, adds up the partial sums of its column itself
+bool xq_sums_column(int64_t M, int64_t K, int nsplit);
 // up to kBatchMax products with the same rp in one launch (plus one finishing launch if any of them splits d_in); m_pad is a multiple of 4
 // half_cu: forwards on another stream hold half of every compute unit
 hipError_t launch_xq_bf16_many(const XqArgs* a, int n, bool half_cu, hipStream_t st);
@@ -272,7 +276,8 @@ int xtt_num_splits(int64_t M, int64_t K);
 // partial[s][d][rp] = sum over token range s of X[t][d] * T[t][k]
 hipError_t launch_xtt_bf16(const bf16_t* X, int64_t ldx, int64_t M, int64_t K, const bf16_t* TpackT, int64_t m_pad,
                            int rp, float* partial, int nsplit, hipStream_t st);
-struct XttArgs { const bf16_t* X; int64_t ldx, M, K; const bf16_t* TpackT; int64_t m_pad; int rp; float* partial; int nsplit; };
+// one = true: only the first column is stored, [s][d]
+struct XttArgs { const bf16_t* X; int64_t ldx, M, K; const bf16_t* TpackT; int64_t m_pad; int rp; float* partial; int nsplit; bool one = false; };
 // (half_cu: as above)
 hipError_t launch_xtt_bf16_many(const XttArgs* a, int n, bool half_cu, hipStream_t st);
 hipError_t launch_reduce_splits(const float* partial, int nsplit, int64_t d, int rp, int r, float* S, hipStream_t st);
@@ -281,7 +286,7 @@ hipError_t launch_pack_planes(const float* Q, int64_t d, int r, int rp, bf16_t* 
 
 // qr.hip : CholeskyQR2
 size_t qr_workspace_bytes(int64_t d, int r);
-// S explicit, or splits [nsplit][d][rp] (then their fp32 sum is also stored to S_out); Q fp32 out;
+// S explicit, or splits [nsplit][d][rp] ([nsplit][d] for r = 1; then their fp32 sum is also stored to S_out); Q fp32 out;
 // planes (nullable) bf16 [3][rp][d]; refine = false: single Cholesky pass (for iterates that are sketched again)
 hipError_t launch_qr(const float* S, const float* splits, int nsplit, int rp, float* S_out, int64_t d, int r, float* Q,
                      bf16_t* planes, void* workspace, int* numeric_flag, bool refine, hipStream_t st);

@@ -331,7 +331,7 @@ __device__ __forceinline__ doublex4 apply_rinv(const Tin (&y)[RP / 4], const dou
 }
 
 // per problem, what the launches of one factorisation need.  Input: S fp32 [d][r], or (splits != nullptr) partial sketches
-// [nsplit][d][rp] whose sum is stored to S_out as fp32 and used (in its rounded form) for the factorisation
+// [nsplit][d][rp] ([nsplit][d] for r = 1) whose sum is stored to S_out as fp32 and used (in its rounded form) for the factorisation
 struct QrDev {
     const float* S; const float* splits; int nsplit; float* S_out; const float* Sin;
     int64_t d; int r; int nblk;
@@ -658,7 +658,7 @@ constexpr int QR1_ROWS = 256;    // rows per workgroup, one per thread: the chai
 // launch 1: y_i = the column (or the fp64 sum of its partial sketches in split order, rounded to fp32 and stored to
 // S_out like the general path does), partial[b] = sum of y_i^2 over the block's rows (fp64, fixed order)
 template <int CAP>
-__global__ __launch_bounds__(256) void qr1_sumsq_kernel(const KBatch<QrDev, CAP> tb, int rp) {
+__global__ __launch_bounds__(256) void qr1_sumsq_kernel(const KBatch<QrDev, CAP> tb) {
     __shared__ double red[4];
     uint32_t bx, by;
     const QrDev& a = tb.a[kbatch_find(tb, bx, by)];
@@ -671,7 +671,7 @@ __global__ __launch_bounds__(256) void qr1_sumsq_kernel(const KBatch<QrDev, CAP>
             for (int sp0 = 0; sp0 < a.nsplit; sp0 += 16) {
                 float x[16];
 #pragma unroll
-                for (int u = 0; u < 16; ++u) x[u] = sp0 + u < a.nsplit ? a.splits[((int64_t)(sp0 + u) * a.d + i) * rp] : 0.f;
+                for (int u = 0; u < 16; ++u) x[u] = sp0 + u < a.nsplit ? a.splits[(int64_t)(sp0 + u) * a.d + i] : 0.f;
 #pragma unroll
                 for (int u = 0; u < 16; ++u) acc += (double)x[u];
             }
@@ -728,11 +728,73 @@ __global__ __launch_bounds__(256) void qr1_scale_kernel(const KBatch<QrDev, CAP>
 }
 int qr_norm_blocks(int64_t d) { return (int)((d + QR1_ROWS - 1) / QR1_ROWS); }
 
+// Both launches as one workgroup a column, for columns that nobody else has to read in between: the sums in the same order, so the same bits.
+// The last launch of a lone layer's basis: 37.4 us with the two and 36.6 so at 1024 wide on 128 tokens, 41.4 and 40.7 at 256 on 2048.  1536 wide it is the
+// same and 2048 wide 1 to 3 % slower (1000 tokens: 48.3 and 49.8), so a row a thread is the most it takes
+constexpr int QR1S_ROWS = 1024;
+template <int CAP>
+__global__ __launch_bounds__(QR1S_ROWS) void qr1_small_kernel(const KBatch<QrDev, CAP> tb, int rp, int* flag) {
+    __shared__ double red[QR1S_ROWS / 64];
+    const QrDev& a = tb.a[CAP == 1 ? 0 : blockIdx.x];
+    const int i = threadIdx.x, d = (int)a.d, nsplit = a.nsplit, at = min(i, d - 1);
+    float y;
+    if (a.splits != nullptr) {
+        double acc = 0.0;
+        for (int sp0 = 0; sp0 < nsplit; sp0 += 16) {
+            float x[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) x[u] = sp0 + u < nsplit ? a.splits[(int64_t)(sp0 + u) * d + at] : 0.f;
+#pragma unroll
+            for (int u = 0; u < 16; ++u) acc += (double)x[u];
+        }
+        y = (float)acc;
+    } else {
+        y = a.S[at];
+    }
+    if (i >= d) y = 0.f;
+    double ss = (double)y * (double)y;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
+    if ((i & 63) == 0) red[i >> 6] = ss;
+    __syncthreads();
+    double sum = 0.0;
+    for (int b = 0; b < a.nblk; ++b) sum += (red[4 * b] + red[4 * b + 1]) + (red[4 * b + 2] + red[4 * b + 3]);
+    if (!(sum > 0.0)) {
+        if (i == 0) *flag = 1;
+        sum = 1.0;
+    }
+    const double scale = 1.0 / sqrt(sum);
+    const float q = (float)((double)y * scale);
+    if (i < d) a.Q[i] = q;
+    if (a.planes == nullptr) return;
+    if (i < d) {
+        bf16_t part[3];
+        split3_bf16(q, part[0], part[1], part[2]);
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl) a.planes[(int64_t)pl * rp * d + i] = part[pl];
+    }
+    const int rest = rp - 1;                                   // the padding columns: zero
+    for (int row = 0; row < 3 * rest; ++row) {
+        const int pl = row / rest;
+        if (i < d) a.planes[((int64_t)pl * rp + 1 + row - pl * rest) * d + i] = 0;
+    }
+}
+template <int CAP>
+static bool qr1_small(const KBatch<QrDev, CAP>& tb, const KBatch<QrDev, CAP>& scaled) {
+    for (int m = 0; m < tb.n; ++m)
+        if (tb.a[m].d > QR1S_ROWS) return false;
+    return scaled.n == tb.n;
+}
+
 // tb: every column; scaled: those that this factorisation normalises itself
 template <int CAP>
 static hipError_t launch_qr1(const KBatch<QrDev, CAP>& tb, unsigned blocks, const KBatch<QrDev, CAP>& scaled, unsigned scaled_blocks, int rp, int* flag,
-                             hipStream_t st) {
-    hipLaunchKernelGGL(qr1_sumsq_kernel<CAP>, dim3(blocks), dim3(256), 0, st, tb, rp);
+                             bool refine, hipStream_t st) {
+    if (refine && qr1_small(tb, scaled)) {
+        hipLaunchKernelGGL(qr1_small_kernel<CAP>, dim3((unsigned)tb.n), dim3(QR1S_ROWS), 0, st, tb, rp, flag);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(qr1_sumsq_kernel<CAP>, dim3(blocks), dim3(256), 0, st, tb);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || scaled_blocks == 0) return e;      // the launch below consumes what this one would have written
     hipLaunchKernelGGL(qr1_scale_kernel<CAP>, dim3(scaled_blocks), dim3(256), 0, st, scaled, rp, flag);
@@ -860,8 +922,12 @@ hipError_t launch_qr_many(const QrArgs* a, int n, int* numeric_flag, bool refine
     if (tb.n == 0) return hipSuccess;
     if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
     if (rank1 == 1) {
-        if (tb.n == 1) return launch_qr1(kbatch_one(tb), (unsigned)blocks, kbatch_one(tb), (unsigned)scaled_blocks, rp, numeric_flag, st);
-        return launch_qr1(tb, (unsigned)blocks, scaled, (unsigned)scaled_blocks, rp, numeric_flag, st);
+        if (tb.n == 1) {
+            KBatch<QrDev, 1> one = kbatch_one(tb), none = one;
+            none.n = scaled.n;
+            return launch_qr1(one, (unsigned)blocks, none, (unsigned)scaled_blocks, rp, numeric_flag, refine, st);
+        }
+        return launch_qr1(tb, (unsigned)blocks, scaled, (unsigned)scaled_blocks, rp, numeric_flag, refine, st);
     }
     if (tb.n == 1) return launch_qr_cap(kbatch_one(tb), (unsigned)blocks, rp, numeric_flag, refine, st);
     return launch_qr_cap(tb, (unsigned)blocks, rp, numeric_flag, refine, st);

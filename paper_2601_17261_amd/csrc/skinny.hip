@@ -707,12 +707,25 @@ struct XqNarrowDev {
     float* T; bf16_t* TpackT; bf16_t* Xext;
     int kw, vec;                 // waves that share d_in; 16-byte loads of Q
     const double* norm2; int norm_blocks; int* flag;
+    const float* splits; int nsplit;
 };
+// A column of partial sums that every workgroup adds up for itself, instead of a launch that does: up to 16 loads a thread, 32 for one or two rows of
+// the column each.  A lone layer's basis (K = 3) with that launch and so, us: 256 wide on 100 tokens 37.2 and 32.8, on 2048 51.8 and 41.2; 512 on 2048 51.5
+// and 47.1; 1024 on 432 41.9 and 39.9.  Beyond the lines: 1024 on 1000 (two turns of loads) 45.0 and 46.1, on 2000 (four) 52.5 and 58.6; 2048 on 100
+// 40.6 and 41.5, on 256 41.9 and 43.0.  Many layers at once (686 workgroups, where the sums wait for each other) 12 a launch and 19.5, for a launch
+// less: a product alone in its launch, of a workgroup a compute unit at most
+constexpr int XQN_SUM_ROWS = 1024;
 static int xqn_waves(int64_t K) { return K > 3 * XQN_CHUNK ? 4 : K > XQN_CHUNK ? 2 : 1; }
+bool xq_sums_column(int64_t M, int64_t K, int nsplit) {
+    return K <= XQN_SUM_ROWS && (K + 255) / 256 * nsplit <= (K <= 512 ? 32 : 16) && M * xqn_waves(K) <= 256 * 4 * XQN_TOK;
+}
 
+template <bool SUMS>
 __device__ __forceinline__ void xq_narrow_body(const XqNarrowDev& a, uint32_t bx) {
     constexpr int U = 2;                                        // chunks in flight
     __shared__ float part[4][XQN_TOK];
+    __shared__ __align__(16) float column[SUMS ? XQN_SUM_ROWS : 4];
+    __shared__ double norms[SUMS ? XQN_SUM_ROWS / 256 : 1][4];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kw = a.kw, wk = wave % kw, wt = wave / kw;
     const int64_t K = a.K, tw = ((int64_t)bx * (4 / kw) + wt) * XQN_TOK;        // the wave's first token
@@ -735,6 +748,7 @@ __device__ __forceinline__ void xq_narrow_body(const XqNarrowDev& a, uint32_t bx
             const int64_t k = min((c0 + u * kw) * XQN_CHUNK + 8 * lane, K - 8);
 #pragma unroll
             for (int t = 0; t < XQN_TOK; ++t) x[u][t] = *reinterpret_cast<const uint4*>(xr[t] + k);
+            if constexpr (SUMS) continue;
             const float* src = a.Q + k;
             if (a.vec) {
 #pragma unroll
@@ -747,7 +761,58 @@ __device__ __forceinline__ void xq_narrow_body(const XqNarrowDev& a, uint32_t bx
                 for (int i = 0; i < 8; ++i) q[u][i] = src[i];
             }
         }
-        if (a.norm2 != nullptr && c0 == wk) {                      // (behind the first chunks' loads: ahead of them the bases of 12288-wide layers take 1 to 4 % longer)
+        if (SUMS && c0 == wk) {                     // (every wave has a chunk: all of them are here together)
+            const int rows = (int)K, nsplit = a.nsplit, blocks = (rows + 255) / 256, loads = blocks * nsplit;
+            double sum = 0.0;
+            int ls = 0, lrow = tid, s = 0, row = tid;
+            for (int e0 = 0; e0 < loads; e0 += 16) {                // (uniform)
+                float v[16];
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    v[e] = e0 + e < loads ? a.splits[ls * rows + min(lrow, rows - 1)] : 0.f;
+                    if (++ls == nsplit) { ls = 0; lrow += 256; }
+                }
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    if (e0 + e >= loads) break;
+                    sum += (double)v[e];
+                    if (++s == nsplit) {
+                        column[row] = row < rows ? (float)sum : 0.f;
+                        sum = 0.0; s = 0; row += 256;
+                    }
+                }
+            }
+            // the squared norm as qr1_sumsq_kernel and the branch above add it up; four blocks of 256 rows side by side (of those past the end
+            // nothing is used)
+            for (int b0 = 0; b0 < blocks; b0 += 4) {
+                double ss[4];
+#pragma unroll
+                for (int b = 0; b < 4; ++b) ss[b] = (double)column[(b0 + b) * 256 + tid] * (double)column[(b0 + b) * 256 + tid];
+#pragma unroll
+                for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) ss[b] += __shfl_xor(ss[b], off);
+                if (lane == 0)
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) norms[b0 + b][wave] = ss[b];
+            }
+            __syncthreads();
+            for (int b = 0; b < blocks; ++b) sum += (norms[b][0] + norms[b][1]) + (norms[b][2] + norms[b][3]);
+            if (!(sum > 0.0)) {
+                if (tid == 0 && bx == 0) *a.flag = 1;
+                sum = 1.0;
+            }
+            down = ((__double2hiint(sum) >> 20) - 1023) >> 1;
+            scale = ldexp(1.0 / sqrt(sum), down);
+        }
+        if constexpr (SUMS)
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int k = (int)min((c0 + u * kw) * XQN_CHUNK + 8 * lane, K - 8);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) q[u][i] = column[k + i];
+            }
+        if (!SUMS && a.norm2 != nullptr && c0 == wk) {                      // (behind the first chunks' loads: ahead of them the bases of 12288-wide layers take 1 to 4 % longer)
             double sum = 0.0;
             for (int b0 = 0; b0 < a.norm_blocks; b0 += 16) {       // uniform: every thread adds the same values
                 double v[16];
@@ -798,11 +863,11 @@ __device__ __forceinline__ void xq_narrow_body(const XqNarrowDev& a, uint32_t bx
     }
     xq_emit(v, a.M, 1, 16, a.T, a.TpackT, a.m_pad, a.Xext, ((int64_t)bx * (4 / kw) + g) * XQN_TOK, k);
 }
-template <int CAP>
+template <int CAP, bool SUMS>
 __global__ __launch_bounds__(256) void xq_narrow_many_kernel(const KBatch<XqNarrowDev, CAP> tb) {
     uint32_t bx, by;
     const XqNarrowDev& a = tb.a[kbatch_find(tb, bx, by)];
-    xq_narrow_body(a, bx);
+    xq_narrow_body<SUMS>(a, bx);
 }
 // with the W sides of forwards' extension operands
 struct XqNarrowExtDev { XqNarrowDev q; uint32_t blocks; ExtDev ext; };
@@ -811,13 +876,13 @@ template <int CAP>
 __global__ __launch_bounds__(256) void xq_narrow_ext_kernel(const KBatch<XqNarrowExtDev, CAP> tb) {
     uint32_t bx, by;
     const XqNarrowExtDev& a = tb.a[kbatch_find(tb, bx, by)];
-    if (bx < a.blocks) xq_narrow_body(a.q, bx);
+    if (bx < a.blocks) xq_narrow_body<false>(a.q, bx);
     else ext_prep_body(a.ext, (int64_t)(bx - a.blocks) * 256 + threadIdx.x);
 }
 
 static XqNarrowDev xqn_dev(const XqArgs& a, uint64_t& workgroups) {
     XqNarrowDev d{a.X, a.Q, a.ldx, a.M, a.K, a.m_pad, a.T, a.TpackT, a.Xext, xqn_waves(a.K), (reinterpret_cast<uintptr_t>(a.Q) & 15) == 0,
-                  a.norm2, a.norm_blocks, a.flag};
+                  a.norm2, a.norm_blocks, a.flag, a.splits, a.nsplit};
     const int64_t tok = XQN_TOK * (4 / d.kw);
     workgroups = (uint64_t)(((a.TpackT ? a.m_pad : a.M) + tok - 1) / tok);
     return d;
@@ -844,8 +909,9 @@ static hipError_t launch_xq_narrow(const XqArgs* const* a, int n, hipStream_t st
         }
         if (blocks > 0x7FFFFFFFull || eblocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
     }
-    if (tb.n == 1) hipLaunchKernelGGL(xq_narrow_many_kernel<1>, dim3((unsigned)blocks), dim3(256), 0, st, kbatch_one(tb));
-    else if (tb.n > 1) hipLaunchKernelGGL(xq_narrow_many_kernel<kBatchMax>, dim3((unsigned)blocks), dim3(256), 0, st, tb);
+    if (tb.n == 1 && tb.a[0].splits) hipLaunchKernelGGL((xq_narrow_many_kernel<1, true>), dim3((unsigned)blocks), dim3(256), 0, st, kbatch_one(tb));
+    else if (tb.n == 1) hipLaunchKernelGGL((xq_narrow_many_kernel<1, false>), dim3((unsigned)blocks), dim3(256), 0, st, kbatch_one(tb));
+    else if (tb.n > 1) hipLaunchKernelGGL((xq_narrow_many_kernel<kBatchMax, false>), dim3((unsigned)blocks), dim3(256), 0, st, tb);
     const hipError_t err = tb.n > 0 ? hipGetLastError() : hipSuccess;
     if (err != hipSuccess || eb.n == 0) return err;
     if (eb.n == 1) hipLaunchKernelGGL(xq_narrow_ext_kernel<1>, dim3((unsigned)eblocks), dim3(256), 0, st, kbatch_one(eb));
@@ -1107,7 +1173,7 @@ hipError_t launch_xq_bf16_many(const XqArgs* a, int n, bool half_cu, hipStream_t
         if (rp == 0) rp = a[m].rp;
         if (a[m].rp != rp || a[m].m_pad % 4 || (a[m].ext && (a[m].ext->planes || a[m].ext->P))) return hipErrorInvalidValue;       // one padded rank per launch
         if (xq_narrow(a[m].M, a[m].K, a[m].r)) {
-            if (!a[m].Q) return hipErrorInvalidValue;
+            if (a[m].splits ? n > 1 || a[m].ext || !xq_sums_column(a[m].M, a[m].K, a[m].nsplit) : !a[m].Q) return hipErrorInvalidValue;
             narrow[n_narrow++] = &a[m];
             continue;
         }
@@ -1200,7 +1266,7 @@ int xtt_num_splits(int64_t M, int64_t K) {
 template <int NB>
 __device__ __forceinline__ void xtt_bf16_body(const bf16_t* __restrict__ X, int64_t ldx, int64_t M, int64_t K,
                                               const bf16_t* __restrict__ TpackT, int64_t m_pad,
-                                              float* __restrict__ partial, int64_t tok_per_split, uint32_t bx, uint32_t by) {
+                                              float* __restrict__ partial, int64_t tok_per_split, int one, uint32_t bx, uint32_t by) {
     constexpr int RP = NB * 16;
     extern __shared__ __align__(16) float sbuf[];   // [XTT_PANEL][RP]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1270,6 +1336,16 @@ __device__ __forceinline__ void xtt_bf16_body(const bf16_t* __restrict__ X, int6
         }
     }
     // D layout: row (k within block) = 4*(lane/16) + e, col = lane%16 -> feature db + 8*lc + j
+    if (NB == 1 && one) {
+        // the first column alone: the waves' sums side by side, added in the same order
+        if (lg == 0)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) sbuf[wave * XTT_PANEL + lc * 8 + j] = acc[0][j][0];
+        __syncthreads();
+        if (tid < XTT_PANEL && db + tid < K)
+            partial[(int64_t)split * K + db + tid] = ((sbuf[tid] + sbuf[XTT_PANEL + tid]) + sbuf[2 * XTT_PANEL + tid]) + sbuf[3 * XTT_PANEL + tid];
+        return;
+    }
     for (int w = 0; w < 4; ++w) {
         if (wave == w) {
 #pragma unroll
@@ -1439,13 +1515,14 @@ struct XttDev {
     const bf16_t* X; int64_t ldx, M, K;
     const bf16_t* TpackT; int64_t m_pad;
     float* partial; int64_t tok_per_split;
+    int one;
 };
 template <int NB, bool ALONE, int CAP>
 __global__ __launch_bounds__(ALONE ? 64 * XttAlone<NB>::WAVES : 256) __attribute__((amdgpu_waves_per_eu(ALONE ? XttAlone<NB>::WAVES / 4 : NB == 2 ? 2 : 1))) void xtt_bf16_many_kernel(const KBatch<XttDev, CAP> tb) {
     uint32_t bx, by;
     const XttDev& a = tb.a[kbatch_find(tb, bx, by)];
     if constexpr (ALONE) xtt_alone_body<NB>(a.X, a.ldx, a.M, a.K, a.TpackT, a.m_pad, a.partial, a.tok_per_split, bx, by);
-    else xtt_bf16_body<NB>(a.X, a.ldx, a.M, a.K, a.TpackT, a.m_pad, a.partial, a.tok_per_split, bx, by);
+    else xtt_bf16_body<NB>(a.X, a.ldx, a.M, a.K, a.TpackT, a.m_pad, a.partial, a.tok_per_split, a.one, bx, by);
 }
 
 // Products of several layers that read the same activations (q, k and v; gate and up), up to four with up to 16 columns each: X is read once
@@ -1453,7 +1530,7 @@ __global__ __launch_bounds__(ALONE ? 64 * XttAlone<NB>::WAVES : 256) __attribute
 // waves: four panels by two halves of the column blocks (NB = 1: the second half only loads).  Sums and bits are those of a product by itself
 struct XttGroupDev {
     const bf16_t* X; int64_t ldx, M, K, m_pad, tok_per_split;
-    int nb;
+    int nb, one;
     const bf16_t* T[kXShare]; float* partial[kXShare];
 };
 template <int NB>
@@ -1583,6 +1660,13 @@ __device__ __forceinline__ void xtt_group_body(const XttGroupDev& a, uint32_t bx
 #pragma unroll
     for (int nb = 0; nb < NBW; ++nb) {
         if (nb0 + nb >= NB) break;
+        if (a.one) {                                          // the first column alone
+            float* dst = a.partial[nb0 + nb] + (int64_t)split * K + dcol;
+            if (lg == 0)
+#pragma unroll
+                for (int j = 0; j < 8; j += 4) *reinterpret_cast<floatx4*>(dst + j) = floatx4{tot[nb][j][0], tot[nb][j + 1][0], tot[nb][j + 2][0], tot[nb][j + 3][0]};
+            continue;
+        }
         float* dst = a.partial[nb0 + nb] + ((int64_t)split * K + dcol) * 16 + lg * 4;
 #pragma unroll
         for (int j = 0; j < 8; ++j) *reinterpret_cast<floatx4*>(dst + j * 16) = tot[nb][j];
@@ -1647,12 +1731,13 @@ static hipError_t launch_xtt_groups(const XttArgs* a, int n, hipStream_t st, boo
         int g = 0;
         for (; g < tb.n; ++g)
             if (tb.a[g].nb < kXShare && tb.a[g].X == a[m].X && tb.a[g].ldx == a[m].ldx && tb.a[g].M == a[m].M && tb.a[g].K == a[m].K && tb.a[g].m_pad == a[m].m_pad &&
-                nsplit[g] == a[m].nsplit) break;
+                nsplit[g] == a[m].nsplit && (tb.a[g].one != 0) == a[m].one) break;
         XttGroupDev& d = tb.a[g];
         if (g == tb.n) {
             d.X = a[m].X; d.ldx = a[m].ldx; d.M = a[m].M; d.K = a[m].K; d.m_pad = a[m].m_pad;
             d.tok_per_split = xtt_tokens_per_split(a[m].m_pad, a[m].nsplit);
             d.nb = 0;
+            d.one = a[m].one ? 1 : 0;
             nsplit[tb.n++] = a[m].nsplit;
         }
         d.T[d.nb] = a[m].TpackT;
@@ -1703,7 +1788,7 @@ hipError_t launch_xtt_bf16_many(const XttArgs* a, int n, bool half_cu, hipStream
     for (int m = 0; m < n; ++m) {
         if (a[m].M == 0 || a[m].K == 0) continue;
         if (rp == 0) rp = a[m].rp;
-        if (a[m].rp != rp || a[m].nsplit < 1) return hipErrorInvalidValue;
+        if (a[m].rp != rp || a[m].nsplit < 1 || (a[m].one && rp != 16)) return hipErrorInvalidValue;
         // (ranges that hold tokens, and their steps)
         const int64_t panels = (a[m].K + XTT_PANEL - 1) / XTT_PANEL, tok = xtt_tokens_per_split(a[m].m_pad, a[m].nsplit);
         busy += panels * ((a[m].m_pad + tok - 1) / tok);
@@ -1729,6 +1814,7 @@ hipError_t launch_xtt_bf16_many(const XttArgs* a, int n, bool half_cu, hipStream
         XttDev d;
         d.X = a[m].X; d.ldx = a[m].ldx; d.M = a[m].M; d.K = a[m].K; d.TpackT = a[m].TpackT; d.m_pad = a[m].m_pad;
         d.partial = a[m].partial; d.tok_per_split = xtt_tokens_per_split(a[m].m_pad, a[m].nsplit);
+        d.one = a[m].one ? 1 : 0;
         const uint32_t gx = (uint32_t)((a[m].K + panel - 1) / panel);
         tb.first[tb.n] = (uint32_t)blocks; tb.gx[tb.n] = gx; tb.a[tb.n++] = d;
         blocks += (uint64_t)gx * (uint32_t)a[m].nsplit;
