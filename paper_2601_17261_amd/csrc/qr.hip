@@ -108,8 +108,9 @@ __device__ __forceinline__ double read_lane(double x, int lane) {
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 template <int J>
-__device__ __forceinline__ void eliminate(double (&v)[4], double (&w)[4], int c, int g, int& bad) {
+__device__ __forceinline__ void eliminate(double (&v)[4], double (&w)[4], int c, int g, int n, int& bad) {
     if constexpr (J < 16) {
+        if (J > 0 && J % 4 == 0 && J >= n) return;               // (uniform) the rest is padding, which changes nothing
         constexpr int src = (J >> 2) * 16;                       // the lanes that hold row J
         double d = read_lane(v[J & 3], src + J);
         if (!(d > 0.0)) { bad |= 1 << J; d = 1.0; }
@@ -124,11 +125,13 @@ __device__ __forceinline__ void eliminate(double (&v)[4], double (&w)[4], int c,
             v[i] = fma(-col, f, v[i]);
             w[i] = fma(-col, fw, w[i]);
         }
-        eliminate<J + 1>(v, w, c, g, bad);
+        eliminate<J + 1>(v, w, c, g, n, bad);
     }
 }
 // Rinv <- R^-1 of the block's factor R^T R (upper triangle, zeros below).  Rows and columns from n on are padding: unit diagonal.
-// Returns nonzero (wave-uniform) on a non-positive pivot
+// Returns nonzero (wave-uniform) on a non-positive pivot.  Sixteen columns are a chain of sixteen steps, so it ends behind the last four that are
+// not all padding, the same bits: at rank 4 a factorisation takes 1.5 us less (a step of a 256-wide fp32 layer on 512 tokens 100.6 us with all steps and
+// 93.7 so, of the 4B projections on 512 tokens 513 and 505), at rank 8 1 (of the 0.6B ones on 2048 365 and 360)
 __device__ int factor16(const double* G, double* Rinv, int n) {
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
     double v[4], w[4];
@@ -139,7 +142,7 @@ __device__ int factor16(const double* G, double* Rinv, int n) {
         v[i] = (row < n && c < n) ? G[row * QR_LD + c] : w[i];
     }
     int bad = 0;
-    eliminate<0>(v, w, c, g, bad);
+    eliminate<0>(v, w, c, g, n, bad);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int row = 4 * g + i;
@@ -503,7 +506,7 @@ __global__ __launch_bounds__(QrShape<RP>::THREADS) void qr_apply_final_kernel(co
 }
 
 // ---- up to 512 rows and 16 columns: the launches above as one workgroup.  Bound by the latency of a launch each, they took 4.6 + 6.3 us
-// (single pass of 256 rows) and 4.6 + 7.5 + 6.2; this takes some 7.5 and 11, 2 of it for a factorisation.  Everything is added in the order of those launches, so the results are the same bits and a
+// (single pass of 256 rows) and 4.6 + 7.5 + 6.2; this takes some 7.5 and 11 (r = 16; 6 and 10 for four columns), 2 of it for a factorisation.  Everything is added in the order of those launches, so the results are the same bits and a
 // call may take either way.  (A wave has 64 rows, two quarters of a Gram partial there: with all four in a row the matrix instructions took
 // a third of the time, and more rows than these take longer than the launches.)
 constexpr int QRS_BLOCKS = 4, QRS_WAVES = 2 * QRS_BLOCKS, QRS_ROWS = QRS_BLOCKS * QR_ROWS, QRS_LD = 17;

@@ -46,3 +46,21 @@ def test_qr(d, r):
     ctx.qr(torch.from_numpy(np.zeros_like(Y)).cuda(), Q)
     with pytest.raises(binding.AgzoError):
         ctx.check()
+
+
+@pytest.mark.parametrize("d", [300, 700])
+@pytest.mark.parametrize("r", [1, 4, 5, 8, 9, 12, 13, 20, 21, 36, 49])
+def test_ranks_that_fill_part_of_a_block(d, r):
+    """the factorisation ends behind the last four columns that are there.  Bounds as above"""
+    rng = np.random.default_rng(d + r)
+    Y = (rng.standard_normal((d, r)) @ np.diag(np.logspace(0, -2, r))).astype(np.float32)
+    Q = torch.full((d, r), 9.0, device="cuda")
+    ctx = binding.Context()
+    ctx.qr(torch.from_numpy(Y).cuda(), Q)
+    ctx.check()
+    want, _ = oagzo.qr_pos(Y.astype(np.float64))
+    assert np.linalg.norm(Q.cpu().numpy().astype(np.float64) - want) < 1e-5 * np.linalg.norm(want)
+    Y[:, r - 1] = 0.0                                              # the last pivot, of the last four columns
+    ctx.qr(torch.from_numpy(Y).cuda(), Q)
+    with pytest.raises(binding.AgzoError):
+        ctx.check()
