@@ -462,14 +462,15 @@ struct LayerJob {
 };
 
 // the same for fp32 storage: S (or T and S) of every job in the workspace
-int stage_sketch_many_f32(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, const int* idx, int n, bool range) {
+int stage_sketch_many_f32(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, const int* idx, int n, bool range, const float* const* raw) {
     FillNormalArgs f[kBatchMax];
     F32SkinnyArgs q[kBatchMax], t[kBatchMax];
     for (int i = 0; i < n; ++i) {
         const LayerJob& j = jobs[idx[i]];
         const float* X = static_cast<const float*>(j.X);
         f[i] = FillNormalArgs{wsf(ctx, j.p.off_T), j.L.n_tokens, j.L.r, j.seed};
-        q[i] = F32SkinnyArgs{X, j.L.ldx, j.L.n_tokens, j.L.d_in, wsf(ctx, j.p.off_Q), j.L.r, wsf(ctx, j.p.off_T)};
+        q[i] = F32SkinnyArgs{X, j.L.ldx, j.L.n_tokens, j.L.d_in, raw && raw[i] ? raw[i] : wsf(ctx, j.p.off_Q), j.L.r, wsf(ctx, j.p.off_T),
+                             raw && raw[i] ? ctx->flag : nullptr};
         t[i] = F32SkinnyArgs{X, j.L.ldx, j.L.n_tokens, j.L.d_in, wsf(ctx, j.p.off_T), j.L.r, wsf(ctx, j.p.off_S)};
     }
     if (range) HIPCHK(launch_fill_normal_many(f, n, AGZO_TAG_OMEGA, ctx->stream));
@@ -483,7 +484,7 @@ int stage_sketch_many_f32(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, cons
 // partial sums of that column are all there is
 // half_cu (here and below): forwards on another stream may hold half of every compute unit
 int stage_sketch_many(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, const int* idx, int n, bool range, bool half_cu, const float* const* raw = nullptr, const bool* summed = nullptr) {
-    if (n > 0 && jobs[idx[0]].L.dtype != AGZO_BF16) return stage_sketch_many_f32(ctx, jobs, idx, n, range);
+    if (n > 0 && jobs[idx[0]].L.dtype != AGZO_BF16) return stage_sketch_many_f32(ctx, jobs, idx, n, range, raw);
     hipStream_t st = ctx->stream;
     if (range) {
         FillPackTArgs f[kBatchMax];
@@ -569,6 +570,10 @@ int basis_many_impl(agzo_ctx* ctx, const std::vector<LayerJob>& jobs, int K, int
                 summed[i] = n == 1 && defer && partials && xq_sums_column(j.L.n_tokens, j.L.d_in, j.p.nsplit);
                 raw[i] = nullptr;
                 if (summed[i]) continue;
+                if (!bf && k < K && j.L.r == 1) {                // (and with fp32 storage, where the sums are in fp64, it finds the norm as well)
+                    raw[i] = k == 0 && given[i] ? j.S0 : wsf(ctx, j.p.off_S);
+                    continue;
+                }
                 float* out = (k == K) ? j.B : wsf(ctx, j.p.off_Q);
                 bf16_t* planes = reads_planes(j.L) ? wsh(ctx, j.p.off_pack) : nullptr;
                 QrArgs& one = q[nq++];

@@ -238,7 +238,8 @@ hipError_t launch_forward_f32_many(const F32FwdArgs* a, int n, hipStream_t st);
 hipError_t launch_rank_term_f32(float* Y, int64_t ldy, int64_t M, int64_t N, const float* P, int r, float eps_signed, uint64_t seed,
                                 hipStream_t st);
 // X [M][K]; xq: out [M][r] = X V, V [K][r]; xtt: out [K][r] = X^T V, V [M][r].  One padded rank (r rounded up to 16) per launch
-struct F32SkinnyArgs { const float* X; int64_t ldx, M, K; const float* V; int r; float* out; };
+// flag (xq, r = 1; nullable): V is still to be divided by its norm; *flag = 1 if that is not positive
+struct F32SkinnyArgs { const float* X; int64_t ldx, M, K; const float* V; int r; float* out; int* flag = nullptr; };
 hipError_t launch_xq_f32_many(const F32SkinnyArgs* a, int n, hipStream_t st);
 hipError_t launch_xtt_f32_many(const F32SkinnyArgs* a, int n, hipStream_t st);
 

@@ -436,9 +436,23 @@ struct F32SkinnyDev {
 };
 
 // the waves' 16 x 16 blocks -> sum in wave order -> out (row0 + row, col0 + col), rows < nrow, columns < r
+// xq, r = 1, flag != nullptr: V is a column that is still to be divided by its norm, and the result is instead, in fp64 as the sums are.  Every workgroup
+// multiplies with every value of the column, so it adds up their squares as it goes: no launch for the norm between power steps, and none that
+// scales the column (4.5 us each).  A lone layer's basis, K = 3, with those launches and so, us: 64 wide on 100 tokens 30.2 and 20.9, 256 on 512 38.5 and 29.5,
+// 1024 42.3 and 31.2, 4096 51.1 and 38.6, 3072 on 1000 60.0 and 47.7; a step of the 0.6B-sized layers on 1000 tokens 1665 and 1647.  One rounding less: errors against
+// 64 bits 5.3 to 5.9e-8 and 4.4 to 5.1e-8
+__device__ __forceinline__ double column_scale(const double* norms, int n, int* flag, bool report) {
+    double sum = 0.0;
+    for (int w = 0; w < n; ++w) sum += norms[w];
+    if (!(sum > 0.0)) {
+        if (report) *flag = 1;
+        sum = 1.0;
+    }
+    return 1.0 / sqrt(sum);
+}
 template <int NB>
 __device__ __forceinline__ void skinny_f32_finish(const doublex4 (&acc)[NB], double* red, int64_t row0, int64_t nrow, int r,
-                                                  float* __restrict__ out) {
+                                                  float* __restrict__ out, const double* norms = nullptr, int* flag = nullptr, bool first = false) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lc = lane & 15, lg = lane >> 4;
 #pragma unroll
@@ -450,6 +464,7 @@ __device__ __forceinline__ void skinny_f32_finish(const doublex4 (&acc)[NB], dou
             double s = 0.0;
 #pragma unroll
             for (int w = 0; w < SK_WAVES; ++w) s += red[w * 256 + tid];
+            if (flag) s *= column_scale(norms, SK_WAVES, flag, first && tid == 0);
             const int64_t row = row0 + (tid >> 4);
             const int col = nb * 16 + (tid & 15);
             if (row < nrow && col < r) out[row * r + col] = (float)s;
@@ -469,6 +484,9 @@ __device__ __forceinline__ void xq_f32_rows(const F32SkinnyArgs& a, double* red,
     for (int nb = 0; nb < NB; ++nb) acc[nb] = doublex4{0.0, 0.0, 0.0, 0.0};
     const int nchunk = (int)((a.K + 15) / 16);
     constexpr int U = (NB == 1) ? 4 : 2;                   // chunks in flight per wave
+    __shared__ double norms[NB == 1 ? SK_WAVES : 1];
+    const bool norm = NB == 1 && a.flag != nullptr;        // (r = 1: the values are lane 0's of each sixteen, the others' are zero)
+    double squares = 0.0;
     for (int c0 = wave; c0 < nchunk; c0 += U * SK_WAVES) {
         float x[U][4], q[U][NB][4];
 #pragma unroll
@@ -506,9 +524,17 @@ __device__ __forceinline__ void xq_f32_rows(const F32SkinnyArgs& a, double* red,
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb)
                     acc[nb] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[u][s], (double)q[u][nb][s], acc[nb], 0, 0, 0);
+            if (norm)
+#pragma unroll
+                for (int s = 0; s < 4; ++s) squares = fma((double)q[u][0][s], (double)q[u][0][s], squares);
         }
     }
-    skinny_f32_finish<NB>(acc, red, t0, a.M, a.r, a.out);
+    if (norm) {
+        squares += __shfl_xor(squares, 16);
+        squares += __shfl_xor(squares, 32);
+        if (lane == 0) norms[wave] = squares;
+    }
+    skinny_f32_finish<NB>(acc, red, t0, a.M, a.r, a.out, norms, NB == 1 ? a.flag : nullptr, bx == 0);
 }
 template <int NB>
 __global__ __launch_bounds__(64 * SK_WAVES) void xq_f32_kernel(const KBatch<F32SkinnyDev> tb) {
@@ -535,7 +561,8 @@ __device__ __forceinline__ void xq_f32_narrow_rows(const F32SkinnyArgs& a, doubl
     const float* xr[XQN_TOK];
 #pragma unroll
     for (int t = 0; t < XQN_TOK; ++t) xr[t] = a.X + min(t0 + t, a.M - 1) * a.ldx;
-    double acc[XQN_TOK][R] = {};
+    __shared__ double norms[4];
+    double acc[XQN_TOK][R] = {}, squares = 0.0;
     const int64_t nchunk = (K + 255) / 256;
     constexpr int U = 2;
     for (int64_t c0 = wave; c0 < nchunk; c0 += 4 * U) {
@@ -570,6 +597,7 @@ __device__ __forceinline__ void xq_f32_narrow_rows(const F32SkinnyArgs& a, doubl
 #pragma unroll
                 for (int j = 0; j < R; ++j) {
                     const double qd = (double)q[u][s][j];
+                    if (R == 1) squares = fma(k + s < K ? qd : 0.0, qd, squares);
 #pragma unroll
                     for (int t = 0; t < XQN_TOK; ++t) acc[t][j] = fma(k + s < K ? (double)x[u][t][s] : 0.0, k + s < K ? qd : 0.0, acc[t][j]);
                 }
@@ -583,9 +611,18 @@ __device__ __forceinline__ void xq_f32_narrow_rows(const F32SkinnyArgs& a, doubl
             for (int off = 32; off > 0; off >>= 1) acc[t][j] += __shfl_xor(acc[t][j], off);
             if (lane == 0) red[wave][t * R + j] = acc[t][j];
         }
+    if (R == 1 && a.flag) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) squares += __shfl_xor(squares, off);
+        if (lane == 0) norms[wave] = squares;
+    }
     __syncthreads();
     const int e = threadIdx.x;
-    if (e < XQN_TOK * R && t0 + e / R < a.M) a.out[t0 * R + e] = (float)((red[0][e] + red[1][e]) + (red[2][e] + red[3][e]));
+    if (e < XQN_TOK * R && t0 + e / R < a.M) {
+        double v = (red[0][e] + red[1][e]) + (red[2][e] + red[3][e]);
+        if (R == 1 && a.flag) v *= column_scale(norms, 4, a.flag, bx == 0 && e == 0);
+        a.out[t0 * R + e] = (float)v;
+    }
 }
 template <int R>
 __global__ __launch_bounds__(256) void xq_f32_narrow_kernel(const KBatch<F32SkinnyDev> tb) {
@@ -678,7 +715,7 @@ static hipError_t launch_skinny_f32(const F32SkinnyArgs* a, int n, bool transpos
         if (a[i].r < 1 || a[i].r > kMaxRank) return hipErrorInvalidValue;
         const int want = (a[i].r + 15) / 16;
         if (nb == 0) nb = want;
-        if (nb != want) return hipErrorInvalidValue;        // one padded rank per launch
+        if (nb != want || (a[i].flag && (transposed || a[i].r != 1))) return hipErrorInvalidValue;        // one padded rank per launch
         if (!transposed && a[i].r <= 4 && a[i].K >= XQN_MIN) {
             narrow[a[i].r - 1][n_narrow[a[i].r - 1]++] = i;
             continue;
