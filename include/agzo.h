@@ -258,7 +258,9 @@ int agzo_step_no_update(agzo_ctx* ctx, const agzo_layer* L, void* W, const void*
  *            the rotary embedding (pairs (i, i + 64) of a head by the angle t rope_theta^(-2i/128), t the position inside
  *            the sequence), scores scaled by 1/sqrt(128), softmax in fp32, probabilities rounded to bf16 for the second
  *            product.  q [N][n_heads 128], k and v [N][n_kv_heads 128], out [N][n_heads 128], N = n_seq seq_len tokens,
- *            the sequences back to back; n_heads a multiple of n_kv_heads.  Uses (and may grow) the context's workspace.
+ *            the sequences back to back; n_heads a multiple of n_kv_heads.  out may overlap any of q, k and v (q is then
+ *            copied first, unless out is q with the same leading dimension, and so is v).  Uses (and may grow) the
+ *            context's workspace.
  * Errors: AGZO_EINVAL for NULL or misaligned tensors, d % 8 != 0, leading dimensions below d, a bad attention shape. */
 int agzo_glue_attention(agzo_ctx* ctx, const void* q, int64_t ldq, const void* k, int64_t ldk, const void* v, int64_t ldv,
                         void* out, int64_t ldo, int32_t n_seq, int32_t seq_len, int32_t n_heads, int32_t n_kv_heads,

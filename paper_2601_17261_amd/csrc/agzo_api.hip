@@ -1330,7 +1330,8 @@ int agzo_glue_attention(agzo_ctx* ctx, const void* q, int64_t ldq, const void* k
     TRY(check_glue(ctx, n, dkv, {k, v}, {ldk, ldv}));
     if (n == 0) return AGZO_OK;
     // (as much as the layer's inputs: its MLP's forwards ask for about that next, and a growth waits for the stream)
-    TRY(reserve(ctx, std::max(glue_attention_workspace_bytes(n_seq, seq_len, n_heads, n_kv_heads), (size_t)n * (n_heads + 2 * n_kv_heads) * 256)));
+    const GlueCopies copies = glue_attention_copies(static_cast<const bf16_t*>(q), ldq, static_cast<const bf16_t*>(v), ldv, static_cast<const bf16_t*>(out), ldo, n_seq, seq_len, n_heads, n_kv_heads);
+    TRY(reserve(ctx, std::max(glue_attention_workspace_bytes(n_seq, seq_len, n_heads, n_kv_heads, copies), (size_t)n * (n_heads + 2 * n_kv_heads) * 256)));
     HIPCHK(launch_glue_attention(static_cast<const bf16_t*>(q), ldq, static_cast<const bf16_t*>(k), ldk, static_cast<const bf16_t*>(v), ldv,
                                  static_cast<bf16_t*>(out), ldo, n_seq, seq_len, n_heads, n_kv_heads, rope_theta, ctx->ws, ctx->stream));
     return AGZO_OK;

@@ -3,6 +3,7 @@
 // runs them three times per block, so they are single-pass kernels here: bf16 in and out, fp32 arithmetic, one
 // rounding to bf16, 16-byte accesses.  All three are bound by HBM.
 #include "agzo_internal.h"
+#include "overlap.h"
 
 namespace agzo {
 
@@ -394,20 +395,62 @@ __global__ __launch_bounds__(64 * ATT_WAVES) __attribute__((amdgpu_waves_per_eu(
     }
 }
 
-// prepared keys, angles
-size_t glue_attention_workspace_bytes(int n_seq, int seq_len, int n_heads, int n_kv) {
-    return (size_t)n_seq * n_kv * seq_len * HEAD_DIM * sizeof(bf16_t) + (size_t)seq_len * (HEAD_DIM / 2) * sizeof(float2);
+// rows of d (a multiple of 8) side by side
+__global__ __launch_bounds__(256) void glue_copy_rows_kernel(const bf16_t* __restrict__ x, int64_t ldx, bf16_t* __restrict__ y, int64_t n, int64_t d) {
+    const int64_t nvec = d / 8, idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (idx >= n * nvec) return;
+    const int64_t row = idx / nvec, v = idx - row * nvec;
+    *reinterpret_cast<uint4*>(y + row * d + v * 8) = *reinterpret_cast<const uint4*>(x + row * ldx + v * 8);
+}
+static hipError_t copy_rows(const bf16_t* x, int64_t ldx, bf16_t* y, int64_t n, int64_t d, hipStream_t st) {
+    const int64_t blocks = (n * (d / 8) + 255) / 256;
+    if (blocks > 0x7FFFFFFFLL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(glue_copy_rows_kernel, dim3((unsigned)blocks), dim3(256), 0, st, x, ldx, y, n, d);
+    return hipGetLastError();
+}
+
+// The kernel reads queries and values where the caller holds them, while other workgroups store: tensors that `out` lies in are copied ahead of it.
+// (Not queries that it replaces row by row: a workgroup stores the rows and the head that it alone reads, behind its reads.  Keys are
+// read by the launch ahead)
+GlueCopies glue_attention_copies(const bf16_t* q, int64_t ldq, const bf16_t* v, int64_t ldv, const bf16_t* out, int64_t ldo, int n_seq, int seq_len, int n_heads, int n_kv) {
+    const int64_t n = (int64_t)n_seq * seq_len, dq = (int64_t)n_heads * HEAD_DIM * 2, dv = (int64_t)n_kv * HEAD_DIM * 2;
+    const Rows o{reinterpret_cast<uintptr_t>(out), 2 * ldo, n, dq};
+    const bool in_place = q == out && ldq == ldo;
+    return GlueCopies{!in_place && rows_overlap(Rows{reinterpret_cast<uintptr_t>(q), 2 * ldq, n, dq}, o), rows_overlap(Rows{reinterpret_cast<uintptr_t>(v), 2 * ldv, n, dv}, o)};
+}
+
+// prepared keys, angles, copies
+size_t glue_attention_workspace_bytes(int n_seq, int seq_len, int n_heads, int n_kv, GlueCopies copies) {
+    const size_t head = (size_t)n_seq * seq_len * HEAD_DIM * sizeof(bf16_t);
+    return head * (n_kv + (copies.q ? n_heads : 0) + (copies.v ? n_kv : 0)) + (size_t)seq_len * (HEAD_DIM / 2) * sizeof(float2);
 }
 
 hipError_t launch_glue_attention(const bf16_t* q, int64_t ldq, const bf16_t* k, int64_t ldk, const bf16_t* v, int64_t ldv,
                                  bf16_t* out, int64_t ldo, int n_seq, int seq_len, int n_heads, int n_kv, float rope_theta,
                                  void* workspace, hipStream_t st) {
     if (n_seq == 0 || seq_len == 0) return hipSuccess;
+    const int64_t n = (int64_t)n_seq * seq_len;
     bf16_t* Kr = static_cast<bf16_t*>(workspace);
-    float2* angles = reinterpret_cast<float2*>(Kr + (int64_t)n_seq * n_kv * seq_len * HEAD_DIM);
-    const int64_t items = (int64_t)n_seq * seq_len * ((n_kv + PREP_HEADS - 1) / PREP_HEADS) * 16;
+    float2* angles = reinterpret_cast<float2*>(Kr + n * n_kv * HEAD_DIM);
+    bf16_t* copy = reinterpret_cast<bf16_t*>(angles + (int64_t)seq_len * (HEAD_DIM / 2));
+    const GlueCopies copies = glue_attention_copies(q, ldq, v, ldv, out, ldo, n_seq, seq_len, n_heads, n_kv);
+    hipError_t e = hipSuccess;
+    if (copies.q) {
+        e = copy_rows(q, ldq, copy, n, (int64_t)n_heads * HEAD_DIM, st);
+        if (e != hipSuccess) return e;
+        q = copy;
+        ldq = (int64_t)n_heads * HEAD_DIM;
+        copy += n * ldq;
+    }
+    if (copies.v) {
+        e = copy_rows(v, ldv, copy, n, (int64_t)n_kv * HEAD_DIM, st);
+        if (e != hipSuccess) return e;
+        v = copy;
+        ldv = (int64_t)n_kv * HEAD_DIM;
+    }
+    const int64_t items = n * ((n_kv + PREP_HEADS - 1) / PREP_HEADS) * 16;
     hipLaunchKernelGGL(glue_k_prep_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, st, k, ldk, Kr, angles, n_seq, seq_len, n_kv, log2f(rope_theta));
-    hipError_t e = hipGetLastError();
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
     static bool attr_set = false;
     if (!attr_set) {
