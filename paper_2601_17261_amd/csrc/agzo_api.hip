@@ -12,6 +12,7 @@
 
 #include "agzo_internal.h"
 #include "fork.h"
+#include "grow.h"
 
 using namespace agzo;
 
@@ -175,29 +176,25 @@ Plan make_forward_plan(const agzo_layer& L, bool need_ybuf, bool ce, bool fused_
     return p;
 }
 
-constexpr size_t kMapBytes = (size_t)2 << 20, kGrowBytes = (size_t)32 << 20;
-int reserve(agzo_ctx* ctx, size_t bytes) {
+// wish: what a growth is to cover as well where there is room (grow.h)
+int reserve(agzo_ctx* ctx, size_t bytes, size_t wish = 0) {
     if (bytes <= ctx->ws_bytes) return 0;
     HIPCHK(hipStreamSynchronize(ctx->stream));
     if (ctx->side) HIPCHK(hipStreamSynchronize(ctx->side));      // (joined to the above, unless joining failed)
-    // a context that needs more once will need more again (the layers of a model, one after the other): half as much again, at first more, up to
-    // the 2 MiB that device memory is mapped by (a page of it is some 10 us).  (A growth is up to 0.5 ms of a first pass: the dense estimator's over seven 0.6B-sized
-    // layers on 1131 tokens takes 0.97 ms growing by what a call needs, 1.24 by half, 0.77 so)
-    const size_t need = bytes;
-    if (ctx->ws) bytes = (std::max({bytes, ctx->ws_bytes + ctx->ws_bytes / 2, std::min(16 * ctx->ws_bytes, ctx->ws_bytes + kGrowBytes)}) + kMapBytes - 1) / kMapBytes * kMapBytes;
     if (ctx->ws) HIPCHK(hipFree(ctx->ws));
+    const size_t had = ctx->ws_bytes;
     ctx->ws = nullptr;
     ctx->ws_bytes = 0;
     void* p = nullptr;
-    hipError_t e = hipMalloc(&p, bytes);
-    if (e != hipSuccess && bytes > need) {      // not that much left: what the call needs
-        (void)hipGetLastError();
-        bytes = need;
-        e = hipMalloc(&p, bytes);
-    }
-    if (e != hipSuccess) return fail(ctx, AGZO_ENOMEM, "workspace of %zu bytes: %s", bytes, hipGetErrorString(e));
+    hipError_t e = hipSuccess;
+    const size_t got = grow(had, bytes, wish, [&](size_t n) {
+        if (e != hipSuccess) (void)hipGetLastError();      // (of the attempt before)
+        e = hipMalloc(&p, n);
+        return e == hipSuccess;
+    });
+    if (!got) return fail(ctx, AGZO_ENOMEM, "workspace of %zu bytes: %s", bytes, hipGetErrorString(e));
     ctx->ws = static_cast<char*>(p);
-    ctx->ws_bytes = bytes;
+    ctx->ws_bytes = got;
     return 0;
 }
 
@@ -1329,9 +1326,9 @@ int agzo_glue_attention(agzo_ctx* ctx, const void* q, int64_t ldq, const void* k
     TRY(check_glue(ctx, n, dq, {q, out}, {ldq, ldo}));
     TRY(check_glue(ctx, n, dkv, {k, v}, {ldk, ldv}));
     if (n == 0) return AGZO_OK;
-    // (as much as the layer's inputs: its MLP's forwards ask for about that next, and a growth waits for the stream)
+    // (a growth covers as much as the layer's inputs: its MLP's forwards ask for about that next, and a growth waits for the stream)
     const GlueCopies copies = glue_attention_copies(static_cast<const bf16_t*>(q), ldq, static_cast<const bf16_t*>(v), ldv, static_cast<const bf16_t*>(out), ldo, n_seq, seq_len, n_heads, n_kv_heads);
-    TRY(reserve(ctx, std::max(glue_attention_workspace_bytes(n_seq, seq_len, n_heads, n_kv_heads, copies), (size_t)n * (n_heads + 2 * n_kv_heads) * 256)));
+    TRY(reserve(ctx, glue_attention_workspace_bytes(n_seq, seq_len, n_heads, n_kv_heads, copies), (size_t)n * (n_heads + 2 * n_kv_heads) * 256));
     HIPCHK(launch_glue_attention(static_cast<const bf16_t*>(q), ldq, static_cast<const bf16_t*>(k), ldk, static_cast<const bf16_t*>(v), ldv,
                                  static_cast<bf16_t*>(out), ldo, n_seq, seq_len, n_heads, n_kv_heads, rope_theta, ctx->ws, ctx->stream));
     return AGZO_OK;
