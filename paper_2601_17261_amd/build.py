@@ -22,7 +22,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wno-unused-com
 def _compile(src, force):
     obj = os.path.join(OBJ, src.replace(".hip", ".o"))
     srcp = os.path.join(CSRC, src)
-    deps = [srcp, os.path.join(CSRC, "agzo_internal.h"), os.path.join(CSRC, "gemm_bf16_common.h"), os.path.join(CSRC, "ext_prep.h"), os.path.join(CSRC, "fork.h"), os.path.join(CSRC, "overlap.h"), os.path.join(CSRC, "grow.h"),
+    deps = [srcp, os.path.join(CSRC, "agzo_internal.h"), os.path.join(CSRC, "gemm_bf16_common.h"), os.path.join(CSRC, "ext_prep.h"), os.path.join(CSRC, "fork.h"), os.path.join(CSRC, "overlap.h"), os.path.join(CSRC, "grow.h"), os.path.join(CSRC, "slots.h"),
             os.path.join(ROOT, "include", "agzo.h")]
     if not force and os.path.exists(obj) and all(os.path.getmtime(obj) > os.path.getmtime(d) for d in deps):
         return obj, ""

@@ -72,6 +72,7 @@
 // layers, the deepest first: a launch per layer ends on a round that is partly idle, seven times for a set (4096 tokens
 // of the 4B-sized layers, 64 to 608 tiles each, r = 64: 1031 us in seven launches, 775 in one).
 #include "gemm_bf16_common.h"
+#include "slots.h"
 
 namespace agzo {
 
@@ -998,8 +999,8 @@ static int slots_beside(const GemmBeside& b, double total, double deepest, int s
     return best;
 }
 
-// The same for one problem in a launch of its own, whose workgroups take whole rounds of tiles together, against both one after the other; four
-// compute units of each XCD at least are left (a chain on 16 in all took longer than its forward: 20000 outputs of 4096 on 1500 tokens, r =
+// The same for one problem in a launch of its own (slots.h).  Four compute units of each XCD at least are left (a chain on 16 in all took longer
+// than its forward: 20000 outputs of 4096 on 1500 tokens, r =
 // 16, 735 and 755).  A step of one layer, us, one stream and two (K = 3): cross-entropy, 2048 -> 32000 on 3001 tokens, r = 16, 1105 and 1003, on
 // 8192 2522 and 2514, 1024 -> 9000 on 700 241 and 223, on 8192 629 and 531; squared error, 4096 -> 4096 on 3001 394 and 349, 1024 ->
 // 8192 on 8192 489 and 422, 8192 -> 8192 on 8192 2507 and 2391, r = 1 2427 and 2374, r = 64 3072 and 2876.  Of 19 shapes and r = 1, 16 and 64 none
@@ -1007,17 +1008,8 @@ static int slots_beside(const GemmBeside& b, double total, double deepest, int s
 int gemm_bf16_aligned_slots(const GemmParams& p, const GemmBeside& b) {
     int slots = 0;
     if (list_slots(&slots) != hipSuccess) return 0;
-    const double tile = tile_us(aligned_item(p)) + (p.loss_kind == AGZO_LOSS_CE ? kStatisticsUs : 0.0), all = b.latency_us + b.sweep_us;
-    const int64_t run = ((int64_t)p.tiles_m * p.tiles_n + 7) / 8;
-    auto rounds = [&](int s) { return (double)((run + s - 1) / s) * tile; };
-    int best = 0;
-    double best_us = rounds(slots) + all - kForkUs;
-    for (int s = slots - 4; s >= 1; --s) {
-        const double left = 22.0 / 29.0 * slots / (slots - s), slow = b.latency_us + b.sweep_us * (left > 1.0 ? left : 1.0);
-        const double done = rounds(s) / slow, us = done >= 1.0 ? rounds(s) : rounds(s) + (1.0 - done) * all;
-        if (us <= best_us) { best_us = us; best = s; }      // (of equal ones the fewest)
-    }
-    return best;
+    const double tile = tile_us(aligned_item(p)) + (p.loss_kind == AGZO_LOSS_CE ? kStatisticsUs : 0.0);
+    return lone_slots(((int64_t)p.tiles_m * p.tiles_n + 7) / 8, slots, tile, b.latency_us, b.sweep_us, kForkUs);
 }
 
 static bool aligned_fits(const GemmParams& p) { return p.M >= BT && p.N >= BT && p.K >= 2 * BK && (p.P == nullptr || p.Xext != nullptr); }
