@@ -13,6 +13,7 @@
 #include "agzo_internal.h"
 #include "fork.h"
 #include "grow.h"
+#include "overlap.h"
 
 using namespace agzo;
 
@@ -165,10 +166,15 @@ Plan make_plan(const agzo_layer& L, bool need_ybuf, bool ce = false, bool shared
     return p;
 }
 
-// with the scratch of a lone stored output (the forwards that a model makes layer by layer)
-Plan make_forward_plan(const agzo_layer& L, bool need_ybuf, bool ce, bool fused_sketch, bool stored) {
+// with the scratch of a lone stored output (the forwards that a model makes layer by layer; Y may be NULL)
+Plan make_forward_plan(const agzo_layer& L, bool need_ybuf, bool ce, bool fused_sketch, const void* W, const void* X, const void* Y) {
     Plan p = make_plan(L, need_ybuf, ce, false, 0, fused_sketch);
-    const size_t split = (stored && L.dtype == AGZO_BF16 && L.y_dtype == AGZO_BF16) ? gemm_bf16_split_bytes(L.n_tokens, L.d_out, L.d_in, fused_sketch) : 0;
+    if (!Y || L.dtype != AGZO_BF16 || L.y_dtype != AGZO_BF16) return p;
+    // where Y lies in X or W, few tiles are shares again: the launch that adds them stores behind every read
+    auto rows = [](const void* at, int64_t ld, int64_t n, int64_t d) { return Rows{reinterpret_cast<uintptr_t>(at), 2 * ld, n, 2 * d}; };
+    const Rows y = rows(Y, L.ldy, L.n_tokens, L.d_out);
+    const bool over = rows_overlap(y, rows(X, L.ldx, L.n_tokens, L.d_in)) || rows_overlap(y, rows(W, L.ldw, L.d_out, L.d_in));
+    const size_t split = gemm_bf16_split_bytes(L.n_tokens, L.d_out, L.d_in, fused_sketch || over);
     if (split) {
         p.off_split = p.total;
         p.total += align_up(split);
@@ -870,7 +876,7 @@ int agzo_layer_forward_sketch(agzo_ctx* ctx, const agzo_layer* L, const void* W,
         TRY(check_y(ctx, L, Y));
         TRY(check_loss(ctx, L, loss, loss_dev));
     }
-    const Plan p = make_forward_plan(*L, gemm && L->dtype == AGZO_F32 && !Y && loss && loss->kind == AGZO_LOSS_CE, loss && loss->kind == AGZO_LOSS_CE, fused, gemm && Y);
+    const Plan p = make_forward_plan(*L, gemm && L->dtype == AGZO_F32 && !Y && loss && loss->kind == AGZO_LOSS_CE, loss && loss->kind == AGZO_LOSS_CE, fused, W, X, Y);
     TRY(reserve(ctx, p.total));
     if (fused) {
         {
@@ -925,7 +931,7 @@ int agzo_perturbed_forward(agzo_ctx* ctx, const agzo_layer* L, const void* W, co
     TRY(check_operands(ctx, L, W, X));
     TRY(check_y(ctx, L, Y));
     TRY(check_loss(ctx, L, loss, loss_dev));
-    const Plan p = make_forward_plan(*L, L->dtype == AGZO_F32 && !Y && loss && loss->kind == AGZO_LOSS_CE, loss && loss->kind == AGZO_LOSS_CE, false, Y != nullptr);
+    const Plan p = make_forward_plan(*L, L->dtype == AGZO_F32 && !Y && loss && loss->kind == AGZO_LOSS_CE, loss && loss->kind == AGZO_LOSS_CE, false, W, X, Y);
     TRY(reserve(ctx, p.total));
     float* P = wsf(ctx, p.off_T);
     if (L->dtype != AGZO_BF16) {

@@ -188,7 +188,7 @@ struct GemmBf16Args {
 // mode, no cross-entropy), which is then used for shapes with few 256 x 256 tiles
 int gemm_bf16_num_workgroups(int64_t M, int64_t N, bool small_ok);
 size_t gemm_bf16_ext_bytes(int64_t M, int64_t N, int r);
-size_t gemm_bf16_split_bytes(int64_t M, int64_t N, int64_t K, bool sketch);      // (sketch: the forward that emits it)
+size_t gemm_bf16_split_bytes(int64_t M, int64_t N, int64_t K, bool shares);      // (shares: of few tiles, too; else gemm_bf16_few.hip takes them)
 // true: a squared-error forward of this shape (not in shared-forward mode) runs in the 128 x 128 tiling
 bool gemm_bf16_small_tiles(int64_t M, int64_t N, bool large_tiles);
 // true: a plain forward of this shape (no rank-r term, no shared-forward mode, no cross-entropy) runs in the 128 x 128

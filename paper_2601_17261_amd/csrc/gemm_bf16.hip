@@ -693,7 +693,7 @@ hipError_t choose(const GemmBf16Args& a, Choice& c) {
     c.out = (p.Y && p.loss_kind == AGZO_LOSS_NONE && p.y_dtype == AGZO_BF16) ? 1 : (!p.Y && p.loss_kind == AGZO_LOSS_MSE) ? 0 : -1;
     // one output or one loss and tiles that lie inside the layer: the pipelined kernel
     c.kernel = (c.out >= 0 && gemm_bf16_mid_ok(g, c.out)) ? Kernel::mid : Kernel::small;
-    if (c.kernel == Kernel::mid && c.out == 1 && !g.sk_T && gemm_bf16_few_shape(p.M, p.N, p.K)) c.kernel = Kernel::few;
+    if (c.kernel == Kernel::mid && c.out == 1 && !g.sk_T && !g.part && gemm_bf16_few_shape(p.M, p.N, p.K)) c.kernel = Kernel::few;
     return hipSuccess;
 }
 

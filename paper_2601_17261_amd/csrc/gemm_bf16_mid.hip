@@ -406,12 +406,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_mid_finish_kernel(const GemmIte
 // launch with
 int gemm_bf16_mid_splits(int64_t M, int64_t N, int64_t K) {
     const int64_t tiles = ((M + MT - 1) / MT) * ((N + MT - 1) / MT), slices = K / BK;
-    if (gemm_bf16_few_shape(M, N, K)) return kFewShares;      // (with a fused sketch)
+    if (gemm_bf16_few_shape(M, N, K)) return kFewShares;      // (with a fused sketch, or an output over an operand)
     if (M < MT || N < MT || tiles > 128) return 1;
     return (int)std::max<int64_t>(1, std::min<int64_t>(256 / tiles, slices / 8));
 }
-size_t gemm_bf16_split_bytes(int64_t M, int64_t N, int64_t K, bool sketch) {
-    if (!sketch && gemm_bf16_few_shape(M, N, K)) return 0;
+size_t gemm_bf16_split_bytes(int64_t M, int64_t N, int64_t K, bool shares) {
+    if (!shares && gemm_bf16_few_shape(M, N, K)) return 0;
     const int s = gemm_bf16_mid_splits(M, N, K);
     return s > 1 ? (size_t)s * ((M + MT - 1) / MT) * ((N + MT - 1) / MT) * MT * MT * sizeof(float) : 0;
 }
@@ -468,9 +468,10 @@ hipError_t launch_gemm_bf16_mid(const GemmItem* a, int n, int out, bool target_f
         g.tiles_n = (int)((g.N + MT - 1) / MT);
         if (g.splits > g.K / BK) return hipErrorInvalidValue;
         const unsigned tiles = (unsigned)(g.tiles_m * g.tiles_n);
-        // the bits of the forward without a sketch: its shares are added in pairs, here or, where they are more than fill the chip, two to a workgroup
+        // the bits of gemm_bf16_few.hip: its shares are added in pairs, here or, where they are more than fill the chip and are sketched as well, two
+        // to a workgroup
         const bool few = gemm_bf16_few_shape(g.M, g.N, g.K);
-        g.fold = few && tiles > 64;
+        g.fold = few && sk && tiles > 64;
         g.pairs = few && !g.fold;
         if (g.fold) g.splits = kFewShares / 2;
         one.gx[0] = tiles * (unsigned)g.splits;
