@@ -122,20 +122,21 @@ inline int64_t round32(int64_t n) { return (n + 31) / 32 * 32; }
 // carve-out of the ctx workspace for one layer; everything a step can need at the same time
 struct Plan {
     size_t off_S, off_Q, off_B, off_pack, off_T, off_TpackT, off_xtt, off_qr, off_part, off_Ybuf, off_ce_ms, off_ce_tl, off_upd, off_ext, off_xqpart, off_split, total;
-    int rp, nsplit;
+    int rp, nsplit, sketch_tokens;
     int64_t m_pad;
     int n_part;
     size_t part_count;   // doubles in the loss-partials region
 };
 
 // base: where this layer's carve-out starts inside the workspace (several layers side by side in the batched calls)
-// fused_sketch: the range sketch comes out of the forward GEMM, one partial sum per 128-token tile
-Plan make_plan(const agzo_layer& L, bool need_ybuf, bool ce = false, bool shared = false, size_t base = 0, bool fused_sketch = false) {
+// sketch_tokens: the range sketch comes out of the forward GEMM, one partial sum per token tile of that many (0: it does not)
+Plan make_plan(const agzo_layer& L, bool need_ybuf, bool ce = false, bool shared = false, size_t base = 0, int sketch_tokens = 0) {
     Plan p;
     const bool bf = (L.dtype == AGZO_BF16);
     p.rp = round16(L.r);
-    p.m_pad = fused_sketch ? gemm_bf16_sketch_mpad(L.n_tokens) : round32(L.n_tokens);
-    p.nsplit = !bf ? 1 : fused_sketch ? gemm_bf16_sketch_splits(L.n_tokens) : xtt_num_splits(L.n_tokens, L.d_in);
+    p.sketch_tokens = sketch_tokens;
+    p.m_pad = sketch_tokens ? gemm_bf16_sketch_mpad(L.n_tokens) : round32(L.n_tokens);
+    p.nsplit = !bf ? 1 : sketch_tokens ? gemm_bf16_sketch_splits(L.n_tokens, sketch_tokens) : xtt_num_splits(L.n_tokens, L.d_in);
     const int n_gemm = bf ? gemm_bf16_num_workgroups(L.n_tokens, L.d_out, !ce && !shared && L.tiling != AGZO_TILING_LARGE) : forward_f32_num_workgroups(L.n_tokens, L.d_out);
     p.n_part = n_gemm;
     size_t o = align_up(base);
@@ -167,14 +168,15 @@ Plan make_plan(const agzo_layer& L, bool need_ybuf, bool ce = false, bool shared
 }
 
 // with the scratch of a lone stored output (the forwards that a model makes layer by layer; Y may be NULL)
-Plan make_forward_plan(const agzo_layer& L, bool need_ybuf, bool ce, bool fused_sketch, const void* W, const void* X, const void* Y) {
-    Plan p = make_plan(L, need_ybuf, ce, false, 0, fused_sketch);
-    if (!Y || L.dtype != AGZO_BF16 || L.y_dtype != AGZO_BF16) return p;
+Plan make_forward_plan(const agzo_layer& L, const agzo_loss_spec* loss, bool fused_sketch, const void* W, const void* X, const void* Y) {
+    const bool ce = loss && loss->kind == AGZO_LOSS_CE, stored = Y && L.dtype == AGZO_BF16 && L.y_dtype == AGZO_BF16 && (!loss || loss->kind == AGZO_LOSS_NONE);
     // where Y lies in X or W, few tiles are shares again: the launch that adds them stores behind every read
     auto rows = [](const void* at, int64_t ld, int64_t n, int64_t d) { return Rows{reinterpret_cast<uintptr_t>(at), 2 * ld, n, 2 * d}; };
     const Rows y = rows(Y, L.ldy, L.n_tokens, L.d_out);
-    const bool over = rows_overlap(y, rows(X, L.ldx, L.n_tokens, L.d_in)) || rows_overlap(y, rows(W, L.ldw, L.d_out, L.d_in));
-    const size_t split = gemm_bf16_split_bytes(L.n_tokens, L.d_out, L.d_in, fused_sketch || over);
+    const bool over = stored && (rows_overlap(y, rows(X, L.ldx, L.n_tokens, L.d_in)) || rows_overlap(y, rows(W, L.ldw, L.d_out, L.d_in)));
+    const bool few = stored && !over && gemm_bf16_few_tiles(L.n_tokens, L.d_out, L.d_in, L.tiling == AGZO_TILING_LARGE);
+    Plan p = make_plan(L, W && L.dtype == AGZO_F32 && !Y && ce, ce, false, 0, !fused_sketch ? 0 : few ? 64 : 128);
+    const size_t split = stored ? gemm_bf16_split_bytes(L.n_tokens, L.d_out, L.d_in, over) : 0;
     if (split) {
         p.off_split = p.total;
         p.total += align_up(split);
@@ -403,7 +405,7 @@ int op_forward(agzo_ctx* ctx, const agzo_layer& L, const Plan& p, const void* W,
         a.ext_ready = ext_ready;
         a.ext_side = ext_side;
         if (side) a.slots = side->slots;
-        if (fused_sketch) { a.sk_T = wsh(ctx, p.off_TpackT); a.sk_mpad = p.m_pad; a.sk_partial = wsf(ctx, p.off_xtt); }
+        if (fused_sketch) { a.sk_T = wsh(ctx, p.off_TpackT); a.sk_mpad = p.m_pad; a.sk_partial = wsf(ctx, p.off_xtt); a.sk_tokens = p.sketch_tokens; }
         {
             ProfScope ps(ctx, AGZO_PROF_GEMM);
             HIPCHK(launch_gemm_bf16(a, st));
@@ -876,7 +878,7 @@ int agzo_layer_forward_sketch(agzo_ctx* ctx, const agzo_layer* L, const void* W,
         TRY(check_y(ctx, L, Y));
         TRY(check_loss(ctx, L, loss, loss_dev));
     }
-    const Plan p = make_forward_plan(*L, gemm && L->dtype == AGZO_F32 && !Y && loss && loss->kind == AGZO_LOSS_CE, loss && loss->kind == AGZO_LOSS_CE, fused, W, X, Y);
+    const Plan p = make_forward_plan(*L, loss, fused, W, X, Y);
     TRY(reserve(ctx, p.total));
     if (fused) {
         {
@@ -931,7 +933,7 @@ int agzo_perturbed_forward(agzo_ctx* ctx, const agzo_layer* L, const void* W, co
     TRY(check_operands(ctx, L, W, X));
     TRY(check_y(ctx, L, Y));
     TRY(check_loss(ctx, L, loss, loss_dev));
-    const Plan p = make_forward_plan(*L, L->dtype == AGZO_F32 && !Y && loss && loss->kind == AGZO_LOSS_CE, loss && loss->kind == AGZO_LOSS_CE, false, W, X, Y);
+    const Plan p = make_forward_plan(*L, loss, false, W, X, Y);
     TRY(reserve(ctx, p.total));
     float* P = wsf(ctx, p.off_T);
     if (L->dtype != AGZO_BF16) {

@@ -174,9 +174,9 @@ struct GemmBf16Args {
     // in, 1 the one with coef2
     bool ext_ready = false; int ext_side = 0;
     // fused range sketch S = X^T Omega (NULL: none; only where gemm_bf16_fuses_sketch() says so): Omega^T as bf16
-    // planes [3][16][sk_mpad], sk_mpad = gemm_bf16_sketch_mpad(M); sk_partial receives gemm_bf16_sketch_splits(M)
-    // partial sums [split][K][16], one per 128-token tile
-    const bf16_t* sk_T = nullptr; int64_t sk_mpad = 0; float* sk_partial = nullptr;
+    // planes [3][16][sk_mpad], sk_mpad = gemm_bf16_sketch_mpad(M); sk_partial receives gemm_bf16_sketch_splits(M, sk_tokens)
+    // partial sums [split][K][16], one per token tile: sk_tokens, 64 where gemm_bf16_few_tiles() says so and 128 otherwise
+    const bf16_t* sk_T = nullptr; int64_t sk_mpad = 0; float* sk_partial = nullptr; int sk_tokens = 0;
     // gemm_bf16_split_bytes() bytes of device scratch for a stored output whose few tiles share out d_in (NULL: they do not)
     void* split_ws = nullptr;
     // telemetry (NULL: none): four 64-bit device words that workgroup 0 fills with the shader-clock counter and the
@@ -188,14 +188,17 @@ struct GemmBf16Args {
 // mode, no cross-entropy), which is then used for shapes with few 256 x 256 tiles
 int gemm_bf16_num_workgroups(int64_t M, int64_t N, bool small_ok);
 size_t gemm_bf16_ext_bytes(int64_t M, int64_t N, int r);
-size_t gemm_bf16_split_bytes(int64_t M, int64_t N, int64_t K, bool shares);      // (shares: of few tiles, too; else gemm_bf16_few.hip takes them)
+// (over: the output lies in an operand.  Otherwise gemm_bf16_few.hip takes those of few tiles)
+size_t gemm_bf16_split_bytes(int64_t M, int64_t N, int64_t K, bool over);
+// true: a plain or perturbed forward with a stored bf16 output, which does not lie in an operand, runs in 64 x 64 tiles
+bool gemm_bf16_few_tiles(int64_t M, int64_t N, int64_t K, bool large_tiles);
 // true: a squared-error forward of this shape (not in shared-forward mode) runs in the 128 x 128 tiling
 bool gemm_bf16_small_tiles(int64_t M, int64_t N, bool large_tiles);
 // true: a plain forward of this shape (no rank-r term, no shared-forward mode, no cross-entropy) runs in the 128 x 128
 // tiling, whose kernel can emit the range sketch from its LDS-staged X tiles (r <= 16, at most 64 token tiles)
 bool gemm_bf16_fuses_sketch(int64_t M, int64_t N, int r, bool large_tiles);
 inline int64_t gemm_bf16_sketch_mpad(int64_t M) { return (M + 127) / 128 * 128; }
-inline int gemm_bf16_sketch_splits(int64_t M) { return (int)((M + 127) / 128); }
+inline int gemm_bf16_sketch_splits(int64_t M, int tokens) { return (int)((M + tokens - 1) / tokens); }
 hipError_t launch_gemm_bf16(const GemmBf16Args& a, hipStream_t st);
 // whether a perturbed forward multiplies prepared operands (in the shared schedule only the persistent kernel does; the others work from P)
 bool gemm_bf16_reads_ext(const GemmBf16Args& a);

@@ -31,8 +31,10 @@ static bool small_shape(int64_t M, int64_t N) {
 bool gemm_bf16_small_tiles(int64_t M, int64_t N, bool large_tiles) { return !large_tiles && small_shape(M, N); }
 
 bool gemm_bf16_fuses_sketch(int64_t M, int64_t N, int r, bool large_tiles) {
-    return gemm_bf16_small_tiles(M, N, large_tiles) && r <= 16 && gemm_bf16_sketch_splits(M) <= 64;
+    return gemm_bf16_small_tiles(M, N, large_tiles) && r <= 16 && gemm_bf16_sketch_splits(M, BT_SMALL) <= 64;
 }
+
+bool gemm_bf16_few_tiles(int64_t M, int64_t N, int64_t K, bool large_tiles) { return gemm_bf16_small_tiles(M, N, large_tiles) && gemm_bf16_few_shape(M, N, K); }
 
 int gemm_bf16_ce_chunks(int64_t N) { return (int)((N + BT - 1) / BT) * 2; }   // 128-column chunks (2 per tile)
 
@@ -658,7 +660,7 @@ hipError_t choose(const GemmBf16Args& a, Choice& c) {
     p.ce_tl = a.loss.ce_tl;
     p.clk = a.clk;
     p.slots = a.slots;
-    p.sk_T = a.sk_T; p.sk_mpad = a.sk_T ? a.sk_mpad : 0; p.sk_partial = a.sk_T ? a.sk_partial : nullptr;
+    p.sk_T = a.sk_T; p.sk_mpad = a.sk_T ? a.sk_mpad : 0; p.sk_partial = a.sk_T ? a.sk_partial : nullptr; p.sk_tokens = a.sk_tokens;
     const bool small = takes_small(a), persistent = takes_persistent(a);
     p.Xext = nullptr; p.Wext = nullptr; p.Wext2 = nullptr; p.ext_ld = 0;
     c.prep = false;
@@ -689,11 +691,13 @@ hipError_t choose(const GemmBf16Args& a, Choice& c) {
         g.splits = gemm_bf16_mid_splits(p.M, p.N, p.K);
         g.part = static_cast<float*>(a.split_ws);
     }
-    g.sk_T = p.sk_T; g.sk_mpad = p.sk_mpad; g.sk_partial = p.sk_partial;
+    g.sk_T = p.sk_T; g.sk_mpad = p.sk_mpad; g.sk_partial = p.sk_partial; g.sk_tokens = p.sk_tokens;
     c.out = (p.Y && p.loss_kind == AGZO_LOSS_NONE && p.y_dtype == AGZO_BF16) ? 1 : (!p.Y && p.loss_kind == AGZO_LOSS_MSE) ? 0 : -1;
     // one output or one loss and tiles that lie inside the layer: the pipelined kernel
     c.kernel = (c.out >= 0 && gemm_bf16_mid_ok(g, c.out)) ? Kernel::mid : Kernel::small;
-    if (c.kernel == Kernel::mid && c.out == 1 && !g.sk_T && !g.part && gemm_bf16_few_shape(p.M, p.N, p.K)) c.kernel = Kernel::few;
+    if (c.kernel == Kernel::mid && c.out == 1 && !g.part && gemm_bf16_few_shape(p.M, p.N, p.K)) c.kernel = Kernel::few;
+    // (the partial sums were sized for this kernel's token tiles)
+    if (a.sk_T && a.sk_tokens != (c.kernel == Kernel::few ? 64 : BT_SMALL)) return hipErrorInvalidValue;
     return hipSuccess;
 }
 

@@ -56,9 +56,9 @@ struct GemmParams {
     int shared;                 // one pass evaluates f0, f+ and f- (three loss partials per tile)
     // cross-entropy: per (128-column chunk, token) running max and sum of exponentials, and the target's logit
     const int32_t* ce_target; float2* ce_ms; float* ce_tl;
-    // fused range sketch (128 x 128 tiling only; NULL: none): Omega^T planes [3][16][sk_mpad] (sk_mpad a multiple of
-    // 128 that covers every token tile, zero past the last token) and the per-token-tile partial sums [tiles_m][K][16]
-    const bf16_t* sk_T; int64_t sk_mpad; float* sk_partial;
+    // fused range sketch (128 x 128 tiling, or 64 x 64; NULL: none): Omega^T planes [3][16][sk_mpad] (sk_mpad a multiple of
+    // 128 that covers every token tile, zero past the last token) and the partial sums of every sk_tokens tokens, a tile's edge, [tiles_m][K][16]
+    const bf16_t* sk_T; int64_t sk_mpad; float* sk_partial; int sk_tokens;
     // optional telemetry: workgroup 0 leaves {shader clock, constant-rate clock} at entry and at exit
     unsigned long long* clk;
     int slots;                  // workgroups per XCD of the persistent kernel at most (0: one to a compute unit)
@@ -80,11 +80,11 @@ struct GemmItem {
     void* Y; int64_t ldy;                                  // stored bf16 output
     int tiles_m, tiles_n;                                  // (set by the launch)
     // fused range sketch (a launch of one problem; NULL: none): as in GemmParams
-    const bf16_t* sk_T; int64_t sk_mpad; float* sk_partial;
+    const bf16_t* sk_T; int64_t sk_mpad; float* sk_partial; int sk_tokens;
     unsigned long long* clk;
     // out 1 in a launch of one problem: so many shares of the slices, their sums in part (gemm_bf16_split_bytes(); NULL: one share)
     int splits; float* part;
-    int fold, pairs;                                       // (set by the launch: shares summed as gemm_bf16_few.hip does)
+    int pairs;                                             // (set by the launch: shares summed as gemm_bf16_few.hip does)
 };
 int gemm_bf16_mid_splits(int64_t M, int64_t N, int64_t K);
 // out 0: squared error (target_f32: of fp32 targets), 1: stored bf16 output (one problem a launch)

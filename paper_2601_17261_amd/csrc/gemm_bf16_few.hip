@@ -27,7 +27,13 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t few_rsrc(const bf16_t* base, u
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, (int)bytes, 0x00020000);
 }
 
-template <int STAGES>
+// SK: also emits the range sketch of Alg. 1, S = X^T Omega, from the X slices in LDS: the tiles of a token block take the slices in turn, and a
+// wave contracts those of its own that fall to its tile, ahead of the reads of the slice's fragments.  Omega^T of the 64 tokens stays in
+// registers.  Y has the bits of the forward without it.  (128 x 128 tiles that add the same quarters, in four shares or in one, take longer.)  The whole
+// call (Omega, forward, sum of the token tiles), us, 128 x 128 tiles in one share or as many as fill the chip, whose bits are others, in such
+// quarters, and so: 1000 tokens of 256 -> 2048 13.1, 22.8 and 11.6, of 2048 -> 2048 27, 27 and 22.6, 432 of 1024 -> 1024 17.0, 17.8 and 13.2, 8192 of
+// 256 -> 256 29, 40 and 19.4; 385 of 320 -> 2048 11.9, 21.3 and 13.0 is the worst against the first
+template <int STAGES, bool SK>
 __device__ __forceinline__ void few_body(const GemmItem& p) {
     extern __shared__ __align__(16) char smem[];
     typedef __attribute__((address_space(3))) void* lptr_t;
@@ -51,6 +57,47 @@ __device__ __forceinline__ void few_body(const GemmItem& p) {
     const int kbeg = nd_all * wave / WAVES, nd = nd_all * (wave + 1) / WAVES - kbeg;
     const int n = nd + (p.Xext != nullptr && wave == WAVES - 1 ? p.ext_ld / BK : 0);
     char* const ring = smem + wave * STAGES * FSLOT;
+
+    // fragment (plane, 32 tokens): row lc, 8 tokens from 8 lg on; tokens that the tile before this one has covered add nothing
+    bf16x8 omega[SK ? 3 : 1][2];
+    int sk_next = tn + max(0, kbeg - tn + p.tiles_n - 1) / p.tiles_n * p.tiles_n;
+    if constexpr (SK) {
+        const int skip = (int)((int64_t)tm * FT - m0);
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl)
+#pragma unroll
+            for (int tc = 0; tc < 2; ++tc) {
+                const int t = 32 * tc + 8 * lg;
+                const uint4 raw = load16_any(p.sk_T + (int64_t)(pl * 16 + lc) * p.sk_mpad + m0 + t);
+                uint32_t v[4] = {raw.x, raw.y, raw.z, raw.w};
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v[u] &= (t + 2 * u >= skip ? 0xFFFFu : 0u) | (t + 2 * u + 1 >= skip ? 0xFFFF0000u : 0u);
+                omega[pl][tc] = __builtin_bit_cast(bf16x8, make_uint4(v[0], v[1], v[2], v[3]));
+            }
+    }
+    // features 8 c + 2 w + (lc / 8), c = lc mod 8, of the slice at `at`, slice `it` of d_in
+    auto sketch = [&](const char* at, int it) __attribute__((always_inline)) {
+        int row = 8 * lg;
+        asm volatile("" : "+v"(row));               // (addresses made here: kept over the loop they make one slot a wave spill)
+        const int c = lc & 7;
+        const uint32_t sel = (lc >> 3) ? 0x07060302u : 0x05040100u;
+#pragma unroll 1
+        for (int w = 0; w < 4; ++w) {
+            floatx4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int tc = 0; tc < 2; ++tc) {
+                uint32_t v[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = *reinterpret_cast<const uint32_t*>(at + lds_off(32 * tc + row + i, c) + 4 * w);
+                const uint4 b = make_uint4(__builtin_amdgcn_perm(v[1], v[0], sel), __builtin_amdgcn_perm(v[3], v[2], sel),
+                                           __builtin_amdgcn_perm(v[5], v[4], sel), __builtin_amdgcn_perm(v[7], v[6], sel));
+#pragma unroll
+                for (int pl = 0; pl < 3; ++pl) s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(omega[pl][tc], __builtin_bit_cast(bf16x8, b), s, 0, 0, 0);
+            }
+            const int64_t f = (int64_t)it * BK + 8 * c + 2 * w + (lc >> 3);
+            if (f < p.K) *reinterpret_cast<float4*>(p.sk_partial + ((int64_t)tm * p.K + f) * 16 + 4 * lg) = make_float4(s[0], s[1], s[2], s[3]);
+        }
+    };
 
     // direct load t of an operand: LDS rows 8 t + lane / 8 (of W the permuted ones: a lane then holds 16 consecutive outputs), the
     // chunks in the swizzled order, which turns by four between even and odd t
@@ -110,6 +157,8 @@ __device__ __forceinline__ void few_body(const GemmItem& p) {
         else __builtin_amdgcn_s_waitcnt(0x0F70);
         __builtin_amdgcn_sched_barrier(0);
         char* const at = ring + slot * FSLOT;
+        if constexpr (SK)
+            if (kbeg + i == sk_next && i < nd) { sketch(at, sk_next); sk_next += p.tiles_n; }
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
 #pragma unroll
@@ -157,21 +206,21 @@ __device__ __forceinline__ void few_body(const GemmItem& p) {
     if (p.clk && blockIdx.x == 0 && tid == 0) { p.clk[2] = __builtin_readcyclecounter(); p.clk[3] = wall_clock64(); }
 }
 
-template <int STAGES>
+template <int STAGES, bool SK>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(STAGES == 1 ? 2 : 1))) void gemm_bf16_few_kernel(const GemmItem p) {
-    few_body<STAGES>(p);
+    few_body<STAGES, SK>(p);
 }
 
-template <int STAGES>
+template <int STAGES, bool SK>
 static hipError_t launch_few(const GemmItem& g, unsigned tiles, hipStream_t st) {
     constexpr int smem = WAVES * STAGES * FSLOT;
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_bf16_few_kernel<STAGES>), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_bf16_few_kernel<STAGES, SK>), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    hipLaunchKernelGGL((gemm_bf16_few_kernel<STAGES>), dim3(tiles), dim3(64 * WAVES), smem, st, g);
+    hipLaunchKernelGGL((gemm_bf16_few_kernel<STAGES, SK>), dim3(tiles), dim3(64 * WAVES), smem, st, g);
     return hipGetLastError();
 }
 
@@ -186,13 +235,15 @@ bool gemm_bf16_few_shape(int64_t M, int64_t N, int64_t K) {
 }
 
 hipError_t launch_gemm_bf16_few(const GemmItem& a, hipStream_t st) {
-    if (!gemm_bf16_few_shape(a.M, a.N, a.K) || !a.Y || a.sk_T) return hipErrorInvalidValue;
+    if (!gemm_bf16_few_shape(a.M, a.N, a.K) || !a.Y) return hipErrorInvalidValue;
+    if (a.sk_T && (!a.sk_partial || a.sk_tokens != FT || a.sk_mpad < (a.M + FT - 1) / FT * FT || a.Xext)) return hipErrorInvalidValue;
     GemmItem g = a;
     g.tiles_m = (int)((g.M + FT - 1) / FT);
     g.tiles_n = (int)((g.N + FT - 1) / FT);
     const int64_t tiles = (int64_t)g.tiles_m * g.tiles_n;
     // (two slots a wave and one workgroup to a compute unit, or one slot and two)
-    return tiles <= 256 ? launch_few<2>(g, (unsigned)tiles, st) : launch_few<1>(g, (unsigned)tiles, st);
+    if (g.sk_T) return tiles <= 256 ? launch_few<2, true>(g, (unsigned)tiles, st) : launch_few<1, true>(g, (unsigned)tiles, st);
+    return tiles <= 256 ? launch_few<2, false>(g, (unsigned)tiles, st) : launch_few<1, false>(g, (unsigned)tiles, st);
 }
 
 }  // namespace agzo

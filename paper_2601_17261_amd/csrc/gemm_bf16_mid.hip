@@ -86,8 +86,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // this workgroup's slices: all, or a share of the d_in slices (the last share: with the extension behind them)
     const int nd_all = (int)((p.K + BK - 1) / BK);
     const int kbeg = OUT == 2 ? nd_all * share / p.splits : 0, kend = OUT == 2 ? nd_all * (share + 1) / p.splits : nd_all;
-    // (two of gemm_bf16_few.hip's shares in one of this kernel's: each is summed by itself, for the bits of that kernel)
-    const int fold = SK && OUT == 2 && p.fold ? nd_all * (2 * share + 1) / kFewShares - kbeg : -1;
     const bool has_ext = p.Xext != nullptr && kend == nd_all;
     const bf16_t *xb = p.X + m0 * p.ldx + (int64_t)kbeg * BK, *wb_ = p.W + n0 * p.ldw + (int64_t)kbeg * BK;
     const bf16_t *xb2 = has_ext ? p.Xext + m0 * p.ext_ld : xb, *wb2 = has_ext ? p.Wext + n0 * p.ext_ld : wb_;
@@ -257,18 +255,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int I = 0; I < 4; ++I) { read_w(0, 0, I); read_x(0, 0, I); }
     int wcur = 0, xcur = 0, wput = (WS == AHEAD) ? 0 : AHEAD, xput = (XS == AHEAD) ? 0 : AHEAD;    // stages of this slice and of slice kt + AHEAD
-    floatx4 before[SK && OUT == 2 ? 16 : 1];
-    if constexpr (SK && OUT == 2)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) before[q] = floatx4{0.f, 0.f, 0.f, 0.f};
     for (int kt = 0; kt < npipe; ++kt) {
-        if constexpr (SK && OUT == 2)
-            if (kt == fold) {
-                settle();
-#pragma unroll
-                for (int q = 0; q < 16; ++q) { before[q] = acc[q & 3][q >> 2]; acc[q & 3][q >> 2] = floatx4{0.f, 0.f, 0.f, 0.f}; }
-                settle();
-            }
         if (__builtin_expect(kt + AHEAD >= nfull, 0)) select_slice(kt + AHEAD);
         else src_so = (kt + AHEAD) * (BK * 2);
         block(IC<0>{}, wcur, xcur, IC<LATE_W ? 0 : 1>{}, wput);
@@ -286,9 +273,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         xput = (xput == XS - 1) ? 0 : xput + 1;
     }
     settle();
-    if constexpr (SK && OUT == 2)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) acc[q & 3][q >> 2] = before[q] + acc[q & 3][q >> 2];
     __builtin_amdgcn_s_waitcnt(0x0F70);                      // the slices fetched past the end
     const int64_t row_new = (int64_t)tm * MT, col_new = (int64_t)tn * MT;
     if constexpr (OUT == 2) {
@@ -406,12 +390,12 @@ __global__ __launch_bounds__(256) void gemm_bf16_mid_finish_kernel(const GemmIte
 // launch with
 int gemm_bf16_mid_splits(int64_t M, int64_t N, int64_t K) {
     const int64_t tiles = ((M + MT - 1) / MT) * ((N + MT - 1) / MT), slices = K / BK;
-    if (gemm_bf16_few_shape(M, N, K)) return kFewShares;      // (with a fused sketch, or an output over an operand)
+    if (gemm_bf16_few_shape(M, N, K)) return kFewShares;      // (an output over an operand: the bits of gemm_bf16_few.hip)
     if (M < MT || N < MT || tiles > 128) return 1;
     return (int)std::max<int64_t>(1, std::min<int64_t>(256 / tiles, slices / 8));
 }
-size_t gemm_bf16_split_bytes(int64_t M, int64_t N, int64_t K, bool shares) {
-    if (!shares && gemm_bf16_few_shape(M, N, K)) return 0;
+size_t gemm_bf16_split_bytes(int64_t M, int64_t N, int64_t K, bool over) {
+    if (!over && gemm_bf16_few_shape(M, N, K)) return 0;
     const int s = gemm_bf16_mid_splits(M, N, K);
     return s > 1 ? (size_t)s * ((M + MT - 1) / MT) * ((N + MT - 1) / MT) * MT * MT * sizeof(float) : 0;
 }
@@ -460,7 +444,7 @@ hipError_t launch_gemm_bf16_mid(const GemmItem* a, int n, int out, bool target_f
         order[at] = i;
     }
     const bool sk = n > 0 && a[0].sk_T != nullptr;
-    if (sk && (n != 1 || !a[0].sk_partial || a[0].sk_mpad < (a[0].M + MT - 1) / MT * MT)) return hipErrorInvalidValue;
+    if (sk && (n != 1 || !a[0].sk_partial || a[0].sk_tokens != MT || a[0].sk_mpad < (a[0].M + MT - 1) / MT * MT)) return hipErrorInvalidValue;
     if (out == 1 && n == 1 && a[0].part && a[0].splits > 1) {
         KBatch<GemmItem, 1> one{1, {0}, {0}, {a[0]}};
         GemmItem& g = one.a[0];
@@ -468,12 +452,7 @@ hipError_t launch_gemm_bf16_mid(const GemmItem* a, int n, int out, bool target_f
         g.tiles_n = (int)((g.N + MT - 1) / MT);
         if (g.splits > g.K / BK) return hipErrorInvalidValue;
         const unsigned tiles = (unsigned)(g.tiles_m * g.tiles_n);
-        // the bits of gemm_bf16_few.hip: its shares are added in pairs, here or, where they are more than fill the chip and are sketched as well, two
-        // to a workgroup
-        const bool few = gemm_bf16_few_shape(g.M, g.N, g.K);
-        g.fold = few && sk && tiles > 64;
-        g.pairs = few && !g.fold;
-        if (g.fold) g.splits = kFewShares / 2;
+        g.pairs = gemm_bf16_few_shape(g.M, g.N, g.K);
         one.gx[0] = tiles * (unsigned)g.splits;
         hipError_t e = sk ? launch_mid_ring<2, false, true, true>(one, one.gx[0], st) : launch_mid_ring<2, false, false, true>(one, one.gx[0], st);
         if (e != hipSuccess) return e;

@@ -64,3 +64,31 @@ def test_beyond_the_line(n, d_out, d_in):
     ctx.check()
     names, _ = kernels(stream, call)
     assert any("gemm_bf16_mid_kernel" in s for s in names) and not any("gemm_bf16_few" in s for s in names), names
+
+
+# one slice a wave and two tiles that share them out; shifted tiles, one and two workgroups to a compute unit; more tiles than slices, which then sketch
+# nothing; partial sums of 128 token tiles; more slices than tiles and a last one that d_in does not fill
+@pytest.mark.parametrize("n,d_out,d_in,r", [(128, 128, 256, 16), (191, 200, 328, 7), (1025, 1030, 712, 16), (130, 2000, 2048, 1), (8192, 256, 264, 3), (300, 130, 2040, 13)])
+def test_sketched(n, d_out, d_in, r):
+    """the output's bits with and without the sketch, and the sketch against fp64: sums of 64 products and of their roundings, as in
+    test_gpu_sketch_rings.py, whose sums are longer"""
+    W, X, _ = synth.single_layer_problem(5, n, d_in, d_out, kind="rmsnorm", storage="bf16")
+    Xd = torch.full((n, d_in + 8), float("nan"), device="cuda", dtype=torch.bfloat16)[:, :d_in].copy_(torch.from_numpy(X))
+    Wd = torch.from_numpy(W).cuda().to(torch.bfloat16)
+    stream = torch.cuda.Stream()
+    ctx, got = binding.Context(stream), []
+    for mode in (binding.SKETCH_NONE, binding.SKETCH_RANGE_FUSED):
+        Y, S = torch.full((n, d_out), 7.0, device="cuda", dtype=torch.bfloat16), torch.full((d_in, r), 9.0, device="cuda")
+        L = binding.make_layer(Wd, Xd, r, Y=Y)
+
+        def call():
+            ctx.layer_forward_sketch(L, Wd, Xd, Y, mode, None, 91, S, None, None)
+        torch.cuda.synchronize()
+        call()
+        ctx.check()
+        names, _ = kernels(stream, call)
+        assert sum("gemm_bf16_few_kernel" in s for s in names) == 1 and not any("gemm_bf16_mid" in s for s in names), names
+        got.append(Y)
+    assert torch.equal(got[0], got[1])
+    want = oagzo.range_sketch(X.astype(np.float64), r, 91)
+    assert np.linalg.norm(S.double().cpu().numpy() - want) < 4e-6 * np.linalg.norm(want)

@@ -52,6 +52,27 @@ def test_output_over_an_operand(n, d, r, over):
         assert sum("gemm_bf16_few_kernel" in s for s in names) == 1, names
 
 
+@pytest.mark.parametrize("n,d,r", [(300, 1032, 16), (1100, 1160, 3)])
+def test_sketched_output_over_its_input(n, d, r):
+    """shares of the 128 x 128 kernel, which also sketches them: the output's bits, and the sketch that the 64 x 64 tiles make up to fp32 sums"""
+    g, stream = _gen(n), torch.cuda.Stream()
+    ctx = binding.Context(stream)
+    x, w = (torch.randn(t, d, device="cuda", generator=g).bfloat16() for t in (n, d))
+    apart, over = torch.empty_like(x), x.clone()
+    s = [torch.empty(d, r, device="cuda") for _ in range(2)]
+
+    def call(X, Y, S):
+        ctx.layer_forward_sketch(binding.make_layer(w, X, r, Y=Y), w, X, Y, binding.SKETCH_RANGE_FUSED, None, 91, S, None, None)
+    torch.cuda.synchronize()
+    call(x, apart, s[0])
+    call(over, over, s[1])
+    ctx.check()
+    assert torch.equal(over, apart)
+    assert (s[0].double() - s[1].double()).norm() < 4e-6 * s[0].double().norm()
+    names, _ = kernels(stream, lambda: call(over, over, s[1]))
+    assert sum("gemm_bf16_mid_finish" in k for k in names) == 1 and not any("gemm_bf16_few" in k for k in names), names
+
+
 def test_output_beside_its_input_is_apart():
     """columns of one buffer that X does not have: no shares"""
     buf, w, stream = torch.randn(300, 1024, device="cuda", generator=_gen(1)).bfloat16(), torch.randn(400, 512, device="cuda", generator=_gen(2)).bfloat16(), torch.cuda.Stream()

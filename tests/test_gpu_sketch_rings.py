@@ -10,8 +10,10 @@ from paper_2601_17261_amd import binding, synth
 pytestmark = pytest.mark.gpu
 
 # tokens, d_in, d_out, r: 21 x 16 tiles, 2 x 129 (129 workgroups of two tokens' tiles); shares of 8 slices and a last one that d_in
-# does not fill, with more and with fewer output tiles than slices in a share; two slices
-SHAPES = [(2600, 200, 2000, 5), (129, 136, 16500, 16), (300, 1100 - 4, 300, 16), (3001, 2056, 264, 13), (140, 1032, 1300, 1), (256, 128, 256, 7)]
+# does not fill, with more and with fewer output tiles than slices in a share; two slices.  (Stored, the former run in 64 x 64 tiles whose waves share
+# d_in; past their line:) shares of eight and nine slices, of thirteen and fourteen, of eight and nine for more output tiles than that
+SHAPES = [(2600, 200, 2000, 5), (129, 136, 16500, 16), (300, 1100 - 4, 300, 16), (3001, 2056, 264, 13), (140, 1032, 1300, 1), (256, 128, 256, 7),
+          (300, 4168, 300, 16), (3001, 2632, 264, 13), (140, 2664, 1300, 1)]
 
 
 @pytest.mark.parametrize("out", ["y", "mse_bf16", "mse_f32"])
