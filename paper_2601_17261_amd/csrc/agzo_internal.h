@@ -290,7 +290,8 @@ hipError_t launch_pack_planes(const float* Q, int64_t d, int r, int rp, bf16_t* 
 
 // qr.hip : CholeskyQR2
 size_t qr_workspace_bytes(int64_t d, int r);
-// S explicit, or splits [nsplit][d][rp] ([nsplit][d] for r = 1; then their fp32 sum is also stored to S_out); Q fp32 out;
+// S explicit, or splits [nsplit][d][rp] ([nsplit][d] for r = 1), whose fp32 sum goes to S_out: scratch of the factorisation, which it may
+// leave unwritten, but for a deferred column (below), whose place it is.  Q fp32 out;
 // planes (nullable) bf16 [3][rp][d]; refine = false: single Cholesky pass (for iterates that are sketched again)
 hipError_t launch_qr(const float* S, const float* splits, int nsplit, int rp, float* S_out, int64_t d, int r, float* Q,
                      bf16_t* planes, void* workspace, int* numeric_flag, bool refine, hipStream_t st);

@@ -334,7 +334,8 @@ __device__ __forceinline__ doublex4 apply_rinv(const Tin (&y)[RP / 4], const dou
 }
 
 // per problem, what the launches of one factorisation need.  Input: S fp32 [d][r], or (splits != nullptr) partial sketches
-// [nsplit][d][rp] ([nsplit][d] for r = 1) whose sum is stored to S_out as fp32 and used (in its rounded form) for the factorisation
+// [nsplit][d][rp] ([nsplit][d] for r = 1) whose sum, rounded to fp32, is used for the factorisation and stored to S_out (not by qr1_small_kernel,
+// behind which no launch reads it)
 struct QrDev {
     const float* S; const float* splits; int nsplit; float* S_out; const float* Sin;
     int64_t d; int r; int nblk;
