@@ -22,7 +22,7 @@ def test_stored_output(n, d_out, d_in, r):
         t = torch.full((a.shape[0], a.shape[1] + pad), float("nan"), device="cuda", dtype=torch.bfloat16)[:, :a.shape[1]]
         return t.copy_(torch.from_numpy(a))
     Wd, Xd = strided(W, 16), strided(X, 8)
-    B = torch.linalg.qr(torch.randn(d_in, r, device="cuda"))[0].contiguous()
+    B = torch.linalg.qr(torch.randn(d_in, r, device="cuda", generator=torch.Generator(device="cuda").manual_seed(r)))[0].contiguous()
     stream = torch.cuda.Stream()
     ctx = binding.Context(stream)
     torch.cuda.synchronize()
@@ -52,7 +52,8 @@ def test_stored_output(n, d_out, d_in, r):
 @pytest.mark.parametrize("n,d_out,d_in", [(128, 128, 248), (1088, 1984, 512), (300, 300, 2056), (512, 512, 2568)])
 def test_beyond_the_line(n, d_out, d_in):
     """d_in of fewer than four slices, 527 tiles, 25 tiles of more than 32 slices, 64 of more than 40: 128 x 128 tiles"""
-    x, w = torch.randn(n, d_in, device="cuda").bfloat16(), torch.randn(d_out, d_in, device="cuda").bfloat16()
+    g = torch.Generator(device="cuda").manual_seed(d_in)
+    x, w = torch.randn(n, d_in, device="cuda", generator=g).bfloat16(), torch.randn(d_out, d_in, device="cuda", generator=g).bfloat16()
     stream = torch.cuda.Stream()
     ctx, y = binding.Context(stream), torch.empty(n, d_out, device="cuda", dtype=torch.bfloat16)
     L = binding.make_layer(w, x, 1, Y=y)
@@ -62,6 +63,8 @@ def test_beyond_the_line(n, d_out, d_in):
     torch.cuda.synchronize()
     call()
     ctx.check()
+    want = x.double() @ w.double().T
+    assert ((y.double() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5 * want.square().mean().sqrt()).all()
     names, _ = kernels(stream, call)
     assert any("gemm_bf16_mid_kernel" in s for s in names) and not any("gemm_bf16_few" in s for s in names), names
 
