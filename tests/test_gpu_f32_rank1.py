@@ -10,6 +10,11 @@ pytestmark = pytest.mark.gpu
 SHAPES = [(1, 1), (5, 3), (17, 16), (40, 63), (300, 250), (33, 257), (100, 1000), (61, 1020), (300, 1023), (300, 1024), (7, 1027), (130, 2052), (600, 4100)]
 
 
+def _randn(seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    return lambda *shape: torch.randn(*shape, device="cuda", generator=g)
+
+
 def _want(X, q, K):
     q = q.double() / q.double().norm()
     for _ in range(K):
@@ -23,7 +28,8 @@ def _want(X, q, K):
 def test_from_a_given_sketch(n, d, of_s0):
     """against fp64: a power step rounds T and the sketch to fp32 once each, 2^-24 of a vector's norm; two steps and the last rounding"""
     ctx = binding.Context()
-    X, S0 = torch.randn(n, d, device="cuda"), of_s0 * torch.randn(d, 1, device="cuda")
+    randn = _randn(1000 * n + d)
+    X, S0 = randn(n, d), of_s0 * randn(d, 1)
     L = binding.make_layer(torch.empty(16, d, device="cuda"), X, 1)
     B, many, other = torch.full((d, 1), 9.0, device="cuda"), torch.full((d, 1), 9.0, device="cuda"), torch.empty(72, 1, device="cuda")
     ctx.basis(L, X, 2, 3, S0, 0, B)
@@ -32,8 +38,8 @@ def test_from_a_given_sketch(n, d, of_s0):
     first = (X.double() @ (S0.double() / S0.double().norm())).norm() * torch.linalg.matrix_norm(X.double(), 2) / (X.double().T @ (X.double() @ (S0.double() / S0.double().norm()))).norm()
     second = torch.linalg.matrix_norm(X.double(), 2) ** 2 / (X.double().T @ (X.double() @ _want(X, S0, 1))).norm()
     assert (B.double() - want).norm() <= 2.0 ** -23 * (1 + 2 * second * (1 + first))
-    Xo = torch.randn(50, 72, device="cuda")
-    ctx.basis_many([(L, X, 3, S0, many), (binding.make_layer(torch.empty(16, 72, device="cuda"), Xo, 1), Xo, 4, torch.randn(72, 1, device="cuda"), other)], 2, 0)
+    Xo = randn(50, 72)
+    ctx.basis_many([(L, X, 3, S0, many), (binding.make_layer(torch.empty(16, 72, device="cuda"), Xo, 1), Xo, 4, randn(72, 1), other)], 2, 0)
     ctx.check()
     assert torch.equal(B, many)
 
@@ -41,7 +47,7 @@ def test_from_a_given_sketch(n, d, of_s0):
 @pytest.mark.parametrize("d", [64, 1024])
 def test_no_column_is_reported(d):
     ctx = binding.Context()
-    X, B = torch.randn(100, d, device="cuda"), torch.empty(d, 1, device="cuda")
+    X, B = _randn(d)(100, d), torch.empty(d, 1, device="cuda")
     L = binding.make_layer(torch.empty(16, d, device="cuda"), X, 1)
     ctx.basis(L, X, 1, 3, torch.zeros(d, 1, device="cuda"), 0, B)
     with pytest.raises(binding.AgzoError):

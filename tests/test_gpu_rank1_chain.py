@@ -16,7 +16,8 @@ SHAPES = [(1, 8), (40, 248), (300, 256), (300, 264), (2049, 504), (2048, 512), (
 @pytest.mark.parametrize("n,d", SHAPES)
 def test_alone_and_in_company(n, d, K):
     ctx = binding.Context()
-    X, other = (torch.randn(t, w, device="cuda").bfloat16() for t, w in ((n, d), (500, 2048)))
+    g = torch.Generator(device="cuda").manual_seed(10 * n + d)
+    X, other = (torch.randn(t, w, device="cuda", generator=g).bfloat16() for t, w in ((n, d), (500, 2048)))
     lay = [binding.make_layer(torch.empty(16, x.shape[1], device="cuda", dtype=torch.bfloat16), x, 1) for x in (X, other)]
     alone, many, beside = torch.full((d, 1), 9.0, device="cuda"), torch.full((d, 1), 9.0, device="cuda"), torch.empty(2048, 1, device="cuda")
     ctx.basis(lay[0], X, K, 5, None, 0, alone)
@@ -46,7 +47,7 @@ def test_no_activations_are_reported(n, d):
 def test_one_column(d):
     """against fp64: the column is rounded once"""
     ctx = binding.Context()
-    Y, Q = torch.randn(d, 1, device="cuda"), torch.full((d, 1), 9.0, device="cuda")
+    Y, Q = torch.randn(d, 1, device="cuda", generator=torch.Generator(device="cuda").manual_seed(d)), torch.full((d, 1), 9.0, device="cuda")
     ctx.qr(Y, Q)
     ctx.check()
     want = Y.double() / Y.double().norm()
