@@ -84,7 +84,6 @@ struct GemmItem {
     unsigned long long* clk;
     // out 1 in a launch of one problem: so many shares of the slices, their sums in part (gemm_bf16_split_bytes(); NULL: one share)
     int splits; float* part;
-    int pairs;                                             // (set by the launch: shares summed as gemm_bf16_few.hip does)
 };
 int gemm_bf16_mid_splits(int64_t M, int64_t N, int64_t K);
 // out 0: squared error (target_f32: of fp32 targets), 1: stored bf16 output (one problem a launch)

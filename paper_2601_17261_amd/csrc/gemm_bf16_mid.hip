@@ -349,28 +349,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 }
 
 // Y from the shares' sums: one workgroup per tile and token block of every wave, four shares' loads of a thread in flight (a
-// workgroup per tile took 7 us for 64 tiles of four shares: latency)
+// workgroup per tile took 7 us for 64 tiles of four shares: latency).  PAIRS: four shares, added as gemm_bf16_few.hip does (a launch that asks which
+// of the two takes up to 1 us longer: 1009 tokens of 7568 -> 377 5.3 and 6.3 us)
+template <bool PAIRS>
 __global__ __launch_bounds__(256) void gemm_bf16_mid_finish_kernel(const GemmItem p) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wa = wave >> 1, wb = wave & 1, lc = lane & 15, lg = lane >> 4;
     const int tiles = p.tiles_m * p.tiles_n, tm = blockIdx.x / p.tiles_n, tn = blockIdx.x % p.tiles_n, J = blockIdx.y;
     const int64_t m0 = min((int64_t)tm * MT, p.M - MT), n0 = min((int64_t)tn * MT, p.N - MT);
     const floatx4* src = reinterpret_cast<const floatx4*>(p.part) + (((int64_t)blockIdx.x * 4 + wave) * 16 + J * 4) * 64 + lane;
     floatx4 sum[4] = {};
-    for (int s0 = 0; s0 < p.splits; s0 += 4) {
+    if constexpr (PAIRS) {
+        static_assert(kFewShares == 4, "two pairs");
         floatx4 v[4][4];
 #pragma unroll
         for (int s = 0; s < 4; ++s)
 #pragma unroll
-            for (int I = 0; I < 4; ++I) v[s][I] = s0 + s < p.splits ? src[(int64_t)(s0 + s) * tiles * 4096 + I * 64] : floatx4{0.f, 0.f, 0.f, 0.f};
-        if (p.pairs) {
+            for (int I = 0; I < 4; ++I) v[s][I] = src[(int64_t)s * tiles * 4096 + I * 64];
 #pragma unroll
-            for (int I = 0; I < 4; ++I) sum[I] = (v[0][I] + v[1][I]) + (v[2][I] + v[3][I]);
-            break;
+        for (int I = 0; I < 4; ++I) sum[I] = (v[0][I] + v[1][I]) + (v[2][I] + v[3][I]);
+    } else {
+        for (int s0 = 0; s0 < p.splits; s0 += 4) {
+            floatx4 v[4][4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int I = 0; I < 4; ++I) v[s][I] = s0 + s < p.splits ? src[(int64_t)(s0 + s) * tiles * 4096 + I * 64] : floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int I = 0; I < 4; ++I) sum[I] += v[s][I];
         }
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int I = 0; I < 4; ++I) sum[I] += v[s][I];
     }
     uint32_t w[8];
 #pragma unroll
@@ -452,11 +460,13 @@ hipError_t launch_gemm_bf16_mid(const GemmItem* a, int n, int out, bool target_f
         g.tiles_n = (int)((g.N + MT - 1) / MT);
         if (g.splits > g.K / BK) return hipErrorInvalidValue;
         const unsigned tiles = (unsigned)(g.tiles_m * g.tiles_n);
-        g.pairs = gemm_bf16_few_shape(g.M, g.N, g.K);
+        const bool pairs = gemm_bf16_few_shape(g.M, g.N, g.K);
+        if (pairs && g.splits != kFewShares) return hipErrorInvalidValue;
         one.gx[0] = tiles * (unsigned)g.splits;
         hipError_t e = sk ? launch_mid_ring<2, false, true, true>(one, one.gx[0], st) : launch_mid_ring<2, false, false, true>(one, one.gx[0], st);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(gemm_bf16_mid_finish_kernel, dim3(tiles, 4), dim3(256), 0, st, g);
+        if (pairs) hipLaunchKernelGGL(gemm_bf16_mid_finish_kernel<true>, dim3(tiles, 4), dim3(256), 0, st, g);
+        else hipLaunchKernelGGL(gemm_bf16_mid_finish_kernel<false>, dim3(tiles, 4), dim3(256), 0, st, g);
         return hipGetLastError();
     }
     for (int i = 0; i < n; ++i) {
