@@ -616,8 +616,9 @@ static_assert(sizeof(KBatch<XqGroupDev>) <= 4096, "kernel arguments");
 // sums the d_in splits of xq in fixed order and writes what the unsplit kernel's epilogue writes.  For the planes a workgroup takes
 // 64 tokens of 16 columns and a thread four tokens of a column, so that the stores of a wave are whole rows (with a thread per value,
 // columns side by side, every plane was written in 2-byte pieces: 28 us for 4096 tokens of seven layers at r = 64, 9 so).  T and the
-// extension operands are token by token, as their partial sums are: a thread eight columns of a token
-constexpr int XQF_TOK = 64;
+// extension operands are token by token, as their partial sums are: 16 tokens of 16 columns, a thread a value, the operands then from LDS
+// in 16-byte pieces.  (A thread for eight columns, 1009 tokens of a 7568-wide layer, r = 8: 4.4 us in eight workgroups and 3.1 so)
+constexpr int XQF_TOK = 64, XQF_TOK_ROWS = 16;
 __device__ __forceinline__ void xq_finish_body(const XqDev& a, int rp, uint32_t bx, uint32_t by) {
     const int tid = threadIdx.x, nsplit = a.ns, r = a.r;
     const int64_t m_pad = a.m_pad, M = a.M;
@@ -639,35 +640,32 @@ __device__ __forceinline__ void xq_finish_body(const XqDev& a, int rp, uint32_t 
         xq_emit(v, M, r, rp, a.T, a.TpackT, m_pad, a.Xext, t, k);
         return;
     }
-    const int groups = rp / 8, e = (int)bx * 256 + tid;
-    const int64_t t = e / groups;
-    const int k0 = (e % groups) * 8;
-    float v[8] = {};
-    const float* src = a.part + min(t, m_pad - 1) * rp + k0;
-    for (int s0 = 0; s0 < nsplit; s0 += 4) {
-        floatx4 x[4][2];
+    __shared__ float block[XQF_TOK_ROWS][20];
+    const int64_t t = (int64_t)bx * XQF_TOK_ROWS + (tid >> 4);
+    const int k = (int)by * 16 + (tid & 15);
+    float v = 0.f;
+    const float* src = a.part + min(t, m_pad - 1) * rp + k;
+    for (int s0 = 0; s0 < nsplit; s0 += 8) {
+        float x[8];
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
+        for (int s = 0; s < 8; ++s) x[s] = s0 + s < nsplit ? src[(int64_t)(s0 + s) * m_pad * rp] : 0.f;
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
-                x[s][h] = s0 + s < nsplit ? *reinterpret_cast<const floatx4*>(src + (int64_t)(s0 + s) * m_pad * rp + 4 * h) : floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] += x[s][i >> 2][i & 3];
+        for (int s = 0; s < 8; ++s) v += x[s];
     }
-    if (t >= M) return;
+    if (k >= r) v = 0.f;
+    if (t < M && k < r && a.T != nullptr) a.T[t * r + k] = v;
+    if (a.Xext == nullptr) return;
+    block[tid >> 4][tid & 15] = v;
+    __syncthreads();
+    const int64_t te = (int64_t)bx * XQF_TOK_ROWS + (tid >> 1);
+    if (tid >= 2 * XQF_TOK_ROWS || te >= M) return;
+    float c[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        if (k0 + i >= r) v[i] = 0.f;
-        else if (a.T != nullptr) a.T[t * r + k0 + i] = v[i];
-    }
-    if (a.Xext != nullptr) {
-        uint4 hi, lo;
-        ext_split(v, hi, lo);
-        const int ext_ld = (3 * rp + 63) / 64 * 64;
-        ext_store(a.Xext + t * ext_ld, ext_ld, rp, k0, hi, hi, lo);
-    }
+    for (int i = 0; i < 8; ++i) c[i] = block[tid >> 1][8 * (tid & 1) + i];
+    uint4 hi, lo;
+    ext_split(c, hi, lo);
+    const int ext_ld = (3 * rp + 63) / 64 * 64;
+    ext_store(a.Xext + te * ext_ld, ext_ld, rp, (int)by * 16 + 8 * (tid & 1), hi, hi, lo);
 }
 template <int CAP>
 __global__ __launch_bounds__(256) void xq_finish_many_kernel(const KBatch<XqDev, CAP> tb, int rp) {
@@ -1203,8 +1201,8 @@ hipError_t launch_xq_bf16_many(const XqArgs* a, int n, bool half_cu, hipStream_t
         const uint32_t gx = (uint32_t)((rows + mb * XQ_TOK - 1) / (mb * XQ_TOK));
         tb.first[tb.n] = (uint32_t)blocks; tb.gx[tb.n] = gx; tb.a[tb.n++] = d;
         blocks += (uint64_t)gx * (uint32_t)d.ns;
-        // (planes: blocks of 64 tokens by 16 columns, fx of them along the tokens; otherwise 256 times eight columns a workgroup)
-        const uint32_t fx = (uint32_t)(d.TpackT ? (rows + XQF_TOK - 1) / XQF_TOK : (rows * (rp / 8) + 255) / 256), fwgs = d.TpackT ? fx * (uint32_t)(rp / 16) : fx;
+        const int ftok = d.TpackT ? XQF_TOK : XQF_TOK_ROWS;
+        const uint32_t fx = (uint32_t)((rows + ftok - 1) / ftok), fwgs = fx * (uint32_t)(rp / 16);
         if (a[m].ext) {
             uint64_t wgs;
             XqFinishExtDev& x = fext.a[fext.n];
