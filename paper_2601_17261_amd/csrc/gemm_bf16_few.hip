@@ -227,10 +227,17 @@ static hipError_t launch_few(const GemmItem& g, unsigned tiles, hipStream_t st) 
 // Up to two workgroups a compute unit, and a d_in that 128 x 128 tiles in shares do not walk as fast, for they take in half the bytes an output.  us,
 // those and this kernel: 2048 -> 1024 outputs 23.5 and 19.5 at d_in = 2560, 28.6 and 26.2 at 4096, 385 -> 2048 18.7 and 12.5, 19.6 and 17.1, but 128 ->
 // 4096 18.8 and 21.1 at 3064, 256 -> 2048 20.0 and 26.8 at 6144; of fewer than 64 tiles, which the shares spread over more compute units, 200 -> 256
-// 11.0 and 11.7 at 2560, 9.6 and 6.7 at 1024.  Rows of X and W that do not start on 128 bytes cost this kernel more (700 -> 2048, 2056:
-// 20.4 and 20.6).  More tiles: 1500 -> 2048, 768 of them, 16.4 and 23.2
+// 11.0 and 11.7 at 2560, 9.6 and 6.7 at 1024.  More tiles: 1500 -> 2048, 768 of them, 16.4 and 23.2.
+// Rows of X and W that do not start on 128 bytes cost two workgroups of one slot more: there 128 x 128 tiles are left what they walk in one share of 13 to 20
+// slices (598 -> 3238, 1272: 12.9 and 15.5; 553 -> 3556, 952: 10.4 and 13.2; but 431 -> 3028, 824 8.9 and 9.3, 146 -> 10013, 1424 17.7 and 16.1) and, in two
+// or three, of more than 32 (695 -> 1857, 2520: 22.8 and 27.2; 725 -> 2365, 2104 22.3 and 23.9; but 577 -> 2416, 1976 20.2 and 20.9, 603 -> 3178, 1032 20.5
+// and 12.6)
 bool gemm_bf16_few_shape(int64_t M, int64_t N, int64_t K) {
     const int64_t tiles = ((M + FT - 1) / FT) * ((N + FT - 1) / FT);
+    if (tiles > 256 && K % BK != 0 && K >= 13 * BK) {
+        const bool one_share = ((M + BT_SMALL - 1) / BT_SMALL) * ((N + BT_SMALL - 1) / BT_SMALL) > 128 || K < 16 * BK;
+        if (one_share ? K < 21 * BK : K > 32 * BK) return false;
+    }
     return M >= BT_SMALL && N >= BT_SMALL && tiles <= 512 && K >= WAVES * BK && K <= (tiles >= 64 ? 40 : 32) * BK;
 }
 

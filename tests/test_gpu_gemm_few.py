@@ -14,7 +14,8 @@ EPS = float(np.float32(1e-2))
 
 
 @pytest.mark.parametrize("n,d_out,d_in,r", [(128, 128, 256, 1), (129, 131, 264, 16), (191, 200, 328, 17), (1024, 1024, 320, 4), (1025, 1030, 712, 64),
-                                            (130, 2000, 2048, 33), (260, 1100, 2552, 8)])
+                                            (130, 2000, 2048, 33), (260, 1100, 2552, 8), (1025, 1030, 824, 4), (1025, 1030, 1032, 1), (1025, 1030, 2040, 16),
+                                            (598, 3238, 1352, 2)])
 def test_stored_output(n, d_out, d_in, r):
     W, X, _ = synth.single_layer_problem(5, n, d_in, d_out, kind="rmsnorm", storage="bf16")
 
@@ -49,9 +50,11 @@ def test_stored_output(n, d_out, d_in, r):
         assert sum("gemm_bf16_few_kernel" in s for s in names) == 1 and not any("gemm_bf16_mid" in s for s in names), names
 
 
-@pytest.mark.parametrize("n,d_out,d_in", [(128, 128, 248), (1088, 1984, 512), (300, 300, 2056), (512, 512, 2568)])
+@pytest.mark.parametrize("n,d_out,d_in", [(128, 128, 248), (1088, 1984, 512), (300, 300, 2056), (512, 512, 2568), (1025, 1030, 840), (1025, 1030, 1016),
+                                          (1025, 1030, 2056), (598, 3238, 1336)])
 def test_beyond_the_line(n, d_out, d_in):
-    """d_in of fewer than four slices, 527 tiles, 25 tiles of more than 32 slices, 64 of more than 40: 128 x 128 tiles"""
+    """d_in of fewer than four slices, 527 tiles, 25 tiles of more than 32 slices, 64 of more than 40, and, of rows that do not start on 128 bytes, more than
+    256 tiles of 13 to 15 slices, of more than 32, and of up to 20 where there are more than 128 tiles of 128 x 128: these"""
     g = torch.Generator(device="cuda").manual_seed(d_in)
     x, w = torch.randn(n, d_in, device="cuda", generator=g).bfloat16(), torch.randn(d_out, d_in, device="cuda", generator=g).bfloat16()
     stream = torch.cuda.Stream()
